@@ -136,18 +136,17 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
                            out_merged ? (size_t)F * K : 0, ss ? nullptr : row_offsets, adapter_ids, R, m->n_adapters, w.meta, w.frame_of_row,
                            w.adapter_of_row, dev_status, st));
     // The lagged loop: after the shared layers the base head scores the frames, Alg. 2 turns the scores of frame t - 1 into
-    // the adapter set of frame t, and the CSR check builds the row maps -- all on this stream, no host in between.
+    // the adapter set of frame t with its row maps -- all on this stream, no host in between.
     bool selected = ss == nullptr;
     auto select_now = [&]() -> int {
         selected = true;
         const poly_stream *s = ss->s;
         POLY_TRY(launch_base_head(w.xa, T, D, base->lnf_g, base->lnf_b, m->ln_eps, s->base_w, s->base_b, s->K, F, ss->lag,
                                   ss->out_base_scores, s->carry, dt, st));
-        POLY_TRY(poly_select(ss->lag, F, s->K, s->group_membership, s->M, &s->opts, s->state, ss->row_offsets, ss->adapter_ids, R,
-                             ss->counters, stream));
-        if (hipMemcpyAsync(s->carry, ss->lag + (size_t)F * s->K, sizeof(float) * (size_t)s->K, hipMemcpyDeviceToDevice, st) != hipSuccess)
-            return POLY_EHIP;
-        return launch_prep(ss->row_offsets, ss->adapter_ids, F, R, m->n_adapters, w.meta, w.frame_of_row, w.adapter_of_row, dev_status, st);
+        // the selection also writes the row maps and carries the last frame's scores to the next call: two launches less
+        const SelectFollow fo = {w.meta, w.frame_of_row, w.adapter_of_row, dev_status, s->carry, ss->lag + (size_t)F * s->K};
+        return launch_select(ss->lag, F, s->K, s->group_membership, s->M, &s->opts, s->state, ss->row_offsets, ss->adapter_ids, R, ss->counters,
+                             fo, st);
     };
     {
         GemmArgs g = {};

@@ -261,6 +261,17 @@ int launch_shrink(const void *X, int T, int K, const void *At, int r, int RP, fl
 int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev,
                      int dtype, hipStream_t st);
 
+// poly_select with what the lagged loop needs right behind it done in the same launch (select.hip): meta != null: the row maps and
+// the bookkeeping words of the CSR arrays just written; carry != null: K floats carry_src -> carry
+struct SelectFollow {
+    PolyMeta *meta;
+    int32_t *frame_of_row, *adapter_of_row, *dev_status;
+    float *carry;
+    const float *carry_src;
+};
+int launch_select(const float *label_scores, int F, int K, const uint8_t *group_membership, int M, const poly_select_opts *opts, void *state,
+                  int32_t *row_offsets, int32_t *adapter_ids, int cap, int32_t *counters, const SelectFollow &fo, hipStream_t st);
+
 // ---- bookkeeping and row-wise stages (rowops.hip) ----
 int launch_prep(const int32_t *row_offsets, const int32_t *adapter_ids, int F, int R_cap, int n_adapters, PolyMeta *meta,
                 int32_t *frame_of_row, int32_t *adapter_of_row, int32_t *dev_status, hipStream_t st);

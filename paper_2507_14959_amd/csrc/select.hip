@@ -1,21 +1,31 @@
 // Context detection (Alg. 2, Sec. 3.5): label threshold -> greedy cover by contexts in (size, id)
 // order -> CSR adapter sets.  Integer work on 64-bit sets, one workgroup per call: a batch is
-// F x K = 64 x 80 scores, so latency, not throughput, is what matters.
+// F x K = 64 x 80 scores, so the length of the chain of dependent steps, not throughput, is what matters.
 //
 // Label sets are bitsets built with wave ballots (one 64-label word per ballot, coalesced score
 // reads).  Contexts are renumbered by scan position, so a context set is a 64-bit mask whose
-// ascending bit order IS the selection order.  Frames are covered in parallel (one thread each);
-// the reuse branches of Alg. 2 need the previous frame's result and are resolved by a short
-// sequential pass that only runs when a state is carried or context_copy is set.
+// ascending bit order IS the selection order.  One thread per frame, up to 1024 frames per pass:
+//
+//  - Greedy cover.  A context is taken iff it provides a label that is still uncovered, so the next context taken is the
+//    lowest first[l] over the uncovered labels l (first[l] = lowest scan position that provides l): whatever precedes it
+//    provides none of them.  The candidates are therefore the first[] of the frame's few labels, not all M positions.
+//  - Reuse branches.  S_t = S_{t-1} where the labels repeat or (context copy) where S_{t-1} provides them all, so every S_t is
+//    the greedy set of the last frame that was NOT reused.  If frame t took its own set, the next frame to do so is
+//    next[t] = the first t' > t whose labels are new and not all provided by the greedy set of t -- a function of t alone, found
+//    for all t side by side.  The frames that really took their own set are the ones on the chain that starts at the first
+//    frame of the pass that the carried set does not serve; they are marked by pointer doubling (log2 n rounds), and a scan
+//    gives every frame the last marked one before it.
+//
+// 1024 frames x 80 labels, 45 overlapping contexts with an accuracy table and context copy: 1665 us per call with M tests per frame
+// and a sequential pass over the frames, 18.9 us this way (20 k cycles of it kernel phases: scores 5, links 1, chain 3.5, the rest
+// memory round trips of the set-up).  64 frames, 16 contexts: 17.9 -> 8.9 us, the rate at which the host can launch.
 #include "poly_dev.h"
-
-#include <type_traits>
 
 namespace {
 
-constexpr int CH = 128;  // frames per pass
-constexpr int KWMAX = POLY_MAX_LABELS / 64;
+constexpr int SEL_THREADS = 1024, SEL_WAVES = SEL_THREADS / 64;
 constexpr int MMAX = POLY_MAX_CONTEXTS;
+constexpr int FEW_LABELS = 24;       // active labels up to which looking up first[] beats testing every context
 
 struct SelState {       // device image of (Y_{t-1}, S_{t-1})
     int32_t valid, pad;
@@ -23,250 +33,293 @@ struct SelState {       // device image of (Y_{t-1}, S_{t-1})
     uint64_t labels[1]; // KW words
 };
 
-__global__ __launch_bounds__(256) void select_kernel(const float *scores, int F, int K, const uint8_t *member, int M, float theta,
-                                                     int context_copy, const float *acc, float tau, SelState *state,
-                                                     int32_t *row_offsets, int32_t *adapter_ids, int cap, int32_t *counters)
+// NW: words per label set (64 labels each).  One thread per frame of a pass; wide label sets get fewer frames per pass so that
+// the two bitset arrays stay at 16 KB each.  VEC: scores per load (4 when K and the address allow 16-byte loads).
+// Every phase runs once per call, so its instructions come from memory once: short code is worth more here than unrolled loops.
+template <int NW, int VEC>
+__global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float *scores, int F, int K, const uint8_t *member, int M, float theta,
+                                                             int context_copy, const float *acc, float tau, SelState *state,
+                                                             int32_t *row_offsets, int32_t *adapter_ids, int cap, int32_t *counters,
+                                                             const SelectFollow fo)
 {
-    __shared__ int size_of[MMAX];
+    constexpr int CH = NW <= 2 ? 1024 : NW <= 4 ? 512 : 128;   // frames per pass
+    constexpr int LB = 4;                                      // score loads a thread has in flight
+    __shared__ uint64_t cmask[MMAX][NW];       // labels that the context at a scan position provides
+    __shared__ uint64_t prov_id[MMAX][NW];     // provided labels by context id
+    __shared__ uint64_t Y[CH][NW];             // Y_t; labels of frames that repeat the previous ones are cleared before `next` is built
+    __shared__ uint64_t P[CH][NW];             // labels that the greedy set of frame t provides
+    __shared__ uint64_t S[CH];                 // greedy set of frame t as a mask over scan positions
+    __shared__ uint64_t prevY[NW], prevP[NW], prevS, wmask[SEL_WAVES];
     __shared__ int order[MMAX];                // scan position -> context id
-    __shared__ uint64_t cmask[MMAX][KWMAX];    // labels that the context at a scan position provides
-    __shared__ uint64_t mem_id[MMAX][KWMAX], prov_id[MMAX][KWMAX];   // member / provided labels by context id
-    __shared__ uint64_t Y[CH][KWMAX];          // Y_t
-    __shared__ uint64_t S[CH];                 // S_t as a mask over scan positions
-    __shared__ int cnt[CH];
-    __shared__ int unc[CH];
-    __shared__ uint64_t prevY[KWMAX], prevProv[KWMAX];
-    __shared__ uint64_t prevS;
-    __shared__ int prevValid, total, total_unc, lead_s;
-    __shared__ int wtot[4], wunc[4];           // per wave: selected contexts, uncovered labels (scan below)
+    __shared__ int size_of[MMAX], first[64 * NW];
+    __shared__ int wtot[SEL_WAVES], wunc[SEL_WAVES], prevValid, total_s, unc_s;
+    __shared__ uint16_t nxt[CH + 1];
+    __shared__ uint8_t reach[CH + 1];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int KW = (K + 63) / 64;
-
-    // Membership and provided-label bitsets per (context id, 64-label word), one ballot each.  The loads of eight
-    // words are requested together (a loop that loads, ballots and stores one word at a time pays a full memory
-    // round trip per word), with clamped addresses instead of per-lane conditions.
-    for (int w0 = wave * 8; w0 < M * KW; w0 += 32) {
-        uint8_t mb[8];
-        float ac[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int w = min(w0 + u, M * KW - 1), c = w / KW, l = min((w % KW) * 64 + lane, K - 1);
-            mb[u] = member[(size_t)c * K + l];
-            ac[u] = acc ? acc[(size_t)c * K + l] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int w = w0 + u;
-            if (w < M * KW) {     // uniform
-                const bool in = (w % KW) * 64 + lane < K, mem = in && mb[u] != 0;
-                const uint64_t mm = __ballot(mem), pm = __ballot(mem && (acc == nullptr || ac[u] >= tau));
-                if (lane == 0) { mem_id[w / KW][w % KW] = mm; prov_id[w / KW][w % KW] = pm; }
-            }
-        }
-    }
-    __syncthreads();
-    // contexts in scan order: size ascending, id ascending
-    if (tid < M) {
-        int sz = 0;
-        for (int j = 0; j < KW; ++j) sz += __popcll(mem_id[tid][j]);
-        size_of[tid] = sz;
-    }
-    __syncthreads();
-    if (tid < M) {
-        int rank = 0;
-        for (int c = 0; c < M; ++c) rank += (size_of[c] < size_of[tid] || (size_of[c] == size_of[tid] && c < tid)) ? 1 : 0;
-        order[rank] = tid;
-    }
-    __syncthreads();
-    for (int w = tid; w < M * KW; w += 256) cmask[w / KW][w % KW] = prov_id[order[w / KW]][w % KW];
-    if (tid == 0) {
-        total = 0; total_unc = 0; prevS = 0; prevValid = 0;
-        if (state && state->valid) {
-            prevValid = 1;
-            uint64_t pos_mask = 0;
-            for (int pos = 0; pos < M; ++pos)
-                if ((state->set_ids >> order[pos]) & 1ull) pos_mask |= 1ull << pos;
-            prevS = pos_mask;
-        }
-    }
-    if (tid < KW) prevY[tid] = (state && state->valid) ? state->labels[tid] : 0ull;
-    __syncthreads();
-    if (tid < KW) {
-        uint64_t pv = 0;
-        for (int pos = 0; pos < M; ++pos)
-            if ((prevS >> pos) & 1ull) pv |= cmask[pos][tid];
-        prevProv[tid] = pv;
-    }
-    if (tid == 0) row_offsets[0] = 0;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int KW = NW <= 2 ? NW : (K + 63) / 64;
     const bool sequential = state != nullptr || context_copy != 0;
 
+    // Scores: thread i takes the VEC scores at i, i + 1024, .. of a pass, LB loads in flight (addresses clamped, not predicated).
+    // Few labels are active, so each piece that has one sets its bits in the frame's words with an LDS atomic.
+    typedef float vec_t __attribute__((ext_vector_type(VEC)));
+    const int KV = K / VEC, step_t = SEL_THREADS / KV, step_q = SEL_THREADS - step_t * KV;
+    vec_t sv[LB];
+    auto load_scores = [&](int f0, int tot, int i0) {
+#pragma unroll
+        for (int u = 0; u < LB; ++u) sv[u] = *(const vec_t *)(scores + (size_t)f0 * K + (size_t)min(i0 + u * SEL_THREADS, tot - 1) * VEC);
+    };
+    if (F > 0) load_scores(0, min(CH, F) * KV, tid);           // on their way while the contexts are set up
+
+    // membership and provided-label bitsets, one ballot per (context id, 64-label word); a context's size is the sum of its words'
+    for (int i = tid; i < CH * NW; i += SEL_THREADS) (&Y[0][0])[i] = 0;
+    if (tid < 64 * NW) first[tid] = 64;
+    if (tid < MMAX) size_of[tid] = 0;
+    if (tid == 0) { total_s = 0; unc_s = 0; prevValid = state ? state->valid : 0; prevS = 0; row_offsets[0] = 0; }
+    if (tid < NW) { prevY[tid] = (state && state->valid && tid < KW) ? state->labels[tid] : 0ull; prevP[tid] = 0; }
+    __syncthreads();
+    for (int w0 = wave; w0 < M * KW; w0 += 4 * SEL_WAVES) {
+        uint8_t mb[4];
+        float ac[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int w = min(w0 + u * SEL_WAVES, M * KW - 1), c = w / KW;
+            const size_t at = (size_t)c * K + min((w - c * KW) * 64 + lane, K - 1);
+            mb[u] = member[at];
+            ac[u] = acc ? acc[at] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int w = w0 + u * SEL_WAVES, c = w / KW, j = w - c * KW;
+            const bool mem = j * 64 + lane < K && mb[u] != 0;
+            const uint64_t mm = __ballot(mem), pm = __ballot(mem && (acc == nullptr || ac[u] >= tau));
+            if (lane == 0 && w < M * KW) { prov_id[c][j] = pm; atomicAdd(&size_of[c], __popcll(mm)); }
+        }
+    }
+    __syncthreads();
+    // contexts in scan order: size ascending, id ascending.  The rank of context c is the number of contexts before it: one ballot
+    for (int c = wave; c < M; c += SEL_WAVES) {
+        const int sz_l = lane < M ? size_of[lane] : 0x7fffffff, sz_c = size_of[c];
+        const int rank = __popcll(__ballot(sz_l < sz_c || (sz_l == sz_c && lane < c)));
+        if (lane == 0) order[rank] = c;
+#pragma unroll 2
+        for (int j = 0; j < KW; ++j) {
+            const uint64_t pm = prov_id[c][j];
+            if (lane == 0) cmask[rank][j] = pm;
+            if ((pm >> lane) & 1ull) atomicMin(&first[j * 64 + lane], rank);
+        }
+    }
+
     for (int f0 = 0; f0 < F; f0 += CH) {
-        const int n = min(CH, F - f0);
-        __syncthreads();
-        // Y_t: one ballot per 64 labels, the scores of eight words requested together (see above)
-        for (int w0 = wave * 8; w0 < n * KW; w0 += 32) {
-            float sv[8];
+        const int n = min(CH, F - f0), tot = n * KV;
+        if (f0) {
+            for (int i = tid; i < CH * NW; i += SEL_THREADS) (&Y[0][0])[i] = 0;
+            load_scores(f0, tot, tid);
+            __syncthreads();
+        }
+        for (int i0 = tid, t = tid / KV, q = tid - t * KV; i0 < tot;) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int w = min(w0 + u, n * KW - 1);
-                sv[u] = scores[(size_t)(f0 + w / KW) * K + min((w % KW) * 64 + lane, K - 1)];
-            }
+            for (int u = 0; u < LB; ++u) {
+                unsigned bits = 0;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int w = w0 + u;
-                if (w < n * KW) {     // uniform
-                    const uint64_t m = __ballot((w % KW) * 64 + lane < K && sv[u] >= theta);
-                    if (lane == 0) Y[w / KW][w % KW] = m;
-                }
+                for (int z = 0; z < VEC; ++z) bits |= (sv[u][z] >= theta ? 1u : 0u) << z;
+                const int l = q * VEC;
+                if (bits && i0 < tot) atomicOr((unsigned *)&Y[t][0] + (l >> 5), bits << (l & 31));
+                i0 += SEL_THREADS; t += step_t; q += step_q;
+                if (q >= KV) { q -= KV; ++t; }
             }
+            load_scores(f0, tot, i0);
         }
         __syncthreads();
-        // greedy cover, one frame per thread; the uncovered set stays in registers (a round trip through LDS per scan position
-        // and word made this the longest phase of the kernel)
+        if (f0 == 0 && wave == SEL_WAVES - 1 && state && prevValid) {   // the carried set: context ids -> scan positions, and what it provides
+            const uint64_t ids = state->set_ids;
+            uint64_t s = __ballot(lane < M && ((ids >> order[lane < M ? lane : 0]) & 1ull));
+            if (lane == 0) prevS = s;
+            uint64_t pv = 0;
+            for (; s; s &= s - 1) pv |= cmask[__ffsll((unsigned long long)s) - 1][lane < KW ? lane : 0];
+            if (lane < KW) prevP[lane] = pv;
+        }
+        // greedy cover of frame `tid`
+        uint64_t y[NW];
+        uint64_t sel = 0;
+        bool same = false;                                     // the labels of the previous frame (or the carried ones) again
         if (tid < n) {
-            // NW: compile-time bound of the words per label set (the registers are indexed by unrolled loops)
-            auto greedy = [&](auto NWC) {
-                constexpr int NW = decltype(NWC)::value;
-                uint64_t u[NW];
-                bool left = false;
+            uint64_t u[NW], pv[NW];
+            int active = 0;
+            bool eq = true;
 #pragma unroll
-                for (int j = 0; j < NW; ++j) {
-                    u[j] = j < KW ? Y[tid][j] : 0ull;
-                    left |= u[j] != 0;
+            for (int j = 0; j < NW; ++j) {
+                y[j] = j < KW ? Y[tid][j] : 0ull;
+                u[j] = y[j]; pv[j] = 0;
+                active += __popcll(y[j]);
+                if (j < KW) eq &= y[j] == (tid ? Y[tid - 1][j] : prevY[j]);
+            }
+            same = eq && (tid > 0 || prevValid);
+            uint64_t cand = M == 64 ? ~0ull : (1ull << M) - 1;
+            if (active <= FEW_LABELS) {
+                cand = 0;
+#pragma unroll
+                for (int j = 0; j < NW; ++j)
+                    for (uint64_t b = u[j]; b; b &= b - 1) {
+                        const int f = first[j * 64 + __ffsll((unsigned long long)b) - 1];
+                        if (f < 64) cand |= 1ull << f;         // 64: provided by nobody
+                    }
+            }
+            for (; cand; cand &= cand - 1) {
+                const int pos = __ffsll((unsigned long long)cand) - 1;
+                uint64_t m[NW], hit = 0;
+#pragma unroll
+                for (int j = 0; j < NW; ++j) { m[j] = j < KW ? cmask[pos][j] : 0ull; hit |= u[j] & m[j]; }
+                if (hit) {
+                    sel |= 1ull << pos;
+#pragma unroll
+                    for (int j = 0; j < NW; ++j) { u[j] &= ~m[j]; pv[j] |= m[j]; }
                 }
-                uint64_t sel = 0;
-                for (int pos = 0; pos < M && left; ++pos) {
-                    bool got = false;
+            }
+            S[tid] = sel;
+#pragma unroll
+            for (int j = 0; j < NW; ++j)
+                if (j < KW) P[tid][j] = pv[j];
+        }
+        // own: this frame took its own greedy set
+        bool own = true;
+        if (sequential) {
+            if (!context_copy) {
+                own = !same;
+            } else {
+                __syncthreads();
+                if (tid < n && same) {
 #pragma unroll
                     for (int j = 0; j < NW; ++j)
-                        if (NW <= 2 || j < KW) got |= (u[j] & cmask[pos][j]) != 0;
-                    if (got) {
-                        sel |= 1ull << pos;
-                        left = false;
+                        if (j < KW) Y[tid][j] = 0;
+                }
+                // first frame of the pass that the carried set does not serve
+                bool brk = false;
+                if (tid < n && !same) {
+                    brk = tid == 0 && !prevValid;
+#pragma unroll
+                    for (int j = 0; j < NW; ++j)
+                        if (j < KW) brk |= (y[j] & ~prevP[j]) != 0;
+                }
+                const uint64_t bm = __ballot(brk);
+                if (lane == 0) wmask[wave] = bm;
+                if (tid < n) reach[tid] = 0;
+                if (tid == 0) { reach[n] = 0; nxt[n] = (uint16_t)n; }
+                __syncthreads();
+                if (tid < n) {
+                    uint64_t np[NW];
+#pragma unroll
+                    for (int j = 0; j < NW; ++j) np[j] = j < KW ? ~P[tid][j] : 0ull;
+                    int t = tid + 1;
+                    for (bool hit = false; t < n; ++t) {
 #pragma unroll
                         for (int j = 0; j < NW; ++j)
-                            if (NW <= 2 || j < KW) { u[j] &= ~cmask[pos][j]; left |= u[j] != 0; }
+                            if (j < KW) hit |= (Y[t][j] & np[j]) != 0;
+                        if (hit) break;
+                    }
+                    nxt[tid] = (uint16_t)t;
+                }
+                if (tid == 0) {
+                    for (int w = 0; w < SEL_WAVES; ++w)
+                        if (wmask[w]) { reach[w * 64 + __ffsll((unsigned long long)wmask[w]) - 1] = 1; break; }
+                }
+                for (int span = 1; span <= n; span <<= 1) {    // the chain up to `span` links past the start is marked
+                    __syncthreads();
+                    int a = n, b = n;
+                    bool r = false;
+                    if (tid < n) { a = nxt[tid]; b = nxt[a]; r = reach[tid] != 0; }
+                    __syncthreads();
+                    if (tid < n) {
+                        nxt[tid] = (uint16_t)b;
+                        if (r) reach[a] = 1;
                     }
                 }
-                S[tid] = sel;
-                int nu = 0;
-#pragma unroll
-                for (int j = 0; j < NW; ++j) nu += __popcll(u[j]);
-                unc[tid] = nu;                   // uncovered labels of the greedy result (recomputed below if a set is reused)
-            };
-            if (KW <= 2) greedy(std::integral_constant<int, 2>{});       // (cmask words past KW are never read as set: u is 0 there)
-            else if (KW <= 4) greedy(std::integral_constant<int, 4>{});
-            else greedy(std::integral_constant<int, KWMAX>{});
-        }
-        __syncthreads();
-        // Reuse branches of Alg. 2.  Without context_copy a reused set is the greedy set of the same labels, so only the
-        // frames at the head of the call that repeat the carried labels take something else than their own greedy set
-        // (the carried one): found in parallel.  With context_copy a kept set need not be greedy: frame order.
-        if (sequential && context_copy == 0) {
-            if (tid == 0) lead_s = n;
-            __syncthreads();
-            if (tid < n) {
-                bool eq = true;
-                for (int j = 0; j < KW; ++j) eq &= Y[tid][j] == (tid ? Y[tid - 1][j] : prevY[j]);
-                if (!eq) atomicMin(&lead_s, tid);
-            }
-            __syncthreads();
-            const int lead = prevValid ? lead_s : 0;     // frames [0, lead) repeat the carried labels
-            if (tid < lead) S[tid] = prevS;
-            __syncthreads();
-            if (tid == 0) { prevS = S[n - 1]; prevValid = 1; }
-            if (tid < KW) prevY[tid] = Y[n - 1][tid];
-        } else if (sequential && tid == 0) {
-            for (int t = 0; t < n; ++t) {
-                bool same = prevValid != 0, covered = prevValid != 0 && context_copy != 0;
-                for (int j = 0; j < KW; ++j) {
-                    same &= Y[t][j] == prevY[j];
-                    covered &= (Y[t][j] & ~prevProv[j]) == 0;
-                }
-                if (same || covered) {
-                    S[t] = prevS;
-                } else if (S[t] != prevS) {
-                    prevS = S[t];
-                    for (int j = 0; j < KW; ++j) {
-                        uint64_t pv = 0;
-                        for (int pos = 0; pos < M; ++pos)
-                            if ((prevS >> pos) & 1ull) pv |= cmask[pos][j];
-                        prevProv[j] = pv;
-                    }
-                }
-                for (int j = 0; j < KW; ++j) prevY[j] = Y[t][j];
-                prevValid = 1;
+                __syncthreads();
+                own = tid < n && reach[tid] != 0;
             }
         }
+        // the last frame up to this one that took its own set (-1: the carried set still serves)
+        const uint64_t om = __ballot(tid < n && own);
+        if (lane == 0) wmask[wave] = om;
         __syncthreads();
-        // sizes; uncovered labels again where the reuse branches may have replaced the set
-        if (tid < n) {
-            const uint64_t sel = S[tid];
-            if (sequential) {
-                int u = 0;
-                for (int j = 0; j < KW; ++j) {
-                    uint64_t pv = 0;
-                    for (int pos = 0; pos < M; ++pos)
-                        if ((sel >> pos) & 1ull) pv |= cmask[pos][j];
-                    u += __popcll(Y[tid][j] & ~pv);
-                }
-                unc[tid] = u;
-            }
-            cnt[tid] = __popcll(sel);
-        }
-        __syncthreads();
-        // exclusive scan of at most CH counts: inside each wave by shuffles, then the totals of the waves before
+        int last = -1;
         {
-            const int c = tid < n ? cnt[tid] : 0, uu = tid < n ? unc[tid] : 0;
-            int inc = c, usum = uu;
+            const uint64_t upto = om & (~0ull >> (63 - lane));
+            if (upto) last = wave * 64 + 63 - __clzll((long long)upto);
+            else
+                for (int w = wave - 1; w >= 0; --w)
+                    if (wmask[w]) { last = w * 64 + 63 - __clzll((long long)wmask[w]); break; }
+        }
+        int c = 0, uu = 0;
+        if (tid < n) {
+            sel = last >= 0 ? S[last] : prevS;
+            c = __popcll(sel);
 #pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int v = __shfl_up(inc, o, 64);
-                if (lane >= o) inc += v;
-            }
+            for (int j = 0; j < NW; ++j)
+                if (j < KW) uu += __popcll(y[j] & ~(last >= 0 ? P[last][j] : prevP[j]));
+        }
+        // exclusive scan of the set sizes: a count has at most seven bits, so seven ballots give a wave's prefix sums
+        int before = 0, wsum = 0, usum = 0;
+        const uint64_t below = (1ull << lane) - 1;
 #pragma unroll
+        for (int b = 0; b < 7; ++b) {
+            const uint64_t m = __ballot((c >> b) & 1);
+            before += __popcll(m & below) << b;
+            wsum += __popcll(m) << b;
+        }
+        if (__ballot(uu != 0)) {                               // rare: some label is provided by nobody
+            usum = uu;
             for (int o = 32; o > 0; o >>= 1) usum += __shfl_xor(usum, o, 64);
-            if (lane == 63) { wtot[wave] = inc; wunc[wave] = usum; }
-            __syncthreads();
-            int before = total, ubefore = total_unc;
-            for (int w = 0; w < wave; ++w) before += wtot[w];
-            if (tid < n) {
-                cnt[tid] = before + inc - c;
-                row_offsets[f0 + tid + 1] = before + inc;
-            }
-            __syncthreads();
-            if (tid == 0) {
-                int run = total;
-                for (int w = 0; w < 4; ++w) { run += wtot[w]; ubefore += wunc[w]; }
-                total = run; total_unc = ubefore;
+        }
+        if (lane == 0) { wtot[wave] = wsum; wunc[wave] = usum; }
+        __syncthreads();
+        int base = total_s;
+        for (int w = 0; w < wave; ++w) base += wtot[w];
+        if (tid < n) {
+            int o = base + before;
+            row_offsets[f0 + tid + 1] = o + c;
+            for (uint64_t s = sel; s; s &= s - 1, ++o) {
+                const int id = order[__ffsll((unsigned long long)s) - 1];
+                if (o < cap) {
+                    adapter_ids[o] = id;
+                    if (fo.meta) { fo.frame_of_row[o] = f0 + tid; fo.adapter_of_row[o] = id; }
+                }
             }
         }
-        __syncthreads();
-        if (tid < n) {
-            uint64_t sel = S[tid];
-            int o = cnt[tid];
-            while (sel) {
-                const int pos = __ffsll((unsigned long long)sel) - 1;
-                sel &= sel - 1;
-                if (o < cap) adapter_ids[o] = order[pos];
-                ++o;
-            }
+        __syncthreads();                                       // everybody has read the carried values and this pass's arrays
+        if (tid == n - 1) {
+            prevS = sel; prevValid = 1;
+#pragma unroll
+            for (int j = 0; j < NW; ++j)
+                if (j < KW) { prevY[j] = y[j]; if (last >= 0) prevP[j] = P[last][j]; }
+        }
+        if (wave == 0) {
+            int a = lane < SEL_WAVES ? wtot[lane] : 0, b = lane < SEL_WAVES ? wunc[lane] : 0;
+#pragma unroll
+            for (int o = SEL_WAVES / 2; o > 0; o >>= 1) { a += __shfl_xor(a, o, 64); b += __shfl_xor(b, o, 64); }
+            if (lane == 0) { total_s += a; unc_s += b; }
         }
     }
     __syncthreads();
     if (tid == 0) {
-        counters[0] = total;
-        counters[1] = total_unc;
-        if (state && F > 0) {
-            uint64_t ids = 0;
-            for (int pos = 0; pos < M; ++pos)
-                if ((prevS >> pos) & 1ull) ids |= 1ull << order[pos];
-            state->valid = 1;
-            state->set_ids = ids;
+        counters[0] = total_s;
+        counters[1] = unc_s;
+        if (fo.meta) {                                         // ids and offsets are valid by construction; only the capacity can be exceeded
+            const bool bad = total_s > cap;
+            fo.meta->R = bad ? 0 : total_s;
+            fo.meta->F_ok = bad ? 0 : F;
+            fo.meta->status = bad ? POLY_ERANGE : POLY_OK;
+            if (fo.dev_status) *fo.dev_status = fo.meta->status;
         }
     }
-    if (state && F > 0 && tid < KW) state->labels[tid] = prevY[tid];
+    if (wave == 0 && state && F > 0) {
+        uint64_t ids = 0;
+        for (uint64_t s = prevS; s; s &= s - 1) ids |= 1ull << order[__ffsll((unsigned long long)s) - 1];
+        if (lane == 0) { state->valid = 1; state->set_ids = ids; }
+        if (lane < KW) state->labels[lane] = prevY[lane];
+    }
+    if (fo.carry)
+        for (int i = tid; i < K; i += SEL_THREADS) fo.carry[i] = fo.carry_src[i];
 }
 
 }  // namespace
@@ -277,14 +330,34 @@ extern "C" size_t poly_select_state_bytes(int K)
     return 16 + 8 * (size_t)((K + 63) / 64);
 }
 
-extern "C" int poly_select(const float *label_scores, int F, int K, const uint8_t *group_membership, int M,
-                           const poly_select_opts *opts, void *state, int32_t *row_offsets, int32_t *adapter_ids, int cap,
-                           int32_t *counters, void *stream)
+int launch_select(const float *label_scores, int F, int K, const uint8_t *group_membership, int M, const poly_select_opts *opts, void *state,
+                  int32_t *row_offsets, int32_t *adapter_ids, int cap, int32_t *counters, const SelectFollow &fo, hipStream_t st)
 {
     if (!opts || !group_membership || !row_offsets || !counters) return POLY_EINVAL;
     if (F < 0 || K <= 0 || K > POLY_MAX_LABELS || M <= 0 || M > POLY_MAX_CONTEXTS || cap < 0) return POLY_EINVAL;
     if ((F > 0 && !label_scores) || (cap > 0 && !adapter_ids)) return POLY_EINVAL;
-    POLY_LAUNCH(POLY_STAGE_SELECT, select_kernel, dim3(1), dim3(256), (hipStream_t)stream, label_scores, F, K, group_membership, M, opts->theta,
-                       opts->context_copy, opts->acc, opts->tau, (SelState *)state, row_offsets, adapter_ids, cap, counters);
+    const bool wide = K % 4 == 0 && ((uintptr_t)label_scores & 15) == 0;
+#define SELECT_LAUNCH(NW, VEC)                                                                                                           \
+    POLY_LAUNCH(POLY_STAGE_SELECT, (select_kernel<NW, VEC>), dim3(1), dim3(SEL_THREADS), st, label_scores, F, K, group_membership, M,       \
+                opts->theta, opts->context_copy, opts->acc, opts->tau, (SelState *)state, row_offsets, adapter_ids, cap, counters, fo)
+#define SELECT_CASE(NW)                    \
+    do {                                   \
+        if (wide) SELECT_LAUNCH(NW, 4);    \
+        else SELECT_LAUNCH(NW, 1);         \
+    } while (0)
+    if (K <= 64) SELECT_CASE(1);
+    else if (K <= 128) SELECT_CASE(2);
+    else if (K <= 256) SELECT_CASE(4);
+    else SELECT_CASE(16);
+#undef SELECT_LAUNCH
+#undef SELECT_CASE
     return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
+}
+
+extern "C" int poly_select(const float *label_scores, int F, int K, const uint8_t *group_membership, int M,
+                           const poly_select_opts *opts, void *state, int32_t *row_offsets, int32_t *adapter_ids, int cap,
+                           int32_t *counters, void *stream)
+{
+    return launch_select(label_scores, F, K, group_membership, M, opts, state, row_offsets, adapter_ids, cap, counters, SelectFollow{},
+                         (hipStream_t)stream);
 }

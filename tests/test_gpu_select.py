@@ -145,3 +145,28 @@ def test_tau_sweep_on_overlapping_contexts_built_from_co_occurrence(M_max):
             assert binding.poly_stream_metrics(off, ids, M_max) == oracle.stream_metrics(o_off, o_ids, M_max)
             seen.add((len(o_ids), o_unc))
     assert len(seen) > 9                                  # tau and the copy branch both change the outcome on this stream
+
+
+@pytest.mark.parametrize("K,M,F,dense", [(4, 1, 1, False), (63, 9, 65, True), (64, 64, 1025, False), (65, 20, 1024, True), (128, 33, 1100, True),
+                                         (129, 64, 513, True), (256, 40, 512, False), (257, 64, 129, True), (1024, 64, 128, True)])
+@pytest.mark.parametrize("copy", [False, True])
+def test_edges_of_passes_label_words_and_candidate_lists(K, M, F, dense, copy):
+    """Label counts around the 64-label words and the 16-byte loads, frame counts around a pass, and frames with more active labels
+    than are looked up one by one; a carried state throughout."""
+    rng = np.random.default_rng(K * 7 + F)
+    mem, acc = synth.make_cover_instance(K + F, K, M, max_size=max(1, K // 8), with_acc=True)
+    Y, cur = np.zeros((F, K), dtype=bool), rng.random(K) < 0.3
+    for t in range(F):
+        if rng.random() < 0.5:
+            cur = rng.random(K) < ((0.6 if t % 3 == 0 else 0.1) if dense else 3.0 / K)
+        elif rng.random() < 0.5 and cur.any():
+            cur = cur.copy()
+            cur[rng.choice(np.flatnonzero(cur))] = False
+        Y[t] = cur
+    scores = np.where(Y, 0.9, 0.1).astype(np.float32)
+    o_state = oracle.SelectState(K, M)
+    g_state = torch.zeros(binding.poly_select_state_bytes(K), dtype=torch.uint8, device="cuda")
+    for _ in range(2):
+        o_off, o_ids, o_unc = oracle.select(scores, mem, acc=acc, tau=0.2, context_copy=copy, state=o_state)
+        off, ids, n, unc = gpu_select(scores, mem, acc=acc, tau=0.2, context_copy=copy, state=g_state)
+        assert np.array_equal(off, o_off) and np.array_equal(ids, o_ids) and unc == o_unc and n == len(o_ids)
