@@ -259,8 +259,15 @@ void gemm_bf16_dma_kernel(const GemmArgs g, int tiles_m, int tiles_n)
     static_assert(NW * 32 * NC * 16 <= NS * STAGE_EL * 2, "staging must fit in the tile ring");
     extern __shared__ __attribute__((aligned(16))) bf16_t dsmem[];
 
+    // The eight runs are cut from the tiles that exist: the grid is sized for the caller's bound on the blocks, which can be
+    // half as many again as the true count, and the tiles past it would all fall on the last XCDs (config 3 with room for 3
+    // adapters on each of 64 frames: five of eight XCDs busy, 178 us per qkv or fc1 launch instead of 131).  The workgroups left over exit at once.
+    const bool flat = g.Tb > 0;                            // one run of rows over all blocks: xb = 0, t0 = first row of the tile
+    const int n_bound = flat ? g.nb : g.n_in;
+    const int n_true = g.n_in_dev ? min(*g.n_in_dev, n_bound) : n_bound;
+    const int Tlim = flat ? n_true * g.Tb : g.T;           // rows that exist
     int mt, tn;
-    if (!xcd_tile(blockIdx.x, g.n_in * tiles_m, tiles_n, PANEL, mt, tn)) return;
+    if (!xcd_tile(blockIdx.x, flat ? (Tlim + BM - 1) / BM : n_true * tiles_m, tiles_n, PANEL, mt, tn)) return;
     const int xb = mt / tiles_m, t0 = (mt - xb * tiles_m) * BM, n0 = tn * BN;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -314,18 +321,14 @@ void gemm_bf16_dma_kernel(const GemmArgs g, int tiles_m, int tiles_n)
             bias_q[j][q] = (rowwise && g.bias && bcol < g.N) ? *(const f32x4 *)(g.bias + bcol) : z4;
         }
 
-    // The tile loads need nothing but the tile coordinates, so they go out first; the row count, the fan-out
-    // offsets and the adapter id are read while they fly.  A tile that turns out to be past the true row count
-    // still read inside the caller's buffers (sized for the row bound); it drains its loads and leaves.
+    // The tile loads need nothing but the tile coordinates, so they go out first; the fan-out offsets and the adapter id are
+    // read while they fly.  A tile whose block has no output drains its loads and leaves.
     const int nk = g.K / BK;
     const int npro = min(NS, nk);
     for (int s = 0; s < npro; ++s) issue(s, s);
-    const bool flat = g.Tb > 0;                            // one run of rows over all blocks: xb = 0, t0 = first row of the tile
-    const int n_in = flat ? 1 : (g.n_in_dev ? min(*g.n_in_dev, g.n_in) : g.n_in);
-    const int Tlim = flat ? (g.n_in_dev ? min(*g.n_in_dev, g.nb) : g.nb) * g.Tb : g.T;   // rows that exist
     int ob0 = xb, ob1 = xb + 1;
-    if (g.out_off && !flat && xb < n_in) { ob0 = g.out_off[xb]; ob1 = g.out_off[xb + 1]; }
-    if (xb >= n_in || ob0 >= ob1 || t0 >= Tlim) {
+    if (g.out_off && !flat) { ob0 = g.out_off[xb]; ob1 = g.out_off[xb + 1]; }
+    if (ob0 >= ob1) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         return;
     }
