@@ -5,7 +5,7 @@
 // softmax over its registers in fp32, and feeds the unnormalised probabilities straight back as the B
 // operand of O^T = V^T P^T -- the accumulator layout of S^T is already a valid B layout once the keys of
 // each 16-key step are read from V^T in the matching order.  1/sum is applied per lane at the end.
-// fp32: one thread per query with an online softmax, keys and values streamed through LDS.
+// fp32: the same on fp32 matrix instructions, key tiles streamed through LDS with an online softmax.
 #include "poly_dev.h"
 
 namespace {
@@ -174,54 +174,94 @@ __global__ __launch_bounds__(512) void attn_bf16_kernel(const bf16_t *qkv, bf16_
     }
 }
 
-// fp32 path: keys and values go through LDS in chunks of 64; each thread keeps q, the running
-// maximum, the running sum and the 64 output columns of one query.
+// fp32: v_mfma_f32_32x32x2_f32, one wave per 32-query tile and four query tiles per workgroup, keys and values in tiles of 32
+// through LDS with an online softmax (any T).  As above, S^T = K Q^T leaves a lane all scores of one query, and the probabilities
+// are the B operand of O^T = V^T P^T as they are: step e of the second product takes key 8 (e / 4) + 4 lh + e % 4 from lane half
+// lh, so V is read from LDS at that key.  (One thread per query with the dot products on the vector ALU took 44 us for 17 tokens,
+// 6 us this way: a 32 x 32 tile is 64 + 64 matrix instructions of 64 cycles.)
 __global__ __launch_bounds__(256) void attn_f32_kernel(const float *qkv, float *out, int T, int D, int heads, int n_blocks,
                                                        const int *n_blocks_dev)
 {
-    __shared__ float Ks[64][65];
-    __shared__ float Vs[64][65];
+    constexpr int VS = 72;                                     // row stride of V: the two lane halves (rows 4 apart) hit different banks
+    __shared__ __attribute__((aligned(16))) float Ks[32 * 64]; // 16-byte chunk c of row r at c ^ (r & 15)
+    __shared__ __attribute__((aligned(16))) float Vs[32 * VS];
     const int nb = n_blocks_dev ? min(*n_blocks_dev, n_blocks) : n_blocks;
-    const int b = blockIdx.x / heads, hd = blockIdx.x % heads;
+    const int groups = (T + 127) / 128;
+    const int b = blockIdx.x / (heads * groups), hd = (blockIdx.x / groups) % heads, gq = blockIdx.x % groups;
     if (b >= nb) return;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lm = lane & 31, lh = lane >> 5;
     const size_t ld = (size_t)3 * D;
     const float *base = qkv + (size_t)b * T * ld + hd * 64;
-
-    for (int q0 = 0; q0 < T; q0 += 256) {
-        const int query = q0 + tid;
-        float q[64], o[64];
-        float mx = -INFINITY, sum = 0.f;
+    const int query = gq * 128 + wave * 32 + lm;
+    const bool live = gq * 128 + wave * 32 < T;                // (wave-uniform)
+    f32x4 qf[8];
 #pragma unroll
-        for (int c = 0; c < 64; ++c) { q[c] = query < T ? base[(size_t)query * ld + c] * 0.125f : 0.f; o[c] = 0.f; }
-        for (int k0 = 0; k0 < T; k0 += 64) {
-            __syncthreads();
-            for (int v = tid; v < 64 * 64; v += 256) {
-                const int key = v >> 6, c = v & 63;
-                const bool ok = k0 + key < T;
-                Ks[key][c] = ok ? base[(size_t)(k0 + key) * ld + D + c] : 0.f;
-                Vs[key][c] = ok ? base[(size_t)(k0 + key) * ld + 2 * D + c] : 0.f;
-            }
-            __syncthreads();
-            const int kn = min(64, T - k0);
-            for (int key = 0; key < kn; ++key) {
-                float sdot = 0.f;
+    for (int kk = 0; kk < 8; ++kk) qf[kk] = *(const f32x4 *)(base + (size_t)min(query, T - 1) * ld + 8 * kk + 4 * lh) * 0.125f;
+    f32x4 kv[4];                                               // this thread's pieces of the next tile: two of K, two of V
+    auto load = [&](int k0) {
 #pragma unroll
-                for (int c = 0; c < 64; ++c) sdot = fmaf(q[c], Ks[key][c], sdot);
-                const float nm = fmaxf(mx, sdot);
-                const float corr = expf(mx - nm), p = expf(sdot - nm);
-                sum = sum * corr + p;
-#pragma unroll
-                for (int c = 0; c < 64; ++c) o[c] = fmaf(p, Vs[key][c], o[c] * corr);
-                mx = nm;
-            }
+        for (int i = 0; i < 2; ++i) {
+            const int v = tid + 256 * i;
+            const float *row = base + (size_t)min(k0 + (v >> 4), T - 1) * ld + (v & 15) * 4;
+            kv[i] = *(const f32x4 *)(row + D);
+            kv[2 + i] = *(const f32x4 *)(row + 2 * D);
         }
-        if (query < T) {
-            const float inv = 1.0f / sum;
-            float *orow = out + ((size_t)b * T + query) * D + hd * 64;
+    };
+    load(0);
+    f32x16 o[2];
 #pragma unroll
-            for (int c = 0; c < 64; ++c) orow[c] = o[c] * inv;
+    for (int e = 0; e < 16; ++e) o[0][e] = o[1][e] = 0.f;
+    float mx = -INFINITY, sum = 0.f;
+    for (int k0 = 0; k0 < T; k0 += 32) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int v = tid + 256 * i, r = v >> 4, c = v & 15;
+            *(f32x4 *)(Ks + r * 64 + ((c ^ (r & 15)) << 2)) = kv[i];
+            *(f32x4 *)(Vs + r * VS + c * 4) = kv[2 + i];
         }
+        __syncthreads();
+        if (k0 + 32 < T) load(k0 + 32);
+        if (!live) continue;
+        f32x16 s;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[e] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {
+            const f32x4 kf = *(const f32x4 *)(Ks + lm * 64 + (((2 * kk + lh) ^ (lm & 15)) << 2));
+#pragma unroll
+            for (int z = 0; z < 4; ++z) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[z], qf[kk][z], s, 0, 0, 0);
+        }
+        float m = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            if (k0 + 8 * (e >> 2) + 4 * lh + (e & 3) >= T) s[e] = -INFINITY;
+            m = fmaxf(m, s[e]);
+        }
+        m = fmaxf(mx, fmaxf(m, __shfl_xor(m, 32, 64)));        // (a tile always has a key inside T)
+        const float corr = expf(mx - m);
+        mx = m;
+        float t = 0.f;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) { s[e] = expf(s[e] - m); t += s[e]; }
+        sum = fmaf(sum, corr, t);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) { o[0][e] *= corr; o[1][e] *= corr; }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const float *vr = Vs + (8 * (e >> 2) + 4 * lh + (e & 3)) * VS + lm;
+            o[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[0], s[e], o[0], 0, 0, 0);
+            o[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[32], s[e], o[1], 0, 0, 0);
+        }
+    }
+    if (query < T) {
+        const float inv = 1.0f / (sum + __shfl_xor(sum, 32, 64));
+        float *orow = out + ((size_t)b * T + query) * D + hd * 64 + 4 * lh;
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *(f32x4 *)(orow + dt * 32 + 8 * q) = f32x4{o[dt][4 * q], o[dt][4 * q + 1], o[dt][4 * q + 2], o[dt][4 * q + 3]} * inv;
     }
 }
 
@@ -264,7 +304,7 @@ int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_
         default: return POLY_EINVAL;  // bf16 attention holds all keys of a block in 64 KB of LDS: T <= 224
         }
     } else {
-        POLY_LAUNCH(POLY_STAGE_ATTN, attn_f32_kernel, dim3((unsigned)(n_blocks * heads)), dim3(256), st, (const float *)qkv, (float *)out, T, D, heads,
+        POLY_LAUNCH(POLY_STAGE_ATTN, attn_f32_kernel, dim3((unsigned)(n_blocks * heads * ((T + 127) / 128))), dim3(256), st, (const float *)qkv, (float *)out, T, D, heads,
                            n_blocks, n_blocks_dev);
     }
     return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;

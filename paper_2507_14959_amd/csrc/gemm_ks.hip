@@ -1,0 +1,384 @@
+// The linears of small calls and of single precision: y = x W + b (+ s (x A_k) B_k) on tiles of 32 or 64 rows and columns, the
+// contraction split over the four waves of a workgroup.
+//
+// What bounds a product of a few hundred rows is not arithmetic: a grid of 128 x 128 tiles leaves most of the 256 CUs idle, and
+// the busy ones wait for K / 64 round trips of an LDS ring that all their waves share through a barrier.  Here
+//  - tiles are small, so that the weights and rows a CU has to pull through its load path (30-50 bytes per clock) are few and the
+//    grid covers the chip;
+//  - wave w takes the k-tiles w, w + 4, .. (128 bytes of every row each) of the whole tile through a ring of its own: up to three
+//    of its k-tiles are in flight, there is no barrier in the loop, and a 768-long contraction is three steps;
+//  - the four partial sums meet in LDS once, in fixed order (the same order for every tile size, so results do not depend on
+//    which one the size of the call selects), and each wave finishes one 32 x 32 subtile: low-rank expand, bias, GELU or residual;
+//  - the chain offsets -> adapter ids -> operands of the expand, and the residual rows, are requested before the loop.
+// v_mfma_f32_32x32x16_bf16, or v_mfma_f32_32x32x2_f32 (true single precision: twice the rate of the vector ALU without packed
+// operations).  A lane's 16 bytes are 8 or 4 consecutive contraction elements of one row; both operands use the same order.
+//
+// 3 frames (591 rows) through the 768-wide backbone: proj and fc2 30 us each with 128 x 128 tiles, 16 us here, 1338 -> 906 us per
+// forward.  fp32 (config 1: 68-119 rows, K = 192 and 768) 49 us per product on the vector ALU, 11 us here.
+#include "poly_dev.h"
+#include "rowtile.h"
+
+namespace {
+
+template <typename T> struct Elt;
+template <> struct Elt<bf16_t> {
+    static constexpr int V = 8;                            // elements per 16 bytes
+    typedef bf16x8 frag;
+    static __device__ __forceinline__ f32x16 mma(frag w, frag x, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, x, c, 0, 0, 0); }
+    static __device__ __forceinline__ f32x4 gelu4(f32x4 v) { return gelu_poly4(v); }
+};
+template <> struct Elt<float> {
+    static constexpr int V = 4;
+    typedef f32x4 frag;
+    static __device__ __forceinline__ f32x16 mma(frag w, frag x, f32x16 c)
+    {
+#pragma unroll
+        for (int z = 0; z < 4; ++z) c = __builtin_amdgcn_mfma_f32_32x32x2f32(w[z], x[z], c, 0, 0, 0);
+        return c;
+    }
+    static __device__ __forceinline__ f32x4 gelu4(f32x4 v) { return f32x4{gelu_erf(v[0]), gelu_erf(v[1]), gelu_erf(v[2]), gelu_erf(v[3])}; }
+};
+
+// a value that every lane of the wave reads from the same address, written by an earlier launch: through the scalar cache, whose
+// counter is not the one the tile loads wait on
+__device__ __forceinline__ int uload(const int *p) { return *(const int __attribute__((address_space(4))) *)(uintptr_t)p; }
+
+constexpr int KS_NSMAX = 3;
+
+// MI x NI subtiles of 32 x 32 per tile.  ns: ring stages per wave.  SHRINK: S = scale * x At_k^T (weights of the output block's own
+// adapter, row tiles inside blocks, columns past the rank zero) instead of a linear with shared weights.
+template <typename T, int MI, int NI, bool SHRINK>
+__global__ __launch_bounds__(256) void gemm_ks_kernel(const GemmArgs g, int tiles_m, int tiles_n, int ns)
+{
+    typedef Elt<T> E;
+    typedef typename E::frag frag;
+    constexpr int V = E::V, BK = 8 * V, BM = 32 * MI, BN = 32 * NI;
+    constexpr int STAGE = (BM + BN) * 128, NLD = (BM + BN) / 8;      // bytes / loads (8 rows x 128 bytes) per stage
+    constexpr int NF = MI * NI;                                       // subtiles, finished by waves 0 .. NF - 1
+    static_assert(NF <= 4, "one subtile per wave at most");
+    extern __shared__ __attribute__((aligned(16))) char ks_lds[];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lm = lane & 31, lh = lane >> 5;
+    const bool flat = g.Tb > 0;                            // one run of rows over all input blocks
+    const int n_bound = flat ? g.nb : g.n_in;
+    const int n_true = g.n_in_dev ? min(uload(g.n_in_dev), n_bound) : n_bound;
+    const int Tlim = flat ? n_true * g.Tb : g.T, Tblk = flat ? g.Tb : g.T;
+    const int mtot = flat ? (Tlim + BM - 1) / BM : n_true * tiles_m;
+    // the tiles that exist are cut into eight equal runs, one per XCD: of columns with all their rows when there are more columns
+    // than rows (a column's weights come to one L2 only), else of rows with all their columns
+    int mt, tn;
+    {
+        const int xcd = blockIdx.x & 7;
+        const long total = (long)mtot * tiles_n, lo = total * xcd / 8, hi = total * (xcd + 1) / 8, L = lo + (blockIdx.x >> 3);
+        if (L >= hi) return;
+        if (mtot <= tiles_n) { tn = (int)(L / mtot); mt = (int)(L - (long)tn * mtot); }
+        else { mt = (int)(L / tiles_n); tn = (int)(L - (long)mt * tiles_n); }
+    }
+    const int blk = flat ? 0 : mt / tiles_m, t0 = (flat ? mt : mt - blk * tiles_m) * BM, n0 = tn * BN;
+    int xb = blk, k_own = -1;                              // input block; SHRINK: adapter whose weights this tile uses
+    if (SHRINK) {
+        k_own = uload(g.adapter_of_out + blk);
+        if (g.res_block_of_out) xb = uload(g.res_block_of_out + blk);
+        if (k_own < 0) return;
+    }
+    const int nw = SHRINK ? g.r : g.N;                     // weight rows
+    const T *A = (const T *)g.A + ((size_t)xb * g.T + t0) * g.K;
+    const T *W = (const T *)g.Wt + ((size_t)(SHRINK ? k_own * g.r : 0) + n0) * g.K;
+
+    // ---- k-tiles of this wave: wave, wave + 4, ..  A lane loads 16 bytes: row 8 g + lane / 8 of a tile, position lane % 8; the
+    // 128-byte rows are stored with their chunks swizzled by (row >> 1) & 7.  Rows past the end repeat the last one (their
+    // results are never stored); chunks past K are read from the row's last chunk and masked below.
+    const int nk = (g.K + BK - 1) / BK, steps = (nk - wave + 3) >> 2;
+    const unsigned rowb = (unsigned)g.K * sizeof(T);
+    const int lr = lane >> 3, c0 = (lane & 7) ^ (lr >> 1), c1 = c0 ^ 4;
+    const int tail = g.K - (nk - 1) * BK;                  // elements in the last k-tile
+    const int adj0 = min(c0, tail / V - 1) - c0, adj1 = min(c1, tail / V - 1) - c1;
+    char *ring = ks_lds + wave * ns * STAGE;
+    auto issue = [&](int i) {
+        const int kt = wave + 4 * i;
+        const bool last = kt == nk - 1;                    // uniform
+        const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_addr_of(ring + (i % ns) * STAGE));
+        const unsigned e0 = (unsigned)(c0 + (last ? adj0 : 0)) * 16, e1 = (unsigned)(c1 + (last ? adj1 : 0)) * 16;
+#pragma unroll
+        for (int q = 0; q < BM / 8; ++q)
+            glds16_s((const char *)A + (size_t)kt * 128, (unsigned)min(8 * q + lr, Tlim - 1 - t0) * rowb + ((q & 1) ? e1 : e0), lds0 + q * 1024);
+#pragma unroll
+        for (int q = 0; q < BN / 8; ++q)
+            glds16_s((const char *)W + (size_t)kt * 128, (unsigned)min(8 * q + lr, nw - 1 - n0) * rowb + ((q & 1) ? e1 : e0), lds0 + (BM / 8 + q) * 1024);
+    };
+    const int npro = min(ns, steps);
+    for (int i = 0; i < npro; ++i) issue(i);
+
+    // ---- what the finishing waves will need: the first output block of their subtile's first input block, its first low-rank
+    // term and its residual rows, requested now
+    const int fi = wave / NI, fj = wave % NI;              // this wave's subtile
+    const int tw = t0 + 32 * fi, nc = n0 + 32 * fj;        // its first row (in the run or the block) and column
+    const bool fin = wave < NF && tw < Tlim && nc < g.N;
+    const int b_lo = flat ? tw / Tblk : xb;
+    const bool has_lora = !SHRINK && g.S && g.adapter_of_out, vec = g.N % 4 == 0;
+    const int rch = lane & 7, rrow = lane >> 3;            // read-back mapping: 8 lanes x 16 bytes cover a row of the subtile
+    const int col = nc + 4 * rch;
+    frag pre_s[16 / (2 * V)], pre_w[16 / (2 * V)];         // operands of ranks [0, 16) of the first term
+    f32x4 pre_r[4];
+    int ob_pre = -1;
+    const frag zero = {};
+    auto load_s = [&](int sb, int t, int s0) { return *(const frag *)((const T *)g.S + ((size_t)sb * Tblk + t) * g.RP + s0 + lh * V); };
+    auto load_w = [&](int k_ad, int s0) {                  // Bt rows of this subtile's columns
+        const int c = min(nc + lm, g.N - 1), j0 = s0 + lh * V;
+        const T *p = (const T *)g.Bt + ((size_t)k_ad * g.N + c) * g.r;
+        frag f = zero;
+        if (g.r % V == 0) {
+            f = *(const frag *)(p + min(j0, g.r - V));
+            if (j0 + V > g.r) f = zero;
+        } else {
+#pragma unroll
+            for (int q = 0; q < V; ++q)
+                if (j0 + q < g.r) f[q] = p[j0 + q];
+        }
+        return f;
+    };
+    auto load_res = [&](f32x4(&v)[4], int ob, int trow0, int rows) {
+        const int rb = g.res_block_of_out ? uload(g.res_block_of_out + ob) : ob;
+        const float *src = g.res + ((size_t)rb * g.Tout + g.t_off) * g.N + min(col, g.N - 4);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = *(const f32x4 *)(src + (long)min(max(trow0 + 8 * q + rrow, 0), rows - 1) * g.N);
+    };
+    if (!SHRINK && fin) {
+        const int o0 = g.out_off ? uload(g.out_off + b_lo) : b_lo, o1 = g.out_off ? uload(g.out_off + b_lo + 1) : b_lo + 1;
+        if (o0 < o1) {
+            ob_pre = o0;
+            const int trow0 = flat ? tw - b_lo * Tblk : tw;
+            if (has_lora) {
+                const int s0 = g.set_off ? uload(g.set_off + o0) : o0, s1 = g.set_off ? uload(g.set_off + o0 + 1) : o0 + 1;
+                const int k_ad = s0 < s1 ? uload(g.adapter_of_out + s0) : -1;
+                if (k_ad >= 0) {
+#pragma unroll
+                    for (int u = 0; u < 16 / (2 * V); ++u) {
+                        pre_s[u] = load_s(s0, min(max(trow0 + lm, 0), Tblk - 1), 2 * V * u);
+                        pre_w[u] = load_w(k_ad, 2 * V * u);
+                    }
+                }
+            }
+            if (g.mode == EPI_RESID && g.res && vec) load_res(pre_r, o0, trow0, Tblk);
+        }
+    }
+
+    // ---- main loop: no barrier.  k-tile i has landed once at most the loads of the k-tiles behind it are pending; the requests
+    // above are younger than the first ns k-tiles, so they make the first waits stricter at most.
+    f32x16 acc[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    const int sw = (lm >> 1) & 7;
+    for (int i = 0; i < steps; ++i) {
+        const int ahead = min(steps - 1, i + ns - 1) - i;  // k-tiles requested after this one
+        if (ahead >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NLD) : "memory");
+        else if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NLD) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const char *st = ring + (i % ns) * STAGE;
+        frag fx[4][MI], fw[4][NI];
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            const int ch = ((2 * kk + lh) ^ sw) << 4;
+#pragma unroll
+            for (int m = 0; m < MI; ++m) fx[kk][m] = *(const frag *)(st + (m * 32 + lm) * 128 + ch);
+#pragma unroll
+            for (int n = 0; n < NI; ++n) fw[kk][n] = *(const frag *)(st + (BM + n * 32 + lm) * 128 + ch);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the stage is in registers: request its next k-tile
+        if (i + ns < steps) issue(i + ns);
+        if (wave + 4 * i == nk - 1 && tail < BK) {         // chunks past K add nothing
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+                if ((2 * kk + lh) * V >= tail) {
+#pragma unroll
+                    for (int m = 0; m < MI; ++m) fx[kk][m] = zero;
+#pragma unroll
+                    for (int n = 0; n < NI; ++n) fw[kk][n] = zero;
+                }
+        }
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+            for (int m = 0; m < MI; ++m)
+#pragma unroll
+                for (int n = 0; n < NI; ++n) acc[m][n] = E::mma(fw[kk][n], fx[kk][m], acc[m][n]);
+    }
+
+    // ---- the four partial sums meet: area (wave, subtile) holds 16 values x 64 lanes
+    __syncthreads();                                       // the rings are dead
+    float *red = (float *)ks_lds;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4)
+                *(f32x4 *)(red + ((wave * NF + i * NI + j) * 4 + e4) * 256 + lane * 4) =
+                    f32x4{acc[i][j][4 * e4], acc[i][j][4 * e4 + 1], acc[i][j][4 * e4 + 2], acc[i][j][4 * e4 + 3]};
+    __syncthreads();
+    if (!fin) return;
+    f32x16 base;                                           // row tw + lm, columns nc + 8 (e / 4) + 4 lh + e % 4
+#pragma unroll
+    for (int e4 = 0; e4 < 4; ++e4) {
+        f32x4 s = *(const f32x4 *)(red + ((0 * NF + wave) * 4 + e4) * 256 + lane * 4);
+#pragma unroll
+        for (int w = 1; w < 4; ++w) s += *(const f32x4 *)(red + ((w * NF + wave) * 4 + e4) * 256 + lane * 4);
+#pragma unroll
+        for (int z = 0; z < 4; ++z) base[4 * e4 + z] = s[z];
+    }
+    float *stg = red + wave * 1024;                        // this wave's part of wave 0's areas: read above, by this wave only
+
+    if (SHRINK) {
+        const int t = tw + lm;
+        if (t < g.T) {
+            T *out = (T *)g.out + ((size_t)blk * g.T + t) * g.RP;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int c = nc + 8 * (e >> 2) + 4 * lh + (e & 3);
+                if (c < g.RP) out[c] = from_f32<T>(c < g.r ? g.scale * base[e] : 0.f);
+            }
+        }
+        return;
+    }
+
+    f32x4 bias4 = {0.f, 0.f, 0.f, 0.f};
+    if (g.bias && vec) bias4 = *(const f32x4 *)(g.bias + min(col, g.N - 4));
+    // rows [lo, hi) of the subtile -> output block ob; row 0 of the subtile is row trow0 of the block
+    auto emit = [&](const f32x16 &c, int ob, int trow0, int lo, int hi) {
+        const long obase = ((long)ob * g.Tout + g.t_off + trow0) * g.N;
+        if (!vec) {                                        // N not a multiple of 4: element by element
+            const int row = lm;
+            if (row < lo || row >= hi) return;
+            const int rb = (g.mode == EPI_RESID && g.res && g.res_block_of_out) ? g.res_block_of_out[ob] : ob;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int cc = nc + 8 * (e >> 2) + 4 * lh + (e & 3);
+                if (cc >= g.N) continue;
+                float v = c[e] + (g.bias ? g.bias[cc] : 0.f);
+                const long o = obase + (long)row * g.N + cc;
+                if (g.mode == EPI_RESID) {
+                    if (g.res) v += g.res[((long)rb * g.Tout + g.t_off + trow0 + row) * g.N + cc];
+                    if (g.pos) v += g.pos[(long)(g.t_off + trow0 + row) * g.N + cc];
+                    ((float *)g.out)[o] = v;
+                } else {
+                    if (g.mode == EPI_GELU) v = E::gelu4(f32x4{v, v, v, v})[0];
+                    ((T *)g.out)[o] = from_f32<T>(v);
+                }
+            }
+            return;
+        }
+        f32x4 rv[4];
+        const bool res = g.mode == EPI_RESID && g.res;
+        if (res) {
+            if (ob == ob_pre) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) rv[q] = pre_r[q];
+            } else load_res(rv, ob, trow0, Tblk);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *(f32x4 *)(stg + lm * 32 + (((2 * q + lh) ^ ((lm >> 1) & 7)) << 2)) = f32x4{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int row = 8 * q + rrow;
+            f32x4 v = *(const f32x4 *)(stg + row * 32 + ((rch ^ ((row >> 1) & 7)) << 2)) + bias4;
+            if (row < lo || row >= hi || col >= g.N) continue;
+            if (g.mode == EPI_RESID) {
+                if (res) v += rv[q];
+                if (g.pos) v += *(const f32x4 *)(g.pos + (long)(g.t_off + trow0 + row) * g.N + col);
+                *(f32x4 *)((float *)g.out + obase + (long)row * g.N + col) = v;
+            } else {
+                if (g.mode == EPI_GELU) v = E::gelu4(v);
+                typedef T out4 __attribute__((ext_vector_type(4)));
+                *(out4 *)((T *)g.out + obase + (long)row * g.N + col) = out4{from_f32<T>(v[0]), from_f32<T>(v[1]), from_f32<T>(v[2]), from_f32<T>(v[3])};
+            }
+        }
+    };
+    int lo = 0;
+    for (int bb = b_lo; lo < 32; ++bb) {                   // the input blocks whose rows lie in this subtile
+        const int trow0 = flat ? tw - bb * Tblk : tw;
+        const int hi = min(32, (flat ? min(Tblk, Tlim - bb * Tblk) : Tlim) - trow0);
+        if (hi <= lo) break;
+        const int o0 = g.out_off ? uload(g.out_off + bb) : bb, o1 = g.out_off ? uload(g.out_off + bb + 1) : bb + 1;
+        for (int ob = o0; ob < o1; ++ob) {                 // the output blocks that fan out of it
+            f32x16 c = base;
+            const int sb0 = g.set_off ? uload(g.set_off + ob) : ob, sb1 = g.set_off ? uload(g.set_off + ob + 1) : ob + 1;
+            for (int sb = sb0; has_lora && sb < sb1; ++sb) {   // one low-rank term, or all the terms summed on this block
+                const int k_ad = uload(g.adapter_of_out + sb);
+                if (k_ad < 0) continue;
+                const int t = min(max(trow0 + lm, 0), Tblk - 1);
+                const bool mine = lm >= lo && lm < hi;     // rows of other blocks add nothing
+                const bool pre = ob == ob_pre && sb == sb0;
+                for (int s0 = 0; s0 < g.RP; s0 += 16) {
+#pragma unroll
+                    for (int u = 0; u < 16 / (2 * V); ++u) {
+                        frag fs = pre_s[u], fw = pre_w[u];
+                        if (!(pre && s0 == 0)) { fs = load_s(sb, t, s0 + 2 * V * u); fw = load_w(k_ad, s0 + 2 * V * u); }
+                        c = E::mma(fw, mine ? fs : zero, c);
+                    }
+                }
+            }
+            emit(c, ob, trow0, lo, hi);
+        }
+        lo = hi;
+        if (!flat) break;
+    }
+}
+
+template <typename T, int MI, int NI, bool SHRINK> int launch_ks(const GemmArgs &g, hipStream_t st)
+{
+    constexpr int STAGE = 32 * (MI + NI) * 128, BK = 8 * Elt<T>::V, RED = 4 * MI * NI * 4096;
+    const int nk = (g.K + BK - 1) / BK;
+    int ns = (nk + 3) / 4 < KS_NSMAX ? (nk + 3) / 4 : KS_NSMAX;   // no more stages than a wave has k-tiles: short contractions leave room for other workgroups
+    while (4 * ns * STAGE > 160 * 1024) --ns;
+    const int lds = 4 * ns * STAGE > RED ? 4 * ns * STAGE : RED;
+    auto kern = gemm_ks_kernel<T, MI, NI, SHRINK>;
+    static bool attr_set = false;       // raising the dynamic LDS limit is a per-kernel, process-wide setting
+    if (!attr_set) {
+        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) return POLY_EHIP;
+        attr_set = true;
+    }
+    const int tiles_m = (g.T + 32 * MI - 1) / (32 * MI), tiles_n = (g.N + 32 * NI - 1) / (32 * NI);
+    const long total = (long)g.n_in * tiles_m * tiles_n;
+    if (total > 0x3fffffffL) return POLY_EINVAL;
+    POLY_LAUNCH_SHMEM(SHRINK ? POLY_STAGE_SHRINK : POLY_STAGE_GEMM, kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(256), lds, st, g, tiles_m, tiles_n, ns);
+    return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
+}
+
+}  // namespace
+
+// Tile by the time of the busiest CU: rounds of tiles over the 256 CUs, each the larger of its loads through the CU's load path
+// (about 40 bytes per clock) and its products, plus what a tile costs whatever its size (first round trip, partial sums, stores).
+int launch_gemm_ks(const GemmArgs &g, int dtype, hipStream_t st)
+{
+    const double es = dtype == POLY_BF16 ? 2 : 4, rate = dtype == POLY_BF16 ? 2048 : 220;    // flop per clock and CU
+    auto cost = [&](int mi, int ni) {
+        const double tiles = (double)g.n_in * ((g.T + 32 * mi - 1) / (32 * mi)) * ((g.N + 32 * ni - 1) / (32 * ni));
+        const double rounds = (double)(long)((tiles + 255) / 256);
+        const double load = es * g.K * 32 * (mi + ni) / 40, prod = 2.0 * g.K * 1024 * mi * ni / rate;
+        return rounds * (3000 + (load > prod ? load : prod));
+    };
+    const double c11 = cost(1, 1), c12 = cost(1, 2), c22 = cost(2, 2);
+    if (dtype == POLY_BF16) {
+        if (c11 < c12 && c11 < c22) return launch_ks<bf16_t, 1, 1, false>(g, st);
+        if (c12 < c22) return launch_ks<bf16_t, 1, 2, false>(g, st);
+        return launch_ks<bf16_t, 2, 2, false>(g, st);
+    }
+    if (c11 < c12 && c11 < c22) return launch_ks<float, 1, 1, false>(g, st);
+    if (c12 < c22) return launch_ks<float, 1, 2, false>(g, st);
+    return launch_ks<float, 2, 2, false>(g, st);
+}
+
+// S[ob] = scale * X[in_block_of_out[ob]] At[adapter_of_out[ob]]^T in single precision, zero padded to RP columns
+int launch_shrink_f32(const float *X, int T, int K, const float *At, int r, int RP, float scale, int n_out, const int *n_out_dev,
+                      const int *in_block_of_out, const int *adapter_of_out, float *S, hipStream_t st)
+{
+    GemmArgs g = {};
+    g.A = X; g.Wt = At; g.T = T; g.K = K; g.N = RP; g.n_in = n_out; g.n_in_dev = n_out_dev; g.r = r; g.RP = RP; g.scale = scale;
+    g.adapter_of_out = adapter_of_out; g.res_block_of_out = in_block_of_out; g.out = S; g.Tout = T;
+    return launch_ks<float, 1, 1, true>(g, st);
+}

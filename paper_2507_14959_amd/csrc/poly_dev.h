@@ -163,6 +163,7 @@ struct GemmArgs {
     const float *res;     // EPI_RESID: float [..*Tout][N] added (row res_block*Tout + t_off + t), or null
     const int *res_block_of_out;  // null = ob
     const float *pos;     // EPI_RESID: float [Tout][N] added (row t_off + t), or null
+    float scale;          // launch_shrink_f32 only
     // set by launch_gemm only.  Tb > 0: the nb input blocks of Tb rows are tiled as ONE run of nb * Tb rows (T = nb * Tb,
     // n_in = 1; n_in_dev still counts blocks and Tout = Tb still places the output blocks), so that row tiles ignore block
     // boundaries; row t of the run belongs to input block t / Tb
@@ -170,6 +171,9 @@ struct GemmArgs {
 };
 
 int launch_gemm(const GemmArgs &g, int dtype, hipStream_t st);
+int launch_gemm_ks(const GemmArgs &g, int dtype, hipStream_t st);    // small calls and fp32 (gemm_ks.hip); called by launch_gemm
+int launch_shrink_f32(const float *X, int T, int K, const float *At, int r, int RP, float scale, int n_out, const int *n_out_dev,
+                      const int *in_block_of_out, const int *adapter_of_out, float *S, hipStream_t st);
 
 // Row-tile linear for K <= 192 (rowlin.hip): y = [LN](x) Wt^T + b + scale ([LN](x) At_k^T) Bt_k^T with the
 // LayerNorm and the low-rank shrink computed inside the kernel.

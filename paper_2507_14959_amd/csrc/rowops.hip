@@ -285,28 +285,6 @@ __global__ __launch_bounds__(256) void shrink_bf16_kernel(const bf16_t *X, int T
     }
 }
 
-// fp32: one thread per (row, rank)
-__global__ void shrink_f32_kernel(const float *X, int T, int K, const float *At, int r, int RP, float scale, int n_out,
-                                  const int *n_out_dev, const int *in_block_of_out, const int *adapter_of_out, float *S)
-{
-    const int n = n_out_dev ? min(*n_out_dev, n_out) : n_out;
-    const size_t total = (size_t)n * T * RP;
-    for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += (size_t)gridDim.x * blockDim.x) {
-        const int j = idx % RP;
-        const size_t row = idx / RP;
-        const int ob = row / T, t = row % T;
-        const int k_ad = adapter_of_out[ob];
-        float acc = 0.f;
-        if (k_ad >= 0 && j < r) {
-            const int xb = in_block_of_out ? in_block_of_out[ob] : ob;
-            const float *xr = X + ((size_t)xb * T + t) * K;
-            const float *ar = At + ((size_t)k_ad * r + j) * K;
-            for (int k = 0; k < K; ++k) acc = fmaf(xr[k], ar[k], acc);
-        }
-        S[idx] = scale * acc;
-    }
-}
-
 // ------------------------------------------------------------------ heads and merge to label space
 // One wave per row-block: z = LN(x[src][0][:]); logits = z H_k + hb_k; scores = sigmoid(logits); lane c
 // then folds class c into the frame's label vector.  Scores are in (0, 1): the order of positive floats
@@ -468,10 +446,7 @@ int launch_shrink(const void *X, int T, int K, const void *At, int r, int RP, fl
             launch_shrink_bf16<2, 1>(st, (const bf16_t *)X, T, K, (const bf16_t *)At, r, RP, scale, n_out, n_out_dev, in_block_of_out,
                                      adapter_of_out, pair_off, (bf16_t *)S);
     } else {
-        const size_t total = (size_t)n_out * T * RP;
-        const unsigned blocks = (unsigned)((total + 255) / 256 > 65536 ? 65536 : (total + 255) / 256);
-        POLY_LAUNCH(POLY_STAGE_SHRINK, shrink_f32_kernel, dim3(blocks), dim3(256), st, (const float *)X, T, K, (const float *)At, r, RP, scale, n_out,
-                           n_out_dev, in_block_of_out, adapter_of_out, (float *)S);
+        return launch_shrink_f32((const float *)X, T, K, (const float *)At, r, RP, scale, n_out, n_out_dev, in_block_of_out, adapter_of_out, (float *)S, st);
     }
     return hip_ok();
 }

@@ -266,3 +266,10 @@ def test_paper_preset_query_value_rank16_scale2_last_two_layers(compose):
     _, want, err = compare(cfg, w, frames, off, ids, cfg.L0, K=cfg.n_adapters * cfg.C, compose=compose)
     # the key columns of the qkv adapter are silent: the same weights with only the query and value blocks kept
     print(f"paper preset ({compose}): R={off[-1]}, logits max-abs error {err:.2e}")
+
+
+@pytest.mark.parametrize("hw,L0", [(48, 1), (88, 0), (128, 1)])
+def test_fp32_attention_query_groups_and_key_tiles(hw, L0):
+    """fp32 attention at T = 37, 122 and 257 tokens: one to three groups of 128 queries, the last key tile full, cut short and with one key."""
+    cfg, w, frames, off, ids = synth.make_small_case(700 + hw, dtype=synth.DT_F32, targets=15, L=2, F=2, r=4, max_set=2, n_adapters=3, hw=hw, patch=8)
+    compare(cfg, w, frames, off, ids, L0, K=cfg.n_adapters * cfg.C)

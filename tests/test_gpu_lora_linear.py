@@ -98,3 +98,19 @@ def test_deep_layer_shape_no_shared_inputs_full_compare():
     assert st == 0
     for b in range(0, 600, 100):
         check(Y[b:b + 100], oracle.lora_linear(case, s=0.5, b_begin=b, b_end=b + 100), synth.DT_BF16)
+
+
+@pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_BF16])
+@pytest.mark.parametrize("shape", [
+    dict(n_xblocks=1, T=1, Kdim=8, Ndim=1, n_adapters=1, r=1, per_block=1),              # one value
+    dict(n_xblocks=2, T=31, Kdim=40, Ndim=33, n_adapters=2, r=3, per_block=2),           # a k-tile cut short, N and rank not multiples of 4
+    dict(n_xblocks=40, T=7, Kdim=512, Ndim=96, n_adapters=5, r=16, per_block=1),         # five blocks in a 32-row subtile
+    dict(n_xblocks=3, T=65, Kdim=776, Ndim=132, n_adapters=3, r=64, per_block=3),        # 13 or 25 k-tiles over four waves, the last one ragged
+    dict(n_xblocks=2, T=300, Kdim=1536, Ndim=256, n_adapters=3, r=8, per_block=1),       # long contraction, few tiles: split over the waves
+    dict(n_xblocks=9, T=197, Kdim=768, Ndim=760, n_adapters=4, r=16, per_block=2),       # the same at the largest tile
+])
+def test_split_contraction_tiles(dtype, shape):
+    case = synth.make_lora_linear_case(dtype=dtype, seed=57, **shape)
+    Y, st = gpu_lora_linear(case, scale=0.75)
+    assert st == 0
+    check(Y, oracle.lora_linear(case, s=0.75), dtype)
