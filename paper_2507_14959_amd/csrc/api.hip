@@ -3,6 +3,7 @@
 
 namespace {
 
+
 inline size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 inline size_t elt_size(int dtype) { return dtype == POLY_BF16 ? 2 : 4; }
 inline int rank_pad(int r) { return (r + 15) / 16 * 16; }
@@ -23,8 +24,29 @@ struct ForwardWs {
     int32_t *frame_of_row, *adapter_of_row;
     float *xa, *xb;  // residual streams: per frame (shared layers), per row-block (adapted layers)
     void *u, *qkv, *o, *h, *S, *patches;
+    float *fl_x1, *fl_x2;
+    bf16_t *fl_qk, *fl_vt, *fl_o, *fl_h;                  // flow.hip, when a segment of the layers may take it
+    unsigned *fl_cnt[2];                    // its counters: shared layers, adapted layers
+    size_t fl_cnt_bytes;                    // of both
     size_t bytes;
 };
+
+// Segments of the layers (shared, adapted) that run as one launch of small tasks (flow.hip) instead of one or more launches per layer: up
+// to 140 tiles of 32 rows where the row kernel is the alternative, 320 where the GEMM path is (ranks it does not take, adapters on the
+// MLP, summed terms).  DeiT-tiny, twelve layers: 20 blocks of 197 tokens 482 against 491 us, 24 blocks 519 against 502; 64 blocks of 50
+// tokens 404 against 435, 96 blocks 532 against 462; summed terms on 32 blocks of 197 tokens 673 against 832, on 48 blocks 945 against 902.
+bool flow_fits(const poly_model_desc *m, int T, int blocks, bool adapted)
+{
+    const int r = adapted ? m->r : 0, tgt = adapted ? m->targets & 15 : 0;
+    if (m->dtype != POLY_BF16 || blocks <= 0 || !flow_supported(T, m->D, m->Dm, m->heads, r, tgt != 0)) return false;
+    const bool row_kernel = !(tgt & 12) && !(adapted && m->compose == POLY_COMPOSE_SUM && tgt) && rowlayer_supported(m->D, m->Dm, tgt ? r : 0);
+    return (long)blocks * ((T + 31) / 32) <= (row_kernel ? 140 : 320);
+}
+bool flow_shared(const poly_model_desc *m, int T, int F) { return m->L0 > 0 && flow_fits(m, T, F, false); }
+bool flow_adapted(const poly_model_desc *m, int T, int F, int R)
+{
+    return m->L0 < m->L && R > 0 && flow_fits(m, T, m->compose == POLY_COMPOSE_SUM ? F : R, true);
+}
 
 ForwardWs carve_forward(const poly_model_desc *m, int F, int R, void *base)
 {
@@ -43,6 +65,25 @@ ForwardWs carve_forward(const poly_model_desc *m, int F, int R, void *base)
     w.h = c.take<void>(es * rows * m->Dm);
     w.S = c.take<void>(es * (size_t)R * T * rank_pad(m->r));
     w.patches = c.take<void>(es * (size_t)F * (T - 1) * 3 * m->patch * m->patch);
+    const bool fs = flow_shared(m, (int)T, F), fa = flow_adapted(m, (int)T, F, R);
+    w.fl_x1 = w.fl_x2 = nullptr;
+    w.fl_qk = w.fl_vt = w.fl_o = w.fl_h = nullptr;
+    w.fl_cnt[0] = w.fl_cnt[1] = nullptr;
+    w.fl_cnt_bytes = 0;
+    if (fs || fa) {
+        const size_t na = m->compose == POLY_COMPOSE_SUM ? F : R;
+        const size_t ns = fs ? (size_t)F * m->L0 : 0, nd = fa ? na * (m->L - m->L0) : 0, nl = ns > nd ? ns : nd;   // blocks x layers
+        w.fl_qk = c.take<bf16_t>(es * nl * flow_elements((int)T, 2 * m->D));
+        w.fl_vt = c.take<bf16_t>(es * nl * flow_elements((int)T, m->D));
+        w.fl_o = c.take<bf16_t>(es * nl * flow_elements((int)T, m->D));
+        w.fl_h = c.take<bf16_t>(es * nl * flow_elements((int)T, m->Dm));
+        w.fl_x1 = c.take<float>(sizeof(float) * nl * T * m->D);
+        w.fl_x2 = c.take<float>(sizeof(float) * nl * T * m->D);
+        const size_t off0 = c.off;
+        if (fs) w.fl_cnt[0] = c.take<unsigned>(flow_counter_bytes(F, m->heads));
+        if (fa) w.fl_cnt[1] = c.take<unsigned>(flow_counter_bytes((int)na, m->heads));
+        w.fl_cnt_bytes = c.off - off0;
+    }
     w.bytes = c.off;
     return w;
 }
@@ -133,7 +174,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
     // tokens: x[f][0] = cls + pos[0]; x[f][1 + t] = patch_t W_pe + b_pe + pos[1 + t].  The same launch checks the CSR arrays and
     // builds the row maps (nothing before the first adapted layer needs them).
     POLY_TRY(launch_im2col(frames, w.patches, F, m->H, m->W, m->patch, dt, w.xa, base->cls, base->pos, T, D, out_merged,
-                           out_merged ? (size_t)F * K : 0, ss ? nullptr : row_offsets, adapter_ids, R, m->n_adapters, w.meta, w.frame_of_row,
+                           out_merged ? (size_t)F * K : 0, w.fl_cnt[0] ? w.fl_cnt[0] : w.fl_cnt[1], w.fl_cnt_bytes / 4, ss ? nullptr : row_offsets, adapter_ids, R, m->n_adapters, w.meta, w.frame_of_row,
                            w.adapter_of_row, dev_status, st));
     // The lagged loop: after the shared layers the base head scores the frames, Alg. 2 turns the scores of frame t - 1 into
     // the adapter set of frame t with its row maps -- all on this stream, no host in between.
@@ -156,9 +197,39 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         POLY_TRY(launch_gemm(g, dt, st));
     }
 
+    auto flow = [&](int l0, int l1, bool ad) -> int {
+        FlowArgs a = {};
+        a.T = T; a.D = D; a.Dm = Dm; a.heads = m->heads; a.layers = l1 - l0; a.eps = m->ln_eps;
+        a.nb = ad && !sum ? R : F;
+        a.nb_dev = !ad ? nullptr : (sum ? &w.meta->F_ok : R_dev);
+        a.x_in = w.xa; a.x = ad && !sum ? w.xb : w.xa;
+        a.in_map = ad && !sum ? w.frame_of_row : nullptr;
+        const size_t ld = (size_t)l0 * D, lm = (size_t)l0 * Dm, dd = (size_t)l0 * D * D, dm = (size_t)l0 * D * Dm;
+        a.ln1_g = base->ln1_g + ld; a.ln1_b = base->ln1_b + ld; a.ln2_g = base->ln2_g + ld; a.ln2_b = base->ln2_b + ld;
+        a.Wq = (const bf16_t *)base->qkv_w + 3 * dd; a.Wp = (const bf16_t *)base->proj_w + dd; a.W1 = (const bf16_t *)base->fc1_w + dm; a.W2 = (const bf16_t *)base->fc2_w + dm;
+        a.bq = base->qkv_b + 3 * ld; a.bp = base->proj_b + ld; a.b1 = base->fc1_b + lm; a.b2 = base->fc2_b + ld;
+        if (ad)
+            for (int t = 0; t < 4; ++t)
+                if (m->targets & (1 << t)) { a.At[t] = (const bf16_t *)lora->At[t]; a.Bt[t] = (const bf16_t *)lora->Bt[t]; }
+        a.n_adapters = m->n_adapters; a.r = m->r; a.scale = m->lora_scale; a.adapter_of_row = w.adapter_of_row;
+        a.set_off = ad && sum ? row_offsets : nullptr;
+        a.qk = w.fl_qk; a.vt = w.fl_vt; a.o = w.fl_o; a.h = w.fl_h; a.x1 = w.fl_x1; a.x2 = w.fl_x2;
+        a.counters = w.fl_cnt[ad ? 1 : 0];
+        return launch_flow(a, st);
+    };
+
     bool qkv_done = false;                     // the qkv linear of layer l was computed by layer l - 1's row kernel
     for (int l = 0; l < m->L; ++l) {
+        if (l == 0 && w.fl_cnt[0]) {
+            POLY_TRY(flow(0, m->L0, false));
+            l = m->L0;
+            if (l == m->L) break;
+        }
         if (l == m->L0 && !selected) POLY_TRY(select_now());
+        if (l == m->L0 && w.fl_cnt[1]) {
+            POLY_TRY(flow(m->L0, m->L, true));
+            break;
+        }
         const bool lora_on = l >= m->L0 && R > 0;
         if (l >= m->L0 && R == 0) break;
         // Summed composition: the frame stays ONE block through the adapted layers; its adapters' low-rank terms

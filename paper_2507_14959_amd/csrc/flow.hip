@@ -1,0 +1,705 @@
+// A stack of transformer layers on few token blocks in ONE launch: the workgroups take small tasks from a queue and a task starts as
+// soon as the tasks that it reads from are done.
+//
+// With a few blocks a layer is no work for this chip, only a chain of dependent steps: a launch per step costs three to five
+// microseconds (issue, dispatch, caches emptied at the boundary), and a kernel that keeps 64 rows to itself through a whole layer
+// (rowlayer.hip) leaves most CUs idle while the busy ones pull 885 KB of weights each through a 24 byte / clock load path.  Here a
+// layer is five steps
+//     Q  qkv = LayerNorm1(x) Wq + bq (+ low rank)      V is stored transposed, as the second product of attention reads it
+//     A  o = softmax(q k^T / 8) v                       one head, 32 queries
+//     P  x += o Wp + bp (+ low rank)
+//     1  h = GELU(LayerNorm2(x) W1 + b1 (+ low rank))
+//     2  x += h W2 + b2 (+ low rank)
+// each cut into tasks of 32 rows x 64 columns (A: 32 queries), so that one block of 197 tokens already gives 21 to 84 tasks a step.
+// The weights of a task are requested before its inputs are waited for.
+//
+// Passing data between XCDs, whose L2s do not see each other's writes, without fences (a device-scope release / acquire pair takes
+// 33 us here, a counted hand-over of 4 KB 1.0 to 2.0 us): results are stored at device scope (sc1: through to memory), the stores are
+// waited for, then the task is counted with an atomic; and every layer has buffers of its own, so that no address is read by this
+// launch before it has been written for good, and no L1 or L2 can hold an old copy of it.  Every 128-byte line is written by the tasks
+// of one counter only, so a line is complete when anything in it is read.  Loads are therefore ordinary ones, and the many tasks that
+// read the same rows hit the L2.  (With loads at device scope, past the L2, 8 frames read 58 MB per layer from memory.)
+//
+// Order and progress: a queue's tickets are numbered layer by layer and step by step, a task waits only for tasks with lower
+// numbers of the same queue, and a workgroup works through the tickets it has drawn in ascending order.  The lowest unfinished ticket
+// is therefore always being worked on by a running workgroup and waits for nothing, whatever other workgroups are not (yet) running:
+// every wait ends.
+//
+// What bounds it: the chain of a block.  DeiT-tiny, one frame: 14 us per layer (row kernel + attention: 35), of which the tasks' own
+// loads, products and stores are 11 and the hand-overs 3; whole forward 449 -> 203 us, lagged loop 466 -> 199 us.  With many blocks the
+// weights that every 32-row task pulls through its CU's load path bound it, and kernels with larger tiles take over (api.hip).
+#include "poly_dev.h"
+#include "rowtile.h"
+
+namespace {
+
+constexpr int FL_THREADS = 512;
+constexpr int FL_MAXQ = 8;             // queues
+constexpr int FL_SC1 = 16;             // cache policy bit of a buffer access: device scope
+constexpr float FL_LOG2E = 1.4426950408889634f;
+
+// counters of a block, 64 bytes apart: per row tile (8 of each) F2 done, A done, P done, F1 done, then per head Q done
+enum { C_F2 = 0, C_A = 8, C_P = 16, C_F1 = 24, C_Q = 32 };
+
+struct Div { unsigned d, m; };         // n / d, exact for n * d < 2^32
+__device__ __forceinline__ unsigned div(unsigned n, Div v) { return v.d == 1 ? n : __umulhi(n, v.m); }
+
+struct FlowParams {
+    FlowArgs a;
+    int nrt, ct_d, ct_m;               // row tiles per block; 64-column tiles of D and Dm
+    Div dQ, dA, dP, d1, drt;           // tasks per block of every step (F2: as P); row tiles
+    unsigned tpb;                      // tasks per block and layer
+    int nQ;                            // column tiles of a Q task
+    unsigned a_p2, a_1;                // tasks per row tile: P and F2; F1
+    unsigned ncnt;                     // counters per block
+    unsigned *queue, *cnt;
+};
+
+typedef unsigned u32x4_ __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2_ __attribute__((ext_vector_type(2)));
+
+// accesses to one block of a buffer (bounds-checked: reads past the end give 0, writes past it are dropped); stores at device scope
+struct Buf {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ Buf(const void *p, unsigned bytes) { r = __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, bytes, 0x00027000); }
+    __device__ __forceinline__ u32x4_ ld16(unsigned off) const { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0); }
+    __device__ __forceinline__ void st16(u32x4_ v, unsigned off) const { __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, FL_SC1); }
+    __device__ __forceinline__ void st8(u32x2_ v, unsigned off) const { __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, FL_SC1); }
+};
+
+__device__ __forceinline__ bf16x4 pack4(f32x4 v) { return bf16x4{(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]}; }
+
+// The kernel's arguments are read where they are used (a scalar load that hits the scalar cache): held in registers across the loop over
+// the tasks they would be five times what fits.
+typedef const __attribute__((address_space(4))) FlowParams *ParamPtr;
+__device__ __forceinline__ ParamPtr params()
+{
+    ParamPtr p = (ParamPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// The next ticket is drawn when this task's inputs are there: the answer arrives under the work, and no workgroup sits on a second
+// ticket while it waits for the inputs of its first.
+struct Task {
+    unsigned *queue, *next;            // ticket counter; thread 0's next ticket
+    unsigned layer;
+    int b, ct, rt;                     // block, 64-column tile (A: head), row tile
+    unsigned *cnt;                     // the block's counters
+};
+
+__device__ __forceinline__ void draw(const Task &t) 
+{
+    // (an increment: an addition of a uniform value would be rewritten for a whole wave, which waits for the answer on the spot)
+    *t.next = __builtin_amdgcn_atomic_inc32(t.queue, 0xffffffffu, __ATOMIC_RELAXED, "agent");
+}
+// a value that an earlier launch has written, at a wave-uniform address: through the scalar cache
+__device__ __forceinline__ int uload(const int *q) { return *(const int __attribute__((address_space(4))) *)(uintptr_t)q; }
+
+__device__ __forceinline__ unsigned *counter(const Task &t, int id) { return t.cnt + id * 16; }
+
+// Inputs ready?  The counter is read once before the weights are requested (answers come in order: behind them it would take a
+// microsecond longer), and again and again afterwards if it was too early.  By wave 0, for all: a barrier follows.
+__device__ __forceinline__ unsigned peek(const unsigned *c) { return __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void await(const unsigned *c, unsigned seen, unsigned want)
+{
+    while (seen < want) {
+        __builtin_amdgcn_s_sleep(1);
+        seen = peek(c);
+    }
+}
+
+// Fragment order of an activation matrix of ks K steps of 32 columns: [32 rows][16 rows][K step][lane][8], what a wave reads as the rows'
+// operand of a 16 x 16 x 32 product with one 1 KB load.  Byte offset of the four columns 16 c16 + 4 g .. of row 16 m + lm of row tile rt
+__device__ __forceinline__ unsigned frag_off(int rt, int m, int ks, int c16, int lm, int g)
+{
+    return ((rt * 2 + m) * ks + (c16 >> 1)) * 1024u + (((c16 & 1) * 2 + (g >> 1)) * 16 + lm) * 16 + (g & 1) * 8;
+}
+
+// ---- attention of one head on 32 queries: wave w takes the keys 32 w ..; returns the counter to raise
+template <int KD>
+__device__ __forceinline__ unsigned *attention_task(const Task &k, char *lds)
+{
+    constexpr int D = 32 * KD;
+    const ParamPtr p = params();
+    float *op = (float *)lds;                                  // partial outputs [wave][2][4][64 lanes] x 4
+    float *ml = op + 8 * 2048;                                 // [wave][32] maxima, [wave][32] sums
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lm = lane & 15, g = lane >> 4;
+    const int T = p->a.T, nrt = p->nrt, TP = nrt * 32;
+    if (wave == 0) await(counter(k, C_Q + k.ct), 0, (k.layer + 1) * (3 / p->nQ) * nrt);
+    __syncthreads();
+    const size_t slot = k.layer * (size_t)p->a.nb + k.b;
+    const Buf qk(p->a.qk + slot * TP * 2 * D, (unsigned)TP * 4 * D), vt(p->a.vt + slot * D * TP, (unsigned)D * TP * 2);
+    const unsigned hq = (unsigned)k.ct * TP * 128, hk = hq + (unsigned)D * TP * 2;   // bytes: this head's queries, keys (and values)
+    if (wave < nrt) {
+        u32x4_ qf[2][2], kf[2][2], vf[4];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                qf[i][ks] = qk.ld16(hq + ((2 * k.rt + i) * 2 + ks) * 1024 + lane * 16);
+                kf[i][ks] = qk.ld16(hk + ((2 * wave + i) * 2 + ks) * 1024 + lane * 16);
+            }
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) vf[dt] = vt.ld16(hq + (4 * wave + dt) * 1024 + lane * 16);
+        f32x4 s[2][2];                                         // [key subtile][query subtile]: keys 16 i + 4 g + e of query lm
+        const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                s[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[i][0]), __builtin_bit_cast(bf16x8, qf[j][0]), z4, 0, 0, 0);
+                s[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[i][1]), __builtin_bit_cast(bf16x8, qf[j][1]), s[i][j], 0, 0, 0);
+            }
+        const float sc = 0.125f * FL_LOG2E;
+        bf16x8 pf[2];
+        float mx[2], sum[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            float m = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (32 * wave + 16 * i + 4 * g + e >= T) s[i][j][e] = -INFINITY;
+                    m = fmaxf(m, s[i][j][e]);
+                }
+            m = fmaxf(m, __shfl_xor(m, 16, 64));
+            m = fmaxf(m, __shfl_xor(m, 32, 64));               // (the tile has a key inside T)
+            const float off = -m * sc;
+            float t = 0.f;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float pr = __builtin_amdgcn_exp2f(fmaf(s[i][j][e], sc, off));
+                    t += pr;
+                    pf[j][4 * i + e] = (bf16_t)pr;
+                }
+            t += __shfl_xor(t, 16, 64);
+            t += __shfl_xor(t, 32, 64);
+            mx[j] = m; sum[j] = t;
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt) {
+                const f32x4 o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf[dt]), pf[j], z4, 0, 0, 0);
+                *(f32x4 *)(op + ((wave * 2 + j) * 4 + dt) * 256 + lane * 4) = o;
+            }
+        if (g == 0) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) { ml[wave * 32 + 16 * j + lm] = mx[j]; ml[256 + wave * 32 + 16 * j + lm] = sum[j]; }
+        }
+    }
+    __syncthreads();
+    if (tid == 0) draw(k);
+    // wave (j, dt) brings its piece of the key tiles' partial outputs together
+    const int j = wave >> 2, dt = wave & 3;
+    float mw[8], M = -INFINITY, L = 0.f;
+    f32x4 ow[8], o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 8; ++w) {
+        const int v = min(w, nrt - 1);
+        mw[w] = ml[v * 32 + 16 * j + lm];
+        ow[w] = *(const f32x4 *)(op + ((v * 2 + j) * 4 + dt) * 256 + lane * 4);
+        M = fmaxf(M, mw[w]);
+    }
+#pragma unroll
+    for (int w = 0; w < 8; ++w) {
+        const float c = w < nrt ? __builtin_amdgcn_exp2f((mw[w] - M) * (0.125f * FL_LOG2E)) : 0.f;
+        L = fmaf(ml[256 + min(w, nrt - 1) * 32 + 16 * j + lm], c, L);
+        o += ow[w] * c;
+    }
+    const Buf ob(p->a.o + slot * TP * D, (unsigned)TP * D * 2);
+    ob.st8(__builtin_bit_cast(u32x2_, pack4(o * (1.0f / L))), frag_off(k.rt, j, KD, k.ct * 4 + dt, lm, g));
+    return counter(k, C_A + k.rt);
+}
+
+// ---- LayerNorm + linear on 32 rows x NT tiles of 64 columns; STAGE: 0 Q, 3 F1.  The normalised rows go through LDS; wave (kh, wc)
+// takes half kh of the contraction for the 16 columns 16 wc .. of a tile, both row halves; returns the counter to raise
+template <int KD, int STAGE, int NT, bool SUM>
+__device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
+{
+    constexpr int D = 32 * KD, KT = KD / 2, HK = KD / 2;       // HK: K steps of a wave
+    constexpr int NA = (KD + 3) / 4;                           // K steps of a wave's share of the shrink
+    bf16_t *As = (bf16_t *)lds;                                // rows: 32 x D, 16-byte chunks swizzled by row
+    char *red = lds + 32 * D * 2;                              // partial sums that the halves of K hand over: NT x 8 KB
+    char *shr = red + NT * 8192;                               // shrink [quarter of K][row half][rank tile][lane]: 16 KB
+    const ParamPtr p = params();
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lm = lane & 15, g = lane >> 4;
+    const int kh = wave >> 2, wc = wave & 3, T = p->a.T, t0 = k.rt * 32, b = k.b;
+    const size_t ld = k.layer;
+    const unsigned *dep = counter(k, (STAGE == 0 ? C_F2 : C_P) + k.rt);
+    const unsigned want = (k.layer + (STAGE == 0 ? 0 : 1)) * p->a_p2;
+    unsigned seen = 0;
+    if (wave == 0) seen = peek(dep);
+    const int N = STAGE == 0 ? 3 * D : p->a.Dm, dt = p->ct_d;
+    // tile i of the task: q, k and v of one head, or neighbours
+    auto tile = [&](int i) { return STAGE == 0 ? k.ct + i * dt : k.ct * NT + i; };
+    auto is_v = [&](int i) { return STAGE == 0 && tile(i) >= 2 * dt; };            // V: product untransposed
+    const bf16_t *W = (STAGE == 0 ? p->a.Wq : p->a.W1) + ld * N * D + (size_t)(wc * 16 + lm) * D + kh * HK * 32 + 8 * g;
+    const float *bias = (STAGE == 0 ? p->a.bq : p->a.b1) + ld * N + wc * 16;
+    bf16x8 wf[NT][HK];
+    f32x4 bias4[NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+#pragma unroll
+        for (int j = 0; j < HK; ++j) wf[i][j] = *(const bf16x8 *)(W + (size_t)tile(i) * 64 * D + 32 * j);
+    }
+    constexpr bool LEAN = NT > 2;                              // gains and biases are requested later: registers
+    auto load_bias = [&]() {
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const float *bp = bias + tile(i) * 64;
+            if (is_v(i)) { const float bv = bp[lm]; bias4[i] = f32x4{bv, bv, bv, bv}; }
+            else bias4[i] = *(const f32x4 *)(bp + 4 * g);
+        }
+    };
+    if (!LEAN) load_bias();
+    const int row = tid >> 4, part = tid & 15, rrow = min(t0 + row, T - 1);
+    const float *gain = (STAGE == 0 ? p->a.ln1_g : p->a.ln2_g) + ld * D + 4 * part, *shift = (STAGE == 0 ? p->a.ln1_b : p->a.ln2_b) + ld * D + 4 * part;
+    f32x4 gn[KT], sh[KT];
+    auto load_gain = [&]() {
+#pragma unroll
+        for (int i = 0; i < KT; ++i) { gn[i] = *(const f32x4 *)(gain + 64 * i); sh[i] = *(const f32x4 *)(shift + 64 * i); }
+    };
+    if (!LEAN) load_gain();
+    // operands of the low-rank terms of this block's adapter(s); those of the first one are requested here
+    constexpr int TGT = STAGE == 0 ? 0 : 2;
+    const bf16_t *At = p->a.At[TGT], *Bt = p->a.Bt[TGT];
+    const int *set_off = p->a.set_off, *adapter = p->a.adapter_of_row, *in_map = p->a.in_map;
+    const int s0 = At ? (SUM ? uload(set_off + b) : b) : 0, s1 = At ? (SUM ? uload(set_off + b + 1) : b + 1) : 0;
+    const int r = p->a.r, nrk = (r + 15) >> 4;
+    const bf16x4 z4 = {0, 0, 0, 0};
+    bf16x8 fat[NA][2];
+    auto load_at = [&](int s) {
+        const bf16_t *Ak = At + (p->a.n_adapters * ld + uload(adapter + s)) * r * D + 8 * g;
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int kk = min(wc + 4 * i, KD - 1);
+            fat[i][0] = *(const bf16x8 *)(Ak + (size_t)min(lm, r - 1) * D + 32 * kk);
+            if (nrk > 1) fat[i][1] = *(const bf16x8 *)(Ak + (size_t)min(16 + lm, r - 1) * D + 32 * kk);
+        }
+    };
+    bf16x8 fb[NT];
+    auto load_bt = [&](int s) {                                // ranks 4 g .. and 16 + 4 g .. of a column
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const bf16_t *bt = Bt + ((p->a.n_adapters * ld + uload(adapter + s)) * N + tile(i) * 64 + wc * 16 + lm) * r + 4 * g;
+            bf16x4 lo = *(const bf16x4 *)(bt + min(0, r - 4 - 4 * g)), hi = z4;
+            if (4 * g >= r) lo = z4;
+            if (nrk > 1) {
+                hi = *(const bf16x4 *)(bt + min(16, r - 4 - 4 * g));
+                if (16 + 4 * g >= r) hi = z4;
+            }
+            fb[i] = bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        }
+    };
+    if (s0 < s1) { load_at(s0); load_bt(s0); }
+    const bool first = STAGE == 0 && k.layer == 0;             // the stream still lies where the caller put it
+    const int xblk = first && in_map ? uload(in_map + b) : b;
+    const size_t step = (size_t)p->a.nb * T * D;
+    const float *xs = STAGE == 3 ? p->a.x1 + ld * step : first ? p->a.x_in : p->a.x2 + (ld - 1) * step;
+    const Buf xb(xs + (size_t)xblk * T * D, (unsigned)T * D * 4);
+    // ---- inputs
+    if (wave == 0) await(dep, seen, want);
+    __syncthreads();
+    {
+        f32x4 v[KT];
+#pragma unroll
+        for (int i = 0; i < KT; ++i) v[i] = __builtin_bit_cast(f32x4, xb.ld16(((unsigned)rrow * D + 4 * (part + 16 * i)) * 4));
+        if (LEAN) load_gain();
+        float t = 0.f;
+#pragma unroll
+        for (int i = 0; i < KT; ++i) t += v[i][0] + v[i][1] + v[i][2] + v[i][3];
+        const float mean = row16_sum(t) * (1.0f / D);
+        float q = 0.f;
+#pragma unroll
+        for (int i = 0; i < KT; ++i)
+#pragma unroll
+            for (int z = 0; z < 4; ++z) { const float d = v[i][z] - mean; q = fmaf(d, d, q); }
+        const float inv = rsqrtf(row16_sum(q) * (1.0f / D) + p->a.eps), nmi = -mean * inv;
+#pragma unroll
+        for (int i = 0; i < KT; ++i) {
+            f32x4 o;
+#pragma unroll
+            for (int z = 0; z < 4; ++z) o[z] = fmaf(fmaf(v[i][z], inv, nmi), gn[i][z], sh[i][z]);
+            const int c = 4 * (part + 16 * i);
+            *(bf16x4 *)(As + row * D + (((c >> 3) ^ (row & 7)) << 3) + (c & 4)) = pack4(o);
+        }
+    }
+    __syncthreads();
+    if (tid == 0) draw(k);
+    // fragment of rows 16 m + lm, K step i: chunk 4 i + g
+    auto frag_a = [&](int m, int i) { return *(const bf16x8 *)(As + (16 * m + lm) * D + (((4 * i + g) ^ (lm & 7)) << 3)); };
+    // the shrink is shared by the waves (row half kh, K steps wc, wc + 4), the partial sums meet in LDS, and ranks 4 g .. and 16 + 4 g ..
+    // of row lm are what a lane feeds to the expand
+    auto shrink_part = [&]() {
+        f32x4 sp[2] = {};
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+            if (wc + 4 * i < KD) {
+                const bf16x8 fa = frag_a(kh, wc + 4 * i);
+                sp[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fat[i][0], fa, sp[0], 0, 0, 0);
+                if (nrk > 1) sp[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fat[i][1], fa, sp[1], 0, 0, 0);
+            }
+        *(f32x4 *)(shr + (((wc * 2 + kh) * 2 + 0) * 64 + lane) * 16) = sp[0];
+        if (nrk > 1) *(f32x4 *)(shr + (((wc * 2 + kh) * 2 + 1) * 64 + lane) * 16) = sp[1];
+    };
+    auto shrink_sum = [&]() {
+        bf16x8 fs = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (q < nrk) {
+                f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int w = 0; w < 4; ++w) t += *(const f32x4 *)(shr + (((w * 2 + kh) * 2 + q) * 64 + lane) * 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) fs[4 * q + e] = (bf16_t)(t[e] * p->a.scale);
+            }
+        return fs;
+    };
+    if (s0 < s1) shrink_part();
+    f32x4 y[NT];                                               // the row half that this wave finishes: 16 kh ..
+    {
+        bf16x8 fa[2][HK];
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int j = 0; j < HK; ++j) fa[m][j] = frag_a(m, kh * HK + j);
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+            for (int j = 0; j < HK; ++j)
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const bf16x8 u = is_v(i) ? fa[m][j] : wf[i][j], v = is_v(i) ? wf[i][j] : fa[m][j];
+                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(u, v, acc[m], 0, 0, 0);
+                }
+            *(f32x4 *)(red + ((i * 8 + wave) * 64 + lane) * 16) = kh ? acc[0] : acc[1];
+            y[i] = kh ? acc[1] : acc[0];
+        }
+    }
+    if (LEAN) load_bias();
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+        const f32x4 other = *(const f32x4 *)(red + ((i * 8 + (wave ^ 4)) * 64 + lane) * 16);
+        y[i] = kh ? other + y[i] : y[i] + other;
+    }
+    for (int s = s0; s < s1; ++s) {
+        if (SUM && s > s0) {                                   // further terms summed on this block
+            load_at(s); load_bt(s);
+            __syncthreads();
+            shrink_part();
+            __syncthreads();
+        }
+        const bf16x8 fs = shrink_sum();
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const bf16x8 u = is_v(i) ? fs : fb[i], v = is_v(i) ? fb[i] : fs;
+            y[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(u, v, y[i], 0, 0, 0);
+        }
+        if (!SUM) break;
+    }
+    const size_t slot = ld * p->a.nb + b;
+    const int TP = p->nrt * 32;
+    // q and k as [head][16 rows][32 columns][lane][8], v as [head][32 rows][16 columns][lane][rows 4 g .., 16 + 4 g ..]: attention
+    // reads 1 KB per instruction (rows past T repeat row T - 1: finite, and masked there)
+    const Buf vt(p->a.vt + slot * D * TP, (unsigned)D * TP * 2), qk(p->a.qk + slot * TP * 2 * D, (unsigned)TP * 4 * D), hb(p->a.h + slot * TP * N, (unsigned)TP * N * 2);
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+        const int ct = tile(i);
+        const f32x4 v = y[i] + bias4[i];
+        if (STAGE == 3) hb.st8(__builtin_bit_cast(u32x2_, pack4(gelu_poly4(v))), frag_off(k.rt, kh, N / 32, ct * 4 + wc, lm, g));
+        else if (is_v(i)) vt.st8(__builtin_bit_cast(u32x2_, pack4(v)), (unsigned)(ct - 2 * dt) * TP * 128 + (4 * k.rt + wc) * 1024 + lane * 16 + kh * 8);
+        else qk.st8(__builtin_bit_cast(u32x2_, pack4(v)), (unsigned)ct * TP * 128 + frag_off(k.rt, kh, 2, wc, lm, g));
+    }
+    return counter(k, STAGE == 0 ? C_Q + (k.ct < dt ? k.ct : k.ct < 2 * dt ? k.ct - dt : k.ct - 2 * dt) : C_F1 + k.rt);
+}
+
+// ---- linear + residual on 32 rows x NT tiles of 32 columns; STAGE: 2 P, 4 F2.  Wave w takes the K steps w, w + 8, .. of the whole tile,
+// both operands straight from memory in fragment order, and the partial sums meet in LDS; returns the counter to raise
+template <int KD, int CH, int STAGE, int NT, bool SUM>
+__device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
+{
+    constexpr int D = 32 * KD, KS = STAGE == 4 ? CH : KD, NS = (KS + 7) / 8;      // K steps of a wave
+    static_assert(NT <= 2, "waves 0 - 3 and 4 - 7 finish a tile each");
+    char *red = lds, *shr = lds + 32768;                       // [tile][wave][row half][column half][lane]; [wave][row half][rank tile][lane]
+    const ParamPtr p = params();
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lm = lane & 15, g = lane >> 4;
+    const int T = p->a.T, TP = p->nrt * 32, b = k.b;
+    const size_t ld = k.layer;
+    const unsigned *dep = counter(k, (STAGE == 2 ? C_A : C_F1) + k.rt);
+    const unsigned want = (k.layer + 1) * (STAGE == 2 ? p->a.heads : p->a_1);
+    unsigned seen = 0;
+    if (wave == 0) seen = peek(dep);
+    const int K = STAGE == 4 ? p->a.Dm : D, ks = K / 32, np = min(ks, 8);
+    const bf16_t *W = (STAGE == 2 ? p->a.Wp : p->a.W2) + (ld * D + k.ct * NT * 32 + lm) * K + 8 * g;
+    bf16x8 wf[NT][NS][2];
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+#pragma unroll
+            for (int n = 0; n < 2; ++n) wf[j][i][n] = *(const bf16x8 *)(W + (size_t)(j * 32 + 16 * n) * K + 32 * min(wave + 8 * i, ks - 1));
+    // waves 4 j .. 4 j + 3 finish the subtiles of tile j: rows 16 fm .., columns 16 fn ..
+    const int fm = (wave >> 1) & 1, fn = wave & 1, trow = k.rt * 32 + 16 * fm + lm, fcol = (k.ct * NT + (wave >> 2)) * 32 + 16 * fn;
+    const bool fin = wave < 4 * NT;
+    const f32x4 bias4 = *(const f32x4 *)((STAGE == 2 ? p->a.bp : p->a.b2) + ld * D + (fin ? fcol : 0) + 4 * g);
+    constexpr int TGT = STAGE == 2 ? 1 : 3;
+    const bf16_t *At = p->a.At[TGT], *Bt = p->a.Bt[TGT];
+    const int *set_off = p->a.set_off, *adapter = p->a.adapter_of_row, *in_map = p->a.in_map;
+    const int s0 = At ? (SUM ? uload(set_off + b) : b) : 0, s1 = At ? (SUM ? uload(set_off + b + 1) : b + 1) : 0;
+    const int r = p->a.r, nrk = (r + 15) >> 4;
+    const bf16x4 z4 = {0, 0, 0, 0};
+    bf16x8 fat[2];                                             // of one K step
+    auto load_at = [&](int s, int i) {
+        const bf16_t *Ak = At + (p->a.n_adapters * ld + uload(adapter + s)) * r * K + 32 * min(wave + 8 * i, ks - 1) + 8 * g;
+        fat[0] = *(const bf16x8 *)(Ak + (size_t)min(lm, r - 1) * K);
+        if (nrk > 1) fat[1] = *(const bf16x8 *)(Ak + (size_t)min(16 + lm, r - 1) * K);
+    };
+    bf16x8 fb;
+    auto load_bt = [&](int s) {
+        const bf16_t *bt = Bt + ((p->a.n_adapters * ld + uload(adapter + s)) * D + (fin ? fcol : 0) + lm) * r + 4 * g;
+        bf16x4 lo = *(const bf16x4 *)(bt + min(0, r - 4 - 4 * g)), hi = z4;
+        if (4 * g >= r) lo = z4;
+        if (nrk > 1) {
+            hi = *(const bf16x4 *)(bt + min(16, r - 4 - 4 * g));
+            if (16 + 4 * g >= r) hi = z4;
+        }
+        fb = bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    };
+    if (s0 < s1) { load_at(s0, 0); load_bt(s0); }
+    const bool first = STAGE == 2 && k.layer == 0;
+    const int xblk = first && in_map ? uload(in_map + b) : b;
+    const size_t step = (size_t)p->a.nb * T * D, slot = ld * p->a.nb + b;
+    const float *xs = STAGE == 4 ? p->a.x1 + ld * step : first ? p->a.x_in : p->a.x2 + (ld - 1) * step;
+    float *xd = STAGE == 2 ? p->a.x1 + ld * step : (int)k.layer + 1 == p->a.layers ? p->a.x : p->a.x2 + ld * step;
+    const Buf xi(xs + (size_t)xblk * T * D, (unsigned)T * D * 4), xo(xd + (size_t)b * T * D, (unsigned)T * D * 4);
+    const Buf src((STAGE == 2 ? p->a.o : p->a.h) + slot * TP * K, (unsigned)TP * K * 2);
+    // ---- inputs
+    if (wave == 0) await(dep, seen, want);
+    __syncthreads();
+    bf16x8 fa[NS][2];
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+            fa[i][m] = __builtin_bit_cast(bf16x8, src.ld16(((k.rt * 2 + m) * ks + min(wave + 8 * i, ks - 1)) * 1024 + lane * 16));
+    const unsigned xoff = ((unsigned)min(trow, T - 1) * D + (fin ? fcol : 0) + 4 * g) * 4;
+    const f32x4 res = __builtin_bit_cast(f32x4, xi.ld16(xoff));
+    auto shrink_part = [&](int s) {                            // (K step 0 of the term is in registers)
+        f32x4 sp[2][2] = {};
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+            if (wave + 8 * i < ks) {
+                if (i) load_at(s, i);
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    sp[m][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fat[0], fa[i][m], sp[m][0], 0, 0, 0);
+                    if (nrk > 1) sp[m][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fat[1], fa[i][m], sp[m][1], 0, 0, 0);
+                }
+            }
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            *(f32x4 *)(shr + (((wave * 2 + m) * 2 + 0) * 64 + lane) * 16) = sp[m][0];
+            if (nrk > 1) *(f32x4 *)(shr + (((wave * 2 + m) * 2 + 1) * 64 + lane) * 16) = sp[m][1];
+        }
+    };
+    auto shrink_sum = [&]() {
+        bf16x8 fs = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (q < nrk) {
+                f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int w = 0; w < 8; ++w) {
+                    const f32x4 u = *(const f32x4 *)(shr + (((min(w, np - 1) * 2 + fm) * 2 + q) * 64 + lane) * 16);
+                    if (w < np) t += u;
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) fs[4 * q + e] = (bf16_t)(t[e] * p->a.scale);
+            }
+        return fs;
+    };
+    bf16x8 fs1 = {0, 0, 0, 0, 0, 0, 0, 0};                     // the first term's
+    if (s0 < s1) shrink_part(s0);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        if (j == 1 && s0 < s1) {                               // (the second tile takes the place of the shrink's partial sums)
+            __syncthreads();
+            fs1 = shrink_sum();
+            __syncthreads();
+        }
+        f32x4 acc[2][2] = {};
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+            if (wave + 8 * i < ks) {
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+#pragma unroll
+                    for (int n = 0; n < 2; ++n) acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j][i][n], fa[i][m], acc[m][n], 0, 0, 0);
+            }
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int n = 0; n < 2; ++n) *(f32x4 *)(red + j * 32768 + (((wave * 2 + m) * 2 + n) * 64 + lane) * 16) = acc[m][n];
+    }
+    __syncthreads();
+    if (tid == 0) draw(k);
+    f32x4 y = {0.f, 0.f, 0.f, 0.f};
+    if (fin) {
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {
+            const f32x4 t = *(const f32x4 *)(red + (wave >> 2) * 32768 + (((min(w, np - 1) * 2 + fm) * 2 + fn) * 64 + lane) * 16);
+            if (w < np) y += t;
+        }
+    }
+    for (int s = s0; s < s1; ++s) {
+        if (SUM && s > s0) {                                   // further terms summed on this block
+            load_at(s, 0); load_bt(s);
+            __syncthreads();
+            shrink_part(s);
+            __syncthreads();
+            fs1 = shrink_sum();
+        } else if (NT == 1) {
+            fs1 = shrink_sum();
+        }
+        y = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb, fs1, y, 0, 0, 0);
+        if (!SUM) break;
+    }
+    if (fin && trow < T) xo.st16(__builtin_bit_cast(u32x4_, y + bias4 + res), xoff);
+    return counter(k, (STAGE == 2 ? C_P : C_F2) + k.rt);
+}
+
+// KD: K steps of 32 in the model width.  CH: K steps at most in the hidden width
+template <int KD, int CH, int NQ, int N1, int NP, bool SUM>
+__global__ __launch_bounds__(FL_THREADS, 4) void flow_kernel(const FlowParams)
+{
+    extern __shared__ __attribute__((aligned(16))) char fl_lds[];
+    __shared__ unsigned s_ticket;
+    const int tid = threadIdx.x;
+    int nb, nq;
+    {
+        const ParamPtr p = params();
+        const int *nb_dev = p->a.nb_dev;
+        nb = p->a.nb; nq = p->a.n_queues;
+        if (nb_dev) nb = min(uload(nb_dev), nb);
+    }
+    if (nb <= 0) return;
+    for (int qi = 0; qi < nq; ++qi) {
+        const int qn = ((int)blockIdx.x + qi) % nq;
+        const int nbq = nb > qn ? (nb - qn + nq - 1) / nq : 0; // blocks of this queue: qn, qn + nq, ..
+        if (nbq == 0) continue;
+        unsigned *qc = params()->queue + qn * 16;
+        if (tid == 0) s_ticket = __hip_atomic_fetch_add(qc, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        unsigned ticket = __builtin_amdgcn_readfirstlane(s_ticket), layer = 0, lbase = 0;
+        for (;;) {
+            const ParamPtr p = params();
+            const unsigned tpl = nbq * p->tpb;
+            while (ticket >= lbase + tpl) { lbase += tpl; ++layer; }
+            if (layer >= (unsigned)p->a.layers) break;
+            // ---- which task
+            unsigned rem = ticket - lbase, bi;
+            int stage = 0;
+            const Div dQ = {p->dQ.d, p->dQ.m}, dA = {p->dA.d, p->dA.m}, dP = {p->dP.d, p->dP.m}, d1 = {p->d1.d, p->d1.m};
+            if (rem < nbq * dQ.d) bi = div(rem, dQ), rem -= bi * dQ.d;
+            else if ((rem -= nbq * dQ.d) < nbq * dA.d) stage = 1, bi = div(rem, dA), rem -= bi * dA.d;
+            else if ((rem -= nbq * dA.d) < nbq * dP.d) stage = 2, bi = div(rem, dP), rem -= bi * dP.d;
+            else if ((rem -= nbq * dP.d) < nbq * d1.d) stage = 3, bi = div(rem, d1), rem -= bi * d1.d;
+            else rem -= nbq * d1.d, stage = 4, bi = div(rem, dP), rem -= bi * dP.d;
+            Task k;
+            unsigned next = 0;
+            k.queue = qc; k.next = &next;
+            k.layer = layer;
+            k.ct = div(rem, Div{p->drt.d, p->drt.m}); k.rt = rem - k.ct * p->nrt; k.b = qn + bi * nq;
+            k.cnt = p->cnt + (size_t)k.b * p->ncnt * 16;
+            unsigned *done;
+            if (stage == 0) done = norm_task<KD, 0, NQ, SUM>(k, fl_lds);
+            else if (stage == 1) done = attention_task<KD>(k, fl_lds);
+            else if (stage == 2) done = resid_task<KD, CH, 2, NP, SUM>(k, fl_lds);
+            else if (stage == 3) done = norm_task<KD, 3, N1, SUM>(k, fl_lds);
+            else done = resid_task<KD, CH, 4, NP, SUM>(k, fl_lds);
+            // ---- done: every wave's stores have reached device scope, then the task is counted
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (tid == 0) s_ticket = next;
+            __syncthreads();
+            if (tid == 0) __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            ticket = __builtin_amdgcn_readfirstlane(s_ticket);
+        }
+        __syncthreads();                                       // (s_ticket is written again for the next queue)
+    }
+}
+
+Div make_div(unsigned d) { return Div{d, d == 1 ? 0u : (unsigned)((0x100000000ull + d - 1) / d)}; }
+
+template <int KD, int NQ, int N1, int NP, bool SUM> int launch_flow_t(FlowParams &p, hipStream_t st)
+{
+    constexpr int LDS = 8 * 8192 + 2048;                       // attention's partial outputs; two workgroups per CU
+    static_assert(LDS >= 32 * 32 * KD * 2 + (NQ > N1 ? NQ : N1) * 8192 + 16384 && LDS >= 65536 && 2 * LDS <= 160 * 1024 - 128, "LDS budget");
+    const FlowArgs &a = p.a;
+    const int nrt = p.nrt;
+    p.nQ = NQ;
+    p.dQ = make_div(nrt * 3 * p.ct_d / NQ); p.dA = make_div(nrt * a.heads); p.dP = make_div(nrt * 2 * p.ct_d / NP); p.d1 = make_div(nrt * p.ct_m / N1);
+    p.drt = make_div(nrt);
+    p.tpb = p.dQ.d + p.dA.d + 2 * p.dP.d + p.d1.d;
+    p.a_p2 = 2 * p.ct_d / NP; p.a_1 = p.ct_m / N1;
+    // one workgroup per CU while that gives every block of a queue 32 of them or more, else two (8 blocks 314 / 338 us, 12 blocks 414 / 408)
+    const long all = (long)p.tpb * a.nb, most = a.nb <= FL_MAXQ ? 256 : 512;
+    auto kern = flow_kernel<KD, 24, NQ, N1, NP, SUM>;
+    static bool attr_set = false;   // raising the dynamic LDS limit is a per-kernel, process-wide setting
+    if (!attr_set) {
+        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS) != hipSuccess) return POLY_EHIP;
+        attr_set = true;
+    }
+    POLY_LAUNCH_SHMEM(POLY_STAGE_GEMM, kern, dim3((unsigned)(all < most ? all : most)), dim3(FL_THREADS), LDS, st, p);
+    return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
+}
+
+template <int KD, int NQ, int N1, int NP> int launch_flow_n(FlowParams &p, hipStream_t st)
+{
+    return p.a.set_off ? launch_flow_t<KD, NQ, N1, NP, true>(p, st) : launch_flow_t<KD, NQ, N1, NP, false>(p, st);
+}
+
+template <int KD> int launch_flow_d(FlowParams &p, hipStream_t st)
+{
+    // Coarse tasks (all three tiles of a head, four of the hidden width, two of the output) load the rows and hand over once for several
+    // tiles, but a stage of one block is then 21 tasks: better from five blocks on (1 block 203 / 232 us, 4 blocks 248 / 256, 6 blocks
+    // 295 / 256, 16 blocks 436 / 416 for the twelve layers of DeiT-tiny, fine / coarse)
+    if (p.a.nb > 4 && p.ct_m % 4 == 0) return launch_flow_n<KD, 3, 4, 2>(p, st);
+    return launch_flow_n<KD, 1, 2, 1>(p, st);
+}
+
+}  // namespace
+
+bool flow_supported(int T, int D, int Dm, int heads, int r, bool lora)
+{
+    if (!(D == 64 || D == 128 || D == 192) || Dm % 128 || Dm > 768 || D != heads * 64 || T > 224 || T <= 0) return false;
+    return !lora || (r % 4 == 0 && r <= 32);
+}
+
+size_t flow_counter_bytes(int nb, int heads) { return 64 * (size_t)(FL_MAXQ + (size_t)nb * (C_Q + heads)); }
+size_t flow_elements(int T, int D) { return (size_t)D * ((T + 31) / 32 * 32); }
+
+int launch_flow(const FlowArgs &args, hipStream_t st)
+{
+    if (args.nb <= 0 || args.layers <= 0) return POLY_OK;
+    FlowParams p;
+    p.a = args;
+    const int nrt = (args.T + 31) / 32;
+    p.nrt = nrt; p.ct_d = args.D / 64; p.ct_m = args.Dm / 64;
+    p.a.n_queues = args.nb < FL_MAXQ ? args.nb : FL_MAXQ;
+    p.ncnt = C_Q + args.heads;
+    p.queue = args.counters;
+    p.cnt = args.counters + FL_MAXQ * 16;
+    switch (args.D) {
+    case 64: return launch_flow_d<2>(p, st);
+    case 128: return launch_flow_d<4>(p, st);
+    case 192: return launch_flow_d<6>(p, st);
+    default: return POLY_EINVAL;
+    }
+}

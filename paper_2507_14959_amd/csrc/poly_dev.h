@@ -250,6 +250,34 @@ bool rowlayer_supported(int D, int Dm, int r);
 int launch_rowlayer(const RowLayerArgs &a, hipStream_t st);
 int launch_rowlin(const RowLinArgs &a, hipStream_t st);
 
+// A run of whole layers on few blocks in one launch (flow.hip); bf16, D <= 192.  Weight pointers are those of the first layer of the
+// run, one layer of a stack behind the other.
+struct FlowArgs {
+    int T, D, Dm, heads, layers;
+    int nb;                          // upper bound of the number of blocks
+    const int *nb_dev;               // true count on the device, or null
+    float eps;
+    const float *x_in;               // residual stream into the first layer: block in_map[b] (null: b) of [..][T][D]
+    const int *in_map;
+    float *x;                        // [nb][T][D]: the residual stream after the last layer (may be x_in)
+    float *x1, *x2;                  // [layers][nb][T][D]: after proj, and [layers - 1][nb][T][D]: after the layer
+    const float *ln1_g, *ln1_b, *ln2_g, *ln2_b;
+    const bf16_t *Wq, *Wp, *W1, *W2;
+    const float *bq, *bp, *b1, *b2;
+    const bf16_t *At[4], *Bt[4];     // adapter stacks of qkv, proj, fc1, fc2; null = none
+    int n_adapters, r;
+    float scale;
+    const int *adapter_of_row;
+    const int *set_off;              // null: block b has the one term adapter_of_row[b]; else the sum of the terms [set_off[b], set_off[b + 1])
+    bf16_t *qk, *vt, *o, *h;         // [layers][nb][flow_elements(T, ..)] of 2 D, D, D and Dm
+    unsigned *counters;              // flow_counter_bytes, cleared by an earlier launch
+    int n_queues;                    // set by launch_flow
+};
+bool flow_supported(int T, int D, int Dm, int heads, int r, bool lora);
+size_t flow_counter_bytes(int nb, int heads);
+size_t flow_elements(int T, int D);
+int launch_flow(const FlowArgs &a, hipStream_t st);
+
 // y = LayerNorm(x) row-wise; x float [n*T][D] -> elt [n*T][D]
 int launch_layernorm(const float *x, void *y, const float *gain, const float *shift, int D, float eps, int T,
                      int n_blocks, const int *n_blocks_dev, int dtype, hipStream_t st);
@@ -279,10 +307,10 @@ int launch_select(const float *label_scores, int F, int K, const uint8_t *group_
 // ---- bookkeeping and row-wise stages (rowops.hip) ----
 int launch_prep(const int32_t *row_offsets, const int32_t *adapter_ids, int F, int R_cap, int n_adapters, PolyMeta *meta,
                 int32_t *frame_of_row, int32_t *adapter_of_row, int32_t *dev_status, hipStream_t st);
-// patches <- frames (im2col), x[f][0][:] <- cls + pos[0], merged[0 .. n_merged) <- 0; and, when row_offsets is given, the work of
+// patches <- frames (im2col), x[f][0][:] <- cls + pos[0], merged[0 .. n_merged) <- 0, zero[0 .. n_zero) <- 0; and, when row_offsets is given, the work of
 // launch_prep as one more block of the same launch
 int launch_im2col(const void *frames, void *patches, int F, int H, int W, int p, int dtype, float *x, const float *cls, const float *pos,
-                  int T_tok, int D, float *merged, size_t n_merged, const int32_t *row_offsets, const int32_t *adapter_ids, int R_cap,
+                  int T_tok, int D, float *merged, size_t n_merged, unsigned *zero, size_t n_zero, const int32_t *row_offsets, const int32_t *adapter_ids, int R_cap,
                   int n_adapters, PolyMeta *meta, int32_t *frame_of_row, int32_t *adapter_of_row, int32_t *dev_status, hipStream_t st);
 // base head of the lagged loop: scores of frame f -> lag[f + 1][K] and out[f][K] (nullable); lag[0] = carry (or zeros)
 int launch_base_head(const float *x, int T, int D, const float *gain, const float *shift, float eps, const void *Wb, const float *bb,

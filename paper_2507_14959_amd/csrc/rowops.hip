@@ -57,7 +57,7 @@ struct PrepArgs {       // the CSR check as the last block of another launch (ro
 // rows x[f][0][:] = cls + pos[0] and clears the merged-score buffer (both are needed much later: two launches less).
 template <typename T, int VEC>
 __global__ void im2col_kernel(const T *frames, T *patches, int F, int H, int W, int p, float *x, const float *cls, const float *pos,
-                              int T_tok, int D, float *merged, size_t n_merged, const PrepArgs pa)
+                              int T_tok, int D, float *merged, size_t n_merged, unsigned *zero, size_t n_zero, const PrepArgs pa)
 {
     const int nblk = pa.row_offsets ? gridDim.x - 1 : gridDim.x;   // the last block checks the CSR arrays (one launch less)
     if ((int)blockIdx.x == nblk) {
@@ -83,6 +83,7 @@ __global__ void im2col_kernel(const T *frames, T *patches, int F, int H, int W, 
         x[f * T_tok * D + c] = cls[c] + pos[c];
     }
     for (size_t idx = gtid; idx < n_merged; idx += gsz) merged[idx] = 0.f;
+    for (size_t idx = gtid; idx < n_zero; idx += gsz) zero[idx] = 0u;
 }
 
 // ------------------------------------------------------------------ LayerNorm
@@ -377,12 +378,12 @@ int launch_prep(const int32_t *row_offsets, const int32_t *adapter_ids, int F, i
 }
 
 int launch_im2col(const void *frames, void *patches, int F, int H, int W, int p, int dtype, float *x, const float *cls, const float *pos,
-                  int T_tok, int D, float *merged, size_t n_merged, const int32_t *row_offsets, const int32_t *adapter_ids, int R_cap,
+                  int T_tok, int D, float *merged, size_t n_merged, unsigned *zero, size_t n_zero, const int32_t *row_offsets, const int32_t *adapter_ids, int R_cap,
                   int n_adapters, PolyMeta *meta, int32_t *frame_of_row, int32_t *adapter_of_row, int32_t *dev_status, hipStream_t st)
 {
     const PrepArgs pa = {row_offsets, adapter_ids, F, R_cap, n_adapters, meta, frame_of_row, adapter_of_row, dev_status};
     const size_t total = (size_t)F * H * W * 3;
-    if (total == 0 && n_merged == 0) {
+    if (total == 0 && n_merged == 0 && n_zero == 0) {
         if (row_offsets) return launch_prep(row_offsets, adapter_ids, F, R_cap, n_adapters, meta, frame_of_row, adapter_of_row, dev_status, st);
         return POLY_OK;
     }
@@ -392,11 +393,11 @@ int launch_im2col(const void *frames, void *patches, int F, int H, int W, int p,
     const size_t work = (wide ? total / vec : total) > n_merged ? (wide ? total / vec : total) : n_merged;
     const unsigned blocks = (unsigned)((work + 255) / 256 > 65536 ? 65536 : (work + 255) / 256 < 1 ? 1 : (work + 255) / 256) + (row_offsets ? 1 : 0);
     if (dtype == POLY_BF16) {
-        if (wide) POLY_LAUNCH(POLY_STAGE_OTHER, (im2col_kernel<bf16_t, 8>), dim3(blocks), dim3(256), st, (const bf16_t *)frames, (bf16_t *)patches, F, H, W, p, x, cls, pos, T_tok, D, merged, n_merged, pa);
-        else POLY_LAUNCH(POLY_STAGE_OTHER, (im2col_kernel<bf16_t, 1>), dim3(blocks), dim3(256), st, (const bf16_t *)frames, (bf16_t *)patches, F, H, W, p, x, cls, pos, T_tok, D, merged, n_merged, pa);
+        if (wide) POLY_LAUNCH(POLY_STAGE_OTHER, (im2col_kernel<bf16_t, 8>), dim3(blocks), dim3(256), st, (const bf16_t *)frames, (bf16_t *)patches, F, H, W, p, x, cls, pos, T_tok, D, merged, n_merged, zero, n_zero, pa);
+        else POLY_LAUNCH(POLY_STAGE_OTHER, (im2col_kernel<bf16_t, 1>), dim3(blocks), dim3(256), st, (const bf16_t *)frames, (bf16_t *)patches, F, H, W, p, x, cls, pos, T_tok, D, merged, n_merged, zero, n_zero, pa);
     } else {
-        if (wide) POLY_LAUNCH(POLY_STAGE_OTHER, (im2col_kernel<float, 4>), dim3(blocks), dim3(256), st, (const float *)frames, (float *)patches, F, H, W, p, x, cls, pos, T_tok, D, merged, n_merged, pa);
-        else POLY_LAUNCH(POLY_STAGE_OTHER, (im2col_kernel<float, 1>), dim3(blocks), dim3(256), st, (const float *)frames, (float *)patches, F, H, W, p, x, cls, pos, T_tok, D, merged, n_merged, pa);
+        if (wide) POLY_LAUNCH(POLY_STAGE_OTHER, (im2col_kernel<float, 4>), dim3(blocks), dim3(256), st, (const float *)frames, (float *)patches, F, H, W, p, x, cls, pos, T_tok, D, merged, n_merged, zero, n_zero, pa);
+        else POLY_LAUNCH(POLY_STAGE_OTHER, (im2col_kernel<float, 1>), dim3(blocks), dim3(256), st, (const float *)frames, (float *)patches, F, H, W, p, x, cls, pos, T_tok, D, merged, n_merged, zero, n_zero, pa);
     }
     return hip_ok();
 }

@@ -87,6 +87,46 @@ def test_row_kernels_repeat_bitwise(D, heads, Dm, hw, r, targets, L0):
         assert np.array_equal(first, again)
 
 
+@pytest.mark.parametrize("D,heads,Dm,hw,r,targets,L0,F", [
+    (64, 1, 128, 48, 4, 3, 0, 75),      # the cases of test_row_kernels_all_widths on so many blocks that they leave the task queue
+    (64, 1, 192, 64, 16, 1, 1, 50),
+    (128, 2, 384, 64, 12, 3, 0, 50),
+    (192, 3, 768, 40, 8, 3, 2, 145),
+    (192, 3, 320, 72, 16, 2, 0, 50),
+])
+def test_row_kernels_on_many_blocks(D, heads, Dm, hw, r, targets, L0, F):
+    cfg, w, frames, off, ids = synth.make_small_case(60 + D + r, dtype=synth.DT_BF16, targets=targets, L=3, F=F, r=r, max_set=3,
+                                                      n_adapters=5, D=D, heads=heads, Dm=Dm, hw=hw, patch=8)
+    compare(cfg, w, frames, off, ids, L0, K=cfg.n_adapters * cfg.C)
+    model = binding.DeviceModel(cfg, w, L0=L0)
+    first = binding.run_forward(model, frames, off, ids)["logits"]
+    assert np.array_equal(first, binding.run_forward(model, frames, off, ids)["logits"])
+
+
+@pytest.mark.parametrize("compose", ["branch", "sum"])
+@pytest.mark.parametrize("D,heads,Dm,hw,r,targets,L0,F", [
+    (64, 1, 128, 16, 4, 15, 0, 1),      # T = 5: one ragged row tile, one K step per half; a single block
+    (64, 1, 256, 64, 32, 15, 1, 5),     # T = 65: a one-row tile; two full rank tiles; coarse tasks
+    (128, 2, 256, 40, 20, 15, 0, 9),    # rank 20: the second rank tile partly empty; more blocks than queues
+    (192, 3, 768, 112, 8, 3, 1, 2),     # DeiT-tiny widths and tokens
+    (192, 3, 640, 24, 12, 15, 2, 4),    # Dm no multiple of 256: no coarse tasks
+    (192, 3, 768, 32, 4, 15, 0, 100),   # T = 17, many blocks per queue
+])
+def test_task_queue_sizes(D, heads, Dm, hw, r, targets, L0, F, compose):
+    """Layers as tasks of 32 rows: tile edges, rank tiles, one block to many per queue; repeated bitwise (a task that starts before
+    its inputs are complete shows up as run-to-run differences)."""
+    cfg, w, frames, off, ids = synth.make_small_case(300 + D + r, dtype=synth.DT_BF16, targets=targets, L=3, F=F, r=r, max_set=3,
+                                                      n_adapters=5, D=D, heads=heads, Dm=Dm, hw=hw, patch=8)
+    model = binding.DeviceModel(cfg, w, L0=L0, compose=compose)
+    got = binding.run_forward(model, frames, off, ids)
+    want = oracle.forward(cfg, w, frames, off, ids, L0=L0, compose=compose)
+    assert got["status"] == 0
+    if len(ids):
+        assert np.abs(got["logits"] - want["logits"]).max() < TOL[cfg.dtype]
+    for _ in range(5):
+        assert np.array_equal(got["logits"], binding.run_forward(model, frames, off, ids)["logits"])
+
+
 def test_frames_without_adapters_and_empty_batch():
     cfg, w, frames, _, _ = synth.make_small_case(50, dtype=synth.DT_BF16, F=4)
     off, ids = synth.sets_to_csr([[], [1, 0], [], [2]])
