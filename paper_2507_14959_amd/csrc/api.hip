@@ -474,9 +474,14 @@ int lora_linear_impl(const void *X, int n_xblocks, int T, int Kdim, const void *
     hipStream_t st = (hipStream_t)stream;
     const int RP = rank_pad(r);
 
-    POLY_TRY(launch_prep(row_offsets, adapter_ids, n_xblocks, R, n_adapters, w.meta, w.frame_of_row, w.adapter_of_row, dev_status, st));
-    if (R == 0) return POLY_OK;
-    POLY_TRY(launch_shrink(X, T, Kdim, At, r, RP, scale, R, &w.meta->R, w.frame_of_row, w.adapter_of_row, row_offsets, w.S, dtype, st));
+    if (R > 0 && shrink_csr_fits(n_xblocks, T, Kdim, dtype)) {
+        POLY_TRY(launch_shrink_csr(X, T, Kdim, At, r, RP, scale, row_offsets, adapter_ids, n_xblocks, R, n_adapters, w.meta, w.frame_of_row,
+                                   w.adapter_of_row, dev_status, w.S, st));
+    } else {
+        POLY_TRY(launch_prep(row_offsets, adapter_ids, n_xblocks, R, n_adapters, w.meta, w.frame_of_row, w.adapter_of_row, dev_status, st));
+        if (R == 0) return POLY_OK;
+        POLY_TRY(launch_shrink(X, T, Kdim, At, r, RP, scale, R, &w.meta->R, w.frame_of_row, w.adapter_of_row, row_offsets, w.S, dtype, st));
+    }
     GemmArgs g = {};
     g.A = X; g.Wt = Wt; g.bias = bias; g.T = T; g.K = Kdim; g.N = Ndim;
     g.n_in = n_xblocks; g.n_in_dev = &w.meta->F_ok; g.out_off = row_offsets;

@@ -289,6 +289,12 @@ int launch_shrink(const void *X, int T, int K, const void *At, int r, int RP, fl
                   const int *n_out_dev, const int *in_block_of_out, const int *adapter_of_out, const int *pair_off, void *S,
                   int dtype, hipStream_t st);
 
+// the CSR check, the row maps and the shrink of an isolated bf16 linear in one launch
+bool shrink_csr_fits(int F, int T, int K, int dtype);
+int launch_shrink_csr(const void *X, int T, int K, const void *At, int r, int RP, float scale, const int32_t *row_offsets, const int32_t *adapter_ids,
+                      int F, int R_cap, int n_adapters, PolyMeta *meta, int32_t *frame_of_row, int32_t *adapter_of_row, int32_t *dev_status, void *S,
+                      hipStream_t st);
+
 // softmax attention of every (block, head); qkv elt [n*T][3D] -> out elt [n*T][D]
 int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev,
                      int dtype, hipStream_t st);

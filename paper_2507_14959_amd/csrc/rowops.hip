@@ -164,36 +164,65 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *x, T *y
 // frame into its row-blocks; pair_off = the CSR offsets of the input blocks) the workgroup of the even one does
 // both and the input rows are read once instead of twice.
 constexpr int SH_NS = 6;    // 32-element K steps whose operands are in flight together
+constexpr int SH_CSR_MAX = 1024;   // input blocks at most where the kernel reads the CSR arrays itself
 
-template <int MS, int NG>
+template <int MS, int NG, bool CSR>
 __global__ __launch_bounds__(256) void shrink_bf16_kernel(const bf16_t *X, int T, int K, const bf16_t *At, int r, int RP,
                                                           float scale, int n_out, const int *n_out_dev,
                                                           const int *in_block_of_out, const int *adapter_of_out, const int *pair_off,
-                                                          bf16_t *S)
+                                                          bf16_t *S, const PrepArgs pa)
 {
     constexpr int NV = MS * NG * 4;                              // values per lane and wave
     constexpr int RV = NV < 32 ? NV : 32;                        // values per reduction round
     static_assert(RV % 4 == 0, "reduction rounds");
     __shared__ float red[4][RV][64];
     const int subs = (T + 16 * MS - 1) / (16 * MS);
-    const int ob = blockIdx.x / subs, row0 = (blockIdx.x % subs) * (16 * MS);
-    const bool paired = NG == 2 && pair_off && in_block_of_out && RP == 16;
-    // first round trip: four loads with unconditional addresses, so that they are requested together.  The arrays have
-    // n_out entries; those past the true count are read here but never used.
-    // (volatile: the compiler would otherwise sink each load below the early exit that precedes its first use)
-    const int *pn = n_out_dev ? n_out_dev : adapter_of_out, *pi = in_block_of_out ? in_block_of_out + ob : adapter_of_out + ob;
-    const int n_ld = *(const volatile int *)pn, xb_ld = *(const volatile int *)pi;
-    const int k1_raw = *(const volatile int *)(adapter_of_out + ob), k2_raw = *(const volatile int *)(adapter_of_out + min(ob + 1, n_out - 1));
-    const int n = n_out_dev ? min(n_ld, n_out) : n_out, xb = in_block_of_out ? xb_ld : ob;
-    if (ob >= n) return;
-    int ob2 = -1;
-    if (paired) {                                                // second round trip
-        const int p0 = *(const volatile int *)(pair_off + xb), p1 = *(const volatile int *)(pair_off + xb + 1);
-        if ((ob - p0) & 1) return;                               // done by the workgroup of ob - 1
-        if (ob + 1 < min(p1, n)) ob2 = ob + 1;
+    // CSR: no launch before this one has built the row maps.  The last workgroup checks the arrays and builds them for the product;
+    // the others look their output block up in the offsets themselves (one launch less: 3.5 of the 15.6 us of a call on 9 blocks)
+    if (CSR && blockIdx.x == gridDim.x - 1) {
+        prep_block(pa.row_offsets, pa.adapter_ids, pa.F, pa.R_cap, pa.n_adapters, pa.meta, pa.frame_of_row, pa.adapter_of_row, pa.dev_status);
+        return;
     }
-    const int k_ad = k1_raw, k_ad2 = ob2 >= 0 ? k2_raw : -1;
-    if (k_ad < 0 && k_ad2 < 0) return;
+    const int ob = blockIdx.x / subs, row0 = (blockIdx.x % subs) * (16 * MS);
+    const bool paired = NG == 2 && RP == 16 && (CSR || (pair_off && in_block_of_out));
+    int xb, k_ad, k_ad2, ob2 = -1;
+    if constexpr (CSR) {
+        __shared__ int offs[SH_CSR_MAX + 1];
+        for (int f = threadIdx.x; f <= pa.F; f += 256) offs[f] = pa.row_offsets[f];
+        __syncthreads();
+        const int R = offs[pa.F];
+        if (offs[0] != 0 || R < 0 || R > pa.R_cap || ob >= R) return;          // (rejected, or past the true count)
+        k_ad = pa.adapter_ids[ob];
+        k_ad2 = pa.adapter_ids[min(ob + 1, R - 1)];
+        int before = 0;                                          // input blocks whose rows all lie before output block ob
+        for (int f = threadIdx.x & 63; f < ((pa.F + 63) & ~63); f += 64) before += __popcll(__ballot(f < pa.F && offs[f + 1] <= ob));
+        xb = min(before, pa.F - 1);
+        if (paired) {
+            const int p0 = offs[xb], p1 = offs[xb + 1];
+            if ((ob - p0) & 1) return;                           // done by the workgroup of ob - 1
+            if (ob + 1 < min(p1, R)) ob2 = ob + 1;
+        }
+        if ((unsigned)k_ad >= (unsigned)pa.n_adapters || (ob2 >= 0 && (unsigned)k_ad2 >= (unsigned)pa.n_adapters)) return;   // (rejected)
+        if (ob2 < 0) k_ad2 = -1;
+    } else {
+        // first round trip: four loads with unconditional addresses, so that they are requested together.  The arrays have
+        // n_out entries; those past the true count are read here but never used.
+        // (volatile: the compiler would otherwise sink each load below the early exit that precedes its first use)
+        const int *pn = n_out_dev ? n_out_dev : adapter_of_out, *pi = in_block_of_out ? in_block_of_out + ob : adapter_of_out + ob;
+        const int n_ld = *(const volatile int *)pn, xb_ld = *(const volatile int *)pi;
+        const int k1_raw = *(const volatile int *)(adapter_of_out + ob), k2_raw = *(const volatile int *)(adapter_of_out + min(ob + 1, n_out - 1));
+        const int n = n_out_dev ? min(n_ld, n_out) : n_out;
+        xb = in_block_of_out ? xb_ld : ob;
+        if (ob >= n) return;
+        if (paired) {                                                // second round trip
+            const int p0 = *(const volatile int *)(pair_off + xb), p1 = *(const volatile int *)(pair_off + xb + 1);
+            if ((ob - p0) & 1) return;                               // done by the workgroup of ob - 1
+            if (ob + 1 < min(p1, n)) ob2 = ob + 1;
+        }
+        k_ad = k1_raw;
+        k_ad2 = ob2 >= 0 ? k2_raw : -1;
+        if (k_ad < 0 && k_ad2 < 0) return;
+    }
     const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, lc = lane >> 4;
     const bf16_t *xblk = X + (size_t)xb * T * K + lc * 8;
     int xoff[MS];                                                // row li of subtile m (the host has checked T * K < 2^31)
@@ -424,13 +453,25 @@ int launch_layernorm(const float *x, void *y, const float *gain, const float *sh
     return hip_ok();
 }
 
-template <int MS, int NG>
+template <int MS, int NG, bool CSR>
 static void launch_shrink_bf16(hipStream_t st, const bf16_t *X, int T, int K, const bf16_t *At, int r, int RP, float scale, int n_out,
-                               const int *n_out_dev, const int *in_block_of_out, const int *adapter_of_out, const int *pair_off, bf16_t *S)
+                               const int *n_out_dev, const int *in_block_of_out, const int *adapter_of_out, const int *pair_off, bf16_t *S,
+                               const PrepArgs &pa)
 {
     const int subs = (T + 16 * MS - 1) / (16 * MS);
-    POLY_LAUNCH(POLY_STAGE_SHRINK, (shrink_bf16_kernel<MS, NG>), dim3((unsigned)((size_t)n_out * subs)), dim3(256), st, X, T, K, At, r, RP, scale,
-                n_out, n_out_dev, in_block_of_out, adapter_of_out, pair_off, S);
+    POLY_LAUNCH(POLY_STAGE_SHRINK, (shrink_bf16_kernel<MS, NG, CSR>), dim3((unsigned)((size_t)n_out * subs + (CSR ? 1 : 0))), dim3(256), st, X, T, K, At, r,
+                RP, scale, n_out, n_out_dev, in_block_of_out, adapter_of_out, pair_off, S, pa);
+}
+
+// launch_prep and launch_shrink of an isolated linear (bf16, output blocks of one input block consecutive) in one launch
+bool shrink_csr_fits(int F, int T, int K, int dtype) { return dtype == POLY_BF16 && F <= SH_CSR_MAX && K % 8 == 0 && (long)T * K <= 0x7fffffffL; }
+int launch_shrink_csr(const void *X, int T, int K, const void *At, int r, int RP, float scale, const int32_t *row_offsets, const int32_t *adapter_ids,
+                      int F, int R_cap, int n_adapters, PolyMeta *meta, int32_t *frame_of_row, int32_t *adapter_of_row, int32_t *dev_status, void *S,
+                      hipStream_t st)
+{
+    const PrepArgs pa = {row_offsets, adapter_ids, F, R_cap, n_adapters, meta, frame_of_row, adapter_of_row, dev_status};
+    launch_shrink_bf16<2, 2, true>(st, (const bf16_t *)X, T, K, (const bf16_t *)At, r, RP, scale, R_cap, nullptr, nullptr, nullptr, nullptr, (bf16_t *)S, pa);
+    return hip_ok();
 }
 
 int launch_shrink(const void *X, int T, int K, const void *At, int r, int RP, float scale, int n_out, const int *n_out_dev,
@@ -441,11 +482,11 @@ int launch_shrink(const void *X, int T, int K, const void *At, int r, int RP, fl
         if (K % 8 != 0 || (long)T * K > 0x7fffffffL) return POLY_EINVAL;
         const bool two_groups = RP > 16 || (pair_off && in_block_of_out);
         if (two_groups)
-            launch_shrink_bf16<2, 2>(st, (const bf16_t *)X, T, K, (const bf16_t *)At, r, RP, scale, n_out, n_out_dev, in_block_of_out,
-                                     adapter_of_out, pair_off, (bf16_t *)S);
+            launch_shrink_bf16<2, 2, false>(st, (const bf16_t *)X, T, K, (const bf16_t *)At, r, RP, scale, n_out, n_out_dev, in_block_of_out,
+                                     adapter_of_out, pair_off, (bf16_t *)S, PrepArgs{});
         else
-            launch_shrink_bf16<2, 1>(st, (const bf16_t *)X, T, K, (const bf16_t *)At, r, RP, scale, n_out, n_out_dev, in_block_of_out,
-                                     adapter_of_out, pair_off, (bf16_t *)S);
+            launch_shrink_bf16<2, 1, false>(st, (const bf16_t *)X, T, K, (const bf16_t *)At, r, RP, scale, n_out, n_out_dev, in_block_of_out,
+                                     adapter_of_out, pair_off, (bf16_t *)S, PrepArgs{});
     } else {
         return launch_shrink_f32((const float *)X, T, K, (const float *)At, r, RP, scale, n_out, n_out_dev, in_block_of_out, adapter_of_out, (float *)S, st);
     }
