@@ -329,6 +329,306 @@ __global__ __launch_bounds__(256) void gemm_ks_kernel(const GemmArgs g, int tile
     }
 }
 
+// ------------------------------------------------------------------ the isolated multi-adapter linear of a small call, one launch
+// Y[b] = X[f] W + bias + s (X[f] A_k) B_k for every output block b = (f, k): the CSR check, the shrink and the product in one kernel.
+// A call of a few blocks is three dependent launches of four to six microseconds each otherwise (check, shrink, product with the
+// expand).  Here every workgroup checks the whole CSR (a few hundred words, under its tile loads) before it stores anything, and
+// the shrink of a tile's rows runs beside its product: the ranks of up to four 16-rank slots (output blocks x rank tiles) are 32 more
+// "columns" per two slots of the same 32 x 32 x 16 steps, split over the waves like the product.  The column tiles of a row tile repeat
+// the shrink, which is why large calls keep the separate one (linear_ks_tile).
+// Measured, one / two launches: 1 x 197 x 192 -> 576 10.4 / 13.9 us, 1 x 197 x 768 -> 2304 11.2 / 15.9, 9 x 17 x 384 -> 1536 10.9 / 48
+// (its separate product has too few rows per block for the large tiles); single precision, 2 x 197 x 192 -> 576: 11.2 / 19.3.
+struct LinearParams {
+    const void *X, *W, *At, *Bt;
+    const float *bias;
+    int F, T, K, N, n_adapters, r, R_cap;
+    float scale;
+    const int *off, *ids;
+    void *Y;
+    int *dev_status;
+};
+
+template <typename T, int MI, int NI>
+__global__ __launch_bounds__(256) void linear_ks_kernel(const LinearParams g, int tiles_m, int tiles_n, int ns)
+{
+    typedef Elt<T> E;
+    typedef typename E::frag frag;
+    constexpr int V = E::V, BK = 8 * V, BM = 32 * MI, BN = 32 * NI, NU = 16 / (2 * V);   // NU: expand steps per 16 ranks
+    constexpr int STAGE = (BM + BN) * 128, NLD = (BM + BN) / 8;
+    constexpr int NF = MI * NI;
+    extern __shared__ __attribute__((aligned(16))) char ks_lds[];
+    __shared__ int bad_s[4];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lm = lane & 31, lh = lane >> 5;
+    // tile of this workgroup: eight equal runs, one per XCD (as gemm_ks_kernel)
+    const int mtot = g.F * tiles_m;
+    int mt, tn;
+    {
+        const unsigned xcd = blockIdx.x & 7, total = (unsigned)mtot * tiles_n, lo = total * xcd / 8, hi = total * (xcd + 1) / 8, L = lo + (blockIdx.x >> 3);
+        if (L >= hi && blockIdx.x) return;                     // (workgroup 0 reports the status in any case)
+        if (mtot <= tiles_n) { tn = (int)(L / (unsigned)mtot); mt = (int)L - tn * mtot; }
+        else { mt = (int)(L / (unsigned)tiles_n); tn = (int)L - mt * tiles_n; }
+        if (L >= hi) { mt = -1; tn = 0; }
+    }
+    const bool idle = mt < 0;
+    const int xb = idle ? 0 : mt / tiles_m, t0 = idle ? 0 : (mt - xb * tiles_m) * BM, n0 = tn * BN;
+    const T *A = (const T *)g.X + ((size_t)xb * g.T + t0) * g.K;
+    const T *W = (const T *)g.W + (size_t)n0 * g.K;
+    const int nk = (g.K + BK - 1) / BK, steps = idle ? 0 : (nk - wave + 3) >> 2;
+    const unsigned rowb = (unsigned)g.K * sizeof(T);
+    const int lr = lane >> 3, c0 = (lane & 7) ^ (lr >> 1), c1 = c0 ^ 4;
+    const int tail = g.K - (nk - 1) * BK;
+    const int adj0 = min(c0, tail / V - 1) - c0, adj1 = min(c1, tail / V - 1) - c1;
+    char *ring = ks_lds + wave * ns * STAGE;
+    auto issue = [&](int i) {
+        const int kt = wave + 4 * i;
+        const bool last = kt == nk - 1;
+        const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_addr_of(ring + (i % ns) * STAGE));
+        const unsigned e0 = (unsigned)(c0 + (last ? adj0 : 0)) * 16, e1 = (unsigned)(c1 + (last ? adj1 : 0)) * 16;
+#pragma unroll
+        for (int q = 0; q < BM / 8; ++q)
+            glds16_s((const char *)A + (size_t)kt * 128, (unsigned)min(8 * q + lr, g.T - 1 - t0) * rowb + ((q & 1) ? e1 : e0), lds0 + q * 1024);
+#pragma unroll
+        for (int q = 0; q < BN / 8; ++q)
+            glds16_s((const char *)W + (size_t)kt * 128, (unsigned)min(8 * q + lr, g.N - 1 - n0) * rowb + ((q & 1) ? e1 : e0), lds0 + (BM / 8 + q) * 1024);
+    };
+    for (int i = 0; i < min(ns, steps); ++i) issue(i);
+
+    // ---- the CSR: this tile's output blocks and adapters first, then the check of all of it
+    const int R = uload(g.off + g.F), o0 = uload(g.off + xb), o1 = uload(g.off + xb + 1), off0 = uload(g.off);
+    const bool sane = off0 == 0 && R >= 0 && R <= g.R_cap && o0 >= 0 && o0 <= o1 && o1 <= R;
+    const int nob = sane && !idle ? o1 - o0 : 0;
+    bool bad = !(off0 == 0 && R >= 0 && R <= g.R_cap);
+    if (!bad) {
+        for (int f = tid; f < g.F; f += 256) {
+            const int a = g.off[f], b = g.off[f + 1];
+            if (a > b || a < 0 || b > R) bad = true;
+        }
+        for (int i = tid; i < R; i += 256) {
+            const int k = g.ids[i];
+            if (k < 0 || k >= g.n_adapters) bad = true;
+        }
+    }
+    const bool any = __ballot(bad) != 0;
+    if (lane == 0) bad_s[wave] = any;
+    const int nrt = (g.r + 15) >> 4, per_pass = nrt <= 2 ? 4 / nrt : 1;   // rank tiles; output blocks per pass of at most four slots
+
+    const int fi = wave / NI, fj = wave % NI;
+    const int tw = t0 + 32 * fi, nc = n0 + 32 * fj;
+    const bool fin = wave < NF && tw < g.T && nc < g.N;
+    const bool vec = g.N % 4 == 0;
+    const int rch = lane & 7, rrow = lane >> 3, col = nc + 4 * rch;
+    f32x4 bias4 = {0.f, 0.f, 0.f, 0.f};
+    if (fin && g.bias && vec) bias4 = *(const f32x4 *)(g.bias + min(col, g.N - 4));
+    const frag zero = {};
+    const int sw = (lm >> 1) & 7;
+    float *red = (float *)ks_lds, *sred = red + 4 * NF * 1024;
+    float *stg = red + wave * 1024;                            // this wave's part of wave 0's areas
+    f32x16 base;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) base[e] = 0.f;
+
+    for (int pass = 0; pass == 0 || pass * per_pass < nob; ++pass) {
+        const int ob_base = o0 + pass * per_pass, nslots = min(per_pass, nob - pass * per_pass) * nrt;   // (<= 0 without output blocks)
+        if (pass) {
+            __syncthreads();                                   // the partial sums of the pass before have been read
+            for (int i = 0; i < min(ns, steps); ++i) issue(i);
+        }
+        // At row of lane lm in the two slots of product q (clamped where there is none: the result is not used)
+        const T *at[2];
+        int kad[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            kad[s] = s < nslots ? uload(g.ids + ob_base + s / nrt) : 0;
+            if ((unsigned)kad[s] >= (unsigned)g.n_adapters) kad[s] = 0;                                  // (reported, and nothing is stored)
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int s = 2 * q + (lm >> 4);
+            const int rank = min((s % nrt) * 16 + (lm & 15), g.r - 1);
+            at[q] = (const T *)g.At + ((size_t)((lm >> 4) ? kad[2 * q + 1] : kad[2 * q]) * g.r + rank) * g.K;
+        }
+        frag fat[2][4];
+        auto load_at = [&](int i) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (2 * q < nslots) {
+#pragma unroll
+                    for (int kk = 0; kk < 4; ++kk) fat[q][kk] = *(const frag *)(at[q] + min((wave + 4 * i) * BK + (2 * kk + lh) * V, g.K - V));
+                }
+        };
+        if (steps > 0) load_at(0);
+        // Bt rows of this wave's columns: ranks 16 jt + 4 lh .. and 16 jt + 8 + 4 lh .. of every slot, as the shrink leaves them in a lane
+        frag fbt[4][NU];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            if (fin && s < nslots) {
+                const T *bt = (const T *)g.Bt + ((size_t)kad[s] * g.N + min(nc + lm, g.N - 1)) * g.r;
+                typedef T quad __attribute__((ext_vector_type(4)));
+                quad w[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int rank = 16 * (s % nrt) + 8 * u + 4 * lh;
+                    if (g.r % 4 == 0) {
+                        w[u] = *(const quad *)(bt + min(rank, g.r - 4));
+                        if (rank >= g.r) w[u] = quad{};
+                    } else {
+#pragma unroll
+                        for (int z = 0; z < 4; ++z) w[u][z] = rank + z < g.r ? bt[rank + z] : from_f32<T>(0.f);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) fbt[s][V == 8 ? 0 : u][V == 8 ? 4 * u + z : z] = w[u][z];
+            }
+
+        f32x16 acc[MI][NI], sac[MI][2];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) sac[i][q][e] = 0.f;
+        }
+        for (int i = 0; i < steps; ++i) {
+            const int ahead = min(steps - 1, i + ns - 1) - i;
+            if (ahead >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NLD) : "memory");
+            else if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NLD) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const char *st = ring + (i % ns) * STAGE;
+            frag fx[4][MI], fw[4][NI];
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                const int ch = ((2 * kk + lh) ^ sw) << 4;
+#pragma unroll
+                for (int m = 0; m < MI; ++m) fx[kk][m] = *(const frag *)(st + (m * 32 + lm) * 128 + ch);
+#pragma unroll
+                for (int n = 0; n < NI; ++n) fw[kk][n] = *(const frag *)(st + (BM + n * 32 + lm) * 128 + ch);
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (i + ns < steps) issue(i + ns);
+            if (wave + 4 * i == nk - 1 && tail < BK) {         // chunks past K add nothing
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk)
+                    if ((2 * kk + lh) * V >= tail) {
+#pragma unroll
+                        for (int m = 0; m < MI; ++m) fx[kk][m] = zero;
+                    }
+            }
+            if (pass == 0) {
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+                    for (int m = 0; m < MI; ++m)
+#pragma unroll
+                        for (int n = 0; n < NI; ++n) acc[m][n] = E::mma(fw[kk][n], fx[kk][m], acc[m][n]);
+            }
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (2 * q < nslots) {
+#pragma unroll
+                    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+                        for (int m = 0; m < MI; ++m) sac[m][q] = E::mma(fat[q][kk], fx[kk][m], sac[m][q]);
+                }
+            if (i + 1 < steps) load_at(i + 1);
+        }
+
+        // ---- the partial sums meet: (wave, subtile) of the product, (wave, row subtile, q) of the shrink
+        __syncthreads();                                       // the rings are dead
+        if (pass == 0) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+#pragma unroll
+                    for (int e4 = 0; e4 < 4; ++e4)
+                        *(f32x4 *)(red + ((wave * NF + i * NI + j) * 4 + e4) * 256 + lane * 4) =
+                            f32x4{acc[i][j][4 * e4], acc[i][j][4 * e4 + 1], acc[i][j][4 * e4 + 2], acc[i][j][4 * e4 + 3]};
+        }
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (2 * q < nslots) {
+#pragma unroll
+                    for (int e4 = 0; e4 < 4; ++e4)
+                        *(f32x4 *)(sred + (((wave * MI + i) * 2 + q) * 4 + e4) * 256 + lane * 4) =
+                            f32x4{sac[i][q][4 * e4], sac[i][q][4 * e4 + 1], sac[i][q][4 * e4 + 2], sac[i][q][4 * e4 + 3]};
+                }
+        __syncthreads();
+        const bool bad_csr = bad_s[0] | bad_s[1] | bad_s[2] | bad_s[3];
+        if (pass == 0 && blockIdx.x == 0 && tid == 0 && g.dev_status) *g.dev_status = bad_csr ? POLY_ERANGE : POLY_OK;
+        if (bad_csr || nob <= 0) return;
+        if (!fin) continue;
+        if (pass == 0) {
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) {
+                f32x4 s = *(const f32x4 *)(red + ((0 * NF + wave) * 4 + e4) * 256 + lane * 4);
+#pragma unroll
+                for (int w = 1; w < 4; ++w) s += *(const f32x4 *)(red + ((w * NF + wave) * 4 + e4) * 256 + lane * 4);
+#pragma unroll
+                for (int z = 0; z < 4; ++z) base[4 * e4 + z] = s[z];
+            }
+        }
+        auto emit = [&](const f32x16 &c, int ob) {
+            const long obase = ((long)ob * g.T + tw) * g.N;
+            const int hi = min(32, g.T - tw);
+            if (!vec) {                                        // N not a multiple of 4: element by element
+                if (lm >= hi) return;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int cc = nc + 8 * (e >> 2) + 4 * lh + (e & 3);
+                    if (cc < g.N) ((T *)g.Y)[obase + (long)lm * g.N + cc] = from_f32<T>(c[e] + (g.bias ? g.bias[cc] : 0.f));
+                }
+                return;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *(f32x4 *)(stg + lm * 32 + (((2 * q + lh) ^ ((lm >> 1) & 7)) << 2)) = f32x4{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int row = 8 * q + rrow;
+                const f32x4 v = *(const f32x4 *)(stg + row * 32 + ((rch ^ ((row >> 1) & 7)) << 2)) + bias4;
+                if (row >= hi || col >= g.N) continue;
+                typedef T out4 __attribute__((ext_vector_type(4)));
+                *(out4 *)((T *)g.Y + obase + (long)row * g.N + col) = out4{from_f32<T>(v[0]), from_f32<T>(v[1]), from_f32<T>(v[2]), from_f32<T>(v[3])};
+            }
+        };
+        f32x16 c = base;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if (s >= nslots) break;
+            const int jt = s % nrt;
+            if (jt == 0) c = base;
+            // ranks 16 jt + 8 u + 4 lh .. (bf16: u = 0 and 1 in one operand) of row lm; the slot's half of product s / 2
+            float sv[8];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const float *sp = sred + ((size_t)fi * 2 + (s >> 1)) * 1024 + (2 * (s & 1) + u) * 256 + lane * 4;
+                f32x4 t = *(const f32x4 *)sp;
+#pragma unroll
+                for (int w = 1; w < 4; ++w) t += *(const f32x4 *)(sp + (size_t)w * MI * 2 * 1024);
+#pragma unroll
+                for (int z = 0; z < 4; ++z) sv[4 * u + z] = t[z] * g.scale;
+            }
+            frag fs[NU];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int z = 0; z < 4; ++z) fs[V == 8 ? 0 : u][V == 8 ? 4 * u + z : z] = from_f32<T>(sv[4 * u + z]);
+#pragma unroll
+            for (int u = 0; u < NU; ++u) c = E::mma(fbt[s][u], fs[u], c);
+            if (jt == nrt - 1) emit(c, ob_base + s / nrt);
+        }
+    }
+}
+
 template <typename T, int MI, int NI, bool SHRINK> int launch_ks(const GemmArgs &g, hipStream_t st)
 {
     constexpr int STAGE = 32 * (MI + NI) * 128, BK = 8 * Elt<T>::V, RED = 4 * MI * NI * 4096;
@@ -371,6 +671,49 @@ int launch_gemm_ks(const GemmArgs &g, int dtype, hipStream_t st)
     if (c11 < c12 && c11 < c22) return launch_ks<float, 1, 1, false>(g, st);
     if (c12 < c22) return launch_ks<float, 1, 2, false>(g, st);
     return launch_ks<float, 2, 2, false>(g, st);
+}
+
+namespace {
+template <typename T, int MI, int NI> int launch_linear_t(const LinearParams &g, hipStream_t st)
+{
+    constexpr int STAGE = 32 * (MI + NI) * 128, BK = 8 * Elt<T>::V, RED = 4 * (MI * NI + 2 * MI) * 4096, LDS_MAX = 144 * 1024;
+    const int nk = (g.K + BK - 1) / BK;
+    int ns = (nk + 3) / 4 < KS_NSMAX ? (nk + 3) / 4 : KS_NSMAX;
+    while (4 * ns * STAGE > LDS_MAX) --ns;
+    const int lds = 4 * ns * STAGE > RED ? 4 * ns * STAGE : RED;
+    auto kern = linear_ks_kernel<T, MI, NI>;
+    static bool attr_set = false;       // raising the dynamic LDS limit is a per-kernel, process-wide setting
+    if (!attr_set) {
+        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_MAX) != hipSuccess) return POLY_EHIP;
+        attr_set = true;
+    }
+    const int tiles_m = (g.T + 32 * MI - 1) / (32 * MI), tiles_n = (g.N + 32 * NI - 1) / (32 * NI);
+    const long total = (long)g.F * tiles_m * tiles_n;
+    POLY_LAUNCH_SHMEM(POLY_STAGE_GEMM, kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(256), lds, st, g, tiles_m, tiles_n, ns);
+    return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
+}
+
+// Tile of the one-launch linear: the smallest of 32 x 32, 32 x 64 and 64 x 64 with which every tile gets a compute unit of its own
+// (0 = none).  Smaller tiles are more of the chip and a shorter serial chain; with more tiles than compute units a second round, and the
+// shrink that every column tile repeats, cost more than the launch that is saved (9 x 197 x 192 -> 576, 378 tiles of 64 x 64: 15.9 us
+// against 15.1 with the separate shrink).
+int linear_ks_tile(long F, int T, int N)
+{
+    auto tiles = [&](int bm, int bn) { return F * ((T + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    return tiles(32, 32) <= 256 ? 1 : tiles(32, 64) <= 256 ? 2 : tiles(64, 64) <= 256 ? 3 : 0;
+}
+}  // namespace
+
+// ranks: four slots of 16 at most; CSR: every workgroup reads all of it, four words per lane at most
+bool linear_ks_fits(int F, int T, int N, int r, int R) { return r <= 64 && F + (long)R <= 1024 && linear_ks_tile(F, T, N) != 0; }
+
+int launch_linear_ks(const void *X, int F, int T, int K, const void *W, const float *bias, int N, const void *At, const void *Bt, int n_adapters,
+                     int r, float scale, const int *off, const int *ids, int R, void *Y, int dtype, int *dev_status, hipStream_t st)
+{
+    const LinearParams g = {X, W, At, Bt, bias, F, T, K, N, n_adapters, r, R, scale, off, ids, Y, dev_status};
+    const int tile = linear_ks_tile(F, T, N);
+    if (dtype == POLY_BF16) return tile == 1 ? launch_linear_t<bf16_t, 1, 1>(g, st) : tile == 2 ? launch_linear_t<bf16_t, 1, 2>(g, st) : launch_linear_t<bf16_t, 2, 2>(g, st);
+    return tile == 1 ? launch_linear_t<float, 1, 1>(g, st) : tile == 2 ? launch_linear_t<float, 1, 2>(g, st) : launch_linear_t<float, 2, 2>(g, st);
 }
 
 // S[ob] = scale * X[in_block_of_out[ob]] At[adapter_of_out[ob]]^T in single precision, zero padded to RP columns

@@ -172,6 +172,10 @@ struct GemmArgs {
 
 int launch_gemm(const GemmArgs &g, int dtype, hipStream_t st);
 int launch_gemm_ks(const GemmArgs &g, int dtype, hipStream_t st);    // small calls and fp32 (gemm_ks.hip); called by launch_gemm
+// the isolated linear of a small call in one launch (gemm_ks.hip): CSR check, shrink, product and expand
+bool linear_ks_fits(int F, int T, int N, int r, int R);
+int launch_linear_ks(const void *X, int F, int T, int K, const void *W, const float *bias, int N, const void *At, const void *Bt, int n_adapters,
+                     int r, float scale, const int *off, const int *ids, int R, void *Y, int dtype, int *dev_status, hipStream_t st);
 int launch_shrink_f32(const float *X, int T, int K, const float *At, int r, int RP, float scale, int n_out, const int *n_out_dev,
                       const int *in_block_of_out, const int *adapter_of_out, float *S, hipStream_t st);
 

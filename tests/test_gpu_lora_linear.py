@@ -50,6 +50,21 @@ def test_matches_checker(dtype, shape):
     check(Y, oracle.lora_linear(case, s=1.5), dtype)
 
 
+@pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_BF16])
+@pytest.mark.parametrize("shape", [
+    dict(n_xblocks=1, T=3, Kdim=8, Ndim=5, n_adapters=2, r=1, per_block=1),              # a corner of one 32 x 32 tile, odd N and rank
+    dict(n_xblocks=2, T=33, Kdim=200, Ndim=100, n_adapters=5, r=20, per_block=3),        # two rank tiles: two output blocks per pass
+    dict(n_xblocks=1, T=197, Kdim=264, Ndim=2046, n_adapters=3, r=48, per_block=3),      # 32 x 64, N no multiple of 4, one block per pass
+    dict(n_xblocks=2, T=197, Kdim=192, Ndim=1840, n_adapters=8, r=8, per_block=6),       # 64 x 64, four blocks and then two
+    dict(n_xblocks=1, T=64, Kdim=1032, Ndim=68, n_adapters=4, r=64, per_block=2),        # the largest rank, ring smaller than the k-tiles
+])
+def test_small_calls_in_one_launch(dtype, shape):
+    case = synth.make_lora_linear_case(dtype=dtype, seed=37, **shape)
+    Y, st = gpu_lora_linear(case, scale=0.75)
+    assert st == 0
+    check(Y, oracle.lora_linear(case, s=0.75), dtype)
+
+
 def test_frames_without_adapters_and_row_bound_above_R():
     case = synth.make_lora_linear_case(n_xblocks=6, T=40, Kdim=64, Ndim=96, n_adapters=4, r=8, per_block=2, seed=5)
     off, ids = synth.sets_to_csr([[1], [], [0, 3], [], [], [2]])
