@@ -120,7 +120,9 @@ int poly_select(const float *label_scores, int F, int K, const uint8_t *group_me
  *                 class_map[k][c] from row-block (f,k), maximum where adapters overlap, 0 where no
  *                 active adapter reports the class.
  *   dev_status    device int32, nullable: POLY_OK or POLY_ERANGE after the call.
- *   workspace     >= poly_forward_workspace_bytes(m, F, R) bytes, 256-byte aligned.
+ *   workspace     >= poly_forward_workspace_bytes(m, F, R) bytes, 256-byte aligned.  That size never shrinks with F or R: a
+ *                 workspace for a program's largest call serves its smaller ones.  (It has room for the fastest kernels; a
+ *                 smaller one is taken as long as some kernels can do with it, POLY_ECAP otherwise.)
  * Rows past row_offsets[F] are left untouched.  Results do not depend on where a frame sits in
  * the batch (fixed reduction order, no atomics on floating-point sums).
  * Shape limits (POLY_EINVAL otherwise): D == 64 * heads; 1 <= r <= 64; 1 <= C <= 64; H, W multiples of patch;

@@ -3,7 +3,6 @@
 
 namespace {
 
-
 inline size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 inline size_t elt_size(int dtype) { return dtype == POLY_BF16 ? 2 : 4; }
 inline int rank_pad(int r) { return (r + 15) / 16 * 16; }
@@ -19,73 +18,146 @@ struct Carver {
     }
 };
 
+inline int tokens(const poly_model_desc *m) { return 1 + (m->H / m->patch) * (m->W / m->patch); }
+
+// A segment of the layers (shared, adapted) that may run as launches of small tasks (flow.hip) instead of one or more launches per layer
+struct FlowSegment {
+    int blocks, layers;                     // 0 blocks: this segment may not
+};
+
+// blocks up to which a segment may: up to 140 tiles of 32 rows where the row kernel is the alternative, 320 where the GEMM path is (ranks
+// it does not take, adapters on the MLP, summed terms).  DeiT-tiny, twelve layers: 20 blocks of 197 tokens 482 against 491 us, 24 blocks 519
+// against 502; 64 blocks of 50 tokens 404 against 435, 96 blocks 532 against 462; summed terms on 32 blocks of 197 tokens 673 against 832,
+// on 48 blocks 945 against 902.
+int flow_limit(const poly_model_desc *m, bool adapted)
+{
+    const int T = tokens(m), r = adapted ? m->r : 0, tgt = adapted ? m->targets & 15 : 0;
+    if (m->dtype != POLY_BF16 || !flow_supported(T, m->D, m->Dm, m->heads, r, tgt != 0)) return 0;
+    const bool row_kernel = !(tgt & 12) && !(adapted && m->compose == POLY_COMPOSE_SUM && tgt) && rowlayer_supported(m->D, m->Dm, tgt ? r : 0);
+    return (row_kernel ? 140 : 320) / ((T + 31) / 32);
+}
+
+// of a call of F frames and R row-blocks; capped: of the largest call with no more frames and row-blocks that still may
+FlowSegment flow_segment(const poly_model_desc *m, int F, int R, bool adapted, bool capped)
+{
+    const int layers = adapted ? m->L - m->L0 : m->L0;
+    const int blocks = adapted && m->compose != POLY_COMPOSE_SUM ? R : F, limit = flow_limit(m, adapted);
+    if (layers == 0 || (adapted && R == 0) || (blocks > limit && !capped)) return {0, layers};
+    return {blocks < limit ? blocks : limit, layers};
+}
+
+// Every layer of a launch of flow.hip has buffers of its own (see there), so what they take grows with the layers of a launch: a segment
+// whose buffers would take more than FLOW_BYTES is cut into equal launches, down to FLOW_MIN_LAYERS layers each.  DeiT-tiny, twelve layers
+// in 1, 2 and 3 launches: 18 blocks of 197 tokens 375, 390, 398 us with 188, 94, 63 MB (the row kernels: 475), 20 blocks 487, 483, 497 with
+// 209, 105, 70 MB (491), 24 blocks of 113 tokens with summed terms 429, 429, 447 with 155, 78, 52 MB (707 on the GEMM path).
+constexpr int FLOW_MIN_LAYERS = 4;
+constexpr size_t FLOW_BYTES = (size_t)128 << 20;
+
+struct FlowBuffers {
+    bf16_t *qk, *vt, *o, *h;
+    float *x1, *x2;
+};
+FlowBuffers carve_flow(const poly_model_desc *m, size_t n, Carver &c)      // n: blocks x layers of a launch
+{
+    const int T = tokens(m);
+    FlowBuffers f;
+    f.qk = c.take<bf16_t>(sizeof(bf16_t) * n * flow_elements(T, 2 * m->D));
+    f.vt = c.take<bf16_t>(sizeof(bf16_t) * n * flow_elements(T, m->D));
+    f.o = c.take<bf16_t>(sizeof(bf16_t) * n * flow_elements(T, m->D));
+    f.h = c.take<bf16_t>(sizeof(bf16_t) * n * flow_elements(T, m->Dm));
+    f.x1 = c.take<float>(sizeof(float) * n * T * m->D);
+    f.x2 = c.take<float>(sizeof(float) * n * T * m->D);
+    return f;
+}
+size_t flow_bytes(const poly_model_desc *m, size_t n)
+{
+    Carver c{nullptr, 0};
+    carve_flow(m, n, c);
+    return c.off;
+}
+int flow_min_layers(const FlowSegment &s) { return s.layers < FLOW_MIN_LAYERS ? s.layers : FLOW_MIN_LAYERS; }
+size_t flow_counters(const poly_model_desc *m, const FlowSegment &s)       // of all its launches, at their largest number
+{
+    return s.blocks ? (size_t)((s.layers + FLOW_MIN_LAYERS - 1) / FLOW_MIN_LAYERS) * flow_counter_bytes(s.blocks, m->heads) : 0;
+}
+
 struct ForwardWs {
     PolyMeta *meta;
     int32_t *frame_of_row, *adapter_of_row;
     float *xa, *xb;  // residual streams: per frame (shared layers), per row-block (adapted layers)
     void *u, *qkv, *o, *h, *S, *patches;
-    float *fl_x1, *fl_x2;
-    bf16_t *fl_qk, *fl_vt, *fl_o, *fl_h;                  // flow.hip, when a segment of the layers may take it
-    unsigned *fl_cnt[2];                    // its counters: shared layers, adapted layers
-    size_t fl_cnt_bytes;                    // of both
-    size_t bytes;
+    size_t fixed, bytes;                    // up to xb; all of it: what a call needs at least
+    int fl_layers[2];                       // layers per launch of flow.hip in the shared and in the adapted layers (0: not there)
+    FlowBuffers fl[2];                      // in the place of u .. patches: the patches are embedded before the first launch
+    unsigned *fl_cnt[2];                    // counters of its launches, behind everything else
+    size_t fl_cnt_bytes;                    // of both segments
 };
 
-// Segments of the layers (shared, adapted) that run as one launch of small tasks (flow.hip) instead of one or more launches per layer: up
-// to 140 tiles of 32 rows where the row kernel is the alternative, 320 where the GEMM path is (ranks it does not take, adapters on the
-// MLP, summed terms).  DeiT-tiny, twelve layers: 20 blocks of 197 tokens 482 against 491 us, 24 blocks 519 against 502; 64 blocks of 50
-// tokens 404 against 435, 96 blocks 532 against 462; summed terms on 32 blocks of 197 tokens 673 against 832, on 48 blocks 945 against 902.
-bool flow_fits(const poly_model_desc *m, int T, int blocks, bool adapted)
+// `bytes`: what there is.  The layers run as tasks where it holds their buffers too, which a workspace of poly_forward_workspace_bytes for
+// this many frames and row-blocks or more does; the kernels that go layer by layer need no more than w.bytes.
+ForwardWs carve_forward(const poly_model_desc *m, int F, int R, void *base, size_t bytes)
 {
-    const int r = adapted ? m->r : 0, tgt = adapted ? m->targets & 15 : 0;
-    if (m->dtype != POLY_BF16 || blocks <= 0 || !flow_supported(T, m->D, m->Dm, m->heads, r, tgt != 0)) return false;
-    const bool row_kernel = !(tgt & 12) && !(adapted && m->compose == POLY_COMPOSE_SUM && tgt) && rowlayer_supported(m->D, m->Dm, tgt ? r : 0);
-    return (long)blocks * ((T + 31) / 32) <= (row_kernel ? 140 : 320);
-}
-bool flow_shared(const poly_model_desc *m, int T, int F) { return m->L0 > 0 && flow_fits(m, T, F, false); }
-bool flow_adapted(const poly_model_desc *m, int T, int F, int R)
-{
-    return m->L0 < m->L && R > 0 && flow_fits(m, T, m->compose == POLY_COMPOSE_SUM ? F : R, true);
-}
-
-ForwardWs carve_forward(const poly_model_desc *m, int F, int R, void *base)
-{
-    const size_t T = 1 + (size_t)(m->H / m->patch) * (m->W / m->patch), es = elt_size(m->dtype);
+    const size_t T = tokens(m), es = elt_size(m->dtype);
     const size_t nb = (size_t)(F > R ? F : R), rows = nb * T;
     Carver c{(char *)base, 0};
-    ForwardWs w;
+    ForwardWs w = {};
     w.meta = c.take<PolyMeta>(sizeof(PolyMeta));
     w.frame_of_row = c.take<int32_t>(sizeof(int32_t) * (size_t)(R + 1));
     w.adapter_of_row = c.take<int32_t>(sizeof(int32_t) * (size_t)(R + 1));
     w.xa = c.take<float>(sizeof(float) * (size_t)F * T * m->D);
     w.xb = c.take<float>(sizeof(float) * (size_t)R * T * m->D);
+    w.fixed = c.off;
     w.u = c.take<void>(es * rows * m->D);
     w.qkv = c.take<void>(es * rows * 3 * m->D);
     w.o = c.take<void>(es * rows * m->D);
     w.h = c.take<void>(es * rows * m->Dm);
     w.S = c.take<void>(es * (size_t)R * T * rank_pad(m->r));
     w.patches = c.take<void>(es * (size_t)F * (T - 1) * 3 * m->patch * m->patch);
-    const bool fs = flow_shared(m, (int)T, F), fa = flow_adapted(m, (int)T, F, R);
-    w.fl_x1 = w.fl_x2 = nullptr;
-    w.fl_qk = w.fl_vt = w.fl_o = w.fl_h = nullptr;
-    w.fl_cnt[0] = w.fl_cnt[1] = nullptr;
-    w.fl_cnt_bytes = 0;
-    if (fs || fa) {
-        const size_t na = m->compose == POLY_COMPOSE_SUM ? F : R;
-        const size_t ns = fs ? (size_t)F * m->L0 : 0, nd = fa ? na * (m->L - m->L0) : 0, nl = ns > nd ? ns : nd;   // blocks x layers
-        w.fl_qk = c.take<bf16_t>(es * nl * flow_elements((int)T, 2 * m->D));
-        w.fl_vt = c.take<bf16_t>(es * nl * flow_elements((int)T, m->D));
-        w.fl_o = c.take<bf16_t>(es * nl * flow_elements((int)T, m->D));
-        w.fl_h = c.take<bf16_t>(es * nl * flow_elements((int)T, m->Dm));
-        w.fl_x1 = c.take<float>(sizeof(float) * nl * T * m->D);
-        w.fl_x2 = c.take<float>(sizeof(float) * nl * T * m->D);
-        const size_t off0 = c.off;
-        if (fs) w.fl_cnt[0] = c.take<unsigned>(flow_counter_bytes(F, m->heads));
-        if (fa) w.fl_cnt[1] = c.take<unsigned>(flow_counter_bytes((int)na, m->heads));
-        w.fl_cnt_bytes = c.off - off0;
-    }
     w.bytes = c.off;
+
+    const FlowSegment seg[2] = {flow_segment(m, F, R, false, false), flow_segment(m, F, R, true, false)};
+    const size_t cnt = flow_counters(m, seg[0]) + flow_counters(m, seg[1]);
+    if (cnt == 0 || bytes < w.bytes + cnt) return w;
+    const size_t end = (bytes - cnt) & ~(size_t)255;                       // the counters' place
+    if (end < w.bytes) return w;
+    Carver cc{(char *)base, end};
+    for (int a = 0; a < 2; ++a) {
+        if (seg[a].blocks == 0) continue;
+        const int least = flow_min_layers(seg[a]);
+        int launches = 1, n = seg[a].layers;                   // layers of a launch: as few launches as there is room for
+        auto fits = [&]() { return w.fixed + flow_bytes(m, (size_t)seg[a].blocks * n) <= end; };
+        while (!fits() && n > least) {
+            ++launches;
+            n = (seg[a].layers + launches - 1) / launches;
+            if (n < least) n = least;
+        }
+        if (!fits()) continue;
+        Carver cf{(char *)base, w.fixed};
+        w.fl[a] = carve_flow(m, (size_t)seg[a].blocks * n, cf);
+        w.fl_layers[a] = n;
+        const size_t one = flow_counter_bytes(seg[a].blocks, m->heads) * (size_t)((seg[a].layers + n - 1) / n);
+        w.fl_cnt[a] = (unsigned *)((char *)base + cc.off);
+        cc.off += one;
+        w.fl_cnt_bytes += one;
+    }
     return w;
+}
+
+// Never less for more frames or row-blocks, so that a workspace for the largest call of a program serves its smaller ones: the task
+// buffers are those of the largest call up to this one that runs as tasks
+size_t forward_bytes(const poly_model_desc *m, int F, int R)
+{
+    const ForwardWs w = carve_forward(m, F, R, nullptr, 0);
+    size_t end = w.bytes, cnt = 0;
+    for (int a = 0; a < 2; ++a) {
+        const FlowSegment s = flow_segment(m, F, R, a == 1, true);
+        if (s.blocks == 0) continue;
+        const size_t all = flow_bytes(m, (size_t)s.blocks * s.layers), least = flow_bytes(m, (size_t)s.blocks * flow_min_layers(s));
+        const size_t most = least > FLOW_BYTES ? least : FLOW_BYTES, want = all < most ? all : most;
+        if (w.fixed + want > end) end = w.fixed + want;
+        cnt += flow_counters(m, s);
+    }
+    return align_up(end) + align_up(cnt);
 }
 
 int check_model(const poly_model_desc *m)
@@ -98,7 +170,7 @@ int check_model(const poly_model_desc *m)
     if (m->r <= 0 || m->r > POLY_MAX_RANK || m->n_adapters <= 0 || m->C <= 0 || m->C > POLY_MAX_HEAD_CLASSES) return POLY_EINVAL;
     if (m->targets & ~15) return POLY_EINVAL;
     if (m->compose != POLY_COMPOSE_BRANCH && m->compose != POLY_COMPOSE_SUM) return POLY_EINVAL;
-    const int T = 1 + (m->H / m->patch) * (m->W / m->patch);
+    const int T = tokens(m);
     if (m->dtype == POLY_BF16) {
         // 16-byte vector loads along the contraction index; attention keeps a block's keys in LDS
         if (m->Dm % 8 || (3 * m->patch * m->patch) % 8 || T > 224) return POLY_EINVAL;
@@ -131,7 +203,7 @@ extern "C" const char *poly_status_string(int status)
 extern "C" size_t poly_forward_workspace_bytes(const poly_model_desc *m, int F, int R)
 {
     if (check_model(m) != POLY_OK || F < 0 || R < 0) return 0;
-    return carve_forward(m, F, R, nullptr).bytes;
+    return forward_bytes(m, F, R);
 }
 
 namespace {
@@ -161,11 +233,11 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
     for (int t = 0; t < 4; ++t)
         if (adapted && (m->targets & (1 << t)) && (!lora || !lora->At[t] || !lora->Bt[t])) return POLY_EINVAL;
     if (((uintptr_t)workspace & 255) != 0 || !workspace) return POLY_EINVAL;
-    const ForwardWs w = carve_forward(m, F, R, workspace);
+    const ForwardWs w = carve_forward(m, F, R, workspace, workspace_bytes);
     if (workspace_bytes < w.bytes) return POLY_ECAP;
 
     hipStream_t st = (hipStream_t)stream;
-    const int dt = m->dtype, D = m->D, Dm = m->Dm, T = 1 + (m->H / m->patch) * (m->W / m->patch), pd = 3 * m->patch * m->patch;
+    const int dt = m->dtype, D = m->D, Dm = m->Dm, T = tokens(m), pd = 3 * m->patch * m->patch;
     const int RP = rank_pad(m->r);
     const size_t es = elt_size(dt);
     const int *R_dev = &w.meta->R;
@@ -174,8 +246,8 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
     // tokens: x[f][0] = cls + pos[0]; x[f][1 + t] = patch_t W_pe + b_pe + pos[1 + t].  The same launch checks the CSR arrays and
     // builds the row maps (nothing before the first adapted layer needs them).
     POLY_TRY(launch_im2col(frames, w.patches, F, m->H, m->W, m->patch, dt, w.xa, base->cls, base->pos, T, D, out_merged,
-                           out_merged ? (size_t)F * K : 0, w.fl_cnt[0] ? w.fl_cnt[0] : w.fl_cnt[1], w.fl_cnt_bytes / 4, ss ? nullptr : row_offsets, adapter_ids, R, m->n_adapters, w.meta, w.frame_of_row,
-                           w.adapter_of_row, dev_status, st));
+                           out_merged ? (size_t)F * K : 0, w.fl_cnt[0] ? w.fl_cnt[0] : w.fl_cnt[1], w.fl_cnt_bytes / 4, ss ? nullptr : row_offsets,
+                           adapter_ids, R, m->n_adapters, w.meta, w.frame_of_row, w.adapter_of_row, dev_status, st));
     // The lagged loop: after the shared layers the base head scores the frames, Alg. 2 turns the scores of frame t - 1 into
     // the adapter set of frame t with its row maps -- all on this stream, no host in between.
     bool selected = ss == nullptr;
@@ -197,37 +269,48 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         POLY_TRY(launch_gemm(g, dt, st));
     }
 
-    auto flow = [&](int l0, int l1, bool ad) -> int {
+    auto flow = [&](bool ad) -> int {
         FlowArgs a = {};
-        a.T = T; a.D = D; a.Dm = Dm; a.heads = m->heads; a.layers = l1 - l0; a.eps = m->ln_eps;
+        a.T = T; a.D = D; a.Dm = Dm; a.heads = m->heads; a.eps = m->ln_eps;
         a.nb = ad && !sum ? R : F;
         a.nb_dev = !ad ? nullptr : (sum ? &w.meta->F_ok : R_dev);
         a.x_in = w.xa; a.x = ad && !sum ? w.xb : w.xa;
         a.in_map = ad && !sum ? w.frame_of_row : nullptr;
-        const size_t ld = (size_t)l0 * D, lm = (size_t)l0 * Dm, dd = (size_t)l0 * D * D, dm = (size_t)l0 * D * Dm;
-        a.ln1_g = base->ln1_g + ld; a.ln1_b = base->ln1_b + ld; a.ln2_g = base->ln2_g + ld; a.ln2_b = base->ln2_b + ld;
-        a.Wq = (const bf16_t *)base->qkv_w + 3 * dd; a.Wp = (const bf16_t *)base->proj_w + dd; a.W1 = (const bf16_t *)base->fc1_w + dm; a.W2 = (const bf16_t *)base->fc2_w + dm;
-        a.bq = base->qkv_b + 3 * ld; a.bp = base->proj_b + ld; a.b1 = base->fc1_b + lm; a.b2 = base->fc2_b + ld;
-        if (ad)
-            for (int t = 0; t < 4; ++t)
-                if (m->targets & (1 << t)) { a.At[t] = (const bf16_t *)lora->At[t]; a.Bt[t] = (const bf16_t *)lora->Bt[t]; }
         a.n_adapters = m->n_adapters; a.r = m->r; a.scale = m->lora_scale; a.adapter_of_row = w.adapter_of_row;
         a.set_off = ad && sum ? row_offsets : nullptr;
-        a.qk = w.fl_qk; a.vt = w.fl_vt; a.o = w.fl_o; a.h = w.fl_h; a.x1 = w.fl_x1; a.x2 = w.fl_x2;
-        a.counters = w.fl_cnt[ad ? 1 : 0];
-        return launch_flow(a, st);
+        const FlowBuffers &f = w.fl[ad];
+        a.qk = f.qk; a.vt = f.vt; a.o = f.o; a.h = f.h; a.x1 = f.x1; a.x2 = f.x2;
+        a.counters = w.fl_cnt[ad];
+        const int first = ad ? m->L0 : 0, last = ad ? m->L : m->L0;
+        for (int l = first; l < last; l += a.layers) {
+            a.layers = last - l < w.fl_layers[ad] ? last - l : w.fl_layers[ad];
+            const size_t ld = (size_t)l * D, lm = (size_t)l * Dm, dd = ld * D, dm = ld * Dm;
+            a.ln1_g = base->ln1_g + ld; a.ln1_b = base->ln1_b + ld; a.ln2_g = base->ln2_g + ld; a.ln2_b = base->ln2_b + ld;
+            a.Wq = (const bf16_t *)base->qkv_w + 3 * dd; a.Wp = (const bf16_t *)base->proj_w + dd;
+            a.W1 = (const bf16_t *)base->fc1_w + dm; a.W2 = (const bf16_t *)base->fc2_w + dm;
+            a.bq = base->qkv_b + 3 * ld; a.bp = base->proj_b + ld; a.b1 = base->fc1_b + lm; a.b2 = base->fc2_b + ld;
+            const size_t din[4] = {(size_t)D, (size_t)D, (size_t)D, (size_t)Dm}, dout[4] = {(size_t)3 * D, (size_t)D, (size_t)Dm, (size_t)D};
+            for (int t = 0; ad && t < 4; ++t) {
+                const size_t ranks = (size_t)(l - first) * m->n_adapters * m->r;
+                if (m->targets & (1 << t)) { a.At[t] = (const bf16_t *)lora->At[t] + ranks * din[t]; a.Bt[t] = (const bf16_t *)lora->Bt[t] + ranks * dout[t]; }
+            }
+            POLY_TRY(launch_flow(a, st));
+            a.x_in = a.x; a.in_map = nullptr;                  // the next launch continues on this one's blocks
+            a.counters += flow_counter_bytes(a.nb, m->heads) / sizeof(unsigned);
+        }
+        return POLY_OK;
     };
 
     bool qkv_done = false;                     // the qkv linear of layer l was computed by layer l - 1's row kernel
     for (int l = 0; l < m->L; ++l) {
         if (l == 0 && w.fl_cnt[0]) {
-            POLY_TRY(flow(0, m->L0, false));
+            POLY_TRY(flow(false));
             l = m->L0;
             if (l == m->L) break;
         }
         if (l == m->L0 && !selected) POLY_TRY(select_now());
         if (l == m->L0 && w.fl_cnt[1]) {
-            POLY_TRY(flow(m->L0, m->L, true));
+            POLY_TRY(flow(true));
             break;
         }
         const bool lora_on = l >= m->L0 && R > 0;
@@ -407,15 +490,13 @@ extern "C" int poly_forward(const poly_model_desc *m, const poly_base_weights *b
                         workspace, workspace_bytes, stream, nullptr);
 }
 
-static size_t stream_lag_offset(const poly_model_desc *m, int F, int R)
-{
-    return (carve_forward(m, F, R, nullptr).bytes + 255) & ~(size_t)255;
-}
+// the lagged scores take the end of the workspace, the forward what is in front of them
+static size_t stream_lag_bytes(int F, int K) { return sizeof(float) * (size_t)(F + 1) * K; }
 
 extern "C" size_t poly_stream_step_workspace_bytes(const poly_model_desc *m, int F, int R, int K)
 {
     if (check_model(m) != POLY_OK || F < 0 || R < 0 || K <= 0) return 0;
-    return stream_lag_offset(m, F, R) + sizeof(float) * (size_t)(F + 1) * K;
+    return forward_bytes(m, F, R) + stream_lag_bytes(F, K);
 }
 
 extern "C" int poly_stream_step(const poly_model_desc *m, const poly_base_weights *base, const poly_lora_weights *lora,
@@ -430,10 +511,12 @@ extern "C" int poly_stream_step(const poly_model_desc *m, const poly_base_weight
     if (F < 0 || R < 0) return POLY_EINVAL;
     if (F == 0) return POLY_OK;
     if (!workspace || ((uintptr_t)workspace & 255) != 0) return POLY_EINVAL;
-    if (workspace_bytes < poly_stream_step_workspace_bytes(m, F, R, s->K)) return POLY_ECAP;
-    StreamStep ss = {s, row_offsets, adapter_ids, counters, out_base_scores, (float *)((char *)workspace + stream_lag_offset(m, F, R))};
+    const size_t lag = stream_lag_bytes(F, s->K);
+    if (workspace_bytes < lag) return POLY_ECAP;
+    const size_t forward = (workspace_bytes - lag) & ~(size_t)255;
+    StreamStep ss = {s, row_offsets, adapter_ids, counters, out_base_scores, (float *)((char *)workspace + forward)};
     return forward_impl(m, base, lora, heads, frames, F, row_offsets, adapter_ids, R, out_logits, out_scores, out_merged, s->K, dev_status,
-                        workspace, workspace_bytes, stream, &ss);
+                        workspace, forward, stream, &ss);
 }
 
 // ------------------------------------------------------------------ isolated multi-LoRA linear
