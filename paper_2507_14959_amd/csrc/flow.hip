@@ -413,7 +413,7 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
     for (int i = 0; i < NT; ++i) {
         const int ct = tile(i);
         const f32x4 v = y[i] + bias4[i];
-        if (STAGE == 3) hb.st8(__builtin_bit_cast(u32x2_, pack4(gelu_poly4(v))), frag_off(k.rt, kh, N / 32, ct * 4 + wc, lm, g));
+        if (STAGE == 3) hb.st8(__builtin_bit_cast(u32x2_, pack4(gelu_fine4(v))), frag_off(k.rt, kh, N / 32, ct * 4 + wc, lm, g));
         else if (is_v(i)) vt.st8(__builtin_bit_cast(u32x2_, pack4(v)), (unsigned)(ct - 2 * dt) * TP * 128 + (4 * k.rt + wc) * 1024 + lane * 16 + kh * 8);
         else qk.st8(__builtin_bit_cast(u32x2_, pack4(v)), (unsigned)ct * TP * 128 + frag_off(k.rt, kh, 2, wc, lm, g));
     }
