@@ -39,7 +39,8 @@ typedef enum poly_status {
     POLY_EINVAL = -1, /* null pointer, bad shape, unsupported size or enum */
     POLY_ERANGE = -2, /* adapter id outside [0, n_adapters), offsets not monotone, R above its bound */
     POLY_ECAP = -3,   /* an output or the workspace is too small */
-    POLY_EHIP = -4    /* the HIP runtime reported an error */
+    POLY_EHIP = -4,   /* the HIP runtime reported an error */
+    POLY_ESTALL = -5  /* dev_status only: a kernel gave up waiting for its own workgroups; two calls were using one workspace at a time */
 } poly_status;
 
 enum { POLY_F32 = 0, POLY_BF16 = 1 };
@@ -119,10 +120,11 @@ int poly_select(const float *label_scores, int F, int K, const uint8_t *group_me
  *   out_merged    [F][K] float, nullable (needs heads->class_map): score of class
  *                 class_map[k][c] from row-block (f,k), maximum where adapters overlap, 0 where no
  *                 active adapter reports the class.
- *   dev_status    device int32, nullable: POLY_OK or POLY_ERANGE after the call.
+ *   dev_status    device int32, nullable: POLY_OK, POLY_ERANGE or POLY_ESTALL after the call.
  *   workspace     >= poly_forward_workspace_bytes(m, F, R) bytes, 256-byte aligned.  That size never shrinks with F or R: a
  *                 workspace for a program's largest call serves its smaller ones.  (It has room for the fastest kernels; a
  *                 smaller one is taken as long as some kernels can do with it, POLY_ECAP otherwise.)
+ *                 A workspace serves one call at a time: calls that may overlap (two streams, two threads) need one each.
  * Rows past row_offsets[F] are left untouched.  Results do not depend on where a frame sits in
  * the batch (fixed reduction order, no atomics on floating-point sums).
  * Shape limits (POLY_EINVAL otherwise): D == 64 * heads; 1 <= r <= 64; 1 <= C <= 64; H, W multiples of patch;

@@ -37,6 +37,10 @@ typedef struct poly_profile {
 int poly_profile_begin(int max_launches);
 int poly_profile_end(poly_profile *out); /* host struct */
 
+/* How often a workgroup of the task-queue kernel may look at a counter that is not there yet, in calls of the calling thread from
+ * now on; negative = the built-in limit (the default).  For tests of what a call does when that kernel gives up (POLY_ESTALL). */
+void poly_wait_limit(int looks);
+
 #ifdef __cplusplus
 }
 #endif

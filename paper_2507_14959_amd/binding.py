@@ -13,7 +13,7 @@ from typing import Dict, Optional
 import numpy as np
 import torch
 
-POLY_OK, POLY_EINVAL, POLY_ERANGE, POLY_ECAP, POLY_EHIP = 0, -1, -2, -3, -4
+POLY_OK, POLY_EINVAL, POLY_ERANGE, POLY_ECAP, POLY_EHIP, POLY_ESTALL = 0, -1, -2, -3, -4, -5
 POLY_F32, POLY_BF16 = 0, 1
 TARGETS = ("qkv", "proj", "fc1", "fc2")
 
@@ -23,7 +23,7 @@ LIB_PATH = os.path.join(_HERE, "libpoly.so")
 EXPORTS = ("poly_status_string", "poly_select_state_bytes", "poly_select", "poly_forward_workspace_bytes",
            "poly_forward", "poly_stream_step_workspace_bytes", "poly_stream_step", "poly_lora_linear_workspace_bytes",
            "poly_lora_linear", "poly_lora_linear_static", "poly_build_contexts", "poly_intra_coherence", "poly_stream_metrics",
-           "poly_profile_begin", "poly_profile_end")
+           "poly_profile_begin", "poly_profile_end", "poly_wait_limit")
 STATIC_SCRATCH_BYTES = 4 * 1024 * 1024
 STAGES = ("select", "gemm", "shrink", "attention", "layernorm", "other")
 
@@ -111,6 +111,8 @@ def lib():
         L.poly_profile_begin.argtypes = [C.c_int]
         L.poly_profile_end.restype = C.c_int
         L.poly_profile_end.argtypes = [C.POINTER(Profile)]
+        L.poly_wait_limit.restype = None
+        L.poly_wait_limit.argtypes = [C.c_int]
         _lib = L
     return _lib
 

@@ -23,7 +23,9 @@
 // Order and progress: a queue's tickets are numbered layer by layer and step by step, a task waits only for tasks with lower
 // numbers of the same queue, and a workgroup works through the tickets it has drawn in ascending order.  The lowest unfinished ticket
 // is therefore always being worked on by a running workgroup and waits for nothing, whatever other workgroups are not (yet) running:
-// every wait ends.
+// every wait ends, as long as nobody else writes the counters.  Two calls on one workspace at a time would: their results are undefined, but
+// the kernel has to come to its end all the same, so a workgroup looks at counters a limited number of times per launch (a million, about
+// a second; a whole launch takes under a millisecond), then works on without waiting and the call reports POLY_ESTALL.
 //
 // What bounds it: the chain of a block.  DeiT-tiny, one frame: 14 us per layer (row kernel + attention: 35), of which the tasks' own
 // loads, products and stores are 11 and the hand-overs 3; whole forward 449 -> 203 us, lagged loop 466 -> 199 us.  With many blocks the
@@ -36,6 +38,7 @@ namespace {
 constexpr int FL_THREADS = 512;
 constexpr int FL_MAXQ = 8;             // queues
 constexpr int FL_SC1 = 16;             // cache policy bit of a buffer access: device scope
+constexpr int FL_PATIENCE = 1 << 20;   // counter reads of a workgroup that find its inputs not there yet, per launch
 constexpr float FL_LOG2E = 1.4426950408889634f;
 
 // counters of a block, 64 bytes apart: per row tile (8 of each) F2 done, A done, P done, F1 done, then per head Q done
@@ -86,6 +89,7 @@ struct Task {
     unsigned layer;
     int b, ct, rt;                     // block, 64-column tile (A: head), row tile
     unsigned *cnt;                     // the block's counters
+    int *patience;                     // in LDS, wave 0's: how often the workgroup may still find a counter too low; < 0: given up
 };
 
 __device__ __forceinline__ void draw(const Task &t) 
@@ -101,11 +105,15 @@ __device__ __forceinline__ unsigned *counter(const Task &t, int id) { return t.c
 // Inputs ready?  The counter is read once before the weights are requested (answers come in order: behind them it would take a
 // microsecond longer), and again and again afterwards if it was too early.  By wave 0, for all: a barrier follows.
 __device__ __forceinline__ unsigned peek(const unsigned *c) { return __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void await(const unsigned *c, unsigned seen, unsigned want)
+__device__ __forceinline__ void await(const Task &t, const unsigned *c, unsigned seen, unsigned want)
 {
     while (seen < want) {
         __builtin_amdgcn_s_sleep(1);
-        seen = peek(c);
+        const unsigned now = peek(c);                          // in flight while the look is counted
+        const int left = *t.patience - 1;
+        *t.patience = left;
+        if (left < 0) break;
+        seen = now;
     }
 }
 
@@ -126,7 +134,7 @@ __device__ __forceinline__ unsigned *attention_task(const Task &k, char *lds)
     float *ml = op + 8 * 2048;                                 // [wave][32] maxima, [wave][32] sums
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lm = lane & 15, g = lane >> 4;
     const int T = p->a.T, nrt = p->nrt, TP = nrt * 32;
-    if (wave == 0) await(counter(k, C_Q + k.ct), 0, (k.layer + 1) * (3 / p->nQ) * nrt);
+    if (wave == 0) await(k, counter(k, C_Q + k.ct), 0, (k.layer + 1) * (3 / p->nQ) * nrt);
     __syncthreads();
     const size_t slot = k.layer * (size_t)p->a.nb + k.b;
     const Buf qk(p->a.qk + slot * TP * 2 * D, (unsigned)TP * 4 * D), vt(p->a.vt + slot * D * TP, (unsigned)D * TP * 2);
@@ -303,7 +311,7 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
     const float *xs = STAGE == 3 ? p->a.x1 + ld * step : first ? p->a.x_in : p->a.x2 + (ld - 1) * step;
     const Buf xb(xs + (size_t)xblk * T * D, (unsigned)T * D * 4);
     // ---- inputs
-    if (wave == 0) await(dep, seen, want);
+    if (wave == 0) await(k, dep, seen, want);
     __syncthreads();
     {
         f32x4 v[KT];
@@ -481,7 +489,7 @@ __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
     const Buf xi(xs + (size_t)xblk * T * D, (unsigned)T * D * 4), xo(xd + (size_t)b * T * D, (unsigned)T * D * 4);
     const Buf src((STAGE == 2 ? p->a.o : p->a.h) + slot * TP * K, (unsigned)TP * K * 2);
     // ---- inputs
-    if (wave == 0) await(dep, seen, want);
+    if (wave == 0) await(k, dep, seen, want);
     __syncthreads();
     bf16x8 fa[NS][2];
 #pragma unroll
@@ -581,6 +589,7 @@ __global__ __launch_bounds__(FL_THREADS, 4) void flow_kernel(const FlowParams)
 {
     extern __shared__ __attribute__((aligned(16))) char fl_lds[];
     __shared__ unsigned s_ticket;
+    __shared__ int s_patience;
     const int tid = threadIdx.x;
     int nb, nq;
     {
@@ -588,6 +597,7 @@ __global__ __launch_bounds__(FL_THREADS, 4) void flow_kernel(const FlowParams)
         const int *nb_dev = p->a.nb_dev;
         nb = p->a.nb; nq = p->a.n_queues;
         if (nb_dev) nb = min(uload(nb_dev), nb);
+        if (tid == 0) s_patience = p->a.patience;
     }
     if (nb <= 0) return;
     for (int qi = 0; qi < nq; ++qi) {
@@ -614,7 +624,7 @@ __global__ __launch_bounds__(FL_THREADS, 4) void flow_kernel(const FlowParams)
             else rem -= nbq * d1.d, stage = 4, bi = div(rem, dP), rem -= bi * dP.d;
             Task k;
             unsigned next = 0;
-            k.queue = qc; k.next = &next;
+            k.queue = qc; k.next = &next; k.patience = &s_patience;
             k.layer = layer;
             k.ct = div(rem, Div{p->drt.d, p->drt.m}); k.rt = rem - k.ct * p->nrt; k.b = qn + bi * nq;
             k.cnt = p->cnt + (size_t)k.b * p->ncnt * 16;
@@ -632,6 +642,14 @@ __global__ __launch_bounds__(FL_THREADS, 4) void flow_kernel(const FlowParams)
             ticket = __builtin_amdgcn_readfirstlane(s_ticket);
         }
         __syncthreads();                                       // (s_ticket is written again for the next queue)
+    }
+    if (tid == 0 && s_patience < 0) {                          // no later launch of the call finds a block to work on, and the caller is told
+        const ParamPtr p = params();
+        PolyMeta *meta = p->a.meta;
+        int *status = p->a.dev_status;
+        *p->a.stalled = 1;
+        meta->R = 0; meta->F_ok = 0; meta->status = POLY_ESTALL;
+        if (status) *status = POLY_ESTALL;
     }
 }
 
@@ -692,6 +710,7 @@ int launch_flow(const FlowArgs &args, hipStream_t st)
     p.a = args;
     const int nrt = (args.T + 31) / 32;
     p.nrt = nrt; p.ct_d = args.D / 64; p.ct_m = args.Dm / 64;
+    if (p.a.patience < 0) p.a.patience = FL_PATIENCE;
     p.a.n_queues = args.nb < FL_MAXQ ? args.nb : FL_MAXQ;
     p.ncnt = C_Q + args.heads;
     p.queue = args.counters;

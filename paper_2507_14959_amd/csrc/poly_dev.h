@@ -19,7 +19,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // Device-visible bookkeeping at the head of the workspace.
 struct PolyMeta {
     int32_t R;       // row_offsets[F] as read on the device (0 when the inputs are rejected)
-    int32_t status;  // POLY_OK or POLY_ERANGE
+    int32_t status;  // POLY_OK, POLY_ERANGE or POLY_ESTALL
     int32_t F_ok;    // number of frames, or 0 when the inputs are rejected
     int32_t pad[61];
 };
@@ -139,6 +139,7 @@ __device__ __forceinline__ f32x4 gelu_tab4(f32x4 x, const float *tab)
 
 // ---- launch with optional per-stage timing (profile.hip) ----
 bool poly_prof_next(int stage, hipEvent_t *a, hipEvent_t *b);
+int poly_patience();     // FlowArgs::patience of this thread's calls
 
 #define POLY_LAUNCH(stage, kernel, grid, block, st, ...)                                         \
     do {                                                                                         \
@@ -299,6 +300,10 @@ struct FlowArgs {
     const int *set_off;              // null: block b has the one term adapter_of_row[b]; else the sum of the terms [set_off[b], set_off[b + 1])
     bf16_t *qk, *vt, *o, *h;         // [layers][nb][flow_elements(T, ..)] of 2 D, D, D and Dm
     unsigned *counters;              // flow_counter_bytes, cleared by an earlier launch
+    int patience;                    // looks at a counter that is not there yet, per workgroup; < 0: as many as flow.hip finds enough
+    int *stalled;                    // set to 1 when a workgroup has run out of them, together with meta (no blocks) and dev_status
+    PolyMeta *meta;
+    int *dev_status;                 // or null
     int n_queues;                    // set by launch_flow
 };
 bool flow_supported(int T, int D, int Dm, int heads, int r, bool lora);
@@ -334,6 +339,7 @@ struct SelectFollow {
     int32_t *frame_of_row, *adapter_of_row, *dev_status;
     float *carry;
     const float *carry_src;
+    const int *stalled;              // null or != 0: the scores are not to be used (FlowArgs): POLY_ESTALL, state and carry stay
 };
 int launch_select(const float *label_scores, int F, int K, const uint8_t *group_membership, int M, const poly_select_opts *opts, void *state,
                   int32_t *row_offsets, int32_t *adapter_ids, int cap, int32_t *counters, const SelectFollow &fo, hipStream_t st);

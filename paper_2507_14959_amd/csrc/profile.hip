@@ -10,7 +10,11 @@ struct Record { int stage; hipEvent_t a, b; };
 std::vector<Record> g_pool;
 size_t g_used = 0;
 bool g_on = false;
+thread_local int t_patience = -1;
 }  // namespace
+
+int poly_patience() { return t_patience; }
+extern "C" void poly_wait_limit(int looks) { t_patience = looks; }
 
 bool poly_prof_next(int stage, hipEvent_t *a, hipEvent_t *b)
 {
