@@ -20,6 +20,9 @@
  *         W -> Wt[D_out][D_in],   A -> At[r][D_in],   B -> Bt[D_out][r].
  *     "elt" below is float for POLY_F32 and bf16 (uint16 bit pattern) for POLY_BF16; vectors
  *     (biases, LayerNorm gains and shifts, cls, pos) are always float.
+ *   - Alignment: POLY_F32 operands need no more than a float's (poly_forward with D a multiple of 256: LayerNorm gains
+ *     and shifts 16 bytes); POLY_BF16 matrices and LayerNorm gains and shifts 16 bytes, biases and other vectors of floats
+ *     a float's.  Everything on 16-byte boundaries takes the fast kernels.
  *   - Row-block b = (frame f, adapter k): frame f's adapters are
  *     adapter_ids[row_offsets[f] .. row_offsets[f+1]) -- the CSR image of the active context
  *     sets S_t of Sec. 3.3; adapter id = context id.

@@ -562,7 +562,7 @@ int lora_linear_impl(const void *X, int n_xblocks, int T, int Kdim, const void *
     hipStream_t st = (hipStream_t)stream;
     const int RP = rank_pad(r);
 
-    if (R > 0 && linear_ks_fits(n_xblocks, T, Ndim, r, R))
+    if (R > 0 && linear_ks_fits(X, n_xblocks, T, Wt, bias, Ndim, At, Bt, r, R, Y))
         return launch_linear_ks(X, n_xblocks, T, Kdim, Wt, bias, Ndim, At, Bt, n_adapters, r, scale, row_offsets, adapter_ids, R, Y, dtype, dev_status, st);
     if (R > 0 && shrink_csr_fits(n_xblocks, T, Kdim, dtype)) {
         POLY_TRY(launch_shrink_csr(X, T, Kdim, At, r, RP, scale, row_offsets, adapter_ids, n_xblocks, R, n_adapters, w.meta, w.frame_of_row,

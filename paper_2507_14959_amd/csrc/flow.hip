@@ -261,7 +261,7 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
         for (int i = 0; i < NT; ++i) {
             const float *bp = bias + tile(i) * 64;
             if (is_v(i)) { const float bv = bp[lm]; bias4[i] = f32x4{bv, bv, bv, bv}; }
-            else bias4[i] = *(const f32x4 *)(bp + 4 * g);
+            else bias4[i] = *(const f32x4_u *)(bp + 4 * g);
         }
     };
     if (!LEAN) load_bias();
@@ -270,7 +270,7 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
     f32x4 gn[KT], sh[KT];
     auto load_gain = [&]() {
 #pragma unroll
-        for (int i = 0; i < KT; ++i) { gn[i] = *(const f32x4 *)(gain + 64 * i); sh[i] = *(const f32x4 *)(shift + 64 * i); }
+        for (int i = 0; i < KT; ++i) { gn[i] = *(const f32x4_u *)(gain + 64 * i); sh[i] = *(const f32x4_u *)(shift + 64 * i); }
     };
     if (!LEAN) load_gain();
     // operands of the low-rank terms of this block's adapter(s); those of the first one are requested here
@@ -456,7 +456,7 @@ __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
     // waves 4 j .. 4 j + 3 finish the subtiles of tile j: rows 16 fm .., columns 16 fn ..
     const int fm = (wave >> 1) & 1, fn = wave & 1, trow = k.rt * 32 + 16 * fm + lm, fcol = (k.ct * NT + (wave >> 2)) * 32 + 16 * fn;
     const bool fin = wave < 4 * NT;
-    const f32x4 bias4 = *(const f32x4 *)((STAGE == 2 ? p->a.bp : p->a.b2) + ld * D + (fin ? fcol : 0) + 4 * g);
+    const f32x4 bias4 = *(const f32x4_u *)((STAGE == 2 ? p->a.bp : p->a.b2) + ld * D + (fin ? fcol : 0) + 4 * g);
     constexpr int TGT = STAGE == 2 ? 1 : 3;
     const bf16_t *At = p->a.At[TGT], *Bt = p->a.Bt[TGT];
     const int *set_off = p->a.set_off, *adapter = p->a.adapter_of_row, *in_map = p->a.in_map;

@@ -757,7 +757,7 @@ int launch_gemm(const GemmArgs &g, int dtype, hipStream_t st)
         gf.Tb = g.T; gf.nb = g.n_in;
         gf.T = (int)rows; gf.n_in = 1;          // (Tout stays the block length: it places the output blocks)
     }
-    if (!bf16 || g.K % 64 != 0 || g.N % 8 != 0) return launch_gemm_ks(gf, dtype, st);
+    if (!bf16 || g.K % 64 != 0 || g.N % 8 != 0 || !gemm_aligned(g)) return launch_gemm_ks(gf, dtype, st);
     // a long contraction on fewer 128 x 128 tiles than half the CUs: smaller tiles and a split contraction (3 frames of the
     // 768-wide backbone: 30 tiles for proj and fc2, 90 and 120 for qkv and fc1; 1338 -> 906 us per forward)
     if (g.K >= 512 && (long)gf.n_in * ((gf.T + 127) / 128) * ((g.N + 127) / 128) < 128) return launch_gemm_ks(gf, dtype, st);

@@ -46,8 +46,10 @@ __device__ __forceinline__ int uload(const int *p) { return *(const int __attrib
 constexpr int KS_NSMAX = 3;
 
 // MI x NI subtiles of 32 x 32 per tile.  ns: ring stages per wave.  SHRINK: S = scale * x At_k^T (weights of the output block's own
-// adapter, row tiles inside blocks, columns past the rank zero) instead of a linear with shared weights.
-template <typename T, int MI, int NI, bool SHRINK>
+// adapter, row tiles inside blocks, columns past the rank zero) instead of a linear with shared weights.  AL: every pointer is on a
+// 16-byte boundary; else the operands are fetched and the results stored element by element (the addresses the caller gave need no more
+// than the alignment of an element; loads to LDS need 16 bytes).
+template <typename T, int MI, int NI, bool SHRINK, bool AL>
 __global__ __launch_bounds__(256) void gemm_ks_kernel(const GemmArgs g, int tiles_m, int tiles_n, int ns)
 {
     typedef Elt<T> E;
@@ -94,17 +96,29 @@ __global__ __launch_bounds__(256) void gemm_ks_kernel(const GemmArgs g, int tile
     const int tail = g.K - (nk - 1) * BK;                  // elements in the last k-tile
     const int adj0 = min(c0, tail / V - 1) - c0, adj1 = min(c1, tail / V - 1) - c1;
     char *ring = ks_lds + wave * ns * STAGE;
+    // 16 bytes of this lane's: to LDS at lds + 16 lane
+    auto fetch = [&](const char *base, unsigned off, char *lds) {
+        if constexpr (AL) {
+            glds16_s(base, off, __builtin_amdgcn_readfirstlane(lds_addr_of(lds)));
+        } else {
+            const T *src = (const T *)(base + off);
+            frag v;
+#pragma unroll
+            for (int z = 0; z < V; ++z) v[z] = src[z];
+            *(frag *)(lds + lane * 16) = v;
+        }
+    };
     auto issue = [&](int i) {
         const int kt = wave + 4 * i;
         const bool last = kt == nk - 1;                    // uniform
-        const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_addr_of(ring + (i % ns) * STAGE));
+        char *st = ring + (i % ns) * STAGE;
         const unsigned e0 = (unsigned)(c0 + (last ? adj0 : 0)) * 16, e1 = (unsigned)(c1 + (last ? adj1 : 0)) * 16;
 #pragma unroll
         for (int q = 0; q < BM / 8; ++q)
-            glds16_s((const char *)A + (size_t)kt * 128, (unsigned)min(8 * q + lr, Tlim - 1 - t0) * rowb + ((q & 1) ? e1 : e0), lds0 + q * 1024);
+            fetch((const char *)A + (size_t)kt * 128, (unsigned)min(8 * q + lr, Tlim - 1 - t0) * rowb + ((q & 1) ? e1 : e0), st + q * 1024);
 #pragma unroll
         for (int q = 0; q < BN / 8; ++q)
-            glds16_s((const char *)W + (size_t)kt * 128, (unsigned)min(8 * q + lr, nw - 1 - n0) * rowb + ((q & 1) ? e1 : e0), lds0 + (BM / 8 + q) * 1024);
+            fetch((const char *)W + (size_t)kt * 128, (unsigned)min(8 * q + lr, nw - 1 - n0) * rowb + ((q & 1) ? e1 : e0), st + (BM / 8 + q) * 1024);
     };
     const int npro = min(ns, steps);
     for (int i = 0; i < npro; ++i) issue(i);
@@ -115,7 +129,7 @@ __global__ __launch_bounds__(256) void gemm_ks_kernel(const GemmArgs g, int tile
     const int tw = t0 + 32 * fi, nc = n0 + 32 * fj;        // its first row (in the run or the block) and column
     const bool fin = wave < NF && tw < Tlim && nc < g.N;
     const int b_lo = flat ? tw / Tblk : xb;
-    const bool has_lora = !SHRINK && g.S && g.adapter_of_out, vec = g.N % 4 == 0;
+    const bool has_lora = !SHRINK && g.S && g.adapter_of_out, vec = AL && g.N % 4 == 0;
     const int rch = lane & 7, rrow = lane >> 3;            // read-back mapping: 8 lanes x 16 bytes cover a row of the subtile
     const int col = nc + 4 * rch;
     frag pre_s[16 / (2 * V)], pre_w[16 / (2 * V)];         // operands of ranks [0, 16) of the first term
@@ -127,7 +141,7 @@ __global__ __launch_bounds__(256) void gemm_ks_kernel(const GemmArgs g, int tile
         const int c = min(nc + lm, g.N - 1), j0 = s0 + lh * V;
         const T *p = (const T *)g.Bt + ((size_t)k_ad * g.N + c) * g.r;
         frag f = zero;
-        if (g.r % V == 0) {
+        if (AL && g.r % V == 0) {
             f = *(const frag *)(p + min(j0, g.r - V));
             if (j0 + V > g.r) f = zero;
         } else {
@@ -250,7 +264,7 @@ __global__ __launch_bounds__(256) void gemm_ks_kernel(const GemmArgs g, int tile
     // rows [lo, hi) of the subtile -> output block ob; row 0 of the subtile is row trow0 of the block
     auto emit = [&](const f32x16 &c, int ob, int trow0, int lo, int hi) {
         const long obase = ((long)ob * g.Tout + g.t_off + trow0) * g.N;
-        if (!vec) {                                        // N not a multiple of 4: element by element
+        if (!vec) {                                        // N not a multiple of 4, or an address no multiple of 16: element by element
             const int row = lm;
             if (row < lo || row >= hi) return;
             const int rb = (g.mode == EPI_RESID && g.res && g.res_block_of_out) ? g.res_block_of_out[ob] : ob;
@@ -629,14 +643,14 @@ __global__ __launch_bounds__(256) void linear_ks_kernel(const LinearParams g, in
     }
 }
 
-template <typename T, int MI, int NI, bool SHRINK> int launch_ks(const GemmArgs &g, hipStream_t st)
+template <typename T, int MI, int NI, bool SHRINK, bool AL> int launch_ks_t(const GemmArgs &g, hipStream_t st)
 {
     constexpr int STAGE = 32 * (MI + NI) * 128, BK = 8 * Elt<T>::V, RED = 4 * MI * NI * 4096;
     const int nk = (g.K + BK - 1) / BK;
     int ns = (nk + 3) / 4 < KS_NSMAX ? (nk + 3) / 4 : KS_NSMAX;   // no more stages than a wave has k-tiles: short contractions leave room for other workgroups
     while (4 * ns * STAGE > 160 * 1024) --ns;
     const int lds = 4 * ns * STAGE > RED ? 4 * ns * STAGE : RED;
-    auto kern = gemm_ks_kernel<T, MI, NI, SHRINK>;
+    auto kern = gemm_ks_kernel<T, MI, NI, SHRINK, AL>;
     static bool attr_set = false;       // raising the dynamic LDS limit is a per-kernel, process-wide setting
     if (!attr_set) {
         if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) return POLY_EHIP;
@@ -649,7 +663,17 @@ template <typename T, int MI, int NI, bool SHRINK> int launch_ks(const GemmArgs 
     return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
 }
 
+template <typename T, int MI, int NI, bool SHRINK> int launch_ks(const GemmArgs &g, hipStream_t st)
+{
+    return gemm_aligned(g) ? launch_ks_t<T, MI, NI, SHRINK, true>(g, st) : launch_ks_t<T, 1, 1, SHRINK, false>(g, st);
+}
+
 }  // namespace
+
+bool gemm_aligned(const GemmArgs &g)
+{
+    return aligned16(g.A) && aligned16(g.Wt) && aligned16(g.bias) && aligned16(g.S) && aligned16(g.Bt) && aligned16(g.out) && aligned16(g.res) && aligned16(g.pos);
+}
 
 // Tile by the time of the busiest CU: rounds of tiles over the 256 CUs, each the larger of its loads through the CU's load path
 // (about 40 bytes per clock) and its products, plus what a tile costs whatever its size (first round trip, partial sums, stores).
@@ -704,8 +728,12 @@ int linear_ks_tile(long F, int T, int N)
 }
 }  // namespace
 
-// ranks: four slots of 16 at most; CSR: every workgroup reads all of it, four words per lane at most
-bool linear_ks_fits(int F, int T, int N, int r, int R) { return r <= 64 && F + (long)R <= 1024 && linear_ks_tile(F, T, N) != 0; }
+// ranks: four slots of 16 at most; CSR: every workgroup reads all of it, four words per lane at most; every address a multiple of 16
+bool linear_ks_fits(const void *X, int F, int T, const void *W, const float *bias, int N, const void *At, const void *Bt, int r, int R, const void *Y)
+{
+    return r <= 64 && F + (long)R <= 1024 && linear_ks_tile(F, T, N) != 0 && aligned16(X) && aligned16(W) && aligned16(bias) && aligned16(At) &&
+           aligned16(Bt) && aligned16(Y);
+}
 
 int launch_linear_ks(const void *X, int F, int T, int K, const void *W, const float *bias, int N, const void *At, const void *Bt, int n_adapters,
                      int r, float scale, const int *off, const int *ids, int R, void *Y, int dtype, int *dev_status, hipStream_t st)

@@ -13,6 +13,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));   // the caller's vectors of floats: no more than a float's alignment
 
 #define POLY_WAVE 64
 
@@ -196,9 +197,11 @@ struct GemmArgs {
 };
 
 int launch_gemm(const GemmArgs &g, int dtype, hipStream_t st);
-int launch_gemm_ks(const GemmArgs &g, int dtype, hipStream_t st);    // small calls and fp32 (gemm_ks.hip); called by launch_gemm
+int launch_gemm_ks(const GemmArgs &g, int dtype, hipStream_t st);    // small calls, fp32 and any alignment (gemm_ks.hip); called by launch_gemm
+bool gemm_aligned(const GemmArgs &g);                                // every address a multiple of 16
+inline bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 // the isolated linear of a small call in one launch (gemm_ks.hip): CSR check, shrink, product and expand
-bool linear_ks_fits(int F, int T, int N, int r, int R);
+bool linear_ks_fits(const void *X, int F, int T, const void *W, const float *bias, int N, const void *At, const void *Bt, int r, int R, const void *Y);
 int launch_linear_ks(const void *X, int F, int T, int K, const void *W, const float *bias, int N, const void *At, const void *Bt, int n_adapters,
                      int r, float scale, const int *off, const int *ids, int R, void *Y, int dtype, int *dev_status, hipStream_t st);
 int launch_shrink_f32(const float *X, int T, int K, const float *At, int r, int RP, float scale, int n_out, const int *n_out_dev,
