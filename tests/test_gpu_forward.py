@@ -55,7 +55,8 @@ def test_small_models_all_target_sets(dtype, targets, L0, r):
     (128, 2, 384, 64, 8, 3, 0),     # Dm = 6 chunks: the last feed-forward item and the second qkv item share a stage of the weight ring
 ])
 def test_row_kernels_all_widths(D, heads, Dm, hw, r, targets, L0):
-    """bf16 models whose layers run in the fused row kernels (no adapters on fc1 / fc2): every tile width, ragged tiles."""
+    """bf16 models that the fused row kernels take (no adapters on fc1 / fc2): every tile width, ragged tiles.  (So few blocks run as tasks;
+    test_gpu_layer_kernels.py has the row kernels on the same cases.)"""
     cfg, w, frames, off, ids = synth.make_small_case(60 + D + r, dtype=synth.DT_BF16, targets=targets, L=4, F=4, r=r, max_set=3,
                                                       n_adapters=5, D=D, heads=heads, Dm=Dm, hw=hw, patch=8)
     compare(cfg, w, frames, off, ids, L0, K=cfg.n_adapters * cfg.C)
@@ -77,7 +78,8 @@ def test_wide_path_widths(D, heads, Dm, hw, r, targets, L0):
 @pytest.mark.parametrize("D,heads,Dm,hw,r,targets,L0", [(64, 1, 192, 64, 16, 1, 1), (128, 2, 384, 64, 8, 3, 0), (192, 3, 768, 40, 8, 3, 2)])
 def test_row_kernels_repeat_bitwise(D, heads, Dm, hw, r, targets, L0):
     """The fused row kernels hand LDS stages from a stream wave to the computing waves by hand-counted waits: a stage that is
-    refilled one step early shows up as run-to-run differences long before it shows up as a wrong answer."""
+    refilled one step early shows up as run-to-run differences long before it shows up as a wrong answer.  (So few blocks run as tasks, with
+    the same symptom for a task that starts early; test_gpu_layer_kernels.py repeats the row kernels.)"""
     cfg, w, frames, off, ids = synth.make_small_case(60 + D + r, dtype=synth.DT_BF16, targets=targets, L=4, F=4, r=r, max_set=3,
                                                       n_adapters=5, D=D, heads=heads, Dm=Dm, hw=hw, patch=8)
     model = binding.DeviceModel(cfg, w, L0=L0)
@@ -254,7 +256,8 @@ def test_lora_scale_and_layernorm_eps_other_than_the_defaults(D, heads, Dm, hw, 
 
 def test_rank_outside_the_row_layer_kernel_takes_the_single_linear_and_mlp_kernels():
     """Adapters on qkv and proj with rank 20 at D = 192: the one-launch-per-layer kernel refuses the rank, so proj runs as a GEMM
-    with the shrink kernel and the MLP half in the fused MLP kernel."""
+    with the shrink kernel and the MLP half in the fused MLP kernel.  (Not for so few blocks, which run as tasks: the kernels named here run
+    in the test of the same case in test_gpu_layer_kernels.py.)"""
     cfg, w, frames, off, ids = synth.make_small_case(140, dtype=synth.DT_BF16, targets=3, L=3, F=5, r=20, max_set=3, n_adapters=4,
                                                       D=192, heads=3, Dm=768, hw=72, patch=8)     # T = 82: a full and a ragged tile
     compare(cfg, w, frames, off, ids, 0, K=cfg.n_adapters * cfg.C)
@@ -276,8 +279,8 @@ def test_sum_composition_small_models_all_target_sets(dtype, targets, L0, r):
 
 
 @pytest.mark.parametrize("D,heads,Dm,hw,r,targets,L0", [
-    (192, 3, 768, 72, 8, 3, 2),      # DeiT-tiny widths, T = 82: shared layers in the row kernels, adapted ones on the GEMM path
-    (192, 3, 768, 72, 16, 1, 0),     # adapters on qkv only: proj + MLP of an adapted layer stay in the row kernel
+    (192, 3, 768, 72, 8, 3, 2),      # DeiT-tiny widths, T = 82 (few blocks: as tasks; by layer in test_gpu_layer_kernels.py)
+    (192, 3, 768, 72, 16, 1, 0),     # adapters on qkv only (as above)
     (256, 4, 1024, 72, 16, 15, 1),   # wide path throughout
     (768, 12, 1024, 64, 16, 15, 0),  # ViT-base width: the large GEMM tiles with summed terms
 ])
