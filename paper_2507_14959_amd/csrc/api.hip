@@ -25,16 +25,17 @@ struct FlowSegment {
     int blocks, layers;                     // 0 blocks: this segment may not
 };
 
-// blocks up to which a segment may: up to 140 tiles of 32 rows where the row kernel is the alternative, 320 where the GEMM path is (ranks
-// it does not take, adapters on the MLP, summed terms).  DeiT-tiny, twelve layers: 20 blocks of 197 tokens 482 against 491 us, 24 blocks 519
-// against 502; 64 blocks of 50 tokens 404 against 435, 96 blocks 532 against 462; summed terms on 32 blocks of 197 tokens 673 against 832,
-// on 48 blocks 945 against 902.
+// blocks up to which a segment may: up to 140 tiles of 32 rows where the row kernel is the alternative, 270 where the GEMM path is (ranks
+// it does not take, adapters on the MLP, summed terms).  DeiT-tiny, twelve layers, as tasks / layer by layer: 18 blocks of 197 tokens (126
+// tiles) 469 / 487 us, 20 (140) 494 / 491, 24 (168) 509 / 503, 32 (224) 624 / 509; 70 blocks of 50 tokens (140) 427 / 438, 96 (192) 533 / 462;
+// GEMM path, rank 32: 32 blocks of 197 tokens (224) 644 / 748, 45 (315) 883 / 791; summed terms: 678 / 835 and 936 / 895, 60 blocks of 113
+// tokens (240) 729 / 828, 80 (320) 894 / 871.
 int flow_limit(const poly_model_desc *m, bool adapted)
 {
     const int T = tokens(m), r = adapted ? m->r : 0, tgt = adapted ? m->targets & 15 : 0;
     if (m->dtype != POLY_BF16 || !flow_supported(T, m->D, m->Dm, m->heads, r, tgt != 0)) return 0;
     const bool row_kernel = !(tgt & 12) && !(adapted && m->compose == POLY_COMPOSE_SUM && tgt) && rowlayer_supported(m->D, m->Dm, tgt ? r : 0);
-    return (row_kernel ? 140 : 320) / ((T + 31) / 32);
+    return (row_kernel ? 140 : 270) / ((T + 31) / 32);
 }
 
 // of a call of F frames and R row-blocks; capped: of the largest call with no more frames and row-blocks that still may
