@@ -53,7 +53,6 @@ FlowSegment flow_segment(const poly_model_desc *m, int F, int R, bool adapted, b
 // 209, 105, 70 MB (491), 24 blocks of 113 tokens with summed terms 429, 429, 447 with 155, 78, 52 MB (707 on the GEMM path).
 constexpr int FLOW_MIN_LAYERS = 4;
 constexpr size_t FLOW_BYTES = (size_t)128 << 20;
-constexpr size_t FL_HEAD = 64;
 
 struct FlowBuffers {
     bf16_t *qk, *vt, *o, *h;
@@ -91,9 +90,9 @@ struct ForwardWs {
     size_t fixed, bytes;                    // up to xb; all of it: what a call needs at least
     int fl_layers[2];                       // layers per launch of flow.hip in the shared and in the adapted layers (0: not there)
     FlowBuffers fl[2];                      // in the place of u .. patches: the patches are embedded before the first launch
-    unsigned *fl_head;                      // behind everything else: FL_HEAD bytes whose first word a launch sets when it gives up ..
-    unsigned *fl_cnt[2];                    // .. and the counters of its launches
-    size_t fl_clear_bytes;                  // of them all
+    unsigned *fl_cnt[2];                    // counters of its launches, behind everything else
+    unsigned *fl_clear;                     // where they start
+    size_t fl_clear_bytes;                  // of both
 };
 
 // `bytes`: what there is.  The layers run as tasks where it holds their buffers too, which a workspace of poly_forward_workspace_bytes for
@@ -119,12 +118,11 @@ ForwardWs carve_forward(const poly_model_desc *m, int F, int R, void *base, size
     w.bytes = c.off;
 
     const FlowSegment seg[2] = {flow_segment(m, F, R, false, false), flow_segment(m, F, R, true, false)};
-    const size_t cnt = FL_HEAD + flow_counters(m, seg[0]) + flow_counters(m, seg[1]);
-    if (cnt == FL_HEAD || bytes < w.bytes + cnt) return w;
+    const size_t cnt = flow_counters(m, seg[0]) + flow_counters(m, seg[1]);
+    if (cnt == 0 || bytes < w.bytes + cnt) return w;
     const size_t end = (bytes - cnt) & ~(size_t)255;                       // the counters' place
     if (end < w.bytes) return w;
-    w.fl_head = (unsigned *)((char *)base + end);
-    size_t at = FL_HEAD;
+    w.fl_clear = (unsigned *)((char *)base + end);
     for (int a = 0; a < 2; ++a) {
         if (seg[a].blocks == 0) continue;
         const int least = flow_min_layers(seg[a]);
@@ -139,9 +137,8 @@ ForwardWs carve_forward(const poly_model_desc *m, int F, int R, void *base, size
         Carver cf{(char *)base, w.fixed};
         w.fl[a] = carve_flow(m, (size_t)seg[a].blocks * n, cf);
         w.fl_layers[a] = n;
-        w.fl_cnt[a] = w.fl_head + at / sizeof(unsigned);
-        at += flow_counter_bytes(seg[a].blocks, m->heads) * (size_t)((seg[a].layers + n - 1) / n);
-        w.fl_clear_bytes = at;
+        w.fl_cnt[a] = w.fl_clear + w.fl_clear_bytes / sizeof(unsigned);
+        w.fl_clear_bytes += flow_counter_bytes(seg[a].blocks, m->heads) * (size_t)((seg[a].layers + n - 1) / n);
     }
     return w;
 }
@@ -151,7 +148,7 @@ ForwardWs carve_forward(const poly_model_desc *m, int F, int R, void *base, size
 size_t forward_bytes(const poly_model_desc *m, int F, int R)
 {
     const ForwardWs w = carve_forward(m, F, R, nullptr, 0);
-    size_t end = w.bytes, cnt = FL_HEAD;
+    size_t end = w.bytes, cnt = 0;
     for (int a = 0; a < 2; ++a) {
         const FlowSegment s = flow_segment(m, F, R, a == 1, true);
         if (s.blocks == 0) continue;
@@ -160,7 +157,7 @@ size_t forward_bytes(const poly_model_desc *m, int F, int R)
         if (w.fixed + want > end) end = w.fixed + want;
         cnt += flow_counters(m, s);
     }
-    return cnt > FL_HEAD ? end + align_up(cnt) : end;
+    return end + align_up(cnt);
 }
 
 int check_model(const poly_model_desc *m)
@@ -250,7 +247,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
     // tokens: x[f][0] = cls + pos[0]; x[f][1 + t] = patch_t W_pe + b_pe + pos[1 + t].  The same launch checks the CSR arrays and
     // builds the row maps (nothing before the first adapted layer needs them).
     POLY_TRY(launch_im2col(frames, w.patches, F, m->H, m->W, m->patch, dt, w.xa, base->cls, base->pos, T, D, out_merged,
-                           out_merged ? (size_t)F * K : 0, w.fl_head, w.fl_clear_bytes / sizeof(unsigned), ss ? nullptr : row_offsets,
+                           out_merged ? (size_t)F * K : 0, w.fl_clear, w.fl_clear_bytes / sizeof(unsigned), ss ? nullptr : row_offsets,
                            adapter_ids, R, m->n_adapters, w.meta, w.frame_of_row, w.adapter_of_row, dev_status, st));
     // The lagged loop: after the shared layers the base head scores the frames, Alg. 2 turns the scores of frame t - 1 into
     // the adapter set of frame t with its row maps -- all on this stream, no host in between.
@@ -261,8 +258,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         POLY_TRY(launch_base_head(w.xa, T, D, base->lnf_g, base->lnf_b, m->ln_eps, s->base_w, s->base_b, s->K, F, ss->lag,
                                   ss->out_base_scores, s->carry, dt, st));
         // the selection also writes the row maps and carries the last frame's scores to the next call: two launches less
-        const SelectFollow fo = {w.meta, w.frame_of_row, w.adapter_of_row, dev_status, s->carry, ss->lag + (size_t)F * s->K,
-                                 w.fl_clear_bytes ? (const int *)w.fl_head : nullptr};
+        const SelectFollow fo = {w.meta, w.frame_of_row, w.adapter_of_row, dev_status, s->carry, ss->lag + (size_t)F * s->K};
         return launch_select(ss->lag, F, s->K, s->group_membership, s->M, &s->opts, s->state, ss->row_offsets, ss->adapter_ids, R, ss->counters,
                              fo, st);
     };
@@ -286,7 +282,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         const FlowBuffers &f = w.fl[ad];
         a.qk = f.qk; a.vt = f.vt; a.o = f.o; a.h = f.h; a.x1 = f.x1; a.x2 = f.x2;
         a.counters = w.fl_cnt[ad];
-        a.patience = poly_patience(); a.stalled = (int *)w.fl_head; a.meta = w.meta; a.dev_status = dev_status;
+        a.patience = poly_patience(); a.meta = w.meta; a.dev_status = dev_status;
         const int first = ad ? m->L0 : 0, last = ad ? m->L : m->L0;
         for (int l = first; l < last; l += a.layers) {
             a.layers = last - l < w.fl_layers[ad] ? last - l : w.fl_layers[ad];

@@ -647,8 +647,7 @@ __global__ __launch_bounds__(FL_THREADS, 4) void flow_kernel(const FlowParams)
         const ParamPtr p = params();
         PolyMeta *meta = p->a.meta;
         int *status = p->a.dev_status;
-        *p->a.stalled = 1;
-        meta->R = 0; meta->F_ok = 0; meta->status = POLY_ESTALL;
+        meta->stalled = 1; meta->R = 0; meta->F_ok = 0; meta->status = POLY_ESTALL;
         if (status) *status = POLY_ESTALL;
     }
 }

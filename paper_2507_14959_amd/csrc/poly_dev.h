@@ -22,7 +22,8 @@ struct PolyMeta {
     int32_t R;       // row_offsets[F] as read on the device (0 when the inputs are rejected)
     int32_t status;  // POLY_OK, POLY_ERANGE or POLY_ESTALL
     int32_t F_ok;    // number of frames, or 0 when the inputs are rejected
-    int32_t pad[61];
+    int32_t stalled; // 1 when the task queue has given up waiting in this call (flow.hip): cleared by the first launch of a forward
+    int32_t pad[60];
 };
 
 __device__ __forceinline__ float wave_sum(float v)
@@ -303,9 +304,8 @@ struct FlowArgs {
     bf16_t *qk, *vt, *o, *h;         // [layers][nb][flow_elements(T, ..)] of 2 D, D, D and Dm
     unsigned *counters;              // flow_counter_bytes, cleared by an earlier launch
     int patience;                    // looks at a counter that is not there yet, per workgroup; < 0: as many as flow.hip finds enough
-    int *stalled;                    // set to 1 when a workgroup has run out of them, together with meta (no blocks) and dev_status
-    PolyMeta *meta;
-    int *dev_status;                 // or null
+    PolyMeta *meta;                  // a workgroup that has run out of them sets stalled, no blocks, and the status here ..
+    int *dev_status;                 // .. and here (or null)
     int n_queues;                    // set by launch_flow
 };
 bool flow_supported(int T, int D, int Dm, int heads, int r, bool lora);
@@ -335,13 +335,12 @@ int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_
                      int dtype, hipStream_t st);
 
 // poly_select with what the lagged loop needs right behind it done in the same launch (select.hip): meta != null: the row maps and
-// the bookkeeping words of the CSR arrays just written; carry != null: K floats carry_src -> carry
+// the bookkeeping words of the CSR arrays just written (nothing is selected and state and carry stay where meta->stalled is set); carry != null: K floats carry_src -> carry
 struct SelectFollow {
     PolyMeta *meta;
     int32_t *frame_of_row, *adapter_of_row, *dev_status;
     float *carry;
     const float *carry_src;
-    const int *stalled;              // null or != 0: the scores are not to be used (FlowArgs): POLY_ESTALL, state and carry stay
 };
 int launch_select(const float *label_scores, int F, int K, const uint8_t *group_membership, int M, const poly_select_opts *opts, void *state,
                   int32_t *row_offsets, int32_t *adapter_ids, int cap, int32_t *counters, const SelectFollow &fo, hipStream_t st);

@@ -84,6 +84,7 @@ __global__ void im2col_kernel(const T *frames, T *patches, int F, int H, int W, 
     }
     for (size_t idx = gtid; idx < n_merged; idx += gsz) merged[idx] = 0.f;
     for (size_t idx = gtid; idx < n_zero; idx += gsz) zero[idx] = 0u;
+    if (gtid == 0 && pa.meta) pa.meta->stalled = 0;
 }
 
 // ------------------------------------------------------------------ LayerNorm

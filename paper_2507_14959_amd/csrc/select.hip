@@ -301,19 +301,18 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float *scores
         }
     }
     __syncthreads();
-    const bool stalled = fo.stalled && *fo.stalled;
     if (tid == 0) {
         counters[0] = total_s;
         counters[1] = unc_s;
         if (fo.meta) {                                         // ids and offsets are valid by construction; only the capacity can be exceeded
-            const bool bad = total_s > cap || stalled;
+            const bool stalled = fo.meta->stalled != 0, bad = total_s > cap || stalled;
             fo.meta->R = bad ? 0 : total_s;
             fo.meta->F_ok = bad ? 0 : F;
             fo.meta->status = stalled ? POLY_ESTALL : bad ? POLY_ERANGE : POLY_OK;
             if (fo.dev_status) *fo.dev_status = fo.meta->status;
         }
     }
-    if (stalled) return;
+    if (fo.meta && fo.meta->stalled) return;
     if (wave == 0 && state && F > 0) {
         uint64_t ids = 0;
         for (uint64_t s = prevS; s; s &= s - 1) ids |= 1ull << order[__ffsll((unsigned long long)s) - 1];
