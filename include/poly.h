@@ -129,7 +129,9 @@ int poly_select(const float *label_scores, int F, int K, const uint8_t *group_me
  *                 smaller one is taken as long as some kernels can do with it, POLY_ECAP otherwise.)
  *                 A workspace serves one call at a time: calls that may overlap (two streams, two threads) need one each.
  * Rows past row_offsets[F] are left untouched.  Results do not depend on where a frame sits in
- * the batch (fixed reduction order, no atomics on floating-point sums).
+ * the batch (fixed reduction order, no atomics on floating-point sums), and the same call gives the same bits again.
+ * Calls of another F, another bound R or a workspace below poly_forward_workspace_bytes may run in other kernels, which sum
+ * in other orders: equal within rounding, not bit for bit.  (Also poly_lora_linear: n_xblocks, R and address alignment.)
  * Shape limits (POLY_EINVAL otherwise): D == 64 * heads; 1 <= r <= 64; 1 <= C <= 64; H, W multiples of patch;
  * POLY_BF16: T = 1 + (H/patch)(W/patch) <= 224 tokens (a block's keys stay on chip), Dm % 8 == 0 and
  * (3 * patch * patch) % 8 == 0 (16-byte loads along the contraction index); POLY_F32: both % 4 == 0.

@@ -13,12 +13,12 @@
 // each cut into tasks of 32 rows x 64 columns (A: 32 queries), so that one block of 197 tokens already gives 21 to 84 tasks a step.
 // The weights of a task are requested before its inputs are waited for.
 //
-// Passing data between XCDs, whose L2s do not see each other's writes, without fences (a device-scope release / acquire pair takes
-// 33 us here, a counted hand-over of 4 KB 1.0 to 2.0 us): results are stored at device scope (sc1: through to memory), the stores are
-// waited for, then the task is counted with an atomic; and every layer has buffers of its own, so that no address is read by this
-// launch before it has been written for good, and no L1 or L2 can hold an old copy of it.  Every 128-byte line is written by the tasks
-// of one counter only, so a line is complete when anything in it is read.  Loads are therefore ordinary ones, and the many tasks that
-// read the same rows hit the L2.  (With loads at device scope, past the L2, 8 frames read 58 MB per layer from memory.)
+// Passing data between XCDs, whose L2s do not see each other's writes, without fences: results are stored at device scope (sc1: through to
+// memory), the stores are waited for, then the task is counted with an atomic; and every layer of a launch has buffers of its own, so that
+// no address is read by this launch before it has been written for good, and no L1 or L2 can hold an old copy of it.  Every 128-byte line
+// is written by the tasks of one counter only, so a line is complete when anything in it is read.  Loads are therefore ordinary ones, and
+// the many tasks that read the same rows hit the L2.  4 KB change hands in 1.2 us this way between two workgroups of an idle chip, in 2.2 us
+// with release and acquire fences, which moreover empty the L2 that holds the weights.
 //
 // Order and progress: a queue's tickets are numbered layer by layer and step by step, a task waits only for tasks with lower
 // numbers of the same queue, and a workgroup works through the tickets it has drawn in ascending order.  The lowest unfinished ticket
@@ -27,9 +27,10 @@
 // the kernel has to come to its end all the same, so a workgroup looks at counters a limited number of times per launch (a million, about
 // a second; a whole launch takes under a millisecond), then works on without waiting and the call reports POLY_ESTALL.
 //
-// What bounds it: the chain of a block.  DeiT-tiny, one frame: 14 us per layer (row kernel + attention: 35), of which the tasks' own
-// loads, products and stores are 11 and the hand-overs 3; whole forward 449 -> 203 us, lagged loop 466 -> 199 us.  With many blocks the
-// weights that every 32-row task pulls through its CU's load path bound it, and kernels with larger tiles take over (api.hip).
+// What bounds it: the chain of a block, five steps per layer with a hand-over each.  DeiT-tiny, one live frame: 15.7 us per layer (two launches
+// of ten and two layers), the matrix unit busy 0.7 % of the time; the lagged loop takes 209 us instead of the 473 of row kernels and
+// attention launches.  With many blocks the weights that every 32-row task pulls through its CU's load path bound it, and kernels with
+// larger tiles take over (api.hip).
 #include "poly_dev.h"
 #include "rowtile.h"
 
@@ -665,7 +666,8 @@ template <int KD, int NQ, int N1, int NP, bool SUM> int launch_flow_t(FlowParams
     p.drt = make_div(nrt);
     p.tpb = p.dQ.d + p.dA.d + 2 * p.dP.d + p.d1.d;
     p.a_p2 = 2 * p.ct_d / NP; p.a_1 = p.ct_m / N1;
-    // one workgroup per CU while that gives every block of a queue 32 of them or more, else two (8 blocks 314 / 338 us, 12 blocks 414 / 408)
+    // one workgroup per CU while that gives every block of a queue 32 of them or more, else two (DeiT-tiny, twelve layers, 256 / 512 of them:
+    // 4 blocks 249 / 271 us, 8 blocks 314 / 334, 9 blocks 372 / 368, 12 blocks 426 / 408, 20 blocks 599 / 488)
     const long all = (long)p.tpb * a.nb, most = a.nb <= FL_MAXQ ? 256 : 512;
     auto kern = flow_kernel<KD, 24, NQ, N1, NP, SUM>;
     static bool attr_set = false;   // raising the dynamic LDS limit is a per-kernel, process-wide setting
@@ -685,8 +687,8 @@ template <int KD, int NQ, int N1, int NP> int launch_flow_n(FlowParams &p, hipSt
 template <int KD> int launch_flow_d(FlowParams &p, hipStream_t st)
 {
     // Coarse tasks (all three tiles of a head, four of the hidden width, two of the output) load the rows and hand over once for several
-    // tiles, but a stage of one block is then 21 tasks: better from five blocks on (1 block 203 / 232 us, 4 blocks 248 / 256, 6 blocks
-    // 295 / 256, 16 blocks 436 / 416 for the twelve layers of DeiT-tiny, fine / coarse)
+    // tiles, but a stage of one block is then 21 tasks: better from five blocks on (1 block 201 / 232 us, 4 blocks 249 / 254, 5 blocks
+    // 288 / 254, 8 blocks 385 / 314, 16 blocks 424 / 412 for the twelve layers of DeiT-tiny, fine / coarse)
     if (p.a.nb > 4 && p.ct_m % 4 == 0) return launch_flow_n<KD, 3, 4, 2>(p, st);
     return launch_flow_n<KD, 1, 2, 1>(p, st);
 }

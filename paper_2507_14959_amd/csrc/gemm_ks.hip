@@ -7,8 +7,8 @@
 //    grid covers the chip;
 //  - wave w takes the k-tiles w, w + 4, .. (128 bytes of every row each) of the whole tile through a ring of its own: up to three
 //    of its k-tiles are in flight, there is no barrier in the loop, and a 768-long contraction is three steps;
-//  - the four partial sums meet in LDS once, in fixed order (the same order for every tile size, so results do not depend on
-//    which one the size of the call selects), and each wave finishes one 32 x 32 subtile: low-rank expand, bias, GELU or residual;
+//  - the four partial sums meet in LDS once, in fixed order (the same for every tile size of this file; the kernels that larger calls
+//    take sum in other orders), and each wave finishes one 32 x 32 subtile: low-rank expand, bias, GELU or residual;
 //  - the chain offsets -> adapter ids -> operands of the expand, and the residual rows, are requested before the loop.
 // v_mfma_f32_32x32x16_bf16, or v_mfma_f32_32x32x2_f32 (true single precision: twice the rate of the vector ALU without packed
 // operations).  A lane's 16 bytes are 8 or 4 consecutive contraction elements of one row; both operands use the same order.
@@ -676,7 +676,9 @@ bool gemm_aligned(const GemmArgs &g)
 }
 
 // Tile by the time of the busiest CU: rounds of tiles over the 256 CUs, each the larger of its loads through the CU's load path
-// (about 40 bytes per clock) and its products, plus what a tile costs whatever its size (first round trip, partial sums, stores).
+// (about 40 bytes per clock) and its products, plus what a tile costs whatever its size (first round trip, partial sums, stores).  On 24
+// products of 68 to 6304 rows it picks the fastest of the three tiles 23 times and one that is 10 % slower once, e.g. 591 x 768 -> 768 12.4,
+// 8.5 and 9.8 us with 32 x 32, 32 x 64 and 64 x 64, 591 x 768 -> 3072 39.4, 25.6, 17.1, single precision 68 x 192 -> 576 10.0, 11.4, 14.0.
 int launch_gemm_ks(const GemmArgs &g, int dtype, hipStream_t st)
 {
     const double es = dtype == POLY_BF16 ? 2 : 4, rate = dtype == POLY_BF16 ? 2048 : 220;    // flop per clock and CU
@@ -719,8 +721,8 @@ template <typename T, int MI, int NI> int launch_linear_t(const LinearParams &g,
 
 // Tile of the one-launch linear: the smallest of 32 x 32, 32 x 64 and 64 x 64 with which every tile gets a compute unit of its own
 // (0 = none).  Smaller tiles are more of the chip and a shorter serial chain; with more tiles than compute units a second round, and the
-// shrink that every column tile repeats, cost more than the launch that is saved (9 x 197 x 192 -> 576, 378 tiles of 64 x 64: 15.9 us
-// against 15.1 with the separate shrink).
+// shrink that every column tile repeats, cost more than the launch that is saved (9 x 197 x 192 -> 576, 324 tiles of 64 x 64: 14.4 us of
+// kernel time against 11.7 in two launches; 6 x 197 x 192 -> 576 15.7, 12.8, 8.9 with the three tiles, 9 x 17 x 384 -> 1536 13.2, 8.6, 9.5).
 int linear_ks_tile(long F, int T, int N)
 {
     auto tiles = [&](int bm, int bn) { return F * ((T + bm - 1) / bm) * ((N + bn - 1) / bn); };

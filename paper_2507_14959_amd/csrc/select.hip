@@ -12,9 +12,12 @@
 //  - Reuse branches.  S_t = S_{t-1} where the labels repeat or (context copy) where S_{t-1} provides them all, so every S_t is
 //    the greedy set of the last frame that was NOT reused.  If frame t took its own set, the next frame to do so is
 //    next[t] = the first t' > t whose labels are new and not all provided by the greedy set of t -- a function of t alone, found
-//    for all t side by side.  The frames that really took their own set are the ones on the chain that starts at the first
-//    frame of the pass that the carried set does not serve; they are marked by pointer doubling (log2 n rounds), and a scan
-//    gives every frame the last marked one before it.
+//    for all t side by side: every thread walks forward from its frame to the next break.  The frames that really took their own set
+//    are the ones on the chain that starts at the first frame of the pass that the carried set does not serve; they are marked by
+//    pointer doubling (log2 n rounds), and a scan gives every frame the last marked one before it.
+//
+// The walk is as long as a scene whose labels do not change.  1024 frames with context copy whose labels change every 16 frames 18 us,
+// every 64 23 us, every 256 43 us, never 102 us.
 //
 // 1024 frames x 80 labels, 45 overlapping contexts with an accuracy table and context copy: 1665 us per call with M tests per frame
 // and a sequential pass over the frames, 18.9 us this way (20 k cycles of it kernel phases: scores 5, links 1, chain 3.5, the rest
