@@ -240,7 +240,7 @@ def test_config4_select_then_forward_without_host_round_trip():
 
 
 @pytest.mark.parametrize("D,heads,Dm,hw,r,targets,L0,dtype", [
-    (192, 3, 768, 40, 8, 3, 1, synth.DT_BF16),      # fused row kernels: the scale multiplies the shrink accumulator
+    (192, 3, 768, 40, 8, 3, 1, synth.DT_BF16),      # narrow (few blocks: as tasks; row kernels in test_gpu_layer_kernels.py)
     (256, 4, 512, 40, 16, 15, 0, synth.DT_BF16),    # shrink kernel + expand in the GEMM
     (128, 2, 256, 32, 4, 15, 0, synth.DT_F32),
 ])
