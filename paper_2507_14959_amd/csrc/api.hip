@@ -367,6 +367,16 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         // ---- attention half
         if (qkv_done) {
             qkv_done = false;
+        } else if (dt == POLY_BF16 && !(summed && use(0)) && rowlayer_supported(D, Dm, use(0) ? m->r : 0)) {
+            RowLayerArgs a = {};
+            a.T = T; a.D = D; a.Dm = Dm; a.n_out = n_out; a.n_out_dev = n_out_dev;
+            a.adapter_of_out = use(0) ? w.adapter_of_row : nullptr; a.r = m->r; a.scale = m->lora_scale; a.eps = m->ln_eps;
+            a.res = x_in; a.res_block_of_out = fan_map;
+            a.lnq_g = base->ln1_g + (size_t)l * D; a.lnq_b = base->ln1_b + (size_t)l * D;
+            a.Wqt = (const bf16_t *)Wqkv; a.bq = base->qkv_b + (size_t)l * 3 * D;
+            if (use(0)) { a.Aqt = (const bf16_t *)lora_ptr(lora->At[0], 0, D, 3 * D, true); a.Bqt = (const bf16_t *)lora_ptr(lora->Bt[0], 0, D, 3 * D, false); }
+            a.qkv_out = (bf16_t *)w.qkv;
+            POLY_TRY(launch_rowlayer(a, st));
         } else if (fused(0)) {
             POLY_TRY(rowlin(0, x_in, base->ln1_g + (size_t)l * D, base->ln1_b + (size_t)l * D, nullptr, fan_map, Wqkv,
                             base->qkv_b + (size_t)l * 3 * D, 3 * D, EPI_STORE, w.qkv, nullptr, nullptr));
@@ -391,7 +401,8 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         if (dt == POLY_BF16 && !use(2) && !use(3) && !(summed && (use(0) || use(1))) && rowlayer_supported(D, Dm, (use(0) || use(1)) ? m->r : 0)) {
             RowLayerArgs a = {};
             a.T = T; a.D = D; a.Dm = Dm; a.n_out = n_out; a.n_out_dev = n_out_dev;
-            a.adapter_of_out = (lora_on && !sum) ? w.adapter_of_row : nullptr; a.r = m->r; a.scale = m->lora_scale; a.eps = m->ln_eps;
+            const bool adapters = lora_on && !sum && (use(1) || (m->targets & 1));
+            a.adapter_of_out = adapters ? w.adapter_of_row : nullptr; a.r = m->r; a.scale = m->lora_scale; a.eps = m->ln_eps;
             a.o = (const bf16_t *)w.o; a.Wpt = (const bf16_t *)Wproj; a.bp = base->proj_b + (size_t)l * D;
             if (use(1)) { a.Apt = (const bf16_t *)lora_ptr(lora->At[1], 1, D, D, true); a.Bpt = (const bf16_t *)lora_ptr(lora->Bt[1], 1, D, D, false); }
             a.res = x_in; a.res_block_of_out = fan_map;

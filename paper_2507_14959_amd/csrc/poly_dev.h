@@ -109,33 +109,34 @@ __device__ __forceinline__ f32x4 gelu_fine4(f32x4 x)
 }
 
 // erf-GELU through a table of Phi in LDS, for kernels whose inner loop is bound by the number of instructions it
-// issues: GELU(x) = x * Phi(x), Phi linearly interpolated between samples 1/64 apart on [-4.5, 4.5] (clamped
-// outside: Phi(-4.5) = 3.4e-6, 1 - Phi(4.5) = 3.4e-6).  Interpolation error <= h^2 / 8 * max|Phi''| = 7.4e-6.
-// Entry i holds (Phi(x_i), Phi(x_{i+1}) - Phi(x_i)), x_i = (i - 288) / 64, i = 0 .. 576: 4616 bytes.
+// issues: GELU(x) = x * Phi(x), Phi on the 1/64-wide interval around x_i = (i - 288) / 64, i = 0 .. 576, by the line whose error changes sign
+// twice on it, 0 and 1 on and past the outermost ones (Phi(-4.49) = 3.6e-6).  Error <= h^2 / 16 * max|Phi''| = 3.7e-6.  Entry i holds the line as (value at 0, slope):
+// 4616 bytes.  Rounding 64 x + 288 by adding 1.5 * 2^23 leaves i in the low bits of the sum, so the address is one shift-and-add of its bit
+// pattern: six vector instructions per value and one 8-byte LDS read.
 constexpr int GELU_TAB_ENTRIES = 577;
-__device__ __forceinline__ void gelu_tab_build(float *tab, int tid, int nthreads)
-{
-    for (int i = tid; i < GELU_TAB_ENTRIES; i += nthreads) {
-        const float x0 = (i - 288) * (1.0f / 64), x1 = x0 + 1.0f / 64;
-        const float p0 = 0.5f * erfcf(-x0 * 0.70710678118654752440f), p1 = i < GELU_TAB_ENTRIES - 1 ? 0.5f * erfcf(-x1 * 0.70710678118654752440f) : p0;
-        tab[2 * i] = p0;
-        tab[2 * i + 1] = p1 - p0;
-    }
-}
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ f32x4 gelu_tab4(f32x4 x, const float *tab)
+__device__ __forceinline__ f32x2 gelu_tab_entry(int i)
 {
-    f32x4 fr;
-    f32x2 e[4];
+    const float x = (i - 288) * (1.0f / 64), h = 1.0f / 128;
+    const float lo = 0.5f * erfcf((h - x) * 0.70710678118654752440f), hi = 0.5f * erfcf((-h - x) * 0.70710678118654752440f);
+    const float slope = (hi - lo) * 64.0f, mid = 0.5f * (0.5f * erfcf(-x * 0.70710678118654752440f) + 0.5f * (lo + hi));
+    if (i == 0 || i == GELU_TAB_ENTRIES - 1) return f32x2{i == 0 ? 0.f : 1.f, 0.f};
+    return f32x2{fmaf(-slope, x, mid), slope};
+}
+// the entry of a value (tab: LDS address of the table), and the GELU of four from theirs: apart, so that other work can stand between a read and
+// its use
+__device__ __forceinline__ void gelu_look(float x, unsigned tab, float &xc, f32x2 &e)
+{
+    xc = __builtin_amdgcn_fmed3f(x, -4.5f, 4.5f);
+    const unsigned u = __builtin_bit_cast(unsigned, fmaf(xc, 64.0f, 12582912.0f + 288.0f));
+    e = *(const __attribute__((address_space(3))) f32x2 *)(size_t)((u << 3) + (tab - (0x4b400000u << 3)));
+}
+__device__ __forceinline__ f32x4 gelu_tab4(f32x4 x, const float (&xc)[4], const f32x2 (&e)[4])
+{
+    f32x4 v;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float t = fmaf(__builtin_amdgcn_fmed3f(x[i], -4.5f, 4.5f), 64.0f, 288.0f), fl = floorf(t);
-        fr[i] = t - fl;
-        e[i] = *(const f32x2 *)(tab + 2 * (int)fl);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) fr[i] = x[i] * fmaf(fr[i], e[i][1], e[i][0]);
-    return fr;
+    for (int i = 0; i < 4; ++i) v[i] = x[i] * fmaf(xc[i], e[i][1], e[i][0]);
+    return v;
 }
 
 // ---- launch with optional per-stage timing (profile.hip) ----
@@ -247,14 +248,15 @@ bool mlp_supported(int D, int Dm);
 int launch_mlp(const MlpArgs &a, hipStream_t st);
 
 // The row-wise part of a layer in one launch (rowlayer.hip):
-//   A (if o != null)        x' = res + o Wp + bp + scale (o Ap_k) Bp_k,  else x' = x_out
+//   A                       x' = res + o Wp + bp + scale (o Ap_k) Bp_k
 //   B                       x_out = x' + GELU(LayerNorm2(x') W1 + b1) W2 + b2
 //   C (if qkv_out != null)  qkv_out = LayerNorm1'(x_out) Wq + bq + scale (.. Aq_k) Bq_k     (the next layer's qkv)
+// o == null: C alone, on res instead of x_out
 // bf16 weights stored contraction-fastest, adapter stacks indexed by adapter_of_out[block]
 struct RowLayerArgs {
     int T, D, Dm, n_out;
     const int *n_out_dev;            // optional device-side block count (the smaller of the two is used)
-    const int *adapter_of_out;       // [n_out] or null
+    const int *adapter_of_out;       // [n_out] or null: no adapters in this launch
     int r;
     float scale, eps;
     // A

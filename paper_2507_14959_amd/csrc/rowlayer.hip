@@ -1,30 +1,30 @@
 // Everything of a pre-LN transformer layer that works row by row, for narrow models (D <= 192), in one kernel
 // on tiles of 64 token rows:
 //
-//   A (optional)  x' = res + o Wp + bp + s (o Ap_k) Bp_k                 attention output projection, Sec. 3.1 form
-//   B             x'' = x' + GELU(LayerNorm2(x') W1 + b1) W2 + b2        feed-forward block (no low-rank branch here)
-//   C (optional)  qkv = LayerNorm1'(x'') Wq + bq + s (.. Aq_k) Bq_k      qkv linear of the NEXT layer
+//   A   x' = res + o Wp + bp + s (o Ap_k) Bp_k                       attention output projection, Sec. 3.1 form
+//   B   x'' = x' + b2 + GELU(LayerNorm2(x') W1 + b1) W2              feed-forward block (no low-rank branch here)
+//   C   qkv = LayerNorm1'(x'') Wq + bq + s (.. Aq_k) Bq_k            qkv linear of the NEXT layer (optional)
 //
-// Only softmax attention needs whole blocks; with A, B and C in one launch a layer is two kernels instead of
-// four, and x', the hidden activation and LayerNorm outputs never leave the chip.  Launch overhead and the cold
-// start of every kernel (inputs written by the previous kernel come from HBM) were a quarter of the layer time.
+// (LAYER = false: C alone, on rows read from memory: the first layer's qkv and the one where frames fan out into row-blocks.)
+// Only softmax attention needs whole blocks, so a layer is two launches, and x', the hidden activation and the LayerNorm outputs never leave the
+// chip.  Without adapters the rows of all blocks are tiled as one run: 333 blocks of 197 rows are 1026 tiles, five rounds of 256 CUs, where tiles
+// that end with their block are 1332, six rounds.
 //
-// Eight waves.  A wave that issues a load into the saturated L2 path is held at the issue stage, so the weight stream
-// has a wave of its own and the waves that compute issue no loads while they compute:
-//   waves 0-3 (2 x 2 over a 64 x 64 chunk): the MFMA work of A and C; in B the first product and the GELU;
-//   wave 4: the weight stream into a ring of LDS stages (24 KB items; five stages in A and C, four in B);
-//   waves 5-7: in B the second product (wave 5 + j owns output columns 64 j .. 64 j + 63 of all 64 rows), each fed from its
-//             own tile of the current W2 slice in the fifth stage, which it refills itself as soon as it has copied the
-//             tile into registers.  A stage of a shared ring is freed by a workgroup barrier, so what is read in one step can
-//             be requested again in the next step at the earliest and the stream runs dry at every barrier; with W2 out
-//             of the ring the stream of W1 runs three chunks ahead and the loads of W2 never wait for a barrier;
-//   waves 4-7 together: At_k / Bt_k of the block's adapter into LDS, and the residual stream: they hold x' (fp32,
-//             16 threads per row) in registers from phase A to the end, do both LayerNorms on it and write x''.
-// The loop of B is bound by the number of instructions a wave issues (a wave issues one every five cycles or so,
-// whatever the instruction; two waves on a SIMD issue twice as many), which is why its two products sit on
-// different waves: the GELU's arithmetic and the second product's operand reads are issued side by side.
-// Phase boundaries pass a 64 x D fp32 tile through LDS; it takes the place of ring stages 0-2, so every phase's
-// stream starts in stage 3 and at most two items of the next phase are prefetched across a boundary.
+// Eight waves (kh, wc), two per SIMD, all of which compute and request the weights they multiply:
+//   product with D outputs (proj, W2)  wave (kh, wc): 16 KT columns of all 64 rows for half kh of the contraction; the halves meet once, at the end of
+//                                      A and of B, through LDS (exchange), and from there on wave (kh, wc) owns row half kh of its columns: the
+//                                      residual stream is 24 fp32 registers of a lane and never a tile in LDS.
+//   product with D inputs (W1, Wq)     wave w: 16 of 128 columns of all 64 rows, whose operands stay in registers (96 of them).
+// A wave thus multiplies weights that no other wave needs: each byte of them passes the CU's load path and LDS once, into a slot of the wave's
+// own (two of 6 KB), refilled as soon as it has been read, with no barrier between.  What is left to share are the hidden columns: one barrier per 128.
+//
+// Bounds, for DeiT-tiny (885 KB of weights per tile), in cycles of a 57 k-cycle launch of 248 tiles: start and the first loads 8.5 k, proj + exchange +
+// shrink 6 k, the two LayerNorms 7 k, the six chunks of the feed-forward block 21 k, qkv 11 k.  A chunk takes 3.35 k: LDS is busy for about 2.6 k of
+// it (96 KB of weights in and out, GELU lookups at 6.3 cycles per instruction, hidden columns), the matrix units 1.54 k; without the stream it takes
+// 2.4 k, without the lookups 2.6 k.  32.8 us per launch with one wave for the stream and three for the second product became 30.4 us (62 blocks of 197
+// rows, rank 8), 156 us became 118 us (333 blocks, no adapters).  Tried and dropped: weights in a ring shared by all waves with a barrier per 24 KB
+// (31 us; its steps wait for each other), the same with the two row halves a barrier apart, one multiplying while the other reads (32 us), tiles of 96
+// and 128 rows (registers spill), the GELU as a polynomial (the same: fewer lookups, more issue slots).
 #include "poly_dev.h"
 #include "rowtile.h"
 
@@ -32,623 +32,564 @@
 
 namespace {
 
-constexpr int LY_NS = 5;            // LDS stages of the weight stream
 constexpr int LY_THREADS = 512;
+constexpr int LY_TILE = 8192;       // bytes of a [64][64] bf16 tile in LDS: 128 bytes a row, its 16-byte pieces permuted
+constexpr int LY_TILES = 4;         // of activations
 constexpr int LY_MAX_DM = 768;
-constexpr int LY_MAX_NQ = 576;      // qkv columns: 9 chunks, their accumulators stay in registers
-constexpr int LY_MAXCH = LY_MAX_NQ / 64;
+constexpr int LY_GELU = (GELU_TAB_ENTRIES + 1) & ~1;    // (what lies behind is read in 16-byte pieces)
 constexpr int LY_AT_STRIDE = 200;   // elements per rank row of At_k in LDS (192 + 8: rows start 4 banks apart)
 
-template <int KT, bool HAS_PROJ, bool HAS_QKV>
-__global__ __launch_bounds__(LY_THREADS) void rowlayer_kernel(const RowLayerArgs a)
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(3))) char *lds_ptr;
+
+// sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48 that share a token row, in every one of them
+__device__ __forceinline__ float quad16_sum(float v)
 {
-    constexpr int D = 64 * KT;
-    constexpr int A_EL = (KT < 2 ? 2 : KT) * 64 * 64;   // activation rows (KT tiles of [64][64]) / Bt_k / the two hidden tiles
-    constexpr int IT_EL = KT * 64 * 64;          // one stream item: KT tiles of [64][64]
-    constexpr int NLD = 8 * KT;                  // loads per item (all by wave 4): 64 rows of each tile, 8 rows per load
-    constexpr int NV = D / 16;                   // 16-byte pieces of fp32 rows per loader thread (four rows, 16 threads per row)
-    constexpr int XSTRIDE = D * 4 + 16;          // bytes per row of the fp32 hand-over tile
-    extern __shared__ __attribute__((aligned(16))) bf16_t lds[];
-    bf16_t *As = lds, *Ws = lds + A_EL;
-    float *b1_s = (float *)(lds + A_EL + LY_NS * IT_EL);   // [Dm]
+    unsigned p = __builtin_bit_cast(unsigned, v);
+    const u32x2 a = __builtin_amdgcn_permlane32_swap(p, p, false, false);
+    const unsigned a0 = a[0], a1 = a[1];
+    p = __builtin_bit_cast(unsigned, __builtin_bit_cast(float, a0) + __builtin_bit_cast(float, a1));
+    const u32x2 b = __builtin_amdgcn_permlane16_swap(p, p, false, false);
+    const unsigned b0 = b[0], b1 = b[1];
+    return __builtin_bit_cast(float, b0) + __builtin_bit_cast(float, b1);
+}
+
+template <int KT, bool LAYER, bool QKV>
+__global__ __launch_bounds__(LY_THREADS, 2) void rowlayer_kernel(const RowLayerArgs a, const int flat_rows)
+{
+    constexpr int D = 64 * KT, Nq = 3 * D, NQ = (Nq + 127) / 128;
+    constexpr int CT = KT;                                 // column tiles of 16 per wave of a product with D columns
+    constexpr int SLOT = KT * 2048;                        // bytes of a slot: 16 rows of D columns, or 16 CT rows of 64 columns
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    char *As = lds;                                        // activations: KT tiles [64][64] bf16; two pairs of tiles for the hidden columns, and for qkv
+    char *Ws = lds + LY_TILES * LY_TILE;                   // two slots per wave
+    float *b1_s = (float *)(Ws + 16 * SLOT);               // [Dm]
     float *bq_s = b1_s + LY_MAX_DM;                        // [3 D]
-    float *bp_s = bq_s + LY_MAX_NQ;                        // [D]
+    float *bp_s = bq_s + Nq;                               // [D]
     float *b2_s = bp_s + D;                                // [D]
     float *gb2_s = b2_s + D;                               // LayerNorm2 gain [D], shift [D]
     float *gbq_s = gb2_s + 2 * D;                          // LayerNorm1' gain, shift
-    bf16_t *at_s = (bf16_t *)(gbq_s + 2 * D);              // At_k of the current phase: [16][LY_AT_STRIDE]
-    // Phi table of the GELU (phase B): behind the two hidden tiles in the activation-row area when that has 24 KB, else in
-    // a region of its own (narrower models leave LDS to spare)
-    float *gelu_s = KT == 3 ? (float *)(As + 2 * 4096) : (float *)(at_s + 16 * LY_AT_STRIDE);
+    f32x2 *stat_s = (f32x2 *)(gbq_s + 2 * D);              // [64][4]: mean and squared deviations of a wave's columns of a row
+    s16x4 *sh_s = (s16x4 *)stat_s;                         // in C: shrink output, [4][64 lanes]
+    float *gelu_s = (float *)(stat_s + 64 * 4);
+    bf16_t *at_s = (bf16_t *)(gelu_s + 2 * LY_GELU);       // At_k of the phase, [16][LY_AT_STRIDE]
+    bf16_t *bt_s = at_s + 16 * LY_AT_STRIDE;               // Bt_k of A, [D][r]
 
-    const int tiles = (a.T + 63) / 64;
-    const int ob = blockIdx.x / tiles, t0 = (blockIdx.x % tiles) * 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool loader = wave >= 4;
-    const int wr = (wave >> 1) & 1, wc = wave & 1, lm = lane & 31, lh = lane >> 5;
-    const int lw = wave & 3, lr = lane >> 3, lt = tid & 255;
-    const int Dm = a.Dm, nch = Dm >> 6;
-    const int Nq = 3 * D, nchq = (Nq + 63) / 64;
-    const int rows = min(64, a.T - t0);
+    const int kh = wave >> 2, wc = wave & 3, lm = lane & 15, lg = lane >> 4, lr = lane >> 3;
+    const int Dm = a.Dm, nc = LAYER ? (Dm + 127) >> 7 : 0;
 
-    // ---- the stream.  Items (KT tiles each), in order: phase A: Wp chunk c (stage c); phase B: W1's rows of chunk c, for
-    // the first product, in the four stages 0-3 (stage (SB0 + c) % 4; SB0 = 3 when A comes first, whose hand-over tile takes
-    // stages 0-2); phase C: Wq chunk c at position PC + c (stage = position % 5, PC = 3 mod 5).  The slices of W2 do not pass
-    // through the ring: each wave of the second product keeps its own tile of the current slice in stage 4 and requests the
-    // next one itself (see phase B).
-    const int NA = HAS_PROJ ? KT : 0;
-    constexpr int SB0 = HAS_PROJ ? 3 : 0;
-    const int PC = 8;
-    const int NI = NA + nch + (HAS_QKV ? nchq : 0);                 // items, numbered in order
-    // ring position for the items of A and C; those of B are requested explicitly (never by refill)
-    auto pos_of = [&](int i) { return i < NA ? i : (i < NA + nch ? 1 << 20 : PC + (i - NA - nch)); };
-    // wave 4 loads each of the item's KT tiles, 8 rows (1 KB) per load; a row's 128 bytes land in lane order, the tile
-    // swizzle is applied by permuting the 16-byte pieces on the global side
-    auto issue_item = [&](int i) {
-        const bf16_t *base;
-        int stage;
-        if (i < NA) { base = a.Wpt + (size_t)i * 64 * D; stage = i; }
-        else if (i < NA + nch) { const int c = i - NA; base = a.W1t + (size_t)c * 64 * D; stage = (SB0 + c) & 3; }
-        else { const int c = i - NA - nch; base = a.Wqt + (size_t)c * 64 * D; stage = (PC + c) % LY_NS; }
-        bf16_t *st = Ws + stage * IT_EL;
-        const int rstride = D, tstride = 64;              // elements between rows / between tiles (tile t: k = 64 t ..)
-        // row 8 g + lr of a tile: its 16-byte pieces are permuted by (row >> 1) & 7 = 4 (g & 1) + (lr >> 1).  Every matrix
-        // here has a multiple of 64 rows, so no row of a tile is past its end.
-        const unsigned rb = rstride * 2;
-        const unsigned e0 = lr * rb + ((((lane & 7) ^ (lr >> 1))) << 4), e1 = lr * rb + ((((lane & 7) ^ (4 + (lr >> 1)))) << 4);
-        const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_addr_of(st));
-#pragma unroll
-        for (int t = 0; t < KT; ++t)
-            glds16_tile8(base + (size_t)t * tstride, lds0 + t * 8192, e0, e1 + 8 * rb, e0 + 16 * rb, e1 + 24 * rb, e0 + 32 * rb, e1 + 40 * rb,
-                         e0 + 48 * rb, e1 + 56 * rb);
-    };
-    // At_k [r][D] -> at_s, one rank row per load (24 * KT / 3 lanes), rows LY_AT_STRIDE elements apart
-    auto issue_at = [&](const bf16_t *At_k, int r) {
-        for (int rk = lw; rk < r; rk += 4)
-            if (lane < D / 8) glds16(At_k + (size_t)rk * D + lane * 8, __builtin_amdgcn_readfirstlane(lds_addr_of(at_s + rk * LY_AT_STRIDE)));
-    };
-    // Bt_k [N][r] -> As, as it is
-    auto issue_bt = [&](const bf16_t *Bt_k, int N, int r) {
-        const int n16 = (N * r) >> 3;
-        for (int i0 = lw * 64; i0 < n16; i0 += 256)
-            if (i0 + lane < n16) glds16((const char *)Bt_k + (size_t)(i0 + lane) * 16, __builtin_amdgcn_readfirstlane(lds_addr_of(As) + i0 * 16));
-    };
-
-    // ---- everything whose address needs no metadata is requested first: it comes from HBM (another kernel has just
-    // written it), and whatever is requested first is served first
-    bf16x8 pv[D / 32];                           // computing waves: o rows (4 threads per row, pieces part, part + 4, ..)
-    f32x4 xr[NV];                                // loader waves: residual rows, then x', then x''
-    f32x4 gb2v = {0.f, 0.f, 0.f, 0.f}, gbqv = {0.f, 0.f, 0.f, 0.f};
-    float b1v[LY_MAX_DM / 256], bqv[(LY_MAX_NQ + 255) / 256], b2v = 0.f, bpv = 0.f;
-    const bool res_early = !HAS_PROJ || a.res_block_of_out == nullptr;
-    // Rows of the residual stream in the loader waves: 16 threads per row.  Thread (slot = lt / 16, part = lt % 16) holds, of
-    // the four rows slot + 16 k, the 16-byte pieces part + 16 i (i < KT) as xr[k * KT + i]: the 16 lanes of a row read and
-    // write 256 contiguous bytes per instruction (whole cache lines), the row statistics are sums over a DPP row, and a
-    // thread needs the gains of only KT pieces for its four rows.
-    const int xslot = lt >> 4, xpart = lt & 15;
-    auto load_res = [&](int rblk) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float *src = (HAS_PROJ ? a.res : a.x_out) + ((size_t)rblk * a.T + min(t0 + xslot + 16 * k, a.T - 1)) * D + 4 * xpart;
-#pragma unroll
-            for (int i = 0; i < KT; ++i) xr[k * KT + i] = *(const f32x4 *)(src + 64 * i);
-        }
-    };
-    if (!loader) {
-        if (HAS_PROJ) {
-            const bf16_t *src = a.o + ((size_t)ob * a.T + min(t0 + (tid >> 2), a.T - 1)) * D + 8 * (tid & 3);
-#pragma unroll
-            for (int i = 0; i < D / 32; ++i) pv[i] = *(const bf16x8 *)(src + 32 * i);
-            bpv = a.bp[min(tid, D - 1)];
-        }
-        gb2v = ln_gb_load<KT>(a.ln2_g, a.ln2_b, tid);
-#pragma unroll
-        for (int j = 0; j < LY_MAX_DM / 256; ++j) b1v[j] = a.b1[min(tid + 256 * j, Dm - 1)];   // unconditional: see ln_gb_load
-        b2v = a.b2[min(tid, D - 1)];
-        if (HAS_QKV) {
-            gbqv = ln_gb_load<KT>(a.lnq_g, a.lnq_b, tid);
-#pragma unroll
-            for (int j = 0; j < (LY_MAX_NQ + 255) / 256; ++j) bqv[j] = a.bq[min(tid + 256 * j, Nq - 1)];
-        }
-    } else if (res_early) {
-        load_res(ob);
+    // ---- this tile's rows
+    int ob = 0, t0;
+    size_t row0;                                           // of the output
+    int rows;
+    if (flat_rows) {
+        t0 = blockIdx.x * 64;
+        row0 = t0;
+        rows = min(64, flat_rows - t0);
+    } else {
+        const int tiles = (a.T + 63) / 64;
+        ob = blockIdx.x / tiles;
+        t0 = (blockIdx.x % tiles) * 64;
+        row0 = (size_t)ob * a.T + t0;
+        rows = min(64, a.T - t0);
+    }
+    const int n_out = a.n_out_dev ? min(*a.n_out_dev, a.n_out) : a.n_out;
+    const int k_ad = a.adapter_of_out ? a.adapter_of_out[ob] : -1;      // (meaningless past n_out)
+    size_t xrow0 = row0;
+    if (a.res_block_of_out) {                              // (the map has entries for the blocks that exist only)
+        if (ob >= n_out) return;
+        xrow0 = (size_t)a.res_block_of_out[ob] * a.T + t0;
     }
 
-    const int n_out = a.n_out_dev ? min(*a.n_out_dev, a.n_out) : a.n_out;
-    if (ob >= n_out) {
+    // ---- the stream of weights, into slots of the wave that multiplies them: 8 rows x 128 bytes per instruction, the swizzle of the LDS rows applied
+    // on the global side.
+    const unsigned slot0 = __builtin_amdgcn_readfirstlane(lds_addr_of(Ws)) + wave * (2 * SLOT);     // N slot, then K slot
+    const unsigned piece = (unsigned)(((lane & 7) ^ (lr >> 1)) << 4);                               // of rows lr; of rows 8 + lr: ^ 64
+    const unsigned off_d = (unsigned)lr * (D * 2) + piece, off_m = (unsigned)lr * (Dm * 2) + piece;
+    // 16 rows of a matrix with D columns from row `row`
+    auto issue_n1 = [&](const bf16_t *W, int row, unsigned slot, int j) {
+        const bf16_t *base = W + (size_t)(row + 8 * (j & 1)) * D + 64 * (j >> 1);
+        glds16_s(base, off_d ^ (64 * (j & 1)), slot + j * 1024);
+    };
+    auto issue_n = [&](const bf16_t *W, int row, unsigned slot) {
+#pragma unroll
+        for (int j = 0; j < 2 * KT; ++j) issue_n1(W, row, slot, j);
+    };
+    // W2: rows 16 CT wc .., 64 columns from column `col`
+    auto issue_k1 = [&](int col, int j) { glds16_s(a.W2t + (size_t)(16 * CT * wc + 8 * j) * Dm + col, off_m ^ (64 * (j & 1)), slot0 + SLOT + j * 1024); };
+    // first row of W1 / first column of W2 that this wave multiplies of chunk c (the last chunk may be half a one: what lies past it is not used)
+    auto row_n = [&](int c) { return min(128 * c + 16 * wave, Dm - 16); };
+    auto col_k = [&](int c) { return min(128 * c + 64 * kh, Dm - 64); };
+    auto row_q = [&](int q) { return 128 * q + 16 * (128 * q + 128 <= Nq ? wave : wc); };
+    auto slot_q = [&](int q) { return slot0 + (q & 1 ? 0 : SLOT); };
+
+    // ---- prologue: everything is requested at once, in the order in which it is needed
+    if (LAYER) {
+        const char *src = (const char *)(a.o + row0 * D);
+#pragma unroll
+        for (int t = 0; t < KT; ++t) {                     // rows 8 wave .. + 7 of each tile
+            const unsigned p = (unsigned)(((lane & 7) ^ ((wave & 1) * 4 + (lr >> 1))) << 4);
+            glds16_s(src + t * 128, (unsigned)min(8 * wave + lr, rows - 1) * (D * 2) + p, __builtin_amdgcn_readfirstlane(lds_addr_of(As)) + t * LY_TILE + wave * 1024);
+        }
+        // Wp: rows 16 CT wc .., columns 64 t + 32 kh .. + 31 as [16 CT][32], 16 rows x 64 bytes per instruction
+        const unsigned vo = (unsigned)(lane >> 2) * (D * 2) + (((lane & 3) ^ ((lane >> 4) & 3)) << 4);
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+                glds16_s(a.Wpt + (size_t)(16 * CT * wc + 16 * ct) * D + 64 * t + 32 * kh, vo, slot0 + (t * CT + ct) * 1024);
+    } else {
+        issue_n(a.Wqt, row_q(0), slot_q(0));
+        issue_n(a.Wqt, row_q(1), slot_q(1));
+    }
+    // vectors -> LDS, 64 floats per instruction (any alignment of a float), shared out by wave
+    auto vec = [&](const float *src, int from, int to, const float *dst) {
+        for (int i = from; i < to; i += 64) glds4(src + i + lane, __builtin_amdgcn_readfirstlane(lds_addr_of(dst)) + i * 4);
+    };
+    if (LAYER) {
+        if (wave == 0) vec(a.b1, 0, Dm >> 1 & ~63, b1_s);
+        if (wave == 1) vec(a.b1, Dm >> 1 & ~63, Dm, b1_s);
+        if (wave == 2) { vec(a.bp, 0, D, bp_s); vec(a.b2, 0, D, b2_s); }
+        if (wave == 3) { vec(a.ln2_g, 0, D, gb2_s); vec(a.ln2_b, 0, D, gb2_s + D); }
+    }
+    if (QKV) {
+        if (wave == 4) { vec(a.lnq_g, 0, D, gbq_s); vec(a.lnq_b, 0, D, gbq_s + D); }
+        if (wave >= 5) vec(a.bq, (wave - 5) * D, (wave - 4) * D, bq_s);
+    }
+    // the residual stream of the row half kh: row lm of tile rt, columns 16 CT wc + 16 ct + 4 lg + {0..3}
+    const int wrow = 32 * kh, wcol = 16 * CT * wc + 4 * lg;
+    const bool none = flat_rows ? (long)t0 >= (long)n_out * a.T : ob >= n_out;
+    if (none) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         return;
     }
-    const int k_ad = a.adapter_of_out ? a.adapter_of_out[ob] : -1;
-    const bool lora_p = HAS_PROJ && a.Apt && k_ad >= 0, lora_q = HAS_QKV && a.Aqt && k_ad >= 0;
-
-    // ---- loader bookkeeping.  last: newest item requested; cpos: newest ring position every wave is done with.
-    // An item may be requested once the item five positions earlier has been consumed, and never beyond `cap`
-    // (the positions that a hand-over tile is about to use).
-    int last = -1;
-    auto refill = [&](int cpos, int cap) {
-        while (last + 1 < NI && pos_of(last + 1) <= min(cpos + LY_NS, cap)) {
-            ++last;
-            if (wave == 4) { issue_item(last); }
-        }
+    if (flat_rows) rows = min(rows, (int)((long)n_out * a.T - t0));
+    const bool lora_p = LAYER && a.Apt && k_ad >= 0, lora_q = QKV && a.Aqt && k_ad >= 0;
+    const int r = a.r;
+    // At_k [r][D] -> at_s, a rank row per instruction; Bt_k [D][r] -> bt_s, as it is
+    auto issue_at = [&](const bf16_t *At_k) {
+        for (int rk = wave; rk < r; rk += 8)
+            if (lane < D / 8) glds16(At_k + rk * D + lane * 8, __builtin_amdgcn_readfirstlane(lds_addr_of(at_s + rk * LY_AT_STRIDE)));
     };
-    // item `need` has landed; newer ones may stay in flight (loads complete in issue order; the counter holds 63).
-    // Waves 5-7 have no part in the stream: whatever else they requested has landed after this.
-    auto wait_item = [&](int need) {
-        const int ahead = wave == 4 ? last - need : 0;
-        if (ahead >= 2) rl_wait_barrier<2 * NLD>();
-        else if (ahead == 1) rl_wait_barrier<NLD>();
-        else rl_wait_barrier<0>();
-    };
-    auto issue_next = [&]() {                    // the next item, whatever its position (the caller knows its stage is free)
-        ++last;
-        if (wave == 4) { issue_item(last); }
-    };
-
-    if (loader) {
-        if (!res_early) load_res(a.res_block_of_out[ob]);
-        // the first items only (all of phase A, or two of B) -- the rows above are still on their way and would be slowed
-        // down by more.  At_k first: the wait for the first chunks then covers it (loads complete in issue order).
-        if (lora_p) issue_at(a.Apt + (size_t)k_ad * a.r * D, a.r);
-        if (HAS_PROJ) refill(-1, KT - 1);
-        else { issue_next(); issue_next(); }       // (nch >= 2)
-    } else {
-        // prologue of the computing waves: what they requested -> LDS
-        if (HAS_PROJ) {
-#pragma unroll
-            for (int i = 0; i < D / 32; ++i) {
-                const int k = 8 * (4 * i + (tid & 3));
-                *(bf16x8 *)(As + (k >> 6) * 4096 + tile_off(tid >> 2, (k & 63) >> 3)) = pv[i];
-            }
-            if (tid < D) bp_s[tid] = bpv;
-        }
-        ln_gb_store<KT>(gb2v, gb2_s, tid);
-        if (HAS_QKV) {
-            ln_gb_store<KT>(gbqv, gbq_s, tid);
-#pragma unroll
-            for (int j = 0; j < (LY_MAX_NQ + 255) / 256; ++j)
-                if (tid + 256 * j < Nq) bq_s[tid + 256 * j] = bqv[j];
-        }
-#pragma unroll
-        for (int j = 0; j < LY_MAX_DM / 256; ++j)
-            if (tid + 256 * j < Dm) b1_s[tid + 256 * j] = b1v[j];
-        if (tid < D) b2_s[tid] = b2v;
+    // rank lm (repeated past r: such ranks meet zeros of Bt_k), columns 32 k + 8 lg + {0..7}
+    auto at_frag = [&](int k) { return *(const bf16x8 *)(at_s + min(lm, r - 1) * LY_AT_STRIDE + 32 * k + 8 * lg); };
+    // column n of Bt_k [.][r], ranks 4 lg + {0..3} (r is a multiple of 4; zero where the rank does not exist)
+    auto bt_frag = [&](const bf16_t *Bt_k, int n) { return *(const s16x4 *)(Bt_k + n * r + min(4 * lg, r - 4)); };
+    auto bt_operand = [&](s16x4 v) { return 4 * lg < r ? v : s16x4{0, 0, 0, 0}; };
+    if (lora_p) {
+        issue_at(a.Apt + (size_t)k_ad * r * D);
+        const char *Bt_k = (const char *)(a.Bpt + (size_t)k_ad * D * r);
+        const int n16 = D * r / 8;                         // 16-byte pieces
+        for (int i = wave * 64; i < n16; i += 512)
+            if (i + lane < n16) glds16(Bt_k + (i + lane) * 16, __builtin_amdgcn_readfirstlane(lds_addr_of(bt_s)) + i * 16);
     }
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // B0: o rows, biases, gains are in LDS
+    if (!LAYER && lora_q) issue_at(a.Aqt + (size_t)k_ad * r * D);
+    f32x4 x[CT][2];
+    auto load_x = [&]() {
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+                x[ct][rt] = *(const f32x4 *)(a.res + xrow0 * D + (unsigned)(min(wrow + 16 * rt + lm, rows - 1) * D + wcol + 16 * ct));
+    };
+    if (!LAYER) load_x();
+    const bf16_t *Bq_k = QKV && lora_q ? a.Bqt + (size_t)k_ad * Nq * r : nullptr;
+    if (LAYER) {                                           // Phi table of the GELU
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int i = tid + LY_THREADS * j;
+            if (i < GELU_TAB_ENTRIES) *(f32x2 *)(gelu_s + 2 * i) = gelu_tab_entry(i);
+        }
+    }
 
-    const bf16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
-    const bf16x4 zero4 = {0, 0, 0, 0};
-    bf16x8 fa[KT * 4];                           // the resident rows wr*32 + lm as the B operand of the transposed product
+    // ---- operands.  A fragment is 16 rows x 32 contraction columns: lane (lm, lg) holds columns 8 lg .. + 7 of row lm, the 16-byte piece
+    // (4 kk + lg) ^ (row >> 1 & 7) of a 128-byte row.
+    const int fo0 = lm * 128 + ((lg ^ ((lm >> 1) & 7)) << 4), fo1 = fo0 ^ 64;
+    lds_ptr act[2], wn[2];                                 // [k & 1]: rows of activations, rows of a slot
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        act[k] = (lds_ptr)(As + (k ? fo1 : fo0));
+        wn[k] = (lds_ptr)(Ws + wave * (2 * SLOT) + (k ? fo1 : fo0));
+        asm("" : "+v"(act[k]));
+        asm("" : "+v"(wn[k]));
+    }
+    auto rd = [&](lds_ptr p, int off) { return *(const __attribute__((address_space(3))) bf16x8 *)(p + off); };
+    auto act_frag = [&](int tile, int rt, int kk) { return rd(act[kk], tile * LY_TILE + rt * 2048); };
+    bf16x8 fa[2 * KT][4];                                  // the resident rows as the B operand of the transposed product
     auto load_fa = [&]() {
 #pragma unroll
-        for (int kk = 0; kk < KT * 4; ++kk)
-            fa[kk] = *(const bf16x8 *)(As + (kk >> 2) * 4096 + tile_off(wr * 32 + lm, 2 * (kk & 3) + lh));
+        for (int k = 0; k < 2 * KT; ++k)
+#pragma unroll
+            for (int rt = 0; rt < 4; ++rt) fa[k][rt] = act_frag(k >> 1, rt, k & 1);
     };
-    // shrink: c[n][m] = sum_k At[n][k] x[m][k] with At_k from at_s; lane (lm, lh) ends up with ranks 4*lh + {0..3} (c[0..3])
-    // and 8 + 4*lh + {0..3} (c[4..7]) of row lm -- exactly the 8 contraction slots it must supply to the expand
-    auto shrink = [&](int r) {
-        f32x16 c;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) c[e] = 0.f;
-#pragma unroll
-        for (int kk = 0; kk < KT * 4; ++kk) {
-            const bf16x8 ft = lm < r ? *(const bf16x8 *)(at_s + min(lm, 15) * LY_AT_STRIDE + kk * 16 + lh * 8) : zero8;
-            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ft, fa[kk], c, 0, 0, 0);
-        }
-        bf16x8 fs;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) fs[j] = (bf16_t)(a.scale * c[j]);
-        return fs;
+    // s (x At_k): ranks 4 lg + {0..3} of row lm, the operand of the expand as it is
+    auto shrink_out = [&](f32x4 c) {
+        const bf16x4 o = {(bf16_t)(a.scale * c[0]), (bf16_t)(a.scale * c[1]), (bf16_t)(a.scale * c[2]), (bf16_t)(a.scale * c[3])};
+        return __builtin_bit_cast(s16x4, o);
     };
-    // expand operand of output column n from Bt_k (in As): ranks 4*lh + {0..3} and 8 + 4*lh + {0..3}; r is a multiple of 4:
-    // each half is one 8-byte read at a clamped offset, zeroed where the rank does not exist
-    auto bt_frag = [&](int n, int r) {
-        const bool lo_ok = 4 * lh + 4 <= r, hi_ok = 8 + 4 * lh + 4 <= r;
-        const bf16_t *bt = As + (size_t)n * r;
-        const bf16x4 lo = lo_ok ? *(const bf16x4 *)(bt + 4 * lh) : zero4, hi = hi_ok ? *(const bf16x4 *)(bt + 8 + 4 * lh) : zero4;
-        return bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    // 4 columns 16 cg + 4 lg + {0..3} (cg < 4) of row 16 rt + lm -> a [64][64] tile
+    auto put = [&](char *tile, int cg, int rt, f32x4 v) {
+        const bf16x4 o = {(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]};
+        *(bf16x4 *)(tile + (16 * rt + lm) * 128 + (((2 * cg + (lg >> 1)) ^ ((lm >> 1) & 7)) << 4) + 8 * (lg & 1)) = o;
     };
-    // one or two chunks of a plain linear against the resident rows: acc starts from the bias; operands are fetched one
-    // K step (16) ahead of the MFMAs that use them (LDS latency is a hundred-odd cycles, and the compiler on its own
-    // keeps only two or three reads in flight)
-    auto linear_step = [&](f32x16 &acc0, f32x16 &acc1, int c0, int pos0, int N, const float *bias_s, auto PAIR) {
-        constexpr bool pair = decltype(PAIR)::value;
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        const bf16_t *st0 = Ws + (pos0 % LY_NS) * IT_EL, *st1 = Ws + ((pos0 + 1) % LY_NS) * IT_EL;
-        bf16x8 fw0[2][KT], fw1[2][KT];
-        auto load = [&](int kk, int sl) {
+    // The sums over the two halves of the contraction meet: a wave hands the row half that is not its own to the wave with the same columns, through
+    // its own N slot, and adds what it is handed.
+    auto exchange = [&](f32x4 (&acc)[CT][4], f32x4 (&own)[CT][2]) {
+        f32x4 *mine = (f32x4 *)(Ws + wave * (2 * SLOT)) + lane;
+        const f32x4 *theirs = (const f32x4 *)(Ws + (wave ^ 4) * (2 * SLOT)) + lane;
 #pragma unroll
-            for (int kt = 0; kt < KT; ++kt) {
-                fw0[sl][kt] = *(const bf16x8 *)(st0 + kt * 4096 + tile_off(wc * 32 + lm, 2 * kk + lh));
-                if (pair) fw1[sl][kt] = *(const bf16x8 *)(st1 + kt * 4096 + tile_off(wc * 32 + lm, 2 * kk + lh));
-            }
-        };
-        load(0, 0);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const f32x4 b0 = *(const f32x4 *)(bias_s + min(c0 * 64 + wc * 32 + 8 * g + 4 * lh, N - 4));
-#pragma unroll
-            for (int z = 0; z < 4; ++z) acc0[4 * g + z] = b0[z];
-            if (pair) {
-                const f32x4 b1 = *(const f32x4 *)(bias_s + min((c0 + 1) * 64 + wc * 32 + 8 * g + 4 * lh, N - 4));
-#pragma unroll
-                for (int z = 0; z < 4; ++z) acc1[4 * g + z] = b1[z];
-            }
-        }
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            if (kk < 3) load(kk + 1, (kk + 1) & 1);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int kt = 0; kt < KT; ++kt) {
-                acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw0[kk & 1][kt], fa[kt * 4 + kk], acc0, 0, 0, 0);
-                if (pair) acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw1[kk & 1][kt], fa[kt * 4 + kk], acc1, 0, 0, 0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-    char *xtile = (char *)Ws;                    // the fp32 hand-over tile: ring stages 0-2
-    // loaders: xr += the tile (the product that the other waves staged)
-    auto add_tile = [&]() {
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int i = 0; i < KT; ++i) xr[k * KT + i] += *(const f32x4 *)(xtile + (xslot + 16 * k) * XSTRIDE + (xpart + 16 * i) * 16);
-    };
-    // loaders: the rows in xr -> LayerNorm (fp32 statistics, centred second moment) -> bf16 tiles at As, gains from gb_s
-    auto ln_rows = [&](const float *gb_s) {
-        f32x4 gn[KT], sh[KT];
-#pragma unroll
-        for (int i = 0; i < KT; ++i) { gn[i] = *(const f32x4 *)(gb_s + 4 * (xpart + 16 * i)); sh[i] = *(const f32x4 *)(gb_s + D + 4 * (xpart + 16 * i)); }
-        float mean[4], inv[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            float t = 0.f;
-#pragma unroll
-            for (int i = 0; i < KT; ++i) t += xr[k * KT + i][0] + xr[k * KT + i][1] + xr[k * KT + i][2] + xr[k * KT + i][3];
-            mean[k] = row16_sum(t) * (1.0f / D);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            float q = 0.f;
-#pragma unroll
-            for (int i = 0; i < KT; ++i)
-#pragma unroll
-                for (int z = 0; z < 4; ++z) { const float d = xr[k * KT + i][z] - mean[k]; q = fmaf(d, d, q); }
-            inv[k] = rsqrtf(row16_sum(q) * (1.0f / D) + a.eps);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float nmi = -mean[k] * inv[k];
-            const int row = xslot + 16 * k;
-#pragma unroll
-            for (int i = 0; i < KT; ++i) {
-                const int col = 4 * (xpart + 16 * i);         // first of this piece's 4 elements
-                bf16x4 o;
-#pragma unroll
-                for (int z = 0; z < 4; ++z) o[z] = (bf16_t)fmaf(fmaf(xr[k * KT + i][z], inv[k], nmi), gn[i][z], sh[i][z]);   // ((x - mean) inv) g + b
-                *(bf16x4 *)(As + (col >> 6) * 4096 + tile_off(row, (col & 63) >> 3) + (col & 4)) = o;
-            }
-        }
-    };
-
-    // ================================================================ phase A: x' = res + o Wp + bp + lora
-    if (HAS_PROJ) {
-        constexpr int SA = (KT + 1) / 2;
-        if (loader) {
-            // (the ring is refilled after each step's barrier, never before it: a loader that is still issuing -- it is held
-            // at the issue stage while the L2 path is busy -- would keep every wave waiting at that barrier)
-            for (int s = 0; s < SA; ++s) {
-                wait_item(min(2 * s + 1, KT - 1));
-                if (s == 0 && lora_p) issue_bt(a.Bpt + (size_t)k_ad * D * a.r, D, a.r);     // the computing waves hold their fragments by now
-                refill(2 * s - 1, 1 << 20);
-                if (s == 0) issue_next();                                           // W1's first rows: stage 3 is free all through A
-            }
-            wait_item(NA - 1);                                                  // Bf: Bt_k has landed (it is older than the items still in flight)
-            asm volatile("s_barrier" ::: "memory");                             // Bs: the tile is complete
-            add_tile();
-            ln_rows(gb2_s);
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // Bl: LayerNorm2(x') is in As, the tile is dead
-        } else {
-            load_fa();
-            f32x16 accp[KT + 1];
-#pragma unroll
-            for (int s = 0; s < SA; ++s) {
-                if (2 * s + 1 < KT) linear_step(accp[2 * s], accp[2 * s + 1], 2 * s, 2 * s, D, bp_s, std::true_type{});
-                else linear_step(accp[2 * s], accp[2 * s], 2 * s, 2 * s, D, bp_s, std::false_type{});
-            }
-            bf16x8 fs = zero8;
-            if (lora_p) fs = shrink(a.r);                                       // At_k landed before the first chunk did
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // Bf
-            if (lora_p) {
-#pragma unroll
-                for (int c = 0; c < KT; ++c) accp[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bt_frag(c * 64 + wc * 32 + lm, a.r), fs, accp[c], 0, 0, 0);
-            }
-            // the ring positions 0 .. KT - 1 are consumed: the tile takes stages 0-2
-            char *trow = xtile + (wr * 32 + lm) * XSTRIDE + (wc * 32 + 4 * lh) * 4;
-#pragma unroll
-            for (int c = 0; c < KT; ++c)
-#pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    *(f32x4 *)(trow + (c * 64 + 8 * g) * 4) = f32x4{accp[c][4 * g], accp[c][4 * g + 1], accp[c][4 * g + 2], accp[c][4 * g + 3]};
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // Bs
-            asm volatile("s_barrier" ::: "memory");                             // Bl
-        }
-    } else {
-        if (loader) {
-            ln_rows(gb2_s);
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // Bl: LayerNorm2(x') is in As
-        } else {
-            asm volatile("s_barrier" ::: "memory");                             // Bl
-        }
-    }
-
-    // ================================================================ phase B: y = GELU(LayerNorm2(x') W1 + b1) W2
-    // Step h (0 .. nch + 1), one barrier each:
-    //   waves 0-3: hb[h & 1] = LayerNorm2(x') W1 rows of chunk h; hidden tile of chunk h - 1 = GELU(hb[(h - 1) & 1] + b1),
-    //              a quarter of the GELU's arithmetic between the MFMAs of each K step;
-    //   waves 5-7: y += hidden(chunk h - 2) W2 slice;   wave 4: the stream.
-    bf16_t *Hs = As;                             // hidden tiles [64 rows][64 columns of a chunk], chunk c in tile c & 1 (As is dead
-                                                 // once every wave has its fa: the barrier of step 0 comes before the first write)
-    using T_ = std::true_type;
-    using F_ = std::false_type;
-    if (loader) {
-        const int j = wave - 5;                  // waves 5-7: output columns 64 j .. 64 j + 63, rows rt*32 + lm, as y[rt][ct]
-        const bool second = j >= 0 && j < KT;
-        f32x16 y[2][2];
-        if (second) {
-#pragma unroll
-            for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-                for (int g4 = 0; g4 < 4; ++g4) {
-                    const f32x4 b = *(const f32x4 *)(b2_s + 64 * j + ct * 32 + 8 * g4 + 4 * lh);   // the accumulators start from b2
-#pragma unroll
-                    for (int z = 0; z < 4; ++z) y[0][ct][4 * g4 + z] = y[1][ct][4 * g4 + z] = b[z];
-                }
-        }
-        // this wave's tile of W2's slice c (output columns 64 j .., hidden columns 64 c ..) -> its 8 KB of stage 4
-        bf16_t *w2_s = Ws + 4 * IT_EL + (second ? j : 0) * 4096;
-        auto issue_w2 = [&](int c) {
-            const unsigned rb = Dm * 2;
-            const unsigned e0 = lr * rb + ((((lane & 7) ^ (lr >> 1))) << 4), e1 = lr * rb + ((((lane & 7) ^ (4 + (lr >> 1)))) << 4);
-            glds16_tile8(a.W2t + (size_t)j * 64 * Dm + (size_t)c * 64, __builtin_amdgcn_readfirstlane(lds_addr_of(w2_s)), e0, e1 + 8 * rb,
-                         e0 + 16 * rb, e1 + 24 * rb, e0 + 32 * rb, e1 + 40 * rb, e0 + 48 * rb, e1 + 56 * rb);
-        };
-        for (int h = 0; h < nch + 2; ++h) {
-            // wave 4: W1(h) has landed (later chunks may be in flight).  Waves 5-7 keep their own loads in flight across the
-            // barrier and wait for them below.
-            if (wave == 4) wait_item(NA + min(h, nch - 1));
-            else asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            if (h == 0) gelu_tab_build(gelu_s, lt, 256);   // every computing wave holds its fragments of LayerNorm2(x') by now; first used in step 1
-            // At_k of the qkv linear: at_s is idle since the shrink of phase A, and a request made here does not queue up
-            // behind the first chunks of C
-            if (h == 1 && lora_q) issue_at(a.Aqt + (size_t)k_ad * a.r * D, a.r);
-            // the stream of W1: chunks 1-3 into stages 0-2 once the hand-over tile is dead, then chunk h + 3 into the stage
-            // that chunk h - 1 has left; the first chunk of C once W1 is through (stage 3; the second one needs stage 4)
-            if (h == 0) { while (last + 1 < NA + min(nch, 4)) issue_next(); }
-            else if (last + 1 < NA + nch) issue_next();
-            else if (HAS_QKV && h == nch && last + 1 == NA + nch) issue_next();
-            if (second && h == 0) issue_w2(0);
-            if (second && h >= 2) {
-                // The slice of W2 does not pass through the shared ring: this wave's tile of it landed in its own 8 KB (requested
-                // one step ago), is copied into registers, and the next slice is requested into the same place at once.
-                const bf16_t *Hr = Hs + (h & 1) * 4096;                                                            // chunk h - 2
-                bf16x8 fh[2][2], f2[4][2];
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) f2[kk][t] = *(const bf16x8 *)(w2_s + tile_off(t * 32 + lm, 2 * kk + lh));
-                auto load = [&](int kk, int s) {
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) fh[s][t] = *(const bf16x8 *)(Hr + tile_off(t * 32 + lm, 2 * kk + lh));
-                };
-                load(0, 0);
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                if (h - 1 < nch) issue_w2(h - 1);
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk) {
-                    if (kk < 3) load(kk + 1, (kk + 1) & 1);
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-                        for (int ct = 0; ct < 2; ++ct)
-                            y[rt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f2[kk][ct], fh[kk & 1][rt], y[rt][ct], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-        }
-        wait_item(NA + nch - 1);                                                // Be: every chunk and slice of B is consumed
-        refill(HAS_QKV ? PC - 1 : 0, HAS_QKV ? PC + 1 : -1);                    // (the tile still needs stages 0-2)
-        if (second) {
+        for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
             for (int rt = 0; rt < 2; ++rt) {
-                char *trow = xtile + (rt * 32 + lm) * XSTRIDE + (64 * j + 4 * lh) * 4;
+                mine[(ct * 2 + rt) * 64] = kh ? acc[ct][rt] : acc[ct][2 + rt];
+                own[ct][rt] = kh ? acc[ct][2 + rt] : acc[ct][rt];
+            }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
-                for (int ct = 0; ct < 2; ++ct)
+        for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-                    for (int g4 = 0; g4 < 4; ++g4)
-                        *(f32x4 *)(trow + (ct * 32 + 8 * g4) * 4) = f32x4{y[rt][ct][4 * g4], y[rt][ct][4 * g4 + 1], y[rt][ct][4 * g4 + 2], y[rt][ct][4 * g4 + 3]};
+            for (int rt = 0; rt < 2; ++rt) own[ct][rt] += theirs[(ct * 2 + rt) * 64];
+    };
+    // LayerNorm (fp32 statistics, centred second moments of 16 CT columns each, put together by Chan's rule) of x -> bf16 tiles at As -> fragments.
+    // Behind the first barrier every wave is done with what it read before: `between` runs there.
+    auto layernorm = [&](const float *gb_s, auto between) {
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) {
+            float t = 0.f;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) t += (x[ct][rt][0] + x[ct][rt][1]) + (x[ct][rt][2] + x[ct][rt][3]);
+            const float m = quad16_sum(t) * (1.0f / (16 * CT));
+            float q = 0.f;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                for (int z = 0; z < 4; ++z) { const float d = x[ct][rt][z] - m; q = fmaf(d, d, q); }
+            q = quad16_sum(q);
+            if (lg == 0) stat_s[(wrow + 16 * rt + lm) * 4 + wc] = f32x2{m, q};
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        between();
+        f32x4 g[CT], b[CT];
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) { g[ct] = *(const f32x4 *)(gb_s + wcol + 16 * ct); b[ct] = *(const f32x4 *)(gb_s + D + wcol + 16 * ct); }
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) {
+            const int row = wrow + 16 * rt + lm;
+            const f32x4 s0 = *(const f32x4 *)(stat_s + row * 4), s1 = *(const f32x4 *)(stat_s + row * 4 + 2);
+            const float mean = 0.25f * ((s0[0] + s0[2]) + (s1[0] + s1[2]));
+            const float d0 = s0[0] - mean, d1 = s0[2] - mean, d2 = s1[0] - mean, d3 = s1[2] - mean;
+            const float q = (s0[1] + s0[3]) + (s1[1] + s1[3]) + (16 * CT) * ((d0 * d0 + d1 * d1) + (d2 * d2 + d3 * d3));
+            const float inv = rsqrtf(q * (1.0f / D) + a.eps), nmi = -mean * inv;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                bf16x4 o;
+#pragma unroll
+                for (int z = 0; z < 4; ++z) o[z] = (bf16_t)fmaf(fmaf(x[ct][rt][z], inv, nmi), g[ct][z], b[ct][z]);   // ((x - mean) inv) g + b
+                const int col = wcol + 16 * ct;
+                *(bf16x4 *)(As + (col >> 6) * LY_TILE + row * 128 + ((((col & 63) >> 3) ^ ((lm >> 1) & 7)) << 4) + 2 * (col & 4)) = o;
             }
         }
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");         // By: the y tile is complete
-        add_tile();                                                             // x'' = x' + y
-        if (HAS_QKV) {
-            // Bt: the tile is dead.  Chunks 2-4 of C (stages 0-2) are requested now, by a computing wave: requested by a
-            // loader after its stores of x'', they would queue up behind those and arrive three thousand cycles into C.
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            last = max(last, NA + nch + min(nchq, 5) - 1);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int row = xslot + 16 * k;
-            if (row < rows) {
-                float *dst = a.x_out + ((size_t)ob * a.T + t0 + row) * D + 4 * xpart;
-#pragma unroll
-                for (int i = 0; i < KT; ++i) *(f32x4 *)(dst + 64 * i) = xr[k * KT + i];
-            }
-        }
-        if (HAS_QKV) ln_rows(gbq_s);
-    } else {
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         load_fa();
-        f32x16 hb[2];                            // first product of chunks h / h - 1: row lm, columns wc*32 + 8*(e/4) + 4*lh + e%4
-        auto first_step = [&](auto D1, auto DG, auto PAR, int h) {
-            constexpr bool d1 = decltype(D1)::value, dg = decltype(DG)::value;
-            constexpr int par = decltype(PAR)::value ? 1 : 0;          // h & 1
-            f32x16 &hout = hb[par], &hin = hb[par ^ 1];
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            const bf16_t *s1 = Ws + ((SB0 + h) & 3) * IT_EL;                                        // W1(h)
-            bf16_t *Hw = Hs + ((h - 1) & 1) * 4096;                                                  // chunk h - 1
-            bf16x8 f1[2][KT];
-            f32x4 b[4];
-            auto load = [&](int kk, int s) {
+    };
+    constexpr int NS = 4 * KT;                             // MFMAs of a segment
+    // a segment: every MFMA is followed by a share of the other work
+    auto segment = [&](auto mfma, auto side) {
 #pragma unroll
-                for (int kt = 0; kt < KT; ++kt) f1[s][kt] = *(const bf16x8 *)(s1 + kt * 4096 + tile_off(wc * 32 + lm, 2 * kk + lh));
-            };
-            if (dg) {
-                const float *bp = b1_s + (h - 1) * 64 + wc * 32 + 4 * lh;
-#pragma unroll
-                for (int g4 = 0; g4 < 4; ++g4) b[g4] = *(const f32x4 *)(bp + 8 * g4);
-            }
-            if (d1) load(0, 0);
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                if (d1 && kk < 3) load(kk + 1, (kk + 1) & 1);
-                __builtin_amdgcn_sched_barrier(0);
-                if (d1) {
-#pragma unroll
-                    for (int kt = 0; kt < KT; ++kt) {
-                        const f32x16 z16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                        hout = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1[kk & 1][kt], fa[kt * 4 + kk], kk == 0 && kt == 0 ? z16 : hout, 0, 0, 0);
-                    }
-                }
-                if (dg) {
-                    // a quarter of the chunk's GELU per K step, through the Phi table (fewer instructions than the polynomial)
-                    const f32x4 v = gelu_tab4(f32x4{hin[4 * kk], hin[4 * kk + 1], hin[4 * kk + 2], hin[4 * kk + 3]} + b[kk], gelu_s);
-                    const bf16x4 o = {(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]};
-                    *(bf16x4 *)(Hw + tile_off(wr * 32 + lm, 4 * wc + kk) + 4 * lh) = o;
-                }
-                if (d1 && dg) {
-                    // one MFMA, then a share of the vector work, so that the vector work is issued while an MFMA runs
-#pragma unroll
-                    for (int i = 0; i < KT; ++i) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x002, (40 + KT - 1) / KT, 0);
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-        first_step(T_{}, F_{}, F_{}, 0);
-        for (int h = 1; h < nch; ++h) {
-            if (h & 1) first_step(T_{}, T_{}, T_{}, h);
-            else first_step(T_{}, T_{}, F_{}, h);
+        for (int n = 0; n < NS; ++n) {
+            mfma(n);
+            side(n);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        if (nch & 1) first_step(F_{}, T_{}, T_{}, nch);
-        else first_step(F_{}, T_{}, F_{}, nch);
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");         // step nch + 1: the other waves' last product
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");         // Be: the ring positions of B are consumed
-        asm volatile("s_barrier" ::: "memory");                                 // By
-        if (HAS_QKV) {
-            asm volatile("s_barrier" ::: "memory");                             // Bt
-            if (wave == 0)
-                for (int c = 2; c < min(nchq, 5); ++c) issue_item(NA + nch + c);
-        }
-    }
-    if (!HAS_QKV) return;
+    };
+    // pieces 0 .. count - 1 over the slots [first, last) of a segment
+    auto share = [&](int n, int first, int last, int count, auto piece) {
+#pragma unroll
+        for (int j = 0; j < count; ++j)
+            if (n == first + j * (last - first) / count) piece(j);
+    };
 
-    // ================================================================ phase C: qkv = LayerNorm1'(x'') Wq + bq + lora
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");             // Bz: LayerNorm1'(x'') is in As, the tile is dead
-    f32x16 acc[LY_MAXCH + 1];                    // acc[c][e]: row wr*32 + lm, column c*64 + wc*32 + 8*(e/4) + 4*lh + e%4
-    const int i0q = NA + nch;                    // first item of C
-    if (loader) {
-        for (int s = 0; 2 * s < nchq; ++s) {
-            if (s == 0 && wave == 4) {
-                // The first two chunks of C were requested by this wave before it stored its rows of x''; chunks 2-4 are wave 0's
-                // (`last` counts them, so wait_item would let two items' worth of this wave's requests stay in flight and
-                // guarantee nothing about chunk 1).  What may stay in flight is exactly the stores: KT per group of 16 rows
-                // that has a row of this wave's inside the tile -- the stores that are issued whatever the compiler does with
-                // the others.
-                switch (min(4, (rows + 15) >> 4)) {
-                case 4: rl_wait_barrier<4 * KT>(); break;
-                case 3: rl_wait_barrier<3 * KT>(); break;
-                case 2: rl_wait_barrier<2 * KT>(); break;
-                default: rl_wait_barrier<KT>(); break;
+    if (LAYER) {
+        // ============================================================ A: x' = res + o Wp + bp + lora
+        f32x4 y[CT][4];
+        rl_wait_barrier<0>();                              // o, Wp, At_k, Bt_k and the vectors
+        {
+            const lds_ptr wp = (lds_ptr)(Ws + wave * (2 * SLOT) + lm * 64 + ((lg ^ ((lm >> 2) & 3)) << 4));
+            bf16x8 w[KT][CT], h[KT][4];
+#pragma unroll
+            for (int t = 0; t < KT; ++t) {
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) w[t][ct] = rd(wp, (t * CT + ct) * 1024);
+#pragma unroll
+                for (int rt = 0; rt < 4; ++rt) h[t][rt] = rd(kh ? act[1] : act[0], t * LY_TILE + rt * 2048);
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int j = 0; j < 2 * CT; ++j) issue_k1(col_k(0), j);
+            load_x();                                      // (16 rows x 64 bytes an instruction hold the load path up: not in front of the first product)
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                    for (int rt = 0; rt < 4; ++rt)
+                        y[ct][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[t][ct], h[t][rt], t == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : y[ct][rt], 0, 0, 0);
+        }
+        {
+            f32x4 own[CT][2];
+            exchange(y, own);
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                const f32x4 b = *(const f32x4 *)(bp_s + wcol + 16 * ct);
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt) x[ct][rt] += own[ct][rt] + b;
+            }
+        }
+        if (lora_p) {                                      // 
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) {
+                f32x4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int k = 0; k < 2 * KT; ++k) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(at_frag(k), rd(act[k & 1], (k >> 1) * LY_TILE + wrow * 128 + rt * 2048), c, 0, 0, 0);
+                const s16x4 fs = shrink_out(c);
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) x[ct][rt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bt_operand(bt_frag(bt_s, 16 * CT * wc + 16 * ct + lm)), fs, x[ct][rt], 0, 0, 0);
+            }
+        }
+        layernorm(gb2_s, [&]() { issue_n(a.W1t, row_n(0), slot0); });
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {                  // the second product of B adds to x' + b2 in the row half of this wave
+            const f32x4 b = *(const f32x4 *)(b2_s + wcol + 16 * ct), z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int rt = 0; rt < 4; ++rt) y[ct][rt] = (rt >> 1) == kh ? x[ct][rt & 1] + b : z;
+        }
+
+        // ============================================================ B: x'' = x' + b2 + GELU(LayerNorm2(x') W1 + b1) W2
+        bf16x8 wN[2 * KT], wK[2][CT], hk[2][4];
+        f32x4 h[4];
+        float xc[4];
+        f32x2 en[4];
+        const unsigned gelu_a = lds_addr_of(gelu_s);
+        auto fetch_n1 = [&](int j) { wN[j] = rd(wn[j & 1], (j >> 1) * 2048); };
+        auto fetch_w1 = [&](int kk, int j) { wK[kk][j] = rd(wn[kk], SLOT + j * 2048); };
+        auto fetch_h1 = [&](int kk, int buf, int rt) { hk[kk][rt] = rd(act[kk], buf * (2 * LY_TILE) + kh * LY_TILE + rt * 2048); };
+        auto mfma_n = [&](int n, int rt0, f32x4 b) {       // rows of two tiles
+            const int k = n / 2, rt = rt0 + n % 2;
+            h[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wN[k], fa[k][rt], k == 0 ? b : h[rt], 0, 0, 0);
+        };
+        auto mfma_k = [&](int n, int kk) {
+            const int ct = n / 4, rt = n % 4;
+            y[ct][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wK[kk][ct], hk[kk][rt], y[ct][rt], 0, 0, 0);
+        };
+        // GELU of one row tile: four lookups, then (fin) the results
+        auto look = [&](int rt, int j) { gelu_look(h[rt][j], gelu_a, xc[j], en[j]); };
+        auto fin = [&](int rt, int buf) { put(As + buf * (2 * LY_TILE) + kh * LY_TILE, wc, rt, gelu_tab4(h[rt], xc, en)); };
+        auto gelu_side = [&](int n, int rt0, int buf) {    // of two row tiles in a segment of NS slots
+            share(n, 0, NS / 4, 4, [&](int j) { look(rt0, j); });
+            if (n == NS / 2 - 1) fin(rt0, buf);
+            share(n, NS / 2, 3 * NS / 4, 4, [&](int j) { look(rt0 + 1, j); });
+            if (n == NS - 1) fin(rt0 + 1, buf);
+        };
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int j = 0; j < 2 * KT; ++j) fetch_n1(j);
+        auto chunk = [&](int c, auto FIRST) {              // first product of chunk c, second of chunk c - 1
+            constexpr bool first = decltype(FIRST)::value;
+            const int buf = c & 1;
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // hidden columns of chunk c - 1 are there; wN is in registers
+            const f32x4 b = *(const f32x4 *)(b1_s + min(128 * c + 16 * wave, Dm - 16) + 4 * lg);
+            if (c + 1 < nc) issue_n(a.W1t, row_n(c + 1), slot0);
+            segment([&](int n) { mfma_n(n, 0, b); }, [&](int n) {});
+            segment([&](int n) { mfma_n(n, 2, b); },
+                    [&](int n) {
+                        gelu_side(n, 0, buf);
+                        if (!first) {
+                            share(n, 0, NS / 2, 4, [&](int j) { fetch_h1(0, buf ^ 1, j); });
+                            if (n == NS / 2) {
+                                if (c + 1 < nc) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * KT) : "memory");
+                                else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                            }
+                            share(n, NS / 2, NS, CT, [&](int j) { fetch_w1(0, j); });
+                        }
+                    });
+            if (first) {
+#pragma unroll
+                for (int n = 0; n < NS; ++n) gelu_side(n, 2, buf);
+            } else {
+                segment([&](int n) { mfma_k(n, 0); },
+                        [&](int n) {
+                            gelu_side(n, 2, buf);
+                            share(n, 0, NS / 2, 4, [&](int j) { fetch_h1(1, buf ^ 1, j); });
+                            share(n, NS / 2, NS - 1, CT, [&](int j) { fetch_w1(1, j); });
+                        });
+            }
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            if (first) {
+                if (c + 1 < nc) {
+#pragma unroll
+                    for (int j = 0; j < 2 * KT; ++j) fetch_n1(j);
                 }
             } else {
-                wait_item(i0q + min(2 * s + 1, nchq - 1));
+                segment([&](int n) { mfma_k(n, 1); },
+                        [&](int n) {
+                            share(n, 0, NS, 2 * CT, [&](int j) { issue_k1(col_k(c), j); });
+                            if (c + 1 < nc) share(n, 0, NS - 1, 2 * KT, [&](int j) { fetch_n1(j); });
+                        });
             }
-            if (s == 0 && lora_q) issue_bt(a.Bqt + (size_t)k_ad * Nq * a.r, Nq, a.r);   // the computing waves hold their fragments by now
-            refill(PC + 2 * s - 1, 1 << 30);
-        }
-        rl_wait_barrier<0>();                                                   // Bf2: Bt_k has landed; the ring is dead
-        asm volatile("s_barrier" ::: "memory");                                 // Bg2: expand done, Bt_k is dead
-    } else {
-        load_fa();
-        // the shrink first (At_k has been in LDS since phase B): these waves would only wait for the first chunks otherwise
-        bf16x8 fs = zero8;
-        if (lora_q) fs = shrink(a.r);
+        };
+        chunk(0, std::true_type{});
+#pragma unroll 1
+        for (int c = 1; c < nc; ++c) chunk(c, std::false_type{});
+        {                                                  // second product of the last chunk; where that is half a chunk, the second half has nothing
+            const int buf = (nc - 1) & 1;
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
-        for (int s = 0; s < (LY_MAXCH + 1) / 2; ++s) {
-            // chunks 2-4 were requested by wave 0: it waits for its own loads (the other waves have none in flight)
-            if (s == 1) {
-                if (nchq >= 5) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NLD) : "memory");
-                else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) fetch_h1(kk, buf, j);
+#pragma unroll
+                for (int j = 0; j < CT; ++j) fetch_w1(kk, j);
             }
-            if (s == 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            // uniform conditions, written as guards (not a break) so that the loop unrolls and acc stays in registers
-            if (2 * s + 1 < nchq) linear_step(acc[2 * s], acc[2 * s + 1], 2 * s, PC + 2 * s, Nq, bq_s, std::true_type{});
-            else if (2 * s < nchq) linear_step(acc[2 * s], acc[2 * s], 2 * s, PC + 2 * s, Nq, bq_s, std::false_type{});
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (QKV) issue_n(a.Wqt, row_q(0), slot_q(0));
+            if (lora_q) issue_at(a.Aqt + (size_t)k_ad * r * D);
+            if (!kh || !(Dm & 64)) {
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                    for (int n = 0; n < NS; ++n) mfma_k(n, kk);
+            }
         }
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");         // Bf2
-        if (lora_q) {
-            // all operands first, then the MFMAs (one read-then-multiply per chunk would pay the LDS latency nine times)
-            bf16x8 fbt[LY_MAXCH];
+        exchange(y, x);
+    }
+    auto store_x = [&](int e) {                            // piece e of x''
+        const int rt = e / CT, ct = e % CT, row = wrow + 16 * rt + lm;
+        if (row < rows) *(f32x4 *)(a.x_out + (row0 + row) * D + wcol + 16 * ct) = x[ct][rt];
+    };
+    if (!QKV) {
 #pragma unroll
-            for (int c = 0; c < LY_MAXCH; ++c) fbt[c] = bt_frag(min(c * 64 + wc * 32 + lm, Nq - 1), a.r);
-            __builtin_amdgcn_sched_barrier(0);
+        for (int e = 0; e < 2 * CT; ++e) store_x(e);
+        return;
+    }
+
+    // ================================================================ C: qkv = LayerNorm1'(x'') Wq + bq + lora
+    layernorm(gbq_s, [&]() { if (LAYER) issue_n(a.Wqt, row_q(1), slot_q(1)); });
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // Q(0), Q(1), At_k
+    s16x4 fs[4];
+    if (lora_q) {                                          // one row tile per wave, to every wave
+        asm volatile("s_barrier" ::: "memory");
+        f32x4 c = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int c = 0; c < LY_MAXCH; ++c)
-                if (c < nchq) acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fbt[c], fs, acc[c], 0, 0, 0);
+        for (int k = 0; k < 2 * KT; ++k) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(at_frag(k), rd(act[k & 1], (k >> 1) * LY_TILE + wc * 2048), c, 0, 0, 0);
+        if (!kh) sh_s[wc * 64 + lane] = shrink_out(c);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt) fs[rt] = sh_s[rt * 64 + lane];
+    }
+    char *out = (char *)a.qkv_out + row0 * Nq * 2;
+    f32x4 sv[2];
+    // the columns of a round, staged in tiles 2 (q & 1) .., leave as whole rows of them
+    auto stage_read = [&](int q) {
+        const int pr = 128 * q + 128 <= Nq ? 16 : 8;       // 16-byte pieces of a row
+#pragma unroll
+        for (int j = 0; j < pr / 8; ++j) {
+            const int idx = tid + LY_THREADS * j, row = idx / pr, p = idx % pr;
+            sv[j] = *(const f32x4 *)(As + (2 * (q & 1) + (p >> 3)) * LY_TILE + row * 128 + (((p & 7) ^ ((row >> 1) & 7)) << 4));
         }
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");         // Bg2
-        // A lane owns one row, so storing from registers would touch 32 cache lines per instruction with 8 bytes each:
-        // the finished bf16 tile is laid out row-major in LDS and copied out in 16-byte pieces of consecutive threads
-        const int qstride = ((Nq * 2 + 255) & ~255) + 16;
-        // A lane holds columns 8 g + 4 lh + {0..3} of its row; the two lanes of a row trade halves (lane < 32 gives its piece of
-        // group g + 1 for the other's piece of group g) so that each ends up with eight consecutive columns: half as many
-        // LDS writes, 16 bytes each (a wave's LDS writes cost the same whatever their width).  Nq is a multiple of 64.
-        char *trow = (char *)lds + (wr * 32 + lm) * qstride + (wc * 32 + 8 * lh) * 2;
+    };
+    auto store = [&](int q) {
+        const int pr = 128 * q + 128 <= Nq ? 16 : 8;
 #pragma unroll
-        for (int c = 0; c < LY_MAXCH; ++c) {
-            if (c < nchq) {
+        for (int j = 0; j < pr / 8; ++j) {
+            const int idx = tid + LY_THREADS * j, row = idx / pr, p = idx % pr;
+            if (row < rows) *(f32x4 *)(out + (size_t)row * Nq * 2 + q * 256 + p * 16) = sv[j];
+        }
+    };
+    bf16x8 W[2][2 * KT];
+    auto fetch = [&](int q, int j) { W[q & 1][j] = rd(wn[j & 1], (q & 1 ? 0 : SLOT) + (j >> 1) * 2048); };
 #pragma unroll
-                for (int g = 0; g < 4; g += 2) {
-                    const bf16x4 w0 = {(bf16_t)acc[c][4 * g], (bf16_t)acc[c][4 * g + 1], (bf16_t)acc[c][4 * g + 2], (bf16_t)acc[c][4 * g + 3]};
-                    const bf16x4 w1 = {(bf16_t)acc[c][4 * g + 4], (bf16_t)acc[c][4 * g + 5], (bf16_t)acc[c][4 * g + 6], (bf16_t)acc[c][4 * g + 7]};
-                    *(u32x4 *)(trow + (c * 64 + 8 * g) * 2) = pair_halves(w0, w1);
+    for (int j = 0; j < 2 * KT; ++j) fetch(0, j);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const bool full = 128 * q + 128 <= Nq;
+        const int col = row_q(q);
+        s16x4 b2 = {0, 0, 0, 0};
+        if (lora_q) b2 = bt_frag(Bq_k, col + lm);
+        if (q + 2 < NQ) issue_n(a.Wqt, row_q(q + 2), slot_q(q + 2));    // W[q & 1] is in registers
+        const f32x4 b = *(const f32x4 *)(bq_s + col + 4 * lg);
+        f32x4 acc[4];
+        auto mfma = [&](int n, int rt0) {
+            const int k = n / 2, rt = rt0 + n % 2;
+            acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[q & 1][k], fa[k][rt], k == 0 ? b : acc[rt], 0, 0, 0);
+        };
+        auto next = [&](int n) {                           // the operands of the next round
+            if (q + 1 == NQ) return;
+            if (n == 0 && q > 0) {                         // (behind it: at least two stores of the last round, in a tile that has all its rows)
+                constexpr int ahead = 2 * KT;
+                const bool two = rows == 64 && (LAYER || q > 2);
+                if (q + 2 < NQ) {
+                    if (two) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ahead + 2) : "memory");
+                    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ahead) : "memory");
+                } else {
+                    if (two) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+                    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 }
             }
+            share(n, 0, NS - 2, 2 * KT, [&](int j) { fetch(q + 1, j); });
+        };
+        if (full) {
+            segment([&](int n) { mfma(n, 0); }, next);
+            segment([&](int n) { mfma(n, 2); }, [&](int n) {
+                if (n == 0 && q > 1) store(q - 2);
+                if (LAYER && n == NS - 1) {
+#pragma unroll
+                    for (int e = 0; e < 2 * CT; ++e)
+                        if (e / 2 == q) store_x(e);
+                }
+            });
+        } else {                                           // half a round: 64 columns, every wave 16 of them for its row half
+            if (kh) {
+#pragma unroll
+                for (int n = 0; n < NS; ++n) mfma(n, 2);
+                acc[0] = acc[2];
+                acc[1] = acc[3];
+            } else {
+#pragma unroll
+                for (int n = 0; n < NS; ++n) mfma(n, 0);
+            }
+            if (q > 1) store(q - 2);
         }
-    }
-    __syncthreads();
-    {
-        const int qstride = ((Nq * 2 + 255) & ~255) + 16, pieces = (Nq * 2) >> 4;
-        char *out = (char *)a.qkv_out + ((size_t)ob * a.T + t0) * Nq * 2;
-        for (int idx = tid; idx < rows * pieces; idx += LY_THREADS) {
-            const int row = idx / pieces, p = idx - row * pieces;
-            *(f32x4 *)(out + (size_t)row * Nq * 2 + p * 16) = *(const f32x4 *)((const char *)lds + row * qstride + p * 16);
+        if (lora_q) {
+            const s16x4 w = bt_operand(b2);
+            if (full) {
+#pragma unroll
+                for (int rt = 0; rt < 4; ++rt) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w, fs[rt], acc[rt], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w, kh ? fs[2 + rt] : fs[rt], acc[rt], 0, 0, 0);
+            }
         }
+        // the columns of round q - 1 are staged, those of round q - 2 have been read; the operands of the next round are in registers
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (q > 0) stage_read(q - 1);
+#pragma unroll
+        for (int rt = 0; rt < (full ? 4 : 2); ++rt)
+            put(As + (2 * (q & 1) + (full ? kh : 0)) * LY_TILE, wc, full ? rt : 2 * kh + rt, acc[rt]);
     }
+    store(NQ - 2);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    stage_read(NQ - 1);
+    store(NQ - 1);
 }
 
-template <int KT, bool HAS_PROJ, bool HAS_QKV> int launch_layer_t(const RowLayerArgs &a, hipStream_t st)
+template <int KT, bool LAYER, bool QKV> int launch_t(const RowLayerArgs &a, hipStream_t st)
 {
     constexpr int D = 64 * KT;
-    constexpr int LDS = ((KT < 2 ? 2 : KT) + LY_NS * KT) * 64 * 64 * 2 + (LY_MAX_DM + LY_MAX_NQ + 2 * D + 4 * D) * 4 + 16 * LY_AT_STRIDE * 2 + (KT == 3 ? 0 : GELU_TAB_ENTRIES * 8);
+    constexpr int LDS = LY_TILES * LY_TILE + 16 * KT * 2048 + (LY_MAX_DM + 3 * D + 2 * D + 4 * D) * 4 + 64 * 4 * 8 + LY_GELU * 8 + 16 * LY_AT_STRIDE * 2 + D * 16 * 2;
     static_assert(LDS <= 160 * 1024, "LDS budget");
-    auto kern = rowlayer_kernel<KT, HAS_PROJ, HAS_QKV>;
+    auto kern = rowlayer_kernel<KT, LAYER, QKV>;
     if (LDS > 64 * 1024) {
         static bool attr_set = false;   // raising the dynamic LDS limit is a per-kernel, process-wide setting
         if (!attr_set) {
@@ -656,18 +597,17 @@ template <int KT, bool HAS_PROJ, bool HAS_QKV> int launch_layer_t(const RowLayer
             attr_set = true;
         }
     }
-    const int tiles = (a.T + 63) / 64;
-    POLY_LAUNCH_SHMEM(POLY_STAGE_GEMM, kern, dim3((unsigned)(a.n_out * tiles)), dim3(LY_THREADS), LDS, st, a);
+    const bool flat = !a.adapter_of_out && !a.res_block_of_out;
+    const int flat_rows = flat ? a.n_out * a.T : 0;
+    const int grid = flat ? (flat_rows + 63) / 64 : a.n_out * ((a.T + 63) / 64);
+    POLY_LAUNCH_SHMEM(POLY_STAGE_GEMM, kern, dim3((unsigned)grid), dim3(LY_THREADS), LDS, st, a, flat_rows);
     return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
 }
 
-template <int KT> int launch_layer_kt(const RowLayerArgs &a, hipStream_t st)
+template <int KT> int launch_kt(const RowLayerArgs &a, hipStream_t st)
 {
-    const bool p = a.o != nullptr, q = a.qkv_out != nullptr;
-    if (p && q) return launch_layer_t<KT, true, true>(a, st);
-    if (p) return launch_layer_t<KT, true, false>(a, st);
-    if (q) return launch_layer_t<KT, false, true>(a, st);
-    return launch_layer_t<KT, false, false>(a, st);
+    if (!a.o) return launch_t<KT, false, true>(a, st);
+    return a.qkv_out ? launch_t<KT, true, true>(a, st) : launch_t<KT, true, false>(a, st);
 }
 
 }  // namespace
@@ -676,9 +616,7 @@ template <int KT> int launch_layer_kt(const RowLayerArgs &a, hipStream_t st)
 bool rowlayer_supported(int D, int Dm, int r)
 {
     if (!((D == 64 || D == 128 || D == 192) && Dm >= 128 && Dm % 64 == 0 && Dm <= LY_MAX_DM)) return false;
-    if (r != 0 && !(r >= 4 && r <= 16 && r % 4 == 0)) return false;
-    // Bt_k of the qkv linear [3 D][r] takes the place of the activation rows
-    return (long)3 * D * r * 2 <= (long)(D / 64 < 2 ? 2 : D / 64) * 64 * 64 * 2;
+    return r == 0 || (r >= 4 && r <= 16 && r % 4 == 0);
 }
 
 int launch_rowlayer(const RowLayerArgs &a, hipStream_t st)
@@ -687,8 +625,8 @@ int launch_rowlayer(const RowLayerArgs &a, hipStream_t st)
     const bool lora = (a.o && a.Apt) || (a.qkv_out && a.Aqt);
     if (!rowlayer_supported(a.D, a.Dm, lora ? a.r : 0)) return POLY_EINVAL;
     switch (a.D / 64) {
-    case 1: return launch_layer_kt<1>(a, st);
-    case 2: return launch_layer_kt<2>(a, st);
-    default: return launch_layer_kt<3>(a, st);
+    case 1: return launch_kt<1>(a, st);
+    case 2: return launch_kt<2>(a, st);
+    default: return launch_kt<3>(a, st);
     }
 }
