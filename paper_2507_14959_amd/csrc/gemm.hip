@@ -742,6 +742,8 @@ static int launch_gemm_dma(const GemmArgs &g, hipStream_t st)
     return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
 }
 
+static long product_tiles(const GemmArgs &g, int bm, int bn) { return (long)g.n_in * ((g.T + bm - 1) / bm) * ((g.N + bn - 1) / bn); }
+
 int launch_gemm(const GemmArgs &g, int dtype, hipStream_t st)
 {
     if (g.n_in <= 0 || g.T <= 0) return POLY_OK;
@@ -758,8 +760,17 @@ int launch_gemm(const GemmArgs &g, int dtype, hipStream_t st)
         gf.T = (int)rows; gf.n_in = 1;          // (Tout stays the block length: it places the output blocks)
     }
     if (!bf16 || g.K % 64 != 0 || g.N % 8 != 0 || !gemm_aligned(g)) return launch_gemm_ks(gf, dtype, st);
-    // a long contraction on fewer 128 x 128 tiles than half the CUs: smaller tiles and a split contraction (3 frames of the
-    // 768-wide backbone: 30 tiles for proj and fc2, 90 and 120 for qkv and fc1; 1338 -> 906 us per forward)
-    if (g.K >= 512 && (long)gf.n_in * ((gf.T + 127) / 128) * ((g.N + 127) / 128) < 128) return launch_gemm_ks(gf, dtype, st);
+    // A long contraction on fewer 128 x 128 tiles than half the CUs takes smaller tiles: with the contraction split over the waves (gemm_ks.hip)
+    // where tiles of 32 x 64 get a CU each, and above a contraction of 1024 also where tiles of 64 x 64 do; else tiles of 64 x 64 that share a
+    // ring, two workgroups per CU.  us per product of the 768-wide backbone, split / shared ring / 128 x 128 (rows x K -> N):
+    //   197 x 768 -> 2304  7.0 / 7.1 / 12.9    591 x 768 -> 768   8.3 / 8.6 / 15.6    591 x 3072 -> 768   13.4 / 19.2 / 41.7
+    //   197 x 768 -> 3072  8.6 / 7.6 / 14.6    985 x 768 -> 768   9.4 / 8.8 / 15.8    1182 x 3072 -> 768  16.8 / 19.5 / 42.2
+    //   591 x 768 -> 2304 15.1 / 9.5 / 13.1    1576 x 768 -> 768 15.9 / 10.3 / 16.0   1576 x 3072 -> 768  29.2 / 23.6 / 42.0
+    //   591 x 768 -> 3072 16.6 / 10.3 / 14.8   985 x 768 -> 2304 21.4 / 14.2 / 13.8 (144 tiles of 128 x 128)
+    if (g.K >= 512 && product_tiles(gf, 128, 128) < 128) {
+        if (product_tiles(gf, 32, 64) <= 256 || (g.K > 1024 && product_tiles(gf, 64, 64) <= 256)) return launch_gemm_ks(gf, dtype, st);
+        launch_dma<64, 64, 2, 2, 4>(gf, st);
+        return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
+    }
     return launch_gemm_dma(gf, st);
 }

@@ -1,0 +1,40 @@
+"""Products between the few tiles whose contraction is split over the waves and the many of 128 x 128: tiles of 64 x 64 that share a ring."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2507_14959_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_xblocks,T,K,N,r,per_block", [
+    (1, 197, 768, 3072, 8, 1),       # 336 tiles of 32 x 64: the first side of the rule
+    (5, 197, 768, 768, 16, 2),       # row tiles across blocks, two branches each
+    (31, 17, 768, 1000, 20, 2),      # a block ends inside nearly every tile; columns that fill no tile; a rank of two steps
+    (2, 131, 1088, 2048, 8, 1),      # above a contraction of 1024, more tiles of 64 x 64 than fit: shared ring
+    (2, 131, 1088, 1600, 8, 1),      # and few enough: split contraction
+    (4, 128, 512, 2112, 4, 1),       # the shortest contraction of the rule, whole row tiles
+])
+def test_against_the_oracle(n_xblocks, T, K, N, r, per_block):
+    case = synth.make_lora_linear_case(dtype=synth.DT_BF16, seed=N + T, n_xblocks=n_xblocks, T=T, Kdim=K, Ndim=N, n_adapters=5, r=r, per_block=per_block)
+    up = lambda a, dt=torch.bfloat16: torch.from_numpy(np.ascontiguousarray(a)).to(device="cuda", dtype=dt).contiguous()  # noqa: E731
+    R = int(case["row_offsets"][-1])
+    y = torch.full((R, T, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(binding.poly_lora_linear_workspace_bytes(n_xblocks, T, r, R, synth.DT_BF16), dtype=torch.uint8, device="cuda")
+    binding.poly_lora_linear(up(case["X"]), up(case["W"].T), up(case["bias"], torch.float32), up(np.swapaxes(case["A"], 1, 2)),
+                             up(np.swapaxes(case["B"], 1, 2)), 0.75, up(case["row_offsets"], torch.int32), up(case["adapter_ids"], torch.int32), R, y, ws,
+                             dev_status=status)
+    torch.cuda.synchronize()
+    want = oracle.lora_linear(case, s=0.75)
+    assert int(status.item()) == 0
+    # bf16 (8 bits) rounds the output and every rank of the shrink output by at most 2^-8 of itself; sums are fp32
+    slack = np.empty_like(want)
+    for f in range(n_xblocks):
+        for b in range(case["row_offsets"][f], case["row_offsets"][f + 1]):
+            k = case["adapter_ids"][b]
+            slack[b] = np.abs(0.75 * case["X"][f].astype(np.float64) @ case["A"][k]) @ np.abs(case["B"][k])
+    over = np.abs(y.float().cpu().numpy() - want) - (2.0 ** -8 * np.abs(want) + 2.0 ** -8 * slack + 1e-4)
+    assert over.max() <= 0
