@@ -719,30 +719,57 @@ static void launch_dma(const GemmArgs &g, hipStream_t st)
     launch_dma_ek<BM, BN, WM, WN, NS, 0>(g, st);
 }
 
-static int launch_gemm_dma(const GemmArgs &g, hipStream_t st)
+static long product_tiles(const GemmArgs &g, int bm, int bn) { return (long)g.n_in * ((g.T + bm - 1) / bm) * ((g.N + bn - 1) / bn); }
+
+// What a product takes on a tile, in us: rounds of as many workgroups as fit the chip, and a last round that is cheaper where it leaves CUs with
+// fewer workgroups than they hold.  Per round f + k K, plus `fan` where rows fan out, plus `res` with a residual.  Fitted to 89 products
+// (788 to 50432 rows; K -> N 192 -> 576, 768; 384 -> 384, 1152, 1536; 768 -> 768, 2304, 3072; 3072 -> 768; rank 16) within 5 to 10 %: the tile it
+// picks is on average 0.9 % slower than the fastest of the four, at worst 16 % (17730 x 192 -> 768); fixed thresholds for tiles of 256 x 256 and
+// 256 x 128, and 128 x 128 on four waves of 64 x 64 else, were 12 % slower on average.
+// us, 256 x 256 / 256 x 128 / 128 x 128 / 128 x 64 (rows x K -> N): 1773 x 192 -> 576, two branches 16.0 / 11.2 / 7.8 / 7.2;
+// 5910 x 768 -> 3072 58 / 57 / 47 / 48; 12608 x 768 -> 768 45 / 45 / 47 / 34; 12608 x 768 -> 2304 55 / 71 / 62 / 69;
+// 26201 x 3072 -> 768 223 / 185 / 255 / 216; 50432 x 768 -> 2304, two branches 238 / 278 / 267 / 308.
+struct TileCost {
+    int bm, bn, per_cu;                                    // workgroups per CU
+    float start, f, k, fan, res, last1, last2;             // last1, last2: share of a round with one / two workgroups per CU in it
+};
+// Where the device alone knows how many blocks there are, the mean over half to all of the bound: which round ends well at the bound says nothing
+// (64 frames with one to three adapters each have 115 blocks of a bound of 192).
+static float tile_cost(const TileCost &c, const GemmArgs &g)
 {
-    // long contractions with many tiles: 256-row tiles cut the L2 -> LDS traffic per flop; short contractions (K = 192)
-    // and small batches keep 128-row tiles, whose workgroups are light enough to overlap their load latency and epilogues
-    // across a CU
-    const long tiles256 = (long)g.n_in * ((g.T + 255) / 256) * ((g.N + 255) / 256);
-    const bool big = g.T > 128 && g.K >= 512;
-    if (big && g.N % 256 == 0 && tiles256 >= 512) {
-        launch_dma<256, 256, 2, 4, 2>(g, st);
-    } else if (big && g.N % 128 == 0 && (long)g.n_in * ((g.T + 255) / 256) * ((g.N + 127) / 128) >= 512) {
-        launch_dma<256, 128, 4, 2, 3>(g, st);
-    } else if (g.N % 128 == 0 || g.N >= 1024) {
-        launch_dma<128, 128, 2, 2, 2>(g, st);
-    } else if ((long)g.n_in * ((g.T + 127) / 128) * ((g.N + 63) / 64) < 256) {
-        // fewer 128 x 64 tiles than CUs (the patch embedding of a small batch): half the rows per tile, twice the workgroups,
-        // two of them per CU
-        launch_dma<64, 64, 2, 2, 4>(g, st);
-    } else {
-        launch_dma<128, 64, 2, 2, 2>(g, st);
+    const long all = product_tiles(g, c.bm, c.bn), slots = 256L * c.per_cu;
+    const float round = c.f + c.k * g.K + (g.out_off ? c.fan : 0.f) + (g.mode == EPI_RESID ? c.res : 0.f);
+    float rounds = 0.f;
+    const int from = g.n_in_dev ? 8 : 16;
+    for (int part = from; part <= 16; ++part) {
+        const long n = (all * part + 15) / 16, rest = n % slots;
+        const int per_cu = (int)((rest + 255) / 256);
+        rounds += (float)(n / slots) + (rest == 0 ? 0.f : per_cu == c.per_cu ? 1.f : per_cu == 1 ? c.last1 : c.last2);
     }
-    return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
+    return c.start + round * rounds / (float)(17 - from);
 }
 
-static long product_tiles(const GemmArgs &g, int bm, int bn) { return (long)g.n_in * ((g.T + bm - 1) / bm) * ((g.N + bn - 1) / bn); }
+static int launch_gemm_dma(const GemmArgs &g, hipStream_t st)
+{
+    static const TileCost cost[4] = {{128, 64, 3, 2.1f, 3.7f, 0.0140f, 2.5f, 3.5f, 0.62f, 0.80f},
+                                     {128, 128, 2, 3.3f, 2.7f, 0.0196f, 3.1f, 8.6f, 0.51f, 0.f},
+                                     {256, 128, 1, -1.5f, 8.1f, 0.0137f, 2.4f, 4.0f, 0.f, 0.f},
+                                     {256, 256, 1, -3.4f, 11.4f, 0.0235f, 4.9f, 13.3f, 0.f, 0.f}};
+    if (g.pos) {                                           // patch embedding: row tiles inside blocks, an epilogue that fetches nothing ahead
+        if (g.N % 128 == 0) launch_dma<128, 128, 2, 2, 2>(g, st);
+        else if (product_tiles(g, 128, 64) < 256) launch_dma<64, 64, 2, 2, 4>(g, st);    // (147 tiles of 128 x 64: 14.3 us, as 64 x 64 9 us)
+        else launch_dma<128, 64, 2, 2, 2>(g, st);
+        return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
+    }
+    int best = 0;
+    for (int i = 1; i < 4; ++i)
+        if (tile_cost(cost[i], g) < tile_cost(cost[best], g)) best = i;
+    if (best == 3) launch_dma<256, 256, 2, 4, 2>(g, st);
+    else if (best == 2) launch_dma<256, 128, 4, 2, 3>(g, st);
+    else if (best == 1) launch_dma<128, 128, 4, 2, 2>(g, st);
+    else launch_dma<128, 64, 4, 1, 2>(g, st);
+    return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
+}
 
 int launch_gemm(const GemmArgs &g, int dtype, hipStream_t st)
 {

@@ -38,3 +38,13 @@ def test_against_the_oracle(n_xblocks, T, K, N, r, per_block):
             slack[b] = np.abs(0.75 * case["X"][f].astype(np.float64) @ case["A"][k]) @ np.abs(case["B"][k])
     over = np.abs(y.float().cpu().numpy() - want) - (2.0 ** -8 * np.abs(want) + 2.0 ** -8 * slack + 1e-4)
     assert over.max() <= 0
+
+
+@pytest.mark.parametrize("n_xblocks,T,K,N,r,per_block", [
+    (9, 197, 192, 576, 8, 2),        # 128 x 64, two branches: the expand's operands fetched ahead
+    (40, 37, 192, 200, 20, 3),       # blocks shorter than a wave's rows, columns that fill no tile, a rank of two steps
+    (24, 131, 192, 1000, 8, 1),      # 128 x 128 on eight waves, the last column tile cut short
+    (30, 64, 320, 1032, 16, 2),      # as many rows as a wave's region: two blocks in it
+])
+def test_tiles_of_a_wave_per_32_rows(n_xblocks, T, K, N, r, per_block):
+    test_against_the_oracle(n_xblocks, T, K, N, r, per_block)
