@@ -322,8 +322,8 @@ int launch_layernorm(const float *x, void *y, const float *gain, const float *sh
 // S[ob] = scale * X[in_block_of_out[ob]] At[adapter_of_out[ob]]^T, zero padded to RP columns.  pair_off (nullable): CSR offsets
 // [n_in + 1] of the output blocks of every input block, when the output blocks of one input block are consecutive (fan-out):
 // lets one workgroup serve two of them from one read of the input rows
-int launch_shrink(const void *X, int T, int K, const void *At, int r, int RP, float scale, int n_out,
-                  const int *n_out_dev, const int *in_block_of_out, const int *adapter_of_out, const int *pair_off, void *S,
+int launch_shrink(const void *X, int T, int K, const void *At, int r, int RP, float scale, int n_in, int n_out,
+                  const int *n_out_dev, const int *in_block_of_out, const int *adapter_of_out, const int *out_off, void *S,
                   int dtype, hipStream_t st);
 
 // the CSR check, the row maps and the shrink of an isolated bf16 linear in one launch

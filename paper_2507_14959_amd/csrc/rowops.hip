@@ -1,6 +1,6 @@
 // Row-wise and bookkeeping kernels of the forward: CSR validation, patch gathering, LayerNorm,
 // LoRA shrink (x A_k), per-adapter heads with sigmoid, and the optional merge to label space.
-#include "poly_dev.h"
+#include "rowtile.h"
 
 #include <type_traits>
 
@@ -167,6 +167,54 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *x, T *y
 constexpr int SH_NS = 6;    // 32-element K steps whose operands are in flight together
 constexpr int SH_CSR_MAX = 1024;   // input blocks at most where the kernel reads the CSR arrays itself
 
+// What a workgroup of output block ob works on: input block xb, adapter k_ad, and the output block ob2 (adapter k_ad2, -1: none) that it does
+// along with its own.  False: nothing to do (past the true count, no adapter, done by the workgroup of ob - 1, arrays that the check rejects).
+template <bool CSR>
+__device__ __forceinline__ bool shrink_blocks(int ob, bool paired, int n_out, const int *n_out_dev, const int *in_block_of_out,
+                                              const int *adapter_of_out, const int *pair_off, const PrepArgs &pa, int &xb, int &k_ad,
+                                              int &k_ad2, int &ob2)
+{
+    ob2 = -1;
+    if constexpr (CSR) {
+        __shared__ int offs[SH_CSR_MAX + 1];
+        for (int f = threadIdx.x; f <= pa.F; f += 256) offs[f] = pa.row_offsets[f];
+        __syncthreads();
+        const int R = offs[pa.F];
+        if (offs[0] != 0 || R < 0 || R > pa.R_cap || ob >= R) return false;    // (rejected, or past the true count)
+        k_ad = pa.adapter_ids[ob];
+        k_ad2 = pa.adapter_ids[min(ob + 1, R - 1)];
+        int before = 0;                                          // input blocks whose rows all lie before output block ob
+        for (int f = threadIdx.x & 63; f < ((pa.F + 63) & ~63); f += 64) before += __popcll(__ballot(f < pa.F && offs[f + 1] <= ob));
+        xb = min(before, pa.F - 1);
+        if (paired) {
+            const int p0 = offs[xb], p1 = offs[xb + 1];
+            if ((ob - p0) & 1) return false;                     // done by the workgroup of ob - 1
+            if (ob + 1 < min(p1, R)) ob2 = ob + 1;
+        }
+        if ((unsigned)k_ad >= (unsigned)pa.n_adapters || (ob2 >= 0 && (unsigned)k_ad2 >= (unsigned)pa.n_adapters)) return false;   // (rejected)
+        if (ob2 < 0) k_ad2 = -1;
+    } else {
+        // first round trip: four loads with unconditional addresses, so that they are requested together.  The arrays have
+        // n_out entries; those past the true count are read here but never used.
+        // (volatile: the compiler would otherwise sink each load below the early exit that precedes its first use)
+        const int *pn = n_out_dev ? n_out_dev : adapter_of_out, *pi = in_block_of_out ? in_block_of_out + ob : adapter_of_out + ob;
+        const int n_ld = *(const volatile int *)pn, xb_ld = *(const volatile int *)pi;
+        const int k1_raw = *(const volatile int *)(adapter_of_out + ob), k2_raw = *(const volatile int *)(adapter_of_out + min(ob + 1, n_out - 1));
+        const int n = n_out_dev ? min(n_ld, n_out) : n_out;
+        xb = in_block_of_out ? xb_ld : ob;
+        if (ob >= n) return false;
+        if (paired) {                                                // second round trip
+            const int p0 = *(const volatile int *)(pair_off + xb), p1 = *(const volatile int *)(pair_off + xb + 1);
+            if ((ob - p0) & 1) return false;                         // done by the workgroup of ob - 1
+            if (ob + 1 < min(p1, n)) ob2 = ob + 1;
+        }
+        k_ad = k1_raw;
+        k_ad2 = ob2 >= 0 ? k2_raw : -1;
+        if (k_ad < 0 && k_ad2 < 0) return false;
+    }
+    return true;
+}
+
 template <int MS, int NG, bool CSR>
 __global__ __launch_bounds__(256) void shrink_bf16_kernel(const bf16_t *X, int T, int K, const bf16_t *At, int r, int RP,
                                                           float scale, int n_out, const int *n_out_dev,
@@ -186,44 +234,8 @@ __global__ __launch_bounds__(256) void shrink_bf16_kernel(const bf16_t *X, int T
     }
     const int ob = blockIdx.x / subs, row0 = (blockIdx.x % subs) * (16 * MS);
     const bool paired = NG == 2 && RP == 16 && (CSR || (pair_off && in_block_of_out));
-    int xb, k_ad, k_ad2, ob2 = -1;
-    if constexpr (CSR) {
-        __shared__ int offs[SH_CSR_MAX + 1];
-        for (int f = threadIdx.x; f <= pa.F; f += 256) offs[f] = pa.row_offsets[f];
-        __syncthreads();
-        const int R = offs[pa.F];
-        if (offs[0] != 0 || R < 0 || R > pa.R_cap || ob >= R) return;          // (rejected, or past the true count)
-        k_ad = pa.adapter_ids[ob];
-        k_ad2 = pa.adapter_ids[min(ob + 1, R - 1)];
-        int before = 0;                                          // input blocks whose rows all lie before output block ob
-        for (int f = threadIdx.x & 63; f < ((pa.F + 63) & ~63); f += 64) before += __popcll(__ballot(f < pa.F && offs[f + 1] <= ob));
-        xb = min(before, pa.F - 1);
-        if (paired) {
-            const int p0 = offs[xb], p1 = offs[xb + 1];
-            if ((ob - p0) & 1) return;                           // done by the workgroup of ob - 1
-            if (ob + 1 < min(p1, R)) ob2 = ob + 1;
-        }
-        if ((unsigned)k_ad >= (unsigned)pa.n_adapters || (ob2 >= 0 && (unsigned)k_ad2 >= (unsigned)pa.n_adapters)) return;   // (rejected)
-        if (ob2 < 0) k_ad2 = -1;
-    } else {
-        // first round trip: four loads with unconditional addresses, so that they are requested together.  The arrays have
-        // n_out entries; those past the true count are read here but never used.
-        // (volatile: the compiler would otherwise sink each load below the early exit that precedes its first use)
-        const int *pn = n_out_dev ? n_out_dev : adapter_of_out, *pi = in_block_of_out ? in_block_of_out + ob : adapter_of_out + ob;
-        const int n_ld = *(const volatile int *)pn, xb_ld = *(const volatile int *)pi;
-        const int k1_raw = *(const volatile int *)(adapter_of_out + ob), k2_raw = *(const volatile int *)(adapter_of_out + min(ob + 1, n_out - 1));
-        const int n = n_out_dev ? min(n_ld, n_out) : n_out;
-        xb = in_block_of_out ? xb_ld : ob;
-        if (ob >= n) return;
-        if (paired) {                                                // second round trip
-            const int p0 = *(const volatile int *)(pair_off + xb), p1 = *(const volatile int *)(pair_off + xb + 1);
-            if ((ob - p0) & 1) return;                               // done by the workgroup of ob - 1
-            if (ob + 1 < min(p1, n)) ob2 = ob + 1;
-        }
-        k_ad = k1_raw;
-        k_ad2 = ob2 >= 0 ? k2_raw : -1;
-        if (k_ad < 0 && k_ad2 < 0) return;
-    }
+    int xb, k_ad, k_ad2, ob2;
+    if (!shrink_blocks<CSR>(ob, paired, n_out, n_out_dev, in_block_of_out, adapter_of_out, pair_off, pa, xb, k_ad, k_ad2, ob2)) return;
     const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, lc = lane >> 4;
     const bf16_t *xblk = X + (size_t)xb * T * K + lc * 8;
     int xoff[MS];                                                // row li of subtile m (the host has checked T * K < 2^31)
@@ -314,6 +326,187 @@ __global__ __launch_bounds__(256) void shrink_bf16_kernel(const bf16_t *X, int T
             }
         }
     }
+}
+
+// The same product with the rows streamed through LDS and a workgroup that stays with them (K a multiple of 128 or 192).
+// A wave owns a ring of items of 16 rows x 32 CS columns (global_load_lds_dwordx4, contiguous runs of 64 CS bytes; the other slots are on
+// their way while one is read) and needs no barrier for it.  Per chunk of 32 CS columns it holds the At rows of its one or two groups
+// as fragments and passes over up to SH_MS subtiles of X, so an adapter's At is read once per 16 SH_MS rows.  The four waves are WK
+// parts of K times 4 / WK runs of subtiles (WK = 4, 2 or 1, the largest that divides the chunks of K); partial sums meet in LDS once, at the end.
+// The product is transposed (At is the A operand): a lane ends up with four consecutive ranks of one row and stores them in one piece.
+// Where output blocks fan out of input blocks (MODE 1: row maps made before; 2: the CSR arrays themselves, checked by the last workgroup) the
+// grid runs over the input blocks and `units` shares of their branches: the rows are requested before anything else is known.
+template <int CS> constexpr int sh_ring() { return CS == 6 ? 3 : 4; }
+constexpr int SH_MS = 7;
+
+template <int CS, int MODE>
+__global__ __launch_bounds__(256, 2) void shrink_stream_kernel(const bf16_t *X, int T, int K, const bf16_t *At, int r, int RP, float scale, int n_out,
+                                                               const int *n_out_dev, const int *in_block_of_out, const int *adapter_of_out,
+                                                               const int *out_off, bf16_t *S, int wk_log, int parts, int wgs, int units, const PrepArgs pa)
+{
+    constexpr int ROW = 64 * CS, ITEM = 16 * ROW, RING = sh_ring<CS>();      // bytes, bytes, items
+    __shared__ __attribute__((aligned(16))) char ring[4][RING * ITEM];
+    static_assert(SH_MS * 2 * 1024 <= RING * ITEM, "a wave's partial sums fit its ring");
+    if (MODE == 2 && blockIdx.x == gridDim.x - 1) {
+        prep_block(pa.row_offsets, pa.adapter_ids, pa.F, pa.R_cap, pa.n_adapters, pa.meta, pa.frame_of_row, pa.adapter_of_row, pa.dev_status);
+        return;
+    }
+    const int b = MODE == 0 ? blockIdx.x / wgs : blockIdx.x / (wgs * units);          // output block (MODE 0) or input block
+    const int unit = MODE == 0 ? 0 : blockIdx.x / wgs % units;                      // of the branches, pair by pair (RP = 16) or one by one
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, lc = lane >> 4;
+    const int wk = wave & ((1 << wk_log) - 1), wr = wave >> wk_log;
+    // subtiles of 16 rows, cut into `parts` runs that differ by one at most (wgs workgroups of 4 / WK runs each)
+    const int nt = (T + 15) >> 4, part = (blockIdx.x % wgs) * (4 >> wk_log) + wr;
+    const int m0 = part < parts ? (int)((long)nt * part / parts) : nt, ms = part < parts ? (int)((long)nt * (part + 1) / parts) - m0 : 0;
+    const int chunks = (K / (32 * CS)) >> wk_log;                // of this wave
+    // item layout: 16-byte piece c of row i at position c ^ f(i) of the row, where the 16 lanes of a fragment read (one piece of 16 rows) then
+    // lie in 16 different groups of four banks; the lane that fills a position fetches the piece that belongs there
+    auto swz = [](int i) { return CS == 6 ? (i >> 1) & 7 : i & 15; };
+    int d_row[CS], d_col[CS];
+#pragma unroll
+    for (int i = 0; i < CS; ++i) {
+        const int p = 64 * i + lane;
+        d_row[i] = p / (4 * CS);
+        d_col[i] = ((p % (4 * CS)) ^ swz(d_row[i])) * 16;
+    }
+    const char *const mine = ring[wave];
+    const unsigned ring0 = __builtin_amdgcn_readfirstlane(lds_addr_of(mine));
+    int xb = b, ob = b, ob_end = b + 1;
+    if constexpr (MODE == 0) {
+        const int *pn = n_out_dev ? n_out_dev : adapter_of_out;
+        const int n_ld = *(const volatile int *)pn, xb_ld = *(const volatile int *)(in_block_of_out ? in_block_of_out + b : adapter_of_out + b);
+        if (b >= (n_out_dev ? min(n_ld, n_out) : n_out)) return;
+        if (in_block_of_out) xb = __builtin_amdgcn_readfirstlane(xb_ld);
+    }
+    const char *const xbase = (const char *)(X + (size_t)xb * T * K + (size_t)wk * chunks * (32 * CS));
+    const char *const abase = (const char *)(At + (size_t)wk * chunks * (32 * CS));
+    // Items of one pass, in order: subtiles 0 .. ms - 1 of chunk 0, then for every further chunk the At rows of its groups (item < 0) and the
+    // subtiles.  Chunk 0's At comes straight into registers.
+    int q_item = 0, q_chunk = 0, ng = 1;
+    unsigned q_slot = 0, slot = 0;
+    const char *a_row[2];
+    int a_last[2];
+    auto request = [&]() {
+        const bool is_a = q_item < 0;
+        const int g = q_item == -1 ? ng - 1 : 0, row = 16 * (m0 + q_item);
+        // rows past the last one repeat it: they feed results that are dropped (X) or zeroed (At) at the store
+        const char *base = (is_a ? (g ? a_row[1] : a_row[0]) : xbase + (size_t)row * K * 2) + (size_t)q_chunk * ROW;
+        const int last = is_a ? (g ? a_last[1] : a_last[0]) : T - 1 - row;
+#pragma unroll
+        for (int i = 0; i < CS; ++i) glds16_s(base, (unsigned)(min(d_row[i], last) * (2 * K) + d_col[i]), ring0 + q_slot + i * 1024);
+        if (++q_item == ms) { q_item = -ng; ++q_chunk; }
+        q_slot = q_slot == (RING - 1) * ITEM ? 0 : q_slot + ITEM;
+    };
+    const int first = max(0, min(RING - 1, ms - 1));                     // requested before the groups are known (the last subtile's successor depends on them)
+    bool asked = unit == 0;                                      // (of the later ones it is not known whether there is work)
+    for (int i = 0; asked && i < first; ++i) request();
+    if constexpr (MODE > 0) {
+        const int *off = MODE == 2 ? pa.row_offsets : out_off;
+        const int p0 = off[b], p1 = off[b + 1], n = MODE == 2 ? off[pa.F] : n_out_dev ? min(*n_out_dev, n_out) : n_out;
+        ob = __builtin_amdgcn_readfirstlane(p0);
+        ob_end = __builtin_amdgcn_readfirstlane(p1);
+        if (ob < 0 || ob_end > n || n > n_out || (MODE == 2 && off[0] != 0)) ob_end = ob;      // (rejected)
+    }
+    const bool paired = MODE > 0 && RP == 16;
+    const int *ids = MODE == 2 ? pa.adapter_ids : adapter_of_out;
+    const int step = paired ? 2 : 1;
+    bool again = false;
+    for (ob += step * unit; ob < ob_end; ob += step * units) {
+        int ksel[2], osel[2] = {ob, ob};
+        ksel[0] = ksel[1] = __builtin_amdgcn_readfirstlane(ids[ob]);
+        if (paired) {
+            osel[1] = ob + 1 < ob_end ? ob + 1 : -1;
+            ksel[1] = __builtin_amdgcn_readfirstlane(ids[min(ob + 1, ob_end - 1)]);
+        }
+        if (MODE == 2 && ((unsigned)ksel[0] >= (unsigned)pa.n_adapters || (unsigned)ksel[1] >= (unsigned)pa.n_adapters)) break;     // (rejected)
+        if (ksel[0] < 0 && (ksel[1] < 0 || osel[1] < 0)) continue;
+        for (int j0 = 0; j0 < (paired ? 16 : RP); j0 += 32) {
+            ng = paired ? (osel[1] >= 0 ? 2 : 1) : RP - j0 > 16 ? 2 : 1;
+            const int rank0[2] = {j0, paired ? 0 : j0 + 16};
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                const int r0 = min(rank0[g], r - 1);
+                a_row[g] = abase + ((size_t)max(ksel[g], 0) * r + r0) * K * 2;
+                a_last[g] = r - 1 - r0;
+            }
+            if (again) {                                         // another pass over the rows: the ring is free once all have read the sums
+                __syncthreads();
+                q_item = q_chunk = 0; q_slot = slot = 0;
+            }
+            if (again || !asked)
+                for (int i = 0; i < first; ++i) request();
+            again = asked = true;
+            bf16x8 fa[2][CS], fx[CS];
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+                if (g < ng)
+#pragma unroll
+                    for (int u = 0; u < CS; ++u) fa[g][u] = *(const bf16x8 *)(a_row[g] + (size_t)min(li, a_last[g]) * (2 * K) + (4 * u + lc) * 16);
+            f32x4 acc[SH_MS][2];
+#pragma unroll
+            for (int m = 0; m < SH_MS; ++m) acc[m][0] = acc[m][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            int left = ms > 0 ? ms * chunks + ng * (chunks - 1) : 0;   // items not yet requested
+            const int ahead = min(RING - 1, left);
+            for (int i = first; i < ahead; ++i) request();
+            left -= ahead;
+            // the next item: request one more (its slot was read before the last MFMAs), wait for this one's loads, read it
+            auto next = [&](bf16x8 (&f)[CS]) {
+                if (left > 0) {
+                    request();
+                    --left;
+                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((RING - 1) * CS) : "memory");
+                } else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                const char *it = mine + slot + li * ROW;
+#pragma unroll
+                for (int u = 0; u < CS; ++u) f[u] = *(const bf16x8 *)(it + ((4 * u + lc) ^ swz(li)) * 16);
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // before the slot is requested again
+                slot = slot == (RING - 1) * ITEM ? 0 : slot + ITEM;
+            };
+            if (ms > 0)
+                for (int c = 0; c < chunks; ++c) {
+                    if (c > 0) {
+                        next(fa[0]);
+                        if (ng == 2) next(fa[1]);
+                    }
+#pragma unroll
+                    for (int m = 0; m < SH_MS; ++m)
+                        if (m < ms) {
+                            next(fx);
+#pragma unroll
+                            for (int u = 0; u < CS; ++u) acc[m][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[0][u], fx[u], acc[m][0], 0, 0, 0);
+                            if (ng == 2) {
+#pragma unroll
+                                for (int u = 0; u < CS; ++u) acc[m][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[1][u], fx[u], acc[m][1], 0, 0, 0);
+                            }
+                        }
+                }
+            // partial sums of the WK waves of a run: wave wk finishes the values v = 2 m + g with v % WK == wk
+            if (wk_log > 0) {
+                f32x4 *red = (f32x4 *)ring[wave];
+#pragma unroll
+                for (int v = 0; v < 2 * SH_MS; ++v)
+                    if (v / 2 < ms && v % 2 < ng) red[v * 64 + lane] = acc[v / 2][v % 2];
+                __syncthreads();
+            }
+            const int share = wk_log == 0 ? 0 : ng == 2 ? wk : 2 * wk, stride = wk_log == 0 ? 1 : (ng == 2 ? 1 : 2) << wk_log;
+#pragma unroll
+            for (int v = 0; v < 2 * SH_MS; ++v) {
+                const int m = v / 2, g = v % 2;
+                if (m >= ms || g >= ng || (v & (stride - 1)) != share) continue;
+                f32x4 sum = acc[m][g];
+                if (wk_log > 0) {
+                    sum = ((const f32x4 *)ring[wr << wk_log])[v * 64 + lane];
+                    for (int w = 1; w < 1 << wk_log; ++w) sum += ((const f32x4 *)ring[(wr << wk_log) + w])[v * 64 + lane];
+                }
+                const int tt = 16 * (m0 + m) + li, rk = rank0[g] + 4 * lc;
+                bf16x4 o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = rk + e < r ? (bf16_t)(scale * sum[e]) : (bf16_t)0.f;
+                if (tt < T && ksel[g] >= 0 && osel[g] >= 0 && rk < RP) *(bf16x4 *)(S + ((size_t)osel[g] * T + tt) * RP + rk) = o;
+            }
+        }
+    }
+    if (!again) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // nothing lands in this LDS once another workgroup owns it
 }
 
 // ------------------------------------------------------------------ heads and merge to label space
@@ -464,6 +657,39 @@ static void launch_shrink_bf16(hipStream_t st, const bf16_t *X, int T, int K, co
                 RP, scale, n_out, n_out_dev, in_block_of_out, adapter_of_out, pair_off, S, pa);
 }
 
+// False where the other kernel is to run: columns that the items do not divide, addresses that their 16-byte loads do not allow, and little work.
+// The other one's chain is shorter where a wave has one batch of columns (K <= 768) and few workgroups; per call on 197-token blocks of rank 16, us,
+// other / this: 16 blocks x 2 branches x 768 6.3 / 6.8, 32 x 2 8.7 / 7.9, 256 x 2 42.4 / 18.2 (77 MB of rows, in a call of poly_lora_linear on
+// 2304 columns; 77 MB at the rate of a large copy take 16); 64 x 2 x 384 8.3 / 8.6, 128 x 2 12.2 / 9.8; 128 x 2 x 192 8.5 / 8.0;
+// 4 x 1 x 1024 5.5 / 5.1, 4 x 1 x 3072 11.9 / 7.0, 64 x 2 x 3072 34.6 / 19.4.  Of rank 32, 113 tokens: 64 x 2 x 768 8.6 / 9.9, 128 x 2 15.4 / 12.6.
+// Runs of 16 to 112 rows, the shortest with which all workgroups are on the chip at once (two per CU).
+// blocks: output blocks (MODE 0) or input blocks
+template <int MODE>
+static bool launch_shrink_stream(hipStream_t st, const bf16_t *X, int T, int K, const bf16_t *At, int r, int RP, float scale, int blocks, int n_out,
+                                 const int *n_out_dev, const int *in_block_of_out, const int *adapter_of_out, const int *out_off, bf16_t *S,
+                                 const PrepArgs &pa)
+{
+    const int cs = K % 192 == 0 ? 6 : K % 128 == 0 ? 4 : 0;
+    if (!cs || (((uintptr_t)X | (uintptr_t)At) & 15) || ((uintptr_t)S & 7) || RP % 4) return false;
+    if ((RP > 16 || K <= 768) && (long)n_out * T * K < (RP > 16 ? 12L : 8L) * 1000000) return false;
+    const int units = MODE == 0 ? 1 : RP == 16 ? (n_out + 2 * blocks - 1) / (2 * blocks) : (n_out + blocks - 1) / blocks;
+    const int chunks = K / (32 * cs), wk_log = chunks % 4 == 0 ? 2 : chunks % 2 == 0 ? 1 : 0, runs = 4 >> wk_log, nt = (T + 15) / 16;
+    int parts = 0, wgs = 0;
+    for (int per = 1; per <= SH_MS; ++per) {
+        parts = (nt + per - 1) / per;
+        wgs = (parts + runs - 1) / runs;
+        if ((long)blocks * units * wgs <= 512) break;
+    }
+    const dim3 grid((unsigned)((size_t)blocks * units * wgs + (MODE == 2 ? 1 : 0)));
+    if (cs == 6)
+        POLY_LAUNCH(POLY_STAGE_SHRINK, (shrink_stream_kernel<6, MODE>), grid, dim3(256), st, X, T, K, At, r, RP, scale, n_out, n_out_dev,
+                    in_block_of_out, adapter_of_out, out_off, S, wk_log, parts, wgs, units, pa);
+    else
+        POLY_LAUNCH(POLY_STAGE_SHRINK, (shrink_stream_kernel<4, MODE>), grid, dim3(256), st, X, T, K, At, r, RP, scale, n_out, n_out_dev,
+                    in_block_of_out, adapter_of_out, out_off, S, wk_log, parts, wgs, units, pa);
+    return true;
+}
+
 // launch_prep and launch_shrink of an isolated linear (bf16, output blocks of one input block consecutive) in one launch
 bool shrink_csr_fits(int F, int T, int K, int dtype) { return dtype == POLY_BF16 && F <= SH_CSR_MAX && K % 8 == 0 && (long)T * K <= 0x7fffffffL; }
 int launch_shrink_csr(const void *X, int T, int K, const void *At, int r, int RP, float scale, const int32_t *row_offsets, const int32_t *adapter_ids,
@@ -471,26 +697,28 @@ int launch_shrink_csr(const void *X, int T, int K, const void *At, int r, int RP
                       hipStream_t st)
 {
     const PrepArgs pa = {row_offsets, adapter_ids, F, R_cap, n_adapters, meta, frame_of_row, adapter_of_row, dev_status};
-    launch_shrink_bf16<2, 2, true>(st, (const bf16_t *)X, T, K, (const bf16_t *)At, r, RP, scale, R_cap, nullptr, nullptr, nullptr, nullptr, (bf16_t *)S, pa);
+    if (!launch_shrink_stream<2>(st, (const bf16_t *)X, T, K, (const bf16_t *)At, r, RP, scale, F, R_cap, nullptr, nullptr, nullptr, nullptr, (bf16_t *)S, pa))
+        launch_shrink_bf16<2, 2, true>(st, (const bf16_t *)X, T, K, (const bf16_t *)At, r, RP, scale, R_cap, nullptr, nullptr, nullptr, nullptr, (bf16_t *)S, pa);
     return hip_ok();
 }
 
-int launch_shrink(const void *X, int T, int K, const void *At, int r, int RP, float scale, int n_out, const int *n_out_dev,
-                  const int *in_block_of_out, const int *adapter_of_out, const int *pair_off, void *S, int dtype, hipStream_t st)
+// out_off: offsets of the output blocks of the n_in input blocks where they fan out (then in_block_of_out is their map), else nullptr
+int launch_shrink(const void *X, int T, int K, const void *At, int r, int RP, float scale, int n_in, int n_out, const int *n_out_dev,
+                  const int *in_block_of_out, const int *adapter_of_out, const int *out_off, void *S, int dtype, hipStream_t st)
 {
     if (n_out == 0) return POLY_OK;
-    if (dtype == POLY_BF16) {
-        if (K % 8 != 0 || (long)T * K > 0x7fffffffL) return POLY_EINVAL;
-        const bool two_groups = RP > 16 || (pair_off && in_block_of_out);
-        if (two_groups)
-            launch_shrink_bf16<2, 2, false>(st, (const bf16_t *)X, T, K, (const bf16_t *)At, r, RP, scale, n_out, n_out_dev, in_block_of_out,
-                                     adapter_of_out, pair_off, (bf16_t *)S, PrepArgs{});
-        else
-            launch_shrink_bf16<2, 1, false>(st, (const bf16_t *)X, T, K, (const bf16_t *)At, r, RP, scale, n_out, n_out_dev, in_block_of_out,
-                                     adapter_of_out, pair_off, (bf16_t *)S, PrepArgs{});
-    } else {
+    if (dtype != POLY_BF16)
         return launch_shrink_f32((const float *)X, T, K, (const float *)At, r, RP, scale, n_out, n_out_dev, in_block_of_out, adapter_of_out, (float *)S, st);
-    }
+    if (K % 8 != 0 || (long)T * K > 0x7fffffffL) return POLY_EINVAL;
+    const bf16_t *x = (const bf16_t *)X, *at = (const bf16_t *)At;
+    const bool fan = out_off && in_block_of_out;
+    if (fan ? launch_shrink_stream<1>(st, x, T, K, at, r, RP, scale, n_in, n_out, n_out_dev, nullptr, adapter_of_out, out_off, (bf16_t *)S, PrepArgs{})
+            : launch_shrink_stream<0>(st, x, T, K, at, r, RP, scale, n_out, n_out, n_out_dev, in_block_of_out, adapter_of_out, nullptr, (bf16_t *)S, PrepArgs{}))
+        return hip_ok();
+    if (RP > 16 || fan)
+        launch_shrink_bf16<2, 2, false>(st, x, T, K, at, r, RP, scale, n_out, n_out_dev, in_block_of_out, adapter_of_out, out_off, (bf16_t *)S, PrepArgs{});
+    else
+        launch_shrink_bf16<2, 1, false>(st, x, T, K, at, r, RP, scale, n_out, n_out_dev, in_block_of_out, adapter_of_out, out_off, (bf16_t *)S, PrepArgs{});
     return hip_ok();
 }
 
