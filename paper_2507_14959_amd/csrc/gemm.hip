@@ -4,19 +4,26 @@
 // The low-rank expand (x A_k) B_k is one more K step of the same MFMA per 16 ranks, fed with the
 // shrink output S and the adapter's Bt slab, so W + A_k B_k is never formed and the base product of
 // an input block is shared by all the row-blocks that fan out of it.
-#include "poly_dev.h"
+#include "rowtile.h"
+
+#include <utility>
 
 namespace {
 
 // ------------------------------------------------------------------ bf16 MFMA, K % 64 == 0 and N % 8 == 0
-// 128 x BN x 64 tiles, 4 waves in a 2 x 2 grid, v_mfma_f32_32x32x16_bf16.
+// BM x BN x 64 tiles, v_mfma_f32_32x32x16_bf16.
 //
 // Loads: global_load_lds_dwordx4 -- each wave instruction drops 64 x 16 bytes (8 tile rows of 64 elements)
-// straight into LDS, so NS - 1 k-tiles are in flight per workgroup without costing registers.  The lane that
+// straight into LDS, so up to NS k-tiles are in flight per workgroup without costing registers.  The lane that
 // fills position p of row r fetches chunk p ^ ((r >> 1) & 7): a swizzle that keeps 16-byte reads free of bank
 // conflicts for 8 or 16 lanes per LDS cycle, without padding.  Waits are counted by hand (vmcnt = loads of
 // the k-tiles still allowed in flight) and the barrier is a bare s_barrier, because a fenced barrier would
 // drain every outstanding load.
+//
+// Main loop: fragments are read a 16-column step ahead of their MFMAs, across the barrier too, and nothing in it makes the compiler wait for more
+// than the reads it needs (no scalar load outstanding, no branch around a load).  Reads, wait and MFMAs of a step one after the other left the
+// matrix unit idle for a read's latency in every step: 22655 x 3072 -> 768 166 us (256 x 128 tiles; now 146), 50432 x 768 -> 2304 514 k cycles at
+// 2.10 GHz (256 x 256; now 479 k).  The second gains 3 % of time for 7 % of cycles: the clock follows the power, 2.02 GHz now.
 //
 // The product is accumulated transposed (Wt fragment as the A operand) so that a lane ends up with four
 // consecutive output columns of one row; the epilogue adds the low-rank expand as one more MFMA K step per
@@ -27,14 +34,19 @@ namespace {
 // PANEL column tiles, then row tile, then column tile, are cut into eight equal runs, one per XCD: an XCD works on one
 // W panel at a time (it stays in that XCD's 4 MB L2 instead of all of W streaming past every row tile) and the XCDs
 // finish together (a ninth of a round more on one XCD is a whole round more for the kernel).
-#define POLY_GLDS16(gptr, lptr)                                                                          \
-    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)(gptr),           \
-                                     (void __attribute__((address_space(3))) *)(lptr), 16, 0, 0)
 
-template <int N> __device__ __forceinline__ void wait_vm_and_barrier()
+// 16 bytes per lane from uniform base + byte offset to lds_byte_addr + 16 lane; nothing where go <= 0, but counted as a load all the same.  Inline
+// assembly: the compiler would make LDS reads wait for loads it knows of, and a branch around them costs the reads' counted waits.
+// (All lanes of the wave are active.)
+__device__ __forceinline__ void glds16_if(const void *sbase, unsigned voff, unsigned lds_byte_addr, int go)
 {
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_cmp_gt_i32 %3, 0\n\ts_cselect_b64 exec, -1, 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1" ::"s"(
+                     lds_byte_addr),
+                 "v"(voff), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(go))
+                 : "memory", "m0", "scc");
 }
+template <typename F, int... I> __device__ __forceinline__ void static_for_each(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>()), ...); }
+template <int N, typename F> __device__ __forceinline__ void static_for(F f) { static_for_each(f, std::make_integer_sequence<int, N>()); }
 
 // (row tile, column tile) of workgroup `bid`; false if this workgroup has nothing to do.  All tiles in the order (panel of
 // `panel` column tiles, row tile, column tile inside the panel) are cut into eight equal runs, one per XCD: a run covers one
@@ -95,68 +107,46 @@ void gemm_bf16_dma_kernel(const GemmArgs g, int tiles_m, int tiles_n)
     // rows past the end of the block / of W are clamped: their products land in accumulator rows / columns that
     // are never stored
     const int lr = lane >> 3;   // row inside an 8-row group; lane & 7 = position inside the row
-    int ga[AG], gb[BG];
+    unsigned ga[AG], gb[BG];                               // bytes (the host has checked that they fit)
 #pragma unroll
     for (int i = 0; i < AG; ++i) {
         const int row = (wave * AG + i) * 8 + lr;
-        ga[i] = min(t0 + row, g.T - 1) * g.K + (((lane & 7) ^ ((row >> 1) & 7)) << 3);
+        ga[i] = 2u * (unsigned)(min(t0 + row, g.T - 1) * g.K + (((lane & 7) ^ ((row >> 1) & 7)) << 3));
     }
 #pragma unroll
     for (int i = 0; i < BG; ++i) {
         const int row = (wave * BG + i) * 8 + lr;
-        gb[i] = min(n0 + row, g.N - 1) * g.K + (((lane & 7) ^ ((row >> 1) & 7)) << 3);
+        gb[i] = 2u * (unsigned)(min(n0 + row, g.N - 1) * g.K + (((lane & 7) ^ ((row >> 1) & 7)) << 3));
     }
-    auto issue = [&](int kt, int s) {
-        bf16_t *st = dsmem + s * STAGE_EL;
-#pragma unroll
-        for (int i = 0; i < AG; ++i) POLY_GLDS16(A + ga[i] + kt * BK, st + (wave * AG + i) * 512);
-#pragma unroll
-        for (int i = 0; i < BG; ++i) POLY_GLDS16(Wt + gb[i] + kt * BK, st + A_EL + (wave * BG + i) * 512);
-    };
-
-    auto issue_one = [&](int kt, int s, int l) {            // load l (of NLD) of this wave for k-tile kt into stage s
-        bf16_t *st = dsmem + s * STAGE_EL;
-#pragma unroll
-        for (int i = 0; i < AG; ++i) if (l == i) POLY_GLDS16(A + ga[i] + kt * BK, st + (wave * AG + i) * 512);
-#pragma unroll
-        for (int i = 0; i < BG; ++i) if (l == AG + i) POLY_GLDS16(Wt + gb[i] + kt * BK, st + A_EL + (wave * BG + i) * 512);
+    const int nk = g.K / BK;
+    const unsigned ring = __builtin_amdgcn_readfirstlane(lds_addr_of(dsmem));
+    auto issue_one = [&](int kt, int s, auto load) {        // one of the NLD loads of this wave for k-tile kt into stage s; past the last
+        constexpr int l = decltype(load)::value, i = l < AG ? l : l - AG;       // k-tile it moves nothing, so that the waits count the same
+        const int go = nk - kt;                                                 // loads everywhere
+        const unsigned st = ring + s * (STAGE_EL * 2);
+        if constexpr (l < AG) glds16_if(A + (size_t)kt * BK, ga[i], st + (wave * AG + i) * 1024, go);
+        else glds16_if(Wt + (size_t)kt * BK, gb[i], st + A_EL * 2 + (wave * BG + i) * 1024, go);
     };
 
     // Row-wise epilogue (two column subtiles per wave, bf16 output): the accumulators start from the bias, so no output block
-    // has to add it later.  These loads go out before the tile loads: the in-order load counter then never makes their first
-    // use wait for a tile.
+    // has to add it later.  It comes through LDS with the tiles: the compiler would wait for all of them before it used a register load.
     constexpr bool RW = EK > 0;
     static_assert(!RW || NJ == 2, "row-wise epilogue: two column subtiles per wave");
-    constexpr bool rowwise = RW;
-    f32x4 bias_q[NJ][4];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int bcol = n0 + wn * NJ * 32 + j * 32 + 8 * q + 4 * lh;
-            const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
-            bias_q[j][q] = (rowwise && g.bias && bcol < g.N) ? *(const f32x4 *)(g.bias + bcol) : z4;
-        }
+    float *const bias_s = (float *)(dsmem + NS * STAGE_EL);
+    if constexpr (RW) {
+        if (g.bias && wave == 0 && lane < BN / 4) glds16_s(g.bias, 4u * (unsigned)min(n0 + 4 * lane, g.N - 4), ring + NS * STAGE_EL * 2);
+    }
 
     // The tile loads need nothing but the tile coordinates, so they go out first; the fan-out offsets and the adapter id are
     // read while they fly.  A tile whose block has no output drains its loads and leaves.
-    const int nk = g.K / BK;
-    const int npro = min(NS, nk);
-    for (int s = 0; s < npro; ++s) issue(s, s);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) static_for<NLD>([&](auto l) { issue_one(s, s, l); });
     int ob0 = xb, ob1 = xb + 1;
     if (g.out_off && !flat) { ob0 = g.out_off[xb]; ob1 = g.out_off[xb + 1]; }
     if (ob0 >= ob1) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         return;
     }
-
-    f32x16 acc[MI][NJ];
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = bias_q[j][e >> 2][e & 3];
 
     // operands of the low-rank expand for ranks [s0, s0 + 16) of output block ob: S rows of this wave's MI row
     // subtiles and Bt rows of its NJ column subtiles (rows past T / columns past N are clamped or zero: they only
@@ -231,62 +221,78 @@ void gemm_bf16_dma_kernel(const GemmArgs g, int tiles_m, int tiles_n)
     auto request_ids = [&](int pp, int &kav, int &kbv) {       // adapters of pass pp for blocks A and B (-1: nothing to add)
         kav = kbv = -1;
         if (!has_lora || pp >= maxfan) return;
-        if (oA0 + pp < oA1) kav = g.adapter_of_out[oA0 + pp];
-        if (hasB && oB0 + pp < oB1) kbv = g.adapter_of_out[oB0 + pp];
+        // (as vector loads: an outstanding scalar load would make the compiler wait for all LDS reads at once in the main loop)
+        int ia, ib;
+        asm("v_mov_b32 %0, %1" : "=v"(ia) : "s"(oA0 + pp));
+        asm("v_mov_b32 %0, %1" : "=v"(ib) : "s"(oB0 + pp));
+        if (oA0 + pp < oA1) kav = g.adapter_of_out[ia];
+        if (hasB && oB0 + pp < oB1) kbv = g.adapter_of_out[ib];
     };
-    const int it_ids = nk > 1 ? 1 : 0;
 
     // fragment rows are wm*MI*32 + i*32 + lm and wn*NJ*32 + j*32 + lm: (row >> 1) & 7 == (lm >> 1) & 7 for all
     const int fa0 = (wm * MI * 32 + lm) * BK, fb0 = A_EL + (wn * NJ * 32 + lm) * BK, sw = (lm >> 1) & 7;
-    for (int it = 0; it < nk; ++it) {
-        // k-tiles issued beyond `it` may stay in flight; everything up to `it` must have landed
-        const int last_issued = it == 0 ? npro - 1 : min(nk - 1, it + NS - 2);
-        const int ahead = last_issued - it;
-        if (NS >= 4 && ahead >= 3) wait_vm_and_barrier<(NS >= 4 ? 3 : 0) * NLD>();
-        else if (NS >= 3 && ahead == 2) wait_vm_and_barrier<(NS >= 3 ? 2 : 0) * NLD>();
-        else if (ahead == 1) wait_vm_and_barrier<NLD>();
-        else wait_vm_and_barrier<0>();
-        // every wave is past compute(it - 1): its stage can be refilled
-        const bool refill = it >= 1 && it + NS - 1 < nk;
-        const int rkt = it + NS - 1, rst = (it + NS - 1) % NS;
-        if constexpr (EK >= 2) {
-            if (it == it_ids) {                               // (younger than every tile load in flight: the counted waits over-wait at most)
-                fanout_arrived();
-                request_ids(0, kAv, kBv);
-                request_ids(1, kAnv, kBnv);
-            }
-        }
-        const bf16_t *cur = dsmem + (it % NS) * STAGE_EL;
+    // Fragments are read one 16-column step ahead of their MFMAs, the first ones of the next k-tile too: the wait for it and the barrier stand
+    // before the last step's MFMAs, when every wave has read all of the current k-tile, so its stage can be refilled from there on.
+    bf16x8 fa[2][MI], fb[2][NJ];
+    auto read_frags = [&](int buf, const bf16_t *tile, int kk) {
+        const int ko = ((2 * kk + lh) ^ sw) << 3;
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            const int ko = ((2 * kk + lh) ^ sw) << 3;
-            bf16x8 fa[MI], fb[NJ];
+        for (int i = 0; i < MI; ++i) fa[buf][i] = *(const bf16x8 *)(tile + fa0 + i * 32 * BK + ko);
 #pragma unroll
-            for (int i = 0; i < MI; ++i) fa[i] = *(const bf16x8 *)(cur + fa0 + i * 32 * BK + ko);
+        for (int j = 0; j < NJ; ++j) fb[buf][j] = *(const bf16x8 *)(tile + fb0 + j * 32 * BK + ko);
+    };
+    rl_wait_barrier<(NS - 1) * NLD>();
+    read_frags(0, dsmem, 0);
+    f32x16 acc[MI][NJ];
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) fb[j] = *(const bf16x8 *)(cur + fb0 + j * 32 * BK + ko);
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            f32x4 bq = {0.f, 0.f, 0.f, 0.f};
+            if (RW && g.bias) bq = *(const f32x4 *)(bias_s + wn * NJ * 32 + j * 32 + 8 * q + 4 * lh);
 #pragma unroll
             for (int i = 0; i < MI; ++i)
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    // The refill of the stage that was read in the previous step, spread over this step: PER loads per 16
-                    // k-columns, one every GAP MFMAs.  Issued as one burst the loads hold the wave at the issue stage until the
-                    // L2 path has taken them, and the MFMAs behind them start that much later.
-                    constexpr int NM = MI * NJ, PER = (NLD + 3) / 4;
-                    constexpr int GAP = NM / PER > 0 ? NM / PER : 1;
-                    const int m = i * NJ + j;
-                    if (m % GAP == 0 && m / GAP < PER) {
-                        const int l = kk * PER + m / GAP;
-                        if (l < NLD) {
-                            __builtin_amdgcn_sched_barrier(0);
-                            if (refill) issue_one(rkt, rst, l);
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
-                    }
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
-                }
+                for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] = bq[e];
         }
+    if constexpr (EK >= 2) {                                  // (younger than every tile load in flight: the counted waits over-wait at most)
+        fanout_arrived();
+        request_ids(0, kAv, kBv);
+        request_ids(1, kAnv, kBnv);
     }
+    int st = 0;                                               // stage of k-tile it
+    auto step = [&](auto first, int it) {                     // (k-tile 0 apart: a branch around loads would cost the reads' counted waits)
+        const int st_prev = st == 0 ? NS - 1 : st - 1, st_next = st == NS - 1 ? 0 : st + 1;
+        const bf16_t *cur = dsmem + st * STAGE_EL;
+        static_for<4>([&](auto kk_) {
+            constexpr int kk = decltype(kk_)::value, NM = MI * NJ, PER = (NLD + 2) / 3, part = (kk + 1) & 3;
+            if constexpr (kk < 3) read_frags((kk + 1) & 1, cur, kk + 1);
+            else {
+                rl_wait_barrier<(NS - 2) * NLD>();            // k-tile it + 1 has landed, the younger ones may stay in flight
+                read_frags(0, dsmem + st_next * STAGE_EL, 0);
+            }
+            // The refill of the stage that is free, spread over this step and the next two, between the MFMAs.  Issued as one
+            // burst the loads hold the wave at the issue stage until the L2 path has taken them, and the MFMAs behind them
+            // start that much later.
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<NM>([&](auto m_) {
+                constexpr int m = decltype(m_)::value, from = part * PER + m * PER / NM, to = part * PER + (m + 1) * PER / NM;
+                static_for<NLD>([&](auto l) {
+                    if constexpr (part < 3 && l() >= from && l() < to) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        if constexpr (kk == 3) issue_one(it + NS, st, l);
+                        else if constexpr (!decltype(first)::value) issue_one(it - 1 + NS, st_prev, l);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                });
+                acc[m / NJ][m % NJ] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kk & 1][m % NJ], fa[kk & 1][m / NJ], acc[m / NJ][m % NJ], 0, 0, 0);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        st = st_next;
+    };
+    step(std::true_type(), 0);
+    for (int it = 1; it < nk; ++it) step(std::false_type(), it);
     __syncthreads();   // all loads have landed (vmcnt(0) above) and all waves are done with the tiles
 
     // ---- row-wise epilogue (bf16 output, two column subtiles per wave).  Per pass p the wave produces, for every row of its
@@ -686,7 +692,7 @@ static unsigned dma_grid(int tiles_mtot, int tiles_n)
 template <int BM, int BN, int WM, int WN, int NS, int EK>
 static void launch_dma_ek(const GemmArgs &g, hipStream_t st)
 {
-    constexpr int LDS = NS * (BM + BN) * 64 * 2;
+    constexpr int LDS = NS * (BM + BN) * 64 * 2 + (EK > 0 ? BN * 4 : 0);
     auto kern = gemm_bf16_dma_kernel<BM, BN, WM, WN, NS, EK>;
     if (LDS > 64 * 1024) {
         static bool attr_set = false;   // raising the dynamic LDS limit is a per-kernel, process-wide setting
@@ -723,12 +729,11 @@ static long product_tiles(const GemmArgs &g, int bm, int bn) { return (long)g.n_
 
 // What a product takes on a tile, in us: rounds of as many workgroups as fit the chip, and a last round that is cheaper where it leaves CUs with
 // fewer workgroups than they hold.  Per round f + k K, plus `fan` where rows fan out, plus `res` with a residual.  Fitted to 89 products
-// (788 to 50432 rows; K -> N 192 -> 576, 768; 384 -> 384, 1152, 1536; 768 -> 768, 2304, 3072; 3072 -> 768; rank 16) within 5 to 10 %: the tile it
-// picks is on average 0.9 % slower than the fastest of the four, at worst 16 % (17730 x 192 -> 768); fixed thresholds for tiles of 256 x 256 and
-// 256 x 128, and 128 x 128 on four waves of 64 x 64 else, were 12 % slower on average.
-// us, 256 x 256 / 256 x 128 / 128 x 128 / 128 x 64 (rows x K -> N): 1773 x 192 -> 576, two branches 16.0 / 11.2 / 7.8 / 7.2;
-// 5910 x 768 -> 3072 58 / 57 / 47 / 48; 12608 x 768 -> 768 45 / 45 / 47 / 34; 12608 x 768 -> 2304 55 / 71 / 62 / 69;
-// 26201 x 3072 -> 768 223 / 185 / 255 / 216; 50432 x 768 -> 2304, two branches 238 / 278 / 267 / 308.
+// (788 to 50432 rows; K -> N 192 -> 576, 768; 384 -> 384, 1152, 1536; 768 -> 768, 2304, 3072; 3072 -> 768; rank 16) within 7 to 11 %: the tile it
+// picks is on average 1.1 % slower than the fastest of the four, at worst 17 % (17730 x 192 -> 768).
+// us, 256 x 256 / 256 x 128 / 128 x 128 / 128 x 64 (rows x K -> N): 1773 x 192 -> 576, two branches 15.4 / 10.3 / 7.7 / 7.1;
+// 5910 x 768 -> 3072 55 / 52 / 47 / 47; 12608 x 768 -> 768 43 / 39 / 43 / 33; 12608 x 768 -> 2304 54 / 67 / 59 / 70;
+// 26201 x 3072 -> 768 221 / 173 / 243 / 210; 50432 x 768 -> 2304, two branches 230 / 290 / 261 / 301.
 struct TileCost {
     int bm, bn, per_cu;                                    // workgroups per CU
     float start, f, k, fan, res, last1, last2;             // last1, last2: share of a round with one / two workgroups per CU in it
@@ -751,10 +756,10 @@ static float tile_cost(const TileCost &c, const GemmArgs &g)
 
 static int launch_gemm_dma(const GemmArgs &g, hipStream_t st)
 {
-    static const TileCost cost[4] = {{128, 64, 3, 2.1f, 3.7f, 0.0140f, 2.5f, 3.5f, 0.62f, 0.80f},
-                                     {128, 128, 2, 3.3f, 2.7f, 0.0196f, 3.1f, 8.6f, 0.51f, 0.f},
-                                     {256, 128, 1, -1.5f, 8.1f, 0.0137f, 2.4f, 4.0f, 0.f, 0.f},
-                                     {256, 256, 1, -3.4f, 11.4f, 0.0235f, 4.9f, 13.3f, 0.f, 0.f}};
+    static const TileCost cost[4] = {{128, 64, 3, 1.9f, 3.6f, 0.0138f, 2.6f, 3.5f, 0.60f, 0.78f},
+                                     {128, 128, 2, 3.2f, 2.7f, 0.0187f, 3.3f, 8.2f, 0.48f, 0.f},
+                                     {256, 128, 1, -3.4f, 9.8f, 0.0102f, 2.8f, 3.9f, 0.f, 0.f},
+                                     {256, 256, 1, -4.6f, 12.4f, 0.0212f, 5.2f, 13.7f, 0.f, 0.f}};
     if (g.pos) {                                           // patch embedding: row tiles inside blocks, an epilogue that fetches nothing ahead
         if (g.N % 128 == 0) launch_dma<128, 128, 2, 2, 2>(g, st);
         else if (product_tiles(g, 128, 64) < 256) launch_dma<64, 64, 2, 2, 4>(g, st);    // (147 tiles of 128 x 64: 14.3 us, as 64 x 64 9 us)
@@ -790,10 +795,10 @@ int launch_gemm(const GemmArgs &g, int dtype, hipStream_t st)
     // A long contraction on fewer 128 x 128 tiles than half the CUs takes smaller tiles: with the contraction split over the waves (gemm_ks.hip)
     // where tiles of 32 x 64 get a CU each, and above a contraction of 1024 also where tiles of 64 x 64 do; else tiles of 64 x 64 that share a
     // ring, two workgroups per CU.  us per product of the 768-wide backbone, split / shared ring / 128 x 128 (rows x K -> N):
-    //   197 x 768 -> 2304  7.0 / 7.1 / 12.9    591 x 768 -> 768   8.3 / 8.6 / 15.6    591 x 3072 -> 768   13.4 / 19.2 / 41.7
-    //   197 x 768 -> 3072  8.6 / 7.6 / 14.6    985 x 768 -> 768   9.4 / 8.8 / 15.8    1182 x 3072 -> 768  16.8 / 19.5 / 42.2
-    //   591 x 768 -> 2304 15.1 / 9.5 / 13.1    1576 x 768 -> 768 15.9 / 10.3 / 16.0   1576 x 3072 -> 768  29.2 / 23.6 / 42.0
-    //   591 x 768 -> 3072 16.6 / 10.3 / 14.8   985 x 768 -> 2304 21.4 / 14.2 / 13.8 (144 tiles of 128 x 128)
+    //   197 x 768 -> 2304  7.6 / 7.0 / 11.9    591 x 768 -> 768   9.3 / 9.1 / 14.6    591 x 3072 -> 768   14.6 / 18.0 / 38.8
+    //   197 x 768 -> 3072  9.0 / 7.4 / 13.4    985 x 768 -> 768  10.7 / 9.2 / 14.9    1182 x 3072 -> 768  19.0 / 19.2 / 39.1
+    //   591 x 768 -> 2304 16.9 / 9.8 / 12.3    1576 x 768 -> 768 17.8 / 11.0 / 15.0   1576 x 3072 -> 768  32.4 / 25.3 / 39.0
+    //   591 x 768 -> 3072 18.0 / 10.9 / 13.7   985 x 768 -> 2304 23.8 / 14.7 / 12.6 (144 tiles of 128 x 128)
     if (g.K >= 512 && product_tiles(gf, 128, 128) < 128) {
         if (product_tiles(gf, 32, 64) <= 256 || (g.K > 1024 && product_tiles(gf, 64, 64) <= 256)) return launch_gemm_ks(gf, dtype, st);
         launch_dma<64, 64, 2, 2, 4>(gf, st);

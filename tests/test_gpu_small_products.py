@@ -48,3 +48,20 @@ def test_against_the_oracle(n_xblocks, T, K, N, r, per_block):
 ])
 def test_tiles_of_a_wave_per_32_rows(n_xblocks, T, K, N, r, per_block):
     test_against_the_oracle(n_xblocks, T, K, N, r, per_block)
+
+
+@pytest.mark.parametrize("n_xblocks,T,K,N,r,per_block", [
+    (30, 131, 64, 1032, 16, 2),      # one 64-column step: every load of the further stages is switched off
+    (64, 197, 128, 768, 8, 1),       # as many steps as stages
+    (100, 197, 192, 256, 20, 2),     # one more
+])
+def test_short_contractions(n_xblocks, T, K, N, r, per_block):
+    test_against_the_oracle(n_xblocks, T, K, N, r, per_block)
+
+
+@pytest.mark.parametrize("n_xblocks,T,K,N,r,per_block", [
+    (128, 197, 768, 2304, 16, 1),    # tiles of 256 x 256
+    (133, 197, 1536, 768, 16, 1),    # tiles of 256 x 128, three stages
+])
+def test_large_tiles(n_xblocks, T, K, N, r, per_block):
+    test_against_the_oracle(n_xblocks, T, K, N, r, per_block)
