@@ -12,21 +12,20 @@
 //  - Reuse branches.  S_t = S_{t-1} where the labels repeat or (context copy) where S_{t-1} provides them all, so every S_t is
 //    the greedy set of the last frame that was NOT reused.  If frame t took its own set, the next frame to do so is
 //    next[t] = the first t' > t whose labels are new and not all provided by the greedy set of t -- a function of t alone, found
-//    for all t side by side: every thread walks forward from its frame to the next break.  The frames that really took their own set
-//    are the ones on the chain that starts at the first frame of the pass that the carried set does not serve; they are marked by
-//    pointer doubling (log2 n rounds), and a scan gives every frame the last marked one before it.
-//
-// The walk is as long as a scene whose labels do not change.  1024 frames with context copy whose labels change every 16 frames 18 us,
-// every 64 23 us, every 256 43 us, never 102 us.
+//    for all t side by side: every thread whose labels are new walks over the later frames with new labels to the next break.  The frames
+//    that really took their own set are the ones on the chain that starts at the first frame of the pass that the carried set does not serve;
+//    they are marked by pointer quadrupling (log4 n rounds), and a scan gives every frame the last marked one before it.
 //
 // 1024 frames x 80 labels, 45 overlapping contexts with an accuracy table and context copy: 1665 us per call with M tests per frame
-// and a sequential pass over the frames, 18.9 us this way (20 k cycles of it kernel phases: scores 5, links 1, chain 3.5, the rest
-// memory round trips of the set-up).  64 frames, 16 contexts: 17.9 -> 8.9 us, the rate at which the host can launch.
+// and a sequential pass over the frames, 17.7 us this way; labels that change every 4, 64, 256 frames or never: 17.2, 16.6, 17.0, 15.7 us (the last
+// 102 us while the walk went over all frames).  328 KB of scores through one CU are 12 k of the 38 k cycles, whatever the form of their loop
+// (ballots instead of atomics, more loads in flight: the same).
+// 64 frames, 16 contexts, in a queue of calls: 17.9 -> 8.8 us; 6.9 us (17.9 -> 13.3 k cycles) with everything the call reads in one round trip,
+// barriers that do not wait for it, eight waves, and no search for the set in use by waves without frames.
 #include "poly_dev.h"
 
 namespace {
 
-constexpr int SEL_THREADS = 1024, SEL_WAVES = SEL_THREADS / 64;
 constexpr int MMAX = POLY_MAX_CONTEXTS;
 constexpr int FEW_LABELS = 24;       // active labels up to which looking up first[] beats testing every context
 
@@ -36,34 +35,46 @@ struct SelState {       // device image of (Y_{t-1}, S_{t-1})
     uint64_t labels[1]; // KW words
 };
 
+// all waves' LDS accesses so far, without waiting for loads that are still on their way to registers
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+__device__ const uint64_t no_state[2 + POLY_MAX_LABELS / 64] = {};   // read in place of what a caller has not given
+
 // NW: words per label set (64 labels each).  One thread per frame of a pass; wide label sets get fewer frames per pass so that
 // the two bitset arrays stay at 16 KB each.  VEC: scores per load (4 when K and the address allow 16-byte loads).
 // Every phase runs once per call, so its instructions come from memory once: short code is worth more here than unrolled loops.
-template <int NW, int VEC>
+template <int NW, int VEC, int SEL_THREADS>
 __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float *scores, int F, int K, const uint8_t *member, int M, float theta,
                                                              int context_copy, const float *acc, float tau, SelState *state,
                                                              int32_t *row_offsets, int32_t *adapter_ids, int cap, int32_t *counters,
                                                              const SelectFollow fo)
 {
-    constexpr int CH = NW <= 2 ? 1024 : NW <= 4 ? 512 : 128;   // frames per pass
+    constexpr int SEL_WAVES = SEL_THREADS / 64;
+    constexpr int CH = NW <= 2 ? SEL_THREADS : NW <= 4 ? 512 : 128;   // frames per pass
+    static_assert(SEL_THREADS >= 64 * NW && SEL_THREADS >= CH, "one thread per label and per frame");
     constexpr int LB = 4;                                      // score loads a thread has in flight
     __shared__ uint64_t cmask[MMAX][NW];       // labels that the context at a scan position provides
     __shared__ uint64_t prov_id[MMAX][NW];     // provided labels by context id
-    __shared__ uint64_t Y[CH][NW];             // Y_t; labels of frames that repeat the previous ones are cleared before `next` is built
+    __shared__ uint64_t Y[CH][NW];             // Y_t
     __shared__ uint64_t P[CH][NW];             // labels that the greedy set of frame t provides
     __shared__ uint64_t S[CH];                 // greedy set of frame t as a mask over scan positions
-    __shared__ uint64_t prevY[NW], prevP[NW], prevS, wmask[SEL_WAVES];
+    __shared__ uint64_t prevY[NW], prevP[NW], prevS;      // of the frame before the pass
+    __shared__ uint64_t wmask[SEL_WAVES], fresh[SEL_WAVES];
     __shared__ int order[MMAX];                // scan position -> context id
     __shared__ int size_of[MMAX], first[64 * NW];
-    __shared__ int wtot[SEL_WAVES], wunc[SEL_WAVES], prevValid, total_s, unc_s;
-    __shared__ uint16_t nxt[CH + 1];
+    __shared__ __attribute__((aligned(16))) int wtot[SEL_WAVES];
+    __shared__ int unc_s;
+    __shared__ uint16_t nxt[2][CH + 1];
     __shared__ uint8_t reach[CH + 1];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int KW = NW <= 2 ? NW : (K + 63) / 64;
     const bool sequential = state != nullptr || context_copy != 0;
 
-    // Scores: thread i takes the VEC scores at i, i + 1024, .. of a pass, LB loads in flight (addresses clamped, not predicated).
+    // (all arguments in one round trip instead of one each where they are first used)
+    asm volatile("" ::"s"(scores), "s"(F), "s"(K), "s"(member), "s"(M), "s"(acc), "s"(state), "s"(fo.meta));
+
+    // Scores: thread i takes the VEC scores at i, i + SEL_THREADS, .. of a pass, LB loads in flight (addresses clamped, not predicated).
     // Few labels are active, so each piece that has one sets its bits in the frame's words with an LDS atomic.
     typedef float vec_t __attribute__((ext_vector_type(VEC)));
     const int KV = K / VEC, step_t = SEL_THREADS / KV, step_q = SEL_THREADS - step_t * KV;
@@ -72,34 +83,50 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float *scores
 #pragma unroll
         for (int u = 0; u < LB; ++u) sv[u] = *(const vec_t *)(scores + (size_t)f0 * K + (size_t)min(i0 + u * SEL_THREADS, tot - 1) * VEC);
     };
-    if (F > 0) load_scores(0, min(CH, F) * KV, tid);           // on their way while the contexts are set up
-
-    // membership and provided-label bitsets, one ballot per (context id, 64-label word); a context's size is the sum of its words'
-    for (int i = tid; i < CH * NW; i += SEL_THREADS) (&Y[0][0])[i] = 0;
-    if (tid < 64 * NW) first[tid] = 64;
-    if (tid < MMAX) size_of[tid] = 0;
-    if (tid == 0) { total_s = 0; unc_s = 0; prevValid = state ? state->valid : 0; prevS = 0; row_offsets[0] = 0; }
-    if (tid < NW) { prevY[tid] = (state && state->valid && tid < KW) ? state->labels[tid] : 0ull; prevP[tid] = 0; }
-    __syncthreads();
-    for (int w0 = wave; w0 < M * KW; w0 += 4 * SEL_WAVES) {
-        uint8_t mb[4];
-        float ac[4];
+    // Everything the call reads is requested here, in one round trip, and no barrier before its use waits for it
+    constexpr int MB = 4096 / SEL_THREADS;                     // membership words of a wave in flight
+    uint8_t mb[MB];
+    float ac[MB];
+    auto load_members = [&](int w0) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < MB; ++u) {
             const int w = min(w0 + u * SEL_WAVES, M * KW - 1), c = w / KW;
             const size_t at = (size_t)c * K + min((w - c * KW) * 64 + lane, K - 1);
             mb[u] = member[at];
             ac[u] = acc ? acc[at] : 0.f;
         }
+    };
+    const SelState *from = state ? state : (const SelState *)no_state;
+    const int carried = from->valid, stalled = *(fo.meta ? &fo.meta->stalled : (const int *)no_state);
+    const uint64_t carried_ids = from->set_ids;
+    uint64_t carried_y[NW];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+    for (int j = 0; j < NW; ++j) carried_y[j] = from->labels[min(j, (K - 1) >> 6)];
+    __builtin_amdgcn_sched_barrier(0);
+    load_members(wave);
+    if (F > 0) load_scores(0, min(CH, F) * KV, tid);
+
+    for (int i = tid; i < min(CH, F) * NW; i += SEL_THREADS) (&Y[0][0])[i] = 0;
+    if (tid < 64 * NW) first[tid] = 64;
+    if (tid < MMAX) size_of[tid] = 0;
+    if (tid == 0) { unc_s = 0; prevS = 0; row_offsets[0] = 0; }
+    lds_barrier();
+    // membership and provided-label bitsets, one ballot per (context id, 64-label word); a context's size is the sum of its words'
+    for (int w0 = wave; w0 < M * KW; w0 += MB * SEL_WAVES) {
+        if (w0 != wave) load_members(w0);
+#pragma unroll
+        for (int u = 0; u < MB; ++u) {
             const int w = w0 + u * SEL_WAVES, c = w / KW, j = w - c * KW;
             const bool mem = j * 64 + lane < K && mb[u] != 0;
             const uint64_t mm = __ballot(mem), pm = __ballot(mem && (acc == nullptr || ac[u] >= tau));
             if (lane == 0 && w < M * KW) { prov_id[c][j] = pm; atomicAdd(&size_of[c], __popcll(mm)); }
         }
     }
-    __syncthreads();
+    if (tid == 0) {
+#pragma unroll
+        for (int j = 0; j < NW; ++j) { prevY[j] = carried && j < KW ? carried_y[j] : 0ull; prevP[j] = 0; }
+    }
+    lds_barrier();
     // contexts in scan order: size ascending, id ascending.  The rank of context c is the number of contexts before it: one ballot
     for (int c = wave; c < M; c += SEL_WAVES) {
         const int sz_l = lane < M ? size_of[lane] : 0x7fffffff, sz_c = size_of[c];
@@ -113,14 +140,16 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float *scores
         }
     }
 
+    int running = 0;                                           // adapters of the passes before
     for (int f0 = 0; f0 < F; f0 += CH) {
         const int n = min(CH, F - f0), tot = n * KV;
+        const bool prevValid = f0 || carried;
         if (f0) {
-            for (int i = tid; i < CH * NW; i += SEL_THREADS) (&Y[0][0])[i] = 0;
             load_scores(f0, tot, tid);
-            __syncthreads();
+            for (int i = tid; i < n * NW; i += SEL_THREADS) (&Y[0][0])[i] = 0;
+            lds_barrier();
         }
-        for (int i0 = tid, t = tid / KV, q = tid - t * KV; i0 < tot;) {
+        for (int i0 = tid, t = tid / KV, q = tid - t * KV;;) {
 #pragma unroll
             for (int u = 0; u < LB; ++u) {
                 unsigned bits = 0;
@@ -131,12 +160,12 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float *scores
                 i0 += SEL_THREADS; t += step_t; q += step_q;
                 if (q >= KV) { q -= KV; ++t; }
             }
+            if (i0 - tid >= tot) break;
             load_scores(f0, tot, i0);
         }
-        __syncthreads();
-        if (f0 == 0 && wave == SEL_WAVES - 1 && state && prevValid) {   // the carried set: context ids -> scan positions, and what it provides
-            const uint64_t ids = state->set_ids;
-            uint64_t s = __ballot(lane < M && ((ids >> order[lane < M ? lane : 0]) & 1ull));
+        lds_barrier();
+        if (f0 == 0 && wave == SEL_WAVES - 1 && carried) {     // the carried set: context ids -> scan positions, and what it provides
+            uint64_t s = __ballot(lane < M && ((carried_ids >> order[lane < M ? lane : 0]) & 1ull));
             if (lane == 0) prevS = s;
             uint64_t pv = 0;
             for (; s; s &= s - 1) pv |= cmask[__ffsll((unsigned long long)s) - 1][lane < KW ? lane : 0];
@@ -163,9 +192,18 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float *scores
                 cand = 0;
 #pragma unroll
                 for (int j = 0; j < NW; ++j)
-                    for (uint64_t b = u[j]; b; b &= b - 1) {
-                        const int f = first[j * 64 + __ffsll((unsigned long long)b) - 1];
-                        if (f < 64) cand |= 1ull << f;         // 64: provided by nobody
+                    for (uint64_t b = u[j]; b;) {              // (with one or two waves per SIMD four labels per round trip to LDS)
+                        constexpr int ZL = SEL_THREADS > 512 ? 1 : 4;
+                        int f[ZL];
+#pragma unroll
+                        for (int z = 0; z < ZL; ++z) {
+                            f[z] = first[j * 64 + (ZL == 1 || b ? __ffsll((unsigned long long)b) - 1 : 0)];
+                            if (ZL > 1 && !b) f[z] = 64;
+                            b &= b - 1;
+                        }
+#pragma unroll
+                        for (int z = 0; z < ZL; ++z)
+                            if (f[z] < 64) cand |= 1ull << f[z];       // 64: provided by nobody
                     }
             }
             for (; cand; cand &= cand - 1) {
@@ -191,11 +229,6 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float *scores
                 own = !same;
             } else {
                 __syncthreads();
-                if (tid < n && same) {
-#pragma unroll
-                    for (int j = 0; j < NW; ++j)
-                        if (j < KW) Y[tid][j] = 0;
-                }
                 // first frame of the pass that the carried set does not serve
                 bool brk = false;
                 if (tid < n && !same) {
@@ -204,37 +237,48 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float *scores
                     for (int j = 0; j < NW; ++j)
                         if (j < KW) brk |= (y[j] & ~prevP[j]) != 0;
                 }
-                const uint64_t bm = __ballot(brk);
-                if (lane == 0) wmask[wave] = bm;
+                const uint64_t bm = __ballot(brk), cm = __ballot(tid < n && !same);
+                if (lane == 0) { wmask[wave] = bm; fresh[wave] = cm; }
                 if (tid < n) reach[tid] = 0;
-                if (tid == 0) { reach[n] = 0; nxt[n] = (uint16_t)n; }
+                if (tid == 0) { reach[n] = 0; nxt[0][n] = nxt[1][n] = (uint16_t)n; }
                 __syncthreads();
+                // only frames with new labels end a run or take a set of their own
                 if (tid < n) {
-                    uint64_t np[NW];
+                    int t = n;
+                    if (!same) {
+                        uint64_t np[NW];
 #pragma unroll
-                    for (int j = 0; j < NW; ++j) np[j] = j < KW ? ~P[tid][j] : 0ull;
-                    int t = tid + 1;
-                    for (bool hit = false; t < n; ++t) {
+                        for (int j = 0; j < NW; ++j) np[j] = j < KW ? ~P[tid][j] : 0ull;
+                        int w = wave;
+                        for (uint64_t m = cm & (lane == 63 ? 0ull : ~0ull << (lane + 1));;) {
+                            if (m == 0) {
+                                if (++w >= SEL_WAVES) break;
+                                m = fresh[w];
+                                continue;
+                            }
+                            const int at = w * 64 + __ffsll((unsigned long long)m) - 1;
+                            m &= m - 1;
+                            bool hit = false;
 #pragma unroll
-                        for (int j = 0; j < NW; ++j)
-                            if (j < KW) hit |= (Y[t][j] & np[j]) != 0;
-                        if (hit) break;
+                            for (int j = 0; j < NW; ++j)
+                                if (j < KW) hit |= (Y[at][j] & np[j]) != 0;
+                            if (hit) { t = at; break; }
+                        }
                     }
-                    nxt[tid] = (uint16_t)t;
+                    nxt[0][tid] = (uint16_t)t;
                 }
                 if (tid == 0) {
                     for (int w = 0; w < SEL_WAVES; ++w)
                         if (wmask[w]) { reach[w * 64 + __ffsll((unsigned long long)wmask[w]) - 1] = 1; break; }
                 }
-                for (int span = 1; span <= n; span <<= 1) {    // the chain up to `span` links past the start is marked
-                    __syncthreads();
-                    int a = n, b = n;
-                    bool r = false;
-                    if (tid < n) { a = nxt[tid]; b = nxt[a]; r = reach[tid] != 0; }
+                // after a round the chain is marked four times as far.  (A mark that a thread sees a round early is on the chain too.)
+                int from = 0;
+                for (int span = 1; span < n; span <<= 2, from ^= 1) {
                     __syncthreads();
                     if (tid < n) {
-                        nxt[tid] = (uint16_t)b;
-                        if (r) reach[a] = 1;
+                        const int a = nxt[from][tid], b2 = nxt[from][a], c3 = nxt[from][b2];
+                        nxt[from ^ 1][tid] = nxt[from][c3];
+                        if (reach[tid]) reach[a] = reach[b2] = reach[c3] = 1;
                     }
                 }
                 __syncthreads();
@@ -249,7 +293,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float *scores
         {
             const uint64_t upto = om & (~0ull >> (63 - lane));
             if (upto) last = wave * 64 + 63 - __clzll((long long)upto);
-            else
+            else if (wave * 64 < n)
                 for (int w = wave - 1; w >= 0; --w)
                     if (wmask[w]) { last = w * 64 + 63 - __clzll((long long)wmask[w]); break; }
         }
@@ -262,7 +306,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float *scores
                 if (j < KW) uu += __popcll(y[j] & ~(last >= 0 ? P[last][j] : prevP[j]));
         }
         // exclusive scan of the set sizes: a count has at most seven bits, so seven ballots give a wave's prefix sums
-        int before = 0, wsum = 0, usum = 0;
+        int before = 0, wsum = 0;
         const uint64_t below = (1ull << lane) - 1;
 #pragma unroll
         for (int b = 0; b < 7; ++b) {
@@ -270,16 +314,20 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float *scores
             before += __popcll(m & below) << b;
             wsum += __popcll(m) << b;
         }
-        if (__ballot(uu != 0)) {                               // rare: some label is provided by nobody
-            usum = uu;
-            for (int o = 32; o > 0; o >>= 1) usum += __shfl_xor(usum, o, 64);
+        if (__ballot(uu != 0)) {                               // some label is provided by nobody
+            for (int o = 32; o > 0; o >>= 1) uu += __shfl_xor(uu, o, 64);
+            if (lane == 0) atomicAdd(&unc_s, uu);
         }
-        if (lane == 0) { wtot[wave] = wsum; wunc[wave] = usum; }
+        if (lane == 0) wtot[wave] = wsum;
         __syncthreads();
-        int base = total_s;
-        for (int w = 0; w < wave; ++w) base += wtot[w];
+        int o = running + before;
+#pragma unroll
+        for (int w = 0; w < SEL_WAVES; ++w) {
+            const int x = wtot[w];
+            running += x;
+            o += w < wave ? x : 0;
+        }
         if (tid < n) {
-            int o = base + before;
             row_offsets[f0 + tid + 1] = o + c;
             for (uint64_t s = sel; s; s &= s - 1, ++o) {
                 const int id = order[__ffsll((unsigned long long)s) - 1];
@@ -289,39 +337,36 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float *scores
                 }
             }
         }
-        __syncthreads();                                       // everybody has read the carried values and this pass's arrays
-        if (tid == n - 1) {
-            prevS = sel; prevValid = 1;
+        if (f0 + CH < F) {
+            __syncthreads();                                   // everybody has read the carried values and this pass's arrays
+            if (tid == n - 1) {
+                prevS = sel;
+#pragma unroll
+                for (int j = 0; j < NW; ++j)
+                    if (j < KW) { prevY[j] = y[j]; if (last >= 0) prevP[j] = P[last][j]; }
+            }
+        } else if (tid == n - 1 && state && !stalled) {        // the last frame's labels and set, for the next call
+            uint64_t ids = 0;
+            for (uint64_t s = sel; s; s &= s - 1) ids |= 1ull << order[__ffsll((unsigned long long)s) - 1];
+            state->valid = 1;
+            state->set_ids = ids;
 #pragma unroll
             for (int j = 0; j < NW; ++j)
-                if (j < KW) { prevY[j] = y[j]; if (last >= 0) prevP[j] = P[last][j]; }
-        }
-        if (wave == 0) {
-            int a = lane < SEL_WAVES ? wtot[lane] : 0, b = lane < SEL_WAVES ? wunc[lane] : 0;
-#pragma unroll
-            for (int o = SEL_WAVES / 2; o > 0; o >>= 1) { a += __shfl_xor(a, o, 64); b += __shfl_xor(b, o, 64); }
-            if (lane == 0) { total_s += a; unc_s += b; }
+                if (j < KW) state->labels[j] = y[j];
         }
     }
-    __syncthreads();
     if (tid == 0) {
-        counters[0] = total_s;
-        counters[1] = unc_s;
+        counters[0] = running;
+        counters[1] = F > 0 ? unc_s : 0;
         if (fo.meta) {                                         // ids and offsets are valid by construction; only the capacity can be exceeded
-            const bool stalled = fo.meta->stalled != 0, bad = total_s > cap || stalled;
-            fo.meta->R = bad ? 0 : total_s;
+            const bool bad = running > cap || stalled;
+            fo.meta->R = bad ? 0 : running;
             fo.meta->F_ok = bad ? 0 : F;
             fo.meta->status = stalled ? POLY_ESTALL : bad ? POLY_ERANGE : POLY_OK;
             if (fo.dev_status) *fo.dev_status = fo.meta->status;
         }
     }
-    if (fo.meta && fo.meta->stalled) return;
-    if (wave == 0 && state && F > 0) {
-        uint64_t ids = 0;
-        for (uint64_t s = prevS; s; s &= s - 1) ids |= 1ull << order[__ffsll((unsigned long long)s) - 1];
-        if (lane == 0) { state->valid = 1; state->set_ids = ids; }
-        if (lane < KW) state->labels[lane] = prevY[lane];
-    }
+    if (stalled) return;
     if (fo.carry)
         for (int i = tid; i < K; i += SEL_THREADS) fo.carry[i] = fo.carry_src[i];
 }
@@ -341,15 +386,21 @@ int launch_select(const float *label_scores, int F, int K, const uint8_t *group_
     if (F < 0 || K <= 0 || K > POLY_MAX_LABELS || M <= 0 || M > POLY_MAX_CONTEXTS || cap < 0) return POLY_EINVAL;
     if ((F > 0 && !label_scores) || (cap > 0 && !adapter_ids)) return POLY_EINVAL;
     const bool wide = K % 4 == 0 && ((uintptr_t)label_scores & 15) == 0;
-#define SELECT_LAUNCH(NW, VEC)                                                                                                           \
-    POLY_LAUNCH(POLY_STAGE_SELECT, (select_kernel<NW, VEC>), dim3(1), dim3(SEL_THREADS), st, label_scores, F, K, group_membership, M,       \
+#define SELECT_LAUNCH(NW, VEC, NT)                                                                                                       \
+    POLY_LAUNCH(POLY_STAGE_SELECT, (select_kernel<NW, VEC, NT>), dim3(1), dim3(NT), st, label_scores, F, K, group_membership, M,            \
                 opts->theta, opts->context_copy, opts->acc, opts->tau, (SelState *)state, row_offsets, adapter_ids, cap, counters, fo)
 #define SELECT_CASE(NW)                    \
     do {                                   \
-        if (wide) SELECT_LAUNCH(NW, 4);    \
-        else SELECT_LAUNCH(NW, 1);         \
+        if (wide) SELECT_LAUNCH(NW, 4, 1024); \
+        else SELECT_LAUNCH(NW, 1, 1024);   \
     } while (0)
-    if (K <= 64) SELECT_CASE(1);
+    // Few frames: eight waves.  Most phases are a chain of LDS round trips that every wave goes through, four waves on a SIMD one behind the other.
+    // us per call in a queue of them, 16 contexts, 80 labels, eight waves / sixteen: 16 frames 7.1 / 7.8, 64 6.9 / 7.5, 128 7.7 / 7.8, 256 8.4 / 8.7
+    if (wide && F <= 256 && K <= 128) {
+        if (K <= 64) SELECT_LAUNCH(1, 4, 512);
+        else SELECT_LAUNCH(2, 4, 512);
+    }
+    else if (K <= 64) SELECT_CASE(1);
     else if (K <= 128) SELECT_CASE(2);
     else if (K <= 256) SELECT_CASE(4);
     else SELECT_CASE(16);
