@@ -17,8 +17,8 @@
 //    they are marked by pointer quadrupling (log4 n rounds), and a scan gives every frame the last marked one before it.
 //
 // 1024 frames x 80 labels, 45 overlapping contexts with an accuracy table and context copy: 1665 us per call with M tests per frame
-// and a sequential pass over the frames, 17.7 us this way; labels that change every 4, 64, 256 frames or never: 17.2, 16.6, 17.0, 15.7 us (the last
-// 102 us while the walk went over all frames).  328 KB of scores through one CU are 12 k of the 38 k cycles, whatever the form of their loop
+// and a sequential pass over the frames, 17.0 us this way (kernel 16.4); labels that never change: 102 us while the walk went over all
+// frames, 15.7 without.  328 KB of scores through one CU are 12 k of the 38 k cycles, whatever the form of their loop
 // (ballots instead of atomics, more loads in flight: the same).
 // 64 frames, 16 contexts, in a queue of calls: 17.9 -> 8.8 us; 6.9 us (17.9 -> 13.3 k cycles) with everything the call reads in one round trip,
 // barriers that do not wait for it, eight waves, and no search for the set in use by waves without frames.
@@ -88,13 +88,16 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float *scores
     uint8_t mb[MB];
     float ac[MB];
     auto load_members = [&](int w0) {
+        unsigned at[MB];
 #pragma unroll
         for (int u = 0; u < MB; ++u) {
-            const int w = min(w0 + u * SEL_WAVES, M * KW - 1), c = w / KW;
-            const size_t at = (size_t)c * K + min((w - c * KW) * 64 + lane, K - 1);
-            mb[u] = member[at];
-            ac[u] = acc ? acc[at] : 0.f;
+            const unsigned w = min(w0 + u * SEL_WAVES, M * KW - 1), c = w / (unsigned)KW;
+            at[u] = c * (unsigned)K + min((w - c * (unsigned)KW) * 64u + lane, (unsigned)K - 1u);
+            mb[u] = member[at[u]];
         }
+        if (acc)
+#pragma unroll
+            for (int u = 0; u < MB; ++u) ac[u] = acc[at[u]];
     };
     const SelState *from = state ? state : (const SelState *)no_state;
     const int carried = from->valid, stalled = *(fo.meta ? &fo.meta->stalled : (const int *)no_state);
@@ -320,13 +323,13 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float *scores
         }
         if (lane == 0) wtot[wave] = wsum;
         __syncthreads();
-        int o = running + before;
-#pragma unroll
-        for (int w = 0; w < SEL_WAVES; ++w) {
-            const int x = wtot[w];
-            running += x;
-            o += w < wave ? x : 0;
-        }
+        int upto_w = wtot[lane & (SEL_WAVES - 1)];             // prefix sums over the waves, in every row of 16 lanes
+        upto_w += __builtin_amdgcn_update_dpp(0, upto_w, 0x111, 0xf, 0xf, true);       // row_shr 1, 2, 4, 8
+        upto_w += __builtin_amdgcn_update_dpp(0, upto_w, 0x112, 0xf, 0xf, true);
+        upto_w += __builtin_amdgcn_update_dpp(0, upto_w, 0x114, 0xf, 0xf, true);
+        if (SEL_WAVES > 8) upto_w += __builtin_amdgcn_update_dpp(0, upto_w, 0x118, 0xf, 0xf, true);
+        int o = running + before + (wave ? __builtin_amdgcn_readlane(upto_w, wave - 1) : 0);
+        running += __builtin_amdgcn_readlane(upto_w, SEL_WAVES - 1);
         if (tid < n) {
             row_offsets[f0 + tid + 1] = o + c;
             for (uint64_t s = sel; s; s &= s - 1, ++o) {
@@ -394,9 +397,10 @@ int launch_select(const float *label_scores, int F, int K, const uint8_t *group_
         if (wide) SELECT_LAUNCH(NW, 4, 1024); \
         else SELECT_LAUNCH(NW, 1, 1024);   \
     } while (0)
-    // Few frames: eight waves.  Most phases are a chain of LDS round trips that every wave goes through, four waves on a SIMD one behind the other.
-    // us per call in a queue of them, 16 contexts, 80 labels, eight waves / sixteen: 16 frames 7.1 / 7.8, 64 6.9 / 7.5, 128 7.7 / 7.8, 256 8.4 / 8.7
-    if (wide && F <= 256 && K <= 128) {
+    // Few frames and contexts: eight waves.  Most phases are a chain of LDS round trips that every wave goes through, four waves on a SIMD one behind
+    // the other; the set-up of many contexts wants the waves.  us of the kernel, 80 labels, eight waves / sixteen: 16 contexts, 1 frame 5.2 / 5.4,
+    // 64 6.1 / 6.6, with context copy 8.0 / 9.5, 256 7.5 / 7.6, with copy 9.3 / 10.3; 45 contexts, 1 frame 7.7 / 7.0, 64 8.8 / 8.3, 256 10.2 / 9.4.
+    if (wide && F <= 256 && K <= 128 && M <= 32) {
         if (K <= 64) SELECT_LAUNCH(1, 4, 512);
         else SELECT_LAUNCH(2, 4, 512);
     }

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("F", [1, 63, 64, 65, 255, 256, 257, 513, 1025, 2049])
-@pytest.mark.parametrize("K,M", [(64, 20), (80, 45), (126, 64)])
+@pytest.mark.parametrize("K,M", [(64, 20), (80, 30), (80, 45), (126, 64)])
 @pytest.mark.parametrize("copy", [False, True])
 def test_against_the_oracle(F, K, M, copy):
     rng = np.random.default_rng(F + K)
