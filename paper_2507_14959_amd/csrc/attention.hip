@@ -1,6 +1,6 @@
 // Fused softmax attention of one (token block, head) per workgroup; head width 64.
 //
-// bf16: K and V^T of the head are staged once in LDS.  Each wave owns 32 queries (one wave per query tile) and computes
+// bf16: K and V^T of the head are staged once in LDS.  Each wave owns 32 queries (or two such tiles, one after the other) and computes
 // S^T = K Q^T on the MFMA (keys down the rows, so every lane holds all scores of ONE query), takes the
 // softmax over its registers in fp32, and feeds the unnormalised probabilities straight back as the B
 // operand of O^T = V^T P^T -- the accumulator layout of S^T is already a valid B layout once the keys of
@@ -12,8 +12,8 @@ namespace {
 
 constexpr float LOG2E = 1.4426950408889634f;
 
-template <int NKT>  // 32-key tiles: T <= 32 * NKT
-__global__ __launch_bounds__(512) void attn_bf16_kernel(const bf16_t *qkv, bf16_t *out, int T, int D, int heads, int n_blocks,
+template <int NKT, int W>  // 32-key tiles: T <= 32 * NKT; waves, each takes the query tiles w, w + W, ..
+__global__ __launch_bounds__(64 * W, 2 * W <= 8 ? 2 : 1) void attn_bf16_kernel(const bf16_t *qkv, bf16_t *out, int T, int D, int heads, int n_blocks,
                                                         const int *n_blocks_dev)
 {
     constexpr int TKP = NKT * 32;
@@ -31,17 +31,19 @@ __global__ __launch_bounds__(512) void attn_bf16_kernel(const bf16_t *qkv, bf16_
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lm = lane & 31, lh = lane >> 5;
     const size_t ld = (size_t)3 * D;
     const bf16_t *base = qkv + (size_t)b * T * ld + hd * 64;
-    const int nthreads = blockDim.x;
+    constexpr int nthreads = 64 * W;
 
-    // everything this thread will read from global memory is requested up front: its queries (wave w owns the 32-query
-    // tile w), then its share of K (16-byte pieces) and of V (an 8 keys x 8 columns block, transposed in registers below).
+    // everything this thread will read from global memory is requested up front: its queries (of its first 32-query
+    // tile), then its share of K (16-byte pieces) and of V (an 8 keys x 8 columns block, transposed in registers below).
     // Rows past T repeat row T - 1 (a load under a per-lane condition would be waited for on the spot): such keys are
     // masked in the softmax and get probability 0, such queries are never stored
-    const int qs = wave, query = qs * 32 + lm;
     bf16x8 qf[4];
+    auto load_q = [&](int qs) {
 #pragma unroll
-    for (int ds = 0; ds < 4; ++ds) qf[ds] = *(const bf16x8 *)(base + (size_t)min(query, T - 1) * ld + ds * 16 + lh * 8);
-    constexpr int NKP = 4;                         // K pieces (256 NKT) per thread: the workgroup has 64 NKT threads
+        for (int ds = 0; ds < 4; ++ds) qf[ds] = *(const bf16x8 *)(base + (size_t)min(qs * 32 + lm, T - 1) * ld + ds * 16 + lh * 8);
+    };
+    load_q(wave);
+    constexpr int NKP = (256 * NKT + nthreads - 1) / nthreads;     // K pieces (256 NKT) per thread
     bf16x8 kp[NKP];
 #pragma unroll
     for (int i = 0; i < NKP; ++i) {
@@ -69,7 +71,7 @@ __global__ __launch_bounds__(512) void attn_bf16_kernel(const bf16_t *qkv, bf16_
     }
     __syncthreads();
 
-    {
+    for (int qs = wave; qs * 32 < T; qs += W) {
         // S^T tile kt: rows = keys kt*32 + 8*(e/4) + 4*lh + e%4, column = this lane's query.  The K fragments of tile
         // kt + 1 are read while the MFMAs of tile kt run (the scheduling barriers pin that order)
         f32x16 s[NKT];
@@ -89,6 +91,8 @@ __global__ __launch_bounds__(512) void attn_bf16_kernel(const bf16_t *qkv, bf16_
             for (int ds = 0; ds < 4; ++ds) s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kt & 1][ds], qf[ds], s[kt], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
+
+        if (NKT > W) load_q(min(qs + W, NKT - 1));             // for the next round: arrives under this one's softmax
 
         // only the last key tile can hold keys past T (T > 32 * (NKT - 1) by construction)
 #pragma unroll
@@ -265,14 +269,12 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *qkv, float *
     }
 }
 
-template <int NKT>
+template <int NKT, int W = NKT>
 int launch_bf16(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, hipStream_t st)
 {
-    // one wave per 32-query tile (up to 7): two waves per SIMD share the softmax's vector work
-    const int waves = (T + 31) / 32;
     constexpr int TKP = NKT * 32;
-    constexpr int LDS = (TKP * 72 + 64 * (TKP + 8) + NKT * 32 * 72) * 2;
-    auto kern = attn_bf16_kernel<NKT>;
+    constexpr int LDS = (TKP * 72 + 64 * (TKP + 8) + W * 32 * 72) * 2;
+    auto kern = attn_bf16_kernel<NKT, W>;
     if (LDS > 64 * 1024) {
         static bool attr_set = false;   // raising the dynamic LDS limit is a per-kernel, process-wide setting
         if (!attr_set) {
@@ -280,7 +282,7 @@ int launch_bf16(const void *qkv, void *out, int T, int D, int heads, int n_block
             attr_set = true;
         }
     }
-    POLY_LAUNCH_SHMEM(POLY_STAGE_ATTN, kern, dim3((unsigned)(n_blocks * heads)), dim3(64 * waves), LDS, st, (const bf16_t *)qkv, (bf16_t *)out, T, D,
+    POLY_LAUNCH_SHMEM(POLY_STAGE_ATTN, kern, dim3((unsigned)(n_blocks * heads)), dim3(64 * W), LDS, st, (const bf16_t *)qkv, (bf16_t *)out, T, D,
                       heads, n_blocks, n_blocks_dev);
     return POLY_OK;
 }
@@ -293,14 +295,19 @@ int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_
     if (n_blocks == 0) return POLY_OK;
     if (D != heads * 64) return POLY_EINVAL;
     if (dtype == POLY_BF16) {
+        // From 161 keys on, K, V and the output tiles of a wave per query tile are more LDS than half a CU has.  Half the waves, two query tiles each,
+        // let two workgroups share a CU, one loading while the other computes, where there are more workgroups than CUs (counted on a
+        // device: three quarters of the bound).  us, one workgroup per CU / two: 999 of 197 tokens 32.3 / 28.4, about 1400 50.6 / 42.6 (heads
+        // 1.5 KB apart), 384 16.6 / 16.2, but 192 9.2 / 10.6.
+        const bool many = (long)n_blocks * heads * (n_blocks_dev ? 3 : 4) > 4 * 256;
         switch ((T + 31) / 32) {
         case 1: if (launch_bf16<1>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
         case 2: if (launch_bf16<2>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
         case 3: if (launch_bf16<3>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
         case 4: if (launch_bf16<4>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
         case 5: if (launch_bf16<5>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
-        case 6: if (launch_bf16<6>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
-        case 7: if (launch_bf16<7>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
+        case 6: if ((many ? launch_bf16<6, 3> : launch_bf16<6>)(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
+        case 7: if ((many ? launch_bf16<7, 4> : launch_bf16<7>)(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
         default: return POLY_EINVAL;  // bf16 attention holds all keys of a block in 64 KB of LDS: T <= 224
         }
     } else {
