@@ -735,40 +735,47 @@ static long product_tiles(const GemmArgs &g, int bm, int bn) { return (long)g.n_
 // 5910 x 768 -> 3072 55 / 52 / 47 / 47; 12608 x 768 -> 768 43 / 39 / 43 / 33; 12608 x 768 -> 2304 54 / 67 / 59 / 70;
 // 26201 x 3072 -> 768 221 / 173 / 243 / 210; 50432 x 768 -> 2304, two branches 230 / 290 / 261 / 301.
 struct TileCost {
-    int bm, bn, per_cu;                                    // workgroups per CU
+    int bm, bn, per_cu, rows;                              // workgroups per CU, rows of a wave's region
     float start, f, k, fan, res, last1, last2;             // last1, last2: share of a round with one / two workgroups per CU in it
-};
-// Where the device alone knows how many blocks there are, the mean over half to all of the bound: which round ends well at the bound says nothing
-// (64 frames with one to three adapters each have 115 blocks of a bound of 192).
-static float tile_cost(const TileCost &c, const GemmArgs &g)
+    float apart, apart_res;                                // more per round (with a residual) where the epilogue cannot fetch ahead: 28 x 197 -> 326 x 17
+};                                                         // rows x 768 -> 3072 45 -> 51 us (128 x 128) to 55 -> 76 (256 x 256)
+static float tile_cost(const TileCost &c, const GemmArgs &g, long n)
 {
-    const long all = product_tiles(g, c.bm, c.bn), slots = 256L * c.per_cu;
-    const float round = c.f + c.k * g.K + (g.out_off ? c.fan : 0.f) + (g.mode == EPI_RESID ? c.res : 0.f);
-    float rounds = 0.f;
-    const int from = g.n_in_dev ? 8 : 16;
-    for (int part = from; part <= 16; ++part) {
-        const long n = (all * part + 15) / 16, rest = n % slots;
-        const int per_cu = (int)((rest + 255) / 256);
-        rounds += (float)(n / slots) + (rest == 0 ? 0.f : per_cu == c.per_cu ? 1.f : per_cu == 1 ? c.last1 : c.last2);
-    }
-    return c.start + round * rounds / (float)(17 - from);
+    const long slots = 256L * c.per_cu, rest = n % slots;
+    const bool apart = (g.Tb && g.Tb < c.rows) || g.set_off || (g.S && (g.RP != 16 || g.r % 8 != 0)), res = g.mode == EPI_RESID;
+    const float round = c.f + c.k * g.K + (g.out_off ? c.fan : 0.f) + (res ? c.res : 0.f) + (!apart ? 0.f : res ? c.apart_res : c.apart);
+    const int per_cu = (int)((rest + 255) / 256);
+    return c.start + round * ((float)(n / slots) + (rest == 0 ? 0.f : per_cu == c.per_cu ? 1.f : per_cu == 1 ? c.last1 : c.last2));
 }
 
 static int launch_gemm_dma(const GemmArgs &g, hipStream_t st)
 {
-    static const TileCost cost[4] = {{128, 64, 3, 1.9f, 3.6f, 0.0138f, 2.6f, 3.5f, 0.60f, 0.78f},
-                                     {128, 128, 2, 3.2f, 2.7f, 0.0187f, 3.3f, 8.2f, 0.48f, 0.f},
-                                     {256, 128, 1, -3.4f, 9.8f, 0.0102f, 2.8f, 3.9f, 0.f, 0.f},
-                                     {256, 256, 1, -4.6f, 12.4f, 0.0212f, 5.2f, 13.7f, 0.f, 0.f}};
+    static const TileCost cost[4] = {{128, 64, 3, 32, 1.9f, 3.6f, 0.0138f, 2.6f, 3.5f, 0.60f, 0.78f, 7.f, 16.f},
+                                     {128, 128, 2, 32, 3.2f, 2.7f, 0.0187f, 3.3f, 8.2f, 0.48f, 0.f, 5.f, 9.f},
+                                     {256, 128, 1, 64, -3.4f, 9.8f, 0.0102f, 2.8f, 3.9f, 0.f, 0.f, 4.f, 9.f},
+                                     {256, 256, 1, 128, -4.6f, 12.4f, 0.0212f, 5.2f, 13.7f, 0.f, 0.f, 6.f, 4.f}};
     if (g.pos) {                                           // patch embedding: row tiles inside blocks, an epilogue that fetches nothing ahead
         if (g.N % 128 == 0) launch_dma<128, 128, 2, 2, 2>(g, st);
         else if (product_tiles(g, 128, 64) < 256) launch_dma<64, 64, 2, 2, 4>(g, st);    // (147 tiles of 128 x 64: 14.3 us, as 64 x 64 9 us)
         else launch_dma<128, 64, 2, 2, 2>(g, st);
         return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
     }
+    // Where the device alone knows how many blocks there are, the smallest mean of a tile's time over the fastest's at half to all of the bound, all of
+    // it (a caller's exact count) three times: which round ends well at the bound says nothing of fewer blocks (64 frames with one to three
+    // adapters each have 115 blocks of a bound of 192), and the mean of the times alone misses the bound by a round (5555 rows of 3072 -> 768 on 264
+    // tiles of 128 x 128 80 us, 128 x 64 44).
+    float worse[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int part = g.n_in_dev ? 8 : 16; part <= 16; ++part) {
+        float us[4], least = 1e30f;
+        for (int i = 0; i < 4; ++i) {
+            us[i] = tile_cost(cost[i], g, (product_tiles(g, cost[i].bm, cost[i].bn) * part + 15) / 16);
+            least = us[i] < least ? us[i] : least;
+        }
+        for (int i = 0; i < 4; ++i) worse[i] += us[i] / least * (part == 16 ? 3.f : 1.f);
+    }
     int best = 0;
     for (int i = 1; i < 4; ++i)
-        if (tile_cost(cost[i], g) < tile_cost(cost[best], g)) best = i;
+        if (worse[i] < worse[best]) best = i;
     if (best == 3) launch_dma<256, 256, 2, 4, 2>(g, st);
     else if (best == 2) launch_dma<256, 128, 4, 2, 3>(g, st);
     else if (best == 1) launch_dma<128, 128, 4, 2, 2>(g, st);
