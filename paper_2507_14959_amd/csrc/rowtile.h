@@ -17,23 +17,6 @@ __device__ __forceinline__ void glds16_s(const void *sbase, unsigned voff, unsig
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_byte_addr), "v"(voff), "s"(sbase) : "memory", "m0");
 }
-// eight such loads in a row, one wave filling a whole [64][64] bf16 tile: load g takes the per-lane byte offset voff[g]
-// from the uniform base and lands at lds_byte_addr + 1024 g + 16 * lane.  Three instructions per load (the LDS
-// position advances inside M0), for a wave whose only job is to keep the stream going.
-__device__ __forceinline__ void glds16_tile8(const void *sbase, unsigned lds_byte_addr, unsigned v0, unsigned v1, unsigned v2, unsigned v3,
-                                             unsigned v4, unsigned v5, unsigned v6, unsigned v7)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %1\n\t"
-                 "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %1\n\t"
-                 "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %1\n\t"
-                 "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %5, %1\n\t"
-                 "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %6, %1\n\t"
-                 "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %7, %1\n\t"
-                 "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %8, %1\n\t"
-                 "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %9, %1" ::"s"(lds_byte_addr),
-                 "s"(sbase), "v"(v0), "v"(v1), "v"(v2), "v"(v3), "v"(v4), "v"(v5), "v"(v6), "v"(v7)
-                 : "memory", "m0", "scc");
-}
 __device__ __forceinline__ unsigned lds_addr_of(const void *p)
 {
     return (unsigned)(size_t)(const __attribute__((address_space(3))) void *)p;
@@ -100,19 +83,8 @@ template <int KT> __device__ __forceinline__ void ln_gb_store(f32x4 v, float *gb
 {
     if (tid < 32 * KT) *(f32x4 *)(gb_s + 4 * tid) = v;
 }
-// Lanes l and l + 32 each hold two 8-byte pieces p0, p1.  Returns, in lane l < 32, (own p0, the other lane's p0) and, in lane
-// l + 32, (the other lane's p1, own p1): with p = four consecutive bf16 columns at offset 4 * (lane / 32) of an 8-column
-// group, lane l gets all eight columns of the first group and lane l + 32 all eight of the second.
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ u32x4 pair_halves(bf16x4 p0, bf16x4 p1)
-{
-    const u32x2 a = __builtin_bit_cast(u32x2, p0), b = __builtin_bit_cast(u32x2, p1);
-    // v_permlane32_swap: lanes 32-63 of the first operand trade places with lanes 0-31 of the second
-    const auto r0 = __builtin_amdgcn_permlane32_swap(a[0], b[0], false, false);
-    const auto r1 = __builtin_amdgcn_permlane32_swap(a[1], b[1], false, false);
-    return u32x4{r0[0], r1[0], r0[1], r1[1]};
-}
 
 // sum over the TPR (4 or 8) adjacent lanes that share a row, in every one of them: data-parallel-primitive moves inside
 // the quad (lane ^ 1, lane ^ 2) and across the two quads of eight lanes (mirror: every lane of a quad holds the quad's sum by
