@@ -760,6 +760,22 @@ static int launch_gemm_dma(const GemmArgs &g, hipStream_t st)
         else launch_dma<128, 64, 2, 2, 2>(g, st);
         return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
     }
+    // Ranks whose terms the epilogue cannot fetch ahead: waves with more rows each look their blocks up fewer times.  Few tiles of columns that 128 does
+    // not divide, and many of the others, take tiles of four waves of 64 (32) x 64 (32).  us, the model's tile / this one (blocks x tokens x K -> N, rank):
+    // 90 x 17 x 192 -> 576, 4 16.6 / 13.6; 160 x 17 x 192 -> 192, 32 23.0 / 18.2; 256 x 50 x 384 -> 1536, 32 98.5 / 73.6; 160 x 50 x 768 -> 2304, 32 112.6 /
+    // 97.1; the other side: 256 x 50 x 192 -> 576, 32 34.6 / 40.6; 90 x 17 x 192 -> 768, 32 a third less with the model's.
+    if (g.S && (g.RP != 16 || g.r % 8 != 0)) {
+        const bool odd = g.N % 128 != 0 && g.N < 1024, big = g.T > 128 && g.K >= 512;
+        const long few = product_tiles(g, 128, 64);
+        bool done = true;
+        if (odd && few < 256) launch_dma<64, 64, 2, 2, 4>(g, st);
+        else if (odd && few < 768) launch_dma<128, 64, 2, 2, 2>(g, st);
+        else if (odd || product_tiles(g, 128, 128) < 384) done = false;
+        else if (big && g.N % 256 == 0 && product_tiles(g, 256, 256) >= 512) launch_dma<256, 256, 2, 4, 2>(g, st);
+        else if (big && g.N % 128 == 0 && product_tiles(g, 256, 128) >= 512) launch_dma<256, 128, 4, 2, 3>(g, st);
+        else launch_dma<128, 128, 2, 2, 2>(g, st);
+        if (done) return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
+    }
     // Where the device alone knows how many blocks there are, the smallest mean of a tile's time over the fastest's at half to all of the bound, all of
     // it (a caller's exact count) three times: which round ends well at the bound says nothing of fewer blocks (64 frames with one to three
     // adapters each have 115 blocks of a bound of 192), and the mean of the times alone misses the bound by a round (5555 rows of 3072 -> 768 on 264

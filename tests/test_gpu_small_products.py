@@ -65,3 +65,13 @@ def test_short_contractions(n_xblocks, T, K, N, r, per_block):
 ])
 def test_large_tiles(n_xblocks, T, K, N, r, per_block):
     test_against_the_oracle(n_xblocks, T, K, N, r, per_block)
+
+
+@pytest.mark.parametrize("n_xblocks,T,K,N,r,per_block", [
+    (60, 17, 192, 576, 4, 1),        # fewer than 256 tiles of 128 x 64: 64 x 64
+    (256, 41, 192, 200, 20, 2),      # fewer than 768: 128 x 64 on waves of 64 x 32
+    (256, 50, 192, 1032, 20, 1),     # 384 tiles of 128 x 128 and more: waves of 64 x 64
+    (600, 101, 192, 200, 4, 1),      # neither
+])
+def test_ranks_that_are_not_fetched_ahead(n_xblocks, T, K, N, r, per_block):
+    test_against_the_oracle(n_xblocks, T, K, N, r, per_block)
