@@ -3,7 +3,7 @@
 //
 // With a few blocks a layer is no work for this chip, only a chain of dependent steps: a launch per step costs three to five
 // microseconds (issue, dispatch, caches emptied at the boundary), and a kernel that keeps 64 rows to itself through a whole layer
-// (rowlayer.hip) leaves most CUs idle while the busy ones pull 885 KB of weights each through a 24 byte / clock load path.  Here a
+// (rowlayer.hip) leaves most CUs idle while the busy ones pull 885 KB of weights each through one CU's load path.  Here a
 // layer is five steps
 //     Q  qkv = LayerNorm1(x) Wq + bq (+ low rank)      V is stored transposed, as the second product of attention reads it
 //     A  o = softmax(q k^T / 8) v                       one head, 32 queries

@@ -14,7 +14,7 @@
 // operations).  A lane's 16 bytes are 8 or 4 consecutive contraction elements of one row; both operands use the same order.
 //
 // 3 frames (591 rows) through the 768-wide backbone: proj and fc2 30 us each with 128 x 128 tiles, 16 us here, 1338 -> 906 us per
-// forward.  fp32 (config 1: 68-119 rows, K = 192 and 768) 49 us per product on the vector ALU, 11 us here.
+// forward.  fp32 (68-119 rows, K = 192 and 768) 49 us per product on the vector ALU, 7 to 9 us here.
 #include "poly_dev.h"
 #include "rowtile.h"
 
