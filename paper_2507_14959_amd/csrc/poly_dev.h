@@ -87,9 +87,9 @@ __device__ __forceinline__ f32x4 gelu_poly4(f32x4 x)
 
 // The same with a polynomial of degree 9 in t = min(2 x^2 / 4.4^2 - 1, 1), whose terms do not cancel (least maximum of |x dPhi| on [0, 4.4], half
 // as much weight past 3.4), and Phi cut off at 0 and 1 by the clamp of its last instruction: exact tails, no clamped copy of x.
-// Absolute error at most 2.4e-5 (8.6e-6 on |x| <= 4), root mean square 2.8e-6 for normal x, relative error below 6e-5 wherever |GELU| > 0.05; in
-// each of them below the table's (2.7e-5, 3.9e-6, 1.4e-4), so that it does not matter to the error whether a call runs in a kernel with
-// the table or in one with this.  14 plain fp32 instructions and no LDS.
+// Absolute error at most 2.4e-5 (8.6e-6 on |x| <= 4), root mean square 2.8e-6 for normal x, relative error below 6e-5 wherever |GELU| > 0.05.  The
+// table below has 1.6e-5, 1.8e-6 and 7e-5 (an interpolated one of the same size 2.7e-5, 3.9e-6, 1.4e-4): next to the bf16 rounding of the result,
+// 2e-3 of it, it does not matter whether a call runs in a kernel with the table or in one with this.  14 plain fp32 instructions and no LDS.
 __device__ __forceinline__ f32x4 gelu_fine4(f32x4 x)
 {
     f32x4 t, q;

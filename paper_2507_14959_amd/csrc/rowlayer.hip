@@ -346,7 +346,7 @@ __global__ __launch_bounds__(LY_THREADS, 2) void rowlayer_kernel(const RowLayerA
                 for (int rt = 0; rt < 2; ++rt) x[ct][rt] += own[ct][rt] + b;
             }
         }
-        if (lora_p) {                                      // 
+        if (lora_p) {
 #pragma unroll
             for (int rt = 0; rt < 2; ++rt) {
                 f32x4 c = {0.f, 0.f, 0.f, 0.f};
