@@ -395,7 +395,8 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
             g.mode = EPI_STORE; g.out = w.qkv; g.Tout = T;
             POLY_TRY(launch_gemm(g, dt, st));
         }
-        POLY_TRY(launch_attention(w.qkv, w.o, T, D, m->heads, n_out, n_out_dev, dt, st));
+        // (as a rule a frame has an adapter, so that there are about as many row-blocks as frames or more)
+        POLY_TRY(launch_attention(w.qkv, w.o, T, D, m->heads, n_out, n_out_dev, n_out < F ? n_out : F, dt, st));
         // narrow models without adapters on fc1 / fc2: everything row-wise of the layer in one launch -- proj with its
         // residual, the MLP half, and the qkv linear of the next layer when that layer works on the same blocks
         if (dt == POLY_BF16 && !use(2) && !use(3) && !(summed && (use(0) || use(1))) && rowlayer_supported(D, Dm, (use(0) || use(1)) ? m->r : 0)) {

@@ -12,14 +12,18 @@ namespace {
 
 constexpr float LOG2E = 1.4426950408889634f;
 
-template <int NKT, int W>  // 32-key tiles: T <= 32 * NKT; waves, each takes the query tiles w, w + W, ..
-__global__ __launch_bounds__(64 * W, 2 * W <= 8 ? 2 : 1) void attn_bf16_kernel(const bf16_t *qkv, bf16_t *out, int T, int D, int heads, int n_blocks,
+// A wave per query tile and, from 161 keys on, room for a second workgroup on the CU: 32 output columns staged at a time, at most 168 registers, and
+// where there are more workgroups than CUs half of the waves leave once K and V are in LDS, so that the next workgroup's fit beside the others.
+constexpr bool att_shares(int nkt, int w) { return nkt == w && nkt >= 6; }
+
+template <int NKT, int W>  // 32-key tiles: T <= 32 * NKT; waves, each takes the query tiles w, w + live, ..
+__global__ __launch_bounds__(64 * W, att_shares(NKT, W) ? 3 : 2 * W <= 8 ? 2 : 1) void attn_bf16_kernel(const bf16_t *qkv, bf16_t *out, int T, int D, int heads, int n_blocks,
                                                         const int *n_blocks_dev)
 {
     constexpr int TKP = NKT * 32;
     constexpr int KS = 64 + 8;    // Ks row stride (elements): 144 B, 16-byte aligned
     constexpr int VS = TKP + 8;   // Vt row stride: multiple of 8 elements
-    constexpr int OS = 64 + 8;    // row stride of a wave's output tile
+    constexpr int OC = att_shares(NKT, W) ? 32 : 64, OS = OC + 8;    // columns of a wave's output tile staged at a time, its row stride
     extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
     bf16_t *Ks = smem;                       // [TKP][KS]
     bf16_t *Vt = Ks + TKP * KS;              // [64][VS]
@@ -71,7 +75,9 @@ __global__ __launch_bounds__(64 * W, 2 * W <= 8 ? 2 : 1) void attn_bf16_kernel(c
     }
     __syncthreads();
 
-    for (int qs = wave; qs * 32 < T; qs += W) {
+    const int live = att_shares(NKT, W) && nb * heads > 256 ? (NKT + 1) / 2 : W;
+    if (wave >= live) return;
+    for (int qs = wave; qs * 32 < T; qs += live) {
         // S^T tile kt: rows = keys kt*32 + 8*(e/4) + 4*lh + e%4, column = this lane's query.  The K fragments of tile
         // kt + 1 are read while the MFMAs of tile kt run (the scheduling barriers pin that order)
         f32x16 s[NKT];
@@ -92,7 +98,7 @@ __global__ __launch_bounds__(64 * W, 2 * W <= 8 ? 2 : 1) void attn_bf16_kernel(c
             __builtin_amdgcn_sched_barrier(0);
         }
 
-        if (NKT > W) load_q(min(qs + W, NKT - 1));             // for the next round: arrives under this one's softmax
+        if (att_shares(NKT, W) ? qs + live < NKT : NKT > W) load_q(min(qs + live, NKT - 1));   // for the next round: arrives under this one's softmax
 
         // only the last key tile can hold keys past T (T > 32 * (NKT - 1) by construction)
 #pragma unroll
@@ -160,20 +166,24 @@ __global__ __launch_bounds__(64 * W, 2 * W <= 8 ? 2 : 1) void attn_bf16_kernel(c
         const float inv = 1.0f / sum;
         bf16_t *ot = Ot + wave * 32 * OS;
 #pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
+        for (int c0 = 0; c0 < 64; c0 += OC) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                bf16x4 w;
+            for (int dt = c0 / 32; dt < (c0 + OC) / 32; ++dt)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) w[q] = (bf16_t)(o[dt][g * 4 + q] * inv);
-                *(bf16x4 *)(ot + lm * OS + dt * 32 + 8 * g + 4 * lh) = w;
+                for (int g = 0; g < 4; ++g) {
+                    bf16x4 w;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) w[q] = (bf16_t)(o[dt][g * 4 + q] * inv);
+                    *(bf16x4 *)(ot + lm * OS + dt * 32 - c0 + 8 * g + 4 * lh) = w;
+                }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");    // the tile is private to the wave: no barrier
+            constexpr int LR = OC / 8, RI = 64 / LR;              // lanes per row, rows per instruction
+#pragma unroll
+            for (int i = 0; i < 32 / RI; ++i) {
+                const int row = i * RI + lane / LR, qrow = qs * 32 + row;
+                const bf16x8 v = *(const bf16x8 *)(ot + row * OS + lane % LR * 8);
+                if (qrow < T) *(bf16x8 *)(out + ((size_t)b * T + qrow) * D + hd * 64 + c0 + lane % LR * 8) = v;
             }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");    // the tile is private to the wave: no barrier
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = i * 8 + (lane >> 3), qrow = qs * 32 + row;
-            const bf16x8 v = *(const bf16x8 *)(ot + row * OS + (lane & 7) * 8);
-            if (qrow < T) *(bf16x8 *)(out + ((size_t)b * T + qrow) * D + hd * 64 + (lane & 7) * 8) = v;
         }
     }
 }
@@ -273,7 +283,7 @@ template <int NKT, int W = NKT>
 int launch_bf16(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, hipStream_t st)
 {
     constexpr int TKP = NKT * 32;
-    constexpr int LDS = (TKP * 72 + 64 * (TKP + 8) + W * 32 * 72) * 2;
+    constexpr int LDS = (TKP * 72 + 64 * (TKP + 8) + W * 32 * (att_shares(NKT, W) ? 40 : 72)) * 2;
     auto kern = attn_bf16_kernel<NKT, W>;
     if (LDS > 64 * 1024) {
         static bool attr_set = false;   // raising the dynamic LDS limit is a per-kernel, process-wide setting
@@ -289,17 +299,17 @@ int launch_bf16(const void *qkv, void *out, int T, int D, int heads, int n_block
 
 }  // namespace
 
-int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, int dtype,
+int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, int n_usual, int dtype,
                      hipStream_t st)
 {
     if (n_blocks == 0) return POLY_OK;
     if (D != heads * 64) return POLY_EINVAL;
     if (dtype == POLY_BF16) {
-        // From 161 keys on, K, V and the output tiles of a wave per query tile are more LDS than half a CU has.  Half the waves, two query tiles each,
-        // let two workgroups share a CU, one loading while the other computes, where there are more workgroups than CUs (counted on a
-        // device: three quarters of the bound).  us, one workgroup per CU / two: 999 of 197 tokens 32.3 / 28.4, about 1400 50.6 / 42.6 (heads
-        // 1.5 KB apart), 384 16.6 / 16.2, but 192 9.2 / 10.6.
-        const bool many = (long)n_blocks * heads * (n_blocks_dev ? 3 : 4) > 4 * 256;
+        // From 161 keys on, two query tiles per wave and two workgroups per CU, one loading while the other computes, are faster where there are more
+        // workgroups than CUs, and slower below.  Half the waves from the start where the usual count says so, else the form that looks at the true
+        // count (its second workgroup cannot load beside the first).  us, a tile per wave and CUs to themselves / half the waves / by the count, 197
+        // tokens: 90 workgroups 7.7 / 9.0 / 7.7, 192 8.3 / 9.8 / 8.4, 255 9.6 / 10.9 / 9.7, 270 15.7 / 14.5 / 14.8, 600 - / 22.0 / 22.7, 999 32.3 / 27.6 / 28.9.
+        const bool many = (long)n_usual * heads > 256;
         switch ((T + 31) / 32) {
         case 1: if (launch_bf16<1>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
         case 2: if (launch_bf16<2>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;

@@ -332,8 +332,8 @@ int launch_shrink_csr(const void *X, int T, int K, const void *At, int r, int RP
                       int F, int R_cap, int n_adapters, PolyMeta *meta, int32_t *frame_of_row, int32_t *adapter_of_row, int32_t *dev_status, void *S,
                       hipStream_t st);
 
-// softmax attention of every (block, head); qkv elt [n*T][3D] -> out elt [n*T][D]
-int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev,
+// softmax attention of every (block, head); qkv elt [n*T][3D] -> out elt [n*T][D].  n_usual: blocks that a call of n_blocks at most has as a rule (<= n_blocks)
+int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, int n_usual,
                      int dtype, hipStream_t st);
 
 // poly_select with what the lagged loop needs right behind it done in the same launch (select.hip): meta != null: the row maps and

@@ -1,7 +1,9 @@
 """Attention of long blocks with two query tiles per wave: more (block, head) pairs than CUs."""
+import numpy as np
 import pytest
 
-from paper_2507_14959_amd import synth
+import oracle
+from paper_2507_14959_amd import binding, synth
 from test_gpu_forward import compare
 
 pytestmark = pytest.mark.gpu
@@ -17,3 +19,24 @@ def test_against_the_oracle(D, heads, Dm, hw, F, L0):
     cfg, w, frames, off, ids = synth.make_small_case(7 + D + hw, dtype=synth.DT_BF16, targets=3, L=2, F=F, r=8, max_set=2, n_adapters=5, D=D, heads=heads,
                                                      Dm=Dm, hw=hw, patch=8)
     compare(cfg, w, frames, off, ids, L0)
+
+
+@pytest.mark.parametrize("hw,n,adapters,cap", [
+    (112, 100, 1, 400),      # 200 pairs of a bound of 800: a tile per wave
+    (112, 100, 2, 200),      # 400 pairs: half the waves leave, one of the others has a single tile
+    (112, 128, 1, 512),      # 256 pairs, the last count of a tile per wave
+    (112, 43, 3, 172),       # 258 pairs
+    (104, 100, 2, 300),      # 170 tokens: six tiles
+    (104, 90, 1, 360),
+])
+def test_form_by_the_true_count(hw, n, adapters, cap):
+    """Room for more adapters than are in use, and frames on the small side of the rule: which form runs is the device's choice."""
+    cfg, w, frames, _, _ = synth.make_small_case(900 + n + hw, dtype=synth.DT_BF16, targets=3, L=2, F=n, r=8, n_adapters=5, D=128, heads=2, Dm=128, hw=hw,
+                                                 patch=8)
+    rng = np.random.default_rng(n)
+    off, ids = synth.sets_to_csr([sorted(rng.choice(5, size=adapters, replace=False)) for _ in range(n)])
+    room = np.concatenate([ids, np.zeros(cap - len(ids), dtype=ids.dtype)])
+    got = binding.run_forward(binding.DeviceModel(cfg, w, L0=0), frames, off, room, R_cap=cap)
+    want = oracle.forward(cfg, w, frames, off, ids, L0=0)["logits"]
+    # 1.1e-3 to 1.7e-3 over the cases; a linear's bias left out of one layer moves the logits by 6e-3 and more
+    assert got["status"] == 0 and np.abs(got["logits"][:len(ids)] - want).max() < 4e-3
