@@ -267,7 +267,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         g.A = w.patches; g.Wt = base->patch_w; g.bias = base->patch_b;
         g.T = T - 1; g.K = pd; g.N = D; g.n_in = F;
         g.mode = EPI_RESID; g.out = w.xa; g.Tout = T; g.t_off = 1; g.pos = base->pos;
-        POLY_TRY(launch_gemm(g, dt, st));
+        POLY_TRY(launch_gemm(g, {true, 0}, dt, st));
     }
 
     auto flow = [&](bool ad) -> int {
@@ -339,6 +339,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         // narrow models (D <= 192, bf16): LayerNorm, shrink, base product and expand of one linear run in one
         // kernel that keeps 64 token rows on chip; otherwise LayerNorm / shrink / GEMM are separate launches
         auto fused = [&](int t) { return dt == POLY_BF16 && !(summed && use(t)) && rowlin_supported(D, t == 0 ? 3 * D : (t == 2 ? Dm : D), m->r, use(t), t == 1); };
+        const int pairs = (F + R) / 2;         // (frame, adapter): between one each and the bound
         // low-rank operands of the GEMM path: S block and adapter per (frame, adapter) pair; summed: the pairs of a frame
         // all land on the frame's block
         const int *shrink_map = summed ? w.frame_of_row : nullptr;
@@ -393,7 +394,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
                 lora_gemm(g, 0, Bt);
             }
             g.mode = EPI_STORE; g.out = w.qkv; g.Tout = T;
-            POLY_TRY(launch_gemm(g, dt, st));
+            POLY_TRY(launch_gemm(g, {!branch, pairs}, dt, st));
         }
         // (as a rule a frame has an adapter, so that there are about as many row-blocks as frames or more)
         POLY_TRY(launch_attention(w.qkv, w.o, T, D, m->heads, n_out, n_out_dev, n_out < F ? n_out : F, dt, st));
@@ -440,7 +441,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
                 lora_gemm(g, 1, Bt);
             }
             g.mode = EPI_RESID; g.out = x_out; g.Tout = T; g.res = x_in; g.res_block_of_out = fan_map;
-            POLY_TRY(launch_gemm(g, dt, st));
+            POLY_TRY(launch_gemm(g, {n_out_dev != R_dev, pairs}, dt, st));
         }
         // ---- MLP half (x_out holds the stream from here on)
         if (dt == POLY_BF16 && !use(2) && !use(3) && mlp_supported(D, Dm)) {
@@ -468,7 +469,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
                 lora_gemm(g, 2, Bt);
             }
             g.mode = EPI_GELU; g.out = w.h; g.Tout = T;
-            POLY_TRY(launch_gemm(g, dt, st));
+            POLY_TRY(launch_gemm(g, {n_out_dev != R_dev, pairs}, dt, st));
         }
         {
             GemmArgs g = {};
@@ -481,7 +482,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
                 lora_gemm(g, 3, Bt);
             }
             g.mode = EPI_RESID; g.out = x_out; g.Tout = T; g.res = x_out;
-            POLY_TRY(launch_gemm(g, dt, st));
+            POLY_TRY(launch_gemm(g, {n_out_dev != R_dev, pairs}, dt, st));
         }
     }
 
@@ -586,7 +587,7 @@ int lora_linear_impl(const void *X, int n_xblocks, int T, int Kdim, const void *
     g.n_in = n_xblocks; g.n_in_dev = &w.meta->F_ok; g.out_off = row_offsets;
     g.S = w.S; g.RP = RP; g.Bt = Bt; g.r = r; g.adapter_of_out = w.adapter_of_row;
     g.mode = EPI_STORE; g.out = Y; g.Tout = T;
-    return launch_gemm(g, dtype, st);
+    return launch_gemm(g, {true, R}, dtype, st);
 }
 
 int check_lora_linear(const void *X, int n_xblocks, int T, int Kdim, const void *Wt, int Ndim, const void *At, const void *Bt,

@@ -725,81 +725,31 @@ static void launch_dma(const GemmArgs &g, hipStream_t st)
     launch_dma_ek<BM, BN, WM, WN, NS, 0>(g, st);
 }
 
-static long product_tiles(const GemmArgs &g, int bm, int bn) { return (long)g.n_in * ((g.T + bm - 1) / bm) * ((g.N + bn - 1) / bn); }
+static long product_tiles(const GemmArgs &g, int bm, int bn) { return product_tiles(g.n_in, g.T, g.N, bm, bn); }
 
-// What a product takes on a tile, in us: rounds of as many workgroups as fit the chip, and a last round that is cheaper where it leaves CUs with
-// fewer workgroups than they hold.  Per round f + k K, plus `fan` where rows fan out, plus `res` with a residual.  Fitted to 89 products
-// (788 to 50432 rows; K -> N 192 -> 576, 768; 384 -> 384, 1152, 1536; 768 -> 768, 2304, 3072; 3072 -> 768; rank 16) within 7 to 11 %: the tile it
-// picks is on average 1.1 % slower than the fastest of the four, at worst 17 % (17730 x 192 -> 768).
-// us, 256 x 256 / 256 x 128 / 128 x 128 / 128 x 64 (rows x K -> N): 1773 x 192 -> 576, two branches 15.4 / 10.3 / 7.7 / 7.1;
-// 5910 x 768 -> 3072 55 / 52 / 47 / 47; 12608 x 768 -> 768 43 / 39 / 43 / 33; 12608 x 768 -> 2304 54 / 67 / 59 / 70;
-// 26201 x 3072 -> 768 221 / 173 / 243 / 210; 50432 x 768 -> 2304, two branches 230 / 290 / 261 / 301.
-struct TileCost {
-    int bm, bn, per_cu, rows;                              // workgroups per CU, rows of a wave's region
-    float start, f, k, fan, res, last1, last2;             // last1, last2: share of a round with one / two workgroups per CU in it
-    float apart, apart_res;                                // more per round (with a residual) where the epilogue cannot fetch ahead: 28 x 197 -> 326 x 17
-};                                                         // rows x 768 -> 3072 45 -> 51 us (128 x 128) to 55 -> 76 (256 x 256)
-static float tile_cost(const TileCost &c, const GemmArgs &g, long n)
+static int launch_gemm_dma(const GemmArgs &g, GemmCount count, hipStream_t st)
 {
-    const long slots = 256L * c.per_cu, rest = n % slots;
-    const bool apart = (g.Tb && g.Tb < c.rows) || g.set_off || (g.S && (g.RP != 16 || g.r % 8 != 0)), res = g.mode == EPI_RESID;
-    const float round = c.f + c.k * g.K + (g.out_off ? c.fan : 0.f) + (res ? c.res : 0.f) + (!apart ? 0.f : res ? c.apart_res : c.apart);
-    const int per_cu = (int)((rest + 255) / 256);
-    return c.start + round * ((float)(n / slots) + (rest == 0 ? 0.f : per_cu == c.per_cu ? 1.f : per_cu == 1 ? c.last1 : c.last2));
-}
-
-static int launch_gemm_dma(const GemmArgs &g, hipStream_t st)
-{
-    static const TileCost cost[4] = {{128, 64, 3, 32, 1.9f, 3.6f, 0.0138f, 2.6f, 3.5f, 0.60f, 0.78f, 7.f, 16.f},
-                                     {128, 128, 2, 32, 3.2f, 2.7f, 0.0187f, 3.3f, 8.2f, 0.48f, 0.f, 5.f, 9.f},
-                                     {256, 128, 1, 64, -3.4f, 9.8f, 0.0102f, 2.8f, 3.9f, 0.f, 0.f, 4.f, 9.f},
-                                     {256, 256, 1, 128, -4.6f, 12.4f, 0.0212f, 5.2f, 13.7f, 0.f, 0.f, 6.f, 4.f}};
     if (g.pos) {                                           // patch embedding: row tiles inside blocks, an epilogue that fetches nothing ahead
         if (g.N % 128 == 0) launch_dma<128, 128, 2, 2, 2>(g, st);
         else if (product_tiles(g, 128, 64) < 256) launch_dma<64, 64, 2, 2, 4>(g, st);    // (147 tiles of 128 x 64: 14.3 us, as 64 x 64 9 us)
         else launch_dma<128, 64, 2, 2, 2>(g, st);
         return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
     }
-    // Ranks whose terms the epilogue cannot fetch ahead: waves with more rows each look their blocks up fewer times.  Few tiles of columns that 128 does
-    // not divide, and many of the others, take tiles of four waves of 64 (32) x 64 (32).  us, the model's tile / this one (blocks x tokens x K -> N, rank):
-    // 90 x 17 x 192 -> 576, 4 16.6 / 13.6; 160 x 17 x 192 -> 192, 32 23.0 / 18.2; 256 x 50 x 384 -> 1536, 32 98.5 / 73.6; 160 x 50 x 768 -> 2304, 32 112.6 /
-    // 97.1; the other side: 256 x 50 x 192 -> 576, 32 34.6 / 40.6; 90 x 17 x 192 -> 768, 32 a third less with the model's.
-    if (g.S && (g.RP != 16 || g.r % 8 != 0)) {
-        const bool odd = g.N % 128 != 0 && g.N < 1024, big = g.T > 128 && g.K >= 512;
-        const long few = product_tiles(g, 128, 64);
-        bool done = true;
-        if (odd && few < 256) launch_dma<64, 64, 2, 2, 4>(g, st);
-        else if (odd && few < 768) launch_dma<128, 64, 2, 2, 2>(g, st);
-        else if (odd || product_tiles(g, 128, 128) < 384) done = false;
-        else if (big && g.N % 256 == 0 && product_tiles(g, 256, 256) >= 512) launch_dma<256, 256, 2, 4, 2>(g, st);
-        else if (big && g.N % 128 == 0 && product_tiles(g, 256, 128) >= 512) launch_dma<256, 128, 4, 2, 3>(g, st);
-        else launch_dma<128, 128, 2, 2, 2>(g, st);
-        if (done) return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
+    const float terms = g.out_off || g.set_off ? (float)count.terms / (g.Tb ? g.nb : g.n_in) : 1.f;
+    switch (cheapest_tile({g.n_in, g.T, g.Tb, g.K, g.N, g.S ? g.RP : 0, g.r, g.mode, g.out_off ? terms : 1.f, terms, g.set_off != nullptr,
+                           !g.n_in_dev || count.known})) {
+    case TILE_128x64: launch_dma<128, 64, 4, 1, 2>(g, st); break;
+    case TILE_128x128: launch_dma<128, 128, 4, 2, 2>(g, st); break;
+    case TILE_256x128: launch_dma<256, 128, 4, 2, 3>(g, st); break;
+    case TILE_256x256: launch_dma<256, 256, 2, 4, 2>(g, st); break;
+    case TILE_64x64: launch_dma<64, 64, 2, 2, 4>(g, st); break;
+    case TILE_128x64_TALL: launch_dma<128, 64, 2, 2, 2>(g, st); break;
+    default: launch_dma<128, 128, 2, 2, 2>(g, st);
     }
-    // Where the device alone knows how many blocks there are, the smallest mean of a tile's time over the fastest's at half to all of the bound, all of
-    // it (a caller's exact count) three times: which round ends well at the bound says nothing of fewer blocks (64 frames with one to three
-    // adapters each have 115 blocks of a bound of 192), and the mean of the times alone misses the bound by a round (5555 rows of 3072 -> 768 on 264
-    // tiles of 128 x 128 80 us, 128 x 64 44).
-    float worse[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int part = g.n_in_dev ? 8 : 16; part <= 16; ++part) {
-        float us[4], least = 1e30f;
-        for (int i = 0; i < 4; ++i) {
-            us[i] = tile_cost(cost[i], g, (product_tiles(g, cost[i].bm, cost[i].bn) * part + 15) / 16);
-            least = us[i] < least ? us[i] : least;
-        }
-        for (int i = 0; i < 4; ++i) worse[i] += us[i] / least * (part == 16 ? 3.f : 1.f);
-    }
-    int best = 0;
-    for (int i = 1; i < 4; ++i)
-        if (worse[i] < worse[best]) best = i;
-    if (best == 3) launch_dma<256, 256, 2, 4, 2>(g, st);
-    else if (best == 2) launch_dma<256, 128, 4, 2, 3>(g, st);
-    else if (best == 1) launch_dma<128, 128, 4, 2, 2>(g, st);
-    else launch_dma<128, 64, 4, 1, 2>(g, st);
     return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
 }
 
-int launch_gemm(const GemmArgs &g, int dtype, hipStream_t st)
+int launch_gemm(const GemmArgs &g, GemmCount count, int dtype, hipStream_t st)
 {
     if (g.n_in <= 0 || g.T <= 0) return POLY_OK;
     const bool bf16 = dtype == POLY_BF16;
@@ -815,17 +765,14 @@ int launch_gemm(const GemmArgs &g, int dtype, hipStream_t st)
         gf.T = (int)rows; gf.n_in = 1;          // (Tout stays the block length: it places the output blocks)
     }
     if (!bf16 || g.K % 64 != 0 || g.N % 8 != 0 || !gemm_aligned(g)) return launch_gemm_ks(gf, dtype, st);
-    // A long contraction on fewer 128 x 128 tiles than half the CUs takes smaller tiles: with the contraction split over the waves (gemm_ks.hip)
-    // where tiles of 32 x 64 get a CU each, and above a contraction of 1024 also where tiles of 64 x 64 do; else tiles of 64 x 64 that share a
-    // ring, two workgroups per CU.  us per product of the 768-wide backbone, split / shared ring / 128 x 128 (rows x K -> N):
+    // A long contraction on fewer 128 x 128 tiles than half the CUs is split over the waves (gemm_ks.hip) where tiles of 32 x 64 get a CU each, and
+    // above a contraction of 1024 also where tiles of 64 x 64 do.  us per product of the 768-wide backbone, split / tiles of 64 x 64 on a shared ring /
+    // 128 x 128 (rows x K -> N):
     //   197 x 768 -> 2304  7.6 / 7.0 / 11.9    591 x 768 -> 768   9.3 / 9.1 / 14.6    591 x 3072 -> 768   14.6 / 18.0 / 38.8
     //   197 x 768 -> 3072  9.0 / 7.4 / 13.4    985 x 768 -> 768  10.7 / 9.2 / 14.9    1182 x 3072 -> 768  19.0 / 19.2 / 39.1
     //   591 x 768 -> 2304 16.9 / 9.8 / 12.3    1576 x 768 -> 768 17.8 / 11.0 / 15.0   1576 x 3072 -> 768  32.4 / 25.3 / 39.0
     //   591 x 768 -> 3072 18.0 / 10.9 / 13.7   985 x 768 -> 2304 23.8 / 14.7 / 12.6 (144 tiles of 128 x 128)
-    if (g.K >= 512 && product_tiles(gf, 128, 128) < 128) {
-        if (product_tiles(gf, 32, 64) <= 256 || (g.K > 1024 && product_tiles(gf, 64, 64) <= 256)) return launch_gemm_ks(gf, dtype, st);
-        launch_dma<64, 64, 2, 2, 4>(gf, st);
-        return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
-    }
-    return launch_gemm_dma(gf, st);
+    if (g.K >= 512 && product_tiles(gf, 128, 128) < 128 && (product_tiles(gf, 32, 64) <= 256 || (g.K > 1024 && product_tiles(gf, 64, 64) <= 256)))
+        return launch_gemm_ks(gf, dtype, st);
+    return launch_gemm_dma(gf, count, st);
 }

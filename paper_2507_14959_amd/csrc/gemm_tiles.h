@@ -1,0 +1,85 @@
+// Which tile a bf16 product takes (gemm.hip).  Host arithmetic alone, so that the rule can be held without a GPU.
+#pragma once
+
+enum { EPI_STORE = 0, EPI_GELU = 1, EPI_RESID = 2 };
+
+struct TiledProduct {
+    int n_in, T, Tb, K, N;    // as in GemmArgs: input blocks (1 where the rows run across blocks), rows of one, block length inside such a run or 0
+    int RP, r;                // padded rank and rank of the low-rank terms, RP = 0: none
+    int mode;                 // EPI_*
+    float fan, terms;         // output blocks and low-rank terms per input block, about
+    bool sums;                // the terms are summed on one output block
+    bool known;               // n_in (T / Tb) blocks or none at all, else a bound of what the device knows
+};
+
+// What a product takes on a tile, in us: rounds of as many workgroups as fit the chip, the last one cheaper the fewer workgroups it has (fewer on a CU,
+// fewer pulling at the memory).  Per round f + k K for the loop and, per output block, `store` (+ `gelu` or `resid`) for the epilogue.  Where the epilogue
+// cannot fetch ahead, `term` (+ `odd` for ranks that fill no 16-byte load) per low-rank term, 16 ranks and block that a wave's region touches, `look` per
+// further block, and `late` for a residual.
+// Fitted to 3300 products, every tile measured on each (300 to 56000 rows; widths 192 to 768 and their two- to fourfold, 17 to 512 tokens; ranks 0 to 32,
+// one to three branches or summed terms): rms 6 to 10 %.  The tile it picks is on average 0.8 % slower than the fastest, more than 10 % on 46 of the 2740
+// that the split contraction is not faster on; the rules before (a model of four tiles without the branches' number, thresholds for ranks that are not
+// fetched ahead) 7 %, more than 10 % on every third, with the count known or a mean over counts alike.
+// us, 256 x 256 / 256 x 128 / 128 x 128 / 128 x 64 / 64 x 64 (blocks x tokens x K -> N): 121 x 197 x 768 -> 2304, three branches 141 / 153 / 133 / 148 / 281;
+// 107 x 101 x 768 -> 768 30 / 28 / 19 / 24 / 37; 233 x 17 x 384 -> 1536, rank 4, two branches 63 / 36 / 27 / 25 / 44; 9 x 170 x 1536 -> 768, rank 32, three
+// branches 61 / 34 / 28 / 26 / 20; with a residual, 161 x 50 x 768 -> 768, two summed terms of rank 4 63 / 37 / 43 / 43 / 43, on four waves of 64 x 32 33.
+struct TileCost {
+    int bm, bn, per_cu, rows;                              // workgroups per CU, rows of a wave's region
+    bool ahead, ahead_resid;                               // an epilogue that fetches ahead, also with a residual
+    float start, f, k, store, gelu, resid, term, odd, look, late, last1, last2, q;   // last1, last2: share of a round with one / two workgroups per CU in it
+};
+enum { TILE_128x64, TILE_128x128, TILE_256x128, TILE_256x256, TILE_64x64, TILE_128x64_TALL, TILE_128x128_TALL, N_TILES };   // (TALL: four waves of 64 rows)
+inline const TileCost &tile_costs(int tile)
+{
+    static const TileCost cost[N_TILES] = {
+        {128, 64, 3, 32, true, true, 3.38f, 0.607f, 0.0129f, 2.32f, 1.01f, 3.99f, 0.944f, 1.49f, 0.405f, 4.f, 0.544f, 0.752f, 0.131f},
+        {128, 128, 2, 32, true, true, 3.79f, 0.643f, 0.0147f, 2.76f, 1.45f, 8.95f, 1.04f, 1.53f, 0.441f, 3.28f, 0.592f, 0.f, 0.21f},
+        {256, 128, 1, 64, true, true, 1.92f, 3.27f, 0.0117f, 3.15f, 1.84f, 5.49f, 1.11f, 1.73f, 0.339f, 3.31f, 0.f, 0.f, 0.329f},
+        {256, 256, 1, 128, true, false, 2.02f, 3.15f, 0.0231f, 5.51f, 3.84f, 16.f, 1.62f, 2.41f, 0.162f, 0.f, 0.f, 0.f, 0.3f},
+        {64, 64, 2, 32, false, false, 3.47f, 1.1f, 0.00542f, 1.43f, 0.444f, 1.55f, 0.547f, 0.499f, 0.719f, 0.f, 0.72f, 0.f, 0.178f},
+        {128, 64, 3, 64, false, false, 3.67f, 0.66f, 0.0128f, 3.1f, 1.03f, 4.69f, 0.889f, 0.902f, 0.648f, 0.f, 0.588f, 0.773f, 0.126f},
+        {128, 128, 2, 64, true, true, 3.14f, 0.944f, 0.0136f, 3.17f, 1.78f, 5.76f, 1.14f, 1.88f, 0.401f, 3.58f, 0.72f, 0.f, 0.199f}};
+    return cost[tile];
+}
+
+inline long product_tiles(int n_in, int T, int N, int bm, int bn) { return (long)n_in * ((T + bm - 1) / bm) * ((N + bn - 1) / bn); }
+
+inline float tile_cost(const TileCost &c, const TiledProduct &p, long n)
+{
+    const bool resid = p.mode == EPI_RESID;
+    const bool ahead = (resid ? c.ahead_resid : c.ahead) && (!p.Tb || p.Tb >= c.rows) && !p.sums && (!p.RP || (p.RP == 16 && p.r % 8 == 0));
+    float round = c.f + c.k * p.K + p.fan * (c.store + (p.mode == EPI_GELU ? c.gelu : resid ? c.resid : 0.f));
+    if (!ahead) {
+        const float more = p.Tb ? (float)(c.rows - 1) / p.Tb : 0.f;    // blocks a region touches beyond the first, on average
+        round += (c.term + (p.r % 8 != 0 ? c.odd : 0.f)) * p.terms * (p.RP / 16) * (1.f + more) + p.fan * (c.look * more + (resid ? c.late : 0.f));
+    }
+    const long slots = 256L * c.per_cu, rest = n % slots;
+    float rounds = (float)(n / slots);
+    if (rest) {
+        const int per_cu = (int)((rest + 255) / 256);
+        rounds += (per_cu == c.per_cu ? 1.f : per_cu == 1 ? c.last1 : c.last2) - c.q * (per_cu - rest / 256.f);
+    }
+    return c.start + round * rounds;
+}
+
+// Where the count is known, the cheapest tile at it.  Where the device alone knows how many blocks there are, the smallest mean of a tile's time over
+// the fastest's at half to all of the bound, all of it three times: which round ends well at the bound says nothing of fewer blocks (64 frames
+// with one to three adapters each have 115 blocks of a bound of 192), and the mean of the times alone misses the bound by a round (5555 rows of
+// 3072 -> 768 on 264 tiles of 128 x 128 80 us, 128 x 64 44).
+inline int cheapest_tile(const TiledProduct &p)
+{
+    float worse[N_TILES] = {};
+    for (int part = p.known ? 16 : 8; part <= 16; ++part) {
+        float us[N_TILES], least = 1e30f;
+        for (int i = 0; i < N_TILES; ++i) {
+            const TileCost &c = tile_costs(i);
+            us[i] = tile_cost(c, p, (product_tiles(p.n_in, p.T, p.N, c.bm, c.bn) * part + 15) / 16);
+            least = us[i] < least ? us[i] : least;
+        }
+        for (int i = 0; i < N_TILES; ++i) worse[i] += us[i] / least * (part == 16 ? 3.f : 1.f);
+    }
+    int best = 0;
+    for (int i = 1; i < N_TILES; ++i)
+        if (worse[i] < worse[best]) best = i;
+    return best;
+}

@@ -7,6 +7,7 @@
 
 #include "../../include/poly.h"
 #include "../../include/poly_profile.h"
+#include "gemm_tiles.h"
 
 typedef __bf16 bf16_t;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -163,7 +164,6 @@ int poly_patience();     // FlowArgs::patience of this thread's calls
 
 // ---- stage launchers (defined in the .hip files, used by the entry points in api.hip) ----
 
-enum { EPI_STORE = 0, EPI_GELU = 1, EPI_RESID = 2 };
 
 // C = A Wt^T with per-block structure.  Rows come in blocks of T; input block xb feeds the output
 // blocks [out_off[xb], out_off[xb+1]) (or block xb itself when out_off is null).  Each output block ob
@@ -197,7 +197,12 @@ struct GemmArgs {
     int Tb, nb;
 };
 
-int launch_gemm(const GemmArgs &g, int dtype, hipStream_t st);
+// What the choice of a tile goes by beside the arguments (kept out of them: the kernels' arguments are a round trip per 64 bytes).
+struct GemmCount {
+    bool known;           // *n_in_dev is n_in or, where the CSR was rejected, 0
+    int terms;            // (input block, adapter) pairs where rows fan out or terms are summed, about
+};
+int launch_gemm(const GemmArgs &g, GemmCount count, int dtype, hipStream_t st);
 int launch_gemm_ks(const GemmArgs &g, int dtype, hipStream_t st);    // small calls, fp32 and any alignment (gemm_ks.hip); called by launch_gemm
 bool gemm_aligned(const GemmArgs &g);                                // every address a multiple of 16
 inline bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
