@@ -38,6 +38,9 @@ namespace {
 // 16 bytes per lane from uniform base + byte offset to lds_byte_addr + 16 lane; nothing where go <= 0, but counted as a load all the same.  Inline
 // assembly: the compiler would make LDS reads wait for loads it knows of, and a branch around them costs the reads' counted waits.
 // (All lanes of the wave are active.)
+// Every wait of a ring rests on this: a load with EXEC = 0 goes through vmcnt in its place in the order.  Were it skipped, the waits past the last k-tile
+// would let loads that move something stay in flight.  tests/test_product_tiles.py has contractions of a single k-tile on two and four stages, where all
+// loads behind those of the first wait are off; three stages are taken from a contraction of 512 on, where the last two waits rest on it.
 __device__ __forceinline__ void glds16_if(const void *sbase, unsigned voff, unsigned lds_byte_addr, int go)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_cmp_gt_i32 %3, 0\n\ts_cselect_b64 exec, -1, 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1" ::"s"(
@@ -293,7 +296,7 @@ void gemm_bf16_dma_kernel(const GemmArgs g, int tiles_m, int tiles_n)
     };
     step(std::true_type(), 0);
     for (int it = 1; it < nk; ++it) step(std::false_type(), it);
-    __syncthreads();   // all loads have landed (vmcnt(0) above) and all waves are done with the tiles
+    __syncthreads();   // all loads that move something have landed (the last wait leaves none but those switched off) and all waves are done with the tiles
 
     // ---- row-wise epilogue (bf16 output, two column subtiles per wave).  Per pass p the wave produces, for every row of its
     // (MI * 32) x 64 region, the p-th output block of that row's input block: base product (+ bias, in the accumulators) + the

@@ -1,4 +1,5 @@
-// Building blocks shared by the kernels that keep a tile of 64 token rows on chip (rowlin.hip, mlp.hip).
+// Building blocks of the kernels that load through LDS by hand-counted waits or keep a tile of 64 token rows on chip: rowlin.hip, mlp.hip, rowlayer.hip,
+// rowops.hip, gemm.hip, gemm_ks.hip, flow.hip.
 #pragma once
 #include "poly_dev.h"
 
@@ -83,7 +84,6 @@ template <int KT> __device__ __forceinline__ void ln_gb_store(f32x4 v, float *gb
 {
     if (tid < 32 * KT) *(f32x4 *)(gb_s + 4 * tid) = v;
 }
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 // sum over the TPR (4 or 8) adjacent lanes that share a row, in every one of them: data-parallel-primitive moves inside
