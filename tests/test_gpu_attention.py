@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 def test_against_the_oracle(D, heads, Dm, hw, F, L0):
     cfg, w, frames, off, ids = synth.make_small_case(7 + D + hw, dtype=synth.DT_BF16, targets=3, L=2, F=F, r=8, max_set=2, n_adapters=5, D=D, heads=heads,
                                                      Dm=Dm, hw=hw, patch=8)
-    compare(cfg, w, frames, off, ids, L0)
+    compare(cfg, w, frames, off, ids, L0, tol=6e-3)          # (0.8e-3 to 2.1e-3; a bias left out of one linear of a layer: 9.5e-3 and more)
 
 
 @pytest.mark.parametrize("hw,n,adapters,cap", [

@@ -19,4 +19,5 @@ pytestmark = pytest.mark.gpu
 def test_against_the_oracle(dtype, D, heads, Dm, hw, r, L0, compose):
     cfg, w, frames, off, ids = synth.make_small_case(11 + D + hw, dtype=dtype, targets=15, L=2, F=7, r=r, max_set=3, n_adapters=5, D=D, heads=heads, Dm=Dm,
                                                      hw=hw, patch=8)
-    compare(cfg, w, frames, off, ids, L0, compose=compose)
+    # bf16: 1.6e-3 to 2.9e-3; a bias left out of one linear of a layer moves the logits by 1.3e-2 and more
+    compare(cfg, w, frames, off, ids, L0, compose=compose, tol=8e-3 if dtype == synth.DT_BF16 else None)
