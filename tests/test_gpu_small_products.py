@@ -1,4 +1,4 @@
-"""Products between the few tiles whose contraction is split over the waves and the many of 128 x 128: tiles of 64 x 64 that share a ring."""
+"""Products of the isolated linear: the few that run in one launch with the shrink, those whose contraction is split over the waves, and tiles that share a ring."""
 import numpy as np
 import pytest
 import torch
@@ -10,11 +10,14 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n_xblocks,T,K,N,r,per_block", [
-    (1, 197, 768, 3072, 8, 1),       # 336 tiles of 32 x 64: the first side of the rule
-    (5, 197, 768, 768, 16, 2),       # row tiles across blocks, two branches each
-    (31, 17, 768, 1000, 20, 2),      # a block ends inside nearly every tile; columns that fill no tile; a rank of two steps
-    (2, 131, 1088, 2048, 8, 1),      # above a contraction of 1024, more tiles of 64 x 64 than fit: shared ring
-    (2, 131, 1088, 1600, 8, 1),      # and few enough: split contraction
+    (1, 197, 768, 3072, 8, 1),       # 192 tiles of 64 x 64: one launch with the shrink
+    (5, 197, 768, 768, 16, 2),       # 240: the same, two branches each
+    (2, 131, 1088, 2048, 8, 1),      # 192
+    (2, 131, 1088, 1600, 8, 1),      # 150
+    (31, 17, 768, 1000, 20, 2),      # 272 tiles of 32 x 64: shared ring; a block ends inside nearly every tile; columns that fill no tile; two rank steps
+    (28, 17, 768, 1000, 20, 2),      # 240: split contraction
+    (31, 17, 1088, 1000, 8, 1),      # above a contraction of 1024, few enough tiles of 64 x 64: split contraction
+    (64, 17, 1088, 1032, 8, 2),      # more of them: shared ring
     (4, 128, 512, 2112, 4, 1),       # the shortest contraction of the rule, whole row tiles
 ])
 def test_against_the_oracle(n_xblocks, T, K, N, r, per_block):
@@ -24,10 +27,14 @@ def test_against_the_oracle(n_xblocks, T, K, N, r, per_block):
     y = torch.full((R, T, N), float("nan"), dtype=torch.bfloat16, device="cuda")
     status = torch.zeros(1, dtype=torch.int32, device="cuda")
     ws = torch.empty(binding.poly_lora_linear_workspace_bytes(n_xblocks, T, r, R, synth.DT_BF16), dtype=torch.uint8, device="cuda")
+    binding.poly_profile_begin(8)
     binding.poly_lora_linear(up(case["X"]), up(case["W"].T), up(case["bias"], torch.float32), up(np.swapaxes(case["A"], 1, 2)),
                              up(np.swapaxes(case["B"], 1, 2)), 0.75, up(case["row_offsets"], torch.int32), up(case["adapter_ids"], torch.int32), R, y, ws,
                              dev_status=status)
     torch.cuda.synchronize()
+    prof = binding.poly_profile_end()
+    one = n_xblocks * -(-T // 64) * -(-N // 64) <= 256 and n_xblocks + R <= 1024
+    assert prof["shrink"]["launches"] == (0 if one else 1) and prof["gemm"]["launches"] == 1
     want = oracle.lora_linear(case, s=0.75)
     assert int(status.item()) == 0
     # bf16 (8 bits) rounds the output and every rank of the shrink output by at most 2^-8 of itself; sums are fp32
@@ -41,10 +48,11 @@ def test_against_the_oracle(n_xblocks, T, K, N, r, per_block):
 
 
 @pytest.mark.parametrize("n_xblocks,T,K,N,r,per_block", [
-    (9, 197, 192, 576, 8, 2),        # 128 x 64, two branches: the expand's operands fetched ahead
-    (40, 37, 192, 200, 20, 3),       # blocks shorter than a wave's rows, columns that fill no tile, a rank of two steps
-    (24, 131, 192, 1000, 8, 1),      # 128 x 128 on eight waves, the last column tile cut short
-    (30, 64, 320, 1032, 16, 2),      # as many rows as a wave's region: two blocks in it
+    (9, 197, 192, 576, 8, 2),        # two branches: the expand's operands fetched ahead
+    (40, 37, 192, 200, 20, 3),       # 160 tiles of 64 x 64: one launch; blocks shorter than a wave's rows, columns that fill no tile, two rank steps
+    (70, 37, 192, 200, 20, 3),       # 280: two
+    (24, 131, 192, 1000, 8, 1),      # the last column tile cut short
+    (30, 64, 320, 1032, 16, 2),      # as many rows as a taller wave's region: two blocks in it
 ])
 def test_tiles_of_a_wave_per_32_rows(n_xblocks, T, K, N, r, per_block):
     test_against_the_oracle(n_xblocks, T, K, N, r, per_block)
@@ -61,17 +69,17 @@ def test_short_contractions(n_xblocks, T, K, N, r, per_block):
 
 @pytest.mark.parametrize("n_xblocks,T,K,N,r,per_block", [
     (128, 197, 768, 2304, 16, 1),    # tiles of 256 x 256
-    (133, 197, 1536, 768, 16, 1),    # tiles of 256 x 128, three stages
+    (133, 197, 1536, 768, 16, 1),    # 128 x 128, a long contraction
 ])
 def test_large_tiles(n_xblocks, T, K, N, r, per_block):
     test_against_the_oracle(n_xblocks, T, K, N, r, per_block)
 
 
 @pytest.mark.parametrize("n_xblocks,T,K,N,r,per_block", [
-    (60, 17, 192, 576, 4, 1),        # fewer than 256 tiles of 128 x 64: 64 x 64
-    (256, 41, 192, 200, 20, 2),      # fewer than 768: 128 x 64 on waves of 64 x 32
-    (256, 50, 192, 1032, 20, 1),     # 384 tiles of 128 x 128 and more: waves of 64 x 64
-    (600, 101, 192, 200, 4, 1),      # neither
+    (60, 17, 192, 576, 4, 1),        # 64 x 64
+    (256, 41, 192, 200, 20, 2),      # 128 x 128, column tiles cut short
+    (256, 50, 192, 1032, 20, 1),
+    (600, 101, 192, 200, 4, 1),      # a rank that fills no load
 ])
 def test_ranks_that_are_not_fetched_ahead(n_xblocks, T, K, N, r, per_block):
     test_against_the_oracle(n_xblocks, T, K, N, r, per_block)
