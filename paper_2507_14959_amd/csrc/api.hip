@@ -303,6 +303,21 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         return POLY_OK;
     };
 
+    // What the row-wise part of layer l is: whether one launch does it, whether the next layer's qkv linear is in it (that layer works on the same blocks
+    // and its linear needs no GEMM path for summed terms), with adapters, and the waves of rowreg.hip, 0: tiles of rowlayer.hip
+    struct RowPart { bool fits, qkv, lora_q; int waves; };
+    auto row_part = [&](int l) -> RowPart {
+        const bool lora_on = l >= m->L0 && R > 0, summed = sum && l >= m->L0, branch = !sum && l >= m->L0;
+        auto use = [&](int t) { return lora_on && (m->targets & (1 << t)); };
+        if (dt != POLY_BF16 || use(2) || use(3) || (summed && (use(0) || use(1))) || !rowlayer_supported(D, Dm, use(0) || use(1) ? m->r : 0)) return {};
+        const int ln = l + 1;
+        const bool qkv_lora = ln >= m->L0 && R > 0 && (m->targets & 1);
+        RowPart p = {true, ln < m->L && (sum || ln != m->L0) && !(sum && qkv_lora), false, 0};
+        p.lora_q = p.qkv && qkv_lora;
+        p.waves = rowreg_waves(T, D, Dm, use(1) || p.lora_q ? m->r : 0, use(1) || p.lora_q || (branch && l == m->L0), branch ? (F + R) / 2 : F);
+        return p;
+    };
+    bool x_fragments = false;                  // the residual stream lies in the order of rowreg.hip: between two of its launches only
     bool qkv_done = false;                     // the qkv linear of layer l was computed by layer l - 1's row kernel
     for (int l = 0; l < m->L; ++l) {
         if (l == 0 && w.fl_cnt[0]) {
@@ -365,6 +380,8 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         const void *Wqkv = (const char *)base->qkv_w + es * (size_t)l * 3 * D * D, *Wproj = (const char *)base->proj_w + es * (size_t)l * D * D;
         const void *Wfc1 = (const char *)base->fc1_w + es * (size_t)l * Dm * D;
 
+        const RowPart rows = row_part(l);
+
         // ---- attention half
         if (qkv_done) {
             qkv_done = false;
@@ -377,7 +394,8 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
             a.Wqt = (const bf16_t *)Wqkv; a.bq = base->qkv_b + (size_t)l * 3 * D;
             if (use(0)) { a.Aqt = (const bf16_t *)lora_ptr(lora->At[0], 0, D, 3 * D, true); a.Bqt = (const bf16_t *)lora_ptr(lora->Bt[0], 0, D, 3 * D, false); }
             a.qkv_out = (bf16_t *)w.qkv;
-            POLY_TRY(launch_rowlayer(a, st));
+            const int waves = rowreg_waves(T, D, Dm, use(0) ? m->r : 0, use(0) || fan, n_out_dev == R_dev ? pairs : n_out);
+            POLY_TRY(waves ? launch_rowreg(a, waves, st) : launch_rowlayer(a, st));
         } else if (fused(0)) {
             POLY_TRY(rowlin(0, x_in, base->ln1_g + (size_t)l * D, base->ln1_b + (size_t)l * D, nullptr, fan_map, Wqkv,
                             base->qkv_b + (size_t)l * 3 * D, 3 * D, EPI_STORE, w.qkv, nullptr, nullptr));
@@ -397,10 +415,10 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
             POLY_TRY(launch_gemm(g, {!branch, pairs}, dt, st));
         }
         // (as a rule a frame has an adapter, so that there are about as many row-blocks as frames or more)
-        POLY_TRY(launch_attention(w.qkv, w.o, T, D, m->heads, n_out, n_out_dev, n_out < F ? n_out : F, dt, st));
+        POLY_TRY(launch_attention(w.qkv, w.o, T, D, m->heads, n_out, n_out_dev, n_out < F ? n_out : F, dt, rows.waves > 0, st));
         // narrow models without adapters on fc1 / fc2: everything row-wise of the layer in one launch -- proj with its
         // residual, the MLP half, and the qkv linear of the next layer when that layer works on the same blocks
-        if (dt == POLY_BF16 && !use(2) && !use(3) && !(summed && (use(0) || use(1))) && rowlayer_supported(D, Dm, (use(0) || use(1)) ? m->r : 0)) {
+        if (rows.fits) {
             RowLayerArgs a = {};
             a.T = T; a.D = D; a.Dm = Dm; a.n_out = n_out; a.n_out_dev = n_out_dev;
             const bool adapters = lora_on && !sum && (use(1) || (m->targets & 1));
@@ -412,12 +430,11 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
             a.W1t = (const bf16_t *)Wfc1; a.b1 = base->fc1_b + (size_t)l * Dm;
             a.W2t = (const bf16_t *)((const char *)base->fc2_w + es * (size_t)l * D * Dm); a.b2 = base->fc2_b + (size_t)l * D;
             a.x_out = x_out;
-            const int ln = l + 1;              // next layer: same blocks unless it is the one where frames fan out
-            const bool next_qkv_summed = sum && ln >= m->L0 && R > 0 && (m->targets & 1);   // that linear needs the GEMM path
-            if (ln < m->L && (sum || ln != m->L0) && !next_qkv_summed) {
+            const int ln = l + 1;
+            if (rows.qkv) {
                 a.lnq_g = base->ln1_g + (size_t)ln * D; a.lnq_b = base->ln1_b + (size_t)ln * D;
                 a.Wqt = (const bf16_t *)((const char *)base->qkv_w + es * (size_t)ln * 3 * D * D); a.bq = base->qkv_b + (size_t)ln * 3 * D;
-                if (!sum && ln >= m->L0 && R > 0 && (m->targets & 1)) {
+                if (rows.lora_q) {
                     const size_t per_layer = (size_t)m->n_adapters * m->r * D;
                     a.Aqt = (const bf16_t *)((const char *)lora->At[0] + es * per_layer * (size_t)(ln - m->L0));
                     a.Bqt = (const bf16_t *)((const char *)lora->Bt[0] + es * per_layer * 3 * (size_t)(ln - m->L0));
@@ -425,7 +442,10 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
                 a.qkv_out = (bf16_t *)w.qkv;
                 qkv_done = true;
             }
-            POLY_TRY(launch_rowlayer(a, st));
+            // (rows in the order of rowreg.hip end up to 31 rows past the buffer's last: what lies there, the start of xb, u or h, is in no use then)
+            a.res_fragments = x_fragments;
+            x_fragments = a.out_fragments = rows.waves && rows.qkv && row_part(ln).waves;
+            POLY_TRY(rows.waves ? launch_rowreg(a, rows.waves, st) : launch_rowlayer(a, st));
             continue;
         }
         if (fused(1)) {

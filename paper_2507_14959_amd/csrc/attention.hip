@@ -16,7 +16,7 @@ constexpr float LOG2E = 1.4426950408889634f;
 // where there are more workgroups than CUs half of the waves leave once K and V are in LDS, so that the next workgroup's fit beside the others.
 constexpr bool att_shares(int nkt, int w) { return nkt == w && nkt >= 6; }
 
-template <int NKT, int W>  // 32-key tiles: T <= 32 * NKT; waves, each takes the query tiles w, w + live, ..
+template <int NKT, int W, bool FRAGMENTS>  // 32-key tiles: T <= 32 * NKT; waves, each takes the query tiles w, w + live, ..
 __global__ __launch_bounds__(64 * W, att_shares(NKT, W) ? 3 : 2 * W <= 8 ? 2 : 1) void attn_bf16_kernel(const bf16_t *qkv, bf16_t *out, int T, int D, int heads, int n_blocks,
                                                         const int *n_blocks_dev)
 {
@@ -177,12 +177,22 @@ __global__ __launch_bounds__(64 * W, att_shares(NKT, W) ? 3 : 2 * W <= 8 ? 2 : 1
                     *(bf16x4 *)(ot + lm * OS + dt * 32 - c0 + 8 * g + 4 * lh) = w;
                 }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");    // the tile is private to the wave: no barrier
-            constexpr int LR = OC / 8, RI = 64 / LR;              // lanes per row, rows per instruction
+            if constexpr (FRAGMENTS) {                            // for rowreg.hip: 16 columns of 32 rows an instruction, 512 bytes per half of them
+                const int row = qs * 32 + lm;
+                const size_t flat = (size_t)b * T + row;
 #pragma unroll
-            for (int i = 0; i < 32 / RI; ++i) {
-                const int row = i * RI + lane / LR, qrow = qs * 32 + row;
-                const bf16x8 v = *(const bf16x8 *)(ot + row * OS + lane % LR * 8);
-                if (qrow < T) *(bf16x8 *)(out + ((size_t)b * T + qrow) * D + hd * 64 + c0 + lane % LR * 8) = v;
+                for (int i = 0; i < OC / 16; ++i) {
+                    const bf16x8 v = *(const bf16x8 *)(ot + lm * OS + i * 16 + lh * 8);
+                    if (row < T) *(bf16x8 *)(out + (flat >> 5) * (32 * D) + (hd * 4 + c0 / 16 + i) * 512 + (lh * 32 + (flat & 31)) * 8) = v;
+                }
+            } else {
+                constexpr int LR = OC / 8, RI = 64 / LR;          // lanes per row, rows per instruction
+#pragma unroll
+                for (int i = 0; i < 32 / RI; ++i) {
+                    const int row = i * RI + lane / LR, qrow = qs * 32 + row;
+                    const bf16x8 v = *(const bf16x8 *)(ot + row * OS + lane % LR * 8);
+                    if (qrow < T) *(bf16x8 *)(out + ((size_t)b * T + qrow) * D + hd * 64 + c0 + lane % LR * 8) = v;
+                }
             }
         }
     }
@@ -279,12 +289,12 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *qkv, float *
     }
 }
 
-template <int NKT, int W = NKT>
+template <int NKT, int W, bool FRAGMENTS>
 int launch_bf16(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, hipStream_t st)
 {
     constexpr int TKP = NKT * 32;
     constexpr int LDS = (TKP * 72 + 64 * (TKP + 8) + W * 32 * (att_shares(NKT, W) ? 40 : 72)) * 2;
-    auto kern = attn_bf16_kernel<NKT, W>;
+    auto kern = attn_bf16_kernel<NKT, W, FRAGMENTS>;
     if (LDS > 64 * 1024) {
         static bool attr_set = false;   // raising the dynamic LDS limit is a per-kernel, process-wide setting
         if (!attr_set) {
@@ -296,14 +306,19 @@ int launch_bf16(const void *qkv, void *out, int T, int D, int heads, int n_block
                       heads, n_blocks, n_blocks_dev);
     return POLY_OK;
 }
+template <int NKT, int W = NKT>
+int launch_bf16(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, bool fragments, hipStream_t st)
+{
+    return (fragments ? launch_bf16<NKT, W, true> : launch_bf16<NKT, W, false>)(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st);
+}
 
 }  // namespace
 
 int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, int n_usual, int dtype,
-                     hipStream_t st)
+                     bool fragments, hipStream_t st)
 {
     if (n_blocks == 0) return POLY_OK;
-    if (D != heads * 64) return POLY_EINVAL;
+    if (D != heads * 64 || (fragments && dtype != POLY_BF16)) return POLY_EINVAL;
     if (dtype == POLY_BF16) {
         // From 161 keys on, two query tiles per wave and two workgroups per CU, one loading while the other computes, are faster where there are more
         // workgroups than CUs, and slower below.  Half the waves from the start where the usual count says so, else the form that looks at the true
@@ -311,13 +326,13 @@ int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_
         // tokens: 90 workgroups 7.7 / 9.0 / 7.7, 192 8.3 / 9.8 / 8.4, 255 9.6 / 10.9 / 9.7, 270 15.7 / 14.5 / 14.8, 600 - / 22.0 / 22.7, 999 32.3 / 27.6 / 28.9.
         const bool many = (long)n_usual * heads > 256;
         switch ((T + 31) / 32) {
-        case 1: if (launch_bf16<1>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
-        case 2: if (launch_bf16<2>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
-        case 3: if (launch_bf16<3>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
-        case 4: if (launch_bf16<4>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
-        case 5: if (launch_bf16<5>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
-        case 6: if ((many ? launch_bf16<6, 3> : launch_bf16<6>)(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
-        case 7: if ((many ? launch_bf16<7, 4> : launch_bf16<7>)(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st) != POLY_OK) return POLY_EHIP; break;
+        case 1: if (launch_bf16<1>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
+        case 2: if (launch_bf16<2>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
+        case 3: if (launch_bf16<3>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
+        case 4: if (launch_bf16<4>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
+        case 5: if (launch_bf16<5>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
+        case 6: if ((many ? launch_bf16<6, 3> : launch_bf16<6>)(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
+        case 7: if ((many ? launch_bf16<7, 4> : launch_bf16<7>)(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
         default: return POLY_EINVAL;  // bf16 attention holds all keys of a block in 64 KB of LDS: T <= 224
         }
     } else {

@@ -35,19 +35,6 @@ namespace {
 // W panel at a time (it stays in that XCD's 4 MB L2 instead of all of W streaming past every row tile) and the XCDs
 // finish together (a ninth of a round more on one XCD is a whole round more for the kernel).
 
-// 16 bytes per lane from uniform base + byte offset to lds_byte_addr + 16 lane; nothing where go <= 0, but counted as a load all the same.  Inline
-// assembly: the compiler would make LDS reads wait for loads it knows of, and a branch around them costs the reads' counted waits.
-// (All lanes of the wave are active.)
-// Every wait of a ring rests on this: a load with EXEC = 0 goes through vmcnt in its place in the order.  Were it skipped, the waits past the last k-tile
-// would let loads that move something stay in flight.  tests/test_product_tiles.py has contractions of a single k-tile on two and four stages, where all
-// loads behind those of the first wait are off; three stages are taken from a contraction of 512 on, where the last two waits rest on it.
-__device__ __forceinline__ void glds16_if(const void *sbase, unsigned voff, unsigned lds_byte_addr, int go)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_cmp_gt_i32 %3, 0\n\ts_cselect_b64 exec, -1, 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1" ::"s"(
-                     lds_byte_addr),
-                 "v"(voff), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(go))
-                 : "memory", "m0", "scc");
-}
 template <typename F, int... I> __device__ __forceinline__ void static_for_each(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>()), ...); }
 template <int N, typename F> __device__ __forceinline__ void static_for(F f) { static_for_each(f, std::make_integer_sequence<int, N>()); }
 

@@ -277,9 +277,17 @@ struct RowLayerArgs {
     const float *bq;                 // [3 D]
     const bf16_t *Aqt, *Bqt;         // [n_adapters][r][D], [n_adapters][3 D][r]; null = no adapters on qkv
     bf16_t *qkv_out;                 // [n_out][T][3 D]
+    bool res_fragments, out_fragments;   // launch_rowreg only: res / x_out lie in its order (below); o always does there
 };
 bool rowlayer_supported(int D, int Dm, int r);
 int launch_rowlayer(const RowLayerArgs &a, hipStream_t st);
+// The same on tiles of 32 rows per wave, all of a wave's rows in its registers (rowreg.hip): waves per workgroup where `blocks` blocks of T rows are
+// that many that it is faster, 0 where they are not or it does not apply.  r: rank of the adapters in the launch, 0 without; by_block: adapters or a map.
+// Its order, of o and where the flags say so of the residual stream, on the rows of all blocks as one run: groups of 32 rows; in a group, of a 16-bit
+// value, [column / 16][column / 8 % 2][row][column % 8], of a float [column / 8][column / 4 % 2][row][column % 4].  The last group of a buffer may reach
+// 31 rows past the last row.
+int rowreg_waves(int T, int D, int Dm, int r, bool by_block, int blocks);
+int launch_rowreg(const RowLayerArgs &a, int waves, hipStream_t st);
 int launch_rowlin(const RowLinArgs &a, hipStream_t st);
 
 // A run of whole layers on few blocks in one launch (flow.hip); bf16, D <= 192.  Weight pointers are those of the first layer of the
@@ -330,9 +338,10 @@ int launch_shrink_csr(const void *X, int T, int K, const void *At, int r, int RP
                       int F, int R_cap, int n_adapters, PolyMeta *meta, int32_t *frame_of_row, int32_t *adapter_of_row, int32_t *dev_status, void *S,
                       hipStream_t st);
 
-// softmax attention of every (block, head); qkv elt [n*T][3D] -> out elt [n*T][D].  n_usual: blocks that a call of n_blocks at most has as a rule (<= n_blocks)
+// softmax attention of every (block, head); qkv elt [n*T][3D] -> out elt [n*T][D].  n_usual: blocks that a call of n_blocks at most has as a rule (<= n_blocks);
+// fragments (bf16): out in the order that launch_rowreg takes
 int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, int n_usual,
-                     int dtype, hipStream_t st);
+                     int dtype, bool fragments, hipStream_t st);
 
 // poly_select with what the lagged loop needs right behind it done in the same launch (select.hip): meta != null: the row maps and
 // the bookkeeping words of the CSR arrays just written (nothing is selected and state and carry stay where meta->stalled is set); carry != null: K floats carry_src -> carry

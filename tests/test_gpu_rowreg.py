@@ -1,0 +1,77 @@
+"""Many rows of a model 192 wide: tiles of 128 and 256 rows in registers (rowreg.hip) where they, their waves and the blocks in them end."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2507_14959_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+UNIQUE = 12                      # different frames; the call repeats them, a row depends on its frame and adapter only
+BOUND = 6e-3                     # as for the tiles of 64 rows (test_row_layer.py); 1.0e-3 to 2.5e-3 here
+
+
+def _case(F, hw, patch, Dm, r, targets, per_frame, L=3, seed=0):
+    cfg, w, frames, _, _ = synth.make_small_case(900 + Dm + hw + r + seed, dtype=synth.DT_BF16, targets=targets, L=L, F=UNIQUE, r=r, n_adapters=5, D=192, heads=3,
+                                                 Dm=Dm, hw=hw, patch=patch)
+    rng = np.random.default_rng(Dm + r)
+    sets = [sorted(rng.choice(5, size=1 + f % per_frame, replace=False)) for f in range(UNIQUE)]
+    which = np.arange(F) % UNIQUE
+    off, ids = synth.sets_to_csr([sets[f] for f in which])
+    rows = np.concatenate([[sum(map(len, sets[:f])) + i for i in range(len(sets[f]))] for f in which]).astype(int)
+    return cfg, w, frames, sets, frames[which], off, ids, rows
+
+
+def _want(cfg, w, frames, sets, rows, L0):
+    off, ids = synth.sets_to_csr(sets)
+    return oracle.forward(cfg, w, frames, off, ids, L0=L0)["logits"][rows]
+
+
+@pytest.mark.parametrize("F,hw,patch,Dm,r,targets,per_frame,spare", [
+    (460, 48, 8, 768, 8, 3, 1, 0),        # 37 tokens, 128-row tiles, 28 rows in the last wave
+    (300, 48, 8, 128, 16, 3, 2, 0),       # the count only on the device; the shortest hidden width
+    (460, 48, 8, 192, 16, 1, 1, 60),      # room for more blocks than there are; adapters on qkv only
+    (520, 48, 8, 320, 8, 2, 1, 0),        # on proj only
+    (900, 48, 8, 256, 8, 3, 1, 0),        # 256-row tiles, 20 rows in the last of them: waves without any
+    (700, 40, 8, 192, 16, 3, 1, 0),       # 26 tokens: by itself a block shorter than a wave's rows keeps the tiles of 64 rows where adapters differ
+    (100, 112, 8, 768, 16, 3, 2, 0),      # 197 tokens
+])
+@pytest.mark.parametrize("L0", [0, 1, 3])
+def test_against_the_oracle(F, hw, patch, Dm, r, targets, per_frame, spare, L0):
+    cfg, w, frames, sets, many, off, ids, rows = _case(F, hw, patch, Dm, r, targets, per_frame)
+    model = binding.DeviceModel(cfg, w, L0=L0)
+    binding.poly_profile_begin(400)
+    try:
+        got = binding.run_forward(model, many, off, ids, R_cap=len(ids) + spare)
+    finally:
+        prof = binding.poly_profile_end()
+    assert prof["attention"]["launches"] == 3 and prof["layernorm"]["launches"] == 0       # layer by layer, everything between two attentions in a launch
+    logits = got["logits"][:len(ids)]
+    again = binding.run_forward(model, many, off, ids, R_cap=len(ids) + spare)["logits"][:len(ids)]
+    assert got["status"] == 0 and np.array_equal(logits, again)
+    assert np.abs(logits - _want(cfg, w, frames, sets, rows, L0)).max() < BOUND
+    if L0 == 0 or F * cfg.T > 16384:                       # (shared layers on tiles of 64 rows: the two halves of a tile add in another order)
+        first = np.unique(rows, return_index=True)[1]
+        assert np.array_equal(logits, logits[first[rows]])  # wherever in a tile a block lies
+
+
+def test_summed_shared_layers():
+    """Terms summed on a frame's block from layer 2 on: up to there its rows run here, and leave in the order that the GEMM path reads."""
+    cfg, w, frames, sets, many, off, ids, rows = _case(480, 48, 8, 256, 8, 3, 2)
+    got = binding.run_forward(binding.DeviceModel(cfg, w, L0=2, compose="sum"), many, off, ids)
+    o, i = synth.sets_to_csr(sets)
+    assert got["status"] == 0
+    assert np.abs(got["logits"] - oracle.forward(cfg, w, frames, o, i, L0=2, compose="sum")["logits"][rows]).max() < BOUND
+
+
+def test_an_adapter_stays_with_its_blocks():
+    """Two blocks in a wave's rows: infinities of one block's adapter do not reach the other's rows."""
+    cfg, w, frames, sets, many, off, ids, rows = _case(460, 48, 8, 192, 8, 3, 1)
+    clean = binding.run_forward(binding.DeviceModel(cfg, w, L0=0), many, off, ids)["logits"]
+    bad = dict(w, B_qkv=np.array(w["B_qkv"]), A_proj=np.array(w["A_proj"]))
+    bad["B_qkv"][:, 3] = np.inf
+    bad["A_proj"][:, 3] = -np.inf
+    got = binding.run_forward(binding.DeviceModel(cfg, bad, L0=0), many, off, ids)["logits"]
+    other = np.asarray(ids) != 3
+    assert 0 < other.sum() < len(ids)
+    assert np.array_equal(got[other], clean[other]) and not np.isfinite(got[~other]).any()
