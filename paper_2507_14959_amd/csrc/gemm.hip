@@ -38,16 +38,15 @@ namespace {
 template <typename F, int... I> __device__ __forceinline__ void static_for_each(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>()), ...); }
 template <int N, typename F> __device__ __forceinline__ void static_for(F f) { static_for_each(f, std::make_integer_sequence<int, N>()); }
 
-// (row tile, column tile) of workgroup `bid`; false if this workgroup has nothing to do.  All tiles in the order (panel of
-// `panel` column tiles, row tile, column tile inside the panel) are cut into eight equal runs, one per XCD: a run covers one
-// or two W panels and a contiguous range of row tiles, and no XCD has more than one tile more than another.
-__device__ __forceinline__ bool xcd_tile(int bid, int tiles_mtot, int tiles_n, int panel, int &mt, int &tn)
+// The j-th of the tiles of one of eight runs: all tiles in the order (panel of `panel` column tiles, row tile, column tile inside the panel) are cut
+// into eight equal runs, one per XCD: a run covers one or two W panels and a contiguous range of row tiles, and no XCD has more than one tile more than
+// another.  False, and j less the run's tiles, if the run has no such tile.
+__device__ __forceinline__ bool xcd_tile(int xcd, int &j, int tiles_mtot, int tiles_n, int panel, int &mt, int &tn)
 {
-    const int xcd = bid & 7, j = bid >> 3;
     const long total = (long)tiles_mtot * tiles_n;
     const long lo = total * xcd / 8, hi = total * (xcd + 1) / 8;
     const long L = lo + j;
-    if (L >= hi) return false;
+    if (L >= hi) { j -= (int)(hi - lo); return false; }
     const long full = (long)tiles_mtot * panel;            // tiles per full panel
     const int pn = (int)(L / full);
     const int rem = (int)(L - pn * full);
@@ -63,9 +62,18 @@ __device__ __forceinline__ bool xcd_tile(int bid, int tiles_mtot, int tiles_n, i
 // 1, 2 = row-wise for bf16 output (two column subtiles per wave): 2 when the host knows that a wave's region touches at most two
 // input blocks and every output block has one low-rank term of at most 16 ranks (all operands of a pass prefetched), 1 otherwise;
 // 3 = the same conditions and prefetching as 2 for fp32 output with a residual (no position rows), staged 32 rows at a time.
-template <int BM, int BN, int WM, int WN, int NS, int EK>
-__global__ __launch_bounds__(64 * WM * WN, (BM * BN >= 256 * 256 || NS * (BM + BN) * 128 > 80 * 1024) ? 1 : 2)
-void gemm_bf16_dma_kernel(const GemmArgs g, int tiles_m, int tiles_n)
+// In a kernel of two tiles the compiler merges their loads and loses sight of the bases being uniform.
+template <bool TWO, typename T> __device__ __forceinline__ const T *uniform(const T *p)
+{
+    if (!TWO) return p;
+    const uintptr_t v = (uintptr_t)p;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+    return (const T *)((uintptr_t)hi << 32 | lo);
+}
+
+// One tile (TWO: the kernel has one of another size too): rows t0 .. of block xb (of the run of rows over all blocks, of which Tlim exist: xb = 0), columns n0 ..
+template <int BM, int BN, int WM, int WN, int NS, int EK, bool TWO>
+__device__ __forceinline__ void dma_tile(const GemmArgs &g, const bool flat, const int Tlim, const int xb, const int t0, const int n0)
 {
     constexpr int BK = 64, NW = WM * WN;
     constexpr int MI = BM / WM / 32, NJ = BN / WN / 32;   // 32 x 32 subtiles per wave
@@ -73,21 +81,9 @@ void gemm_bf16_dma_kernel(const GemmArgs g, int tiles_m, int tiles_n)
     constexpr int NC = NJ * 8;                             // 16-byte chunks per staged fp32 row (NJ*32 columns)
     constexpr int AG = BM / 8 / NW, BG = BN / 8 / NW;      // 8-row groups (1 KB each) per wave and stage
     constexpr int NLD = AG + BG;                           // loads per wave and stage
-    constexpr int PANEL = 768 / BN;                        // column tiles per L2 panel (1.2 MB of W at K = 768)
     static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && (NS - 1) * NLD <= 63, "tile / wave layout");
     static_assert(NW * 32 * NC * 16 <= NS * STAGE_EL * 2, "staging must fit in the tile ring");
     extern __shared__ __attribute__((aligned(16))) bf16_t dsmem[];
-
-    // The eight runs are cut from the tiles that exist: the grid is sized for the caller's bound on the blocks, which can be
-    // half as many again as the true count, and the tiles past it would all fall on the last XCDs (config 3 with room for 3
-    // adapters on each of 64 frames: five of eight XCDs busy, 178 us per qkv or fc1 launch instead of 131).  The workgroups left over exit at once.
-    const bool flat = g.Tb > 0;                            // one run of rows over all blocks: xb = 0, t0 = first row of the tile
-    const int n_bound = flat ? g.nb : g.n_in;
-    const int n_true = g.n_in_dev ? min(*g.n_in_dev, n_bound) : n_bound;
-    const int Tlim = flat ? n_true * g.Tb : g.T;           // rows that exist
-    int mt, tn;
-    if (!xcd_tile(blockIdx.x, flat ? (Tlim + BM - 1) / BM : n_true * tiles_m, tiles_n, PANEL, mt, tn)) return;
-    const int xb = mt / tiles_m, t0 = (mt - xb * tiles_m) * BM, n0 = tn * BN;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN, lm = lane & 31, lh = lane >> 5;
@@ -114,8 +110,8 @@ void gemm_bf16_dma_kernel(const GemmArgs g, int tiles_m, int tiles_n)
         constexpr int l = decltype(load)::value, i = l < AG ? l : l - AG;       // k-tile it moves nothing, so that the waits count the same
         const int go = nk - kt;                                                 // loads everywhere
         const unsigned st = ring + s * (STAGE_EL * 2);
-        if constexpr (l < AG) glds16_if(A + (size_t)kt * BK, ga[i], st + (wave * AG + i) * 1024, go);
-        else glds16_if(Wt + (size_t)kt * BK, gb[i], st + A_EL * 2 + (wave * BG + i) * 1024, go);
+        if constexpr (l < AG) glds16_if(uniform<TWO>(A + (size_t)kt * BK), ga[i], st + (wave * AG + i) * 1024, go);
+        else glds16_if(uniform<TWO>(Wt + (size_t)kt * BK), gb[i], st + A_EL * 2 + (wave * BG + i) * 1024, go);
     };
 
     // Row-wise epilogue (two column subtiles per wave, bf16 output): the accumulators start from the bias, so no output block
@@ -195,7 +191,7 @@ void gemm_bf16_dma_kernel(const GemmArgs g, int tiles_m, int tiles_n)
         R0 = t0 + wm * RROWS; Rend = min(R0 + RROWS, Tlim);
         if (R0 < Rend) {
             Tblk = flat ? g.Tb : g.T;                         // rows of a block: stride of S and of the output blocks
-            bbA = flat ? R0 / Tblk : xb; bbZ = flat ? (Rend - 1) / Tblk : xb;
+            bbA = flat ? __builtin_amdgcn_readfirstlane(R0 / Tblk) : xb; bbZ = flat ? __builtin_amdgcn_readfirstlane((Rend - 1) / Tblk) : xb;
             baseA = flat ? bbA * Tblk : 0; tB = baseA + Tblk;  // first row (tile coordinates) of blocks bbA and bbA + 1
             two = bbZ - bbA <= 1; hasB = bbZ > bbA;
             // fan-out of the region's first and last input block (with more than two blocks: looked up per block in the epilogue)
@@ -414,23 +410,32 @@ void gemm_bf16_dma_kernel(const GemmArgs g, int tiles_m, int tiles_n)
                     const int obA = oA0 + p < oA1 ? oA0 + p : -1, obB = (hasB && oB0 + p < oB1) ? oB0 + p : -1;
                     const int rbA = (g.res && obA >= 0) ? (g.res_block_of_out ? g.res_block_of_out[obA] : obA) : 0;
                     const int rbB = (g.res && obB >= 0) ? (g.res_block_of_out ? g.res_block_of_out[obB] : obB) : 0;
+                    // where row 0 of the tile's coordinates would lie in block A and in block B; rows [lo, lo + span) are stored
+                    auto row0 = [&](long blk, int base) { return (blk * g.Tout + g.t_off - base) * g.N; };
+                    const long rA = row0(rbA, baseA), rB = row0(rbB, tB), wA = row0(max(obA, 0), baseA), wB = row0(max(obB, 0), tB);
+                    const int lo = obA >= 0 ? R0 : tB, hi = obB >= 0 ? Rend : min(Rend, tB);
+                    const unsigned span = col4_ok ? max(hi - lo, 0) : 0;
+                    int trow0 = R0 + rrow;
+                    asm volatile("" : "+v"(trow0));           // (or the rows' offsets are worked out ahead of the passes and kept)
+                    constexpr int RQ = MI > 2 ? 4 : 8;        // residual loads in flight (with four row subtiles per wave eight do not fit beside the accumulators)
 #pragma unroll
                     for (int i = 0; i < MI; ++i) {
                         const int tw = R0 + 32 * i;
                         if (tw >= Rend) break;
-                        f32x4 rv[8];
-                        int obq[8];
-                        long oq[8];
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) {
-                            const int t = min(tw + 4 * q + rrow, Rend - 1);
-                            const bool inB = t >= tB;
-                            const int trow = t - (inB ? tB : baseA);
-                            obq[q] = (tw + 4 * q + rrow < Rend) ? (inB ? obB : obA) : -1;
-                            oq[q] = ((long)max(obq[q], 0) * g.Tout + g.t_off + trow) * g.N;
+                        f32x4 rv[RQ];
+                        auto request_res = [&](int q) {
+                            const int t = min(trow0 + 32 * i + 4 * q, Rend - 1);
                             const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
-                            rv[q] = g.res ? *(const f32x4 *)(g.res + ((long)(inB ? rbB : rbA) * g.Tout + g.t_off + trow) * g.N + cfix) : z4;
-                        }
+                            rv[q % RQ] = g.res ? *(const f32x4 *)(g.res + (t >= tB ? rB : rA) + (long)t * g.N + cfix) : z4;
+                        };
+                        auto finish_row = [&](int q) {
+                            const int row = 4 * q + rrow, t = trow0 + 32 * i + 4 * q;
+                            const f32x4 v = *(const f32x4 *)(stg32 + row * RCOLS + ((rch ^ (row & 15)) << 2)) + rv[q % RQ];
+                            if ((unsigned)(t - lo) < span) *(f32x4 *)((float *)g.out + (t >= tB ? wB : wA) + (long)t * g.N + col4) = v;
+                        };
+#pragma unroll
+                        for (int q = 0; q < RQ; ++q) request_res(q);
+                        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                         for (int j = 0; j < NJ; ++j) {
                             const f32x16 cj = result(i, j, tw);
@@ -442,10 +447,11 @@ void gemm_bf16_dma_kernel(const GemmArgs g, int tiles_m, int tiles_n)
                         }
 #pragma unroll
                         for (int q = 0; q < 8; ++q) {
-                            const int row = 4 * q + rrow;
-                            const f32x4 v = *(const f32x4 *)(stg32 + row * RCOLS + ((rch ^ (row & 15)) << 2)) + rv[q];
-                            if (obq[q] >= 0 && col4_ok) *(f32x4 *)((float *)g.out + oq[q] + col4) = v;
+                            if (q == RQ) __builtin_amdgcn_sched_barrier(0);
+                            finish_row(q);
+                            if (q + RQ < 8) request_res(q + RQ);
                         }
+                        __builtin_amdgcn_sched_barrier(0);
                     }
                     kA = __builtin_amdgcn_readfirstlane(kAnv); kB = __builtin_amdgcn_readfirstlane(kBnv);
                     if (p + 1 < maxfan) {
@@ -668,31 +674,70 @@ void gemm_bf16_dma_kernel(const GemmArgs g, int tiles_m, int tiles_n)
     }
 }
 
+// TAIL: the rows past the full rounds on 128 x 128 tiles of the same eight waves, four stages of them in the large tiles' ring (gemm_tiles.h)
+template <int BM, int BN, int WM, int WN, int NS, int EK> struct DmaKernel {
+    static constexpr bool TAIL = EK > 0 && has_tail(BM, BN, EK == 3 ? EPI_RESID : EPI_STORE, true);
+    static constexpr int THREADS = 64 * WM * WN, RING = NS * (BM + BN) * 128, BIAS = EK > 0 ? BN * 4 : 0;
+    static constexpr int TAIL_LDS = TAIL ? 4 * (128 + 128) * 128 + 128 * 4 : 0;
+    static constexpr int LDS = RING + BIAS > TAIL_LDS ? RING + BIAS : TAIL_LDS;
+};
+
+template <int BM, int BN, int WM, int WN, int NS, int EK>
+__global__ __launch_bounds__(64 * WM * WN, (BM * BN >= 256 * 256 || NS * (BM + BN) * 128 > 80 * 1024) ? 1 : 2)
+void gemm_bf16_dma_kernel(const GemmArgs g, int tiles_m, int tiles_n)
+{
+    constexpr int PANEL = 768 / BN;                        // column tiles per L2 panel (1.2 MB of W at K = 768)
+    // The eight runs are cut from the tiles that exist: the grid is sized for the caller's bound on the blocks, which can be
+    // half as many again as the true count, and the tiles past it would all fall on the last XCDs (config 3 with room for 3
+    // adapters on each of 64 frames: five of eight XCDs busy, 178 us per qkv or fc1 launch instead of 131).  The workgroups left over exit at once.
+    const bool flat = g.Tb > 0;                            // one run of rows over all blocks: xb = 0, t0 = first row of the tile
+    const int n_bound = flat ? g.nb : g.n_in;
+    const int n_true = g.n_in_dev ? __builtin_amdgcn_readfirstlane(min(*g.n_in_dev, n_bound)) : n_bound;
+    const int Tlim = flat ? n_true * g.Tb : g.T;           // rows that exist
+    const int xcd = blockIdx.x & 7;                        // workgroups are dealt round-robin to the XCDs
+    constexpr bool TAIL = DmaKernel<BM, BN, WM, WN, NS, EK>::TAIL;
+    const int large = TAIL && flat ? large_tile_rows(Tlim, g.N, BM, BN) : Tlim;
+    int j = blockIdx.x >> 3, mt, tn;
+    const bool has = xcd_tile(xcd, j, flat ? (large + BM - 1) / BM : n_true * tiles_m, tiles_n, PANEL, mt, tn);
+    if constexpr (TAIL) {
+        if (!has) {
+            if (large < Tlim && xcd_tile(xcd, j, (Tlim - large + 127) / 128, (g.N + 127) / 128, 6, mt, tn))
+                dma_tile<128, 128, 4, 2, 4, EK, true>(g, true, Tlim, 0, large + mt * 128, tn * 128);
+            return;
+        }
+    } else {
+        if (!has) return;
+    }
+    const int xb = mt / tiles_m;
+    dma_tile<BM, BN, WM, WN, NS, EK, TAIL>(g, flat, Tlim, xb, (mt - xb * tiles_m) * BM, tn * BN);
+}
+
 }  // namespace
 
 template <int BM, int BN, int WM, int WN, int NS> static void launch_dma(const GemmArgs &g, hipStream_t st);
 
-// grid of the XCD order: every XCD gets ceil(tiles / 8) workgroups
-static unsigned dma_grid(int tiles_mtot, int tiles_n)
-{
-    const long total = (long)tiles_mtot * tiles_n;
-    return (unsigned)((total + 7) / 8 * 8);
-}
-
 template <int BM, int BN, int WM, int WN, int NS, int EK>
 static void launch_dma_ek(const GemmArgs &g, hipStream_t st)
 {
-    constexpr int LDS = NS * (BM + BN) * 64 * 2 + (EK > 0 ? BN * 4 : 0);
+    using K = DmaKernel<BM, BN, WM, WN, NS, EK>;
     auto kern = gemm_bf16_dma_kernel<BM, BN, WM, WN, NS, EK>;
-    if (LDS > 64 * 1024) {
+    if (K::LDS > 64 * 1024) {
         static bool attr_set = false;   // raising the dynamic LDS limit is a per-kernel, process-wide setting
         if (!attr_set) {
-            (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+            (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, K::LDS);
             attr_set = true;
         }
     }
     const int tiles_m = (g.T + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-    POLY_LAUNCH_SHMEM(POLY_STAGE_GEMM, kern, dim3(dma_grid(g.n_in * tiles_m, tiles_n)), dim3(64 * WM * WN), LDS, st, g, tiles_m, tiles_n);
+    long run = ((long)g.n_in * tiles_m * tiles_n + 7) / 8; // workgroups of an XCD
+    if (K::TAIL && g.Tb) {
+        if (g.n_in_dev) run += (MAX_TAIL + 7) / 8;         // (fewer blocks than the bound may have a tail where the bound has none)
+        else {
+            const int large = large_tile_rows(g.T, g.N, BM, BN);
+            run = ((long)((large + BM - 1) / BM) * tiles_n + 7) / 8 + (tail_tiles(g.T - large, g.N) + 7) / 8;
+        }
+    }
+    POLY_LAUNCH_SHMEM(POLY_STAGE_GEMM, kern, dim3((unsigned)(8 * run)), dim3(K::THREADS), K::LDS, st, g, tiles_m, tiles_n);
 }
 
 template <int BM, int BN, int WM, int WN, int NS>
@@ -708,9 +753,7 @@ static void launch_dma(const GemmArgs &g, hipStream_t st)
             else launch_dma_ek<BM, BN, WM, WN, NS, 1>(g, st);
             return;
         }
-        if constexpr (BM / WM <= 64) {   // (with four row subtiles per wave the residual rows in flight do not fit beside the accumulators)
-            if (prefetchable && !g.pos) { launch_dma_ek<BM, BN, WM, WN, NS, 3>(g, st); return; }
-        }
+        if (prefetchable && !g.pos) { launch_dma_ek<BM, BN, WM, WN, NS, 3>(g, st); return; }
     }
     launch_dma_ek<BM, BN, WM, WN, NS, 0>(g, st);
 }

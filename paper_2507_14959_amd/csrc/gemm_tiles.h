@@ -35,26 +35,58 @@ inline const TileCost &tile_costs(int tile)
         {128, 64, 3, 32, true, true, 3.38f, 0.607f, 0.0129f, 2.32f, 1.01f, 3.99f, 0.944f, 1.49f, 0.405f, 4.f, 0.544f, 0.752f, 0.131f},
         {128, 128, 2, 32, true, true, 3.79f, 0.643f, 0.0147f, 2.76f, 1.45f, 8.95f, 1.04f, 1.53f, 0.441f, 3.28f, 0.592f, 0.f, 0.21f},
         {256, 128, 1, 64, true, true, 1.92f, 3.27f, 0.0117f, 3.15f, 1.84f, 5.49f, 1.11f, 1.73f, 0.339f, 3.31f, 0.f, 0.f, 0.329f},
-        {256, 256, 1, 128, true, false, 2.02f, 3.15f, 0.0231f, 5.51f, 3.84f, 16.f, 1.62f, 2.41f, 0.162f, 0.f, 0.f, 0.f, 0.3f},
+        {256, 256, 1, 128, true, true, 2.02f, 3.15f, 0.0231f, 5.51f, 3.84f, 13.f, 1.62f, 2.41f, 0.162f, 3.f, 0.f, 0.f, 0.3f},
         {64, 64, 2, 32, false, false, 3.47f, 1.1f, 0.00542f, 1.43f, 0.444f, 1.55f, 0.547f, 0.499f, 0.719f, 0.f, 0.72f, 0.f, 0.178f},
         {128, 64, 3, 64, false, false, 3.67f, 0.66f, 0.0128f, 3.1f, 1.03f, 4.69f, 0.889f, 0.902f, 0.648f, 0.f, 0.588f, 0.773f, 0.126f},
         {128, 128, 2, 64, true, true, 3.14f, 0.944f, 0.0136f, 3.17f, 1.78f, 5.76f, 1.14f, 1.88f, 0.401f, 3.58f, 0.72f, 0.f, 0.199f}};
     return cost[tile];
 }
 
+// Tiles of 256 rows leave a last round in which few CUs have one (22655 rows x 768: 534 of 256 x 128).  Where MAX_TAIL tiles of 128 x 128, one to a CU,
+// are enough for the rows past the full rounds, they are cut into those by the same launch: rows that stay in large tiles, all of them where not.
+// us without / with: 22064 rows x 768 -> 2304 on 256 x 256 (6 + 768 tiles) 113 / 101, 43734 rows 194 / 184, 22064 rows x 768 -> 768 52.5 / 47.8; with a
+// residual on 256 x 128, 11032 rows x 3072 -> 768 and x 768 -> 768 together 120 / 106, 12608 rows 126 / 110.  Twice as many small tiles gain nothing
+// (a second round of them, with its start, takes what a round of 256 x 256 with half the CUs does), and 256 x 128 without a residual has a cheap last round
+// already (11032 rows x 768 -> 3072 80.5 / 79.3, 12608 rows 84.0 / 86.3).
+constexpr int MAX_TAIL = 256;
+constexpr bool has_tail(int bm, int bn, int mode, bool ahead) { return bm == 256 && (mode == EPI_RESID ? ahead : bn == 256); }
+constexpr long tail_tiles(int rows, int N) { return (long)((rows + 127) / 128) * ((N + 127) / 128); }
+constexpr int large_tile_rows(int rows, int N, int bm, int bn)
+{
+    const int tiles_n = (N + bn - 1) / bn;
+    const long tiles = (long)((rows + bm - 1) / bm) * tiles_n;
+    if (tiles < 256 || tiles % 256 == 0) return rows;
+    const int large = (int)(tiles / 256 * 256 / tiles_n) * bm;
+    return tail_tiles(rows - large, N) <= MAX_TAIL ? large : rows;
+}
+
 inline long product_tiles(int n_in, int T, int N, int bm, int bn) { return (long)n_in * ((T + bm - 1) / bm) * ((N + bn - 1) / bn); }
 
-inline float tile_cost(const TileCost &c, const TiledProduct &p, long n)
+inline bool fetches_ahead(const TileCost &c, const TiledProduct &p)
+{
+    return (p.mode == EPI_RESID ? c.ahead_resid : c.ahead) && (!p.Tb || p.Tb >= c.rows) && !p.sums && (!p.RP || (p.RP == 16 && p.r % 8 == 0));
+}
+
+inline float round_cost(const TileCost &c, const TiledProduct &p)
 {
     const bool resid = p.mode == EPI_RESID;
-    const bool ahead = (resid ? c.ahead_resid : c.ahead) && (!p.Tb || p.Tb >= c.rows) && !p.sums && (!p.RP || (p.RP == 16 && p.r % 8 == 0));
     float round = c.f + c.k * p.K + p.fan * (c.store + (p.mode == EPI_GELU ? c.gelu : resid ? c.resid : 0.f));
-    if (!ahead) {
+    if (!fetches_ahead(c, p)) {
         const float more = p.Tb ? (float)(c.rows - 1) / p.Tb : 0.f;    // blocks a region touches beyond the first, on average
         round += (c.term + (p.r % 8 != 0 ? c.odd : 0.f)) * p.terms * (p.RP / 16) * (1.f + more) + p.fan * (c.look * more + (resid ? c.late : 0.f));
     }
-    const long slots = 256L * c.per_cu, rest = n % slots;
+    return round;
+}
+
+inline float tile_cost(const TileCost &c, const TiledProduct &p, long n)
+{
+    const float round = round_cost(c, p);
+    const long slots = 256L * c.per_cu, rest = n % slots, small = rest * (c.bn / 64);
     float rounds = (float)(n / slots);
+    if (has_tail(c.bm, c.bn, p.mode, fetches_ahead(c, p)) && p.Tb && n >= slots && rest && small <= MAX_TAIL) {
+        const TileCost &t = tile_costs(TILE_128x128);
+        return c.start + round * rounds + 4.f + round_cost(t, p) * (t.last1 - t.q * (1.f - small / 256.f));
+    }
     if (rest) {
         const int per_cu = (int)((rest + 255) / 256);
         rounds += (per_cu == c.per_cu ? 1.f : per_cu == 1 ? c.last1 : c.last2) - c.q * (per_cu - rest / 256.f);
