@@ -30,10 +30,14 @@ struct FlowSegment {
 // tiles) 469 / 487 us, 20 (140) 494 / 491, 24 (168) 509 / 503, 32 (224) 624 / 509; 70 blocks of 50 tokens (140) 427 / 438, 96 (192) 533 / 462;
 // GEMM path, rank 32: 32 blocks of 197 tokens (224) 644 / 748, 45 (315) 883 / 791; summed terms: 678 / 835 and 936 / 895, 60 blocks of 113
 // tokens (240) 729 / 828, 80 (320) 894 / 871.
+// Single precision: 270 tiles times the part of their rows that exist, for the other way runs its rows across blocks.  Two layers of 192 columns, us,
+// as tasks / layer by layer, every frame with one adapter: 32 blocks of 197 tokens (224 tiles) 422 / 453, 24 (168) 321 / 336, 4 (28) 96 / 189;
+// 64 of 101 (256) 463 / 436, 32 (128) 252 / 287; 64 of 50 (128) 251 / 274; 64 of 17 (64) 137 / 160, 115 of at most 192 235 / 222, 4 76 / 127.
 int flow_limit(const poly_model_desc *m, bool adapted)
 {
     const int T = tokens(m), r = adapted ? m->r : 0, tgt = adapted ? m->targets & 15 : 0;
-    if (m->dtype != POLY_BF16 || !flow_supported(T, m->D, m->Dm, m->heads, r, tgt != 0)) return 0;
+    if (!flow_supported(T, m->D, m->Dm, m->heads, r, tgt != 0)) return 0;
+    if (m->dtype == POLY_F32) return 270 * T / (32 * ((T + 31) / 32) * ((T + 31) / 32));
     const bool row_kernel = !(tgt & 12) && !(adapted && m->compose == POLY_COMPOSE_SUM && tgt) && rowlayer_supported(m->D, m->Dm, tgt ? r : 0);
     return (row_kernel ? 140 : 270) / ((T + 31) / 32);
 }
@@ -55,17 +59,18 @@ constexpr int FLOW_MIN_LAYERS = 4;
 constexpr size_t FLOW_BYTES = (size_t)128 << 20;
 
 struct FlowBuffers {
-    bf16_t *qk, *vt, *o, *h;
+    void *qk, *vt, *o, *h;
     float *x1, *x2;
 };
 FlowBuffers carve_flow(const poly_model_desc *m, size_t n, Carver &c)      // n: blocks x layers of a launch
 {
     const int T = tokens(m);
+    const size_t es = elt_size(m->dtype);
     FlowBuffers f;
-    f.qk = c.take<bf16_t>(sizeof(bf16_t) * n * flow_elements(T, 2 * m->D));
-    f.vt = c.take<bf16_t>(sizeof(bf16_t) * n * flow_elements(T, m->D));
-    f.o = c.take<bf16_t>(sizeof(bf16_t) * n * flow_elements(T, m->D));
-    f.h = c.take<bf16_t>(sizeof(bf16_t) * n * flow_elements(T, m->Dm));
+    f.qk = c.take<void>(es * n * flow_elements(T, 2 * m->D));
+    f.vt = c.take<void>(es * n * flow_elements(T, m->D));
+    f.o = c.take<void>(es * n * flow_elements(T, m->D));
+    f.h = c.take<void>(es * n * flow_elements(T, m->Dm));
     f.x1 = c.take<float>(sizeof(float) * n * T * m->D);
     f.x2 = c.take<float>(sizeof(float) * n * T * m->D);
     return f;
@@ -288,15 +293,15 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
             a.layers = last - l < w.fl_layers[ad] ? last - l : w.fl_layers[ad];
             const size_t ld = (size_t)l * D, lm = (size_t)l * Dm, dd = ld * D, dm = ld * Dm;
             a.ln1_g = base->ln1_g + ld; a.ln1_b = base->ln1_b + ld; a.ln2_g = base->ln2_g + ld; a.ln2_b = base->ln2_b + ld;
-            a.Wq = (const bf16_t *)base->qkv_w + 3 * dd; a.Wp = (const bf16_t *)base->proj_w + dd;
-            a.W1 = (const bf16_t *)base->fc1_w + dm; a.W2 = (const bf16_t *)base->fc2_w + dm;
+            a.Wq = (const char *)base->qkv_w + es * 3 * dd; a.Wp = (const char *)base->proj_w + es * dd;
+            a.W1 = (const char *)base->fc1_w + es * dm; a.W2 = (const char *)base->fc2_w + es * dm;
             a.bq = base->qkv_b + 3 * ld; a.bp = base->proj_b + ld; a.b1 = base->fc1_b + lm; a.b2 = base->fc2_b + ld;
             const size_t din[4] = {(size_t)D, (size_t)D, (size_t)D, (size_t)Dm}, dout[4] = {(size_t)3 * D, (size_t)D, (size_t)Dm, (size_t)D};
             for (int t = 0; ad && t < 4; ++t) {
                 const size_t ranks = (size_t)(l - first) * m->n_adapters * m->r;
-                if (m->targets & (1 << t)) { a.At[t] = (const bf16_t *)lora->At[t] + ranks * din[t]; a.Bt[t] = (const bf16_t *)lora->Bt[t] + ranks * dout[t]; }
+                if (m->targets & (1 << t)) { a.At[t] = (const char *)lora->At[t] + es * ranks * din[t]; a.Bt[t] = (const char *)lora->Bt[t] + es * ranks * dout[t]; }
             }
-            POLY_TRY(launch_flow(a, st));
+            POLY_TRY(launch_flow(a, dt, st));
             a.x_in = a.x; a.in_map = nullptr;                  // the next launch continues on this one's blocks
             a.counters += flow_counter_bytes(a.nb, m->heads) / sizeof(unsigned);
         }

@@ -31,6 +31,10 @@
 // of ten and two layers), the matrix unit busy 0.7 % of the time; the lagged loop takes 209 us instead of the 473 of row kernels and
 // attention launches.  With many blocks the weights that every 32-row task pulls through its CU's load path bound it, and kernels with
 // larger tiles take over (api.hip).
+//
+// Single precision: the same tasks on v_mfma_f32_16x16x4_f32, elements and buffers of twice the size, one workgroup per CU (190 registers).  The same
+// chain bounds it: two layers on 4 frames of 17 tokens, 22 launches of 3 to 13 us each before, 128 us per forward / 78 now; one frame of 197 tokens
+// 168 / 82.  Its products are an eighth of the bf16 rate, so the tasks give way to larger tiles with fewer blocks than in bf16 (api.hip).
 #include "poly_dev.h"
 #include "rowtile.h"
 
@@ -72,6 +76,38 @@ struct Buf {
 };
 
 __device__ __forceinline__ bf16x4 pack4(f32x4 v) { return bf16x4{(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]}; }
+
+// What the tasks do with elements of either type.  `op`: eight consecutive contraction elements of a row, a lane's share of a K step of 32: one
+// 16 x 16 x 32 product in bf16, eight of 16 x 16 x 4 in single precision (both operands in the same order).  `quad`: four elements.
+struct f32x8_ { f32x4 a, b; };
+template <typename E> struct El;
+template <> struct El<bf16_t> {
+    typedef bf16x8 op;
+    typedef bf16x4 quad;
+    static __device__ __forceinline__ op load(const Buf &b, unsigned off) { return __builtin_bit_cast(op, b.ld16(off)); }
+    static __device__ __forceinline__ void store4(const Buf &b, f32x4 v, unsigned off) { b.st8(__builtin_bit_cast(u32x2_, pack4(v)), off); }
+    static __device__ __forceinline__ quad round4(f32x4 v) { return pack4(v); }
+    static __device__ __forceinline__ op join(quad lo, quad hi) { return op{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]}; }
+    static __device__ __forceinline__ f32x4 mma(op u, op v, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(u, v, c, 0, 0, 0); }
+    static __device__ __forceinline__ f32x4 gelu4(f32x4 v) { return gelu_fine4(v); }
+};
+template <> struct El<float> {
+    typedef f32x8_ op;
+    typedef f32x4 quad;
+    static __device__ __forceinline__ op load(const Buf &b, unsigned off) { return op{__builtin_bit_cast(f32x4, b.ld16(off)), __builtin_bit_cast(f32x4, b.ld16(off + 16))}; }
+    static __device__ __forceinline__ void store4(const Buf &b, f32x4 v, unsigned off) { b.st16(__builtin_bit_cast(u32x4_, v), off); }
+    static __device__ __forceinline__ quad round4(f32x4 v) { return v; }
+    static __device__ __forceinline__ op join(quad lo, quad hi) { return op{lo, hi}; }
+    static __device__ __forceinline__ f32x4 mma(op u, op v, f32x4 c)
+    {
+#pragma unroll
+        for (int z = 0; z < 4; ++z) c = __builtin_amdgcn_mfma_f32_16x16x4f32(u.a[z], v.a[z], c, 0, 0, 0);
+#pragma unroll
+        for (int z = 0; z < 4; ++z) c = __builtin_amdgcn_mfma_f32_16x16x4f32(u.b[z], v.b[z], c, 0, 0, 0);
+        return c;
+    }
+    static __device__ __forceinline__ f32x4 gelu4(f32x4 v) { return f32x4{gelu_erf(v[0]), gelu_erf(v[1]), gelu_erf(v[2]), gelu_erf(v[3])}; }
+};
 
 // The kernel's arguments are read where they are used (a scalar load that hits the scalar cache): held in registers across the loop over
 // the tasks they would be five times what fits.
@@ -119,17 +155,19 @@ __device__ __forceinline__ void await(const Task &t, const unsigned *c, unsigned
 }
 
 // Fragment order of an activation matrix of ks K steps of 32 columns: [32 rows][16 rows][K step][lane][8], what a wave reads as the rows'
-// operand of a 16 x 16 x 32 product with one 1 KB load.  Byte offset of the four columns 16 c16 + 4 g .. of row 16 m + lm of row tile rt
+// operand of a 16 x 16 x 32 product with one load of 1 KB (single precision: two).  Byte offset, in bf16, of the four columns 16 c16 + 4 g .. of row 16 m + lm of row tile rt
 __device__ __forceinline__ unsigned frag_off(int rt, int m, int ks, int c16, int lm, int g)
 {
     return ((rt * 2 + m) * ks + (c16 >> 1)) * 1024u + (((c16 & 1) * 2 + (g >> 1)) * 16 + lm) * 16 + (g & 1) * 8;
 }
 
 // ---- attention of one head on 32 queries: wave w takes the keys 32 w ..; returns the counter to raise
-template <int KD>
+template <typename E, int KD>
 __device__ __forceinline__ unsigned *attention_task(const Task &k, char *lds)
 {
-    constexpr int D = 32 * KD;
+    typedef El<E> L;
+    typedef typename L::op op_t;
+    constexpr int D = 32 * KD, ES = sizeof(E) / 2;             // ES: of offsets in bf16
     const ParamPtr p = params();
     float *op = (float *)lds;                                  // partial outputs [wave][2][4][64 lanes] x 4
     float *ml = op + 8 * 2048;                                 // [wave][32] maxima, [wave][32] sums
@@ -138,30 +176,30 @@ __device__ __forceinline__ unsigned *attention_task(const Task &k, char *lds)
     if (wave == 0) await(k, counter(k, C_Q + k.ct), 0, (k.layer + 1) * (3 / p->nQ) * nrt);
     __syncthreads();
     const size_t slot = k.layer * (size_t)p->a.nb + k.b;
-    const Buf qk(p->a.qk + slot * TP * 2 * D, (unsigned)TP * 4 * D), vt(p->a.vt + slot * D * TP, (unsigned)D * TP * 2);
-    const unsigned hq = (unsigned)k.ct * TP * 128, hk = hq + (unsigned)D * TP * 2;   // bytes: this head's queries, keys (and values)
+    const Buf qk((const E *)p->a.qk + slot * TP * 2 * D, (unsigned)TP * 4 * D * ES), vt((const E *)p->a.vt + slot * D * TP, (unsigned)D * TP * 2 * ES);
+    const unsigned hq = (unsigned)k.ct * TP * 128 * ES, hk = hq + (unsigned)D * TP * 2 * ES;   // bytes: this head's queries, keys (and values)
     if (wave < nrt) {
-        u32x4_ qf[2][2], kf[2][2], vf[4];
+        op_t qf[2][2], kf[2][2], vf[4];
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                qf[i][ks] = qk.ld16(hq + ((2 * k.rt + i) * 2 + ks) * 1024 + lane * 16);
-                kf[i][ks] = qk.ld16(hk + ((2 * wave + i) * 2 + ks) * 1024 + lane * 16);
+                qf[i][ks] = L::load(qk, hq + (((2 * k.rt + i) * 2 + ks) * 1024 + lane * 16) * ES);
+                kf[i][ks] = L::load(qk, hk + (((2 * wave + i) * 2 + ks) * 1024 + lane * 16) * ES);
             }
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) vf[dt] = vt.ld16(hq + (4 * wave + dt) * 1024 + lane * 16);
+        for (int dt = 0; dt < 4; ++dt) vf[dt] = L::load(vt, hq + ((4 * wave + dt) * 1024 + lane * 16) * ES);
         f32x4 s[2][2];                                         // [key subtile][query subtile]: keys 16 i + 4 g + e of query lm
         const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                s[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[i][0]), __builtin_bit_cast(bf16x8, qf[j][0]), z4, 0, 0, 0);
-                s[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[i][1]), __builtin_bit_cast(bf16x8, qf[j][1]), s[i][j], 0, 0, 0);
+                s[i][j] = L::mma(kf[i][0], qf[j][0], z4);
+                s[i][j] = L::mma(kf[i][1], qf[j][1], s[i][j]);
             }
         const float sc = 0.125f * FL_LOG2E;
-        bf16x8 pf[2];
+        op_t pf[2];
         float mx[2], sum[2];
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
@@ -177,14 +215,15 @@ __device__ __forceinline__ unsigned *attention_task(const Task &k, char *lds)
             m = fmaxf(m, __shfl_xor(m, 32, 64));               // (the tile has a key inside T)
             const float off = -m * sc;
             float t = 0.f;
+            f32x4 pr[2];
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float pr = __builtin_amdgcn_exp2f(fmaf(s[i][j][e], sc, off));
-                    t += pr;
-                    pf[j][4 * i + e] = (bf16_t)pr;
+                    pr[i][e] = __builtin_amdgcn_exp2f(fmaf(s[i][j][e], sc, off));
+                    t += pr[i][e];
                 }
+            pf[j] = L::join(L::round4(pr[0]), L::round4(pr[1]));
             t += __shfl_xor(t, 16, 64);
             t += __shfl_xor(t, 32, 64);
             mx[j] = m; sum[j] = t;
@@ -193,7 +232,7 @@ __device__ __forceinline__ unsigned *attention_task(const Task &k, char *lds)
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int dt = 0; dt < 4; ++dt) {
-                const f32x4 o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf[dt]), pf[j], z4, 0, 0, 0);
+                const f32x4 o = L::mma(vf[dt], pf[j], z4);
                 *(f32x4 *)(op + ((wave * 2 + j) * 4 + dt) * 256 + lane * 4) = o;
             }
         if (g == 0) {
@@ -205,7 +244,7 @@ __device__ __forceinline__ unsigned *attention_task(const Task &k, char *lds)
     if (tid == 0) draw(k);
     // wave (j, dt) brings its piece of the key tiles' partial outputs together
     const int j = wave >> 2, dt = wave & 3;
-    float mw[8], M = -INFINITY, L = 0.f;
+    float mw[8], M = -INFINITY, sum = 0.f;
     f32x4 ow[8], o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < 8; ++w) {
@@ -217,23 +256,27 @@ __device__ __forceinline__ unsigned *attention_task(const Task &k, char *lds)
 #pragma unroll
     for (int w = 0; w < 8; ++w) {
         const float c = w < nrt ? __builtin_amdgcn_exp2f((mw[w] - M) * (0.125f * FL_LOG2E)) : 0.f;
-        L = fmaf(ml[256 + min(w, nrt - 1) * 32 + 16 * j + lm], c, L);
+        sum = fmaf(ml[256 + min(w, nrt - 1) * 32 + 16 * j + lm], c, sum);
         o += ow[w] * c;
     }
-    const Buf ob(p->a.o + slot * TP * D, (unsigned)TP * D * 2);
-    ob.st8(__builtin_bit_cast(u32x2_, pack4(o * (1.0f / L))), frag_off(k.rt, j, KD, k.ct * 4 + dt, lm, g));
+    const Buf ob((const E *)p->a.o + slot * TP * D, (unsigned)TP * D * 2 * ES);
+    L::store4(ob, o * (1.0f / sum), frag_off(k.rt, j, KD, k.ct * 4 + dt, lm, g) * ES);
     return counter(k, C_A + k.rt);
 }
 
 // ---- LayerNorm + linear on 32 rows x NT tiles of 64 columns; STAGE: 0 Q, 3 F1.  The normalised rows go through LDS; wave (kh, wc)
 // takes half kh of the contraction for the 16 columns 16 wc .. of a tile, both row halves; returns the counter to raise
-template <int KD, int STAGE, int NT, bool SUM>
+template <typename E, int KD, int STAGE, int NT, bool SUM>
 __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
 {
+    typedef El<E> L;
+    typedef typename L::op op_t;
+    typedef typename L::quad quad_t;
+    constexpr int ES = sizeof(E) / 2;
     constexpr int D = 32 * KD, KT = KD / 2, HK = KD / 2;       // HK: K steps of a wave
     constexpr int NA = (KD + 3) / 4;                           // K steps of a wave's share of the shrink
-    bf16_t *As = (bf16_t *)lds;                                // rows: 32 x D, 16-byte chunks swizzled by row
-    char *red = lds + 32 * D * 2;                              // partial sums that the halves of K hand over: NT x 8 KB
+    E *As = (E *)lds;                                          // rows: 32 x D, chunks of eight swizzled by row
+    char *red = lds + 32 * D * sizeof(E);                             // partial sums that the halves of K hand over: NT x 8 KB
     char *shr = red + NT * 8192;                               // shrink [quarter of K][row half][rank tile][lane]: 16 KB
     const ParamPtr p = params();
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lm = lane & 15, g = lane >> 4;
@@ -247,14 +290,14 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
     // tile i of the task: q, k and v of one head, or neighbours
     auto tile = [&](int i) { return STAGE == 0 ? k.ct + i * dt : k.ct * NT + i; };
     auto is_v = [&](int i) { return STAGE == 0 && tile(i) >= 2 * dt; };            // V: product untransposed
-    const bf16_t *W = (STAGE == 0 ? p->a.Wq : p->a.W1) + ld * N * D + (size_t)(wc * 16 + lm) * D + kh * HK * 32 + 8 * g;
+    const E *W = (const E *)(STAGE == 0 ? p->a.Wq : p->a.W1) + ld * N * D + (size_t)(wc * 16 + lm) * D + kh * HK * 32 + 8 * g;
     const float *bias = (STAGE == 0 ? p->a.bq : p->a.b1) + ld * N + wc * 16;
-    bf16x8 wf[NT][HK];
+    op_t wf[NT][HK];
     f32x4 bias4[NT];
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
 #pragma unroll
-        for (int j = 0; j < HK; ++j) wf[i][j] = *(const bf16x8 *)(W + (size_t)tile(i) * 64 * D + 32 * j);
+        for (int j = 0; j < HK; ++j) wf[i][j] = *(const op_t *)(W + (size_t)tile(i) * 64 * D + 32 * j);
     }
     constexpr bool LEAN = NT > 2;                              // gains and biases are requested later: registers
     auto load_bias = [&]() {
@@ -276,33 +319,33 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
     if (!LEAN) load_gain();
     // operands of the low-rank terms of this block's adapter(s); those of the first one are requested here
     constexpr int TGT = STAGE == 0 ? 0 : 2;
-    const bf16_t *At = p->a.At[TGT], *Bt = p->a.Bt[TGT];
+    const E *At = (const E *)p->a.At[TGT], *Bt = (const E *)p->a.Bt[TGT];
     const int *set_off = p->a.set_off, *adapter = p->a.adapter_of_row, *in_map = p->a.in_map;
     const int s0 = At ? (SUM ? uload(set_off + b) : b) : 0, s1 = At ? (SUM ? uload(set_off + b + 1) : b + 1) : 0;
     const int r = p->a.r, nrk = (r + 15) >> 4;
-    const bf16x4 z4 = {0, 0, 0, 0};
-    bf16x8 fat[NA][2];
+    const quad_t z4 = {0, 0, 0, 0};
+    op_t fat[NA][2];
     auto load_at = [&](int s) {
-        const bf16_t *Ak = At + (p->a.n_adapters * ld + uload(adapter + s)) * r * D + 8 * g;
+        const E *Ak = At + (p->a.n_adapters * ld + uload(adapter + s)) * r * D + 8 * g;
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
             const int kk = min(wc + 4 * i, KD - 1);
-            fat[i][0] = *(const bf16x8 *)(Ak + (size_t)min(lm, r - 1) * D + 32 * kk);
-            if (nrk > 1) fat[i][1] = *(const bf16x8 *)(Ak + (size_t)min(16 + lm, r - 1) * D + 32 * kk);
+            fat[i][0] = *(const op_t *)(Ak + (size_t)min(lm, r - 1) * D + 32 * kk);
+            if (nrk > 1) fat[i][1] = *(const op_t *)(Ak + (size_t)min(16 + lm, r - 1) * D + 32 * kk);
         }
     };
-    bf16x8 fb[NT];
+    op_t fb[NT];
     auto load_bt = [&](int s) {                                // ranks 4 g .. and 16 + 4 g .. of a column
 #pragma unroll
         for (int i = 0; i < NT; ++i) {
-            const bf16_t *bt = Bt + ((p->a.n_adapters * ld + uload(adapter + s)) * N + tile(i) * 64 + wc * 16 + lm) * r + 4 * g;
-            bf16x4 lo = *(const bf16x4 *)(bt + min(0, r - 4 - 4 * g)), hi = z4;
+            const E *bt = Bt + ((p->a.n_adapters * ld + uload(adapter + s)) * N + tile(i) * 64 + wc * 16 + lm) * r + 4 * g;
+            quad_t lo = *(const quad_t *)(bt + min(0, r - 4 - 4 * g)), hi = z4;
             if (4 * g >= r) lo = z4;
             if (nrk > 1) {
-                hi = *(const bf16x4 *)(bt + min(16, r - 4 - 4 * g));
+                hi = *(const quad_t *)(bt + min(16, r - 4 - 4 * g));
                 if (16 + 4 * g >= r) hi = z4;
             }
-            fb[i] = bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            fb[i] = L::join(lo, hi);
         }
     };
     if (s0 < s1) { load_at(s0); load_bt(s0); }
@@ -335,13 +378,13 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
 #pragma unroll
             for (int z = 0; z < 4; ++z) o[z] = fmaf(fmaf(v[i][z], inv, nmi), gn[i][z], sh[i][z]);
             const int c = 4 * (part + 16 * i);
-            *(bf16x4 *)(As + row * D + (((c >> 3) ^ (row & 7)) << 3) + (c & 4)) = pack4(o);
+            *(quad_t *)(As + row * D + (((c >> 3) ^ (row & 7)) << 3) + (c & 4)) = L::round4(o);
         }
     }
     __syncthreads();
     if (tid == 0) draw(k);
     // fragment of rows 16 m + lm, K step i: chunk 4 i + g
-    auto frag_a = [&](int m, int i) { return *(const bf16x8 *)(As + (16 * m + lm) * D + (((4 * i + g) ^ (lm & 7)) << 3)); };
+    auto frag_a = [&](int m, int i) { return *(const op_t *)(As + (16 * m + lm) * D + (((4 * i + g) ^ (lm & 7)) << 3)); };
     // the shrink is shared by the waves (row half kh, K steps wc, wc + 4), the partial sums meet in LDS, and ranks 4 g .. and 16 + 4 g ..
     // of row lm are what a lane feeds to the expand
     auto shrink_part = [&]() {
@@ -349,30 +392,29 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
 #pragma unroll
         for (int i = 0; i < NA; ++i)
             if (wc + 4 * i < KD) {
-                const bf16x8 fa = frag_a(kh, wc + 4 * i);
-                sp[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fat[i][0], fa, sp[0], 0, 0, 0);
-                if (nrk > 1) sp[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fat[i][1], fa, sp[1], 0, 0, 0);
+                const op_t fa = frag_a(kh, wc + 4 * i);
+                sp[0] = L::mma(fat[i][0], fa, sp[0]);
+                if (nrk > 1) sp[1] = L::mma(fat[i][1], fa, sp[1]);
             }
         *(f32x4 *)(shr + (((wc * 2 + kh) * 2 + 0) * 64 + lane) * 16) = sp[0];
         if (nrk > 1) *(f32x4 *)(shr + (((wc * 2 + kh) * 2 + 1) * 64 + lane) * 16) = sp[1];
     };
     auto shrink_sum = [&]() {
-        bf16x8 fs = {0, 0, 0, 0, 0, 0, 0, 0};
+        quad_t fs[2] = {z4, z4};
 #pragma unroll
         for (int q = 0; q < 2; ++q)
             if (q < nrk) {
                 f32x4 t = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int w = 0; w < 4; ++w) t += *(const f32x4 *)(shr + (((w * 2 + kh) * 2 + q) * 64 + lane) * 16);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) fs[4 * q + e] = (bf16_t)(t[e] * p->a.scale);
+                fs[q] = L::round4(t * p->a.scale);
             }
-        return fs;
+        return L::join(fs[0], fs[1]);
     };
     if (s0 < s1) shrink_part();
     f32x4 y[NT];                                               // the row half that this wave finishes: 16 kh ..
     {
-        bf16x8 fa[2][HK];
+        op_t fa[2][HK];
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
@@ -384,8 +426,8 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
             for (int j = 0; j < HK; ++j)
 #pragma unroll
                 for (int m = 0; m < 2; ++m) {
-                    const bf16x8 u = is_v(i) ? fa[m][j] : wf[i][j], v = is_v(i) ? wf[i][j] : fa[m][j];
-                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(u, v, acc[m], 0, 0, 0);
+                    const op_t u = is_v(i) ? fa[m][j] : wf[i][j], v = is_v(i) ? wf[i][j] : fa[m][j];
+                    acc[m] = L::mma(u, v, acc[m]);
                 }
             *(f32x4 *)(red + ((i * 8 + wave) * 64 + lane) * 16) = kh ? acc[0] : acc[1];
             y[i] = kh ? acc[1] : acc[0];
@@ -405,11 +447,11 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
             shrink_part();
             __syncthreads();
         }
-        const bf16x8 fs = shrink_sum();
+        const op_t fs = shrink_sum();
 #pragma unroll
         for (int i = 0; i < NT; ++i) {
-            const bf16x8 u = is_v(i) ? fs : fb[i], v = is_v(i) ? fb[i] : fs;
-            y[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(u, v, y[i], 0, 0, 0);
+            const op_t u = is_v(i) ? fs : fb[i], v = is_v(i) ? fb[i] : fs;
+            y[i] = L::mma(u, v, y[i]);
         }
         if (!SUM) break;
     }
@@ -417,23 +459,28 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
     const int TP = p->nrt * 32;
     // q and k as [head][16 rows][32 columns][lane][8], v as [head][32 rows][16 columns][lane][rows 4 g .., 16 + 4 g ..]: attention
     // reads 1 KB per instruction (rows past T repeat row T - 1: finite, and masked there)
-    const Buf vt(p->a.vt + slot * D * TP, (unsigned)D * TP * 2), qk(p->a.qk + slot * TP * 2 * D, (unsigned)TP * 4 * D), hb(p->a.h + slot * TP * N, (unsigned)TP * N * 2);
+    const Buf vt((const E *)p->a.vt + slot * D * TP, (unsigned)D * TP * 2 * ES), qk((const E *)p->a.qk + slot * TP * 2 * D, (unsigned)TP * 4 * D * ES),
+        hb((const E *)p->a.h + slot * TP * N, (unsigned)TP * N * 2 * ES);
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
         const int ct = tile(i);
         const f32x4 v = y[i] + bias4[i];
-        if (STAGE == 3) hb.st8(__builtin_bit_cast(u32x2_, pack4(gelu_fine4(v))), frag_off(k.rt, kh, N / 32, ct * 4 + wc, lm, g));
-        else if (is_v(i)) vt.st8(__builtin_bit_cast(u32x2_, pack4(v)), (unsigned)(ct - 2 * dt) * TP * 128 + (4 * k.rt + wc) * 1024 + lane * 16 + kh * 8);
-        else qk.st8(__builtin_bit_cast(u32x2_, pack4(v)), (unsigned)ct * TP * 128 + frag_off(k.rt, kh, 2, wc, lm, g));
+        if (STAGE == 3) L::store4(hb, L::gelu4(v), frag_off(k.rt, kh, N / 32, ct * 4 + wc, lm, g) * ES);
+        else if (is_v(i)) L::store4(vt, v, ((unsigned)(ct - 2 * dt) * TP * 128 + (4 * k.rt + wc) * 1024 + lane * 16 + kh * 8) * ES);
+        else L::store4(qk, v, ((unsigned)ct * TP * 128 + frag_off(k.rt, kh, 2, wc, lm, g)) * ES);
     }
     return counter(k, STAGE == 0 ? C_Q + (k.ct < dt ? k.ct : k.ct < 2 * dt ? k.ct - dt : k.ct - 2 * dt) : C_F1 + k.rt);
 }
 
 // ---- linear + residual on 32 rows x NT tiles of 32 columns; STAGE: 2 P, 4 F2.  Wave w takes the K steps w, w + 8, .. of the whole tile,
 // both operands straight from memory in fragment order, and the partial sums meet in LDS; returns the counter to raise
-template <int KD, int CH, int STAGE, int NT, bool SUM>
+template <typename E, int KD, int CH, int STAGE, int NT, bool SUM>
 __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
 {
+    typedef El<E> L;
+    typedef typename L::op op_t;
+    typedef typename L::quad quad_t;
+    constexpr int ES = sizeof(E) / 2;
     constexpr int D = 32 * KD, KS = STAGE == 4 ? CH : KD, NS = (KS + 7) / 8;      // K steps of a wave
     static_assert(NT <= 2, "waves 0 - 3 and 4 - 7 finish a tile each");
     char *red = lds, *shr = lds + 32768;                       // [tile][wave][row half][column half][lane]; [wave][row half][rank tile][lane]
@@ -446,40 +493,40 @@ __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
     unsigned seen = 0;
     if (wave == 0) seen = peek(dep);
     const int K = STAGE == 4 ? p->a.Dm : D, ks = K / 32, np = min(ks, 8);
-    const bf16_t *W = (STAGE == 2 ? p->a.Wp : p->a.W2) + (ld * D + k.ct * NT * 32 + lm) * K + 8 * g;
-    bf16x8 wf[NT][NS][2];
+    const E *W = (const E *)(STAGE == 2 ? p->a.Wp : p->a.W2) + (ld * D + k.ct * NT * 32 + lm) * K + 8 * g;
+    op_t wf[NT][NS][2];
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
         for (int i = 0; i < NS; ++i)
 #pragma unroll
-            for (int n = 0; n < 2; ++n) wf[j][i][n] = *(const bf16x8 *)(W + (size_t)(j * 32 + 16 * n) * K + 32 * min(wave + 8 * i, ks - 1));
+            for (int n = 0; n < 2; ++n) wf[j][i][n] = *(const op_t *)(W + (size_t)(j * 32 + 16 * n) * K + 32 * min(wave + 8 * i, ks - 1));
     // waves 4 j .. 4 j + 3 finish the subtiles of tile j: rows 16 fm .., columns 16 fn ..
     const int fm = (wave >> 1) & 1, fn = wave & 1, trow = k.rt * 32 + 16 * fm + lm, fcol = (k.ct * NT + (wave >> 2)) * 32 + 16 * fn;
     const bool fin = wave < 4 * NT;
     const f32x4 bias4 = *(const f32x4_u *)((STAGE == 2 ? p->a.bp : p->a.b2) + ld * D + (fin ? fcol : 0) + 4 * g);
     constexpr int TGT = STAGE == 2 ? 1 : 3;
-    const bf16_t *At = p->a.At[TGT], *Bt = p->a.Bt[TGT];
+    const E *At = (const E *)p->a.At[TGT], *Bt = (const E *)p->a.Bt[TGT];
     const int *set_off = p->a.set_off, *adapter = p->a.adapter_of_row, *in_map = p->a.in_map;
     const int s0 = At ? (SUM ? uload(set_off + b) : b) : 0, s1 = At ? (SUM ? uload(set_off + b + 1) : b + 1) : 0;
     const int r = p->a.r, nrk = (r + 15) >> 4;
-    const bf16x4 z4 = {0, 0, 0, 0};
-    bf16x8 fat[2];                                             // of one K step
+    const quad_t z4 = {0, 0, 0, 0};
+    op_t fat[2];                                               // of one K step
     auto load_at = [&](int s, int i) {
-        const bf16_t *Ak = At + (p->a.n_adapters * ld + uload(adapter + s)) * r * K + 32 * min(wave + 8 * i, ks - 1) + 8 * g;
-        fat[0] = *(const bf16x8 *)(Ak + (size_t)min(lm, r - 1) * K);
-        if (nrk > 1) fat[1] = *(const bf16x8 *)(Ak + (size_t)min(16 + lm, r - 1) * K);
+        const E *Ak = At + (p->a.n_adapters * ld + uload(adapter + s)) * r * K + 32 * min(wave + 8 * i, ks - 1) + 8 * g;
+        fat[0] = *(const op_t *)(Ak + (size_t)min(lm, r - 1) * K);
+        if (nrk > 1) fat[1] = *(const op_t *)(Ak + (size_t)min(16 + lm, r - 1) * K);
     };
-    bf16x8 fb;
+    op_t fb;
     auto load_bt = [&](int s) {
-        const bf16_t *bt = Bt + ((p->a.n_adapters * ld + uload(adapter + s)) * D + (fin ? fcol : 0) + lm) * r + 4 * g;
-        bf16x4 lo = *(const bf16x4 *)(bt + min(0, r - 4 - 4 * g)), hi = z4;
+        const E *bt = Bt + ((p->a.n_adapters * ld + uload(adapter + s)) * D + (fin ? fcol : 0) + lm) * r + 4 * g;
+        quad_t lo = *(const quad_t *)(bt + min(0, r - 4 - 4 * g)), hi = z4;
         if (4 * g >= r) lo = z4;
         if (nrk > 1) {
-            hi = *(const bf16x4 *)(bt + min(16, r - 4 - 4 * g));
+            hi = *(const quad_t *)(bt + min(16, r - 4 - 4 * g));
             if (16 + 4 * g >= r) hi = z4;
         }
-        fb = bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        fb = L::join(lo, hi);
     };
     if (s0 < s1) { load_at(s0, 0); load_bt(s0); }
     const bool first = STAGE == 2 && k.layer == 0;
@@ -488,16 +535,16 @@ __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
     const float *xs = STAGE == 4 ? p->a.x1 + ld * step : first ? p->a.x_in : p->a.x2 + (ld - 1) * step;
     float *xd = STAGE == 2 ? p->a.x1 + ld * step : (int)k.layer + 1 == p->a.layers ? p->a.x : p->a.x2 + ld * step;
     const Buf xi(xs + (size_t)xblk * T * D, (unsigned)T * D * 4), xo(xd + (size_t)b * T * D, (unsigned)T * D * 4);
-    const Buf src((STAGE == 2 ? p->a.o : p->a.h) + slot * TP * K, (unsigned)TP * K * 2);
+    const Buf src((const E *)(STAGE == 2 ? p->a.o : p->a.h) + slot * TP * K, (unsigned)TP * K * 2 * ES);
     // ---- inputs
     if (wave == 0) await(k, dep, seen, want);
     __syncthreads();
-    bf16x8 fa[NS][2];
+    op_t fa[NS][2];
 #pragma unroll
     for (int i = 0; i < NS; ++i)
 #pragma unroll
         for (int m = 0; m < 2; ++m)
-            fa[i][m] = __builtin_bit_cast(bf16x8, src.ld16(((k.rt * 2 + m) * ks + min(wave + 8 * i, ks - 1)) * 1024 + lane * 16));
+            fa[i][m] = L::load(src, (((k.rt * 2 + m) * ks + min(wave + 8 * i, ks - 1)) * 1024 + lane * 16) * ES);
     const unsigned xoff = ((unsigned)min(trow, T - 1) * D + (fin ? fcol : 0) + 4 * g) * 4;
     const f32x4 res = __builtin_bit_cast(f32x4, xi.ld16(xoff));
     auto shrink_part = [&](int s) {                            // (K step 0 of the term is in registers)
@@ -508,8 +555,8 @@ __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
                 if (i) load_at(s, i);
 #pragma unroll
                 for (int m = 0; m < 2; ++m) {
-                    sp[m][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fat[0], fa[i][m], sp[m][0], 0, 0, 0);
-                    if (nrk > 1) sp[m][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fat[1], fa[i][m], sp[m][1], 0, 0, 0);
+                    sp[m][0] = L::mma(fat[0], fa[i][m], sp[m][0]);
+                    if (nrk > 1) sp[m][1] = L::mma(fat[1], fa[i][m], sp[m][1]);
                 }
             }
 #pragma unroll
@@ -519,7 +566,7 @@ __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
         }
     };
     auto shrink_sum = [&]() {
-        bf16x8 fs = {0, 0, 0, 0, 0, 0, 0, 0};
+        quad_t fs[2] = {z4, z4};
 #pragma unroll
         for (int q = 0; q < 2; ++q)
             if (q < nrk) {
@@ -529,12 +576,11 @@ __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
                     const f32x4 u = *(const f32x4 *)(shr + (((min(w, np - 1) * 2 + fm) * 2 + q) * 64 + lane) * 16);
                     if (w < np) t += u;
                 }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) fs[4 * q + e] = (bf16_t)(t[e] * p->a.scale);
+                fs[q] = L::round4(t * p->a.scale);
             }
-        return fs;
+        return L::join(fs[0], fs[1]);
     };
-    bf16x8 fs1 = {0, 0, 0, 0, 0, 0, 0, 0};                     // the first term's
+    op_t fs1 = {};                                             // the first term's
     if (s0 < s1) shrink_part(s0);
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
@@ -550,7 +596,7 @@ __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
 #pragma unroll
                 for (int m = 0; m < 2; ++m)
 #pragma unroll
-                    for (int n = 0; n < 2; ++n) acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j][i][n], fa[i][m], acc[m][n], 0, 0, 0);
+                    for (int n = 0; n < 2; ++n) acc[m][n] = L::mma(wf[j][i][n], fa[i][m], acc[m][n]);
             }
 #pragma unroll
         for (int m = 0; m < 2; ++m)
@@ -577,7 +623,7 @@ __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
         } else if (NT == 1) {
             fs1 = shrink_sum();
         }
-        y = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb, fs1, y, 0, 0, 0);
+        y = L::mma(fb, fs1, y);
         if (!SUM) break;
     }
     if (fin && trow < T) xo.st16(__builtin_bit_cast(u32x4_, y + bias4 + res), xoff);
@@ -585,8 +631,8 @@ __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
 }
 
 // KD: K steps of 32 in the model width.  CH: K steps at most in the hidden width
-template <int KD, int CH, int NQ, int N1, int NP, bool SUM>
-__global__ __launch_bounds__(FL_THREADS, 4) void flow_kernel(const FlowParams)
+template <typename E, int KD, int CH, int NQ, int N1, int NP, bool SUM>
+__global__ __launch_bounds__(FL_THREADS, sizeof(E) == 2 ? 4 : 2) void flow_kernel(const FlowParams)
 {
     extern __shared__ __attribute__((aligned(16))) char fl_lds[];
     __shared__ unsigned s_ticket;
@@ -630,11 +676,11 @@ __global__ __launch_bounds__(FL_THREADS, 4) void flow_kernel(const FlowParams)
             k.ct = div(rem, Div{p->drt.d, p->drt.m}); k.rt = rem - k.ct * p->nrt; k.b = qn + bi * nq;
             k.cnt = p->cnt + (size_t)k.b * p->ncnt * 16;
             unsigned *done;
-            if (stage == 0) done = norm_task<KD, 0, NQ, SUM>(k, fl_lds);
-            else if (stage == 1) done = attention_task<KD>(k, fl_lds);
-            else if (stage == 2) done = resid_task<KD, CH, 2, NP, SUM>(k, fl_lds);
-            else if (stage == 3) done = norm_task<KD, 3, N1, SUM>(k, fl_lds);
-            else done = resid_task<KD, CH, 4, NP, SUM>(k, fl_lds);
+            if (stage == 0) done = norm_task<E, KD, 0, NQ, SUM>(k, fl_lds);
+            else if (stage == 1) done = attention_task<E, KD>(k, fl_lds);
+            else if (stage == 2) done = resid_task<E, KD, CH, 2, NP, SUM>(k, fl_lds);
+            else if (stage == 3) done = norm_task<E, KD, 3, N1, SUM>(k, fl_lds);
+            else done = resid_task<E, KD, CH, 4, NP, SUM>(k, fl_lds);
             // ---- done: every wave's stores have reached device scope, then the task is counted
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (tid == 0) s_ticket = next;
@@ -655,10 +701,12 @@ __global__ __launch_bounds__(FL_THREADS, 4) void flow_kernel(const FlowParams)
 
 Div make_div(unsigned d) { return Div{d, d == 1 ? 0u : (unsigned)((0x100000000ull + d - 1) / d)}; }
 
-template <int KD, int NQ, int N1, int NP, bool SUM> int launch_flow_t(FlowParams &p, hipStream_t st)
+template <typename E, int KD, int NQ, int N1, int NP, bool SUM> int launch_flow_t(FlowParams &p, hipStream_t st)
 {
-    constexpr int LDS = 8 * 8192 + 2048;                       // attention's partial outputs; two workgroups per CU
-    static_assert(LDS >= 32 * 32 * KD * 2 + (NQ > N1 ? NQ : N1) * 8192 + 16384 && LDS >= 65536 && 2 * LDS <= 160 * 1024 - 128, "LDS budget");
+    constexpr int PER_CU = sizeof(E) == 2 ? 2 : 1;             // (single precision: fragments of twice the registers)
+    constexpr int ATT = 8 * 8192 + 2048, NORM = 32 * 32 * KD * (int)sizeof(E) + (NQ > N1 ? NQ : N1) * 8192 + 16384;
+    constexpr int LDS = ATT > NORM ? ATT : NORM;               // attention's partial outputs; rows, partial sums and shrink of a norm task
+    static_assert(PER_CU * LDS <= 160 * 1024 - 128, "LDS budget");
     const FlowArgs &a = p.a;
     const int nrt = p.nrt;
     p.nQ = NQ;
@@ -668,8 +716,8 @@ template <int KD, int NQ, int N1, int NP, bool SUM> int launch_flow_t(FlowParams
     p.a_p2 = 2 * p.ct_d / NP; p.a_1 = p.ct_m / N1;
     // one workgroup per CU while that gives every block of a queue 32 of them or more, else two (DeiT-tiny, twelve layers, 256 / 512 of them:
     // 4 blocks 249 / 271 us, 8 blocks 314 / 334, 9 blocks 372 / 368, 12 blocks 426 / 408, 20 blocks 599 / 488)
-    const long all = (long)p.tpb * a.nb, most = a.nb <= FL_MAXQ ? 256 : 512;
-    auto kern = flow_kernel<KD, 24, NQ, N1, NP, SUM>;
+    const long all = (long)p.tpb * a.nb, most = a.nb <= FL_MAXQ || PER_CU == 1 ? 256 : 512;
+    auto kern = flow_kernel<E, KD, 24, NQ, N1, NP, SUM>;
     static bool attr_set = false;   // raising the dynamic LDS limit is a per-kernel, process-wide setting
     if (!attr_set) {
         if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS) != hipSuccess) return POLY_EHIP;
@@ -679,18 +727,19 @@ template <int KD, int NQ, int N1, int NP, bool SUM> int launch_flow_t(FlowParams
     return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
 }
 
-template <int KD, int NQ, int N1, int NP> int launch_flow_n(FlowParams &p, hipStream_t st)
+template <typename E, int KD, int NQ, int N1, int NP> int launch_flow_n(FlowParams &p, hipStream_t st)
 {
-    return p.a.set_off ? launch_flow_t<KD, NQ, N1, NP, true>(p, st) : launch_flow_t<KD, NQ, N1, NP, false>(p, st);
+    return p.a.set_off ? launch_flow_t<E, KD, NQ, N1, NP, true>(p, st) : launch_flow_t<E, KD, NQ, N1, NP, false>(p, st);
 }
 
-template <int KD> int launch_flow_d(FlowParams &p, hipStream_t st)
+template <int KD> int launch_flow_d(FlowParams &p, int dtype, hipStream_t st)
 {
+    if (dtype == POLY_F32) return launch_flow_n<float, KD, 1, 2, 1>(p, st);
     // Coarse tasks (all three tiles of a head, four of the hidden width, two of the output) load the rows and hand over once for several
     // tiles, but a stage of one block is then 21 tasks: better from five blocks on (1 block 201 / 232 us, 4 blocks 249 / 254, 5 blocks
     // 288 / 254, 8 blocks 385 / 314, 16 blocks 424 / 412 for the twelve layers of DeiT-tiny, fine / coarse)
-    if (p.a.nb > 4 && p.ct_m % 4 == 0) return launch_flow_n<KD, 3, 4, 2>(p, st);
-    return launch_flow_n<KD, 1, 2, 1>(p, st);
+    if (p.a.nb > 4 && p.ct_m % 4 == 0) return launch_flow_n<bf16_t, KD, 3, 4, 2>(p, st);
+    return launch_flow_n<bf16_t, KD, 1, 2, 1>(p, st);
 }
 
 }  // namespace
@@ -704,7 +753,7 @@ bool flow_supported(int T, int D, int Dm, int heads, int r, bool lora)
 size_t flow_counter_bytes(int nb, int heads) { return 64 * (size_t)(FL_MAXQ + (size_t)nb * (C_Q + heads)); }
 size_t flow_elements(int T, int D) { return (size_t)D * ((T + 31) / 32 * 32); }
 
-int launch_flow(const FlowArgs &args, hipStream_t st)
+int launch_flow(const FlowArgs &args, int dtype, hipStream_t st)
 {
     if (args.nb <= 0 || args.layers <= 0) return POLY_OK;
     FlowParams p;
@@ -717,9 +766,9 @@ int launch_flow(const FlowArgs &args, hipStream_t st)
     p.queue = args.counters;
     p.cnt = args.counters + FL_MAXQ * 16;
     switch (args.D) {
-    case 64: return launch_flow_d<2>(p, st);
-    case 128: return launch_flow_d<4>(p, st);
-    case 192: return launch_flow_d<6>(p, st);
+    case 64: return launch_flow_d<2>(p, dtype, st);
+    case 128: return launch_flow_d<4>(p, dtype, st);
+    case 192: return launch_flow_d<6>(p, dtype, st);
     default: return POLY_EINVAL;
     }
 }

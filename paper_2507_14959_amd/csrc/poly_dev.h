@@ -302,14 +302,14 @@ struct FlowArgs {
     float *x;                        // [nb][T][D]: the residual stream after the last layer (may be x_in)
     float *x1, *x2;                  // [layers][nb][T][D]: after proj, and [layers - 1][nb][T][D]: after the layer
     const float *ln1_g, *ln1_b, *ln2_g, *ln2_b;
-    const bf16_t *Wq, *Wp, *W1, *W2;
+    const void *Wq, *Wp, *W1, *W2;   // these, the adapters and q .. h: elements of the model's type
     const float *bq, *bp, *b1, *b2;
-    const bf16_t *At[4], *Bt[4];     // adapter stacks of qkv, proj, fc1, fc2; null = none
+    const void *At[4], *Bt[4];       // adapter stacks of qkv, proj, fc1, fc2; null = none
     int n_adapters, r;
     float scale;
     const int *adapter_of_row;
     const int *set_off;              // null: block b has the one term adapter_of_row[b]; else the sum of the terms [set_off[b], set_off[b + 1])
-    bf16_t *qk, *vt, *o, *h;         // [layers][nb][flow_elements(T, ..)] of 2 D, D, D and Dm
+    void *qk, *vt, *o, *h;           // [layers][nb][flow_elements(T, ..)] of 2 D, D, D and Dm
     unsigned *counters;              // flow_counter_bytes, cleared by an earlier launch
     int patience;                    // looks at a counter that is not there yet, per workgroup; < 0: as many as flow.hip finds enough
     PolyMeta *meta;                  // a workgroup that has run out of them sets stalled, no blocks, and the status here ..
@@ -319,7 +319,7 @@ struct FlowArgs {
 bool flow_supported(int T, int D, int Dm, int heads, int r, bool lora);
 size_t flow_counter_bytes(int nb, int heads);
 size_t flow_elements(int T, int D);
-int launch_flow(const FlowArgs &a, hipStream_t st);
+int launch_flow(const FlowArgs &a, int dtype, hipStream_t st);
 
 // y = LayerNorm(x) row-wise; x float [n*T][D] -> elt [n*T][D]
 int launch_layernorm(const float *x, void *y, const float *gain, const float *shift, int D, float eps, int T,
