@@ -43,6 +43,10 @@ int poly_profile_end(poly_profile *out); /* host struct */
  * now on; negative = the built-in limit (the default).  For tests of what a call does when that kernel gives up (POLY_ESTALL). */
 void poly_wait_limit(int looks);
 
+/* Workgroups of a launch of the wide models' task queue, at most, in calls of the calling thread from now on; 0 = one per CU (the default).  For tests
+ * of its progress with fewer workgroups than queues. */
+void poly_wait_workgroups(int most);
+
 #ifdef __cplusplus
 }
 #endif

@@ -23,7 +23,7 @@ LIB_PATH = os.path.join(_HERE, "libpoly.so")
 EXPORTS = ("poly_status_string", "poly_select_state_bytes", "poly_select", "poly_forward_workspace_bytes",
            "poly_forward", "poly_stream_step_workspace_bytes", "poly_stream_step", "poly_lora_linear_workspace_bytes",
            "poly_lora_linear", "poly_lora_linear_static", "poly_build_contexts", "poly_intra_coherence", "poly_stream_metrics",
-           "poly_profile_begin", "poly_profile_end", "poly_wait_limit")
+           "poly_profile_begin", "poly_profile_end", "poly_wait_limit", "poly_wait_workgroups")
 STATIC_SCRATCH_BYTES = 4 * 1024 * 1024
 STAGES = ("select", "gemm", "shrink", "attention", "layernorm", "other")
 
@@ -113,6 +113,8 @@ def lib():
         L.poly_profile_end.argtypes = [C.POINTER(Profile)]
         L.poly_wait_limit.restype = None
         L.poly_wait_limit.argtypes = [C.c_int]
+        L.poly_wait_workgroups.restype = None
+        L.poly_wait_workgroups.argtypes = [C.c_int]
         _lib = L
     return _lib
 

@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpoly.so")
-SOURCES = ["api.hip", "gemm.hip", "gemm_ks.hip", "attention.hip", "rowops.hip", "select.hip", "profile.hip", "rowlin.hip", "mlp.hip", "rowlayer.hip", "rowreg.hip", "flow.hip", "contexts.cpp"]
+SOURCES = ["api.hip", "gemm.hip", "gemm_ks.hip", "attention.hip", "rowops.hip", "select.hip", "profile.hip", "rowlin.hip", "mlp.hip", "rowlayer.hip", "rowreg.hip", "flow.hip", "flow_wide.hip", "contexts.cpp"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed fp32 ops are kept out of the generated code on the test machines
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -22,7 +22,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
         s = os.path.join(CSRC, src)
         o = os.path.join(HERE, "_build", os.path.splitext(src)[0] + ".o")
         objs.append(o)
-        deps = [s, os.path.join(CSRC, "poly_dev.h"), os.path.join(CSRC, "rowtile.h"), os.path.join(CSRC, "gemm_tiles.h"), os.path.join(HERE, "..", "include", "poly.h"), os.path.join(HERE, "..", "include", "poly_profile.h")]
+        deps = [s, os.path.join(CSRC, "poly_dev.h"), os.path.join(CSRC, "rowtile.h"), os.path.join(CSRC, "gemm_tiles.h"), os.path.join(CSRC, "flow_dev.h"), os.path.join(HERE, "..", "include", "poly.h"), os.path.join(HERE, "..", "include", "poly_profile.h")]
         if not force and os.path.exists(o) and all(os.path.getmtime(o) >= os.path.getmtime(d) for d in deps):
             continue
         if src.endswith(".cpp"):   # host-only source

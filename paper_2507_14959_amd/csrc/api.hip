@@ -30,12 +30,17 @@ struct FlowSegment {
 // tiles) 469 / 487 us, 20 (140) 494 / 491, 24 (168) 509 / 503, 32 (224) 624 / 509; 70 blocks of 50 tokens (140) 427 / 438, 96 (192) 533 / 462;
 // GEMM path, rank 32: 32 blocks of 197 tokens (224) 644 / 748, 45 (315) 883 / 791; summed terms: 678 / 835 and 936 / 895, 60 blocks of 113
 // tokens (240) 729 / 828, 80 (320) 894 / 871.
+// The 768-wide backbone: 7 tiles in the shared layers, 21 in the adapted ones, which layer by layer have four shrinks more.  Forward, us: ten layers shared,
+// 1 tile 444 / 483, 4 493 / 567, 7 490 / 626, 8 600 / 579, 10 590 / 572; adapted on every linear, 1 tile 462 / 716, 7 502 / 891, 14 654 / 929, 21 773 / 981,
+// 21 of which 13 exist 569 / 936, 42 with 25 1136 / 1106.
 // Single precision: 270 tiles times the part of their rows that exist, for the other way runs its rows across blocks.  Two layers of 192 columns, us,
 // as tasks / layer by layer, every frame with one adapter: 32 blocks of 197 tokens (224 tiles) 422 / 453, 24 (168) 321 / 336, 4 (28) 96 / 189;
 // 64 of 101 (256) 463 / 436, 32 (128) 252 / 287; 64 of 50 (128) 251 / 274; 64 of 17 (64) 137 / 160, 115 of at most 192 235 / 222, 4 76 / 127.
 int flow_limit(const poly_model_desc *m, bool adapted)
 {
     const int T = tokens(m), r = adapted ? m->r : 0, tgt = adapted ? m->targets & 15 : 0;
+    if (m->dtype == POLY_BF16 && !(adapted && m->compose == POLY_COMPOSE_SUM && tgt) && flow_wide_supported(T, m->D, m->Dm, m->heads, r, tgt != 0))
+        return (adapted && tgt ? 21 : 7) / ((T + 31) / 32);
     if (!flow_supported(T, m->D, m->Dm, m->heads, r, tgt != 0)) return 0;
     if (m->dtype == POLY_F32) return 270 * T / (32 * ((T + 31) / 32) * ((T + 31) / 32));
     const bool row_kernel = !(tgt & 12) && !(adapted && m->compose == POLY_COMPOSE_SUM && tgt) && rowlayer_supported(m->D, m->Dm, tgt ? r : 0);
@@ -287,7 +292,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         const FlowBuffers &f = w.fl[ad];
         a.qk = f.qk; a.vt = f.vt; a.o = f.o; a.h = f.h; a.x1 = f.x1; a.x2 = f.x2;
         a.counters = w.fl_cnt[ad];
-        a.patience = poly_patience(); a.meta = w.meta; a.dev_status = dev_status;
+        a.patience = poly_patience(); a.workgroups = poly_workgroups(); a.meta = w.meta; a.dev_status = dev_status;
         const int first = ad ? m->L0 : 0, last = ad ? m->L : m->L0;
         for (int l = first; l < last; l += a.layers) {
             a.layers = last - l < w.fl_layers[ad] ? last - l : w.fl_layers[ad];

@@ -136,6 +136,7 @@ __device__ __forceinline__ f32x4 gelu_tab4(f32x4 x, const float (&xc)[4], const 
 // ---- launch with optional per-stage timing (profile.hip) ----
 bool poly_prof_next(int stage, hipEvent_t *a, hipEvent_t *b);
 int poly_patience();     // FlowArgs::patience of this thread's calls
+int poly_workgroups();   // and FlowArgs::workgroups
 
 #define POLY_LAUNCH(stage, kernel, grid, block, st, ...)                                         \
     do {                                                                                         \
@@ -312,14 +313,17 @@ struct FlowArgs {
     void *qk, *vt, *o, *h;           // [layers][nb][flow_elements(T, ..)] of 2 D, D, D and Dm
     unsigned *counters;              // flow_counter_bytes, cleared by an earlier launch
     int patience;                    // looks at a counter that is not there yet, per workgroup; < 0: as many as flow.hip finds enough
+    int workgroups;                  // at most so many of them in a launch of flow_wide.hip; 0: as many as there are CUs
     PolyMeta *meta;                  // a workgroup that has run out of them sets stalled, no blocks, and the status here ..
     int *dev_status;                 // .. and here (or null)
     int n_queues;                    // set by launch_flow
 };
 bool flow_supported(int T, int D, int Dm, int heads, int r, bool lora);
+bool flow_wide_supported(int T, int D, int Dm, int heads, int r, bool lora);   // the same for a wide model (flow_wide.hip): bf16, one term per block
 size_t flow_counter_bytes(int nb, int heads);
 size_t flow_elements(int T, int D);
 int launch_flow(const FlowArgs &a, int dtype, hipStream_t st);
+int launch_flow_wide(const FlowArgs &a, int patience, hipStream_t st);   // called by launch_flow
 
 // y = LayerNorm(x) row-wise; x float [n*T][D] -> elt [n*T][D]
 int launch_layernorm(const float *x, void *y, const float *gain, const float *shift, int D, float eps, int T,

@@ -10,11 +10,13 @@ struct Record { int stage; hipEvent_t a, b; };
 std::vector<Record> g_pool;
 size_t g_used = 0;
 bool g_on = false;
-thread_local int t_patience = -1;
+thread_local int t_patience = -1, t_workgroups = 0;
 }  // namespace
 
 int poly_patience() { return t_patience; }
 extern "C" void poly_wait_limit(int looks) { t_patience = looks; }
+int poly_workgroups() { return t_workgroups; }
+extern "C" void poly_wait_workgroups(int most) { t_workgroups = most; }
 
 bool poly_prof_next(int stage, hipEvent_t *a, hipEvent_t *b)
 {
