@@ -27,9 +27,9 @@
 // the kernel has to come to its end all the same, so a workgroup looks at counters a limited number of times per launch (a million, about
 // a second; a whole launch takes under a millisecond), then works on without waiting and the call reports POLY_ESTALL.
 //
-// What bounds it: the chain of a block, five steps per layer with a hand-over each.  DeiT-tiny, one live frame: 15.7 us per layer (two launches
-// of ten and two layers), the matrix unit busy 0.7 % of the time; the lagged loop takes 209 us instead of the 473 of row kernels and
-// attention launches.  With many blocks the weights that every 32-row task pulls through its CU's load path bound it, and kernels with
+// What bounds it: the chain of a block, five steps per layer with a hand-over each, four where P is part of the F1 tasks (few tiles: launch_flow_d).  DeiT-tiny,
+// one live frame: 14.9 us per layer (15.7 in five steps; two launches of ten and two layers), the matrix unit busy 0.7 % of the time; the lagged loop takes
+// 200 us instead of the 473 of row kernels and attention launches.  With many blocks the weights that every 32-row task pulls through its CU's load path bound it, and kernels with
 // larger tiles take over (api.hip).
 //
 // Single precision: the same tasks on v_mfma_f32_16x16x4_f32, elements and buffers of twice the size, one workgroup per CU (190 registers).  The same
@@ -42,9 +42,18 @@ namespace {
 __device__ __forceinline__ f32x4 gelu(f32x4 v, bf16_t) { return gelu_fine4(v); }
 __device__ __forceinline__ f32x4 gelu(f32x4 v, float) { return f32x4{gelu_erf(v[0]), gelu_erf(v[1]), gelu_erf(v[2]), gelu_erf(v[3])}; }
 
+// LDS of a norm task: rows, partial sums that the halves of K hand over (NT x 8 KB; with proj in it KD / 2 x 8 KB), shrink [quarter of K][row half][rank
+// tile][lane], with proj in it the rows of the stream
+template <typename E> constexpr int norm_red(int kd, int nt, bool pre) { return (pre && kd / 2 > nt ? kd / 2 : nt) * 8192; }
+template <typename E> constexpr int norm_lds(int kd, int nt, bool pre)
+{
+    return 32 * 32 * kd * (int)sizeof(E) + norm_red<E>(kd, nt, pre) + 16384 + (pre ? 32 * (32 * kd + 4) * 4 : 0);
+}
+
 // ---- LayerNorm + linear on 32 rows x NT tiles of 64 columns; STAGE: 0 Q, 3 F1.  The normalised rows go through LDS; wave (kh, wc)
-// takes half kh of the contraction for the 16 columns 16 wc .. of a tile, both row halves; returns the counter to raise
-template <typename E, int KD, int STAGE, int NT, bool SUM>
+// takes half kh of the contraction for the 16 columns 16 wc .. of a tile, both row halves; returns the counter to raise.
+// PRE: the rows are not read but made here, x1 = x + o Wp + bp (+ low rank), by every task of these rows, and the first of them stores them for F2
+template <typename E, int KD, int STAGE, int NT, bool SUM, bool PRE>
 __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
 {
     typedef El<E> L;
@@ -54,20 +63,31 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
     constexpr int D = 32 * KD, KT = KD / 2, HK = KD / 2;       // HK: K steps of a wave
     constexpr int NA = (KD + 3) / 4;                           // K steps of a wave's share of the shrink
     E *As = (E *)lds;                                          // rows: 32 x D, chunks of eight swizzled by row
-    char *red = lds + 32 * D * sizeof(E);                             // partial sums that the halves of K hand over: NT x 8 KB
-    char *shr = red + NT * 8192;                               // shrink [quarter of K][row half][rank tile][lane]: 16 KB
+    char *red = lds + 32 * D * sizeof(E), *shr = red + norm_red<E>(KD, NT, PRE);
     const ParamPtr p = params();
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lm = lane & 15, g = lane >> 4;
     const int kh = wave >> 2, wc = wave & 3, T = p->a.T, t0 = k.rt * 32, b = k.b;
     const size_t ld = k.layer;
-    const unsigned *dep = counter(k, (STAGE == 0 ? C_F2 : C_P) + k.rt);
-    const unsigned want = (k.layer + (STAGE == 0 ? 0 : 1)) * p->a_p2;
+    const unsigned *dep = counter(k, (STAGE == 0 ? C_F2 : PRE ? C_A : C_P) + k.rt);
+    const unsigned want = (k.layer + (STAGE == 0 ? 0 : 1)) * (PRE ? p->a.heads : p->a_p2);
     unsigned seen = 0;
     if (wave == 0) seen = peek(dep);
     const int N = STAGE == 0 ? 3 * D : p->a.Dm, dt = p->ct_d;
     // tile i of the task: q, k and v of one head, or neighbours
     auto tile = [&](int i) { return STAGE == 0 ? k.ct + i * dt : k.ct * NT + i; };
     auto is_v = [&](int i) { return STAGE == 0 && tile(i) >= 2 * dt; };            // V: product untransposed
+    constexpr int PT = KT;                                     // PRE: 16-column tiles of proj a wave takes
+    op_t wp[PT][HK];
+    f32x4 biasp[PT];
+    if constexpr (PRE) {
+        const E *Wp = (const E *)p->a.Wp + (ld * D + wc * PT * 16 + lm) * D + kh * HK * 32 + 8 * g;
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+#pragma unroll
+            for (int j = 0; j < HK; ++j) wp[t][j] = *(const op_t *)(Wp + (size_t)t * 16 * D + 32 * j);
+            biasp[t] = *(const f32x4_u *)(p->a.bp + ld * D + (wc * PT + t) * 16 + 4 * g);
+        }
+    }
     const E *W = (const E *)(STAGE == 0 ? p->a.Wq : p->a.W1) + ld * N * D + (size_t)(wc * 16 + lm) * D + kh * HK * 32 + 8 * g;
     const float *bias = (STAGE == 0 ? p->a.bq : p->a.b1) + ld * N + wc * 16;
     op_t wf[NT][HK];
@@ -127,18 +147,134 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
         }
     };
     if (s0 < s1) { load_at(s0); load_bt(s0); }
-    const bool first = STAGE == 0 && k.layer == 0;             // the stream still lies where the caller put it
+    const bool first = (STAGE == 0 || PRE) && k.layer == 0;    // the stream still lies where the caller put it
     const int xblk = first && in_map ? uload(in_map + b) : b;
-    const size_t step = (size_t)p->a.nb * T * D;
-    const float *xs = STAGE == 3 ? p->a.x1 + ld * step : first ? p->a.x_in : p->a.x2 + (ld - 1) * step;
+    const size_t step = (size_t)p->a.nb * T * D, slot = ld * p->a.nb + b;
+    const int TP = p->nrt * 32;
+    const float *xs = STAGE == 3 && !PRE ? p->a.x1 + ld * step : first ? p->a.x_in : p->a.x2 + (ld - 1) * step;
     const Buf xb(xs + (size_t)xblk * T * D, (unsigned)T * D * 4);
+    // the shrink of a term is shared by the waves (row half kh, K steps wc, wc + 4), the partial sums meet in LDS, and ranks 4 g .. and 16 + 4 g ..
+    // of row lm are what a lane feeds to the expand
+    auto shrink_store = [&](const f32x4(&sp)[2]) {
+        *(f32x4 *)(shr + (((wc * 2 + kh) * 2 + 0) * 64 + lane) * 16) = sp[0];
+        if (nrk > 1) *(f32x4 *)(shr + (((wc * 2 + kh) * 2 + 1) * 64 + lane) * 16) = sp[1];
+    };
+    auto shrink_sum = [&]() {
+        quad_t fs[2] = {z4, z4};
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (q < nrk) {
+                f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int w = 0; w < 4; ++w) t += *(const f32x4 *)(shr + (((w * 2 + kh) * 2 + q) * 64 + lane) * 16);
+                fs[q] = L::round4(t * p->a.scale);
+            }
+        return L::join(fs[0], fs[1]);
+    };
+    float *x1s = (float *)(shr + 16384);                       // PRE: rows of D + 4 floats
+    // PRE: operands of proj's low-rank terms
+    const E *Atp = PRE ? (const E *)p->a.At[1] : nullptr, *Btp = PRE ? (const E *)p->a.Bt[1] : nullptr;
+    const int p0 = Atp ? (SUM ? uload(set_off + b) : b) : 0, p1 = Atp ? (SUM ? uload(set_off + b + 1) : b + 1) : 0;
+    op_t fap[PRE ? NA : 1][2], fbp[PRE ? PT : 1];
+    auto load_p = [&](int s) {
+        if constexpr (PRE) {
+            const size_t ad = p->a.n_adapters * ld + uload(adapter + s);
+#pragma unroll
+            for (int i = 0; i < NA; ++i) {
+                const E *Ak = Atp + ad * r * D + 8 * g + 32 * min(wc + 4 * i, KD - 1);
+                fap[i][0] = *(const op_t *)(Ak + (size_t)min(lm, r - 1) * D);
+                if (nrk > 1) fap[i][1] = *(const op_t *)(Ak + (size_t)min(16 + lm, r - 1) * D);
+            }
+#pragma unroll
+            for (int t = 0; t < PT; ++t) {
+                const E *bt = Btp + (ad * D + (wc * PT + t) * 16 + lm) * r + 4 * g;
+                quad_t lo = *(const quad_t *)(bt + min(0, r - 4 - 4 * g)), hi = z4;
+                if (4 * g >= r) lo = z4;
+                if (nrk > 1) {
+                    hi = *(const quad_t *)(bt + min(16, r - 4 - 4 * g));
+                    if (16 + 4 * g >= r) hi = z4;
+                }
+                fbp[t] = L::join(lo, hi);
+            }
+        }
+    };
+    if (p0 < p1) load_p(p0);
     // ---- inputs
     if (wave == 0) await(k, dep, seen, want);
     __syncthreads();
+    if constexpr (PRE) {
+        const Buf src((const E *)p->a.o + slot * TP * D, (unsigned)TP * D * 2 * ES);
+        auto load_o = [&](int m, int j) { return L::load(src, (((k.rt * 2 + m) * KD + j) * 1024 + lane * 16) * ES); };
+        op_t fo[2][HK], fos[NA];
+        f32x4 res[PT];
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int j = 0; j < HK; ++j) fo[m][j] = load_o(m, kh * HK + j);
+        if (p0 < p1) {
+#pragma unroll
+            for (int i = 0; i < NA; ++i) fos[i] = load_o(kh, min(wc + 4 * i, KD - 1));
+        }
+        const int xrow = t0 + 16 * kh + lm;
+        const unsigned xoff = ((unsigned)min(xrow, T - 1) * D + wc * PT * 16 + 4 * g) * 4;
+#pragma unroll
+        for (int t = 0; t < PT; ++t) res[t] = __builtin_bit_cast(f32x4, xb.ld16(xoff + 64 * t));
+        auto shrink_o = [&]() {
+            f32x4 sp[2] = {};
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+                if (wc + 4 * i < KD) {
+                    sp[0] = L::mma(fap[i][0], fos[i], sp[0]);
+                    if (nrk > 1) sp[1] = L::mma(fap[i][1], fos[i], sp[1]);
+                }
+            shrink_store(sp);
+        };
+        f32x4 y[PT];
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+            f32x4 acc[2] = {};
+#pragma unroll
+            for (int j = 0; j < HK; ++j)
+#pragma unroll
+                for (int m = 0; m < 2; ++m) acc[m] = L::mma(wp[t][j], fo[m][j], acc[m]);
+            *(f32x4 *)(red + ((t * 8 + wave) * 64 + lane) * 16) = kh ? acc[0] : acc[1];
+            y[t] = kh ? acc[1] : acc[0];
+        }
+        if (p0 < p1) shrink_o();
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+            const f32x4 other = *(const f32x4 *)(red + ((t * 8 + (wave ^ 4)) * 64 + lane) * 16);
+            y[t] = kh ? other + y[t] : y[t] + other;
+        }
+        for (int s = p0; s < p1; ++s) {
+            if (SUM && s > p0) {                               // further terms summed on this block
+                load_p(s);
+                __syncthreads();
+                shrink_o();
+                __syncthreads();
+            }
+            const op_t fs = shrink_sum();
+#pragma unroll
+            for (int t = 0; t < PT; ++t) y[t] = L::mma(fbp[t], fs, y[t]);
+            if (!SUM) break;
+        }
+        const Buf xo(p->a.x1 + ld * step + (size_t)b * T * D, (unsigned)T * D * 4);
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+            const f32x4 v = y[t] + biasp[t] + res[t];
+            *(f32x4 *)(x1s + (16 * kh + lm) * (D + 4) + (wc * PT + t) * 16 + 4 * g) = v;
+            if (k.ct == 0 && xrow < T) xo.st16(__builtin_bit_cast(u32x4_, v), xoff + 64 * t);
+        }
+        __syncthreads();
+    }
     {
         f32x4 v[KT];
 #pragma unroll
-        for (int i = 0; i < KT; ++i) v[i] = __builtin_bit_cast(f32x4, xb.ld16(((unsigned)rrow * D + 4 * (part + 16 * i)) * 4));
+        for (int i = 0; i < KT; ++i) {
+            if constexpr (PRE) v[i] = *(const f32x4 *)(x1s + row * (D + 4) + 4 * (part + 16 * i));
+            else v[i] = __builtin_bit_cast(f32x4, xb.ld16(((unsigned)rrow * D + 4 * (part + 16 * i)) * 4));
+        }
         if (LEAN) load_gain();
         float t = 0.f;
 #pragma unroll
@@ -163,8 +299,6 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
     if (tid == 0) draw(k);
     // fragment of rows 16 m + lm, K step i: chunk 4 i + g
     auto frag_a = [&](int m, int i) { return *(const op_t *)(As + (16 * m + lm) * D + (((4 * i + g) ^ (lm & 7)) << 3)); };
-    // the shrink is shared by the waves (row half kh, K steps wc, wc + 4), the partial sums meet in LDS, and ranks 4 g .. and 16 + 4 g ..
-    // of row lm are what a lane feeds to the expand
     auto shrink_part = [&]() {
         f32x4 sp[2] = {};
 #pragma unroll
@@ -174,20 +308,7 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
                 sp[0] = L::mma(fat[i][0], fa, sp[0]);
                 if (nrk > 1) sp[1] = L::mma(fat[i][1], fa, sp[1]);
             }
-        *(f32x4 *)(shr + (((wc * 2 + kh) * 2 + 0) * 64 + lane) * 16) = sp[0];
-        if (nrk > 1) *(f32x4 *)(shr + (((wc * 2 + kh) * 2 + 1) * 64 + lane) * 16) = sp[1];
-    };
-    auto shrink_sum = [&]() {
-        quad_t fs[2] = {z4, z4};
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-            if (q < nrk) {
-                f32x4 t = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int w = 0; w < 4; ++w) t += *(const f32x4 *)(shr + (((w * 2 + kh) * 2 + q) * 64 + lane) * 16);
-                fs[q] = L::round4(t * p->a.scale);
-            }
-        return L::join(fs[0], fs[1]);
+        shrink_store(sp);
     };
     if (s0 < s1) shrink_part();
     f32x4 y[NT];                                               // the row half that this wave finishes: 16 kh ..
@@ -233,8 +354,6 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
         }
         if (!SUM) break;
     }
-    const size_t slot = ld * p->a.nb + b;
-    const int TP = p->nrt * 32;
     // q and k as [head][16 rows][32 columns][lane][8], v as [head][32 rows][16 columns][lane][rows 4 g .., 16 + 4 g ..]: attention
     // reads 1 KB per instruction (rows past T repeat row T - 1: finite, and masked there)
     const Buf vt((const E *)p->a.vt + slot * D * TP, (unsigned)D * TP * 2 * ES), qk((const E *)p->a.qk + slot * TP * 2 * D, (unsigned)TP * 4 * D * ES),
@@ -409,8 +528,9 @@ __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
 }
 
 // KD: K steps of 32 in the model width.  CH: K steps at most in the hidden width
-template <typename E, int KD, int CH, int NQ, int N1, int NP, bool SUM>
-__global__ __launch_bounds__(FL_THREADS, sizeof(E) == 2 ? 4 : 2) void flow_kernel(const FlowParams)
+// PRE: proj is in the F1 tasks
+template <typename E, int KD, int CH, int NQ, int N1, int NP, bool SUM, bool PRE>
+__global__ __launch_bounds__(FL_THREADS, sizeof(E) == 2 && !PRE ? 4 : 2) void flow_kernel(const FlowParams)
 {
     extern __shared__ __attribute__((aligned(16))) char fl_lds[];
     __shared__ unsigned s_ticket;
@@ -444,8 +564,8 @@ __global__ __launch_bounds__(FL_THREADS, sizeof(E) == 2 ? 4 : 2) void flow_kerne
             const Div dQ = {p->dQ.d, p->dQ.m}, dA = {p->dA.d, p->dA.m}, dP = {p->dP.d, p->dP.m}, d1 = {p->d1.d, p->d1.m};
             if (rem < nbq * dQ.d) bi = div(rem, dQ), rem -= bi * dQ.d;
             else if ((rem -= nbq * dQ.d) < nbq * dA.d) stage = 1, bi = div(rem, dA), rem -= bi * dA.d;
-            else if ((rem -= nbq * dA.d) < nbq * dP.d) stage = 2, bi = div(rem, dP), rem -= bi * dP.d;
-            else if ((rem -= nbq * dP.d) < nbq * d1.d) stage = 3, bi = div(rem, d1), rem -= bi * d1.d;
+            else if ((rem -= nbq * dA.d) < (PRE ? 0 : nbq * dP.d)) stage = 2, bi = div(rem, dP), rem -= bi * dP.d;
+            else if ((rem -= (PRE ? 0 : nbq * dP.d)) < nbq * d1.d) stage = 3, bi = div(rem, d1), rem -= bi * d1.d;
             else rem -= nbq * d1.d, stage = 4, bi = div(rem, dP), rem -= bi * dP.d;
             Task k;
             unsigned next = 0;
@@ -454,10 +574,10 @@ __global__ __launch_bounds__(FL_THREADS, sizeof(E) == 2 ? 4 : 2) void flow_kerne
             k.ct = div(rem, Div{p->drt.d, p->drt.m}); k.rt = rem - k.ct * p->nrt; k.b = qn + bi * nq;
             k.cnt = p->cnt + (size_t)k.b * p->ncnt * 16;
             unsigned *done;
-            if (stage == 0) done = norm_task<E, KD, 0, NQ, SUM>(k, fl_lds);
+            if (stage == 0) done = norm_task<E, KD, 0, NQ, SUM, false>(k, fl_lds);
             else if (stage == 1) done = attention_task<E, KD, false>(k, fl_lds);
-            else if (stage == 2) done = resid_task<E, KD, CH, 2, NP, SUM>(k, fl_lds);
-            else if (stage == 3) done = norm_task<E, KD, 3, N1, SUM>(k, fl_lds);
+            else if (!PRE && stage == 2) done = resid_task<E, KD, CH, 2, NP, SUM>(k, fl_lds);
+            else if (stage == 3) done = norm_task<E, KD, 3, N1, SUM, PRE>(k, fl_lds);
             else done = resid_task<E, KD, CH, 4, NP, SUM>(k, fl_lds);
             // ---- done: every wave's stores have reached device scope, then the task is counted
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -479,23 +599,23 @@ __global__ __launch_bounds__(FL_THREADS, sizeof(E) == 2 ? 4 : 2) void flow_kerne
 
 Div make_div(unsigned d) { return Div{d, d == 1 ? 0u : (unsigned)((0x100000000ull + d - 1) / d)}; }
 
-template <typename E, int KD, int NQ, int N1, int NP, bool SUM> int launch_flow_t(FlowParams &p, hipStream_t st)
+template <typename E, int KD, int NQ, int N1, int NP, bool SUM, bool PRE> int launch_flow_t(FlowParams &p, hipStream_t st)
 {
-    constexpr int PER_CU = sizeof(E) == 2 ? 2 : 1;             // (single precision: fragments of twice the registers)
-    constexpr int ATT = 8 * 8192 + 2048, NORM = 32 * 32 * KD * (int)sizeof(E) + (NQ > N1 ? NQ : N1) * 8192 + 16384;
-    constexpr int LDS = ATT > NORM ? ATT : NORM;               // attention's partial outputs; rows, partial sums and shrink of a norm task
+    constexpr int PER_CU = sizeof(E) == 2 && !PRE ? 2 : 1;     // (single precision: fragments of twice the registers; proj in F1: more of them)
+    constexpr int ATT = 8 * 8192 + 2048, Q = norm_lds<E>(KD, NQ, false), F1 = norm_lds<E>(KD, N1, PRE);
+    constexpr int LDS = ATT > Q ? (ATT > F1 ? ATT : F1) : Q > F1 ? Q : F1;                // ATT: attention's partial outputs
     static_assert(PER_CU * LDS <= 160 * 1024 - 128, "LDS budget");
     const FlowArgs &a = p.a;
     const int nrt = p.nrt;
     p.nQ = NQ;
     p.dQ = make_div(nrt * 3 * p.ct_d / NQ); p.dA = make_div(nrt * a.heads); p.dP = make_div(nrt * 2 * p.ct_d / NP); p.d1 = make_div(nrt * p.ct_m / N1);
     p.drt = make_div(nrt);
-    p.tpb = p.dQ.d + p.dA.d + 2 * p.dP.d + p.d1.d;
+    p.tpb = p.dQ.d + p.dA.d + (PRE ? 1 : 2) * p.dP.d + p.d1.d;
     p.a_p2 = 2 * p.ct_d / NP; p.a_1 = p.ct_m / N1;
     // one workgroup per CU while that gives every block of a queue 32 of them or more, else two (DeiT-tiny, twelve layers, 256 / 512 of them:
     // 4 blocks 249 / 271 us, 8 blocks 314 / 334, 9 blocks 372 / 368, 12 blocks 426 / 408, 20 blocks 599 / 488)
     const long all = (long)p.tpb * a.nb, most = a.nb <= FL_MAXQ || PER_CU == 1 ? 256 : 512;
-    auto kern = flow_kernel<E, KD, 24, NQ, N1, NP, SUM>;
+    auto kern = flow_kernel<E, KD, 24, NQ, N1, NP, SUM, PRE>;
     static bool attr_set = false;   // raising the dynamic LDS limit is a per-kernel, process-wide setting
     if (!attr_set) {
         if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS) != hipSuccess) return POLY_EHIP;
@@ -505,19 +625,23 @@ template <typename E, int KD, int NQ, int N1, int NP, bool SUM> int launch_flow_
     return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
 }
 
-template <typename E, int KD, int NQ, int N1, int NP> int launch_flow_n(FlowParams &p, hipStream_t st)
+template <typename E, int KD, int NQ, int N1, int NP, bool PRE> int launch_flow_n(FlowParams &p, hipStream_t st)
 {
-    return p.a.set_off ? launch_flow_t<E, KD, NQ, N1, NP, true>(p, st) : launch_flow_t<E, KD, NQ, N1, NP, false>(p, st);
+    return p.a.set_off ? launch_flow_t<E, KD, NQ, N1, NP, true, PRE>(p, st) : launch_flow_t<E, KD, NQ, N1, NP, false, PRE>(p, st);
 }
 
 template <int KD> int launch_flow_d(FlowParams &p, int dtype, hipStream_t st)
 {
-    if (dtype == POLY_F32) return launch_flow_n<float, KD, 1, 2, 1>(p, st);
-    // Coarse tasks (all three tiles of a head, four of the hidden width, two of the output) load the rows and hand over once for several
-    // tiles, but a stage of one block is then 21 tasks: better from five blocks on (1 block 201 / 232 us, 4 blocks 249 / 254, 5 blocks
-    // 288 / 254, 8 blocks 385 / 314, 16 blocks 424 / 412 for the twelve layers of DeiT-tiny, fine / coarse)
-    if (p.a.nb > 4 && p.ct_m % 4 == 0) return launch_flow_n<bf16_t, KD, 3, 4, 2>(p, st);
-    return launch_flow_n<bf16_t, KD, 1, 2, 1>(p, st);
+    if (dtype == POLY_F32) return launch_flow_n<float, KD, 1, 2, 1, false>(p, st);
+    // Up to 30 row tiles (36 of blocks of one or two, whose attention is short) a step of fine tasks fills the chip no more than once or twice, and the chain
+    // of a block is what counts: proj goes into the F1 tasks, a hand-over less per layer for 74 KB more of weights in each.  Beyond that coarse tasks (all three
+    // tiles of a head, four of the hidden width, two of the output), which load the rows and hand over once for several tiles, two workgroups per CU.
+    // Twelve layers of DeiT-tiny, us, proj in F1 / fine with a step of its own / coarse: 1 block of 197 tokens 194 / 202 / 232, 4 (28 tiles) 229 / 252 / 254,
+    // 5 (35) 277 / 288 / 252; 1 of 101 174 / 191, 7 (28) 225 / . / 240, 8 (32) 266 / . / 252; 1 of 17 164 / 175, 5 168 / . / 216, 22 209 / . / 253,
+    // 36 254 / . / 269; 18 of 50 (36) 287 / . / 292.
+    if (p.a.nb * p.nrt <= (p.nrt <= 2 ? 36 : 30)) return launch_flow_n<bf16_t, KD, 1, 2, 1, true>(p, st);
+    if (p.ct_m % 4 == 0) return launch_flow_n<bf16_t, KD, 3, 4, 2, false>(p, st);
+    return launch_flow_n<bf16_t, KD, 1, 2, 1, false>(p, st);
 }
 
 }  // namespace

@@ -1,0 +1,36 @@
+"""The task queue on both sides of its rule: proj in the tasks of the hidden layer, or a step of its own and coarse tasks."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2507_14959_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D,Dm,hw,blocks,r,targets,L0,compose", [
+    (192, 768, 32, 36, 8, 3, 1, "branch"),       # T = 17: 36 tiles, proj in F1
+    (192, 768, 32, 37, 8, 3, 1, "branch"),       # 37: coarse
+    (192, 768, 48, 18, 20, 15, 0, "branch"),     # T = 37, 36 tiles; two rank steps, the second of four; adapters on every linear
+    (192, 768, 48, 19, 20, 15, 0, "branch"),
+    (192, 768, 112, 4, 16, 2, 1, "branch"),      # T = 197, 28 tiles; adapters on proj only
+    (192, 768, 112, 5, 16, 2, 1, "branch"),
+    (192, 512, 80, 7, 8, 7, 0, "sum"),           # T = 101, 28 tiles; terms summed on proj
+    (192, 512, 80, 8, 8, 7, 0, "sum"),
+    (128, 384, 72, 10, 4, 10, 0, "branch"),      # T = 82, 30 tiles; a hidden width that coarse tasks do not divide
+    (128, 384, 72, 11, 4, 10, 0, "sum"),
+    (64, 128, 16, 30, 32, 15, 2, "branch"),      # T = 5; one column tile of proj a wave; the largest rank
+])
+def test_against_the_oracle(D, Dm, hw, blocks, r, targets, L0, compose):
+    cfg, w, frames, _, _ = synth.make_small_case(940 + D + hw + r, dtype=synth.DT_BF16, targets=targets, L=3, F=blocks, r=r, n_adapters=5, D=D, heads=D // 64, Dm=Dm,
+                                                 hw=hw, patch=8)
+    rng = np.random.default_rng(blocks)
+    off, ids = synth.sets_to_csr([np.sort(rng.choice(5, size=2 if compose == "sum" else 1, replace=False)) for _ in range(blocks)])
+    model = binding.DeviceModel(cfg, w, L0=L0, compose=compose)
+    got = binding.run_forward(model, frames, off, ids)
+    again = binding.run_forward(model, frames, off, ids)
+    want = oracle.forward(cfg, w, frames, off, ids, L0=L0, compose=compose)["logits"]
+    err = np.abs(got["logits"] - want).max()
+    print(f"logits max-abs error {err:.2e} of up to {np.abs(want).max():.2f}")
+    assert got["status"] == 0 and np.array_equal(got["logits"], again["logits"])
+    assert err < 8e-3
