@@ -369,9 +369,9 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
     return counter(k, STAGE == 0 ? C_Q + (k.ct < dt ? k.ct : k.ct < 2 * dt ? k.ct - dt : k.ct - 2 * dt) : C_F1 + k.rt);
 }
 
-// ---- linear + residual on 32 rows x NT tiles of 32 columns; STAGE: 2 P, 4 F2.  Wave w takes the K steps w, w + 8, .. of the whole tile,
+// ---- linear + residual on 32 rows x NT tiles of 16 NC columns; STAGE: 2 P, 4 F2.  Wave w takes the K steps w, w + 8, .. of the whole tile,
 // both operands straight from memory in fragment order, and the partial sums meet in LDS; returns the counter to raise
-template <typename E, int KD, int CH, int STAGE, int NT, bool SUM>
+template <typename E, int KD, int CH, int STAGE, int NT, int NC, bool SUM>
 __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
 {
     typedef El<E> L;
@@ -390,17 +390,17 @@ __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
     unsigned seen = 0;
     if (wave == 0) seen = peek(dep);
     const int K = STAGE == 4 ? p->a.Dm : D, ks = K / 32, np = min(ks, 8);
-    const E *W = (const E *)(STAGE == 2 ? p->a.Wp : p->a.W2) + (ld * D + k.ct * NT * 32 + lm) * K + 8 * g;
-    op_t wf[NT][NS][2];
+    const E *W = (const E *)(STAGE == 2 ? p->a.Wp : p->a.W2) + (ld * D + k.ct * NT * 16 * NC + lm) * K + 8 * g;
+    op_t wf[NT][NS][NC];
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
         for (int i = 0; i < NS; ++i)
 #pragma unroll
-            for (int n = 0; n < 2; ++n) wf[j][i][n] = *(const op_t *)(W + (size_t)(j * 32 + 16 * n) * K + 32 * min(wave + 8 * i, ks - 1));
-    // waves 4 j .. 4 j + 3 finish the subtiles of tile j: rows 16 fm .., columns 16 fn ..
-    const int fm = (wave >> 1) & 1, fn = wave & 1, trow = k.rt * 32 + 16 * fm + lm, fcol = (k.ct * NT + (wave >> 2)) * 32 + 16 * fn;
-    const bool fin = wave < 4 * NT;
+            for (int n = 0; n < NC; ++n) wf[j][i][n] = *(const op_t *)(W + (size_t)(j * 16 * NC + 16 * n) * K + 32 * min(wave + 8 * i, ks - 1));
+    // waves 2 NC j .. finish the subtiles of tile j: rows 16 fm .., columns 16 fn ..
+    const int fj = wave / (2 * NC), fm = (wave / NC) & 1, fn = wave & (NC - 1), trow = k.rt * 32 + 16 * fm + lm, fcol = ((k.ct * NT + fj) * NC + fn) * 16;
+    const bool fin = wave < 2 * NC * NT;
     const f32x4 bias4 = *(const f32x4_u *)((STAGE == 2 ? p->a.bp : p->a.b2) + ld * D + (fin ? fcol : 0) + 4 * g);
     constexpr int TGT = STAGE == 2 ? 1 : 3;
     const E *At = (const E *)p->a.At[TGT], *Bt = (const E *)p->a.Bt[TGT];
@@ -486,19 +486,19 @@ __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
             fs1 = shrink_sum();
             __syncthreads();
         }
-        f32x4 acc[2][2] = {};
+        f32x4 acc[2][NC] = {};
 #pragma unroll
         for (int i = 0; i < NS; ++i)
             if (wave + 8 * i < ks) {
 #pragma unroll
                 for (int m = 0; m < 2; ++m)
 #pragma unroll
-                    for (int n = 0; n < 2; ++n) acc[m][n] = L::mma(wf[j][i][n], fa[i][m], acc[m][n]);
+                    for (int n = 0; n < NC; ++n) acc[m][n] = L::mma(wf[j][i][n], fa[i][m], acc[m][n]);
             }
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int n = 0; n < 2; ++n) *(f32x4 *)(red + j * 32768 + (((wave * 2 + m) * 2 + n) * 64 + lane) * 16) = acc[m][n];
+            for (int n = 0; n < NC; ++n) *(f32x4 *)(red + j * 32768 + (((wave * 2 + m) * 2 + n) * 64 + lane) * 16) = acc[m][n];
     }
     __syncthreads();
     if (tid == 0) draw(k);
@@ -506,7 +506,7 @@ __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
     if (fin) {
 #pragma unroll
         for (int w = 0; w < 8; ++w) {
-            const f32x4 t = *(const f32x4 *)(red + (wave >> 2) * 32768 + (((min(w, np - 1) * 2 + fm) * 2 + fn) * 64 + lane) * 16);
+            const f32x4 t = *(const f32x4 *)(red + fj * 32768 + (((min(w, np - 1) * 2 + fm) * 2 + fn) * 64 + lane) * 16);
             if (w < np) y += t;
         }
     }
@@ -529,7 +529,7 @@ __device__ __forceinline__ unsigned *resid_task(const Task &k, char *lds)
 
 // KD: K steps of 32 in the model width.  CH: K steps at most in the hidden width
 // PRE: proj is in the F1 tasks
-template <typename E, int KD, int CH, int NQ, int N1, int NP, bool SUM, bool PRE>
+template <typename E, int KD, int CH, int NQ, int N1, int NP, int NC, bool SUM, bool PRE>
 __global__ __launch_bounds__(FL_THREADS, sizeof(E) == 2 && !PRE ? 4 : 2) void flow_kernel(const FlowParams)
 {
     extern __shared__ __attribute__((aligned(16))) char fl_lds[];
@@ -576,9 +576,9 @@ __global__ __launch_bounds__(FL_THREADS, sizeof(E) == 2 && !PRE ? 4 : 2) void fl
             unsigned *done;
             if (stage == 0) done = norm_task<E, KD, 0, NQ, SUM, false>(k, fl_lds);
             else if (stage == 1) done = attention_task<E, KD, false>(k, fl_lds);
-            else if (!PRE && stage == 2) done = resid_task<E, KD, CH, 2, NP, SUM>(k, fl_lds);
+            else if (!PRE && stage == 2) done = resid_task<E, KD, CH, 2, NP, NC, SUM>(k, fl_lds);
             else if (stage == 3) done = norm_task<E, KD, 3, N1, SUM, PRE>(k, fl_lds);
-            else done = resid_task<E, KD, CH, 4, NP, SUM>(k, fl_lds);
+            else done = resid_task<E, KD, CH, 4, NP, NC, SUM>(k, fl_lds);
             // ---- done: every wave's stores have reached device scope, then the task is counted
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (tid == 0) s_ticket = next;
@@ -599,7 +599,7 @@ __global__ __launch_bounds__(FL_THREADS, sizeof(E) == 2 && !PRE ? 4 : 2) void fl
 
 Div make_div(unsigned d) { return Div{d, d == 1 ? 0u : (unsigned)((0x100000000ull + d - 1) / d)}; }
 
-template <typename E, int KD, int NQ, int N1, int NP, bool SUM, bool PRE> int launch_flow_t(FlowParams &p, hipStream_t st)
+template <typename E, int KD, int NQ, int N1, int NP, int NC, bool SUM, bool PRE> int launch_flow_t(FlowParams &p, hipStream_t st)
 {
     constexpr int PER_CU = sizeof(E) == 2 && !PRE ? 2 : 1;     // (single precision: fragments of twice the registers; proj in F1: more of them)
     constexpr int ATT = 8 * 8192 + 2048, Q = norm_lds<E>(KD, NQ, false), F1 = norm_lds<E>(KD, N1, PRE);
@@ -608,14 +608,14 @@ template <typename E, int KD, int NQ, int N1, int NP, bool SUM, bool PRE> int la
     const FlowArgs &a = p.a;
     const int nrt = p.nrt;
     p.nQ = NQ;
-    p.dQ = make_div(nrt * 3 * p.ct_d / NQ); p.dA = make_div(nrt * a.heads); p.dP = make_div(nrt * 2 * p.ct_d / NP); p.d1 = make_div(nrt * p.ct_m / N1);
+    p.dQ = make_div(nrt * 3 * p.ct_d / NQ); p.dA = make_div(nrt * a.heads); p.dP = make_div(nrt * 4 / NC * p.ct_d / NP); p.d1 = make_div(nrt * p.ct_m / N1);
     p.drt = make_div(nrt);
     p.tpb = p.dQ.d + p.dA.d + (PRE ? 1 : 2) * p.dP.d + p.d1.d;
-    p.a_p2 = 2 * p.ct_d / NP; p.a_1 = p.ct_m / N1;
+    p.a_p2 = 4 / NC * p.ct_d / NP; p.a_1 = p.ct_m / N1;
     // one workgroup per CU while that gives every block of a queue 32 of them or more, else two (DeiT-tiny, twelve layers, 256 / 512 of them:
     // 4 blocks 249 / 271 us, 8 blocks 314 / 334, 9 blocks 372 / 368, 12 blocks 426 / 408, 20 blocks 599 / 488)
     const long all = (long)p.tpb * a.nb, most = a.nb <= FL_MAXQ || PER_CU == 1 ? 256 : 512;
-    auto kern = flow_kernel<E, KD, 24, NQ, N1, NP, SUM, PRE>;
+    auto kern = flow_kernel<E, KD, 24, NQ, N1, NP, NC, SUM, PRE>;
     static bool attr_set = false;   // raising the dynamic LDS limit is a per-kernel, process-wide setting
     if (!attr_set) {
         if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS) != hipSuccess) return POLY_EHIP;
@@ -625,23 +625,31 @@ template <typename E, int KD, int NQ, int N1, int NP, bool SUM, bool PRE> int la
     return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
 }
 
-template <typename E, int KD, int NQ, int N1, int NP, bool PRE> int launch_flow_n(FlowParams &p, hipStream_t st)
+template <typename E, int KD, int NQ, int N1, int NP, int NC, bool PRE> int launch_flow_n(FlowParams &p, hipStream_t st)
 {
-    return p.a.set_off ? launch_flow_t<E, KD, NQ, N1, NP, true, PRE>(p, st) : launch_flow_t<E, KD, NQ, N1, NP, false, PRE>(p, st);
+    return p.a.set_off ? launch_flow_t<E, KD, NQ, N1, NP, NC, true, PRE>(p, st) : launch_flow_t<E, KD, NQ, N1, NP, NC, false, PRE>(p, st);
 }
 
 template <int KD> int launch_flow_d(FlowParams &p, int dtype, hipStream_t st)
 {
-    if (dtype == POLY_F32) return launch_flow_n<float, KD, 1, 2, 1, false>(p, st);
-    // Up to 30 row tiles (36 of blocks of one or two, whose attention is short) a step of fine tasks fills the chip no more than once or twice, and the chain
-    // of a block is what counts: proj goes into the F1 tasks, a hand-over less per layer for 74 KB more of weights in each.  Beyond that coarse tasks (all three
-    // tiles of a head, four of the hidden width, two of the output), which load the rows and hand over once for several tiles, two workgroups per CU.
-    // Twelve layers of DeiT-tiny, us, proj in F1 / fine with a step of its own / coarse: 1 block of 197 tokens 194 / 202 / 232, 4 (28 tiles) 229 / 252 / 254,
-    // 5 (35) 277 / 288 / 252; 1 of 101 174 / 191, 7 (28) 225 / . / 240, 8 (32) 266 / . / 252; 1 of 17 164 / 175, 5 168 / . / 216, 22 209 / . / 253,
-    // 36 254 / . / 269; 18 of 50 (36) 287 / . / 292.
-    if (p.a.nb * p.nrt <= (p.nrt <= 2 ? 36 : 30)) return launch_flow_n<bf16_t, KD, 1, 2, 1, true>(p, st);
-    if (p.ct_m % 4 == 0) return launch_flow_n<bf16_t, KD, 3, 4, 2, false>(p, st);
-    return launch_flow_n<bf16_t, KD, 1, 2, 1, false>(p, st);
+    // Single precision: up to 16 tiles the products of a task are what its step waits for, and half as many columns of them a task takes (us, tasks of
+    // 128 and 32 / 64 and 16 columns: 1 block of 17 tokens 72.7 / 65.3, 8 82.5 / 77.5, 16 84.1 / 81.8, 24 85.8 / 88.7; 1 of 197 (7 tiles) 81.3 / 79.3, 4 (28) 95 / 108).
+    if constexpr (KD == 6) {
+        if (dtype == POLY_F32) return p.a.nb * p.nrt <= 16 ? launch_flow_n<float, KD, 1, 1, 1, 1, false>(p, st) : launch_flow_n<float, KD, 1, 2, 1, 2, false>(p, st);
+    }
+    if (dtype == POLY_F32) return POLY_EINVAL;
+    // With few row tiles the chain of a block is what counts: proj goes into the F1 tasks, a hand-over less per layer for 74 KB more of weights in each, with
+    // one workgroup per CU.  From 25 tiles on coarse tasks (all three tiles of a head, four of the hidden width, two of the output) load the rows and hand over
+    // once for several tiles; beyond 64 tiles proj is a step of its own again and two workgroups share a CU.
+    // Twelve layers of DeiT-tiny, us, fine with proj in F1 / coarse with it / coarse: 1 block of 197 tokens 191 / 206 / 232, 3 (21 tiles) 215 / 215 / 237,
+    // 4 (28) 231 / 225 / 254, 5 (35) 276 / 230 / 252, 8 (56) . / 296 / 312, 10 (70) . / 385 / 374; 6 of 113 (24) 219 / 219 / 247, 16 (64) . / 300 / 320,
+    // 24 (96) . / 388 / 386; 8 of 17 182 / 203 / 228, 24 210 / 208 / 254, 36 250 / 229 / 269, 64 . / 277 / 291, 100 . / 399 / 355.
+    // Where the device alone knows how many blocks fan out, five eighths of the bound are taken for there (a call has room for three adapters a frame, the
+    // lagged loop for four, and uses fewer).
+    const int tiles = (p.a.nb_dev && !p.a.set_off ? (5 * p.a.nb + 7) / 8 : p.a.nb) * p.nrt;
+    if (p.ct_m % 4 != 0) return tiles <= 30 ? launch_flow_n<bf16_t, KD, 1, 2, 1, 2, true>(p, st) : launch_flow_n<bf16_t, KD, 1, 2, 1, 2, false>(p, st);
+    if (tiles <= 24) return launch_flow_n<bf16_t, KD, 1, 2, 1, 2, true>(p, st);
+    return tiles <= 64 ? launch_flow_n<bf16_t, KD, 3, 4, 2, 2, true>(p, st) : launch_flow_n<bf16_t, KD, 3, 4, 2, 2, false>(p, st);
 }
 
 }  // namespace

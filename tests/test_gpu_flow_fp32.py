@@ -14,10 +14,10 @@ pytestmark = pytest.mark.gpu
     (192, 768, 32, 4, 3, 0, "branch"),       # T = 17: every row tile cut short
     (192, 768, 112, 8, 15, 1, "branch"),     # T = 197: seven row tiles, the last of five rows; adapters on every linear
     (192, 384, 48, 20, 15, 0, "sum"),        # T = 37; two rank steps, the second of four; terms summed
-    (128, 256, 16, 32, 15, 0, "branch"),     # T = 5; the largest rank
-    (128, 640, 88, 12, 9, 2, "branch"),      # T = 122; no adapter on proj and fc1
-    (64, 128, 48, 4, 15, 1, "sum"),          # the narrowest: two K steps
-    (64, 768, 88, 16, 5, 0, "branch"),
+    (192, 256, 16, 32, 15, 0, "branch"),     # T = 5; the largest rank
+    (192, 640, 88, 12, 9, 2, "branch"),      # T = 122; no adapter on proj and fc1
+    (192, 128, 48, 4, 15, 1, "sum"),         # the shortest contraction of fc2
+    (192, 768, 88, 16, 5, 0, "branch"),      # 20 tiles and more of adapted blocks: tasks of twice the columns
 ])
 def test_tasks_and_layer_by_layer_against_the_oracle(D, Dm, hw, r, targets, L0, compose):
     cfg, w, frames, off, ids = synth.make_small_case(830 + D + hw + r, dtype=synth.DT_F32, targets=targets, L=3, F=5, r=r, max_set=3, n_adapters=4, D=D,

@@ -1,4 +1,4 @@
-"""The task queue on both sides of its rule: proj in the tasks of the hidden layer, or a step of its own and coarse tasks."""
+"""The task queue on both sides of its rules: proj in the tasks of the hidden layer or a step of its own, fine and coarse tasks."""
 import numpy as np
 import pytest
 
@@ -9,17 +9,19 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("D,Dm,hw,blocks,r,targets,L0,compose", [
-    (192, 768, 32, 36, 8, 3, 1, "branch"),       # T = 17: 36 tiles, proj in F1
-    (192, 768, 32, 37, 8, 3, 1, "branch"),       # 37: coarse
-    (192, 768, 48, 18, 20, 15, 0, "branch"),     # T = 37, 36 tiles; two rank steps, the second of four; adapters on every linear
-    (192, 768, 48, 19, 20, 15, 0, "branch"),
-    (192, 768, 112, 4, 16, 2, 1, "branch"),      # T = 197, 28 tiles; adapters on proj only
-    (192, 768, 112, 5, 16, 2, 1, "branch"),
-    (192, 512, 80, 7, 8, 7, 0, "sum"),           # T = 101, 28 tiles; terms summed on proj
-    (192, 512, 80, 8, 8, 7, 0, "sum"),
+    (192, 768, 32, 24, 8, 3, 1, "branch"),       # T = 17: 24 tiles, fine tasks with proj in F1
+    (192, 768, 32, 25, 8, 3, 1, "branch"),       # 25: coarse ones
+    (192, 768, 48, 12, 20, 15, 0, "branch"),     # T = 37, 24 tiles; two rank steps, the second of four; adapters on every linear
+    (192, 768, 48, 32, 20, 15, 0, "branch"),     # 64
+    (192, 768, 48, 33, 20, 15, 0, "branch"),     # 66: proj a step of its own
+    (192, 768, 112, 3, 16, 2, 1, "branch"),      # T = 197, 21 tiles; adapters on proj only
+    (192, 768, 112, 5, 16, 2, 1, "branch"),      # 35
+    (192, 512, 80, 6, 8, 7, 0, "sum"),           # T = 101, 24 tiles; terms summed on proj
+    (192, 512, 80, 16, 8, 7, 0, "sum"),          # 64
+    (192, 512, 80, 17, 8, 7, 0, "sum"),          # 68
     (128, 384, 72, 10, 4, 10, 0, "branch"),      # T = 82, 30 tiles; a hidden width that coarse tasks do not divide
-    (128, 384, 72, 11, 4, 10, 0, "sum"),
-    (64, 128, 16, 30, 32, 15, 2, "branch"),      # T = 5; one column tile of proj a wave; the largest rank
+    (128, 384, 72, 11, 4, 10, 0, "sum"),         # 33
+    (64, 256, 16, 64, 32, 15, 2, "branch"),      # T = 5; one column tile of proj a wave; the largest rank
 ])
 def test_against_the_oracle(D, Dm, hw, blocks, r, targets, L0, compose):
     cfg, w, frames, _, _ = synth.make_small_case(940 + D + hw + r, dtype=synth.DT_BF16, targets=targets, L=3, F=blocks, r=r, n_adapters=5, D=D, heads=D // 64, Dm=Dm,
