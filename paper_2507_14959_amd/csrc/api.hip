@@ -411,14 +411,18 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
             POLY_TRY(rowlin(0, x_in, base->ln1_g + (size_t)l * D, base->ln1_b + (size_t)l * D, nullptr, fan_map, Wqkv,
                             base->qkv_b + (size_t)l * 3 * D, 3 * D, EPI_STORE, w.qkv, nullptr, nullptr));
         } else {
-            POLY_TRY(launch_layernorm(x_in, w.u, base->ln1_g + (size_t)l * D, base->ln1_b + (size_t)l * D, D, m->ln_eps, T, nb, nb_dev, dt, st));
+            const float *gain = base->ln1_g + (size_t)l * D, *shift = base->ln1_b + (size_t)l * D;
+            const void *At = use(0) ? lora_ptr(lora->At[0], 0, D, 3 * D, true) : nullptr;
+            const bool shrunk = use(0) && launch_layernorm_shrink(x_in, w.u, gain, shift, D, m->ln_eps, T, nb, nb_dev, At, m->r, RP, m->lora_scale, R, R_dev,
+                                                                  (summed || fan) ? row_offsets : nullptr, w.adapter_of_row, w.S, dt, st);
+            if (!shrunk) POLY_TRY(launch_layernorm(x_in, w.u, gain, shift, D, m->ln_eps, T, nb, nb_dev, dt, st));
             GemmArgs g = {};
             g.A = w.u; g.Wt = Wqkv; g.bias = base->qkv_b + (size_t)l * 3 * D;
             g.T = T; g.K = D; g.N = 3 * D; g.n_in = nb; g.n_in_dev = fan ? &w.meta->F_ok : nb_dev;
             g.out_off = fan ? row_offsets : nullptr;
             if (use(0)) {
-                const void *At = lora_ptr(lora->At[0], 0, D, 3 * D, true), *Bt = lora_ptr(lora->Bt[0], 0, D, 3 * D, false);
-                POLY_TRY(launch_shrink(w.u, T, D, At, m->r, RP, m->lora_scale, F, R, R_dev, summed ? shrink_map : fan_map, w.adapter_of_row,
+                const void *Bt = lora_ptr(lora->Bt[0], 0, D, 3 * D, false);
+                if (!shrunk) POLY_TRY(launch_shrink(w.u, T, D, At, m->r, RP, m->lora_scale, F, R, R_dev, summed ? shrink_map : fan_map, w.adapter_of_row,
                                        (summed || fan) ? row_offsets : nullptr, w.S, dt, st));
                 lora_gemm(g, 0, Bt);
             }
@@ -489,13 +493,17 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
             POLY_TRY(rowlin(2, x_out, base->ln2_g + (size_t)l * D, base->ln2_b + (size_t)l * D, nullptr, nullptr, Wfc1,
                             base->fc1_b + (size_t)l * Dm, Dm, EPI_GELU, w.h, nullptr, nullptr));
         } else {
-            POLY_TRY(launch_layernorm(x_out, w.u, base->ln2_g + (size_t)l * D, base->ln2_b + (size_t)l * D, D, m->ln_eps, T, n_out, n_out_dev, dt, st));
+            const float *gain = base->ln2_g + (size_t)l * D, *shift = base->ln2_b + (size_t)l * D;
+            const void *At = use(2) ? lora_ptr(lora->At[2], 2, D, Dm, true) : nullptr;
+            const bool shrunk = use(2) && launch_layernorm_shrink(x_out, w.u, gain, shift, D, m->ln_eps, T, n_out, n_out_dev, At, m->r, RP, m->lora_scale, R, R_dev,
+                                                                  summed ? row_offsets : nullptr, w.adapter_of_row, w.S, dt, st);
+            if (!shrunk) POLY_TRY(launch_layernorm(x_out, w.u, gain, shift, D, m->ln_eps, T, n_out, n_out_dev, dt, st));
             GemmArgs g = {};
             g.A = w.u; g.Wt = Wfc1; g.bias = base->fc1_b + (size_t)l * Dm;
             g.T = T; g.K = D; g.N = Dm; g.n_in = n_out; g.n_in_dev = n_out_dev;
             if (use(2)) {
-                const void *At = lora_ptr(lora->At[2], 2, D, Dm, true), *Bt = lora_ptr(lora->Bt[2], 2, D, Dm, false);
-                POLY_TRY(launch_shrink(w.u, T, D, At, m->r, RP, m->lora_scale, F, R, R_dev, shrink_map, w.adapter_of_row, summed ? row_offsets : nullptr,
+                const void *Bt = lora_ptr(lora->Bt[2], 2, D, Dm, false);
+                if (!shrunk) POLY_TRY(launch_shrink(w.u, T, D, At, m->r, RP, m->lora_scale, F, R, R_dev, shrink_map, w.adapter_of_row, summed ? row_offsets : nullptr,
                                        w.S, dt, st));
                 lora_gemm(g, 2, Bt);
             }

@@ -329,6 +329,12 @@ int launch_flow_wide(const FlowArgs &a, int patience, hipStream_t st);   // call
 int launch_layernorm(const float *x, void *y, const float *gain, const float *shift, int D, float eps, int T,
                      int n_blocks, const int *n_blocks_dev, int dtype, hipStream_t st);
 
+// LayerNorm of n_blocks blocks and S = scale * y At[adapter_of_out[ob]]^T of their outputs ob (out_off: CSR offsets of every block's, null: block b itself)
+// in one launch; false, and nothing launched, where two launches do it
+bool launch_layernorm_shrink(const float *x, void *y, const float *gain, const float *shift, int D, float eps, int T, int n_blocks, const int *n_blocks_dev,
+                             const void *At, int r, int RP, float scale, int n_out, const int *n_out_dev, const int *out_off, const int *adapter_of_out,
+                             void *S, int dtype, hipStream_t st);
+
 // S[ob] = scale * X[in_block_of_out[ob]] At[adapter_of_out[ob]]^T, zero padded to RP columns.  pair_off (nullable): CSR offsets
 // [n_in + 1] of the output blocks of every input block, when the output blocks of one input block are consecutive (fan-out):
 // lets one workgroup serve two of them from one read of the input rows

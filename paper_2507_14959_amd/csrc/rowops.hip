@@ -147,6 +147,86 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *x, T *y
     }
 }
 
+// LayerNorm of 16 rows and their shrink with the adapters of the block's outputs (ranks up to 16) in one launch: the normalised rows, rounded to bf16, are
+// stored for the product and shrunk out of LDS.  Launches of their own read them back, 10 us of 35 MB for 115 blocks of ViT-base, or pay for a launch, 5 us.
+// Bound by the bytes, 120 MB in and 60 out at 768 columns and 40000 rows: many workgroups per CU (32 KB of LDS, five), a wave's four rows requested at once.
+// Wave w shrinks with quarter w of the columns, the partial sums meet in LDS.
+template <int NV>
+__global__ __launch_bounds__(256) void layernorm_shrink_kernel(const float *x, bf16_t *y, const float *gain, const float *shift, float eps, int T, int subs,
+                                                               int n_blocks, const int *n_blocks_dev, const bf16_t *At, int r, float scale, const int *out_off,
+                                                               const int *n_out_dev, int n_out, const int *adapter_of_out, bf16_t *S)
+{
+    constexpr int D = 256 * NV, NS = 2 * NV;                   // K steps of a wave
+    __shared__ __attribute__((aligned(16))) bf16_t rows_s[16 * D];
+    __shared__ __attribute__((aligned(16))) float red[2][4][256];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lm = lane & 15, g4 = lane >> 4;
+    const int blk = blockIdx.x / subs, t0 = (blockIdx.x - blk * subs) * 16;
+    f32x4 v[4][NV], g[NV], b[NV];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)                                // (requested before the counts are known)
+#pragma unroll
+        for (int i = 0; i < NV; ++i) v[q][i] = *(const f32x4 *)(x + ((size_t)blk * T + min(t0 + 4 * wave + q, T - 1)) * D + 4 * lane + 256 * i);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) { g[i] = *(const f32x4 *)(gain + 4 * lane + 256 * i); b[i] = *(const f32x4 *)(shift + 4 * lane + 256 * i); }
+    const int nb = n_blocks_dev ? min(*n_blocks_dev, n_blocks) : n_blocks, R = min(*n_out_dev, n_out);     // (0 outputs if the CSR arrays are rejected)
+    if (blk >= nb) return;
+    const int o0 = out_off ? max(out_off[blk], 0) : blk, o1 = min(out_off ? out_off[blk + 1] : blk + 1, R);
+    bf16x8 at[NS];
+    auto load_at = [&](int ob) {
+        const int k = adapter_of_out[ob];
+        const bf16_t *p = At + ((size_t)max(k, 0) * r + min(lm, r - 1)) * D + wave * (D / 4) + 8 * g4;
+#pragma unroll
+        for (int j = 0; j < NS; ++j) at[j] = *(const bf16x8 *)(p + 32 * j);
+        return k;
+    };
+    int k = o0 < o1 ? load_at(o0) : -1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) s += v[q][i][0] + v[q][i][1] + v[q][i][2] + v[q][i][3];
+        const float mean = wave_sum(s) / D;
+        float p = 0.f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+            for (int z = 0; z < 4; ++z) { const float d = v[q][i][z] - mean; p += d * d; }
+        const float inv = rsqrtf(wave_sum(p) / D + eps);
+        const int row = 4 * wave + q;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            bf16x4 o;
+#pragma unroll
+            for (int z = 0; z < 4; ++z) o[z] = (bf16_t)((v[q][i][z] - mean) * inv * g[i][z] + b[i][z]);
+            if (t0 + row < T) *(bf16x4 *)(y + ((size_t)blk * T + t0 + row) * D + 4 * lane + 256 * i) = o;
+            *(bf16x4 *)(rows_s + row * D + ((((lane >> 1) + 32 * i) ^ (row & 7)) << 3) + 4 * (lane & 1)) = o;
+        }
+    }
+    __syncthreads();
+    for (int ob = o0; ob < o1; ++ob) {
+        f32x4 sp = {0.f, 0.f, 0.f, 0.f};                       // ranks 4 g4 .. of row lm
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            const int chunk = wave * (D / 32) + 4 * j + g4;
+            sp = __builtin_amdgcn_mfma_f32_16x16x32_bf16(at[j], *(const bf16x8 *)(rows_s + lm * D + ((chunk ^ (lm & 7)) << 3)), sp, 0, 0, 0);
+        }
+        float (*part)[256] = red[(ob - o0) & 1];
+        *(f32x4 *)(part[wave] + 4 * lane) = sp;
+        const int k_now = k;
+        if (ob + 1 < o1) k = load_at(ob + 1);
+        __syncthreads();
+        if (wave == ((ob - o0) & 3) && k_now >= 0 && t0 + lm < T) {
+            f32x4 s = *(const f32x4 *)(part[0] + 4 * lane);
+#pragma unroll
+            for (int w = 1; w < 4; ++w) s += *(const f32x4 *)(part[w] + 4 * lane);
+            bf16x4 o;
+#pragma unroll
+            for (int z = 0; z < 4; ++z) o[z] = (bf16_t)(4 * g4 + z < r ? scale * s[z] : 0.f);
+            *(bf16x4 *)(S + ((size_t)ob * T + t0 + lm) * 16 + 4 * g4) = o;
+        }
+    }
+}
+
 // ------------------------------------------------------------------ LoRA shrink
 // bf16: S = scale * X At_k^T (zero padded to RP columns) with v_mfma_f32_16x16x32_bf16, operands read straight from
 // global memory: a lane's 16 bytes are 8 consecutive K elements of one row, four lanes cover 64 contiguous bytes.
@@ -645,6 +725,28 @@ int launch_layernorm(const float *x, void *y, const float *gain, const float *sh
     else
         POLY_LAUNCH(POLY_STAGE_NORM, layernorm_kernel<float>, dim3(blocks), dim3(256), st, x, (float *)y, gain, shift, D, eps, T, n_blocks, n_blocks_dev);
     return hip_ok();
+}
+
+// False where the two run as launches of their own
+bool launch_layernorm_shrink(const float *x, void *y, const float *gain, const float *shift, int D, float eps, int T, int n_blocks, const int *n_blocks_dev,
+                             const void *At, int r, int RP, float scale, int n_out, const int *n_out_dev, const int *out_off, const int *adapter_of_out,
+                             void *S, int dtype, hipStream_t st)
+{
+    if (dtype != POLY_BF16 || RP != 16 || n_blocks <= 0 || n_out <= 0 || !aligned16(x) || !aligned16(y) || !aligned16(gain) || !aligned16(shift) ||
+        !aligned16(At) || !aligned16(S))
+        return false;
+    const int subs = (T + 15) / 16;
+    const dim3 grid((unsigned)((size_t)n_blocks * subs));
+#define LN_SHRINK_CASE(N)                                                                                                                                       \
+    case 256 * N:                                                                                                                                               \
+        POLY_LAUNCH(POLY_STAGE_NORM, layernorm_shrink_kernel<N>, grid, dim3(256), st, x, (bf16_t *)y, gain, shift, eps, T, subs, n_blocks, n_blocks_dev,         \
+                    (const bf16_t *)At, r, scale, out_off, n_out_dev, n_out, adapter_of_out, (bf16_t *)S);                                                       \
+        return true;
+    switch (D) {
+        LN_SHRINK_CASE(1) LN_SHRINK_CASE(2) LN_SHRINK_CASE(3) LN_SHRINK_CASE(4)
+        default: return false;
+    }
+#undef LN_SHRINK_CASE
 }
 
 template <int MS, int NG, bool CSR>
