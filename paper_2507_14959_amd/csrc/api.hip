@@ -415,7 +415,10 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
             const void *At = use(0) ? lora_ptr(lora->At[0], 0, D, 3 * D, true) : nullptr;
             const bool shrunk = use(0) && launch_layernorm_shrink(x_in, w.u, gain, shift, D, m->ln_eps, T, nb, nb_dev, At, m->r, RP, m->lora_scale, R, R_dev,
                                                                   (summed || fan) ? row_offsets : nullptr, w.adapter_of_row, w.S, dt, st);
-            if (!shrunk) POLY_TRY(launch_layernorm(x_in, w.u, gain, shift, D, m->ln_eps, T, nb, nb_dev, dt, st));
+            const NormGemmArgs ng = {x_in, gain, shift, m->ln_eps, (const bf16_t *)Wqkv, base->qkv_b + (size_t)l * 3 * D, (bf16_t *)w.qkv, 3 * D, T, nb, nb_dev, false};
+            const bool few = dt == POLY_BF16 && !use(0) && !fan && norm_gemm_fits(ng, D);
+            if (few) POLY_TRY(launch_norm_gemm(ng, st));
+            else if (!shrunk) POLY_TRY(launch_layernorm(x_in, w.u, gain, shift, D, m->ln_eps, T, nb, nb_dev, dt, st));
             GemmArgs g = {};
             g.A = w.u; g.Wt = Wqkv; g.bias = base->qkv_b + (size_t)l * 3 * D;
             g.T = T; g.K = D; g.N = 3 * D; g.n_in = nb; g.n_in_dev = fan ? &w.meta->F_ok : nb_dev;
@@ -427,7 +430,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
                 lora_gemm(g, 0, Bt);
             }
             g.mode = EPI_STORE; g.out = w.qkv; g.Tout = T;
-            POLY_TRY(launch_gemm(g, {!branch, pairs}, dt, st));
+            if (!few) POLY_TRY(launch_gemm(g, {!branch, pairs}, dt, st));
         }
         // (as a rule a frame has an adapter, so that there are about as many row-blocks as frames or more)
         POLY_TRY(launch_attention(w.qkv, w.o, T, D, m->heads, n_out, n_out_dev, n_out < F ? n_out : F, dt, rows.waves > 0, st));
@@ -497,7 +500,10 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
             const void *At = use(2) ? lora_ptr(lora->At[2], 2, D, Dm, true) : nullptr;
             const bool shrunk = use(2) && launch_layernorm_shrink(x_out, w.u, gain, shift, D, m->ln_eps, T, n_out, n_out_dev, At, m->r, RP, m->lora_scale, R, R_dev,
                                                                   summed ? row_offsets : nullptr, w.adapter_of_row, w.S, dt, st);
-            if (!shrunk) POLY_TRY(launch_layernorm(x_out, w.u, gain, shift, D, m->ln_eps, T, n_out, n_out_dev, dt, st));
+            const NormGemmArgs ng = {x_out, gain, shift, m->ln_eps, (const bf16_t *)Wfc1, base->fc1_b + (size_t)l * Dm, (bf16_t *)w.h, Dm, T, n_out, n_out_dev, true};
+            const bool few = dt == POLY_BF16 && !use(2) && norm_gemm_fits(ng, D);
+            if (few) POLY_TRY(launch_norm_gemm(ng, st));
+            else if (!shrunk) POLY_TRY(launch_layernorm(x_out, w.u, gain, shift, D, m->ln_eps, T, n_out, n_out_dev, dt, st));
             GemmArgs g = {};
             g.A = w.u; g.Wt = Wfc1; g.bias = base->fc1_b + (size_t)l * Dm;
             g.T = T; g.K = D; g.N = Dm; g.n_in = n_out; g.n_in_dev = n_out_dev;
@@ -508,7 +514,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
                 lora_gemm(g, 2, Bt);
             }
             g.mode = EPI_GELU; g.out = w.h; g.Tout = T;
-            POLY_TRY(launch_gemm(g, {n_out_dev != R_dev, pairs}, dt, st));
+            if (!few) POLY_TRY(launch_gemm(g, {n_out_dev != R_dev, pairs}, dt, st));
         }
         {
             GemmArgs g = {};

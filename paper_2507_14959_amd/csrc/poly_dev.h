@@ -329,6 +329,21 @@ int launch_flow_wide(const FlowArgs &a, int patience, hipStream_t st);   // call
 int launch_layernorm(const float *x, void *y, const float *gain, const float *shift, int D, float eps, int T,
                      int n_blocks, const int *n_blocks_dev, int dtype, hipStream_t st);
 
+// LayerNorm + linear of few rows in one launch (norm_gemm.hip): out[row] = [GELU](LayerNorm(x[row]) Wt^T + bias), no low-rank terms
+struct NormGemmArgs {
+    const float *x;                  // [nb * T][D], D = 768
+    const float *gain, *shift;
+    float eps;
+    const bf16_t *W;                 // [N][D]
+    const float *bias;
+    bf16_t *out;                     // [nb * T][N]
+    int N, T, nb;
+    const int *nb_dev;               // true count on the device, or null
+    bool gelu;
+};
+bool norm_gemm_fits(const NormGemmArgs &a, int D);
+int launch_norm_gemm(const NormGemmArgs &a, hipStream_t st);
+
 // LayerNorm of n_blocks blocks and S = scale * y At[adapter_of_out[ob]]^T of their outputs ob (out_off: CSR offsets of every block's, null: block b itself)
 // in one launch; false, and nothing launched, where two launches do it
 bool launch_layernorm_shrink(const float *x, void *y, const float *gain, const float *shift, int D, float eps, int T, int n_blocks, const int *n_blocks_dev,
