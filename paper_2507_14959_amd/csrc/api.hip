@@ -257,7 +257,12 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
 
     // tokens: x[f][0] = cls + pos[0]; x[f][1 + t] = patch_t W_pe + b_pe + pos[1 + t].  The same launch checks the CSR arrays and
     // builds the row maps (nothing before the first adapted layer needs them).
-    POLY_TRY(launch_im2col(frames, w.patches, F, m->H, m->W, m->patch, dt, w.xa, base->cls, base->pos, T, D, out_merged,
+    const PatchArgs embed = {frames, F, m->H, m->W, m->patch, base->cls, base->pos, w.xa, out_merged, out_merged ? (size_t)F * K : 0, w.fl_clear,
+                             w.fl_clear_bytes / sizeof(unsigned), {ss ? nullptr : row_offsets, adapter_ids, F, R, m->n_adapters, w.meta, w.frame_of_row,
+                             w.adapter_of_row, dev_status}};
+    const bool embedded = patch_embed_fits(embed, base->patch_w, base->patch_b, D, dt);
+    if (embedded) POLY_TRY(launch_patch_embed(embed, base->patch_w, base->patch_b, D, dt, st));
+    else POLY_TRY(launch_im2col(frames, w.patches, F, m->H, m->W, m->patch, dt, w.xa, base->cls, base->pos, T, D, out_merged,
                            out_merged ? (size_t)F * K : 0, w.fl_clear, w.fl_clear_bytes / sizeof(unsigned), ss ? nullptr : row_offsets,
                            adapter_ids, R, m->n_adapters, w.meta, w.frame_of_row, w.adapter_of_row, dev_status, st));
     // The lagged loop: after the shared layers the base head scores the frames, Alg. 2 turns the scores of frame t - 1 into
@@ -273,7 +278,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         return launch_select(ss->lag, F, s->K, s->group_membership, s->M, &s->opts, s->state, ss->row_offsets, ss->adapter_ids, R, ss->counters,
                              fo, st);
     };
-    {
+    if (!embedded) {
         GemmArgs g = {};
         g.A = w.patches; g.Wt = base->patch_w; g.bias = base->patch_b;
         g.T = T - 1; g.K = pd; g.N = D; g.n_in = F;

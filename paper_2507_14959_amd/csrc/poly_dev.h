@@ -197,6 +197,7 @@ struct GemmCount {
     int terms;            // (input block, adapter) pairs where rows fan out or terms are summed, about
 };
 int launch_gemm(const GemmArgs &g, GemmCount count, int dtype, hipStream_t st);
+bool small_product(const GemmArgs &g, int dtype);                     // whether it is one of gemm_ks.hip
 int launch_gemm_ks(const GemmArgs &g, int dtype, hipStream_t st);    // small calls, fp32 and any alignment (gemm_ks.hip); called by launch_gemm
 bool gemm_aligned(const GemmArgs &g);                                // every address a multiple of 16
 inline bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
@@ -328,6 +329,60 @@ int launch_flow_wide(const FlowArgs &a, int patience, hipStream_t st);   // call
 // y = LayerNorm(x) row-wise; x float [n*T][D] -> elt [n*T][D]
 int launch_layernorm(const float *x, void *y, const float *gain, const float *shift, int D, float eps, int T,
                      int n_blocks, const int *n_blocks_dev, int dtype, hipStream_t st);
+
+// One block.  Validates row_offsets / adapter_ids against (F, R_cap, n_adapters) and builds
+// frame_of_row / adapter_of_row.  On any violation nothing downstream runs (meta->R = 0).
+__device__ __forceinline__ void prep_block(const int32_t *row_offsets, const int32_t *adapter_ids, int F, int R_cap, int n_adapters,
+                                           PolyMeta *meta, int32_t *frame_of_row, int32_t *adapter_of_row, int32_t *dev_status)
+{
+    __shared__ int bad;
+    if (threadIdx.x == 0) bad = 0;
+    __syncthreads();
+    const int R = row_offsets[F];
+    if (row_offsets[0] != 0 || R < 0 || R > R_cap) {
+        if (threadIdx.x == 0) bad = 1;
+    } else {
+        for (int f = threadIdx.x; f < F; f += blockDim.x) {
+            const int a = row_offsets[f], b = row_offsets[f + 1];
+            if (a > b || a < 0 || b > R) { bad = 1; continue; }
+            for (int i = a; i < b; ++i) {
+                const int k = adapter_ids[i];
+                if (k < 0 || k >= n_adapters) bad = 1;
+                frame_of_row[i] = f;
+                adapter_of_row[i] = k;
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        meta->R = bad ? 0 : R;
+        meta->F_ok = bad ? 0 : F;
+        meta->status = bad ? POLY_ERANGE : POLY_OK;
+        if (dev_status) *dev_status = meta->status;
+    }
+}
+struct PrepArgs {       // the CSR check as the last block of another launch (row_offsets == nullptr: none)
+    const int32_t *row_offsets, *adapter_ids;
+    int F, R_cap, n_adapters;
+    PolyMeta *meta;
+    int32_t *frame_of_row, *adapter_of_row, *dev_status;
+};
+
+// The patch embedding of few frames in one launch with what else comes first (gemm_ks.hip): x[f][1 + t] = patch_t Wt^T + bias + pos[1 + t] with the patches
+// gathered from the frames by the product itself, the class-token rows x[f][0] = cls + pos[0], `merged` and `zero` cleared, the CSR check and the row maps
+struct PatchArgs {
+    const void *frames;              // [F][H][W][3]
+    int F, H, W, p;
+    const float *cls, *pos;
+    float *x;                        // [F][T][D]
+    float *merged;
+    size_t n_merged;
+    unsigned *zero;
+    size_t n_zero;
+    PrepArgs prep;                   // row_offsets == nullptr: none
+};
+bool patch_embed_fits(const PatchArgs &pa, const void *Wt, const float *bias, int D, int dtype);
+int launch_patch_embed(const PatchArgs &pa, const void *Wt, const float *bias, int D, int dtype, hipStream_t st);
 
 // LayerNorm + linear of few rows in one launch (norm_gemm.hip): out[row] = [GELU](LayerNorm(x[row]) Wt^T + bias), no low-rank terms
 struct NormGemmArgs {

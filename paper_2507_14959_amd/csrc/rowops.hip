@@ -7,48 +7,11 @@
 namespace {
 
 // ------------------------------------------------------------------ CSR check + row maps
-// One block.  Validates row_offsets / adapter_ids against (F, R_cap, n_adapters) and builds
-// frame_of_row / adapter_of_row.  On any violation nothing downstream runs (meta->R = 0).
-__device__ __forceinline__ void prep_block(const int32_t *row_offsets, const int32_t *adapter_ids, int F, int R_cap, int n_adapters,
-                                           PolyMeta *meta, int32_t *frame_of_row, int32_t *adapter_of_row, int32_t *dev_status)
-{
-    __shared__ int bad;
-    if (threadIdx.x == 0) bad = 0;
-    __syncthreads();
-    const int R = row_offsets[F];
-    if (row_offsets[0] != 0 || R < 0 || R > R_cap) {
-        if (threadIdx.x == 0) bad = 1;
-    } else {
-        for (int f = threadIdx.x; f < F; f += blockDim.x) {
-            const int a = row_offsets[f], b = row_offsets[f + 1];
-            if (a > b || a < 0 || b > R) { bad = 1; continue; }
-            for (int i = a; i < b; ++i) {
-                const int k = adapter_ids[i];
-                if (k < 0 || k >= n_adapters) bad = 1;
-                frame_of_row[i] = f;
-                adapter_of_row[i] = k;
-            }
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        meta->R = bad ? 0 : R;
-        meta->F_ok = bad ? 0 : F;
-        meta->status = bad ? POLY_ERANGE : POLY_OK;
-        if (dev_status) *dev_status = meta->status;
-    }
-}
 __global__ void prep_kernel(const int32_t *row_offsets, const int32_t *adapter_ids, int F, int R_cap, int n_adapters,
                             PolyMeta *meta, int32_t *frame_of_row, int32_t *adapter_of_row, int32_t *dev_status)
 {
     prep_block(row_offsets, adapter_ids, F, R_cap, n_adapters, meta, frame_of_row, adapter_of_row, dev_status);
 }
-struct PrepArgs {       // the CSR check as the last block of another launch (row_offsets == nullptr: none)
-    const int32_t *row_offsets, *adapter_ids;
-    int F, R_cap, n_adapters;
-    PolyMeta *meta;
-    int32_t *frame_of_row, *adapter_of_row, *dev_status;
-};
 
 // ------------------------------------------------------------------ patch gathering
 // patches[(f*P + ty*gw + tx)][(i*p + j)*3 + c] = frame[f][ty*p + i][tx*p + j][c]; a run of 3p values
