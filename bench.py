@@ -231,10 +231,10 @@ def main():
         fl3 = R3 * cfg3.L * (2.0 * T3 * (4 * cfg3.D ** 2 + 2 * cfg3.D * cfg3.Dm) + 4.0 * T3 * T3 * cfg3.D
                              + 2.0 * T3 * cfg3.r * (4 * cfg3.D + 2 * cfg3.D + 2 * (cfg3.D + cfg3.Dm))) + F3 * 2.0 * (T3 - 1) * 768 * cfg3.D
         ln_us = p3["layernorm"]["ms"] / p3["layernorm"]["launches"] * 1e3
-        ln_bytes = rows3 * cfg3.D * (4 + 2)                                      # fp32 row in, bf16 row out
+        ln_bytes = rows3 * cfg3.D * (4 + 2) + rows3 * 16 * 2.0                   # fp32 row in, bf16 row and its shrink out
         sh_us = p3["shrink"]["ms"] / p3["shrink"]["launches"] * 1e3
-        # per layer: shrink inputs of width D, D, D and Dm (bf16) + S out + the distinct adapters' A
-        sh_bytes = (rows3 * 2.0 * (3 * cfg3.D + cfg3.Dm) + 4 * rows3 * 16 * 2.0) / 4
+        # per layer: shrink inputs of width D (proj) and Dm (fc2), bf16, + S out; the shrinks of qkv and fc1 are in the LayerNorm launches
+        sh_bytes = (rows3 * 2.0 * (cfg3.D + cfg3.Dm) + 2 * rows3 * 16 * 2.0) / 2
         res = {"frames_per_s": round(F3 / sec3, 1), "ms_per_call": round(sec3 * 1e3, 2), "row_blocks": R3,
                "algorithmic_tflops": round(fl3 / sec3 / 1e12, 1), "frac_mfma": round(fl3 / sec3 / 1e12 / PEAK_BF16_TFLOPS, 4),
                "stage_ms_per_call": {k: round(v["ms"] / 5, 3) for k, v in p3.items() if v["launches"]},

@@ -21,12 +21,14 @@ extern "C" {
 enum {
     POLY_STAGE_SELECT = 0, /* Alg. 2 kernel */
     POLY_STAGE_GEMM = 1,   /* base linears with fused expand and epilogue (patch embedding included), and launches that hold more: the
-                              row kernels (LayerNorm and shrink too), the task queue (a run of whole layers: attention, LayerNorm and
-                              shrink too) and the isolated linear of a small call (CSR check and shrink too) */
+                              row kernels (LayerNorm and shrink too), the task queues (a run of whole layers: attention, LayerNorm and
+                              shrink too), the patch embedding of few frames or in single precision (with the gathering, the class token and
+                              the CSR check), LayerNorm + linear of few frames of a wide model, and the isolated linear of a small call (CSR
+                              check and shrink too) */
     POLY_STAGE_SHRINK = 2, /* x A_k, where it is a launch of its own (of the isolated bf16 linear: with the CSR check) */
     POLY_STAGE_ATTN = 3,   /* where it is a launch of its own */
-    POLY_STAGE_NORM = 4,   /* LayerNorm, likewise */
-    POLY_STAGE_OTHER = 5,  /* CSR check, patch gathering, class token, heads, merge */
+    POLY_STAGE_NORM = 4,   /* LayerNorm, likewise; of a wide model with adapters: with the shrink of its rows */
+    POLY_STAGE_OTHER = 5,  /* CSR check, patch gathering and class token, likewise; heads, merge */
     POLY_STAGE_COUNT = 6
 };
 

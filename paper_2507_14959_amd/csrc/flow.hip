@@ -29,12 +29,12 @@
 //
 // What bounds it: the chain of a block, five steps per layer with a hand-over each, four where P is part of the F1 tasks (few tiles: launch_flow_d).  DeiT-tiny,
 // one live frame: 14.9 us per layer (15.7 in five steps; two launches of ten and two layers), the matrix unit busy 0.7 % of the time; the lagged loop takes
-// 200 us instead of the 473 of row kernels and attention launches.  With many blocks the weights that every 32-row task pulls through its CU's load path bound it, and kernels with
+// 195 us instead of the 473 of row kernels and attention launches.  With many blocks the weights that every 32-row task pulls through its CU's load path bound it, and kernels with
 // larger tiles take over (api.hip).
 //
 // Single precision: the same tasks on v_mfma_f32_16x16x4_f32, elements and buffers of twice the size, one workgroup per CU (190 registers).  The same
-// chain bounds it: two layers on 4 frames of 17 tokens, 22 launches of 3 to 13 us each before, 128 us per forward / 78 now; one frame of 197 tokens
-// 168 / 82.  Its products are an eighth of the bf16 rate, so the tasks give way to larger tiles with fewer blocks than in bf16 (api.hip).
+// chain bounds it: two layers on 4 frames of 17 tokens, 22 launches of 3 to 13 us each before, 128 us per forward / 74 now (70 with the patches gathered by the product); one frame of
+// 197 tokens 168 / 82 (78).  Its products are an eighth of the bf16 rate, so the tasks give way to larger tiles with fewer blocks than in bf16 (api.hip).
 #include "flow_dev.h"
 
 namespace {
