@@ -449,7 +449,7 @@ def main():
     alg_bytes = (frames_np.size * 2 + 2.0 * (cfg.patch_dim * cfg.D + cfg.L * (4 * cfg.D * cfg.D + 2 * cfg.D * cfg.Dm))
                  + n_used * 2.0 * cfg.L * cfg.r * (cfg.D + 3 * cfg.D + cfg.D + cfg.D) + R * cfg.C * 4) / n_gemm
     traffic = measured_traffic_per_launch() if args.L0 == 0 else None
-    roofline = {"bound": "mfma", "kernel": "bf16 MFMA linears: rowlayer_kernel (proj + LoRA + residual, LN, fc1, GELU, fc2, residual, LN, next qkv + LoRA in one launch per layer; the first qkv), gemm_bf16_dma_kernel (patch embedding)",
+    roofline = {"bound": "mfma", "kernel": "bf16 MFMA linears: rowlayer_kernel (proj + LoRA + residual, LN, fc1, GELU, fc2, residual, LN, next qkv + LoRA in one launch per layer; the first qkv), patch_rows_kernel (patch embedding)",
                 "achieved": round(achieved, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
                 "traffic": traffic, "traffic_source": os.path.relpath(TRAFFIC_PROFILE, ROOT) if traffic else None,

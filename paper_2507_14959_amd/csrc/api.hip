@@ -260,8 +260,9 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
     const PatchArgs embed = {frames, F, m->H, m->W, m->patch, base->cls, base->pos, w.xa, out_merged, out_merged ? (size_t)F * K : 0, w.fl_clear,
                              w.fl_clear_bytes / sizeof(unsigned), {ss ? nullptr : row_offsets, adapter_ids, F, R, m->n_adapters, w.meta, w.frame_of_row,
                              w.adapter_of_row, dev_status}};
-    const bool embedded = patch_embed_fits(embed, base->patch_w, base->patch_b, D, dt);
-    if (embedded) POLY_TRY(launch_patch_embed(embed, base->patch_w, base->patch_b, D, dt, st));
+    const bool bf16 = dt == POLY_BF16;
+    const bool embedded = bf16 ? patch_rows_fits(embed, base->patch_w, base->patch_b, D) : patch_rows_f32_fits(embed, base->patch_w, base->patch_b, D);
+    if (embedded) POLY_TRY((bf16 ? launch_patch_rows : launch_patch_rows_f32)(embed, base->patch_w, base->patch_b, D, st));
     else POLY_TRY(launch_im2col(frames, w.patches, F, m->H, m->W, m->patch, dt, w.xa, base->cls, base->pos, T, D, out_merged,
                            out_merged ? (size_t)F * K : 0, w.fl_clear, w.fl_clear_bytes / sizeof(unsigned), ss ? nullptr : row_offsets,
                            adapter_ids, R, m->n_adapters, w.meta, w.frame_of_row, w.adapter_of_row, dev_status, st));

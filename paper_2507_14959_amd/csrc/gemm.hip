@@ -782,20 +782,6 @@ static int launch_gemm_dma(const GemmArgs &g, GemmCount count, hipStream_t st)
     return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
 }
 
-// Which products are those of gemm_ks.hip: single precision, what does not fit the tiles here, and of the others:
-// A long contraction on fewer 128 x 128 tiles than half the CUs is split over the waves (gemm_ks.hip) where tiles of 32 x 64 get a CU each, and
-// above a contraction of 1024 also where tiles of 64 x 64 do.  us per product of the 768-wide backbone, split / tiles of 64 x 64 on a shared ring /
-// 128 x 128 (rows x K -> N):
-//   197 x 768 -> 2304  7.6 / 7.0 / 11.9    591 x 768 -> 768   9.3 / 9.1 / 14.6    591 x 3072 -> 768   14.6 / 18.0 / 38.8
-//   197 x 768 -> 3072  9.0 / 7.4 / 13.4    985 x 768 -> 768  10.7 / 9.2 / 14.9    1182 x 3072 -> 768  19.0 / 19.2 / 39.1
-//   591 x 768 -> 2304 16.9 / 9.8 / 12.3    1576 x 768 -> 768 17.8 / 11.0 / 15.0   1576 x 3072 -> 768  32.4 / 25.3 / 39.0
-//   591 x 768 -> 3072 18.0 / 10.9 / 13.7   985 x 768 -> 2304 23.8 / 14.7 / 12.6 (144 tiles of 128 x 128)
-bool small_product(const GemmArgs &g, int dtype)
-{
-    if (dtype != POLY_BF16 || g.K % 64 != 0 || g.N % 8 != 0 || !gemm_aligned(g)) return true;
-    return g.K >= 512 && product_tiles(g, 128, 128) < 128 && (product_tiles(g, 32, 64) <= 256 || (g.K > 1024 && product_tiles(g, 64, 64) <= 256));
-}
-
 int launch_gemm(const GemmArgs &g, GemmCount count, int dtype, hipStream_t st)
 {
     if (g.n_in <= 0 || g.T <= 0) return POLY_OK;
@@ -811,6 +797,15 @@ int launch_gemm(const GemmArgs &g, GemmCount count, int dtype, hipStream_t st)
         gf.Tb = g.T; gf.nb = g.n_in;
         gf.T = (int)rows; gf.n_in = 1;          // (Tout stays the block length: it places the output blocks)
     }
-    if (small_product(gf, dtype)) return launch_gemm_ks(gf, dtype, st);
+    if (!bf16 || g.K % 64 != 0 || g.N % 8 != 0 || !gemm_aligned(g)) return launch_gemm_ks(gf, dtype, st);
+    // A long contraction on fewer 128 x 128 tiles than half the CUs is split over the waves (gemm_ks.hip) where tiles of 32 x 64 get a CU each, and
+    // above a contraction of 1024 also where tiles of 64 x 64 do.  us per product of the 768-wide backbone, split / tiles of 64 x 64 on a shared ring /
+    // 128 x 128 (rows x K -> N):
+    //   197 x 768 -> 2304  7.6 / 7.0 / 11.9    591 x 768 -> 768   9.3 / 9.1 / 14.6    591 x 3072 -> 768   14.6 / 18.0 / 38.8
+    //   197 x 768 -> 3072  9.0 / 7.4 / 13.4    985 x 768 -> 768  10.7 / 9.2 / 14.9    1182 x 3072 -> 768  19.0 / 19.2 / 39.1
+    //   591 x 768 -> 2304 16.9 / 9.8 / 12.3    1576 x 768 -> 768 17.8 / 11.0 / 15.0   1576 x 3072 -> 768  32.4 / 25.3 / 39.0
+    //   591 x 768 -> 3072 18.0 / 10.9 / 13.7   985 x 768 -> 2304 23.8 / 14.7 / 12.6 (144 tiles of 128 x 128)
+    if (g.K >= 512 && product_tiles(gf, 128, 128) < 128 && (product_tiles(gf, 32, 64) <= 256 || (g.K > 1024 && product_tiles(gf, 64, 64) <= 256)))
+        return launch_gemm_ks(gf, dtype, st);
     return launch_gemm_dma(gf, count, st);
 }

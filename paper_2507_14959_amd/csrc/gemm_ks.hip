@@ -49,11 +49,7 @@ constexpr int KS_NSMAX = 3;
 // adapter, row tiles inside blocks, columns past the rank zero) instead of a linear with shared weights.  AL: every pointer is on a
 // 16-byte boundary; else the operands are fetched and the results stored element by element (the addresses the caller gave need no more
 // than the alignment of an element; loads to LDS need 16 bytes).
-// PATCH: the rows are the patches of a frame, gathered by the loads: a run of 3 p elements (a patch's part of an image row) is a whole number of 16-byte pieces.
-struct PatchRows {
-    int p, gw, run;                                        // patch and patches per row; pieces of a run
-    unsigned magic, pitch;                                 // n / run = umulhi(n, magic) for the pieces of a patch; bytes of an image row
-};
+// PATCH: the rows are the patches of a frame, gathered by the loads (PatchRows).
 template <typename T, int MI, int NI, bool SHRINK, bool AL, bool PATCH>
 __device__ __forceinline__ void gemm_ks_tile(const GemmArgs &g, int tiles_m, int tiles_n, int ns, const PatchRows &pr)
 {
@@ -104,15 +100,8 @@ __device__ __forceinline__ void gemm_ks_tile(const GemmArgs &g, int tiles_m, int
     unsigned patch0[PATCH ? BM / 8 : 1];                   // first byte of this lane's patches
     if constexpr (PATCH) {
 #pragma unroll
-        for (int q = 0; q < BM / 8; ++q) {
-            const int t = min(t0 + 8 * q + lr, Tlim - 1), ty = t / pr.gw;
-            patch0[q] = (unsigned)(ty * pr.p) * pr.pitch + (unsigned)(t - ty * pr.gw) * (unsigned)(3 * pr.p * sizeof(T));
-        }
+        for (int q = 0; q < BM / 8; ++q) patch0[q] = patch_start(pr, min(t0 + 8 * q + lr, Tlim - 1), sizeof(T));
     }
-    auto piece = [&](unsigned n) {                         // byte of a patch's 16-byte piece n, from its first
-        const unsigned dy = __umulhi(n, pr.magic);
-        return dy * pr.pitch + (n - dy * pr.run) * 16u;
-    };
     // 16 bytes of this lane's: to LDS at lds + 16 lane
     auto fetch = [&](const char *base, unsigned off, char *lds) {
         if constexpr (AL) {
@@ -131,7 +120,7 @@ __device__ __forceinline__ void gemm_ks_tile(const GemmArgs &g, int tiles_m, int
         char *st = ring + (i % ns) * STAGE;
         const unsigned e0 = (unsigned)(c0 + (last ? adj0 : 0)) * 16, e1 = (unsigned)(c1 + (last ? adj1 : 0)) * 16;
         if constexpr (PATCH) {
-            const unsigned p0 = piece(8 * kt + e0 / 16), p1 = piece(8 * kt + e1 / 16);
+            const unsigned p0 = patch_piece(pr, 8 * kt + e0 / 16), p1 = patch_piece(pr, 8 * kt + e1 / 16);
 #pragma unroll
             for (int q = 0; q < BM / 8; ++q) fetch((const char *)A, patch0[q] + ((q & 1) ? p1 : p0), st + q * 1024);
         } else {
@@ -428,27 +417,16 @@ __global__ __launch_bounds__(256, 2) void gemm_ks_kernel(const GemmArgs g, int t
     gemm_ks_tile<T, MI, NI, SHRINK, AL, false>(g, tiles_m, tiles_n, ns, PatchRows{});
 }
 
-// The patch embedding: the product's tiles, behind them workgroups for the rest, the last one for the CSR check (a gather and a product were two launches).
-// us per forward in one launch / in two: single precision on 4 frames of 17 tokens 69.8 / 72.1, 192 columns of bfloat16 on a frame of 224 x 224 187.5 / 190.3
-template <typename T, int MI, int NI>
-__global__ __launch_bounds__(256, 2) void patch_embed_kernel(const GemmArgs g, int tiles_m, int tiles_n, int ns, const PatchRows pr, const PatchArgs pa, int tile_wgs, int job_wgs)
+// The patch embedding in single precision: the product's tiles, behind them workgroups for the rest, the last one for the CSR check (a gather and a product were
+// two launches).  Bound by the matrix instructions.  Forward in one launch / in two, us: 4 frames of 17 tokens 69.8 / 72.1; of 197 tokens 1, 8, 32, 64 frames
+// 78.7 / 81.5, 140.9 / 146.3, 414.2 / 421.4, 697.9 / 709.1.
+template <int MI, int NI>
+__global__ __launch_bounds__(256, 2) void patch_f32_kernel(const GemmArgs g, int tiles_m, int tiles_n, int ns, const PatchRows pr, const PatchArgs pa, int tile_wgs,
+                                                           int job_wgs)
 {
     const int job = (int)blockIdx.x - tile_wgs;
-    if (job < 0) {
-        gemm_ks_tile<T, MI, NI, false, true, true>(g, tiles_m, tiles_n, ns, pr);
-    } else if (job == job_wgs) {
-        prep_block(pa.prep.row_offsets, pa.prep.adapter_ids, pa.prep.F, pa.prep.R_cap, pa.prep.n_adapters, pa.prep.meta, pa.prep.frame_of_row,
-                   pa.prep.adapter_of_row, pa.prep.dev_status);
-    } else {
-        const size_t first = (size_t)job * 256 + threadIdx.x, step = (size_t)job_wgs * 256;
-        for (size_t i = first; i < (size_t)pa.F * g.N; i += step) {
-            const size_t f = i / g.N, c = i - f * g.N;
-            pa.x[f * g.Tout * g.N + c] = pa.cls[c] + pa.pos[c];
-        }
-        for (size_t i = first; i < pa.n_merged; i += step) pa.merged[i] = 0.f;
-        for (size_t i = first; i < pa.n_zero; i += step) pa.zero[i] = 0u;
-        if (first == 0 && pa.prep.meta) pa.prep.meta->stalled = 0;
-    }
+    if (job < 0) gemm_ks_tile<float, MI, NI, false, true, true>(g, tiles_m, tiles_n, ns, pr);
+    else patch_jobs(pa, g.N, job, job_wgs);
 }
 
 // ------------------------------------------------------------------ the isolated multi-adapter linear of a small call, one launch
@@ -761,11 +739,11 @@ template <typename T, int MI, int NI> int ks_lds_bytes(int K, int &ns)
     return 4 * ns * STAGE > RED ? 4 * ns * STAGE : RED;
 }
 
-template <typename T, int MI, int NI> int launch_patch_t(const GemmArgs &g, const PatchRows &pr, const PatchArgs &pa, hipStream_t st)
+template <int MI, int NI> int launch_patch_t(const GemmArgs &g, const PatchRows &pr, const PatchArgs &pa, hipStream_t st)
 {
     int ns;
-    const int lds = ks_lds_bytes<T, MI, NI>(g.K, ns);
-    auto kern = patch_embed_kernel<T, MI, NI>;
+    const int lds = ks_lds_bytes<float, MI, NI>(g.K, ns);
+    auto kern = patch_f32_kernel<MI, NI>;
     static bool attr_set = false;       // raising the dynamic LDS limit is a per-kernel, process-wide setting
     if (!attr_set) {
         if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024) != hipSuccess) return POLY_EHIP;
@@ -773,10 +751,7 @@ template <typename T, int MI, int NI> int launch_patch_t(const GemmArgs &g, cons
     }
     const int tiles_m = (g.T + 32 * MI - 1) / (32 * MI), tiles_n = (g.N + 32 * NI - 1) / (32 * NI);
     const long tile_wgs = ((long)g.n_in * tiles_m * tiles_n + 7) / 8 * 8;
-    size_t most = (size_t)pa.F * g.N;
-    if (pa.n_merged > most) most = pa.n_merged;
-    if (pa.n_zero > most) most = pa.n_zero;
-    const int job_wgs = most / 1024 + 1 < 64 ? (int)(most / 1024 + 1) : 64;
+    const int job_wgs = patch_job_wgs(pa, g.N);
     POLY_LAUNCH_SHMEM(POLY_STAGE_GEMM, kern, dim3((unsigned)(tile_wgs + job_wgs + (pa.prep.row_offsets ? 1 : 0))), dim3(256), lds, st, g, tiles_m, tiles_n, ns, pr, pa,
                       (int)tile_wgs, job_wgs);
     return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
@@ -844,31 +819,20 @@ static GemmArgs patch_product(const PatchArgs &pa, const void *Wt, const float *
     return g;
 }
 
-// Where the product is one of this file's, and a piece of 16 bytes never crosses from one image row of a patch to the next nor lies off a 16-byte boundary.
-// In bfloat16 every column of tiles gathers the frames anew, in runs of 96 bytes for patches of 16: past 192 tiles of the 768-wide backbone that is what the
-// launch saved costs.  us per forward, gathered by a kernel / by the product, 196 patches a frame: 1 frame (84 tiles) 473.3 / 468.1, 2 (168) 611.7 / 611.2,
-// 3 (252) 646.0 / 647.0; 192 columns, 12 frames (252) 414.4 / 411.6.  Single precision, bound by its matrix instructions, gains up to the largest calls:
-// 1, 8, 32, 64 frames 81.5 / 78.7, 146.3 / 140.9, 421.4 / 414.2, 709.1 / 697.9.
-bool patch_embed_fits(const PatchArgs &pa, const void *Wt, const float *bias, int D, int dtype)
+// A piece of 16 bytes never crosses from one image row of a patch to the next nor lies off a 16-byte boundary
+bool patch_rows_f32_fits(const PatchArgs &pa, const void *Wt, const float *bias, int D)
 {
-    const int V = dtype == POLY_BF16 ? 8 : 4;
     const GemmArgs g = patch_product(pa, Wt, bias, D);
-    if ((3 * pa.p) % V || (3 * pa.W) % V || g.K % (8 * V) || g.N % 4 || pa.F <= 0 || g.K > 4096 || (size_t)pa.H * pa.W * 3 * 16 / V > 0x7fffffffu)
-        return false;
-    if (dtype == POLY_BF16 && D > 256 && product_tiles(g.n_in, g.T, g.N, 32, 64) > 192) return false;
-    return aligned16(pa.frames) && gemm_aligned(g) && small_product(g, dtype);
+    return pa.F > 0 && (3 * pa.p) % 4 == 0 && g.K % 32 == 0 && g.K <= 4096 && g.N % 4 == 0 && (size_t)pa.H * pa.W * 12 <= 0x7fffffffu && aligned16(pa.frames) &&
+           gemm_aligned(g);
 }
 
-int launch_patch_embed(const PatchArgs &pa, const void *Wt, const float *bias, int D, int dtype, hipStream_t st)
+int launch_patch_rows_f32(const PatchArgs &pa, const void *Wt, const float *bias, int D, hipStream_t st)
 {
     const GemmArgs g = patch_product(pa, Wt, bias, D);
-    const size_t es = dtype == POLY_BF16 ? 2 : 4;
-    const unsigned run = (unsigned)(3 * pa.p * es / 16);
-    const PatchRows pr = {pa.p, pa.W / pa.p, (int)run, (unsigned)((0x100000000ull + run - 1) / run), (unsigned)(3 * pa.W * es)};
-    const int tile = ks_tile(g, dtype);
-    if (dtype == POLY_BF16)
-        return tile == 0 ? launch_patch_t<bf16_t, 1, 1>(g, pr, pa, st) : tile == 1 ? launch_patch_t<bf16_t, 1, 2>(g, pr, pa, st) : launch_patch_t<bf16_t, 2, 2>(g, pr, pa, st);
-    return tile == 0 ? launch_patch_t<float, 1, 1>(g, pr, pa, st) : tile == 1 ? launch_patch_t<float, 1, 2>(g, pr, pa, st) : launch_patch_t<float, 2, 2>(g, pr, pa, st);
+    const PatchRows pr = patch_rows(pa, 4);
+    const int tile = ks_tile(g, POLY_F32);
+    return tile == 0 ? launch_patch_t<1, 1>(g, pr, pa, st) : tile == 1 ? launch_patch_t<1, 2>(g, pr, pa, st) : launch_patch_t<2, 2>(g, pr, pa, st);
 }
 
 namespace {

@@ -197,7 +197,6 @@ struct GemmCount {
     int terms;            // (input block, adapter) pairs where rows fan out or terms are summed, about
 };
 int launch_gemm(const GemmArgs &g, GemmCount count, int dtype, hipStream_t st);
-bool small_product(const GemmArgs &g, int dtype);                     // whether it is one of gemm_ks.hip
 int launch_gemm_ks(const GemmArgs &g, int dtype, hipStream_t st);    // small calls, fp32 and any alignment (gemm_ks.hip); called by launch_gemm
 bool gemm_aligned(const GemmArgs &g);                                // every address a multiple of 16
 inline bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
@@ -368,8 +367,8 @@ struct PrepArgs {       // the CSR check as the last block of another launch (ro
     int32_t *frame_of_row, *adapter_of_row, *dev_status;
 };
 
-// The patch embedding of few frames in one launch with what else comes first (gemm_ks.hip): x[f][1 + t] = patch_t Wt^T + bias + pos[1 + t] with the patches
-// gathered from the frames by the product itself, the class-token rows x[f][0] = cls + pos[0], `merged` and `zero` cleared, the CSR check and the row maps
+// The patch embedding in one launch with what else comes first: x[f][1 + t] = patch_t Wt^T + bias + pos[1 + t] with the patches gathered from the frames by
+// the product itself, the class-token rows x[f][0] = cls + pos[0], `merged` and `zero` cleared, the CSR check and the row maps
 struct PatchArgs {
     const void *frames;              // [F][H][W][3]
     int F, H, W, p;
@@ -381,8 +380,54 @@ struct PatchArgs {
     size_t n_zero;
     PrepArgs prep;                   // row_offsets == nullptr: none
 };
-bool patch_embed_fits(const PatchArgs &pa, const void *Wt, const float *bias, int D, int dtype);
-int launch_patch_embed(const PatchArgs &pa, const void *Wt, const float *bias, int D, int dtype, hipStream_t st);
+// Where a row of patches lies: a run of 3 p elements (a patch's part of an image row) is a whole number of 16-byte pieces
+struct PatchRows {
+    int p, gw, gh, run;                                    // patch, patches per row and column; pieces of a run
+    unsigned magic, pitch;                                 // n / run = umulhi(n, magic) for the pieces of a patch; bytes of an image row
+};
+inline PatchRows patch_rows(const PatchArgs &pa, int es)
+{
+    const unsigned run = (unsigned)(3 * pa.p * es / 16);   // a multiple of three
+    return {pa.p, pa.W / pa.p, pa.H / pa.p, (int)run, (unsigned)((0x100000000ull + run - 1) / run), (unsigned)(3 * pa.W * es)};
+}
+__device__ __forceinline__ unsigned patch_start(const PatchRows &pr, int row, int es)      // first byte of patch `row` of all frames
+{
+    const int ty = row / pr.gw;                            // (frames are whole rows of patches)
+    return (unsigned)(ty * pr.p) * pr.pitch + (unsigned)(row - ty * pr.gw) * (unsigned)(3 * pr.p * es);
+}
+__device__ __forceinline__ unsigned patch_piece(const PatchRows &pr, unsigned n)           // byte of a patch's 16-byte piece n, from its first
+{
+    const unsigned dy = __umulhi(n, pr.magic);
+    return dy * pr.pitch + (n - dy * pr.run) * 16u;
+}
+inline int patch_job_wgs(const PatchArgs &pa, int D)       // workgroups behind the product's tiles, one more where pa.prep asks for it
+{
+    size_t most = (size_t)pa.F * D;
+    if (pa.n_merged > most) most = pa.n_merged;
+    if (pa.n_zero > most) most = pa.n_zero;
+    return most / 1024 + 1 < 64 ? (int)(most / 1024 + 1) : 64;
+}
+__device__ __forceinline__ void patch_jobs(const PatchArgs &pa, int D, int job, int job_wgs)
+{
+    if (job == job_wgs) {
+        prep_block(pa.prep.row_offsets, pa.prep.adapter_ids, pa.prep.F, pa.prep.R_cap, pa.prep.n_adapters, pa.prep.meta, pa.prep.frame_of_row,
+                   pa.prep.adapter_of_row, pa.prep.dev_status);
+        return;
+    }
+    const size_t T = (size_t)(pa.H / pa.p) * (pa.W / pa.p) + 1, first = (size_t)job * blockDim.x + threadIdx.x, step = (size_t)job_wgs * blockDim.x;
+    for (size_t i = first; i < (size_t)pa.F * D; i += step) {
+        const size_t f = i / D, c = i - f * D;
+        pa.x[f * T * D + c] = pa.cls[c] + pa.pos[c];
+    }
+    for (size_t i = first; i < pa.n_merged; i += step) pa.merged[i] = 0.f;
+    for (size_t i = first; i < pa.n_zero; i += step) pa.zero[i] = 0u;
+    if (first == 0 && pa.prep.meta) pa.prep.meta->stalled = 0;
+}
+// bf16 (patch.hip) and single precision (gemm_ks.hip); false where a kernel gathers the patches and another multiplies them
+bool patch_rows_fits(const PatchArgs &pa, const void *Wt, const float *bias, int D);
+int launch_patch_rows(const PatchArgs &pa, const void *Wt, const float *bias, int D, hipStream_t st);
+bool patch_rows_f32_fits(const PatchArgs &pa, const void *Wt, const float *bias, int D);
+int launch_patch_rows_f32(const PatchArgs &pa, const void *Wt, const float *bias, int D, hipStream_t st);
 
 // LayerNorm + linear of few rows in one launch (norm_gemm.hip): out[row] = [GELU](LayerNorm(x[row]) Wt^T + bias), no low-rank terms
 struct NormGemmArgs {
