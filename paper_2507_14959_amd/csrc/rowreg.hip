@@ -599,18 +599,23 @@ template <int W> int launch_w(const RowLayerArgs &a, hipStream_t st)
 
 }  // namespace
 
-int rowreg_waves(int T, int D, int Dm, int r, bool by_block, int blocks)
+int rowreg_waves(int T, int D, int Dm, int r, bool by_block, int blocks, int least)
 {
     if (D != RR_D || Dm < 128 || Dm % 64 || Dm > RR_MAX_DM || (r && r != 8 && r != 16) || (by_block && T < 32)) return 0;
-    const long rows = (long)blocks * T, tiles = by_block ? (long)blocks * ((T + 63) / 64) : (rows + 63) / 64;
     // us of n workgroups, a CU each at a time: a round takes `c`, and up to `d` more the more CUs are at work (they share the memory and the power).  A layer
     // of DeiT-tiny, tiles of 64 / 128 / 256 rows, twelve layers and everything else of a forward: 12214 rows 486 / 610 / 772 us, 18912 817 / 678 / 839,
     // 32702 941 / 808 / 941, 37430 1255 / 1247 / 1039, 57130 1656 / 1424 / 1212, 65601 (a row in a round of its own) 1956 / 1875 / 1834; with adapters 14184
     // rows (288 tiles that end with their block) 809 / 714 / 891, 28368 1257 / 897 / 1047, 42552 1665 / 1482 / 1171.
     auto rounds = [](long n, float c, float d) { return (float)(n / 256) * (c + d) + (n % 256 ? c + d * (float)(n % 256) / 256.f : 0.f); };
-    const float us[3] = {rounds(tiles, r ? 31.f : 27.5f, 0.f), rounds((rows + 127) / 128, r ? 46.f : 36.f, 8.f), rounds((rows + 255) / 256, r ? 58.f : 48.f, 30.f)};
-    if (us[0] <= us[1] && us[0] <= us[2]) return 0;
-    return us[1] <= us[2] ? 4 : 8;
+    auto us = [&](int waves, int n) {
+        const long rows = (long)n * T;
+        if (waves == 0) return rounds(by_block ? (long)n * ((T + 63) / 64) : (rows + 63) / 64, r ? 31.f : 27.5f, 0.f);
+        return waves == 4 ? rounds((rows + 127) / 128, r ? 46.f : 36.f, 8.f) : rounds((rows + 255) / 256, r ? 58.f : 48.f, 30.f);
+    };
+    int best = 0;
+    for (int waves : {4, 8})
+        if (us(waves, blocks) < us(best, blocks) && us(waves, least) <= us(0, least)) best = waves;
+    return best;
 }
 
 int launch_rowreg(const RowLayerArgs &a, int waves, hipStream_t st)

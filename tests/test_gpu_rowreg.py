@@ -55,6 +55,19 @@ def test_against_the_oracle(F, hw, patch, Dm, r, targets, per_frame, spare, L0):
         assert np.array_equal(logits, logits[first[rows]])  # wherever in a tile a block lies
 
 
+@pytest.mark.parametrize("F,spare", [
+    (120, 400),      # at one adapter a frame tiles of 64 rows are faster
+    (460, 1000),     # .. waves of 32
+])
+def test_much_room_takes_the_kernels_of_few_adapters(F, spare):
+    """Room for more than three blocks a frame and one on every frame: the kernels, and so the bits, of a call without room."""
+    cfg, w, frames, sets, many, off, ids, rows = _case(F, 48, 8, 192, 8, 3, 1)
+    model = binding.DeviceModel(cfg, w, L0=0)
+    tight, roomy = (binding.run_forward(model, many, off, ids, R_cap=len(ids) + n)["logits"][:len(ids)] for n in (0, spare))
+    assert np.array_equal(tight, roomy)
+    assert np.abs(roomy - _want(cfg, w, frames, sets, rows, 0)).max() < BOUND
+
+
 def test_summed_shared_layers():
     """Terms summed on a frame's block from layer 2 on: up to there its rows run here, and leave in the order that the GEMM path reads."""
     cfg, w, frames, sets, many, off, ids, rows = _case(480, 48, 8, 256, 8, 3, 2)
