@@ -599,7 +599,7 @@ template <int W> int launch_w(const RowLayerArgs &a, hipStream_t st)
 
 }  // namespace
 
-int rowreg_waves(int T, int D, int Dm, int r, bool by_block, int blocks, int least)
+int rowreg_waves(int T, int D, int Dm, int r, bool by_block, int blocks, int least, float slack)
 {
     if (D != RR_D || Dm < 128 || Dm % 64 || Dm > RR_MAX_DM || (r && r != 8 && r != 16) || (by_block && T < 32)) return 0;
     // us of n workgroups, a CU each at a time: a round takes `c`, and up to `d` more the more CUs are at work (they share the memory and the power).  A layer
@@ -614,7 +614,7 @@ int rowreg_waves(int T, int D, int Dm, int r, bool by_block, int blocks, int lea
     };
     int best = 0;
     for (int waves : {4, 8})
-        if (us(waves, blocks) < us(best, blocks) && us(waves, least) <= us(0, least)) best = waves;
+        if (us(waves, blocks) < us(best, blocks) && us(waves, least) <= us(0, least) * slack) best = waves;
     return best;
 }
 

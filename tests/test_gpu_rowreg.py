@@ -57,10 +57,11 @@ def test_against_the_oracle(F, hw, patch, Dm, r, targets, per_frame, spare, L0):
 
 @pytest.mark.parametrize("F,spare", [
     (120, 400),      # at one adapter a frame tiles of 64 rows are faster
+    (250, 300),
     (460, 1000),     # .. waves of 32
 ])
 def test_much_room_takes_the_kernels_of_few_adapters(F, spare):
-    """Room for more than three blocks a frame and one on every frame: the kernels, and so the bits, of a call without room."""
+    """Room for several blocks a frame and one on every frame: the kernels, and so the bits, of a call without room."""
     cfg, w, frames, sets, many, off, ids, rows = _case(F, 48, 8, 192, 8, 3, 1)
     model = binding.DeviceModel(cfg, w, L0=0)
     tight, roomy = (binding.run_forward(model, many, off, ids, R_cap=len(ids) + n)["logits"][:len(ids)] for n in (0, spare))
