@@ -34,16 +34,21 @@ struct FlowSegment {
 // 1 tile 444 / 483, 4 493 / 567, 7 490 / 626, 8 600 / 579, 10 590 / 572; adapted on every linear, 1 tile 462 / 716, 7 502 / 891, 14 654 / 929, 21 773 / 981,
 // 21 of which 13 exist 569 / 936, 42 with 25 1136 / 1106.
 // Single precision: at 64 and 128 columns layer by layer, where the size that poly_forward_workspace_bytes names is the least that is taken and less is
-// refused, as callers may rely on; at 192 columns 270 tiles times the part of their rows that exist, for the other way runs its rows across blocks.  Two layers of 192 columns, us,
-// as tasks / layer by layer, every frame with one adapter: 32 blocks of 197 tokens (224 tiles) 422 / 453, 24 (168) 321 / 336, 4 (28) 96 / 189;
-// 64 of 101 (256) 463 / 436, 32 (128) 252 / 287; 64 of 50 (128) 251 / 274; 64 of 17 (64) 137 / 160, 115 of at most 192 235 / 222, 4 76 / 127.
+// refused, as callers may rely on; at 192 columns 165 tiles (220 adapted ones, of which a call mostly fills a part) times the square of the part of their rows that
+// exist, for the other way runs its rows across blocks and its larger tiles gain with their number.  Four shared layers of 192 columns, us, layer by layer / as
+// tasks, blocks of 17 tokens (1 tile each; 32 in any case): 71 217 / 227, 100 286 / 308, 143 320 / 425; of 50 (2) 52 329 / 324, 73 441 / 434, 84 460 / 490; of 101 (4) 37 470 / 438,
+// 42 488 / 495, 53 503 / 617; of 197 (7) 23 661 / 613 (adapted on all linears), 26 538 / 559; of 122 (4), adapted, 44 573 / 595 (so 168 tiles at most).  With adapters the lines lie a tenth higher.
 int flow_limit(const poly_model_desc *m, bool adapted)
 {
     const int T = tokens(m), r = adapted ? m->r : 0, tgt = adapted ? m->targets & 15 : 0;
     if (m->dtype == POLY_BF16 && !(adapted && m->compose == POLY_COMPOSE_SUM && tgt) && flow_wide_supported(T, m->D, m->Dm, m->heads, r, tgt != 0))
         return (adapted && tgt ? 21 : 7) / ((T + 31) / 32);
     if (!flow_supported(T, m->D, m->Dm, m->heads, r, tgt != 0)) return 0;
-    if (m->dtype == POLY_F32) return m->D < 192 ? 0 : 270 * T / (32 * ((T + 31) / 32) * ((T + 31) / 32));
+    if (m->dtype == POLY_F32) {
+        const int nrt = (T + 31) / 32;
+        const long blocks = (adapted && tgt ? 220L : 165L) * T * T / (1024L * nrt * nrt * nrt);
+        return m->D < 192 ? 0 : (int)(blocks * nrt < 32 ? 32 / nrt : blocks * nrt > 168 ? 168 / nrt : blocks);
+    }
     const bool row_kernel = !(tgt & 12) && !(adapted && m->compose == POLY_COMPOSE_SUM && tgt) && rowlayer_supported(m->D, m->Dm, tgt ? r : 0);
     return (row_kernel ? 140 : 270) / ((T + 31) / 32);
 }
