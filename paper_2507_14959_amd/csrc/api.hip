@@ -349,7 +349,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
                                branch ? pairs_slack : 1.f);
         return p;
     };
-    bool x_fragments = false;                  // the residual stream lies in the order of rowreg.hip: between two of its launches only
+    bool x_fragments = false;                  // the residual stream lies in the order of rowreg.hip: between two of its launches that nothing reads it between
     bool qkv_done = false;                     // the qkv linear of layer l was computed by layer l - 1's row kernel
     for (int l = 0; l < m->L; ++l) {
         if (l == 0 && w.fl_cnt[0]) {
@@ -483,7 +483,8 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
             }
             // (rows in the order of rowreg.hip end up to 31 rows past the buffer's last: what lies there, the start of xb, u or h, is in no use then)
             a.res_fragments = x_fragments;
-            x_fragments = a.out_fragments = rows.waves && rows.qkv && row_part(ln).waves;
+            const bool base_head_reads = ln == m->L0 && !selected;         // .. before the next layer, rows one by one
+            x_fragments = a.out_fragments = rows.waves && rows.qkv && !base_head_reads && row_part(ln).waves;
             POLY_TRY(rows.waves ? launch_rowreg(a, rows.waves, st) : launch_rowlayer(a, st));
             continue;
         }

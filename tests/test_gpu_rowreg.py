@@ -1,6 +1,7 @@
 """Many rows of a model 192 wide: tiles of 128 and 256 rows in registers (rowreg.hip) where they, their waves and the blocks in them end."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2507_14959_amd import binding, synth
@@ -76,6 +77,42 @@ def test_summed_shared_layers():
     o, i = synth.sets_to_csr(sets)
     assert got["status"] == 0
     assert np.abs(got["logits"] - oracle.forward(cfg, w, frames, o, i, L0=2, compose="sum")["logits"][rows]).max() < BOUND
+
+
+@pytest.mark.parametrize("compose,targets,L0,room", [
+    ("sum", 0, 1, 3),        # no linear adapted: the row kernels go on past the selection, which reads the rows before they do
+    ("sum", 0, 2, 3),
+    ("sum", 3, 2, 0),        # no room for a row-block: base scores only
+    ("sum", 3, 1, 3),
+    ("branch", 3, 1, 3),
+    ("branch", 1, 2, 3),
+    ("branch", 3, 3, 3),     # no adapted layer
+])
+def test_the_lagged_loop(compose, targets, L0, room):
+    F, dev = 460, "cuda"
+    cfg, w, _, _, many, _, _, _ = _case(F, 48, 8, 256, 8, targets, 1)
+    K = cfg.n_adapters * cfg.C
+    member = synth.make_group_membership(cfg.n_adapters, cfg.C)
+    cap, theta = room * F, 0.5 if room else 2.0            # (without room no label may be on)
+    bw, bb = synth.make_base_head(cfg, K, 17, bias_mean=-3.5)
+    model = binding.DeviceModel(cfg, w, L0=L0, compose=compose)
+    head = binding.DeviceStream(model, bw, bb, member, theta=theta)
+    off, ids, cnt, status = (torch.zeros(n, dtype=torch.int32, device=dev) for n in (F + 1, max(cap, 1), 2, 1))
+    scores, logits = (torch.zeros(max(cap, 1), cfg.C, device=dev) for _ in range(2))
+    base = torch.zeros(F, K, device=dev)
+    ws = torch.empty(binding.poly_stream_step_workspace_bytes(model, F, cap, K), dtype=torch.uint8, device=dev)
+    binding.poly_stream_step(model, head, model.frames_to_device(many), cap, off, ids, cnt, scores, ws, out_base_scores=base, out_logits=logits, dev_status=status)
+    off, ids, base, logits = (t.cpu().numpy() for t in (off, ids, base, logits))
+    want = oracle.base_head(cfg, w, many[:UNIQUE], bw, bb, L0)
+    assert int(status.item()) == 0 and np.abs(base - want[np.arange(F) % UNIQUE]).max() < 2e-2          # (test_gpu_stream.py's bound of a score)
+    assert np.array_equal(head.carry.cpu().numpy(), base[-1])
+    set_off, set_ids, _ = oracle.select(np.concatenate([np.zeros((1, K), np.float32), base[:-1]]), member, theta=theta)
+    assert np.array_equal(off, set_off) and np.array_equal(ids[:off[-1]], set_ids) and (off[-1] > 0) == (cap > 0)
+    a, b = UNIQUE, 2 * UNIQUE                              # (the first frame has no labels yet)
+    got = logits[off[a]:off[b]]
+    o, i = off[a:b + 1] - off[a], ids[off[a]:off[b]]
+    if cap:
+        assert np.abs(got - oracle.forward(cfg, w, many[a:b], o, i, L0=L0, compose=compose)["logits"]).max() < BOUND
 
 
 def test_an_adapter_stays_with_its_blocks():
