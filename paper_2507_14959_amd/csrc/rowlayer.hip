@@ -69,10 +69,10 @@ __global__ __launch_bounds__(LY_THREADS, 2) void rowlayer_kernel(const RowLayerA
     float *b2_s = bp_s + D;                                // [D]
     float *gb2_s = b2_s + D;                               // LayerNorm2 gain [D], shift [D]
     float *gbq_s = gb2_s + 2 * D;                          // LayerNorm1' gain, shift
-    f32x2 *stat_s = (f32x2 *)(gbq_s + 2 * D);              // [64][4]: mean and squared deviations of a wave's columns of a row
+    float *gelu_s = gbq_s + 2 * D;
+    f32x2 *stat_s = (f32x2 *)(gelu_s + 2 * LY_GELU);       // [64][4]: mean and squared deviations of a wave's columns of a row
     s16x4 *sh_s = (s16x4 *)stat_s;                         // in C: shrink output, [4][64 lanes]
-    float *gelu_s = (float *)(stat_s + 64 * 4);
-    bf16_t *at_s = (bf16_t *)(gelu_s + 2 * LY_GELU);       // At_k of the phase, [16][LY_AT_STRIDE]
+    bf16_t *at_s = (bf16_t *)(stat_s + 64 * 4);            // At_k of the phase, [16][LY_AT_STRIDE]
     bf16_t *bt_s = at_s + 16 * LY_AT_STRIDE;               // Bt_k of A, [D][r]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -358,11 +358,23 @@ __global__ __launch_bounds__(LY_THREADS, 2) void rowlayer_kernel(const RowLayerA
             }
         }
         layernorm(gb2_s, [&]() { issue_n(a.W1t, row_n(0), slot0); });
+        // The second product of B adds to x' + b2 on half 0 of its contraction in every row, so that a row's bits do not depend on its place in the tile: the
+        // waves of half 1 hand their rows over, in LDS that is in no use until the second chunk (tile 3, and what LayerNorm and A are done with).  0.3 us of a
+        // launch of 248 tiles (twelve of them and the rest of 32 frames of 224 x 224, 62 blocks: 498 / 502 us; through the weight slots, before the first of
+        // W1 is requested, 504).
+        auto handed = [&](int ct, int rt) {
+            const int i = ct * 2 + rt;
+            return (f32x4 *)((i < 2 ? As + 3 * LY_TILE + i * 4096 : (char *)stat_s + (i - 2) * 4096) + wc * 1024) + lane;
+        };
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {                  // the second product of B adds to x' + b2 in the row half of this wave
+        for (int ct = 0; ct < CT; ++ct) {
             const f32x4 b = *(const f32x4 *)(b2_s + wcol + 16 * ct), z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int rt = 0; rt < 4; ++rt) y[ct][rt] = (rt >> 1) == kh ? x[ct][rt & 1] + b : z;
+            for (int rt = 0; rt < 2; ++rt) {
+                if (kh) *handed(ct, rt) = x[ct][rt] + b;
+                y[ct][rt] = kh ? z : x[ct][rt] + b;
+                y[ct][2 + rt] = z;
+            }
         }
 
         // ============================================================ B: x'' = x' + b2 + GELU(LayerNorm2(x') W1 + b1) W2
@@ -400,6 +412,12 @@ __global__ __launch_bounds__(LY_THREADS, 2) void rowlayer_kernel(const RowLayerA
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // hidden columns of chunk c - 1 are there; wN is in registers
             const f32x4 b = *(const f32x4 *)(b1_s + min(128 * c + 16 * wave, Dm - 16) + 4 * lg);
             if (c + 1 < nc) issue_n(a.W1t, row_n(c + 1), slot0);
+            if (first && !kh) {
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                    for (int rt = 0; rt < 2; ++rt) y[ct][2 + rt] = *handed(ct, rt);
+            }
             segment([&](int n) { mfma_n(n, 0, b); }, [&](int n) {});
             segment([&](int n) { mfma_n(n, 2, b); },
                     [&](int n) {
@@ -587,7 +605,8 @@ __global__ __launch_bounds__(LY_THREADS, 2) void rowlayer_kernel(const RowLayerA
 template <int KT, bool LAYER, bool QKV> int launch_t(const RowLayerArgs &a, hipStream_t st)
 {
     constexpr int D = 64 * KT;
-    constexpr int LDS = LY_TILES * LY_TILE + 16 * KT * 2048 + (LY_MAX_DM + 3 * D + 2 * D + 4 * D) * 4 + 64 * 4 * 8 + LY_GELU * 8 + 16 * LY_AT_STRIDE * 2 + D * 16 * 2;
+    constexpr int END = 64 * 4 * 8 + 16 * LY_AT_STRIDE * 2 + D * 16 * 2, HANDED = (2 * KT - 2) * 4096;   // from stat_s on
+    constexpr int LDS = LY_TILES * LY_TILE + 16 * KT * 2048 + (LY_MAX_DM + 3 * D + 2 * D + 4 * D) * 4 + LY_GELU * 8 + (END > HANDED ? END : HANDED);
     static_assert(LDS <= 160 * 1024, "LDS budget");
     auto kern = rowlayer_kernel<KT, LAYER, QKV>;
     if (LDS > 64 * 1024) {

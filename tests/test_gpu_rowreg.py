@@ -51,9 +51,8 @@ def test_against_the_oracle(F, hw, patch, Dm, r, targets, per_frame, spare, L0):
     again = binding.run_forward(model, many, off, ids, R_cap=len(ids) + spare)["logits"][:len(ids)]
     assert got["status"] == 0 and np.array_equal(logits, again)
     assert np.abs(logits - _want(cfg, w, frames, sets, rows, L0)).max() < BOUND
-    if L0 == 0 or F * cfg.T > 16384:                       # (shared layers on tiles of 64 rows: the two halves of a tile add in another order)
-        first = np.unique(rows, return_index=True)[1]
-        assert np.array_equal(logits, logits[first[rows]])  # wherever in a tile a block lies
+    first = np.unique(rows, return_index=True)[1]
+    assert np.array_equal(logits, logits[first[rows]])     # wherever in a tile a block lies
 
 
 @pytest.mark.parametrize("F,spare", [

@@ -75,3 +75,17 @@ def test_against_the_oracle(case, L0):
     again = binding.run_forward(model, frames, off, ids)
     assert got["status"] == 0 and np.array_equal(got["logits"], again["logits"])
     assert np.abs(got["logits"] - oracle.forward(cfg, w, frames, off, ids, L0=L0)["logits"]).max() < BOUND
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("L0", [1, 3])
+@pytest.mark.parametrize("case", CASES)
+def test_a_row_does_not_depend_on_its_place_in_a_tile(case, L0):
+    """The frames in another order: in shared layers a frame's rows lie elsewhere in their tiles (other row half, other neighbours)."""
+    cfg, w, frames, off, ids = _case(*case)
+    model = binding.DeviceModel(cfg, w, L0=L0)
+    order = np.roll(np.arange(len(frames))[::-1], 1)
+    o, i = synth.sets_to_csr([ids[off[f]:off[f + 1]] for f in order])
+    here, there = binding.run_forward(model, frames, off, ids)["logits"], binding.run_forward(model, frames[order], o, i)["logits"]
+    rows = np.concatenate([np.arange(off[f], off[f + 1]) for f in order])
+    assert np.array_equal(here[rows], there[:len(rows)])
