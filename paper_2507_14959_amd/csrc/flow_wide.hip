@@ -13,9 +13,12 @@
 //
 // Order and progress.  A queue's tickets are numbered layer by layer and step by step, and a task may wait for tasks of earlier steps of ANY queue.  Were all
 // running workgroups those of one queue, the others' tasks would be nobody's.  A task whose inputs are not there for long is therefore put off, and its
-// workgroup draws a ticket of the earliest step that any queue has left, if that is before its own, works on it, and comes back.  At the time it is drawn no
+// workgroup draws a ticket of the earliest step that any queue has left, if that is before its own, works on it, and so on until there is none; then it looks
+// at its own inputs again.  At the time such a ticket is drawn no
 // ticket of an earlier step is left, so all of those are in the hands of running workgroups; a workgroup works on the earliest ticket it holds; so the
 // earliest unfinished ticket is always being worked on, or will be once somebody's patience with a later one has run out, and waits for nothing.
+// A put-off costs FW_LOOKS of the workgroup's patience, so it must not be one per ticket of the other queues (three blocks of 197 tokens in six layers are 7500
+// tickets, which a lone workgroup would give up on): what was left before its step is done when it comes back, and only tasks in others' hands put it off again.
 // Two calls on one workspace at a time: as in flow.hip, the waits are bounded and the call reports POLY_ESTALL.
 #include "flow_dev.h"
 
@@ -350,7 +353,26 @@ __global__ __launch_bounds__(FL_THREADS, 2) void flow_wide_kernel(const FlowPara
         if (tid == 0) s_ticket = __hip_atomic_fetch_add(params()->queue + own * 16, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         unsigned ticket = __builtin_amdgcn_readfirstlane(s_ticket);
-        unsigned hq = FW_Q, hticket = 0;                       // a ticket of another queue that goes first
+        unsigned hq = FW_Q, hticket = 0, own_step = 0;         // a ticket of another queue that goes first; the step of the ticket that was put off
+        auto help = [&]() {                                    // is there a ticket of a step before that one that nobody has?
+            if (tid == 0) {
+                const ParamPtr p = params();
+                unsigned best = own_step, bt = 0, bq = FW_Q;
+                for (unsigned c = 0; c < FW_Q; ++c) {
+                    const unsigned t = peek(p->queue + c * 16);
+                    unsigned left = t;
+                    int s;
+                    const unsigned l = st.find(c, left, s);
+                    if (l < (unsigned)p->a.layers && l * 5 + s < best) { best = l * 5 + s; bt = t; bq = c; }
+                }
+                unsigned expect = bt;
+                if (bq < FW_Q && !__hip_atomic_compare_exchange_strong(p->queue + bq * 16, &expect, bt + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) bq = FW_Q;
+                s_help[0] = bq; s_help[1] = bt;
+            }
+            __syncthreads();
+            hq = __builtin_amdgcn_readfirstlane(s_help[0]); hticket = __builtin_amdgcn_readfirstlane(s_help[1]);
+            __syncthreads();
+        };
         for (;;) {
             const ParamPtr p = params();
             const bool helping = hq < FW_Q;
@@ -380,23 +402,9 @@ __global__ __launch_bounds__(FL_THREADS, 2) void flow_wide_kernel(const FlowPara
             else if (stage == 2) done = wide_resid_task<KD, CH, 2, NP>(k, fl_lds);
             else if (stage == 3) done = wide_norm_task<KD, 3, N1>(k, fl_lds);
             else done = wide_resid_task<KD, CH, 4, NP>(k, fl_lds);
-            if (!done) {                                       // its inputs are not there for long: is there a ticket of an earlier step that nobody has?
-                if (tid == 0) {
-                    unsigned best = layer * 5 + stage, bt = 0, bq = FW_Q;
-                    for (unsigned c = 0; c < FW_Q; ++c) {
-                        const unsigned t = peek(p->queue + c * 16);
-                        unsigned left = t;
-                        int s;
-                        const unsigned l = st.find(c, left, s);
-                        if (l < (unsigned)p->a.layers && l * 5 + s < best) { best = l * 5 + s; bt = t; bq = c; }
-                    }
-                    unsigned expect = bt;
-                    if (bq < FW_Q && !__hip_atomic_compare_exchange_strong(p->queue + bq * 16, &expect, bt + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) bq = FW_Q;
-                    s_help[0] = bq; s_help[1] = bt;
-                }
-                __syncthreads();
-                hq = __builtin_amdgcn_readfirstlane(s_help[0]); hticket = __builtin_amdgcn_readfirstlane(s_help[1]);
-                __syncthreads();
+            if (!done) {                                       // its inputs are not there for long
+                own_step = layer * 5 + stage;
+                help();
                 continue;
             }
             // ---- done: every wave's stores have reached device scope, then the task is counted
@@ -404,7 +412,7 @@ __global__ __launch_bounds__(FL_THREADS, 2) void flow_wide_kernel(const FlowPara
             if (tid == 0) s_ticket = next;
             __syncthreads();
             if (tid == 0) __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (helping) hq = FW_Q;
+            if (helping) help();
             else ticket = __builtin_amdgcn_readfirstlane(s_ticket);
         }
         __syncthreads();                                       // (s_ticket is written again for the next queue)

@@ -59,6 +59,23 @@ def test_fewer_workgroups_than_queues_come_to_the_end(workgroups):
     assert few["status"] == 0 and all_of_them["status"] == 0 and np.array_equal(few["logits"], all_of_them["logits"])
 
 
+def test_a_lone_workgroup_is_put_off_once_a_step_not_once_a_ticket():
+    cfg, w, frames, off, ids = _case(512, 48, 8, 15, 2, 870)
+    model = binding.DeviceModel(cfg, w, L0=0)
+    want = binding.run_forward(model, frames, off, ids)
+    tickets = len(ids) * 2 * (12 + 12 + 24 + 2 + 24)         # of a layer: two row tiles a block
+    patience = 32 * 256                                      # put-offs of 256 looks each: more than the ten steps of two layers, less than the tickets of seven queues
+    assert cfg.L == 2 and cfg.T == 37 and 10 < 32 < tickets * 7 // 8
+    binding.lib().poly_wait_workgroups(1)
+    binding.lib().poly_wait_limit(patience)
+    try:
+        alone = binding.run_forward(model, frames, off, ids)
+    finally:
+        binding.lib().poly_wait_workgroups(0)
+        binding.lib().poly_wait_limit(-1)
+    assert alone["status"] == 0 and np.array_equal(alone["logits"], want["logits"])
+
+
 def test_no_patience_reports_a_stall_and_writes_no_row():
     cfg, w, frames, off, ids = _case(512, 48, 8, 15, 2, 871)
     model = binding.DeviceModel(cfg, w, L0=1)
