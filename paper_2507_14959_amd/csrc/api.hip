@@ -434,8 +434,9 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         } else {
             const float *gain = base->ln1_g + (size_t)l * D, *shift = base->ln1_b + (size_t)l * D;
             const void *At = use(0) ? lora_ptr(lora->At[0], 0, D, 3 * D, true) : nullptr;
-            const bool shrunk = use(0) && launch_layernorm_shrink(x_in, w.u, gain, shift, D, m->ln_eps, T, nb, nb_dev, At, m->r, RP, m->lora_scale, R, R_dev,
-                                                                  (summed || fan) ? row_offsets : nullptr, w.adapter_of_row, w.S, dt, st);
+            const bool shrunk = use(0) && layernorm_shrink_fits(x_in, w.u, gain, shift, D, nb, At, RP, R, w.S, dt);
+            if (shrunk) POLY_TRY(launch_layernorm_shrink(x_in, w.u, gain, shift, D, m->ln_eps, T, nb, nb_dev, At, m->r, m->lora_scale, R, R_dev,
+                                                         (summed || fan) ? row_offsets : nullptr, w.adapter_of_row, w.S, st));
             const NormGemmArgs ng = {x_in, gain, shift, m->ln_eps, (const bf16_t *)Wqkv, base->qkv_b + (size_t)l * 3 * D, (bf16_t *)w.qkv, 3 * D, T, nb, nb_dev, false};
             const bool few = dt == POLY_BF16 && !use(0) && !fan && norm_gemm_fits(ng, D);
             if (few) POLY_TRY(launch_norm_gemm(ng, st));
@@ -520,8 +521,9 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         } else {
             const float *gain = base->ln2_g + (size_t)l * D, *shift = base->ln2_b + (size_t)l * D;
             const void *At = use(2) ? lora_ptr(lora->At[2], 2, D, Dm, true) : nullptr;
-            const bool shrunk = use(2) && launch_layernorm_shrink(x_out, w.u, gain, shift, D, m->ln_eps, T, n_out, n_out_dev, At, m->r, RP, m->lora_scale, R, R_dev,
-                                                                  summed ? row_offsets : nullptr, w.adapter_of_row, w.S, dt, st);
+            const bool shrunk = use(2) && layernorm_shrink_fits(x_out, w.u, gain, shift, D, n_out, At, RP, R, w.S, dt);
+            if (shrunk) POLY_TRY(launch_layernorm_shrink(x_out, w.u, gain, shift, D, m->ln_eps, T, n_out, n_out_dev, At, m->r, m->lora_scale, R, R_dev,
+                                                         summed ? row_offsets : nullptr, w.adapter_of_row, w.S, st));
             const NormGemmArgs ng = {x_out, gain, shift, m->ln_eps, (const bf16_t *)Wfc1, base->fc1_b + (size_t)l * Dm, (bf16_t *)w.h, Dm, T, n_out, n_out_dev, true};
             const bool few = dt == POLY_BF16 && !use(2) && norm_gemm_fits(ng, D);
             if (few) POLY_TRY(launch_norm_gemm(ng, st));

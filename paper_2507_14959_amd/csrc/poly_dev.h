@@ -445,10 +445,12 @@ bool norm_gemm_fits(const NormGemmArgs &a, int D);
 int launch_norm_gemm(const NormGemmArgs &a, hipStream_t st);
 
 // LayerNorm of n_blocks blocks and S = scale * y At[adapter_of_out[ob]]^T of their outputs ob (out_off: CSR offsets of every block's, null: block b itself)
-// in one launch; false, and nothing launched, where two launches do it
-bool launch_layernorm_shrink(const float *x, void *y, const float *gain, const float *shift, int D, float eps, int T, int n_blocks, const int *n_blocks_dev,
-                             const void *At, int r, int RP, float scale, int n_out, const int *n_out_dev, const int *out_off, const int *adapter_of_out,
-                             void *S, int dtype, hipStream_t st);
+// in one launch; two launches do it where that does not fit
+bool layernorm_shrink_fits(const float *x, const void *y, const float *gain, const float *shift, int D, int n_blocks, const void *At, int RP, int n_out,
+                           const void *S, int dtype);
+int launch_layernorm_shrink(const float *x, void *y, const float *gain, const float *shift, int D, float eps, int T, int n_blocks, const int *n_blocks_dev,
+                            const void *At, int r, float scale, int n_out, const int *n_out_dev, const int *out_off, const int *adapter_of_out, void *S,
+                            hipStream_t st);
 
 // S[ob] = scale * X[in_block_of_out[ob]] At[adapter_of_out[ob]]^T, zero padded to RP columns.  pair_off (nullable): CSR offsets
 // [n_in + 1] of the output blocks of every input block, when the output blocks of one input block are consecutive (fan-out):

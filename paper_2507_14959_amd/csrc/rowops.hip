@@ -690,24 +690,27 @@ int launch_layernorm(const float *x, void *y, const float *gain, const float *sh
     return hip_ok();
 }
 
-// False where the two run as launches of their own
-bool launch_layernorm_shrink(const float *x, void *y, const float *gain, const float *shift, int D, float eps, int T, int n_blocks, const int *n_blocks_dev,
-                             const void *At, int r, int RP, float scale, int n_out, const int *n_out_dev, const int *out_off, const int *adapter_of_out,
-                             void *S, int dtype, hipStream_t st)
+bool layernorm_shrink_fits(const float *x, const void *y, const float *gain, const float *shift, int D, int n_blocks, const void *At, int RP, int n_out,
+                           const void *S, int dtype)
 {
-    if (dtype != POLY_BF16 || RP != 16 || n_blocks <= 0 || n_out <= 0 || !aligned16(x) || !aligned16(y) || !aligned16(gain) || !aligned16(shift) ||
-        !aligned16(At) || !aligned16(S))
-        return false;
+    return dtype == POLY_BF16 && RP == 16 && D % 256 == 0 && D > 0 && D <= 1024 && n_blocks > 0 && n_out > 0 && aligned16(x) && aligned16(y) && aligned16(gain) &&
+           aligned16(shift) && aligned16(At) && aligned16(S);
+}
+
+int launch_layernorm_shrink(const float *x, void *y, const float *gain, const float *shift, int D, float eps, int T, int n_blocks, const int *n_blocks_dev,
+                            const void *At, int r, float scale, int n_out, const int *n_out_dev, const int *out_off, const int *adapter_of_out, void *S,
+                            hipStream_t st)
+{
     const int subs = (T + 15) / 16;
     const dim3 grid((unsigned)((size_t)n_blocks * subs));
 #define LN_SHRINK_CASE(N)                                                                                                                                       \
     case 256 * N:                                                                                                                                               \
         POLY_LAUNCH(POLY_STAGE_NORM, layernorm_shrink_kernel<N>, grid, dim3(256), st, x, (bf16_t *)y, gain, shift, eps, T, subs, n_blocks, n_blocks_dev,         \
                     (const bf16_t *)At, r, scale, out_off, n_out_dev, n_out, adapter_of_out, (bf16_t *)S);                                                       \
-        return true;
+        return hip_ok();
     switch (D) {
         LN_SHRINK_CASE(1) LN_SHRINK_CASE(2) LN_SHRINK_CASE(3) LN_SHRINK_CASE(4)
-        default: return false;
+        default: return POLY_EINVAL;
     }
 #undef LN_SHRINK_CASE
 }

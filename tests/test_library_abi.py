@@ -49,3 +49,18 @@ def test_workspace_size_grows_with_rows_and_rejects_bad_models():
     assert 0 < a < b
     d.D = 200      # not 64 * heads
     assert f(C.byref(d), 32, 58) == 0
+
+
+def test_a_launch_that_fails_is_reported():
+    """LayerNorm + shrink, called by itself: without a GPU no launch succeeds (host addresses, which no kernel gets to see)."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("needs a machine without a GPU")
+    from paper_2507_14959_amd import binding
+    launch = getattr(ctypes.CDLL(LIB), "_Z23launch_layernorm_shrinkPKfPvS0_S0_ifiiPKiPKvifiS3_S3_S3_S1_P12ihipStream_t")
+    p, i, f = ctypes.c_void_p, ctypes.c_int, ctypes.c_float
+    launch.argtypes = [p, p, p, p, i, f, i, i, p, p, i, f, i, p, p, p, p, p]
+    buf = ctypes.create_string_buffer(1 << 16)
+    a = (ctypes.addressof(buf) + 15) & ~15
+    for D, want in ((256, binding.POLY_EHIP), (1024, binding.POLY_EHIP), (320, binding.POLY_EINVAL)):
+        assert launch(a, a, a, a, D, 1e-6, 1, 1, None, a, 8, 1.0, 1, a, None, a, a, None) == want
