@@ -279,7 +279,7 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
         float t = 0.f;
 #pragma unroll
         for (int i = 0; i < KT; ++i) t += v[i][0] + v[i][1] + v[i][2] + v[i][3];
-        const float mean = row16_sum(t) * (1.0f / D);
+        const float mean = L::over(row16_sum(t), D);
         float q = 0.f;
 #pragma unroll
         for (int i = 0; i < KT; ++i)
@@ -290,7 +290,7 @@ __device__ __forceinline__ unsigned *norm_task(const Task &k, char *lds)
         for (int i = 0; i < KT; ++i) {
             f32x4 o;
 #pragma unroll
-            for (int z = 0; z < 4; ++z) o[z] = fmaf(fmaf(v[i][z], inv, nmi), gn[i][z], sh[i][z]);
+            for (int z = 0; z < 4; ++z) o[z] = fmaf(L::centred(v[i][z], mean, inv, nmi), gn[i][z], sh[i][z]);
             const int c = 4 * (part + 16 * i);
             *(quad_t *)(As + row * D + (((c >> 3) ^ (row & 7)) << 3) + (c & 4)) = L::round4(o);
         }
