@@ -200,7 +200,7 @@ __device__ __forceinline__ unsigned *attention_task(const Task &k, char *lds)
                     m = fmaxf(m, s[i][j][e]);
                 }
             m = fmaxf(m, __shfl_xor(m, 16, 64));
-            m = fmaxf(m, __shfl_xor(m, 32, 64));               // (the tile has a key inside T)
+            m = fmaxf(fmaxf(m, __shfl_xor(m, 32, 64)), -3.4e38f);    // (the tile has a key inside T; where all its scores are -infinity its keys count nothing)
             const float off = -m * sc;
             float t = 0.f;
             f32x4 pr[2];

@@ -36,3 +36,23 @@ def test_against_the_oracle(D, Dm, hw, blocks, r, targets, L0, compose):
     print(f"logits max-abs error {err:.2e} of up to {np.abs(want).max():.2f}")
     assert got["status"] == 0 and np.array_equal(got["logits"], again["logits"])
     assert err < 8e-3
+
+
+@pytest.mark.parametrize("dtype,D,bound", [(synth.DT_F32, 192, 2e-6), (synth.DT_BF16, 192, 8e-3), (synth.DT_BF16, 768, 8e-3)])
+def test_keys_whose_scores_overflow_count_nothing(dtype, D, bound):
+    """Every score of the second 32 keys is -infinity in 32 bits (-1e40), those of the first and the last key tile are not."""
+    cfg, w, frames, _, _ = synth.make_small_case(880, dtype=dtype, targets=3, L=1, F=2, r=4, n_adapters=4, D=D, heads=D // 64, Dm=256, hw=64, patch=8)
+    off, ids = synth.sets_to_csr([[0, 2], [3]])
+    rng = np.random.default_rng(880)
+    for n in ("patch_w", "patch_b", "cls", "ln1_b"):
+        w[n] = np.zeros_like(w[n])
+    d = rng.integers(1, 3, size=(cfg.T, D // 2)).astype(np.float32)
+    keys = np.arange(cfg.T)
+    d[(keys < 32) | (keys >= 64), 0] = 0                     # rows add up to nothing, so that a zero stays one when normalised
+    w["pos"] = np.concatenate([d, -d], axis=1)
+    w["qkv_w"][0, :, 0], w["qkv_b"][0, 0] = 0, 1e20          # first column of head 0's queries, and of its keys
+    w["qkv_w"][0, :, D], w["qkv_b"][0, D] = 0, 0
+    w["qkv_w"][0, 0, D] = -1e20
+    got = binding.run_forward(binding.DeviceModel(cfg, w, L0=1), frames, off, ids)
+    want = oracle.forward(cfg, w, frames, off, ids, L0=1)["logits"]
+    assert got["status"] == 0 and np.abs(got["logits"][:len(ids)] - want).max() < bound
