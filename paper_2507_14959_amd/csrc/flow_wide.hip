@@ -101,18 +101,18 @@ __device__ __forceinline__ unsigned *wide_norm_task(const Task &k, char *lds)
         float t = 0.f;
 #pragma unroll
         for (int i = 0; i < KT; ++i) t += v[i][0] + v[i][1] + v[i][2] + v[i][3];
-        const float mean = row16_sum(t) * (1.0f / D);
+        const float mean = row16_sum(t) / D;
         float q = 0.f;
 #pragma unroll
         for (int i = 0; i < KT; ++i)
 #pragma unroll
             for (int z = 0; z < 4; ++z) { const float d = v[i][z] - mean; q = fmaf(d, d, q); }
-        const float inv = rsqrtf(row16_sum(q) * (1.0f / D) + p->a.eps), nmi = -mean * inv;
+        const float inv = rsqrtf(row16_sum(q) * (1.0f / D) + p->a.eps);
 #pragma unroll
         for (int i = 0; i < KT; ++i) {
             f32x4 o;
 #pragma unroll
-            for (int z = 0; z < 4; ++z) o[z] = fmaf(fmaf(v[i][z], inv, nmi), gn[i % GC][z], sh[i % GC][z]);
+            for (int z = 0; z < 4; ++z) o[z] = fmaf((v[i][z] - mean) * inv, gn[i % GC][z], sh[i % GC][z]);     // (x inv - mean inv: an instruction less, see flow_dev.h)
             if (i + GC < KT) load_gain(i + GC);
             const int c = 4 * (part + 16 * i);
             *(bf16x4 *)(As + row * D + (((c >> 3) ^ (row & 7)) << 3) + (c & 4)) = pack4(o);

@@ -45,6 +45,31 @@ def test_tasks_and_layer_by_layer_against_the_oracle(Dm, hw, r, targets, L0, F):
     assert max(err.values()) < 8e-3                          # (as the layers of test_product_tiles.py)
 
 
+def test_rows_whose_mean_is_far_above_their_spread():
+    """Rows of 20001 plus whole numbers that add up to nothing: the mean is exact, and so is the sum of a normalised row, whose elements come in pairs of one size.
+    Values that sum it and a wide proj show a mean that is a rounding off (as in test_gpu_flow_fp32.py)."""
+    cfg, w, frames, _, _ = _case(256, 32, 4, 3, 2, 890, L=1)
+    off, ids = synth.sets_to_csr([[0], [1]])
+    rng = np.random.default_rng(890)
+    for n in ("patch_w", "patch_b", "cls", "qkv_b"):
+        w[n] = np.zeros_like(w[n])
+    d = rng.integers(-8, 9, size=(cfg.T, 384))
+    w["pos"] = (20001 + np.concatenate([d, -d], axis=1)[:, rng.permutation(768)]).astype(np.float32)
+    w["ln1_g"], w["ln1_b"] = np.ones_like(w["ln1_g"]), np.zeros_like(w["ln1_b"])
+    w["qkv_w"][..., 1536:] = 1.0
+    w["proj_w"] = synth.round_to_bf16(25 * w["proj_w"])
+    binding.poly_profile_begin(100)
+    try:
+        got = binding.run_forward(binding.DeviceModel(cfg, w, L0=1), frames, off, ids)
+    finally:
+        prof = binding.poly_profile_end()
+    err = np.abs(got["logits"] - oracle.forward(cfg, w, frames, off, ids, L0=1)["logits"]).max()
+    print(f"{err:.2e}")
+    # the stream is rounded to 2^-9 = 2e-3 of a spread of 5, 1.1e-4 rms; a head sums 768 of that times N(0, 0.02): 0.55 x 1.1e-4 twice, six of it at most.
+    # 4e-2 with the mean a rounding off
+    assert got["status"] == 0 and prof["attention"]["launches"] == 0 and err < 6e-4
+
+
 @pytest.mark.parametrize("workgroups", [1, 3, 9])
 def test_fewer_workgroups_than_queues_come_to_the_end(workgroups):
     """A workgroup that waits for what no running workgroup has drawn does it itself."""
