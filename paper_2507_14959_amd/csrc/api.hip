@@ -1,5 +1,6 @@
 // C-ABI entry points: argument checks, workspace carving and the launch sequence of the forward.
 #include "poly_dev.h"
+#include "row_waves.h"
 
 namespace {
 
@@ -325,14 +326,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         return POLY_OK;
     };
 
-    // (frame, adapter) pairs that only the device knows: between one a frame and the bound, and the choice may fall on one each however much room there is: the row
-    // kernels for many rows are taken only where they are no slower there either.  us per call, 64 rows a tile / many rows, a bound of four a frame, the last two
-    // layers of twelve adapted, one / two / three adapters on every frame: 34 frames 461 / 492, 515 / 497, 531 / 513, 64 frames 495 / 512, 561 / 531,
-    // 622 / 631; a bound of five, every layer, 32 frames: 472 / 672, 553 / 696, 877 / 786.
-    // Room for up to three a frame is mostly half used: a tenth slower at one each is taken (100 frames, a bound of three, 1.8 each, every layer: 1288 / 1050;
-    // the 128-row tiles, no slower at one each, 1398).
-    const int pairs = (F + R) / 2, pairs_least = F;
-    const float pairs_slack = R > 3 * F ? 1.f : 1.1f;
+    const PairCount pairs = pair_count(F, R);
 
     // What the row-wise part of layer l is: whether one launch does it, whether the next layer's qkv linear is in it (that layer works on the same blocks
     // and its linear needs no GEMM path for summed terms), with adapters, and the waves of rowreg.hip, 0: tiles of rowlayer.hip
@@ -345,8 +339,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         const bool qkv_lora = ln >= m->L0 && R > 0 && (m->targets & 1);
         RowPart p = {true, ln < m->L && (sum || ln != m->L0) && !(sum && qkv_lora), false, 0};
         p.lora_q = p.qkv && qkv_lora;
-        p.waves = rowreg_waves(T, D, Dm, use(1) || p.lora_q ? m->r : 0, use(1) || p.lora_q || (branch && l == m->L0), branch ? pairs : F, branch ? pairs_least : F,
-                               branch ? pairs_slack : 1.f);
+        p.waves = rowreg_waves(T, D, Dm, use(1) || p.lora_q ? m->r : 0, use(1) || p.lora_q || (branch && l == m->L0), branch ? pairs : known_count(F));
         return p;
     };
     bool x_fragments = false;                  // the residual stream lies in the order of rowreg.hip: between two of its launches that nothing reads it between
@@ -425,8 +418,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
             a.Wqt = (const bf16_t *)Wqkv; a.bq = base->qkv_b + (size_t)l * 3 * D;
             if (use(0)) { a.Aqt = (const bf16_t *)lora_ptr(lora->At[0], 0, D, 3 * D, true); a.Bqt = (const bf16_t *)lora_ptr(lora->Bt[0], 0, D, 3 * D, false); }
             a.qkv_out = (bf16_t *)w.qkv;
-            const int waves = rowreg_waves(T, D, Dm, use(0) ? m->r : 0, use(0) || fan, n_out_dev == R_dev ? pairs : n_out, n_out_dev == R_dev ? pairs_least : n_out,
-                                           n_out_dev == R_dev ? pairs_slack : 1.f);
+            const int waves = rowreg_waves(T, D, Dm, use(0) ? m->r : 0, use(0) || fan, n_out_dev == R_dev ? pairs : known_count(n_out));
             POLY_TRY(waves ? launch_rowreg(a, waves, st) : launch_rowlayer(a, st));
         } else if (fused(0)) {
             POLY_TRY(rowlin(0, x_in, base->ln1_g + (size_t)l * D, base->ln1_b + (size_t)l * D, nullptr, fan_map, Wqkv,
@@ -452,7 +444,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
                 lora_gemm(g, 0, Bt);
             }
             g.mode = EPI_STORE; g.out = w.qkv; g.Tout = T;
-            if (!few) POLY_TRY(launch_gemm(g, {!branch, pairs}, dt, st));
+            if (!few) POLY_TRY(launch_gemm(g, {!branch, pairs.usual}, dt, st));
         }
         // (as a rule a frame has an adapter, so that there are about as many row-blocks as frames or more)
         POLY_TRY(launch_attention(w.qkv, w.o, T, D, m->heads, n_out, n_out_dev, n_out < F ? n_out : F, dt, rows.waves > 0, st));
@@ -502,7 +494,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
                 lora_gemm(g, 1, Bt);
             }
             g.mode = EPI_RESID; g.out = x_out; g.Tout = T; g.res = x_in; g.res_block_of_out = fan_map;
-            POLY_TRY(launch_gemm(g, {n_out_dev != R_dev, pairs}, dt, st));
+            POLY_TRY(launch_gemm(g, {n_out_dev != R_dev, pairs.usual}, dt, st));
         }
         // ---- MLP half (x_out holds the stream from here on)
         if (dt == POLY_BF16 && !use(2) && !use(3) && mlp_supported(D, Dm)) {
@@ -538,7 +530,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
                 lora_gemm(g, 2, Bt);
             }
             g.mode = EPI_GELU; g.out = w.h; g.Tout = T;
-            if (!few) POLY_TRY(launch_gemm(g, {n_out_dev != R_dev, pairs}, dt, st));
+            if (!few) POLY_TRY(launch_gemm(g, {n_out_dev != R_dev, pairs.usual}, dt, st));
         }
         {
             GemmArgs g = {};
@@ -551,7 +543,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
                 lora_gemm(g, 3, Bt);
             }
             g.mode = EPI_RESID; g.out = x_out; g.Tout = T; g.res = x_out;
-            POLY_TRY(launch_gemm(g, {n_out_dev != R_dev, pairs}, dt, st));
+            POLY_TRY(launch_gemm(g, {n_out_dev != R_dev, pairs.usual}, dt, st));
         }
     }
 

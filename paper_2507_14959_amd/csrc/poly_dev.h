@@ -282,12 +282,10 @@ struct RowLayerArgs {
 };
 bool rowlayer_supported(int D, int Dm, int r);
 int launch_rowlayer(const RowLayerArgs &a, hipStream_t st);
-// The same on tiles of 32 rows per wave, all of a wave's rows in its registers (rowreg.hip): waves per workgroup where `blocks` blocks of T rows are
-// that many that it is faster, and on `least` blocks, where there may be as few, no slower than `slack` times; 0 where they are not or it does not apply.  r: rank of the adapters in the launch, 0 without; by_block: adapters or a map.
+// The same with 32 rows per wave, all of a wave's rows in its registers (rowreg.hip; row_waves.h says where).
 // Its order, of o and where the flags say so of the residual stream, on the rows of all blocks as one run: groups of 32 rows; in a group, of a 16-bit
 // value, [column / 16][column / 8 % 2][row][column % 8], of a float [column / 8][column / 4 % 2][row][column % 4].  The last group of a buffer may reach
 // 31 rows past the last row.
-int rowreg_waves(int T, int D, int Dm, int r, bool by_block, int blocks, int least, float slack);
 int launch_rowreg(const RowLayerArgs &a, int waves, hipStream_t st);
 int launch_rowlin(const RowLinArgs &a, hipStream_t st);
 

@@ -21,17 +21,16 @@
 // Tried and dropped: five, six or seven waves (the SIMDs with two waves set the pace: as slow as eight); a wave's GELU as a block that alternates with the
 // other wave's products (the same time, but nothing under it where there is one wave per SIMD); the GELU as a polynomial (5.6 k cycles per 64 columns).
 #include "poly_dev.h"
+#include "row_waves.h"
 #include "rowtile.h"
 
 #include <type_traits>
 
 namespace {
 
-constexpr int RR_D = 192;           // model width
 constexpr int RR_SLOTS = 4;         // of the ring of weights
 constexpr int RR_UNIT = 24576;      // bytes of one: three tiles [64][64]
 constexpr int RR_STAGE = 4096;      // bytes of a wave's staging area: 32 rows x 128 bytes
-constexpr int RR_MAX_DM = 768;
 constexpr int RR_GELU = (GELU_TAB_ENTRIES + 1) & ~1;
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -404,8 +403,8 @@ __global__ __launch_bounds__(64 * W, 2) void rowreg_kernel(const RowLayerArgs a)
             }
         };
         // step: GELU of `cur` -> out; x += prev * K; next = columns of N
-constexpr int PS = 4;
-                auto step = [&](auto I, const f32x16 &cur, bf16x8(&out)[2], const bf16x8(&prev)[2], f32x16 &next, const float *b, auto last, auto side) {
+        constexpr int PS = 4;
+        auto step = [&](auto I, const f32x16 &cur, bf16x8(&out)[2], const bf16x8(&prev)[2], f32x16 &next, const float *b, auto last, auto side) {
             constexpr int i = decltype(I)::value, M = 4 * NJ;       // 2 NJ of x and as many of the next columns
             constexpr bool end = decltype(last)::value;
 #pragma unroll
@@ -598,25 +597,6 @@ template <int W> int launch_w(const RowLayerArgs &a, hipStream_t st)
 }
 
 }  // namespace
-
-int rowreg_waves(int T, int D, int Dm, int r, bool by_block, int blocks, int least, float slack)
-{
-    if (D != RR_D || Dm < 128 || Dm % 64 || Dm > RR_MAX_DM || (r && r != 8 && r != 16) || (by_block && T < 32)) return 0;
-    // us of n workgroups, a CU each at a time: a round takes `c`, and up to `d` more the more CUs are at work (they share the memory and the power).  A layer
-    // of DeiT-tiny, tiles of 64 / 128 / 256 rows, twelve layers and everything else of a forward: 12214 rows 486 / 610 / 772 us, 18912 817 / 678 / 839,
-    // 32702 941 / 808 / 941, 37430 1255 / 1247 / 1039, 57130 1656 / 1424 / 1212, 65601 (a row in a round of its own) 1956 / 1875 / 1834; with adapters 14184
-    // rows (288 tiles that end with their block) 809 / 714 / 891, 28368 1257 / 897 / 1047, 42552 1665 / 1482 / 1171.
-    auto rounds = [](long n, float c, float d) { return (float)(n / 256) * (c + d) + (n % 256 ? c + d * (float)(n % 256) / 256.f : 0.f); };
-    auto us = [&](int waves, int n) {
-        const long rows = (long)n * T;
-        if (waves == 0) return rounds(by_block ? (long)n * ((T + 63) / 64) : (rows + 63) / 64, r ? 31.f : 27.5f, 0.f);
-        return waves == 4 ? rounds((rows + 127) / 128, r ? 46.f : 36.f, 8.f) : rounds((rows + 255) / 256, r ? 58.f : 48.f, 30.f);
-    };
-    int best = 0;
-    for (int waves : {4, 8})
-        if (us(waves, blocks) < us(best, blocks) && us(waves, least) <= us(0, least) * slack) best = waves;
-    return best;
-}
 
 int launch_rowreg(const RowLayerArgs &a, int waves, hipStream_t st)
 {

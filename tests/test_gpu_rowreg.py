@@ -28,7 +28,7 @@ def _want(cfg, w, frames, sets, rows, L0):
     return oracle.forward(cfg, w, frames, off, ids, L0=L0)["logits"][rows]
 
 
-@pytest.mark.parametrize("F,hw,patch,Dm,r,targets,per_frame,spare", [
+CASES = [
     (460, 48, 8, 768, 8, 3, 1, 0),        # 37 tokens, 128-row tiles, 28 rows in the last wave
     (300, 48, 8, 128, 16, 3, 2, 0),       # the count only on the device; the shortest hidden width
     (460, 48, 8, 192, 16, 1, 1, 60),      # room for more blocks than there are; adapters on qkv only
@@ -36,7 +36,10 @@ def _want(cfg, w, frames, sets, rows, L0):
     (900, 48, 8, 256, 8, 3, 1, 0),        # 256-row tiles, 20 rows in the last of them: waves without any
     (700, 40, 8, 192, 16, 3, 1, 0),       # 26 tokens: by itself a block shorter than a wave's rows keeps the tiles of 64 rows where adapters differ
     (100, 112, 8, 768, 16, 3, 2, 0),      # 197 tokens
-])
+]
+
+
+@pytest.mark.parametrize("F,hw,patch,Dm,r,targets,per_frame,spare", CASES)
 @pytest.mark.parametrize("L0", [0, 1, 3])
 def test_against_the_oracle(F, hw, patch, Dm, r, targets, per_frame, spare, L0):
     cfg, w, frames, sets, many, off, ids, rows = _case(F, hw, patch, Dm, r, targets, per_frame)
@@ -55,12 +58,15 @@ def test_against_the_oracle(F, hw, patch, Dm, r, targets, per_frame, spare, L0):
     assert np.array_equal(logits, logits[first[rows]])     # wherever in a tile a block lies
 
 
-@pytest.mark.parametrize("F,spare", [
-    (120, 400),      # at one adapter a frame tiles of 64 rows are faster
-    (250, 300),
-    (460, 1000),     # .. waves of 32
-])
-def test_much_room_takes_the_kernels_of_few_adapters(F, spare):
+ROOM = [
+    (120, 400, 0),       # at one adapter a frame tiles of 64 rows are faster
+    (250, 300, 0),
+    (460, 1000, 4),      # .. waves of 32
+]
+
+
+@pytest.mark.parametrize("F,spare,taken", ROOM)
+def test_much_room_takes_the_kernels_of_few_adapters(F, spare, taken):
     """Room for several blocks a frame and one on every frame: the kernels, and so the bits, of a call without room."""
     cfg, w, frames, sets, many, off, ids, rows = _case(F, 48, 8, 192, 8, 3, 1)
     model = binding.DeviceModel(cfg, w, L0=0)
@@ -78,6 +84,9 @@ def test_summed_shared_layers():
     assert np.abs(got["logits"] - oracle.forward(cfg, w, frames, o, i, L0=2, compose="sum")["logits"][rows]).max() < BOUND
 
 
+LOOP = (460, 48, 8, 256, 8, 3)   # frames, their size, patch, hidden width, rank, row-blocks a frame that there is room for
+
+
 @pytest.mark.parametrize("compose,targets,L0,room", [
     ("sum", 0, 1, 3),        # no linear adapted: the row kernels go on past the selection, which reads the rows before they do
     ("sum", 0, 2, 3),
@@ -88,8 +97,9 @@ def test_summed_shared_layers():
     ("branch", 3, 3, 3),     # no adapted layer
 ])
 def test_the_lagged_loop(compose, targets, L0, room):
-    F, dev = 460, "cuda"
-    cfg, w, _, _, many, _, _, _ = _case(F, 48, 8, 256, 8, targets, 1)
+    dev = "cuda"
+    F, hw, patch, Dm, r, _ = LOOP
+    cfg, w, _, _, many, _, _, _ = _case(F, hw, patch, Dm, r, targets, 1)
     K = cfg.n_adapters * cfg.C
     member = synth.make_group_membership(cfg.n_adapters, cfg.C)
     cap, theta = room * F, 0.5 if room else 2.0            # (without room no label may be on)
