@@ -38,25 +38,6 @@ namespace {
 template <typename F, int... I> __device__ __forceinline__ void static_for_each(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>()), ...); }
 template <int N, typename F> __device__ __forceinline__ void static_for(F f) { static_for_each(f, std::make_integer_sequence<int, N>()); }
 
-// The j-th of the tiles of one of eight runs: all tiles in the order (panel of `panel` column tiles, row tile, column tile inside the panel) are cut
-// into eight equal runs, one per XCD: a run covers one or two W panels and a contiguous range of row tiles, and no XCD has more than one tile more than
-// another.  False, and j less the run's tiles, if the run has no such tile.
-__device__ __forceinline__ bool xcd_tile(int xcd, int &j, int tiles_mtot, int tiles_n, int panel, int &mt, int &tn)
-{
-    const long total = (long)tiles_mtot * tiles_n;
-    const long lo = total * xcd / 8, hi = total * (xcd + 1) / 8;
-    const long L = lo + j;
-    if (L >= hi) { j -= (int)(hi - lo); return false; }
-    const long full = (long)tiles_mtot * panel;            // tiles per full panel
-    const int pn = (int)(L / full);
-    const int rem = (int)(L - pn * full);
-    const int n_lo = pn * panel;
-    const int width = min(panel, tiles_n - n_lo);
-    mt = rem / width;
-    tn = n_lo + rem - mt * width;
-    return true;
-}
-
 // BM x BN tile, WM x WN waves, each wave (BM/WM) x (BN/WN) = (MI*32) x (NJ*32); NS LDS stages of 64 k-columns.
 // EK, the epilogue: 0 = subtile by subtile (fp32 output with residual / position rows, or one column subtile per wave);
 // 1, 2 = row-wise for bf16 output (two column subtiles per wave): 2 when the host knows that a wave's region touches at most two
@@ -686,7 +667,7 @@ template <int BM, int BN, int WM, int WN, int NS, int EK>
 __global__ __launch_bounds__(64 * WM * WN, (BM * BN >= 256 * 256 || NS * (BM + BN) * 128 > 80 * 1024) ? 1 : 2)
 void gemm_bf16_dma_kernel(const GemmArgs g, int tiles_m, int tiles_n)
 {
-    constexpr int PANEL = 768 / BN;                        // column tiles per L2 panel (1.2 MB of W at K = 768)
+    constexpr int PANEL = panel_tiles(BN);
     // The eight runs are cut from the tiles that exist: the grid is sized for the caller's bound on the blocks, which can be
     // half as many again as the true count, and the tiles past it would all fall on the last XCDs (config 3 with room for 3
     // adapters on each of 64 frames: five of eight XCDs busy, 178 us per qkv or fc1 launch instead of 131).  The workgroups left over exit at once.
@@ -701,7 +682,7 @@ void gemm_bf16_dma_kernel(const GemmArgs g, int tiles_m, int tiles_n)
     const bool has = xcd_tile(xcd, j, flat ? (large + BM - 1) / BM : n_true * tiles_m, tiles_n, PANEL, mt, tn);
     if constexpr (TAIL) {
         if (!has) {
-            if (large < Tlim && xcd_tile(xcd, j, (Tlim - large + 127) / 128, (g.N + 127) / 128, 6, mt, tn))
+            if (large < Tlim && xcd_tile(xcd, j, (Tlim - large + 127) / 128, (g.N + 127) / 128, panel_tiles(128), mt, tn))
                 dma_tile<128, 128, 4, 2, 4, EK, true>(g, true, Tlim, 0, large + mt * 128, tn * 128);
             return;
         }
@@ -729,14 +710,7 @@ static void launch_dma_ek(const GemmArgs &g, hipStream_t st)
         }
     }
     const int tiles_m = (g.T + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-    long run = ((long)g.n_in * tiles_m * tiles_n + 7) / 8; // workgroups of an XCD
-    if (K::TAIL && g.Tb) {
-        if (g.n_in_dev) run += (MAX_TAIL + 7) / 8;         // (fewer blocks than the bound may have a tail where the bound has none)
-        else {
-            const int large = large_tile_rows(g.T, g.N, BM, BN);
-            run = ((long)((large + BM - 1) / BM) * tiles_n + 7) / 8 + (tail_tiles(g.T - large, g.N) + 7) / 8;
-        }
-    }
+    const long run = xcd_workgroups((long)g.n_in * tiles_m * tiles_n, K::TAIL && g.Tb, !g.n_in_dev, g.T, g.N, BM, BN);
     POLY_LAUNCH_SHMEM(POLY_STAGE_GEMM, kern, dim3((unsigned)(8 * run)), dim3(K::THREADS), K::LDS, st, g, tiles_m, tiles_n);
 }
 

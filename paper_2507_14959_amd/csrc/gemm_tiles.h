@@ -60,6 +60,37 @@ constexpr int large_tile_rows(int rows, int N, int bm, int bn)
     return tail_tiles(rows - large, N) <= MAX_TAIL ? large : rows;
 }
 
+// ---- which workgroup takes which tile
+constexpr int panel_tiles(int bn) { return 768 / bn; }     // column tiles per L2 panel (1.2 MB of W at K = 768)
+
+// The j-th of the tiles of one of eight runs: all tiles in the order (panel of `panel` column tiles, row tile, column tile inside the panel) are cut
+// into eight equal runs, one per XCD: a run covers one or two W panels and a contiguous range of row tiles, and no XCD has more than one tile more than
+// another.  False, and j less the run's tiles, if the run has no such tile: with a tail, j is then its place in the XCD's run of the 128 x 128 tiles.  (Inlined before the optimiser looks at the kernel: later, the kernel of two tiles spills ten times the registers.)
+__attribute__((always_inline)) constexpr bool xcd_tile(int xcd, int &j, int tiles_mtot, int tiles_n, int panel, int &mt, int &tn)
+{
+    const long total = (long)tiles_mtot * tiles_n;
+    const long lo = total * xcd / 8, hi = total * (xcd + 1) / 8;
+    const long L = lo + j;
+    if (L >= hi) { j -= (int)(hi - lo); return false; }
+    const long full = (long)tiles_mtot * panel;            // tiles per full panel
+    const int pn = (int)(L / full);
+    const int rem = (int)(L - pn * full);
+    const int n_lo = pn * panel;
+    const int width = panel < tiles_n - n_lo ? panel : tiles_n - n_lo;
+    mt = rem / width;
+    tn = n_lo + rem - mt * width;
+    return true;
+}
+
+// Workgroups of an XCD in a grid of `tiles` large tiles or, with a tail, of `rows` rows; known: the number of rows is no bound
+constexpr long xcd_workgroups(long tiles, bool tail, bool known, int rows, int N, int bm, int bn)
+{
+    if (!tail) return (tiles + 7) / 8;
+    if (!known) return (tiles + 7) / 8 + (MAX_TAIL + 7) / 8;   // (fewer blocks than the bound may have a tail where the bound has none)
+    const int large = large_tile_rows(rows, N, bm, bn);
+    return ((long)((large + bm - 1) / bm) * ((N + bn - 1) / bn) + 7) / 8 + (tail_tiles(rows - large, N) + 7) / 8;
+}
+
 inline long product_tiles(int n_in, int T, int N, int bm, int bn) { return (long)n_in * ((T + bm - 1) / bm) * ((N + bn - 1) / bn); }
 
 inline bool fetches_ahead(const TileCost &c, const TiledProduct &p)

@@ -15,6 +15,22 @@ MORE = """
 extern "C" int large_rows(int rows, int N, int bm, int bn) { return large_tile_rows(rows, N, bm, bn); }
 extern "C" long tail(int rows, int N) { return tail_tiles(rows, N); }
 extern "C" int may(int bm, int bn, int mode, int ahead) { return has_tail(bm, bn, mode, ahead); }
+extern "C" long run(int known, int rows, int N, int bm, int bn)          // workgroups of an XCD
+{
+    return xcd_workgroups((long)((rows + bm - 1) / bm) * ((N + bn - 1) / bn), true, known != 0, rows, N, bm, bn);
+}
+// The tile of workgroup 8 j + xcd of a launch whose true count is `rows`, as the kernel finds it: row, column, tile rows, tile columns
+extern "C" int tile(int xcd, int j, int rows, int N, int bm, int bn, int *at)
+{
+    const int large = large_tile_rows(rows, N, bm, bn);
+    int mt, tn;
+    if (xcd_tile(xcd, j, (large + bm - 1) / bm, (N + bn - 1) / bn, panel_tiles(bn), mt, tn)) { at[0] = mt * bm; at[1] = tn * bn; at[2] = bm; at[3] = bn; return 1; }
+    if (large < rows && xcd_tile(xcd, j, (rows - large + 127) / 128, (N + 127) / 128, panel_tiles(128), mt, tn)) {
+        at[0] = large + mt * 128; at[1] = tn * 128; at[2] = at[3] = 128;
+        return 1;
+    }
+    return 0;
+}
 """
 
 
@@ -25,22 +41,13 @@ def lib(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", f"-I{CSRC}", "-o", str(d / "shim.so"), str(d / "shim.cpp")], check=True)
     lib = ctypes.CDLL(str(d / "shim.so"))
     lib.pick.argtypes = [ctypes.c_int] * 6 + [ctypes.c_float] + [ctypes.c_int] * 3 + [ctypes.POINTER(ctypes.c_float)]
-    lib.tail.restype = ctypes.c_long
+    lib.tail.restype = lib.run.restype = ctypes.c_long
     return lib
 
 
-def workgroups(xcd, j, rows, N, bm, bn, large):
-    """The tile that workgroup 8 j + xcd takes, as the kernel finds it: (row, column, tile rows, tile columns), or None."""
-    for m_tiles, n_tiles, row0, hm, hn in ((-(-large // bm), -(-N // bn), 0, bm, bn), (-(-(rows - large) // 128), -(-N // 128), large, 128, 128)):
-        panel, total = 768 // hn, m_tiles * n_tiles
-        lo, hi = total * xcd // 8, total * (xcd + 1) // 8
-        if lo + j >= hi:
-            j -= hi - lo
-            continue
-        pn, rem = divmod(lo + j, m_tiles * panel)
-        width = min(panel, n_tiles - pn * panel)
-        return row0 + rem // width * hm, (pn * panel + rem % width) * hn, hm, hn
-    return None
+def workgroups(lib, xcd, j, rows, N, bm, bn):
+    at = (ctypes.c_int * 4)()
+    return tuple(at) if lib.tile(xcd, j, rows, N, bm, bn, at) else None
 
 
 @pytest.mark.parametrize("bm,bn", [(256, 256), (256, 128)])
@@ -52,16 +59,16 @@ def test_every_row_is_taken_once_and_the_grid_is_large_enough(lib, bm, bn, N):
         n_tiles = -(-N // bn)
         assert large == rows or (large % bm == 0 and 0 < large < rows and lib.tail(rows - large, N) <= 256 and large // bm * n_tiles % 256 in (0, *range(257 - n_tiles, 256)))
         tails += large < rows
-        run = -(-(-(-large // bm) * n_tiles) // 8) + -(-lib.tail(rows - large, N) // 8)
-        bound = -(-(-(-rows // bm) * n_tiles) // 8) + 32
-        assert run <= bound                                      # (a launch whose count only the device knows)
+        run = lib.run(1, rows, N, bm, bn)
+        for bound in (rows, rows + 971, 2 * rows):
+            assert run <= lib.run(0, bound, N, bm, bn)           # (a launch whose count only the device knows)
         seen = np.zeros((rows // 128 + 2, n_tiles * bn // 128), dtype=int)
         for bid in range(8 * run):
-            at = workgroups(bid & 7, bid >> 3, rows, N, bm, bn, large)
+            at = workgroups(lib, bid & 7, bid >> 3, rows, N, bm, bn)
             if at:
                 seen[at[0] // 128:(at[0] + at[2]) // 128, at[1] // 128:(at[1] + at[3]) // 128] += 1
         assert np.all(seen[:-(-rows // 128), :-(-N // 128)] == 1)
-        assert all(workgroups(x, run, rows, N, bm, bn, large) is None for x in range(8))
+        assert all(workgroups(lib, x, run, rows, N, bm, bn) is None for x in range(8))
     assert tails > 0
 
 
