@@ -22,8 +22,8 @@ enum {
     POLY_STAGE_SELECT = 0, /* Alg. 2 kernel */
     POLY_STAGE_GEMM = 1,   /* base linears with fused expand and epilogue (patch embedding included), and launches that hold more: the
                               row kernels (LayerNorm and shrink too), the task queues (a run of whole layers: attention, LayerNorm and
-                              shrink too), the patch embedding of few frames or in single precision (with the gathering, the class token and
-                              the CSR check), LayerNorm + linear of few frames of a wide model, and the isolated linear of a small call (CSR
+                              shrink too), the patch embedding of frames that its product gathers itself (with the class token and the CSR
+                              check), LayerNorm + linear of few frames of a wide model, and the isolated linear of a small call (CSR
                               check and shrink too) */
     POLY_STAGE_SHRINK = 2, /* x A_k, where it is a launch of its own (of the isolated bf16 linear: with the CSR check) */
     POLY_STAGE_ATTN = 3,   /* where it is a launch of its own */

@@ -34,8 +34,9 @@ struct FlowSegment {
 // The 768-wide backbone: 7 tiles in the shared layers, 21 in the adapted ones, which layer by layer have four shrinks more.  Forward, us: ten layers shared,
 // 1 tile 444 / 483, 4 493 / 567, 7 490 / 626, 8 600 / 579, 10 590 / 572; adapted on every linear, 1 tile 462 / 716, 7 502 / 891, 14 654 / 929, 21 773 / 981,
 // 21 of which 13 exist 569 / 936, 42 with 25 1136 / 1106.
-// Single precision: at 64 and 128 columns layer by layer, where the size that poly_forward_workspace_bytes names is the least that is taken and less is
-// refused, as callers may rely on; at 192 columns 165 tiles (220 adapted ones, of which a call mostly fills a part) times the square of the part of their rows that
+// Single precision: at 64 and 128 columns layer by layer, not for speed (nobody has measured the tasks there) but because tests/test_gpu_stream.py asks that a call
+// of such a model with 256 bytes less than poly_forward_workspace_bytes names is refused, and with room for the tasks in that size it would be taken (as it
+// is at other widths); at 192 columns 165 tiles (220 adapted ones, of which a call mostly fills a part) times the square of the part of their rows that
 // exist, for the other way runs its rows across blocks and its larger tiles gain with their number.  Four shared layers of 192 columns, us, layer by layer / as
 // tasks, blocks of 17 tokens (1 tile each; 32 in any case): 71 217 / 227, 100 286 / 308, 143 320 / 425; of 50 (2) 52 329 / 324, 73 441 / 434, 84 460 / 490; of 101 (4) 37 470 / 438,
 // 42 488 / 495, 53 503 / 617; of 197 (7) 23 661 / 613 (adapted on all linears), 26 538 / 559; of 122 (4), adapted, 44 573 / 595 (so 168 tiles at most).  With adapters the lines lie a tenth higher.

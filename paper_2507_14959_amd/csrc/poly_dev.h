@@ -289,7 +289,7 @@ int launch_rowlayer(const RowLayerArgs &a, hipStream_t st);
 int launch_rowreg(const RowLayerArgs &a, int waves, hipStream_t st);
 int launch_rowlin(const RowLinArgs &a, hipStream_t st);
 
-// A run of whole layers on few blocks in one launch (flow.hip); bf16, D <= 192.  Weight pointers are those of the first layer of the
+// A run of whole layers on few blocks in one launch: bf16 at 64, 128 and 192 columns and single precision at 192 (flow.hip), bf16 at 768 (flow_wide.hip).  Weight pointers are those of the first layer of the
 // run, one layer of a stack behind the other.
 struct FlowArgs {
     int T, D, Dm, heads, layers;

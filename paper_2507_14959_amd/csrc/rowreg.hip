@@ -12,7 +12,8 @@
 // 4.5 k for twice the rows (3.07 k of MFMA; 3.7 k without GELU and without reading the weights again).  A launch of all three parts, 197-token blocks
 // without adapters: 128 blocks 54.6 us as 394 tiles of 64 rows in two rounds, 39 us as 197 tiles of 128; 320 blocks 116 us in four rounds, 76 us as 247
 // tiles of 256.  Of the 76 us 11 are spent on the first loads (75 MB that all CUs want at once, 6.8 TB/s) and 25 behind B on stores of 125 MB beside the
-// qkv products; the 31 to 36 of B run at the clock that the power leaves (1.5 to 1.75 GHz; 2.28 with 80 tiles).
+// qkv products; the 30 to 36 of B run at the clock that the power leaves (cycle counter against the constant clock: 1.75 to 1.9 GHz, 2.3 before B; 256 tiles
+// of 128 rows 2.0 to 2.1, 197 of them 2.3 to 2.4).
 //
 // Rows are tiled as one run over all blocks, with adapters too: a wave's rows lie in one block or two (a block has 32 or more), and a wave in two blocks
 // computes both low-rank terms and takes each row's own.  The attention output and, between two of these launches, the residual stream lie in the order of

@@ -1,5 +1,5 @@
 // Building blocks of the kernels that load through LDS by hand-counted waits or keep a tile of 64 token rows on chip: rowlin.hip, mlp.hip, rowlayer.hip,
-// rowops.hip, gemm.hip, gemm_ks.hip, flow.hip.
+// rowreg.hip, rowops.hip, gemm.hip, gemm_ks.hip, norm_gemm.hip, patch.hip, flow.hip, flow_wide.hip.
 #pragma once
 #include "poly_dev.h"
 
@@ -23,7 +23,8 @@ __device__ __forceinline__ void glds16_s(const void *sbase, unsigned voff, unsig
 // (All lanes of the wave are active.)
 // Every wait of a ring rests on this: a load with EXEC = 0 goes through vmcnt in its place in the order.  Were it skipped, the waits past the last k-tile
 // would let loads that move something stay in flight.  tests/test_product_tiles.py has contractions of a single k-tile on two and four stages, where all
-// loads behind those of the first wait are off; three stages are taken from a contraction of 512 on, where the last two waits rest on it.
+// loads behind those of the first wait are off; its three stages are taken from a contraction of 512 on, where the last two waits rest on it, as they do in
+// norm_gemm.hip (three stages, twelve k-tiles: tests/test_gpu_norm_shrink.py) and patch.hip (three stages, from three k-tiles on: tests/test_gpu_patch_embed.py).
 __device__ __forceinline__ void glds16_if(const void *sbase, unsigned voff, unsigned lds_byte_addr, int go)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_cmp_gt_i32 %3, 0\n\ts_cselect_b64 exec, -1, 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1" ::"s"(
