@@ -273,13 +273,18 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
     else POLY_TRY(launch_im2col(frames, w.patches, F, m->H, m->W, m->patch, dt, w.xa, base->cls, base->pos, T, D, out_merged,
                            out_merged ? (size_t)F * K : 0, w.fl_clear, w.fl_clear_bytes / sizeof(unsigned), ss ? nullptr : row_offsets,
                            adapter_ids, R, m->n_adapters, w.meta, w.frame_of_row, w.adapter_of_row, dev_status, st));
+    // The heads (and with L0 == L the base head) read the class token of every block and nothing else, so of the last layer only the keys and values concern
+    // the other rows: behind its qkv linear the blocks are one row long, kept where the attention output ends.  (Not on a handful of tokens, whose buffer is too short for that.)
+    const bool class_rows = T >= 8;
+    const float *x_end = adapted && !sum ? w.xb : w.xa;    // the residual stream behind the last layer, blocks of T_end rows
+    int T_end = T;
     // The lagged loop: after the shared layers the base head scores the frames, Alg. 2 turns the scores of frame t - 1 into
     // the adapter set of frame t with its row maps -- all on this stream, no host in between.
     bool selected = ss == nullptr;
     auto select_now = [&]() -> int {
         selected = true;
         const poly_stream *s = ss->s;
-        POLY_TRY(launch_base_head(w.xa, T, D, base->lnf_g, base->lnf_b, m->ln_eps, s->base_w, s->base_b, s->K, F, ss->lag,
+        POLY_TRY(launch_base_head(adapted ? w.xa : x_end, T_end, D, base->lnf_g, base->lnf_b, m->ln_eps, s->base_w, s->base_b, s->K, F, ss->lag,
                                   ss->out_base_scores, s->carry, dt, st));
         // the selection also writes the row maps and carries the last frame's scores to the next call: two launches less
         const SelectFollow fo = {w.meta, w.frame_of_row, w.adapter_of_row, dev_status, s->carry, ss->lag + (size_t)F * s->K};
@@ -320,6 +325,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
                 const size_t ranks = (size_t)(l - first) * m->n_adapters * m->r;
                 if (m->targets & (1 << t)) { a.At[t] = (const char *)lora->At[t] + es * ranks * din[t]; a.Bt[t] = (const char *)lora->Bt[t] + es * ranks * dout[t]; }
             }
+            a.class_rows = l + a.layers == m->L;
             POLY_TRY(launch_flow(a, dt, st));
             a.x_in = a.x; a.in_map = nullptr;                  // the next launch continues on this one's blocks
             a.counters += flow_counter_bytes(a.nb, m->heads) / sizeof(unsigned);
@@ -388,11 +394,12 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
             g.set_off = summed ? row_offsets : nullptr;
             (void)t;
         };
+        int Tr = T;                            // rows of a block
         auto rowlin = [&](int t, const float *x_ln, const float *ln_g, const float *ln_b, const void *a_in, const int *in_map,
                           const void *Wt, const float *bias, int N, int mode, void *out, const float *res, const int *res_map) -> int {
             RowLinArgs a = {};
             a.x_ln = x_ln; a.ln_g = ln_g; a.ln_b = ln_b; a.eps = m->ln_eps; a.a_in = (const bf16_t *)a_in; a.in_block_of_out = in_map;
-            a.T = T; a.K = D; a.N = N; a.n_out = n_out; a.n_out_dev = n_out_dev;
+            a.T = Tr; a.K = D; a.N = N; a.n_out = n_out; a.n_out_dev = n_out_dev;
             a.Wt = (const bf16_t *)Wt; a.bias = bias;
             if (use(t)) {
                 a.At = (const bf16_t *)lora_ptr(lora->At[t], t, D, N, true); a.Bt = (const bf16_t *)lora_ptr(lora->Bt[t], t, D, N, false);
@@ -405,7 +412,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         const void *Wqkv = (const char *)base->qkv_w + es * (size_t)l * 3 * D * D, *Wproj = (const char *)base->proj_w + es * (size_t)l * D * D;
         const void *Wfc1 = (const char *)base->fc1_w + es * (size_t)l * Dm * D;
 
-        const RowPart rows = row_part(l);
+        RowPart rows = row_part(l);
 
         // ---- attention half
         if (qkv_done) {
@@ -447,13 +454,22 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
             g.mode = EPI_STORE; g.out = w.qkv; g.Tout = T;
             if (!few) POLY_TRY(launch_gemm(g, {!branch, pairs.usual}, dt, st));
         }
-        // (as a rule a frame has an adapter, so that there are about as many row-blocks as frames or more)
-        POLY_TRY(launch_attention(w.qkv, w.o, T, D, m->heads, n_out, n_out_dev, n_out < F ? n_out : F, dt, rows.waves > 0, st));
+        if (class_rows && l + 1 == m->L) {
+            float *x_class = (float *)((char *)w.o + align_up((size_t)n_out * D * es));
+            POLY_TRY(launch_attention_class(w.qkv, w.o, T, D, m->heads, n_out, n_out_dev, x_in, fan_map, x_fragments, x_class, dt, st));
+            x_in = x_out = x_class;
+            x_end = x_class;
+            fan_map = nullptr; x_fragments = false; rows.waves = 0;
+            Tr = T_end = 1;
+        } else {
+            // (as a rule a frame has an adapter, so that there are about as many row-blocks as frames or more)
+            POLY_TRY(launch_attention(w.qkv, w.o, T, D, m->heads, n_out, n_out_dev, n_out < F ? n_out : F, dt, rows.waves > 0, st));
+        }
         // narrow models without adapters on fc1 / fc2: everything row-wise of the layer in one launch -- proj with its
         // residual, the MLP half, and the qkv linear of the next layer when that layer works on the same blocks
         if (rows.fits) {
             RowLayerArgs a = {};
-            a.T = T; a.D = D; a.Dm = Dm; a.n_out = n_out; a.n_out_dev = n_out_dev;
+            a.T = Tr; a.D = D; a.Dm = Dm; a.n_out = n_out; a.n_out_dev = n_out_dev;
             const bool adapters = lora_on && !sum && (use(1) || (m->targets & 1));
             a.adapter_of_out = adapters ? w.adapter_of_row : nullptr; a.r = m->r; a.scale = m->lora_scale; a.eps = m->ln_eps;
             a.o = (const bf16_t *)w.o; a.Wpt = (const bf16_t *)Wproj; a.bp = base->proj_b + (size_t)l * D;
@@ -487,14 +503,14 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         } else {
             GemmArgs g = {};
             g.A = w.o; g.Wt = Wproj; g.bias = base->proj_b + (size_t)l * D;
-            g.T = T; g.K = D; g.N = D; g.n_in = n_out; g.n_in_dev = n_out_dev;
+            g.T = Tr; g.K = D; g.N = D; g.n_in = n_out; g.n_in_dev = n_out_dev;
             if (use(1)) {
                 const void *At = lora_ptr(lora->At[1], 1, D, D, true), *Bt = lora_ptr(lora->Bt[1], 1, D, D, false);
-                POLY_TRY(launch_shrink(w.o, T, D, At, m->r, RP, m->lora_scale, F, R, R_dev, shrink_map, w.adapter_of_row, summed ? row_offsets : nullptr,
+                POLY_TRY(launch_shrink(w.o, Tr, D, At, m->r, RP, m->lora_scale, F, R, R_dev, shrink_map, w.adapter_of_row, summed ? row_offsets : nullptr,
                                        w.S, dt, st));
                 lora_gemm(g, 1, Bt);
             }
-            g.mode = EPI_RESID; g.out = x_out; g.Tout = T; g.res = x_in; g.res_block_of_out = fan_map;
+            g.mode = EPI_RESID; g.out = x_out; g.Tout = Tr; g.res = x_in; g.res_block_of_out = fan_map;
             POLY_TRY(launch_gemm(g, {n_out_dev != R_dev, pairs.usual}, dt, st));
         }
         // ---- MLP half (x_out holds the stream from here on)
@@ -502,7 +518,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
             // no adapter on fc1 / fc2 in this layer: LayerNorm, both products, GELU and the residual in one kernel
             MlpArgs a = {};
             a.x = x_out; a.ln_g = base->ln2_g + (size_t)l * D; a.ln_b = base->ln2_b + (size_t)l * D; a.eps = m->ln_eps;
-            a.T = T; a.D = D; a.Dm = Dm; a.n_out = n_out; a.n_out_dev = n_out_dev;
+            a.T = Tr; a.D = D; a.Dm = Dm; a.n_out = n_out; a.n_out_dev = n_out_dev;
             a.W1t = (const bf16_t *)Wfc1; a.b1 = base->fc1_b + (size_t)l * Dm;
             a.W2t = (const bf16_t *)((const char *)base->fc2_w + es * (size_t)l * D * Dm); a.b2 = base->fc2_b + (size_t)l * D;
             POLY_TRY(launch_mlp(a, st));
@@ -515,42 +531,43 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
             const float *gain = base->ln2_g + (size_t)l * D, *shift = base->ln2_b + (size_t)l * D;
             const void *At = use(2) ? lora_ptr(lora->At[2], 2, D, Dm, true) : nullptr;
             const bool shrunk = use(2) && layernorm_shrink_fits(x_out, w.u, gain, shift, D, n_out, At, RP, R, w.S, dt);
-            if (shrunk) POLY_TRY(launch_layernorm_shrink(x_out, w.u, gain, shift, D, m->ln_eps, T, n_out, n_out_dev, At, m->r, m->lora_scale, R, R_dev,
+            if (shrunk) POLY_TRY(launch_layernorm_shrink(x_out, w.u, gain, shift, D, m->ln_eps, Tr, n_out, n_out_dev, At, m->r, m->lora_scale, R, R_dev,
                                                          summed ? row_offsets : nullptr, w.adapter_of_row, w.S, st));
-            const NormGemmArgs ng = {x_out, gain, shift, m->ln_eps, (const bf16_t *)Wfc1, base->fc1_b + (size_t)l * Dm, (bf16_t *)w.h, Dm, T, n_out, n_out_dev, true};
-            const bool few = dt == POLY_BF16 && !use(2) && norm_gemm_fits(ng, D);
+            NormGemmArgs ng = {x_out, gain, shift, m->ln_eps, (const bf16_t *)Wfc1, base->fc1_b + (size_t)l * Dm, (bf16_t *)w.h, Dm, T, n_out, n_out_dev, true};
+            const bool few = dt == POLY_BF16 && !use(2) && norm_gemm_fits(ng, D);       // (class rows as the rows of the layers before: 11 us, 5 + 8 in two launches)
+            ng.T = Tr;
             if (few) POLY_TRY(launch_norm_gemm(ng, st));
-            else if (!shrunk) POLY_TRY(launch_layernorm(x_out, w.u, gain, shift, D, m->ln_eps, T, n_out, n_out_dev, dt, st));
+            else if (!shrunk) POLY_TRY(launch_layernorm(x_out, w.u, gain, shift, D, m->ln_eps, Tr, n_out, n_out_dev, dt, st));
             GemmArgs g = {};
             g.A = w.u; g.Wt = Wfc1; g.bias = base->fc1_b + (size_t)l * Dm;
-            g.T = T; g.K = D; g.N = Dm; g.n_in = n_out; g.n_in_dev = n_out_dev;
+            g.T = Tr; g.K = D; g.N = Dm; g.n_in = n_out; g.n_in_dev = n_out_dev;
             if (use(2)) {
                 const void *Bt = lora_ptr(lora->Bt[2], 2, D, Dm, false);
-                if (!shrunk) POLY_TRY(launch_shrink(w.u, T, D, At, m->r, RP, m->lora_scale, F, R, R_dev, shrink_map, w.adapter_of_row, summed ? row_offsets : nullptr,
+                if (!shrunk) POLY_TRY(launch_shrink(w.u, Tr, D, At, m->r, RP, m->lora_scale, F, R, R_dev, shrink_map, w.adapter_of_row, summed ? row_offsets : nullptr,
                                        w.S, dt, st));
                 lora_gemm(g, 2, Bt);
             }
-            g.mode = EPI_GELU; g.out = w.h; g.Tout = T;
+            g.mode = EPI_GELU; g.out = w.h; g.Tout = Tr;
             if (!few) POLY_TRY(launch_gemm(g, {n_out_dev != R_dev, pairs.usual}, dt, st));
         }
         {
             GemmArgs g = {};
             g.A = w.h; g.Wt = (const char *)base->fc2_w + es * (size_t)l * D * Dm; g.bias = base->fc2_b + (size_t)l * D;
-            g.T = T; g.K = Dm; g.N = D; g.n_in = n_out; g.n_in_dev = n_out_dev;
+            g.T = Tr; g.K = Dm; g.N = D; g.n_in = n_out; g.n_in_dev = n_out_dev;
             if (use(3)) {
                 const void *At = lora_ptr(lora->At[3], 3, Dm, D, true), *Bt = lora_ptr(lora->Bt[3], 3, Dm, D, false);
-                POLY_TRY(launch_shrink(w.h, T, Dm, At, m->r, RP, m->lora_scale, F, R, R_dev, shrink_map, w.adapter_of_row, summed ? row_offsets : nullptr,
+                POLY_TRY(launch_shrink(w.h, Tr, Dm, At, m->r, RP, m->lora_scale, F, R, R_dev, shrink_map, w.adapter_of_row, summed ? row_offsets : nullptr,
                                        w.S, dt, st));
                 lora_gemm(g, 3, Bt);
             }
-            g.mode = EPI_RESID; g.out = x_out; g.Tout = T; g.res = x_out;
+            g.mode = EPI_RESID; g.out = x_out; g.Tout = Tr; g.res = x_out;
             POLY_TRY(launch_gemm(g, {n_out_dev != R_dev, pairs.usual}, dt, st));
         }
     }
 
     if (!selected) POLY_TRY(select_now());        // (L0 == L: the shared layers are the whole backbone)
     if (R > 0) {
-        POLY_TRY(launch_head((adapted && !sum) ? w.xb : w.xa, (adapted && !sum) ? nullptr : w.frame_of_row, T, D, base->lnf_g, base->lnf_b, m->ln_eps,
+        POLY_TRY(launch_head(x_end, (adapted && !sum) ? nullptr : w.frame_of_row, T_end, D, base->lnf_g, base->lnf_b, m->ln_eps,
                              heads->head_w, heads->head_b, m->C, w.adapter_of_row, w.frame_of_row, heads->class_map, K, w.meta, R,
                              out_logits, out_scores, out_merged, dt, st));
     }

@@ -8,6 +8,8 @@
 // fp32: the same on fp32 matrix instructions, key tiles streamed through LDS with an online softmax.
 #include "poly_dev.h"
 
+#include <type_traits>
+
 namespace {
 
 constexpr float LOG2E = 1.4426950408889634f;
@@ -289,6 +291,105 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *qkv, float *
     }
 }
 
+// sum over the LPK neighbouring lanes (8 or 16) that hold a row's pieces, in every one of them
+template <int LPK> __device__ __forceinline__ float piece_sum(float v)
+{
+    auto add = [&](auto ctrl) { v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value, 0xf, 0xf, true)); };
+    add(std::integral_constant<int, 0xB1>{});              // quad_perm: lanes l ^ 1, l ^ 2
+    add(std::integral_constant<int, 0x4E>{});
+    add(std::integral_constant<int, 0x141>{});             // row_half_mirror, row_mirror
+    if (LPK == 16) add(std::integral_constant<int, 0x140>{});
+    return v;
+}
+
+// Attention of a block's first query (the class token), all that the heads read of the last layer: one (block, head) per workgroup, and the block's class row
+// of the residual stream beside it, so that what follows works on blocks of one row.  A row of 64 elements is LPK lanes x 16 bytes, for the scores and for the
+// second product alike, so nothing changes lanes but the sums: a lane group keeps a maximum, a sum and its part of the output of its own keys, and the 4 KPI
+// groups meet in LDS once.  Probabilities stay in fp32.
+// Bound by the bytes of K and V (50 KB per workgroup of 197 keys in bf16, all requested up front).
+template <typename E, int NI>       // NI: keys per lane group at a time (bf16: T <= 32 NI; fp32 goes on from there with what it has so far)
+__global__ __launch_bounds__(256) void attn_class_kernel(const E *qkv, E *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, const float *x,
+                                                         const int *x_block, int x_fragments, float *x_out)
+{
+    constexpr int EPL = 16 / (int)sizeof(E), LPK = 64 / EPL, KPI = 64 / LPK, GROUPS = 4 * KPI;      // elements per lane, lanes per key, keys per instruction
+    typedef E piece_t __attribute__((ext_vector_type(EPL)));
+    constexpr bool BF16 = sizeof(E) == 2;
+    __shared__ __attribute__((aligned(16))) float part[GROUPS][64], ml[2][GROUPS];
+    const int nb = n_blocks_dev ? min(*n_blocks_dev, n_blocks) : n_blocks;
+    const int b = blockIdx.x / heads, hd = blockIdx.x % heads;
+    if (b >= nb) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane / LPK, c = lane % LPK;
+    const size_t ld = (size_t)3 * D;
+    const E *base = qkv + (size_t)b * T * ld + hd * 64 + c * EPL;
+    const piece_t qp = *(const piece_t *)base;
+    piece_t kp[NI], vp[NI];
+    auto key = [&](int t0, int i) { return t0 + (i * 4 + wave) * KPI + g; };
+    auto load = [&](int t0) {                              // rows past T repeat row T - 1
+#pragma unroll
+        for (int i = 0; i < NI; ++i) kp[i] = *(const piece_t *)(base + (size_t)min(key(t0, i), T - 1) * ld + D);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) vp[i] = *(const piece_t *)(base + (size_t)min(key(t0, i), T - 1) * ld + 2 * D);
+    };
+    load(0);
+    if (wave == 3) {
+        const size_t row = (size_t)(x_block ? x_block[b] : b) * T;
+        const int col = hd * 64 + lane;
+        const float v = x_fragments ? x[(row >> 5) * 32 * D + (col >> 3) * 256 + (col >> 2 & 1) * 128 + (row & 31) * 4 + (col & 3)] : x[row * D + col];
+        x_out[(size_t)b * D + col] = v;
+    }
+    const float scale = BF16 ? 0.125f * LOG2E : 0.125f;
+    auto pexp = [&](float v) { return BF16 ? __builtin_amdgcn_exp2f(v) : expf(v); };
+    float q[EPL], o[EPL], mx = -INFINITY, sum = 0.f;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) { q[e] = (float)qp[e] * scale; o[e] = 0.f; }
+    for (int t0 = 0;;) {
+        float s[NI], m = mx;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            float a = 0.f;
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) a = fmaf(q[e], (float)kp[i][e], a);
+            a = piece_sum<LPK>(a);
+            s[i] = key(t0, i) < T ? a : -INFINITY;
+            m = fmaxf(m, s[i]);
+        }
+        const float safe = fmaxf(m, -3.4e38f);             // (a group without keys, or with -infinity in all of them, counts nothing)
+        const float corr = pexp(mx - safe);
+        mx = m;
+        sum *= corr;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) o[e] *= corr;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const float p = pexp(s[i] - safe);
+            sum += p;
+            const bool in = key(t0, i) < T;
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) o[e] = fmaf(p, in ? (float)vp[i][e] : 0.f, o[e]);
+        }
+        t0 += NI * GROUPS;
+        if (BF16 || t0 >= T) break;
+        load(t0);
+    }
+    const int gr = wave * KPI + g;
+#pragma unroll
+    for (int e = 0; e < EPL; e += 4) *(f32x4 *)&part[gr][c * EPL + e] = f32x4{o[e], o[e + 1], o[e + 2], o[e + 3]};
+    if (c == 0) { ml[0][gr] = mx; ml[1][gr] = sum; }
+    __syncthreads();
+    if (wave) return;
+    float M = -INFINITY, all = 0.f, y = 0.f;
+#pragma unroll
+    for (int j = 0; j < GROUPS; ++j) M = fmaxf(M, ml[0][j]);
+    M = fmaxf(M, -3.4e38f);
+#pragma unroll
+    for (int j = 0; j < GROUPS; ++j) {
+        const float w = pexp(ml[0][j] - M);
+        all = fmaf(ml[1][j], w, all);
+        y = fmaf(part[j][lane], w, y);
+    }
+    out[(size_t)b * D + hd * 64 + lane] = (E)(y / all);
+}
+
 template <int NKT, int W, bool FRAGMENTS>
 int launch_bf16(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, hipStream_t st)
 {
@@ -339,5 +440,22 @@ int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_
         POLY_LAUNCH(POLY_STAGE_ATTN, attn_f32_kernel, dim3((unsigned)(n_blocks * heads * ((T + 127) / 128))), dim3(256), st, (const float *)qkv, (float *)out, T, D, heads,
                            n_blocks, n_blocks_dev);
     }
+    return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
+}
+
+int launch_attention_class(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, const float *x, const int *x_block,
+                           bool x_fragments, float *x_out, int dtype, hipStream_t st)
+{
+    if (n_blocks == 0) return POLY_OK;
+    if (D != heads * 64 || (dtype == POLY_BF16 && T > 224)) return POLY_EINVAL;
+    const dim3 grid((unsigned)(n_blocks * heads));
+#define ATTN_CLASS(E, NI)                                                                                                                                      \
+    POLY_LAUNCH(POLY_STAGE_ATTN, (attn_class_kernel<E, NI>), grid, dim3(256), st, (const E *)qkv, (E *)out, T, D, heads, n_blocks, n_blocks_dev, x, x_block, \
+                (int)x_fragments, x_out)
+    if (dtype != POLY_BF16) ATTN_CLASS(float, 7);
+    else if (T <= 64) ATTN_CLASS(bf16_t, 2);
+    else if (T <= 128) ATTN_CLASS(bf16_t, 4);
+    else ATTN_CLASS(bf16_t, 7);
+#undef ATTN_CLASS
     return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
 }

@@ -558,10 +558,14 @@ __global__ __launch_bounds__(FL_THREADS, sizeof(E) == 2 && !PRE ? 4 : 2) void fl
             const unsigned tpl = nbq * p->tpb;
             while (ticket >= lbase + tpl) { lbase += tpl; ++layer; }
             if (layer >= (unsigned)p->a.layers) break;
+            // The model's last layer, of which the class token alone is read: behind Q the first row tile of every block
+            const bool end = p->a.class_rows && layer + 1 == (unsigned)p->a.layers;
+            if (end && ticket - lbase >= nbq * p->tpb_end) break;
             // ---- which task
             unsigned rem = ticket - lbase, bi;
             int stage = 0;
-            const Div dQ = {p->dQ.d, p->dQ.m}, dA = {p->dA.d, p->dA.m}, dP = {p->dP.d, p->dP.m}, d1 = {p->d1.d, p->d1.m};
+            const Div dQ = {p->dQ.d, p->dQ.m}, dA = {end ? p->eA.d : p->dA.d, end ? p->eA.m : p->dA.m},
+                      dP = {end ? p->eP.d : p->dP.d, end ? p->eP.m : p->dP.m}, d1 = {end ? p->e1.d : p->d1.d, end ? p->e1.m : p->d1.m};
             if (rem < nbq * dQ.d) bi = div(rem, dQ), rem -= bi * dQ.d;
             else if ((rem -= nbq * dQ.d) < nbq * dA.d) stage = 1, bi = div(rem, dA), rem -= bi * dA.d;
             else if ((rem -= nbq * dA.d) < (PRE ? 0 : nbq * dP.d)) stage = 2, bi = div(rem, dP), rem -= bi * dP.d;
@@ -571,7 +575,9 @@ __global__ __launch_bounds__(FL_THREADS, sizeof(E) == 2 && !PRE ? 4 : 2) void fl
             unsigned next = 0;
             k.queue = qc; k.next = &next; k.patience = &s_patience;
             k.layer = layer;
-            k.ct = div(rem, Div{p->drt.d, p->drt.m}); k.rt = rem - k.ct * p->nrt; k.b = qn + bi * nq;
+            if (end && stage) k.ct = rem, k.rt = 0;
+            else k.ct = div(rem, Div{p->drt.d, p->drt.m}), k.rt = rem - k.ct * p->nrt;
+            k.b = qn + bi * nq;
             k.cnt = p->cnt + (size_t)k.b * p->ncnt * 16;
             unsigned *done;
             if (stage == 0) done = norm_task<E, KD, 0, NQ, SUM, false>(k, fl_lds);
@@ -611,6 +617,8 @@ template <typename E, int KD, int NQ, int N1, int NP, int NC, bool SUM, bool PRE
     p.dQ = make_div(nrt * 3 * p.ct_d / NQ); p.dA = make_div(nrt * a.heads); p.dP = make_div(nrt * 4 / NC * p.ct_d / NP); p.d1 = make_div(nrt * p.ct_m / N1);
     p.drt = make_div(nrt);
     p.tpb = p.dQ.d + p.dA.d + (PRE ? 1 : 2) * p.dP.d + p.d1.d;
+    p.eA = make_div(a.heads); p.eP = make_div(4 / NC * p.ct_d / NP); p.e1 = make_div(p.ct_m / N1);
+    p.tpb_end = p.dQ.d + p.eA.d + (PRE ? 1 : 2) * p.eP.d + p.e1.d;
     p.a_p2 = 4 / NC * p.ct_d / NP; p.a_1 = p.ct_m / N1;
     // one workgroup per CU while that gives every block of a queue 32 of them or more, else two (DeiT-tiny, twelve layers, 256 / 512 of them:
     // 4 blocks 249 / 271 us, 8 blocks 314 / 334, 9 blocks 372 / 368, 12 blocks 426 / 408, 20 blocks 599 / 488)

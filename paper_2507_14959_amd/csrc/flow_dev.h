@@ -23,6 +23,8 @@ struct FlowParams {
     int nrt, ct_d, ct_m;               // row tiles per block; 64-column tiles of D and Dm
     Div dQ, dA, dP, d1, drt;           // tasks per block of every step (F2: as P); row tiles
     unsigned tpb;                      // tasks per block and layer
+    Div eA, eP, e1;                    // the same on one row tile, and all of a block's in the layer whose class token alone is read
+    unsigned tpb_end;
     int nQ;                            // column tiles of a Q task
     unsigned a_p2, a_1;                // tasks per row tile: P and F2; F1
     unsigned ncnt;                     // counters per block

@@ -314,6 +314,7 @@ struct FlowArgs {
     int workgroups;                  // at most so many of them in a launch of flow_wide.hip; 0: as many as there are CUs
     PolyMeta *meta;                  // a workgroup that has run out of them sets stalled, no blocks, and the status here ..
     int *dev_status;                 // .. and here (or null)
+    int class_rows;                  // of the last layer's x only the first row of every block is read: the others need not be there
     int n_queues;                    // set by launch_flow
 };
 bool flow_supported(int T, int D, int Dm, int heads, int r, bool lora);
@@ -467,6 +468,10 @@ int launch_shrink_csr(const void *X, int T, int K, const void *At, int r, int RP
 // fragments (bf16): out in the order that launch_rowreg takes
 int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, int n_usual,
                      int dtype, bool fragments, hipStream_t st);
+// the same for the first query of every block alone: out elt [n][D], and x_out float [n][D], row 0 of block x_block[b] (null: b) of x [..][T][D] (fragments: in
+// the order of launch_rowreg)
+int launch_attention_class(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, const float *x, const int *x_block,
+                           bool x_fragments, float *x_out, int dtype, hipStream_t st);
 
 // poly_select with what the lagged loop needs right behind it done in the same launch (select.hip): meta != null: the row maps and
 // the bookkeeping words of the CSR arrays just written (nothing is selected and state and carry stay where meta->stalled is set); carry != null: K floats carry_src -> carry
