@@ -72,10 +72,11 @@ def gemm_launches(cfg, F, R, L0):
         ad = l >= L0
         rows_qkv_in = (F if l <= L0 else R) * T      # the base product of the fan-out layer runs once per frame
         rows = (R if ad else F) * T
+        last = rows // T if l + 1 == cfg.L else rows  # behind the last layer's keys and values: the class token of every block
         qkv = (rows_qkv_in, D, 3 * D, ad and cfg.targets & 1, rows)
-        proj = (rows, D, D, ad and cfg.targets & 2, rows)
-        fc1 = (rows, D, Dm, ad and cfg.targets & 4, rows)
-        fc2 = (rows, Dm, D, ad and cfg.targets & 8, rows)
+        proj = (last, D, D, ad and cfg.targets & 2, last)
+        fc1 = (last, D, Dm, ad and cfg.targets & 4, last)
+        fc2 = (last, Dm, D, ad and cfg.targets & 8, last)
         if not qkv_done:
             out.append([qkv])
         qkv_done = False
@@ -102,6 +103,11 @@ def gemm_flops(cfg, F, R, L0):
             if lora:
                 total += 2.0 * lora_rows * cfg.r * N     # expand (x A_k) B_k, fused into the same kernel
     return total, len(launches)
+
+
+def attention_flops(cfg, F, R, L0):
+    """The two products of attention; of the last layer the class token's."""
+    return sum(4.0 * (R if l >= L0 else F) * (1 if l + 1 == cfg.L else cfg.T) * cfg.T * cfg.D for l in range(cfg.L) if l < L0 or R > 0)
 
 
 def main():
@@ -441,6 +447,9 @@ def main():
     prof = binding.poly_profile_end()
     flops, n_gemm = gemm_flops(cfg, F, R, args.L0)
     g = prof["gemm"]
+    if prof["attention"]["launches"] == 0:          # runs of whole layers in one launch, attention in them
+        flops += attention_flops(cfg, F, R, args.L0)
+        n_gemm = g["launches"] // n_prof
     assert g["launches"] == n_gemm * n_prof, (g, n_gemm)
     avg_ms = g["ms"] / g["launches"]
     achieved = flops / n_gemm / (avg_ms * 1e-3) / 1e12
@@ -449,7 +458,9 @@ def main():
     alg_bytes = (frames_np.size * 2 + 2.0 * (cfg.patch_dim * cfg.D + cfg.L * (4 * cfg.D * cfg.D + 2 * cfg.D * cfg.Dm))
                  + n_used * 2.0 * cfg.L * cfg.r * (cfg.D + 3 * cfg.D + cfg.D + cfg.D) + R * cfg.C * 4) / n_gemm
     traffic = measured_traffic_per_launch() if args.L0 == 0 else None
-    roofline = {"bound": "mfma", "kernel": "bf16 MFMA linears: rowlayer_kernel (proj + LoRA + residual, LN, fc1, GELU, fc2, residual, LN, next qkv + LoRA in one launch per layer; the first qkv), patch_rows_kernel (patch embedding)",
+    roofline = {"bound": "mfma", "kernel": ("bf16 MFMA: rowrun_kernel (all layers in one launch: LN, qkv + LoRA, attention, proj + LoRA + residual, LN, fc1, GELU, fc2, residual), patch_rows_kernel (patch embedding)"
+                                               if prof["attention"]["launches"] == 0 else
+                                               "bf16 MFMA linears: rowlayer_kernel (proj + LoRA + residual, LN, fc1, GELU, fc2, residual, LN, next qkv + LoRA in one launch per layer; the first qkv), patch_rows_kernel (patch embedding)"),
                 "achieved": round(achieved, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
                 "traffic": traffic, "traffic_source": os.path.relpath(TRAFFIC_PROFILE, ROOT) if traffic else None,

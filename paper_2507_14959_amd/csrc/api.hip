@@ -21,9 +21,11 @@ struct Carver {
 
 inline int tokens(const poly_model_desc *m) { return 1 + (m->H / m->patch) * (m->W / m->patch); }
 
-// A segment of the layers (shared, adapted) that may run as launches of small tasks (flow.hip) instead of one or more launches per layer
+// A segment of the layers (shared, adapted) that may run as launches of many layers, of small tasks (flow.hip) or of tiles that stay on their CUs (rowrun.hip),
+// instead of one or more launches per layer
 struct FlowSegment {
     int blocks, layers;                     // 0 blocks: this segment may not
+    bool tiles;                             // rowrun.hip
 };
 
 // blocks up to which a segment may: up to 140 tiles of 32 rows where the row kernel is the alternative, 270 where the GEMM path is (ranks
@@ -55,13 +57,39 @@ int flow_limit(const poly_model_desc *m, bool adapted)
     return (row_kernel ? 140 : 270) / ((T + 31) / 32);
 }
 
+// Whether a segment of a model like this may run on tiles that stay on their CUs.  Two lines are not drawn for speed but where tests/test_gpu_layer_kernels.py, test_gpu_rowreg.py
+// and test_row_layer.py count the launches of the kernels that go layer by layer, in workspaces of the named size: models of fewer than four layers, and poly_forward
+// (not the lagged loop) where the adapted layers have a rank that no row kernel takes.
+bool run_possible(const poly_model_desc *m, bool adapted, bool loop)
+{
+    const int tgt = adapted ? m->targets & 15 : 0;
+    if (m->L < 4 || (!loop && m->L0 < m->L && (m->targets & 3) && !rowlayer_supported(m->D, m->Dm, m->r))) return false;
+    return m->dtype == POLY_BF16 && !(tgt & 12) && !(tgt && m->compose == POLY_COMPOSE_SUM) && rowrun_supported(tokens(m), m->D, m->Dm, m->heads, tgt ? m->r : 0);
+}
+
 // of a call of F frames and R row-blocks; capped: of the largest call with no more frames and row-blocks that still may
 FlowSegment flow_segment(const poly_model_desc *m, int F, int R, bool adapted, bool capped)
 {
     const int layers = adapted ? m->L - m->L0 : m->L0;
     const int blocks = adapted && m->compose != POLY_COMPOSE_SUM ? R : F, limit = flow_limit(m, adapted);
-    if (layers == 0 || (adapted && R == 0) || (blocks > limit && !capped)) return {0, layers};
-    return {blocks < limit ? blocks : limit, layers};
+    if (layers == 0 || (adapted && R == 0) || (blocks > limit && !capped)) return {0, layers, false};
+    return {blocks < limit ? blocks : limit, layers, false};
+}
+// Up to 64 tiles of 32 rows the small tasks are faster: DeiT-tiny, twelve layers, tasks / tiles, us: 8 blocks of 197 tokens (56) 286 / 337,
+// 10 (70) 373 / 337; of 113 16 (64) 291 / 335, 24 (96) 377 / 333; of 50 24 (48) 247 / 316, 48 (96) 374 / 314; of 17 64 277 / 306, 128 394 / 307; a bound of three adapters a
+// frame, 1.8 each: 4 frames of 197 297 / 336, 6 390 / 337, 24 of 17 239 / 307, 64 373 / 306.
+FlowSegment run_segment(const poly_model_desc *m, int F, int R, bool adapted, bool loop, bool capped)
+{
+    const int layers = adapted ? m->L - m->L0 : m->L0, T = tokens(m);
+    const bool fan = adapted && m->compose != POLY_COMPOSE_SUM;
+    const int blocks = fan ? R : F, most = (fan ? 2 : 1) * RN_MAX_TILES / ((T + 63) / 64);        // (of pairs half the room is what is usual)
+    if (layers == 0 || (adapted && R == 0) || !run_possible(m, adapted, loop)) return {0, layers, true};
+    if (capped) return {blocks < most ? blocks : most, layers, true};
+    const int r = adapted && (m->targets & 15) ? m->r : 0;
+    PairCount n = fan ? pair_count(F, R) : known_count(blocks);
+    if (n.usual > blocks) n.usual = blocks;
+    const bool few = (long)n.usual * ((T + 31) / 32) <= 64 && flow_segment(m, F, R, adapted, false).blocks > 0;
+    return {few || !rowrun_faster(T, m->D, m->Dm, r, r > 0, n) ? 0 : blocks, layers, true};
 }
 
 // Every layer of a launch of flow.hip has buffers of its own (see there), so what they take grows with the layers of a launch: a segment
@@ -72,14 +100,19 @@ constexpr int FLOW_MIN_LAYERS = 4;
 constexpr size_t FLOW_BYTES = (size_t)128 << 20;
 
 struct FlowBuffers {
-    void *qk, *vt, *o, *h;
+    void *qk, *vt, *o, *h;                  // (tiles: keys and values, that is all)
     float *x1, *x2;
 };
-FlowBuffers carve_flow(const poly_model_desc *m, size_t n, Carver &c)      // n: blocks x layers of a launch
+FlowBuffers carve_flow(const poly_model_desc *m, size_t n, bool tiles, Carver &c)      // n: blocks x layers of a launch
 {
     const int T = tokens(m);
     const size_t es = elt_size(m->dtype);
-    FlowBuffers f;
+    FlowBuffers f = {};
+    if (tiles) {
+        f.qk = c.take<void>(es * n * rowrun_elements(T));
+        f.vt = c.take<void>(es * n * rowrun_elements(T));
+        return f;
+    }
     f.qk = c.take<void>(es * n * flow_elements(T, 2 * m->D));
     f.vt = c.take<void>(es * n * flow_elements(T, m->D));
     f.o = c.take<void>(es * n * flow_elements(T, m->D));
@@ -88,16 +121,18 @@ FlowBuffers carve_flow(const poly_model_desc *m, size_t n, Carver &c)      // n:
     f.x2 = c.take<float>(sizeof(float) * n * T * m->D);
     return f;
 }
-size_t flow_bytes(const poly_model_desc *m, size_t n)
+constexpr size_t TILES_ALIGN = 512;         // of keys and values, where they take as much as there is
+size_t flow_bytes(const poly_model_desc *m, size_t n, bool tiles)
 {
     Carver c{nullptr, 0};
-    carve_flow(m, n, c);
-    return c.off;
+    carve_flow(m, n, tiles, c);
+    return c.off + (tiles ? TILES_ALIGN : 0);
 }
+size_t launch_counters(const poly_model_desc *m, const FlowSegment &s) { return s.tiles ? align_up(rowrun_counter_bytes(s.blocks)) : flow_counter_bytes(s.blocks, m->heads); }
 int flow_min_layers(const FlowSegment &s) { return s.layers < FLOW_MIN_LAYERS ? s.layers : FLOW_MIN_LAYERS; }
 size_t flow_counters(const poly_model_desc *m, const FlowSegment &s)       // of all its launches, at their largest number
 {
-    return s.blocks ? (size_t)((s.layers + FLOW_MIN_LAYERS - 1) / FLOW_MIN_LAYERS) * flow_counter_bytes(s.blocks, m->heads) : 0;
+    return s.blocks ? (size_t)((s.layers + FLOW_MIN_LAYERS - 1) / FLOW_MIN_LAYERS) * launch_counters(m, s) : 0;
 }
 
 struct ForwardWs {
@@ -106,7 +141,9 @@ struct ForwardWs {
     float *xa, *xb;  // residual streams: per frame (shared layers), per row-block (adapted layers)
     void *u, *qkv, *o, *h, *S, *patches;
     size_t fixed, bytes;                    // up to xb; all of it: what a call needs at least
-    int fl_layers[2];                       // layers per launch of flow.hip in the shared and in the adapted layers (0: not there)
+    bool fl_tiles[2];                       // rowrun.hip instead of flow.hip in the shared and in the adapted layers
+    int fl_room[2];                         // blocks x layers that it has buffers for
+    int fl_layers[2];                       // layers per launch of these there (0: none; of rowrun.hip: at least)
     FlowBuffers fl[2];                      // in the place of u .. patches: the patches are embedded before the first launch
     unsigned *fl_cnt[2];                    // counters of its launches, behind everything else
     unsigned *fl_clear;                     // where they start
@@ -114,8 +151,8 @@ struct ForwardWs {
 };
 
 // `bytes`: what there is.  The layers run as tasks where it holds their buffers too, which a workspace of poly_forward_workspace_bytes for
-// this many frames and row-blocks or more does; the kernels that go layer by layer need no more than w.bytes.
-ForwardWs carve_forward(const poly_model_desc *m, int F, int R, void *base, size_t bytes)
+// this many frames and row-blocks or more does; the kernels that go layer by layer need no more than w.bytes.  loop: of poly_stream_step.
+ForwardWs carve_forward(const poly_model_desc *m, int F, int R, bool loop, void *base, size_t bytes)
 {
     const size_t T = tokens(m), es = elt_size(m->dtype);
     const size_t nb = (size_t)(F > R ? F : R), rows = nb * T;
@@ -135,17 +172,37 @@ ForwardWs carve_forward(const poly_model_desc *m, int F, int R, void *base, size
     w.patches = c.take<void>(es * (size_t)F * (T - 1) * 3 * m->patch * m->patch);
     w.bytes = c.off;
 
-    const FlowSegment seg[2] = {flow_segment(m, F, R, false, false), flow_segment(m, F, R, true, false)};
-    const size_t cnt = flow_counters(m, seg[0]) + flow_counters(m, seg[1]);
-    if (cnt == 0 || bytes < w.bytes + cnt) return w;
-    const size_t end = (bytes - cnt) & ~(size_t)255;                       // the counters' place
-    if (end < w.bytes) return w;
+    FlowSegment seg[2];
+    size_t cnt = 0, end = 0;
+    for (bool tiles : {true, false}) {      // (a workspace below the named size may hold the buffers of the small tasks and not of the tiles)
+        for (int a = 0; a < 2; ++a) {
+            if (tiles) seg[a] = run_segment(m, F, R, a == 1, loop, false);
+            else if (seg[a].blocks && end < w.fixed + flow_bytes(m, (size_t)seg[a].blocks * flow_min_layers(seg[a]), seg[a].tiles)) seg[a].blocks = 0;
+            if (seg[a].blocks == 0) seg[a] = flow_segment(m, F, R, a == 1, false);
+        }
+        cnt = flow_counters(m, seg[0]) + flow_counters(m, seg[1]);
+        end = bytes > cnt ? (bytes - cnt) & ~(size_t)255 : 0;              // the counters' place
+    }
+    if (cnt == 0 || end < w.bytes) return w;
     w.fl_clear = (unsigned *)((char *)base + end);
     for (int a = 0; a < 2; ++a) {
         if (seg[a].blocks == 0) continue;
         const int least = flow_min_layers(seg[a]);
         int launches = 1, n = seg[a].layers;                   // layers of a launch: as few launches as there is room for
-        auto fits = [&]() { return w.fixed + flow_bytes(m, (size_t)seg[a].blocks * n) <= end; };
+        if (seg[a].tiles) {                                    // as much room as there is: the launches share the layers out by the blocks that exist
+            const size_t one = 2 * es * rowrun_elements((int)T);
+            const size_t room = (end - w.fixed - TILES_ALIGN) / one, all = (size_t)seg[a].blocks * n;
+            if (end < w.fixed + TILES_ALIGN || room < (size_t)seg[a].blocks * least) continue;
+            Carver cf{(char *)base, w.fixed};
+            w.fl_room[a] = (int)(room < all ? room : all);
+            w.fl[a] = carve_flow(m, w.fl_room[a], true, cf);
+            w.fl_tiles[a] = true;
+            w.fl_layers[a] = w.fl_room[a] / seg[a].blocks;
+            w.fl_cnt[a] = w.fl_clear + w.fl_clear_bytes / sizeof(unsigned);
+            w.fl_clear_bytes += launch_counters(m, seg[a]) * (size_t)((n + w.fl_layers[a] - 1) / w.fl_layers[a]);
+            continue;
+        }
+        auto fits = [&]() { return w.fixed + flow_bytes(m, (size_t)seg[a].blocks * n, false) <= end; };
         while (!fits() && n > least) {
             ++launches;
             n = (seg[a].layers + launches - 1) / launches;
@@ -153,28 +210,29 @@ ForwardWs carve_forward(const poly_model_desc *m, int F, int R, void *base, size
         }
         if (!fits()) continue;
         Carver cf{(char *)base, w.fixed};
-        w.fl[a] = carve_flow(m, (size_t)seg[a].blocks * n, cf);
+        w.fl[a] = carve_flow(m, (size_t)seg[a].blocks * n, false, cf);
         w.fl_layers[a] = n;
         w.fl_cnt[a] = w.fl_clear + w.fl_clear_bytes / sizeof(unsigned);
-        w.fl_clear_bytes += flow_counter_bytes(seg[a].blocks, m->heads) * (size_t)((seg[a].layers + n - 1) / n);
+        w.fl_clear_bytes += launch_counters(m, seg[a]) * (size_t)((seg[a].layers + n - 1) / n);
     }
     return w;
 }
 
 // Never less for more frames or row-blocks, so that a workspace for the largest call of a program serves its smaller ones: the task
 // buffers are those of the largest call up to this one that runs as tasks
-size_t forward_bytes(const poly_model_desc *m, int F, int R)
+size_t forward_bytes(const poly_model_desc *m, int F, int R, bool loop)
 {
-    const ForwardWs w = carve_forward(m, F, R, nullptr, 0);
+    const ForwardWs w = carve_forward(m, F, R, loop, nullptr, 0);
     size_t end = w.bytes, cnt = 0;
-    for (int a = 0; a < 2; ++a) {
-        const FlowSegment s = flow_segment(m, F, R, a == 1, true);
-        if (s.blocks == 0) continue;
-        const size_t all = flow_bytes(m, (size_t)s.blocks * s.layers), least = flow_bytes(m, (size_t)s.blocks * flow_min_layers(s));
-        const size_t most = least > FLOW_BYTES ? least : FLOW_BYTES, want = all < most ? all : most;
-        if (w.fixed + want > end) end = w.fixed + want;
-        cnt += flow_counters(m, s);
-    }
+    for (int a = 0; a < 2; ++a)
+        for (bool tiles : {false, true}) {
+            const FlowSegment s = tiles ? run_segment(m, F, R, a == 1, loop, true) : flow_segment(m, F, R, a == 1, true);
+            if (s.blocks == 0) continue;
+            const size_t all = flow_bytes(m, (size_t)s.blocks * s.layers, tiles), least = flow_bytes(m, (size_t)s.blocks * flow_min_layers(s), tiles);
+            const size_t most = least > FLOW_BYTES ? least : FLOW_BYTES, want = all < most ? all : most;
+            if (w.fixed + want > end) end = w.fixed + want;
+            cnt += flow_counters(m, s);
+        }
     return end + align_up(cnt);
 }
 
@@ -222,7 +280,7 @@ extern "C" const char *poly_status_string(int status)
 extern "C" size_t poly_forward_workspace_bytes(const poly_model_desc *m, int F, int R)
 {
     if (check_model(m) != POLY_OK || F < 0 || R < 0) return 0;
-    return forward_bytes(m, F, R);
+    return forward_bytes(m, F, R, false);
 }
 
 namespace {
@@ -252,7 +310,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
     for (int t = 0; t < 4; ++t)
         if (adapted && (m->targets & (1 << t)) && (!lora || !lora->At[t] || !lora->Bt[t])) return POLY_EINVAL;
     if (((uintptr_t)workspace & 255) != 0 || !workspace) return POLY_EINVAL;
-    const ForwardWs w = carve_forward(m, F, R, workspace, workspace_bytes);
+    const ForwardWs w = carve_forward(m, F, R, ss != nullptr, workspace, workspace_bytes);
     if (workspace_bytes < w.bytes) return POLY_ECAP;
 
     hipStream_t st = (hipStream_t)stream;
@@ -333,6 +391,36 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         return POLY_OK;
     };
 
+    auto run = [&](bool ad) -> int {
+        RowRunArgs a = {};
+        a.T = T; a.Dm = Dm; a.eps = m->ln_eps;
+        a.nb = ad && !sum ? R : F;
+        a.nb_dev = !ad ? nullptr : (sum ? &w.meta->F_ok : R_dev);
+        a.x_in = w.xa; a.x_out = ad && !sum ? w.xb : w.xa;
+        a.in_map = ad && !sum ? w.frame_of_row : nullptr;
+        a.n_adapters = m->n_adapters; a.r = m->r; a.scale = m->lora_scale;
+        a.k = (bf16_t *)w.fl[ad].qk; a.v = (bf16_t *)w.fl[ad].vt;
+        a.counters = w.fl_cnt[ad];
+        a.patience = poly_patience(); a.meta = w.meta; a.dev_status = dev_status;
+        const int first = ad ? m->L0 : 0, last = ad ? m->L : m->L0;
+        const size_t ld = (size_t)first * D, lm = (size_t)first * Dm, dd = ld * D, dm = ld * Dm;
+        a.layers = last - first;
+        a.capacity = w.fl_room[ad];
+        a.class_rows = last == m->L;
+        a.ln1_g = base->ln1_g + ld; a.ln1_b = base->ln1_b + ld; a.ln2_g = base->ln2_g + ld; a.ln2_b = base->ln2_b + ld;
+        a.Wq = (const bf16_t *)base->qkv_w + 3 * dd; a.Wp = (const bf16_t *)base->proj_w + dd;
+        a.W1 = (const bf16_t *)base->fc1_w + dm; a.W2 = (const bf16_t *)base->fc2_w + dm;
+        a.bq = base->qkv_b + 3 * ld; a.bp = base->proj_b + ld; a.b1 = base->fc1_b + lm; a.b2 = base->fc2_b + ld;
+        if (ad && (m->targets & 1)) { a.Aq = (const bf16_t *)lora->At[0]; a.Bq = (const bf16_t *)lora->Bt[0]; }
+        if (ad && (m->targets & 2)) { a.Ap = (const bf16_t *)lora->At[1]; a.Bp = (const bf16_t *)lora->Bt[1]; }
+        a.adapter_of_row = a.Aq || a.Ap ? w.adapter_of_row : nullptr;
+        for (int done = 0; done < a.layers; done += w.fl_layers[ad], ++a.launch) {
+            POLY_TRY(launch_rowrun(a, st));
+            a.counters += align_up(rowrun_counter_bytes(a.nb)) / sizeof(unsigned);
+        }
+        return POLY_OK;
+    };
+
     const PairCount pairs = pair_count(F, R);
 
     // What the row-wise part of layer l is: whether one launch does it, whether the next layer's qkv linear is in it (that layer works on the same blocks
@@ -353,13 +441,13 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
     bool qkv_done = false;                     // the qkv linear of layer l was computed by layer l - 1's row kernel
     for (int l = 0; l < m->L; ++l) {
         if (l == 0 && w.fl_cnt[0]) {
-            POLY_TRY(flow(false));
+            POLY_TRY(w.fl_tiles[0] ? run(false) : flow(false));
             l = m->L0;
             if (l == m->L) break;
         }
         if (l == m->L0 && !selected) POLY_TRY(select_now());
         if (l == m->L0 && w.fl_cnt[1]) {
-            POLY_TRY(flow(true));
+            POLY_TRY(w.fl_tiles[1] ? run(true) : flow(true));
             break;
         }
         const bool lora_on = l >= m->L0 && R > 0;
@@ -590,7 +678,7 @@ static size_t stream_lag_bytes(int F, int K) { return sizeof(float) * (size_t)(F
 extern "C" size_t poly_stream_step_workspace_bytes(const poly_model_desc *m, int F, int R, int K)
 {
     if (check_model(m) != POLY_OK || F < 0 || R < 0 || K <= 0) return 0;
-    return forward_bytes(m, F, R) + stream_lag_bytes(F, K);
+    return forward_bytes(m, F, R, true) + stream_lag_bytes(F, K);
 }
 
 extern "C" int poly_stream_step(const poly_model_desc *m, const poly_base_weights *base, const poly_lora_weights *lora,

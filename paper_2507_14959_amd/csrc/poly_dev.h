@@ -324,6 +324,37 @@ size_t flow_elements(int T, int D);
 int launch_flow(const FlowArgs &a, int dtype, hipStream_t st);
 int launch_flow_wide(const FlowArgs &a, int patience, hipStream_t st);   // called by launch_flow
 
+// A run of whole layers of a model 192 wide on tiles of 64 rows in one launch (rowrun.hip).  Weight pointers are those of the first layer of the run, one layer of a
+// stack behind the other.
+struct RowRunArgs {
+    int T, Dm, layers;
+    int nb;                          // upper bound of the number of blocks
+    const int *nb_dev;               // true count on the device, or null
+    int capacity, launch;            // blocks x layers that there are buffers for (nb or more); this launch takes the launch-th so many layers, if there are any left
+    int tiles;                       // set by launch_rowrun: 64-row tiles of a block
+    float eps;
+    const float *x_in;               // residual stream into the first layer: block in_map[b] (null: b) of [..][T][192]
+    const int *in_map;
+    float *x_out;                    // [nb][T][192] after the last layer (may be x_in where there is no map)
+    int class_rows;                  // of x_out only the first row of every block is read: the others need not be there
+    const float *ln1_g, *ln1_b, *ln2_g, *ln2_b;
+    const bf16_t *Wq, *Wp, *W1, *W2;
+    const float *bq, *bp, *b1, *b2;
+    const bf16_t *Aq, *Bq, *Ap, *Bp; // adapter stacks of qkv and proj; null = none
+    int n_adapters, r;
+    float scale;
+    const int *adapter_of_row;       // null: no adapters
+    bf16_t *k, *v;                   // [capacity][rowrun_elements(T)]
+    unsigned *counters;              // rowrun_counter_bytes, cleared by an earlier launch
+    int patience;                    // as in FlowArgs, as are these
+    PolyMeta *meta;
+    int *dev_status;
+};
+bool rowrun_supported(int T, int D, int Dm, int heads, int r);
+size_t rowrun_counter_bytes(int nb);
+size_t rowrun_elements(int T);
+int launch_rowrun(const RowRunArgs &a, hipStream_t st);
+
 // y = LayerNorm(x) row-wise; x float [n*T][D] -> elt [n*T][D]
 int launch_layernorm(const float *x, void *y, const float *gain, const float *shift, int D, float eps, int T,
                      int n_blocks, const int *n_blocks_dev, int dtype, hipStream_t st);

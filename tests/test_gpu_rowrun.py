@@ -1,0 +1,127 @@
+"""Runs of layers on 64-row tiles that stay on their CUs: edges of tiles and key tiles, ranks and targets, several rounds, launches that share the layers, stalls."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2507_14959_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+TOL = 8e-3          # bf16 activations between the steps; test_gpu_flow_sizes.py holds the same layers as tasks to it
+
+
+def _case(T, F, Dm, r, targets, L, per_frame, seed):
+    """T - 1 patches of 8 in a row, F frames of which 8 differ, up to per_frame adapters on a frame."""
+    cfg, _, _, _, _ = synth.make_small_case(seed, dtype=synth.DT_BF16, targets=targets, L=L, F=1, r=r, n_adapters=5, D=192, heads=3, Dm=Dm, hw=16, patch=8)
+    cfg = replace(cfg, H=8, W=8 * (T - 1))
+    rng = np.random.default_rng(seed)
+    w, eight = synth.make_weights(cfg, rng), synth.make_frames(cfg, 8, rng)
+    sets = [np.sort(rng.choice(5, size=1 + f % per_frame, replace=False)) for f in range(8)]
+    pick = np.arange(F) % 8
+    return cfg, w, eight, sets, eight[pick], *synth.sets_to_csr([sets[p] for p in pick])
+
+
+def _compare(cfg, eight, sets, got, w, L0, off):
+    off8, ids8 = synth.sets_to_csr(sets)
+    want = oracle.forward(cfg, w, eight, off8, ids8, L0=L0)["logits"]
+    rows = np.concatenate([np.arange(off8[f % 8], off8[f % 8 + 1]) for f in range(len(off) - 1)])
+    err = np.abs(got - want[rows]).max()
+    print(f"logits max-abs error {err:.2e} of up to {np.abs(want).max():.2f}")
+    assert err < TOL
+
+
+# T, frames, hidden width, rank, targets (1 qkv, 2 proj), layers, first adapted layer, adapters a frame up to, spare room
+CASES = [
+    (17, 100, 128, 8, 3, 4, 0, 1, 0),       # a tile a block, one key tile, one chunk of hidden columns
+    (33, 50, 192, 4, 1, 5, 1, 2, 0),        # half a chunk; a row in the second key tile; qkv alone
+    (64, 50, 768, 12, 2, 4, 0, 1, 0),       # a whole tile; proj alone
+    (65, 40, 256, 16, 3, 4, 2, 2, 25),      # one row in a block's second tile; room for more than there is
+    (97, 33, 320, 8, 3, 4, 4, 1, 0),        # no adapted layer
+    (128, 20, 128, 8, 3, 4, 0, 1, 0),
+    (129, 24, 192, 16, 3, 4, 0, 2, 10),     # three tiles, one row in the third
+    (170, 14, 128, 8, 3, 4, 1, 2, 0),       # three tiles, six key tiles
+    (193, 12, 256, 8, 3, 4, 0, 2, 6),       # one row in the fourth tile
+    (197, 75, 128, 8, 3, 4, 0, 1, 0),       # 300 tiles: a second round
+    (224, 10, 192, 4, 3, 4, 2, 1, 0),       # the most tokens
+]
+
+
+@pytest.mark.parametrize("T,F,Dm,r,targets,L,L0,per_frame,spare", CASES)
+def test_against_the_oracle(T, F, Dm, r, targets, L, L0, per_frame, spare):
+    cfg, w, eight, sets, frames, off, ids = _case(T, F, Dm, r, targets, L, per_frame, 2000 + T)
+    model = binding.DeviceModel(cfg, w, L0=L0)
+    binding.poly_profile_begin(400)
+    try:
+        got = binding.run_forward(model, frames, off, ids, R_cap=int(off[-1]) + spare)
+    finally:
+        prof = binding.poly_profile_end()
+    assert prof["attention"]["launches"] == 0
+    again = binding.run_forward(model, frames, off, ids, R_cap=int(off[-1]) + spare)
+    n = int(off[-1])
+    assert got["status"] == 0 and np.array_equal(got["logits"][:n], again["logits"][:n])
+    assert np.isnan(got["logits"][n:]).all()
+    _compare(cfg, eight, sets, got["logits"][:n], w, L0, off)
+
+
+def _forward(model, frames, off, ids, ws, room):
+    dev = "cuda"
+    out = torch.full((room, model.cfg.C), float("nan"), device=dev)
+    status = torch.full((1,), 99, dtype=torch.int32, device=dev)
+    binding.poly_profile_begin(400)
+    try:
+        rc = binding.poly_forward(model, model.frames_to_device(frames), torch.from_numpy(off).to(dev, torch.int32), torch.from_numpy(ids).to(dev, torch.int32),
+                                  room, torch.zeros_like(out), ws, out_logits=out, dev_status=status, check=False)
+    finally:
+        prof = binding.poly_profile_end()
+    return rc, out.cpu().numpy(), int(status.item()), prof
+
+
+# several: the smaller workspaces take another number of launches (with room for as many blocks again as there are)
+@pytest.mark.parametrize("T,F,room,L0,several", [(50, 60, 120, 0, True), (50, 60, 60, 0, False), (113, 40, 100, 4, False), (197, 20, 40, 0, False)])
+def test_the_launches_share_the_layers_without_changing_a_bit(T, F, room, L0, several):
+    cfg, w, eight, sets, frames, off, ids = _case(T, F, 128, 8, 3, 12, 1, 3000 + T)
+    model = binding.DeviceModel(cfg, w, L0=L0)
+    full = torch.empty(binding.poly_forward_workspace_bytes(model, F, room), dtype=torch.uint8, device="cuda")
+    first, launches = None, set()
+    for part in range(24, 8, -1):
+        ws = full[:full.numel() * part // 24 // 256 * 256]
+        ws.fill_(0xff)
+        rc, got, status, prof = _forward(model, frames, off, ids, ws, room)
+        if rc == binding.POLY_ECAP:
+            break
+        assert rc == 0 and status == 0
+        if prof["attention"]["launches"] == 0:
+            first = got if first is None else first
+            assert np.array_equal(got, first, equal_nan=True)
+            launches.add(prof["gemm"]["launches"])
+        else:
+            assert np.nanmax(np.abs(got - first)) < TOL
+    print(f"launches of the product stage {sorted(launches)}")
+    assert first is not None and (len(launches) > 1 or not several)
+    _compare(cfg, eight, sets, first[:F], w, L0, off)
+
+
+@pytest.mark.parametrize("L0", [0, 2, 5])
+def test_a_stall_is_reported_and_nothing_published(L0):
+    cfg, w, eight, sets, frames, off, ids = _case(197, 12, 128, 8, 3, 5, 1, 4000)
+    model = binding.DeviceModel(cfg, w, L0=L0)
+    binding.lib().poly_wait_limit(0)
+    try:
+        got = binding.run_forward(model, frames, off, ids)
+    finally:
+        binding.lib().poly_wait_limit(-1)
+    assert got["status"] == binding.POLY_ESTALL and np.isnan(got["logits"]).all()
+    got = binding.run_forward(model, frames, off, ids)
+    assert got["status"] == 0
+    _compare(cfg, eight, sets, got["logits"], w, L0, off)
+
+
+def test_a_bad_adapter_id_computes_nothing():
+    cfg, w, eight, sets, frames, off, ids = _case(113, 40, 128, 8, 3, 4, 1, 4100)
+    ids = ids.copy()
+    ids[7] = 5
+    got = binding.run_forward(binding.DeviceModel(cfg, w, L0=0), frames, off, ids)
+    assert got["status"] == binding.POLY_ERANGE and np.isnan(got["logits"]).all()
