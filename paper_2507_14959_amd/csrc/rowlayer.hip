@@ -176,6 +176,8 @@ __global__ __launch_bounds__(LY_THREADS, 2) void rowlayer_kernel(const RowLayerA
     auto at_frag = [&](int k) { return *(const bf16x8 *)(at_s + min(lm, r - 1) * LY_AT_STRIDE + 32 * k + 8 * lg); };
     // column n of Bt_k [.][r], ranks 4 lg + {0..3} (r is a multiple of 4; zero where the rank does not exist)
     auto bt_frag = [&](const bf16_t *Bt_k, int n) { return *(const s16x4 *)(Bt_k + n * r + min(4 * lg, r - 4)); };
+    // four ranks of a lane as a step of 32, the other four zeros on both sides (v_mfma_f32_16x16x16_bf16 takes several times as long)
+    auto wide = [](s16x4 v) { return __builtin_bit_cast(bf16x8, __builtin_shufflevector(v, s16x4{0, 0, 0, 0}, 0, 1, 2, 3, 4, 5, 6, 7)); };
     auto bt_operand = [&](s16x4 v) { return 4 * lg < r ? v : s16x4{0, 0, 0, 0}; };
     if (lora_p) {
         issue_at(a.Apt + (size_t)k_ad * r * D);
@@ -354,7 +356,7 @@ __global__ __launch_bounds__(LY_THREADS, 2) void rowlayer_kernel(const RowLayerA
                 for (int k = 0; k < 2 * KT; ++k) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(at_frag(k), rd(act[k & 1], (k >> 1) * LY_TILE + wrow * 128 + rt * 2048), c, 0, 0, 0);
                 const s16x4 fs = shrink_out(c);
 #pragma unroll
-                for (int ct = 0; ct < CT; ++ct) x[ct][rt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bt_operand(bt_frag(bt_s, 16 * CT * wc + 16 * ct + lm)), fs, x[ct][rt], 0, 0, 0);
+                for (int ct = 0; ct < CT; ++ct) x[ct][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wide(bt_operand(bt_frag(bt_s, 16 * CT * wc + 16 * ct + lm))), wide(fs), x[ct][rt], 0, 0, 0);
             }
         }
         layernorm(gb2_s, [&]() { issue_n(a.W1t, row_n(0), slot0); });
@@ -580,13 +582,13 @@ __global__ __launch_bounds__(LY_THREADS, 2) void rowlayer_kernel(const RowLayerA
             if (q > 1) store(q - 2);
         }
         if (lora_q) {
-            const s16x4 w = bt_operand(b2);
+            const bf16x8 w = wide(bt_operand(b2));
             if (full) {
 #pragma unroll
-                for (int rt = 0; rt < 4; ++rt) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w, fs[rt], acc[rt], 0, 0, 0);
+                for (int rt = 0; rt < 4; ++rt) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, wide(fs[rt]), acc[rt], 0, 0, 0);
             } else {
 #pragma unroll
-                for (int rt = 0; rt < 2; ++rt) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w, kh ? fs[2 + rt] : fs[rt], acc[rt], 0, 0, 0);
+                for (int rt = 0; rt < 2; ++rt) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, wide(kh ? fs[2 + rt] : fs[rt]), acc[rt], 0, 0, 0);
             }
         }
         // the columns of round q - 1 are staged, those of round q - 2 have been read; the operands of the next round are in registers

@@ -191,6 +191,9 @@ template <int NKT> __global__ __launch_bounds__(RN_THREADS, 2) void rowrun_kerne
     auto at_frag = [&](int k) { return *(const bf16x8 *)(at_s + min(lm, r - 1) * RN_AT_STRIDE + 32 * k + 8 * lg); };
     // column n of Bt_k [.][r], ranks 4 lg + {0..3} (r is a multiple of 4; zero where the rank does not exist)
     auto bt_frag = [&](const bf16_t *Bt_k, int n) { return *(const s16x4 *)(Bt_k + n * r + min(4 * lg, r - 4)); };
+    // four ranks of a lane as a step of 32, the other four zeros on both sides: v_mfma_f32_16x16x16_bf16 takes several times as long (the five rounds of C 10.0 k cycles with
+    // it, 7.8 k like this)
+    auto wide = [](s16x4 v) { return __builtin_bit_cast(bf16x8, __builtin_shufflevector(v, s16x4{0, 0, 0, 0}, 0, 1, 2, 3, 4, 5, 6, 7)); };
     auto bt_operand = [&](s16x4 v) { return 4 * lg < r ? v : s16x4{0, 0, 0, 0}; };
     auto rd = [&](lds_ptr p, int off) { return *(const __attribute__((address_space(3))) bf16x8 *)(p + off); };
     auto act_frag = [&](int tile, int rt, int kk) { return rd(act[kk], tile * RN_TILE + rt * 2048); };
@@ -213,10 +216,10 @@ template <int NKT> __global__ __launch_bounds__(RN_THREADS, 2) void rowrun_kerne
         *(bf16x4 *)(tile + (16 * rt + lm) * 128 + (((2 * cg + (lg >> 1)) ^ ((lm >> 1) & 7)) << 4) + 8 * (lg & 1)) = o;
     };
     // The sums over the two halves of the contraction meet: a wave hands the row half that is not its own to the wave with the same columns, through
-    // its own N slot, and adds what it is handed.
-    auto exchange = [&](f32x4 (&acc)[CT][4], f32x4 (&own)[CT][2]) {
-        f32x4 *mine = (f32x4 *)(Ws + wave * (2 * SLOT)) + lane;
-        const f32x4 *theirs = (const f32x4 *)(Ws + (wave ^ 4) * (2 * SLOT)) + lane;
+    // a slot of its own, and adds what it is handed.
+    auto exchange = [&](f32x4 (&acc)[CT][4], f32x4 (&own)[CT][2], int slot) {
+        f32x4 *mine = (f32x4 *)(Ws + wave * (2 * SLOT) + slot) + lane;
+        const f32x4 *theirs = (const f32x4 *)(Ws + (wave ^ 4) * (2 * SLOT) + slot) + lane;
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
@@ -311,16 +314,18 @@ template <int NKT> __global__ __launch_bounds__(RN_THREADS, 2) void rowrun_kerne
         // ============================================================ C: q, k, v = LayerNorm1(x) Wq + bq + lora
         {
             const bf16_t *Wq = run_args()->Wq + (size_t)l * Nq * D;
-            s16x4 b2[NQ] = {};
-            layernorm(gbq_s, [&]() {
-                issue_n(Wq, row_q(1), slot_q(1));
-                if (lora_q) {
-                    const bf16_t *Bq_k = slab(run_args()->Bq, l, Nq);
+            s16x4 b2[NQ] = {};                                         // Bt_k of the rounds
+            if (lora_q) {
+                const bf16_t *Bq_k = slab(run_args()->Bq, l, Nq);
 #pragma unroll
-                    for (int s = 0; s < NQ; ++s) b2[s] = bt_frag(Bq_k, row_q(s) + lm);
-                }
+                for (int s = 0; s < NQ; ++s) b2[s] = bt_frag(Bq_k, row_q(s) + lm);
+            }
+            layernorm(gbq_s, [&]() {
+#pragma unroll
+                for (int s = 0; s < NQ; ++s) asm volatile("" : "+v"(b2[s]));   // (waited for here: behind loads that the compiler does not know it would wait for those too)
+                issue_n(Wq, row_q(1), slot_q(1));
             });
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // rounds 0 and 1, At_k, Bt_k
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * KT) : "memory");     // round 0 and At_k; round 1 is on its way
             s16x4 fs[4];
             if (lora_q) {                                              // one row tile per wave, to every wave
                 asm volatile("s_barrier" ::: "memory");
@@ -350,16 +355,23 @@ template <int NKT> __global__ __launch_bounds__(RN_THREADS, 2) void rowrun_kerne
                 f32x4 b;
                 if (values) { const float t = bq_s[col + lm]; b = f32x4{t, t, t, t}; }
                 else b = *(const f32x4 *)(bq_s + col + 4 * lg);
-                f32x4 acc[4];
+                f32x4 acc[4] = {b, b, b, b};
+                if (lora_q) {
+                    const bf16x8 w = wide(bt_operand(b2[s]));
+#pragma unroll
+                    for (int rt = 0; rt < 4; ++rt)
+                        acc[rt] = values ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(wide(fs[rt]), w, b, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, wide(fs[rt]), b, 0, 0, 0);
+                }
                 auto mfma = [&](int n, int rt0) {
                     const int k = n / 2, rt = rt0 + n % 2;
-                    const f32x4 c = k == 0 ? b : acc[rt];
+                    const f32x4 c = acc[rt];
                     acc[rt] = values ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[k][rt], W[s & 1][k], c, 0, 0, 0)
                                      : __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[s & 1][k], fa[k][rt], c, 0, 0, 0);
                 };
                 auto next = [&](int n) {                               // the operands of the next round
                     if (s + 1 == NQ) return;
                     // behind the next round's weights: those of the round after it; the three stores of the keys; the four of a full round of values
+                    if (n == 0 && s == 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * KT) : "memory");
                     if (n == 0 && s == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * KT) : "memory");
                     if (n == 0 && s == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * KT + 3) : "memory");
                     if (n == 0 && s == 3) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
@@ -375,14 +387,6 @@ template <int NKT> __global__ __launch_bounds__(RN_THREADS, 2) void rowrun_kerne
                         acc[1] = acc[3];
                     } else {
                         segment([&](int n) { mfma(n, 0); }, next);
-                    }
-                }
-                if (lora_q) {
-                    const s16x4 w = bt_operand(b2[s]);
-#pragma unroll
-                    for (int rt = 0; rt < (full ? 4 : 2); ++rt) {
-                        const s16x4 f = full ? fs[rt] : kh ? fs[2 + rt] : fs[rt];
-                        acc[rt] = values ? __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(f, w, acc[rt], 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w, f, acc[rt], 0, 0, 0);
                     }
                 }
                 if (values) {
@@ -417,16 +421,7 @@ template <int NKT> __global__ __launch_bounds__(RN_THREADS, 2) void rowrun_kerne
         unsigned *const count = run_args()->counters + (RN_QUEUES + ob) * 16;
         if (tid == 0) __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (end && tile) break;
-        if (wave == 7 && tiles > 1) {
-            const unsigned want = (unsigned)(l - l0 + 1) * tiles;
-            while (peek(count) < want) {
-                const int looks = word_s[1] - 1;
-                word_s[1] = looks;
-                if (looks < 0) break;
-                __builtin_amdgcn_s_sleep(1);
-            }
-        }
-        {
+        auto proj_loads = [&]() {
             // Wp: rows 16 CT wc .., columns 64 t + 32 kh .. + 31 as [16 CT][32], 16 rows x 64 bytes per instruction
             const RunPtr p = run_args();
             const bf16_t *Wp = p->Wp + (size_t)l * D * D;
@@ -444,8 +439,21 @@ template <int NKT> __global__ __launch_bounds__(RN_THREADS, 2) void rowrun_kerne
                 for (int i = wave * 64; i < n16; i += 512)
                     if (i + lane < n16) glds16(Bt_k + (i + lane) * 16, __builtin_amdgcn_readfirstlane(lds_addr_of(bt_s)) + i * 16);
             }
+        };
+        // (the wave that waits requests its own behind the barrier: it has nothing to do in attention)
+        if (wave == 7) {
+            const unsigned want = tiles > 1 ? (unsigned)(l - l0 + 1) * tiles : 0;
+            while (want && peek(count) < want) {
+                const int looks = word_s[1] - 1;
+                word_s[1] = looks;
+                if (looks < 0) break;
+                __builtin_amdgcn_s_sleep(1);
+            }
+        } else {
+            proj_loads();
         }
         asm volatile("s_barrier" ::: "memory");
+        if (wave == 7) proj_loads();
         // ============================================================ attention: waves 0 .. 2 rows 0 .. 31 of a head each, 3 .. 5 the others
         if (wave < HEADS || (wave < 2 * HEADS && rows > 32 && !end)) {
             const int h = wave < HEADS ? wave : wave - HEADS, j = wave < HEADS ? 0 : 1, am = lane & 31, ah = lane >> 5;
@@ -546,8 +554,7 @@ template <int NKT> __global__ __launch_bounds__(RN_THREADS, 2) void rowrun_kerne
                 for (int rt = 0; rt < 4; ++rt) h[t][rt] = rd(kh ? act[1] : act[0], t * RN_TILE + rt * 2048);
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-            for (int j = 0; j < 2 * CT; ++j) issue_k1(col_k(0), j);
+            issue_n(W1, row_n(0), slot0);
 #pragma unroll
             for (int t = 0; t < KT; ++t)
 #pragma unroll
@@ -558,7 +565,7 @@ template <int NKT> __global__ __launch_bounds__(RN_THREADS, 2) void rowrun_kerne
         }
         {
             f32x4 own[CT][2];
-            exchange(y, own);
+            exchange(y, own, SLOT);
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) {
                 const f32x4 b = *(const f32x4 *)(bp_s + wcol + 16 * ct);
@@ -574,11 +581,14 @@ template <int NKT> __global__ __launch_bounds__(RN_THREADS, 2) void rowrun_kerne
                 for (int k = 0; k < 2 * KT; ++k) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(at_frag(k), rd(act[k & 1], (k >> 1) * RN_TILE + wrow * 128 + rt * 2048), c, 0, 0, 0);
                 const s16x4 fs = shrink_out(c);
 #pragma unroll
-                for (int ct = 0; ct < CT; ++ct) x[ct][rt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bt_operand(bt_frag(bt_s, 16 * CT * wc + 16 * ct + lm)), fs, x[ct][rt], 0, 0, 0);
+                for (int ct = 0; ct < CT; ++ct) x[ct][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wide(bt_operand(bt_frag(bt_s, 16 * CT * wc + 16 * ct + lm))), wide(fs), x[ct][rt], 0, 0, 0);
             }
         }
         renew();
-        layernorm(gb2_s, [&]() { issue_n(W1, row_n(0), slot0); });
+        layernorm(gb2_s, [&]() {
+#pragma unroll
+            for (int j = 0; j < 2 * CT; ++j) issue_k1(col_k(0), j);
+        });
         // The second product of B adds to x' + b2 on half 0 of its contraction in every row, so that a row's bits do not depend on its place in the tile: the
         // waves of half 1 hand their rows over, in LDS that is in no use until the second chunk (tile 3, and what LayerNorm and A are done with).  0.3 us of a
         // launch of 248 tiles (twelve of them and the rest of 32 frames of 224 x 224, 62 blocks: 498 / 502 us; through the weight slots, before the first of
@@ -624,7 +634,7 @@ template <int NKT> __global__ __launch_bounds__(RN_THREADS, 2) void rowrun_kerne
             share(n, NS / 2, 3 * NS / 4, 4, [&](int j) { look(rt0 + 1, j); });
             if (n == NS - 1) fin(rt0 + 1, buf);
         };
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * CT) : "memory");  // the first of W1; W2 is on its way
 #pragma unroll
         for (int j = 0; j < 2 * KT; ++j) fetch_n1(j);
         auto chunk = [&](int c, auto FIRST) {              // first product of chunk c, second of chunk c - 1
@@ -682,15 +692,16 @@ template <int NKT> __global__ __launch_bounds__(RN_THREADS, 2) void rowrun_kerne
         for (int c = 1; c < nc; ++c) chunk(c, std::false_type{});
         {                                                  // second product of the last chunk; where that is half a chunk, the second half has nothing
             const int buf = (nc - 1) & 1;
-            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
-            for (int kk = 0; kk < 2; ++kk) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) fetch_h1(kk, buf, j);
+            for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
                 for (int j = 0; j < CT; ++j) fetch_w1(kk, j);
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) fetch_h1(kk, buf, j);
             if (l + 1 < l1) {
                 const RunPtr p = run_args();
                 issue_n(p->Wq + (size_t)(l + 1) * Nq * D, row_q(0), slot_q(0));
@@ -703,7 +714,7 @@ template <int NKT> __global__ __launch_bounds__(RN_THREADS, 2) void rowrun_kerne
                     for (int n = 0; n < NS; ++n) mfma_k(n, kk);
             }
         }
-        exchange(y, x);
+        exchange(y, x, 0);
         if (l + 1 == l1) {
             float *dst = run_args()->x_out + ((size_t)ob * T + t0) * D + wcol;
 #pragma unroll
