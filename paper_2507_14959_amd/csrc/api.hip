@@ -25,7 +25,7 @@ inline int tokens(const poly_model_desc *m) { return 1 + (m->H / m->patch) * (m-
 // instead of one or more launches per layer
 struct FlowSegment {
     int blocks, layers;                     // 0 blocks: this segment may not
-    bool tiles;                             // rowrun.hip
+    int tiles;                              // rowrun.hip: rows of a tile; 0: flow.hip
 };
 
 // blocks up to which a segment may: up to 140 tiles of 32 rows where the row kernel is the alternative, 270 where the GEMM path is (ranks
@@ -64,7 +64,7 @@ bool run_possible(const poly_model_desc *m, bool adapted, bool loop)
 {
     const int tgt = adapted ? m->targets & 15 : 0;
     if (m->L < 4 || (!loop && m->L0 < m->L && (m->targets & 3) && !rowlayer_supported(m->D, m->Dm, m->r))) return false;
-    return m->dtype == POLY_BF16 && !(tgt & 12) && !(tgt && m->compose == POLY_COMPOSE_SUM) && rowrun_supported(tokens(m), m->D, m->Dm, m->heads, tgt ? m->r : 0);
+    return m->dtype == POLY_BF16 && !(tgt & 12) && rowrun_supported(tokens(m), m->D, m->Dm, m->heads, tgt ? m->r : 0);
 }
 
 // of a call of F frames and R row-blocks; capped: of the largest call with no more frames and row-blocks that still may
@@ -72,24 +72,29 @@ FlowSegment flow_segment(const poly_model_desc *m, int F, int R, bool adapted, b
 {
     const int layers = adapted ? m->L - m->L0 : m->L0;
     const int blocks = adapted && m->compose != POLY_COMPOSE_SUM ? R : F, limit = flow_limit(m, adapted);
-    if (layers == 0 || (adapted && R == 0) || (blocks > limit && !capped)) return {0, layers, false};
-    return {blocks < limit ? blocks : limit, layers, false};
+    if (layers == 0 || (adapted && R == 0) || (blocks > limit && !capped)) return {0, layers, 0};
+    return {blocks < limit ? blocks : limit, layers, 0};
 }
-// Up to 64 tiles of 32 rows the small tasks are faster: DeiT-tiny, twelve layers, tasks / tiles, us: 8 blocks of 197 tokens (56) 286 / 337,
-// 10 (70) 373 / 337; of 113 16 (64) 291 / 335, 24 (96) 377 / 333; of 50 24 (48) 247 / 316, 48 (96) 374 / 314; of 17 64 277 / 306, 128 394 / 307; a bound of three adapters a
-// frame, 1.8 each: 4 frames of 197 297 / 336, 6 390 / 337, 24 of 17 239 / 307, 64 373 / 306.
+// Up to 44 tiles of 32 rows the small tasks are faster: DeiT-tiny, twelve layers, tasks / tiles, us: 6 blocks of 197 tokens (42) 234 / 270, 8 (56) 283 / 270, 10 (70) 370 / 272;
+// of 113 8 (32) 240 / 250, 12 (48) 284 / 250; of 50 16 (32) 230 / 243, 24 (48) 243 / 243, 48 (96) 374 / 243; of 17 24 203 / 243, 64 276 / 243; a bound of three adapters a
+// frame, 1.8 each: 4 frames of 197 297 / 270, 6 390 / 270; summed terms: 8 blocks of 113 (32) 279 / 305, 12 (48) 324 / 304.
+constexpr int FLOW_FEW = 44;
 FlowSegment run_segment(const poly_model_desc *m, int F, int R, bool adapted, bool loop, bool capped)
 {
     const int layers = adapted ? m->L - m->L0 : m->L0, T = tokens(m);
     const bool fan = adapted && m->compose != POLY_COMPOSE_SUM;
-    const int blocks = fan ? R : F, most = (fan ? 2 : 1) * RN_MAX_TILES / ((T + 63) / 64);        // (of pairs half the room is what is usual)
-    if (layers == 0 || (adapted && R == 0) || !run_possible(m, adapted, loop)) return {0, layers, true};
-    if (capped) return {blocks < most ? blocks : most, layers, true};
-    const int r = adapted && (m->targets & 15) ? m->r : 0;
+    const int blocks = fan ? R : F, r = adapted && (m->targets & 15) ? m->r : 0;
+    const bool summed = r && !fan;
+    if (layers == 0 || (adapted && R == 0) || !run_possible(m, adapted, loop)) return {0, layers, 64};
+    if (capped) {                                          // (of pairs half the room is what is usual)
+        const int most = summed ? RN_SUM_ROUNDS * 8 * (32 / ((T + 31) / 32)) : (fan ? 2 : 1) * RN_MAX_TILES / ((T + 63) / 64);
+        return {blocks < most ? blocks : most, layers, 64};
+    }
     PairCount n = fan ? pair_count(F, R) : known_count(blocks);
     if (n.usual > blocks) n.usual = blocks;
-    const bool few = (long)n.usual * ((T + 31) / 32) <= 64 && flow_segment(m, F, R, adapted, false).blocks > 0;
-    return {few || !rowrun_faster(T, m->D, m->Dm, r, r > 0, n) ? 0 : blocks, layers, true};
+    if ((long)n.usual * ((T + 31) / 32) <= FLOW_FEW && flow_segment(m, F, R, adapted, false).blocks > 0) return {0, layers, 64};
+    const int rows = summed ? rowrun_rounds(blocks, (T + 31) / 32) <= RN_SUM_ROUNDS ? 32 : 0 : rowrun_rows(T, m->D, m->Dm, r, r > 0, n);
+    return {rows ? blocks : 0, layers, rows};
 }
 
 // Every layer of a launch of flow.hip has buffers of its own (see there), so what they take grows with the layers of a launch: a segment
@@ -141,7 +146,7 @@ struct ForwardWs {
     float *xa, *xb;  // residual streams: per frame (shared layers), per row-block (adapted layers)
     void *u, *qkv, *o, *h, *S, *patches;
     size_t fixed, bytes;                    // up to xb; all of it: what a call needs at least
-    bool fl_tiles[2];                       // rowrun.hip instead of flow.hip in the shared and in the adapted layers
+    int fl_tiles[2];                        // rowrun.hip instead of flow.hip in the shared and in the adapted layers: rows of a tile
     int fl_room[2];                         // blocks x layers that it has buffers for
     int fl_layers[2];                       // layers per launch of these there (0: none; of rowrun.hip: at least)
     FlowBuffers fl[2];                      // in the place of u .. patches: the patches are embedded before the first launch
@@ -196,7 +201,7 @@ ForwardWs carve_forward(const poly_model_desc *m, int F, int R, bool loop, void 
             Carver cf{(char *)base, w.fixed};
             w.fl_room[a] = (int)(room < all ? room : all);
             w.fl[a] = carve_flow(m, w.fl_room[a], true, cf);
-            w.fl_tiles[a] = true;
+            w.fl_tiles[a] = seg[a].tiles;
             w.fl_layers[a] = w.fl_room[a] / seg[a].blocks;
             w.fl_cnt[a] = w.fl_clear + w.fl_clear_bytes / sizeof(unsigned);
             w.fl_clear_bytes += launch_counters(m, seg[a]) * (size_t)((n + w.fl_layers[a] - 1) / w.fl_layers[a]);
@@ -394,6 +399,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
     auto run = [&](bool ad) -> int {
         RowRunArgs a = {};
         a.T = T; a.Dm = Dm; a.eps = m->ln_eps;
+        a.rows = w.fl_tiles[ad];
         a.nb = ad && !sum ? R : F;
         a.nb_dev = !ad ? nullptr : (sum ? &w.meta->F_ok : R_dev);
         a.x_in = w.xa; a.x_out = ad && !sum ? w.xb : w.xa;
@@ -414,6 +420,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         if (ad && (m->targets & 1)) { a.Aq = (const bf16_t *)lora->At[0]; a.Bq = (const bf16_t *)lora->Bt[0]; }
         if (ad && (m->targets & 2)) { a.Ap = (const bf16_t *)lora->At[1]; a.Bp = (const bf16_t *)lora->Bt[1]; }
         a.adapter_of_row = a.Aq || a.Ap ? w.adapter_of_row : nullptr;
+        a.set_off = ad && sum && a.adapter_of_row ? row_offsets : nullptr;
         for (int done = 0; done < a.layers; done += w.fl_layers[ad], ++a.launch) {
             POLY_TRY(launch_rowrun(a, st));
             a.counters += align_up(rowrun_counter_bytes(a.nb)) / sizeof(unsigned);

@@ -331,7 +331,8 @@ struct RowRunArgs {
     int nb;                          // upper bound of the number of blocks
     const int *nb_dev;               // true count on the device, or null
     int capacity, launch;            // blocks x layers that there are buffers for (nb or more); this launch takes the launch-th so many layers, if there are any left
-    int tiles;                       // set by launch_rowrun: 64-row tiles of a block
+    int rows;                        // of a tile: 64 or 32
+    int tiles;                       // set by launch_rowrun: tiles of a block
     float eps;
     const float *x_in;               // residual stream into the first layer: block in_map[b] (null: b) of [..][T][192]
     const int *in_map;
@@ -344,6 +345,7 @@ struct RowRunArgs {
     int n_adapters, r;
     float scale;
     const int *adapter_of_row;       // null: no adapters
+    const int *set_off;              // null: block b has the one term adapter_of_row[b]; else (32-row tiles) the sum of the terms [set_off[b], set_off[b + 1])
     bf16_t *k, *v;                   // [capacity][rowrun_elements(T)]
     unsigned *counters;              // rowrun_counter_bytes, cleared by an earlier launch
     int patience;                    // as in FlowArgs, as are these

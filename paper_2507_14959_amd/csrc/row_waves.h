@@ -44,16 +44,33 @@ inline int rowreg_waves(int T, int D, int Dm, int r, bool by_block, const PairCo
     return best;
 }
 
-// Whether layers 192 wide run as tiles that stay on their CUs (rowrun.hip), which take a round of 256 at a time through all layers, 26.5 us each with attention
-// in it, rather than in two launches a layer: the row-wise part as above and attention, 4.5 us and what its rows take.  Twelve layers of DeiT-tiny and everything
-// else of a forward, us, two launches a layer / tiles: every layer adapted, 16 blocks of 197 tokens (64 tiles) 440 / 335, 64 (256) 484 / 347, 72 (288) 685 / 635, 96 (384)
-// 753 / 647, 128 (512) 781 / 699, 160 (640) 820 / 1015; ten layers shared, 64 frames 507 / 402, 72 506 / 647; 113 tokens, a bound of three a frame, 1.8 each: 64
-// frames 487 / 339, 96 784 / 646, 128 819 / 672, 160 968 / 971; 17 tokens: 128 375 / 307, 256 397 / 313.
+// Rows of a tile where layers 192 wide run as tiles that stay on their CUs (rowrun.hip), 64 or 32; 0 where two launches a layer are faster.  The tiles take a round of 256
+// at a time through all layers, the row-wise part and attention together: 64 rows 26.5 us a layer, 32 rows, which pull the same weights, 20.5 (197 tokens; shorter blocks
+// have less attention).  Two launches a layer: the row-wise part as above and attention, 4.5 us and what its rows take.  Twelve layers of DeiT-tiny and everything
+// else of a forward, us, two launches a layer / tiles of 64 / of 32 rows: every layer adapted, 16 blocks of 197 tokens (64 and 112 tiles) 440 / 338 / 270, 36 (252 of 32) 461 /
+// 346 / 276, 40 463 / 340 / 528, 64 (256 of 64) 484 / 347 / 535, 72 685 / 635 / 787, 96 753 / 647, 128 781 / 699, 160 (640 of 64) 820 / 1015; ten layers shared, 64 frames
+// 507 / 402, 72 506 / 647; 113 tokens, a bound of three a frame, 1.8 each: 24 frames 424 / 331 / 250, 64 487 / 339 / 495, 96 784 / 646, 160 968 / 971; 17 tokens: 128 375 / 305 / 243, 256
+// 397 / 308 / 245.
 constexpr int RN_MAX_TILES = 512;   // of the usual count: two rounds
-inline bool rowrun_faster(int T, int D, int Dm, int r, bool by_block, const PairCount &n)
+// Rounds that `blocks` of so many tiles take: the tiles of a block run side by side, so of each queue's 32 CUs (rowrun.hip) a round fills what is a multiple of them, unless
+// all there is fits at once (36 blocks of seven tiles 295 us, 64 547, 72 808)
+inline int rowrun_rounds(int blocks, int tiles)
 {
-    const long tiles = (long)n.usual * ((T + 63) / 64);
-    if (tiles > RN_MAX_TILES) return false;
+    const int at_once = 8 * (32 / tiles);
+    return (long)blocks * tiles <= 256 ? 1 : (blocks + at_once - 1) / at_once;
+}
+// Where a block has the sum of several adapters' terms (tiles of 32 rows alone), the other way is the small tasks up to 270 tiles of 32 rows and two launches for each linear
+// beyond: up to four rounds.  Twelve layers, up to three terms on a block, us, the other way / tiles: 8 blocks of 197 tokens 330 / 317, 24 541 / 314, 36 739 / 318, 64 1022 / 573, 128 (four
+// rounds) 1538 / 1114; 64 of 113 712 / 303; 256 of 17 713 / 295.  (333 of 197: eleven rounds would be 2970, the other way 2895.)
+constexpr int RN_SUM_ROUNDS = 4;
+
+inline int rowrun_rows(int T, int D, int Dm, int r, bool by_block, const PairCount &n)
+{
+    auto us = [&](int rows) {
+        const int tiles = (T + rows - 1) / rows;
+        return (long)n.usual * tiles > RN_MAX_TILES ? 1e9f : (rows == 64 ? 24.5f + (float)T / 100.f : 18.f + (float)T / 80.f) * (float)rowrun_rounds(n.usual, tiles);
+    };
+    const int rows = us(32) < us(64) ? 32 : 64;
     const float attention = 4.5f + (float)n.usual * T / 2700.f;
-    return 26.5f * (float)((tiles + 255) / 256) < row_layer_us(rowreg_waves(T, D, Dm, r, by_block, n), T, r, by_block, n.usual) + attention;
+    return us(rows) < row_layer_us(rowreg_waves(T, D, Dm, r, by_block, n), T, r, by_block, n.usual) + attention ? rows : 0;
 }

@@ -1,4 +1,4 @@
-"""Runs of layers on 64-row tiles that stay on their CUs: edges of tiles and key tiles, ranks and targets, several rounds, launches that share the layers, stalls."""
+"""Runs of layers on tiles of 64 or 32 rows that stay on their CUs: edges of tiles and key tiles, ranks and targets, several rounds, launches that share the layers, stalls."""
 from dataclasses import replace
 
 import numpy as np
@@ -33,25 +33,30 @@ def _compare(cfg, eight, sets, got, w, L0, off):
     assert err < TOL
 
 
-# T, frames, hidden width, rank, targets (1 qkv, 2 proj), layers, first adapted layer, adapters a frame up to, spare room
+# rows of a tile in the adapted layers, T, frames, hidden width, rank, targets (1 qkv, 2 proj), layers, first adapted layer, adapters a frame up to, spare room
 CASES = [
-    (17, 100, 128, 8, 3, 4, 0, 1, 0),       # a tile a block, one key tile, one chunk of hidden columns
-    (33, 50, 192, 4, 1, 5, 1, 2, 0),        # half a chunk; a row in the second key tile; qkv alone
-    (64, 50, 768, 12, 2, 4, 0, 1, 0),       # a whole tile; proj alone
-    (65, 40, 256, 16, 3, 4, 2, 2, 25),      # one row in a block's second tile; room for more than there is
-    (97, 33, 320, 8, 3, 4, 4, 1, 0),        # no adapted layer
-    (128, 20, 128, 8, 3, 4, 0, 1, 0),
-    (129, 24, 192, 16, 3, 4, 0, 2, 10),     # three tiles, one row in the third
-    (170, 14, 128, 8, 3, 4, 1, 2, 0),       # three tiles, six key tiles
-    (193, 12, 256, 8, 3, 4, 0, 2, 6),       # one row in the fourth tile
-    (197, 75, 128, 8, 3, 4, 0, 1, 0),       # 300 tiles: a second round
-    (224, 10, 192, 4, 3, 4, 2, 1, 0),       # the most tokens
+    (32, 17, 100, 128, 8, 3, 4, 0, 1, 0),       # a tile a block, the second half of the keys empty, one chunk of hidden columns
+    (32, 33, 40, 192, 4, 1, 5, 1, 2, 0),        # half a chunk; a row in the second tile, which is the second half of the keys; qkv alone
+    (32, 64, 50, 768, 12, 2, 4, 0, 1, 0),       # whole tiles; proj alone
+    (32, 65, 30, 256, 16, 3, 4, 2, 2, 25),      # two key tiles of four with a row in the second half; room for more than there is
+    (32, 97, 33, 320, 8, 3, 4, 4, 1, 0),        # no adapted layer; three chunks, the last half a one
+    (32, 128, 20, 384, 8, 3, 4, 0, 1, 0),
+    (32, 129, 24, 192, 16, 3, 4, 0, 2, 10),     # five key tiles of seven
+    (32, 224, 10, 192, 4, 3, 4, 2, 1, 0),       # the most tokens
+    (32, 70, 140, 128, 8, 3, 4, 0, 1, 0),       # 420 tiles, three a block: two rounds of 80 blocks
+    (64, 64, 140, 128, 8, 3, 4, 0, 1, 0),       # a whole tile a block
+    (64, 65, 90, 256, 16, 3, 4, 2, 2, 0),       # one row in a block's second tile
+    (64, 97, 70, 320, 8, 3, 4, 0, 1, 10),
+    (64, 170, 44, 128, 8, 3, 4, 1, 1, 0),       # three tiles, six key tiles
+    (64, 193, 38, 768, 8, 3, 4, 0, 1, 6),       # one row in the fourth tile
+    (64, 197, 75, 192, 8, 3, 4, 0, 1, 0),       # 300 tiles: a second round
+    (64, 224, 40, 192, 4, 1, 4, 2, 1, 0),
 ]
 
 
-@pytest.mark.parametrize("T,F,Dm,r,targets,L,L0,per_frame,spare", CASES)
-def test_against_the_oracle(T, F, Dm, r, targets, L, L0, per_frame, spare):
-    cfg, w, eight, sets, frames, off, ids = _case(T, F, Dm, r, targets, L, per_frame, 2000 + T)
+@pytest.mark.parametrize("rows,T,F,Dm,r,targets,L,L0,per_frame,spare", CASES)
+def test_against_the_oracle(rows, T, F, Dm, r, targets, L, L0, per_frame, spare):
+    cfg, w, eight, sets, frames, off, ids = _case(T, F, Dm, r, targets, L, per_frame, 2000 + T + rows)
     model = binding.DeviceModel(cfg, w, L0=L0)
     binding.poly_profile_begin(400)
     try:
@@ -125,3 +130,26 @@ def test_a_bad_adapter_id_computes_nothing():
     ids[7] = 5
     got = binding.run_forward(binding.DeviceModel(cfg, w, L0=0), frames, off, ids)
     assert got["status"] == binding.POLY_ERANGE and np.isnan(got["logits"]).all()
+
+
+# The sum of a block's terms: none, one, up to four in LDS (two of rank 16, three of 12), more than have a place there; a second round
+@pytest.mark.parametrize("T,F,Dm,r,targets,L,L0,most", [(17, 100, 128, 8, 3, 4, 0, 2), (50, 40, 192, 4, 1, 4, 1, 4), (113, 24, 256, 16, 3, 4, 0, 4), (197, 12, 128, 12, 2, 4, 2, 5),
+                                                        (97, 30, 768, 8, 3, 4, 0, 8), (224, 40, 128, 8, 3, 4, 0, 3)])
+def test_summed_terms(T, F, Dm, r, targets, L, L0, most):
+    cfg, w, eight, _, frames, _, _ = _case(T, F, Dm, r, targets, L, 1, 5000 + T)
+    cfg = replace(cfg, n_adapters=9)
+    rng = np.random.default_rng(T)
+    w = synth.make_weights(cfg, rng)
+    sets = [np.sort(rng.choice(9, size=f % (most + 1), replace=False)) for f in range(8)]
+    off, ids = synth.sets_to_csr([sets[f % 8] for f in range(F)])
+    model = binding.DeviceModel(cfg, w, L0=L0, compose="sum")
+    binding.poly_profile_begin(400)
+    try:
+        got = binding.run_forward(model, frames, off, ids)
+    finally:
+        prof = binding.poly_profile_end()
+    assert got["status"] == 0 and prof["attention"]["launches"] == 0
+    off8, ids8 = synth.sets_to_csr(sets)
+    want = oracle.forward(cfg, w, eight, off8, ids8, L0=L0, compose="sum")["logits"]
+    rows = np.concatenate([np.arange(off8[f % 8], off8[f % 8 + 1]) for f in range(F)])
+    assert np.abs(got["logits"] - want[rows]).max() < TOL
