@@ -1,13 +1,22 @@
-// A run of whole layers of a model 192 wide in ONE launch, on tiles of 64 token rows: a workgroup keeps its rows from the first layer of the run to the last.
+// A run of whole layers of a model 192 wide in ONE launch, on tiles of 64 or 32 token rows: a workgroup keeps its rows from the first layer of the run to the last.
 //
 // rowlayer.hip and attention.hip are two launches a layer: every one starts cold (4 us to issue and dispatch, 2 to 3 us until the first tile written by the launch
-// before is usable), the residual stream goes out and comes back, and attention stages keys and values in LDS once more.  Here the up to four workgroups that
-// hold a block's rows run side by side, one per CU, and meet once a layer:
+// before is usable), the residual stream goes out and comes back, and attention stages keys and values in LDS once more.  Here the up to four (of 32 rows: seven)
+// workgroups that hold a block's rows run side by side, one per CU, and meet once a layer:
 //     C   [q k v] = LayerNorm1(x) Wq + bq (+ low rank)      q stays in LDS; k and v, in the order attention reads them, go out at device scope
 //     ..  the tiles of the block have all done so
 //     att o = softmax(q k^T / 8) v                          a wave per (head, 32 queries), k and v straight into registers, o over q in LDS
-//     A, B of rowlayer.hip                                  x, 24 fp32 registers of a lane, never leaves them
-// The products, LayerNorms and the GELU are rowlayer.hip's, on the same slots of weights, in the same order of sums.
+//     A, B of rowlayer.hip                                  x, 24 fp32 registers of a lane (12), never leaves them
+// The products, LayerNorms and the GELU are rowlayer.hip's, on the same slots of weights.
+//
+// Tiles of 32 rows are for few blocks, which give every CU one: half the rows for the same weights, and of attention three (head, 32 queries) whose keys are shared out over
+// two waves each.  They alone take the sum of several adapters' terms: two of them are a step of 32 in the expand, and A_k (in A B_k too) of up to four lie in LDS.
+//
+// What bounds it, in cycles of a layer of DeiT-tiny with adapters: 64 rows (62 k, 26 us) feed-forward 22 k -- the LDS: weights in and out, lookups of the GELU, hidden columns --,
+// qkv 8.5 k, attention 11.5 k (360 KB of keys and values through the CU's load path, 6 tasks on 4 SIMDs), the two LayerNorms 8.5 k, proj 5 k, handing over 5 k of which about
+// 2 k are the round trip of the counter.  32 rows (50 k, 20.5 us) 18 k (15.5 k of it the chunks of 128 hidden columns: 14.7 k with no weights coming in), 7.3 k, 9.3 k, 6.5 k, 3.7 k, 4.5 k.
+// Twelve layers and everything else of a forward, us, two launches a layer before / now: 62 blocks of 197 tokens (32 frames) 497 / 349, 24 blocks 448 / 270; 24 of 113
+// with summed terms (small tasks) 417 / 298.  Tried and dropped: the next weights pulled into the L2 ahead (64 rows 1.5 % slower, 32 the same).
 //
 // Handing k and v over without fences: as in flow.hip.  They are stored at device scope, the stores are waited for, then the tile is counted; every layer of a
 // launch has buffers of its own, so no address is read by this launch before it has been written for good and no cache holds an old copy of it.  A 1 KB
@@ -15,9 +24,11 @@
 //
 // Order and progress: tickets of eight queues, block b in queue b % 8, the tiles of a block consecutive.  (Workgroups are dealt to the XCDs in turn, so a block's
 // tiles mostly share an L2; nothing rests on that.)  A workgroup finishes the tile it has drawn before it draws another, from its own queue first, then from
-// the others, and leaves when all are empty.  A tile waits only for tiles of its own block.  At any time at most one block per queue has tickets not
-// yet drawn, so at most 8 x 3 workgroups wait for tiles that nobody has; all others come to their end, and with 25 CUs for the launch one of them draws the next
-// ticket.  Nobody else writes the counters; should two calls use one workspace at a time, the looks at a counter are limited as in flow.hip.
+// the others, and leaves when all are empty.  A tile waits only for tiles of its own block.  At any time at most one block per queue has some of its tickets
+// drawn and others not, so at most 8 x 3 workgroups (of 32 rows: 8 x 6) wait for tiles that nobody has; all others come to their end, and with 25 CUs (49) for the launch one
+// of them draws the next ticket.  How long that takes is up to whatever else runs on the GPU, so the first wait of a tile, for the last ticket of its block to be drawn, has
+// a limit of its own, of half a minute; behind it all of a block's workgroups are at work.  Nobody else writes the counters; should two calls use one workspace at a time,
+// these limits end the waits and the call reports POLY_ESTALL, as in flow.hip.
 #include "flow_dev.h"
 
 #include <type_traits>
@@ -31,6 +42,7 @@ constexpr int RN_MAX_DM = 768;
 constexpr int RN_GELU = (GELU_TAB_ENTRIES + 1) & ~1;    // (what lies behind is read in 16-byte pieces)
 constexpr int RN_AT_STRIDE = 200;   // elements per rank row of At_k in LDS (192 + 8: rows start 4 banks apart)
 constexpr int RN_QUEUES = 8;
+constexpr int RN_FORMING = 1 << 24;  // looks, of 1.5 us and more, for a block's last ticket
 constexpr int KT = 3, D = 64 * KT, HEADS = KT, Nq = 3 * D, NQ = (Nq + 127) / 128;
 constexpr int CT = KT;                                     // column tiles of 16 per wave of a product with D columns
 constexpr int SLOT = KT * 2048;                            // bytes of a slot: 16 rows of D columns, or 16 CT rows of 64 columns
@@ -544,6 +556,15 @@ template <int RT, int NKT, bool SUM> __global__ __launch_bounds__(RN_THREADS, 2)
         // (the wave that waits requests its own behind the barrier: it has nothing to do in attention)
         if (wave == 7) {
             const unsigned want = tiles > 1 ? (unsigned)(l - l0 + 1) * tiles : 0;
+            if (want && l == l0) {
+                const unsigned *const drawn = run_args()->counters + (ob & (RN_QUEUES - 1)) * 16;
+                const unsigned all = (unsigned)(ob / RN_QUEUES + 1) * tiles;
+                const int most = run_args()->patience;
+                for (int looks = word_s[1] < 0 ? 0 : most < FL_PATIENCE ? most : RN_FORMING; peek(drawn) < all;) {
+                    if (--looks < 0) { word_s[1] = -1; break; }
+                    __builtin_amdgcn_s_sleep(16);
+                }
+            }
             while (want && peek(count) < want) {
                 const int looks = word_s[1] - 1;
                 word_s[1] = looks;
