@@ -565,10 +565,10 @@ template <int RT, int NKT, bool SUM> __global__ __launch_bounds__(RN_THREADS, 2)
                     __builtin_amdgcn_s_sleep(16);
                 }
             }
-            while (want && peek(count) < want) {
+            while (want) {                                             // (every look counts, so that without any patience no wait ends well)
                 const int looks = word_s[1] - 1;
                 word_s[1] = looks;
-                if (looks < 0) break;
+                if (looks < 0 || peek(count) >= want) break;
                 __builtin_amdgcn_s_sleep(1);
             }
         } else {
