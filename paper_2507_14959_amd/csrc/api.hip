@@ -88,7 +88,7 @@ FlowSegment run_segment(const poly_model_desc *m, int F, int R, bool adapted, bo
     const bool summed = r && !fan;
     if (layers == 0 || (adapted && R == 0) || !run_possible(m, adapted, loop)) return {0, layers, 64};
     if (capped) {                                          // (of pairs half the room is what is usual)
-        const int most = summed ? RN_SUM_ROUNDS * 8 * (32 / ((T + 31) / 32)) : (fan ? 2 : 1) * RN_MAX_TILES / ((T + 63) / 64);
+        const int most = summed ? RN_SUM_ROUNDS * 8 * (32 / ((T + 31) / 32)) : (fan ? 2 * RN_MOST_TILES : RN_MAX_TILES) / ((T + 63) / 64);
         return {blocks < most ? blocks : most, layers, 64};
     }
     PairCount n = fan ? pair_count(F, R) : known_count(blocks);

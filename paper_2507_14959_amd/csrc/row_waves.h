@@ -52,6 +52,10 @@ inline int rowreg_waves(int T, int D, int Dm, int r, bool by_block, const PairCo
 // 507 / 402, 72 506 / 647; 113 tokens, a bound of three a frame, 1.8 each: 24 frames 424 / 331 / 250, 64 487 / 339 / 495, 96 784 / 646, 160 968 / 971; 17 tokens: 128 375 / 305 / 243, 256
 // 397 / 308 / 245.
 constexpr int RN_MAX_TILES = 512;   // of the usual count: two rounds
+// Four where the other way is tiles of 64 rows too (a bound far above the frames, of which one each may have an adapter; ranks and blocks that rowreg.hip does not take): it takes as
+// many rounds of 27.5 to 31 us.  64 frames of 197 tokens, a bound of four each, 2.5 there: every layer adapted 1131 / 952 us, two of twelve 431 / 411, in the lagged loop one / two / three
+// each 363 / 345, 408 / 401, 450 / 448; 120 of 113 1116 / 950; 17 tokens: 333, a bound of four, 983 / 727, 520, one each, 944 / 725.
+constexpr int RN_MOST_TILES = 1024;
 // Rounds that `blocks` of so many tiles take: the tiles of a block run side by side, so of each queue's 32 CUs (rowrun.hip) a round fills what is a multiple of them, unless
 // all there is fits at once (36 blocks of seven tiles 295 us, 64 547, 72 808)
 inline int rowrun_rounds(int blocks, int tiles)
@@ -64,10 +68,10 @@ inline int rowrun_rounds(int blocks, int tiles)
 // rounds) 1538 / 1114; 64 of 113 712 / 303; 256 of 17 713 / 295.  (333 of 197: eleven rounds would be 2970, the other way 2895.)
 constexpr int RN_SUM_ROUNDS = 4;
 
-inline float rowrun_us(int rows, int T, int blocks)
+inline float rowrun_us(int rows, int T, int blocks, int most = RN_MAX_TILES)
 {
     const int tiles = (T + rows - 1) / rows;
-    return (long)blocks * tiles > RN_MAX_TILES ? 1e9f : (rows == 64 ? 24.5f + (float)T / 100.f : 18.f + (float)T / 80.f) * (float)rowrun_rounds(blocks, tiles);
+    return (long)blocks * tiles > most ? 1e9f : (rows == 64 ? 24.5f + (float)T / 100.f : 18.f + (float)T / 80.f) * (float)rowrun_rounds(blocks, tiles);
 }
 inline float two_launches_us(int T, int D, int Dm, int r, bool by_block, const PairCount &n)
 {
@@ -75,8 +79,9 @@ inline float two_launches_us(int T, int D, int Dm, int r, bool by_block, const P
 }
 inline int rowrun_rows(int T, int D, int Dm, int r, bool by_block, const PairCount &n)
 {
-    const int rows = rowrun_us(32, T, n.usual) < rowrun_us(64, T, n.usual) ? 32 : 64;
-    return rowrun_us(rows, T, n.usual) < two_launches_us(T, D, Dm, r, by_block, n) ? rows : 0;
+    const int most = rowreg_waves(T, D, Dm, r, by_block, n) ? RN_MAX_TILES : RN_MOST_TILES;
+    const int rows = rowrun_us(32, T, n.usual, most) < rowrun_us(64, T, n.usual, most) ? 32 : 64;
+    return rowrun_us(rows, T, n.usual, most) < two_launches_us(T, D, Dm, r, by_block, n) ? rows : 0;
 }
 
 // Of `blocks` without adapters, in two launches a layer: how many of them, where the others, which begin a round of large tiles that they do not fill, run as tiles

@@ -51,6 +51,8 @@ CASES = [
     (64, 193, 38, 768, 8, 3, 4, 0, 1, 6),       # one row in the fourth tile
     (64, 197, 75, 192, 8, 3, 4, 0, 1, 0),       # 300 tiles: a second round
     (64, 224, 40, 192, 4, 1, 4, 2, 1, 0),
+    (64, 197, 64, 128, 8, 3, 4, 2, 3, 100),     # a bound of four a frame, more than 512 tiles of what is usual
+    (32, 20, 520, 128, 8, 3, 4, 0, 1, 0),       # three rounds of blocks too short for rowreg.hip
 ]
 
 

@@ -44,9 +44,10 @@ def test_the_sizes_run_as_tiles(shim, case):
         assert shim.rows(T, Dm, r, 1, F, pairs) == rows and _tasks((F + pairs) // 2, T) > 44
 
 
-# blocks known to the host: one round of 32 rows, one of 64, two of either, never more than 512 tiles
+# blocks known to the host: one round of 32 rows, one of 64, two of either, never more than 512 tiles, or 1024 where the other way is tiles of 64 rows
 @pytest.mark.parametrize("T,r,blocks,rows", [(197, 8, 36, 32), (197, 8, 37, 64), (197, 8, 64, 64), (197, 0, 64, 64), (197, 0, 65, 0), (197, 8, 64, 64), (197, 8, 72, 64), (197, 8, 128, 64),
-                                             (197, 8, 129, 0), (17, 8, 256, 32), (17, 0, 513, 0), (113, 0, 64, 32), (113, 0, 128, 64), (113, 8, 240, 64)])
+                                             (197, 8, 129, 0), (17, 8, 256, 32), (17, 0, 513, 0), (113, 0, 64, 32), (113, 0, 128, 64), (113, 8, 240, 64), (17, 8, 513, 32), (17, 8, 1024, 32),
+                                             (17, 8, 1025, 0)])
 def test_rounds(shim, T, r, blocks, rows):
     assert shim.rows(T, 768, r, int(r > 0), blocks, -1) == rows
 
@@ -64,10 +65,11 @@ def test_it_is_never_taken_where_two_launches_a_layer_cost_less(shim):
         for blocks in list(range(1, 140)) + [200, 256, 300, 512, 600]:
             for r in (0, 8):
                 layer = shim.layer_us(shim.waves(T, 768, r, int(r > 0), blocks), T, r, int(r > 0), blocks) + 4.5 + blocks * T / 2700
+                most = 512 if shim.waves(T, 768, r, int(r > 0), blocks) else 1024
                 us = {}
                 for rows, one in ((64, 24.5 + T / 100), (32, 18 + T / 80)):
                     tiles = -(-T // rows)
-                    us[rows] = one * shim.rounds(blocks, tiles) if blocks * tiles <= 512 else 1e9
+                    us[rows] = one * shim.rounds(blocks, tiles) if blocks * tiles <= most else 1e9
                 best = min(us, key=us.get)
                 if min(abs(layer - us[best]), abs(us[32] - us[64])) > 1e-3:
                     assert shim.rows(T, 768, r, int(r > 0), blocks, -1) == (best if us[best] < layer else 0)
