@@ -26,7 +26,6 @@ inline int tokens(const poly_model_desc *m) { return 1 + (m->H / m->patch) * (m-
 struct FlowSegment {
     int blocks, layers;                     // 0 blocks: this segment may not
     int tiles;                              // rowrun.hip: rows of a tile; 0: flow.hip
-    int first = 0;                          // the blocks before this one go layer by layer (shared layers)
 };
 
 // blocks up to which a segment may: up to 140 tiles of 32 rows where the row kernel is the alternative, 270 where the GEMM path is (ranks
@@ -95,9 +94,7 @@ FlowSegment run_segment(const poly_model_desc *m, int F, int R, bool adapted, bo
     if (n.usual > blocks) n.usual = blocks;
     if ((long)n.usual * ((T + 31) / 32) <= FLOW_FEW && flow_segment(m, F, R, adapted, false).blocks > 0) return {0, layers, 64};
     const int rows = summed ? rowrun_rounds(blocks, (T + 31) / 32) <= RN_SUM_ROUNDS ? 32 : 0 : rowrun_rows(T, m->D, m->Dm, r, r > 0, n);
-    if (rows || adapted || m->compose == POLY_COMPOSE_SUM || m->L0 == m->L) return {rows ? blocks : 0, layers, rows};
-    const int first = rowrun_split(T, m->D, m->Dm, blocks), rest = blocks - first;
-    return {rest, layers, rowrun_us(32, T, rest) < rowrun_us(64, T, rest) ? 32 : 64, first};
+    return {rows ? blocks : 0, layers, rows};
 }
 
 // Every layer of a launch of flow.hip has buffers of its own (see there), so what they take grows with the layers of a launch: a segment
@@ -151,7 +148,6 @@ struct ForwardWs {
     size_t fixed, bytes;                    // up to xb; all of it: what a call needs at least
     int fl_tiles[2];                        // rowrun.hip instead of flow.hip in the shared and in the adapted layers: rows of a tile
     int fl_room[2];                         // blocks x layers that it has buffers for
-    int fl_first;                           // frames that go through the shared layers layer by layer, the others in launches of them (0: no others, or all)
     int fl_layers[2];                       // layers per launch of these there (0: none; of rowrun.hip: at least)
     FlowBuffers fl[2];                      // in the place of u .. patches: the patches are embedded before the first launch
     unsigned *fl_cnt[2];                    // counters of its launches, behind everything else
@@ -206,7 +202,6 @@ ForwardWs carve_forward(const poly_model_desc *m, int F, int R, bool loop, void 
             w.fl_room[a] = (int)(room < all ? room : all);
             w.fl[a] = carve_flow(m, w.fl_room[a], true, cf);
             w.fl_tiles[a] = seg[a].tiles;
-            if (a == 0) w.fl_first = seg[a].first;
             w.fl_layers[a] = w.fl_room[a] / seg[a].blocks;
             w.fl_cnt[a] = w.fl_clear + w.fl_clear_bytes / sizeof(unsigned);
             w.fl_clear_bytes += launch_counters(m, seg[a]) * (size_t)((n + w.fl_layers[a] - 1) / w.fl_layers[a]);
@@ -405,9 +400,9 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         RowRunArgs a = {};
         a.T = T; a.Dm = Dm; a.eps = m->ln_eps;
         a.rows = w.fl_tiles[ad];
-        a.nb = ad && !sum ? R : ad ? F : F - w.fl_first;
+        a.nb = ad && !sum ? R : F;
         a.nb_dev = !ad ? nullptr : (sum ? &w.meta->F_ok : R_dev);
-        a.x_in = ad ? w.xa : w.xa + (size_t)w.fl_first * T * D; a.x_out = ad && !sum ? w.xb : w.xa + (a.x_in - w.xa);
+        a.x_in = w.xa; a.x_out = ad && !sum ? w.xb : w.xa;
         a.in_map = ad && !sum ? w.frame_of_row : nullptr;
         a.n_adapters = m->n_adapters; a.r = m->r; a.scale = m->lora_scale;
         a.k = (bf16_t *)w.fl[ad].qk; a.v = (bf16_t *)w.fl[ad].vt;
@@ -446,7 +441,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         const bool qkv_lora = ln >= m->L0 && R > 0 && (m->targets & 1);
         RowPart p = {true, ln < m->L && (sum || ln != m->L0) && !(sum && qkv_lora), false, 0};
         p.lora_q = p.qkv && qkv_lora;
-        p.waves = rowreg_waves(T, D, Dm, use(1) || p.lora_q ? m->r : 0, use(1) || p.lora_q || (branch && l == m->L0), branch ? pairs : known_count(l < m->L0 && w.fl_first ? w.fl_first : F));
+        p.waves = rowreg_waves(T, D, Dm, use(1) || p.lora_q ? m->r : 0, use(1) || p.lora_q || (branch && l == m->L0), branch ? pairs : known_count(F));
         return p;
     };
     bool x_fragments = false;                  // the residual stream lies in the order of rowreg.hip: between two of its launches that nothing reads it between
@@ -454,7 +449,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
     for (int l = 0; l < m->L; ++l) {
         if (l == 0 && w.fl_cnt[0]) {
             POLY_TRY(w.fl_tiles[0] ? run(false) : flow(false));
-            if (!w.fl_first) l = m->L0;
+            l = m->L0;
             if (l == m->L) break;
         }
         if (l == m->L0 && !selected) POLY_TRY(select_now());
@@ -471,10 +466,9 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         const bool branch = !sum && l > m->L0; // residual stream already per row-block
         float *x_in = branch ? w.xb : w.xa;
         float *x_out = (!sum && l >= m->L0) ? w.xb : w.xa;
-        const int F_here = l < m->L0 && w.fl_first ? w.fl_first : F;
-        const int nb = branch ? R : F_here;    // blocks of the LayerNorm-1 input
+        const int nb = branch ? R : F;         // blocks of the LayerNorm-1 input
         const int *nb_dev = branch ? R_dev : (summed ? &w.meta->F_ok : nullptr);
-        const int n_out = (!sum && l >= m->L0) ? R : F_here;  // blocks after the qkv linear
+        const int n_out = (!sum && l >= m->L0) ? R : F;  // blocks after the qkv linear
         const int *n_out_dev = (!sum && l >= m->L0) ? R_dev : (summed ? &w.meta->F_ok : nullptr);
 
         auto lora_ptr = [&](const void *stack, int t, size_t din, size_t dout, bool is_A) -> const void * {

@@ -83,19 +83,3 @@ inline int rowrun_rows(int T, int D, int Dm, int r, bool by_block, const PairCou
     const int rows = rowrun_us(32, T, n.usual, most) < rowrun_us(64, T, n.usual, most) ? 32 : 64;
     return rowrun_us(rows, T, n.usual, most) < two_launches_us(T, D, Dm, r, by_block, n) ? rows : 0;
 }
-
-// Of `blocks` without adapters, in two launches a layer: how many of them, where the others, which begin a round of large tiles that they do not fill, run as tiles
-// beforehand; all where that is not a tenth faster.  (The two-launch figures are up to 10 us high where a second round is a small part of the first: by them 313 blocks of 113
-// tokens, 256 and 57, would be 6 % faster, and were 882 -> 933 us.)  Whole multiples of 32, so that the rows that rowreg.hip writes 32 at a time end with a block.  Twelve layers,
-// ten of them shared, us, all by two launches a layer / split: 333 blocks of 197 tokens (two rounds of 128-row tiles and one of a single tile; 320 and 13) 1780 / 1519, 384 (320
-// and 64) 1948 / 1637, 666 2952 / 2685; of 113 580 1720 / 1450, 700 1868 / 1602, 1160 2851 / 2593; of 145 500 1846 / 1556; of 64 1025 1728 / 1403; of 50 1313 1776 / 1473.
-inline int rowrun_split(int T, int D, int Dm, int blocks)
-{
-    float best = two_launches_us(T, D, Dm, 0, false, known_count(blocks)) * 0.9f;
-    int first = blocks;
-    for (int m = (blocks - 1) / 32 * 32; m > 0 && (long)(blocks - m) * ((T + 63) / 64) <= 256; m -= 32) {
-        const float one = rowrun_us(32, T, blocks - m), two = rowrun_us(64, T, blocks - m), us = two_launches_us(T, D, Dm, 0, false, known_count(m)) + (one < two ? one : two);
-        if (us < best) { best = us; first = m; }
-    }
-    return first;
-}

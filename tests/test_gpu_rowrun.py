@@ -71,6 +71,12 @@ def test_against_the_oracle(rows, T, F, Dm, r, targets, L, L0, per_frame, spare)
     assert got["status"] == 0 and np.array_equal(got["logits"][:n], again["logits"][:n])
     assert np.isnan(got["logits"][n:]).all()
     _compare(cfg, eight, sets, got["logits"][:n], w, L0, off)
+    _same_wherever_a_frame_sits(got["logits"], off)
+
+
+def _same_wherever_a_frame_sits(logits, off):
+    for f in range(8, len(off) - 1):
+        assert np.array_equal(logits[off[f]:off[f + 1]], logits[off[f % 8]:off[f % 8 + 1]])
 
 
 def _forward(model, frames, off, ids, ws, room):
@@ -134,26 +140,6 @@ def test_a_bad_adapter_id_computes_nothing():
     assert got["status"] == binding.POLY_ERANGE and np.isnan(got["logits"]).all()
 
 
-# Shared layers of which the blocks past full rounds run as tiles and the others layer by layer: T, frames, those, hidden width, layers, first adapted layer.  One block past
-# a round, whole tiles, and the most tokens
-SPLIT = [(197, 333, 320, 128, 4, 2), (64, 1025, 800, 128, 4, 3), (224, 297, 288, 256, 5, 4)]
-
-
-@pytest.mark.parametrize("T,F,first,Dm,L,L0", SPLIT)
-def test_the_blocks_past_full_rounds(T, F, first, Dm, L, L0):
-    cfg, w, eight, sets, frames, off, ids = _case(T, F, Dm, 8, 3, L, 1, 6000 + T)
-    model = binding.DeviceModel(cfg, w, L0=L0)
-    binding.poly_profile_begin(400)
-    try:
-        got = binding.run_forward(model, frames, off, ids)
-    finally:
-        prof = binding.poly_profile_end()
-    assert prof["attention"]["launches"] == L
-    again = binding.run_forward(model, frames, off, ids)
-    assert got["status"] == 0 and np.array_equal(got["logits"], again["logits"])
-    _compare(cfg, eight, sets, got["logits"], w, L0, off)
-
-
 # The sum of a block's terms: none, one, up to four in LDS (two of rank 16, three of 12), more than have a place there; a second round
 @pytest.mark.parametrize("T,F,Dm,r,targets,L,L0,most", [(17, 100, 128, 8, 3, 4, 0, 2), (50, 40, 192, 4, 1, 4, 1, 4), (113, 24, 256, 16, 3, 4, 0, 4), (197, 12, 128, 12, 2, 4, 2, 5),
                                                         (97, 30, 768, 8, 3, 4, 0, 8), (224, 40, 128, 8, 3, 4, 0, 3)])
@@ -175,3 +161,4 @@ def test_summed_terms(T, F, Dm, r, targets, L, L0, most):
     want = oracle.forward(cfg, w, eight, off8, ids8, L0=L0, compose="sum")["logits"]
     rows = np.concatenate([np.arange(off8[f % 8], off8[f % 8 + 1]) for f in range(F)])
     assert np.abs(got["logits"] - want[rows]).max() < TOL
+    _same_wherever_a_frame_sits(got["logits"], off)

@@ -14,7 +14,6 @@ extern "C" int rows(int T, int Dm, int r, int by_block, int F, int R)     // R <
     return rowrun_rows(T, RR_D, Dm, r, by_block != 0, R < 0 ? known_count(F) : pair_count(F, R));
 }
 extern "C" int rounds(int blocks, int tiles) { return rowrun_rounds(blocks, tiles); }
-extern "C" int split(int T, int Dm, int blocks) { return rowrun_split(T, RR_D, Dm, blocks); }
 extern "C" float layer_us(int waves, int T, int r, int by_block, int blocks) { return row_layer_us(waves, T, r, by_block != 0, blocks); }
 extern "C" int waves(int T, int Dm, int r, int by_block, int F) { return rowreg_waves(T, RR_D, Dm, r, by_block != 0, known_count(F)); }
 """
@@ -73,22 +72,3 @@ def test_it_is_never_taken_where_two_launches_a_layer_cost_less(shim):
                 best = min(us, key=us.get)
                 if min(abs(layer - us[best]), abs(us[32] - us[64])) > 1e-3:
                     assert shim.rows(T, 768, r, int(r > 0), blocks, -1) == (best if us[best] < layer else 0)
-
-
-@pytest.mark.parametrize("case", sizes.SPLIT)
-def test_the_sizes_are_split(shim, case):
-    T, F, first, Dm, L, L0 = case
-    assert shim.rows(T, Dm, 0, 0, F, -1) == 0 and shim.split(T, Dm, F) == first
-
-
-# full rounds, a round nearly full, a second round that is a small part of the first, and what the rule keeps of any number
-@pytest.mark.parametrize("T,blocks", [(197, 332), (197, 385), (113, 313), (113, 384), (50, 661), (17, 1400)])
-def test_what_is_not_a_tenth_faster_is_not_split(shim, T, blocks):
-    assert shim.split(T, 768, blocks) == blocks
-
-
-def test_a_split_leaves_whole_groups_of_rows_and_a_round_or_two_of_tiles(shim):
-    for T in (5, 17, 50, 64, 65, 113, 145, 197, 224):
-        for blocks in range(1, 1500, 7):
-            first = shim.split(T, 768, blocks)
-            assert first == blocks or (0 < first < blocks and first % 32 == 0 and (blocks - first) * -(-T // 64) <= 256)
