@@ -13,23 +13,26 @@
 namespace {
 
 constexpr float LOG2E = 1.4426950408889634f;
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
 
-// A wave per query tile and, from 161 keys on, room for a second workgroup on the CU: 32 output columns staged at a time, at most 168 registers, and
-// where there are more workgroups than CUs half of the waves leave once K and V are in LDS, so that the next workgroup's fit beside the others.
+// A wave per query tile and, from 161 keys on, room for others on the CU: at most 168 registers, and where there are more workgroups than CUs half of the waves leave once K
+// and V are in LDS, so that the next workgroup's fit beside the others.
 constexpr bool att_shares(int nkt, int w) { return nkt == w && nkt >= 6; }
+__host__ __device__ constexpr int att_keys(int T) { return (T + 15) & ~15; }      // that have a place in LDS
 
+// Bound by loading in one phase and computing in the next; what helps is another workgroup on the CU in the other phase.  K and V^T alone are in LDS, without padding and for
+// 16 keys at a time (53 KB for 197), so that three fit where 80 KB with padded rows and staged outputs let two.  us per launch, before / now, 197 tokens: 72 workgroups 7.8 / 7.9, 144 8.5 /
+// 8.1, 264 15.1 / 13.8, 516 22.1 / 18.6, 720 23.9 / 20.8, 999 30.0 / 25.3 (its bytes 20); 113 tokens (four instead of two) 360 8.6 / 7.6, 720 13.6 / 11.4, 999 16.2 / 13.8.
 template <int NKT, int W, bool FRAGMENTS>  // 32-key tiles: T <= 32 * NKT; waves, each takes the query tiles w, w + live, ..
-__global__ __launch_bounds__(64 * W, att_shares(NKT, W) ? 3 : 2 * W <= 8 ? 2 : 1) void attn_bf16_kernel(const bf16_t *qkv, bf16_t *out, int T, int D, int heads, int n_blocks,
+__global__ __launch_bounds__(64 * W, att_shares(NKT, W) ? 3 : NKT > W ? 3 : NKT <= 4 ? 4 : 1) void attn_bf16_kernel(const bf16_t *qkv, bf16_t *out, int T, int D, int heads, int n_blocks,
                                                         const int *n_blocks_dev)
 {
-    constexpr int TKP = NKT * 32;
-    constexpr int KS = 64 + 8;    // Ks row stride (elements): 144 B, 16-byte aligned
-    constexpr int VS = TKP + 8;   // Vt row stride: multiple of 8 elements
-    constexpr int OC = att_shares(NKT, W) ? 32 : 64, OS = OC + 8;    // columns of a wave's output tile staged at a time, its row stride
     extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-    bf16_t *Ks = smem;                       // [TKP][KS]
-    bf16_t *Vt = Ks + TKP * KS;              // [64][VS]
-    bf16_t *Ot = Vt + 64 * VS;               // [waves][32][OS]: finished outputs of a wave's query tile, for row-wise stores
+    const int TK = att_keys(T), VS = TK + 4; // Vt's rows are an odd number of 8-byte pieces apart: 8-byte reads of 32 rows meet no bank twice
+    bf16_t *Ks = smem;                       // [TK][64], 16-byte piece c of row r at c ^ (r >> 1 & 7)
+    bf16_t *Vt = Ks + TK * 64;               // [64][VS]
 
     const int nb = n_blocks_dev ? min(*n_blocks_dev, n_blocks) : n_blocks;
     const int b = blockIdx.x / heads, hd = blockIdx.x % heads;
@@ -49,14 +52,14 @@ __global__ __launch_bounds__(64 * W, att_shares(NKT, W) ? 3 : 2 * W <= 8 ? 2 : 1
         for (int ds = 0; ds < 4; ++ds) qf[ds] = *(const bf16x8 *)(base + (size_t)min(qs * 32 + lm, T - 1) * ld + ds * 16 + lh * 8);
     };
     load_q(wave);
-    constexpr int NKP = (256 * NKT + nthreads - 1) / nthreads;     // K pieces (256 NKT) per thread
+    constexpr int NKP = (256 * NKT + nthreads - 1) / nthreads;     // K pieces (8 TK of up to 256 NKT) per thread
     bf16x8 kp[NKP];
 #pragma unroll
     for (int i = 0; i < NKP; ++i) {
         const int v = tid + i * nthreads, key = v >> 3;
         kp[i] = *(const bf16x8 *)(base + (size_t)min(key, T - 1) * ld + D + (v & 7) * 8);
     }
-    for (int blk = tid; blk < (TKP / 8) * 8; blk += nthreads) {
+    for (int blk = tid; blk < TK; blk += nthreads) {
         const int cb = blk & 7, kb = blk >> 3;       // consecutive lanes: consecutive 16-byte pieces of a row of V
         bf16x8 vv[8];
 #pragma unroll
@@ -66,17 +69,22 @@ __global__ __launch_bounds__(64 * W, att_shares(NKT, W) ? 3 : 2 * W <= 8 ? 2 : 1
         }
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-            const bf16x8 t = {vv[0][c], vv[1][c], vv[2][c], vv[3][c], vv[4][c], vv[5][c], vv[6][c], vv[7][c]};
-            *(bf16x8 *)(Vt + (cb * 8 + c) * VS + kb * 8) = t;
+            bf16_t *row = Vt + (cb * 8 + c) * VS + kb * 8;
+            *(bf16x4 *)row = bf16x4{vv[0][c], vv[1][c], vv[2][c], vv[3][c]};
+            *(bf16x4 *)(row + 4) = bf16x4{vv[4][c], vv[5][c], vv[6][c], vv[7][c]};
         }
     }
 #pragma unroll
     for (int i = 0; i < NKP; ++i) {
         const int v = tid + i * nthreads;
-        if (v < TKP * 8) *(bf16x8 *)(Ks + (v >> 3) * KS + (v & 7) * 8) = kp[i];
+        if (v < TK * 8) *(bf16x8 *)(Ks + (v >> 3) * 64 + ((v & 7) ^ (v >> 4 & 7)) * 8) = kp[i];
     }
     __syncthreads();
 
+    // the second 16 keys of the last tile may not be there: their scores are read from V^T's place and masked, their step of the second product is left out
+    const bool half = TK < 32 * NKT;
+    const int sw = lm >> 1 & 7;
+    auto k_piece = [&](int kt, int ds) { return *(const bf16x8 *)(Ks + (kt * 32 + lm) * 64 + ((2 * ds + lh) ^ sw) * 8); };
     const int live = att_shares(NKT, W) && nb * heads > 256 ? (NKT + 1) / 2 : W;
     if (wave >= live) return;
     for (int qs = wave; qs * 32 < T; qs += live) {
@@ -85,12 +93,12 @@ __global__ __launch_bounds__(64 * W, att_shares(NKT, W) ? 3 : 2 * W <= 8 ? 2 : 1
         f32x16 s[NKT];
         bf16x8 kf[2][4];
 #pragma unroll
-        for (int ds = 0; ds < 4; ++ds) kf[0][ds] = *(const bf16x8 *)(Ks + lm * KS + ds * 16 + lh * 8);
+        for (int ds = 0; ds < 4; ++ds) kf[0][ds] = k_piece(0, ds);
 #pragma unroll
         for (int kt = 0; kt < NKT; ++kt) {
             if (kt + 1 < NKT) {
 #pragma unroll
-                for (int ds = 0; ds < 4; ++ds) kf[(kt + 1) & 1][ds] = *(const bf16x8 *)(Ks + ((kt + 1) * 32 + lm) * KS + ds * 16 + lh * 8);
+                for (int ds = 0; ds < 4; ++ds) kf[(kt + 1) & 1][ds] = k_piece(kt + 1, ds);
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -152,7 +160,8 @@ __global__ __launch_bounds__(64 * W, att_shares(NKT, W) ? 3 : 2 * W <= 8 ? 2 : 1
         loadv(0, 0);
 #pragma unroll
         for (int st = 0; st < 2 * NKT; ++st) {
-            if (st + 1 < 2 * NKT) loadv(st + 1, (st + 1) & 1);
+            if (st + 1 == 2 * NKT && half) break;
+            if (st + 2 < 2 * NKT || (st + 2 == 2 * NKT && !half)) loadv(st + 1, (st + 1) & 1);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int dt = 0; dt < 2; ++dt) {
@@ -163,39 +172,25 @@ __global__ __launch_bounds__(64 * W, att_shares(NKT, W) ? 3 : 2 * W <= 8 ? 2 : 1
             __builtin_amdgcn_sched_barrier(0);
         }
 
-        // a lane owns one query: stored from registers, every instruction would touch 32 cache lines with 8 bytes each.
-        // The wave lays its 32 x 64 tile out in LDS and stores 16-byte pieces, 8 lanes per row
+        // a lane owns four columns of every eight of one query: the two lanes of a query trade, so that each has 16 bytes in a row and the wave stores 32 of each query
+        // (for rowreg.hip 1 KB in a run: 16 columns of 32 rows)
         const float inv = 1.0f / sum;
-        bf16_t *ot = Ot + wave * 32 * OS;
+        const int row = qs * 32 + lm;
+        const size_t flat = (size_t)b * T + row;
+        bf16_t *dst = FRAGMENTS ? out + (flat >> 5) * (32 * D) + hd * 2048 + (lh * 32 + (flat & 31)) * 8 : out + flat * D + hd * 64 + lh * 8;
 #pragma unroll
-        for (int c0 = 0; c0 < 64; c0 += OC) {
+        for (int i = 0; i < 4; ++i) {
+            unsigned w[2][2];                              // columns 16 i + 8 q + 4 lh + {0, 1}, {2, 3}
 #pragma unroll
-            for (int dt = c0 / 32; dt < (c0 + OC) / 32; ++dt)
+            for (int q = 0; q < 2; ++q)
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    bf16x4 w;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) w[q] = (bf16_t)(o[dt][g * 4 + q] * inv);
-                    *(bf16x4 *)(ot + lm * OS + dt * 32 - c0 + 8 * g + 4 * lh) = w;
+                for (int h = 0; h < 2; ++h) {
+                    const int e = (2 * (i & 1) + q) * 4 + 2 * h;
+                    const bf16x2 two = {(bf16_t)(o[i >> 1][e] * inv), (bf16_t)(o[i >> 1][e + 1] * inv)};
+                    w[q][h] = __builtin_bit_cast(unsigned, two);
                 }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");    // the tile is private to the wave: no barrier
-            if constexpr (FRAGMENTS) {                            // for rowreg.hip: 16 columns of 32 rows an instruction, 512 bytes per half of them
-                const int row = qs * 32 + lm;
-                const size_t flat = (size_t)b * T + row;
-#pragma unroll
-                for (int i = 0; i < OC / 16; ++i) {
-                    const bf16x8 v = *(const bf16x8 *)(ot + lm * OS + i * 16 + lh * 8);
-                    if (row < T) *(bf16x8 *)(out + (flat >> 5) * (32 * D) + (hd * 4 + c0 / 16 + i) * 512 + (lh * 32 + (flat & 31)) * 8) = v;
-                }
-            } else {
-                constexpr int LR = OC / 8, RI = 64 / LR;          // lanes per row, rows per instruction
-#pragma unroll
-                for (int i = 0; i < 32 / RI; ++i) {
-                    const int row = i * RI + lane / LR, qrow = qs * 32 + row;
-                    const bf16x8 v = *(const bf16x8 *)(ot + row * OS + lane % LR * 8);
-                    if (qrow < T) *(bf16x8 *)(out + ((size_t)b * T + qrow) * D + hd * 64 + c0 + lane % LR * 8) = v;
-                }
-            }
+            const u32x2 a = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false), c = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+            if (row < T) *(u32x4 *)(dst + i * (FRAGMENTS ? 512 : 16)) = u32x4{a[0], c[0], a[1], c[1]};
         }
     }
 }
@@ -393,16 +388,8 @@ __global__ __launch_bounds__(256) void attn_class_kernel(const E *qkv, E *out, i
 template <int NKT, int W, bool FRAGMENTS>
 int launch_bf16(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, hipStream_t st)
 {
-    constexpr int TKP = NKT * 32;
-    constexpr int LDS = (TKP * 72 + 64 * (TKP + 8) + W * 32 * (att_shares(NKT, W) ? 40 : 72)) * 2;
+    const int LDS = (att_keys(T) * 128 + 64 * 4) * 2;
     auto kern = attn_bf16_kernel<NKT, W, FRAGMENTS>;
-    if (LDS > 64 * 1024) {
-        static bool attr_set = false;   // raising the dynamic LDS limit is a per-kernel, process-wide setting
-        if (!attr_set) {
-            if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS) != hipSuccess) return POLY_EHIP;
-            attr_set = true;
-        }
-    }
     POLY_LAUNCH_SHMEM(POLY_STAGE_ATTN, kern, dim3((unsigned)(n_blocks * heads)), dim3(64 * W), LDS, st, (const bf16_t *)qkv, (bf16_t *)out, T, D,
                       heads, n_blocks, n_blocks_dev);
     return POLY_OK;
@@ -421,10 +408,10 @@ int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_
     if (n_blocks == 0) return POLY_OK;
     if (D != heads * 64 || (fragments && dtype != POLY_BF16)) return POLY_EINVAL;
     if (dtype == POLY_BF16) {
-        // From 161 keys on, two query tiles per wave and two workgroups per CU, one loading while the other computes, are faster where there are more
+        // From 161 keys on, two query tiles per wave and up to three workgroups per CU, one loading while another computes, are faster where there are more
         // workgroups than CUs, and slower below.  Half the waves from the start where the usual count says so, else the form that looks at the true
-        // count (its second workgroup cannot load beside the first).  us, a tile per wave and CUs to themselves / half the waves / by the count, 197
-        // tokens: 90 workgroups 7.7 / 9.0 / 7.7, 192 8.3 / 9.8 / 8.4, 255 9.6 / 10.9 / 9.7, 270 15.7 / 14.5 / 14.8, 600 - / 22.0 / 22.7, 999 32.3 / 27.6 / 28.9.
+        // count (whose second workgroup cannot load beside the first).  us, by the count / half the waves, 197 tokens: 96 workgroups 7.7 / 8.8, 192 9.3 / 10.3,
+        // 252 10.4 / 11.6, 264 15.2 / 14.3, 360 16.2 / 15.4, 516 21.0 / 19.3, 720 22.8 / 21.2.
         const bool many = (long)n_usual * heads > 256;
         switch ((T + 31) / 32) {
         case 1: if (launch_bf16<1>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
@@ -434,7 +421,7 @@ int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_
         case 5: if (launch_bf16<5>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
         case 6: if ((many ? launch_bf16<6, 3> : launch_bf16<6>)(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
         case 7: if ((many ? launch_bf16<7, 4> : launch_bf16<7>)(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
-        default: return POLY_EINVAL;  // bf16 attention holds all keys of a block in 64 KB of LDS: T <= 224
+        default: return POLY_EINVAL;  // bf16 attention holds all keys of a block in LDS: T <= 224
         }
     } else {
         POLY_LAUNCH(POLY_STAGE_ATTN, attn_f32_kernel, dim3((unsigned)(n_blocks * heads * ((T + 127) / 128))), dim3(256), st, (const float *)qkv, (float *)out, T, D, heads,

@@ -1,8 +1,10 @@
 """Attention of long blocks with two query tiles per wave: more (block, head) pairs than CUs."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
+import test_gpu_rowrun as run
 from paper_2507_14959_amd import binding, synth
 from test_gpu_forward import compare
 
@@ -40,3 +42,20 @@ def test_form_by_the_true_count(hw, n, adapters, cap):
     want = oracle.forward(cfg, w, frames, off, ids, L0=0)["logits"]
     # 1.1e-3 to 1.7e-3 over the cases; a linear's bias left out of one layer moves the logits by 6e-3 and more
     assert got["status"] == 0 and np.abs(got["logits"][:len(ids)] - want).max() < 4e-3
+
+
+# Keys have a place in LDS 16 at a time, tiles are 32: the second half of the last tile there or not, by one key, in every number of tiles, on few workgroups and on many
+@pytest.mark.parametrize("F", [60, 150])
+@pytest.mark.parametrize("T", [2, 16, 17, 32, 33, 48, 49, 64, 80, 81, 112, 113, 144, 145, 176, 177, 192, 193, 208, 209, 224])
+def test_the_last_tile_of_keys(T, F):
+    cfg, w, eight, sets, frames, off, ids = run._case(T, F, 128, 8, 3, 3, 1, 7000 + T)
+    model = binding.DeviceModel(cfg, w, L0=0)
+    ws = torch.empty(binding.poly_forward_workspace_bytes(model, F, F), dtype=torch.uint8, device="cuda")
+    lo, hi = 0, ws.numel() // 256
+    while hi - lo > 1:                                       # the smallest workspace that is taken: layer by layer
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if run._forward(model, frames, off, ids, ws[:256 * mid], F)[0] == 0 else (mid, hi)
+    rc, got, status, prof = run._forward(model, frames, off, ids, ws[:256 * hi], F)
+    assert rc == 0 and status == 0 and prof["attention"]["launches"] == 3
+    run._compare(cfg, eight, sets, got, w, 0, off)
+    run._same_wherever_a_frame_sits(got, off)
