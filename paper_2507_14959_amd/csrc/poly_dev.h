@@ -278,12 +278,13 @@ struct RowLayerArgs {
     const float *bq;                 // [3 D]
     const bf16_t *Aqt, *Bqt;         // [n_adapters][r][D], [n_adapters][3 D][r]; null = no adapters on qkv
     bf16_t *qkv_out;                 // [n_out][T][3 D]
+    int row_first;                   // set by launch_rowreg
     bool res_fragments, out_fragments;   // launch_rowreg only: res / x_out lie in its order (below); o always does there
 };
 bool rowlayer_supported(int D, int Dm, int r);
 int launch_rowlayer(const RowLayerArgs &a, hipStream_t st);
 // The same with 32 rows per wave, all of a wave's rows in its registers (rowreg.hip; row_waves.h says where).
-// Its order, of o and where the flags say so of the residual stream, on the rows of all blocks as one run: groups of 32 rows; in a group, of a 16-bit
+// waves: 4, 8 or ROWREG_BOTH.  Its order, of o and where the flags say so of the residual stream, on the rows of all blocks as one run: groups of 32 rows; in a group, of a 16-bit
 // value, [column / 16][column / 8 % 2][row][column % 8], of a float [column / 8][column / 4 % 2][row][column % 4].  The last group of a buffer may reach
 // 31 rows past the last row.
 int launch_rowreg(const RowLayerArgs &a, int waves, hipStream_t st);

@@ -20,27 +20,37 @@ struct PairCount {
 inline PairCount pair_count(int F, int R) { return {(F + R) / 2, F, R > 3 * F ? 1.f : 1.1f}; }
 inline PairCount known_count(int blocks) { return {blocks, blocks, 1.f}; }
 
+// Full rounds of 256-row tiles and the rows past them on tiles of 128, in a launch of their own (a lone tile of 128 rows has a wave per SIMD and takes 36 us, one of 256 rows, or a
+// third round of 128, as long or longer).  Only where the count is what the host knows, or at most that.  Twelve layers of DeiT-tiny, ten of them shared, us, before / now: 333 frames of 197
+// tokens 1737 / 1640, 400 1853 / 1721, 498 (one and a half rounds) 1992 / 1854, 700 2981 / 2890; of 113 tokens 581 1708 / 1614, 860 1956 / 1814; of 50 1700 1916 / 1775.
+constexpr int ROWREG_BOTH = 12;
+inline long rowreg_full(long rows) { return rows / 65536 * 65536; }
+
 // us of the row-wise part of a layer of DeiT-tiny on n workgroups, a CU each at a time: a round takes `c`, and up to `d` more the more CUs are at work (they share the
 // memory and the power).  waves 0: tiles of 64 rows; 4, 8: of 128 / 256 rows (rowreg.hip).  Twelve layers and everything else of a forward: 12214 rows 486 / 610 /
 // 772 us, 18912 817 / 678 / 839, 32702 941 / 808 / 941, 37430 1255 / 1247 / 1039, 57130 1656 / 1424 / 1212, 65601 (a row in a round of its own) 1956 / 1875 /
-// 1834; with adapters 14184 rows (288 tiles that end with their block) 809 / 714 / 891, 28368 1257 / 897 / 1047, 42552 1665 / 1482 / 1171.
+// 1834, but see above; with adapters 14184 rows (288 tiles that end with their block) 809 / 714 / 891, 28368 1257 / 897 / 1047, 42552 1665 / 1482 / 1171.
 inline float row_layer_us(int waves, int T, int r, bool by_block, int blocks)
 {
     auto rounds = [](long n, float c, float d) { return (float)(n / 256) * (c + d) + (n % 256 ? c + d * (float)(n % 256) / 256.f : 0.f); };
     const long rows = (long)blocks * T;
     if (waves == 0) return rounds(by_block ? (long)blocks * ((T + 63) / 64) : (rows + 63) / 64, r ? 31.f : 27.5f, 0.f);
-    return waves == 4 ? rounds((rows + 127) / 128, r ? 46.f : 36.f, 8.f) : rounds((rows + 255) / 256, r ? 58.f : 48.f, 30.f);
+    const float few = r ? 46.f : 36.f;
+    if (waves == ROWREG_BOTH) return rounds(rowreg_full(rows) / 256, r ? 58.f : 48.f, 30.f) + rounds((rows - rowreg_full(rows) + 127) / 128, few, 8.f) + 2.f;
+    return waves == 4 ? rounds((rows + 127) / 128, few, 8.f) : rounds((rows + 255) / 256, r ? 58.f : 48.f, 30.f);
 }
 
-// Waves per workgroup of rowreg.hip where `n.usual` blocks of T rows are that many that it is faster, and on `n.least` blocks, where there may be as few, no slower
+// Waves per workgroup of rowreg.hip (or ROWREG_BOTH) where `n.usual` blocks of T rows are that many that it is faster, and on `n.least` blocks, where there may be as few, no slower
 // than `n.slack` times; 0 where they are not or it does not apply.  r: rank of the adapters in the launch, 0 without; by_block: adapters or a map.
 inline int rowreg_waves(int T, int D, int Dm, int r, bool by_block, const PairCount &n)
 {
     if (D != RR_D || Dm < 128 || Dm % 64 || Dm > RR_MAX_DM || (r && r != 8 && r != 16) || (by_block && T < 32)) return 0;
     auto us = [&](int waves, int blocks) { return row_layer_us(waves, T, r, by_block, blocks); };
     int best = 0;
-    for (int waves : {4, 8})
+    for (int waves : {4, 8, ROWREG_BOTH}) {
+        if (waves == ROWREG_BOTH && (n.usual != n.least || (long)n.usual * T <= 65536 || (long)n.usual * T % 65536 == 0)) continue;
         if (us(waves, n.usual) < us(best, n.usual) && us(waves, n.least) <= us(0, n.least) * n.slack) best = waves;
+    }
     return best;
 }
 

@@ -80,8 +80,8 @@ __global__ __launch_bounds__(64 * W, 2) void rowreg_kernel(const RowLayerArgs a)
     const int Dm = a.Dm, nc = LAYER ? Dm >> 6 : 0;
     const int n_out = a.n_out_dev ? min(*a.n_out_dev, a.n_out) : a.n_out;
     const int total = n_out * a.T;
-    if ((int)blockIdx.x * 32 * W >= total) return;
-    const int row0 = (blockIdx.x * W + wave) * 32;
+    if (a.row_first + (int)blockIdx.x * 32 * W >= total) return;
+    const int row0 = a.row_first + (blockIdx.x * W + wave) * 32;
     const int rows = min(max(total - row0, 0), 32);        // none in the last waves of the last tile: they load weights and compute what is not stored
     const bool full = rows == 32;
 
@@ -573,7 +573,7 @@ __global__ __launch_bounds__(64 * W, 2) void rowreg_kernel(const RowLayerArgs a)
     }
 }
 
-template <int W, bool LAYER, bool QKV, bool LORA> int launch_t(const RowLayerArgs &a, hipStream_t st)
+template <int W, bool LAYER, bool QKV, bool LORA> int launch_t(const RowLayerArgs &a, long rows, hipStream_t st)
 {
     constexpr int D = RR_D;
     constexpr int LDS = RR_SLOTS * RR_UNIT + W * RR_STAGE + (RR_MAX_DM + 3 * D + 2 * D + 4 * D) * 4 + RR_GELU * 8;
@@ -584,17 +584,16 @@ template <int W, bool LAYER, bool QKV, bool LORA> int launch_t(const RowLayerArg
         if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS) != hipSuccess) return POLY_EHIP;
         attr_set = true;
     }
-    const long rows = (long)a.n_out * a.T;
     POLY_LAUNCH_SHMEM(POLY_STAGE_GEMM, kern, dim3((unsigned)((rows + 32 * W - 1) / (32 * W))), dim3(64 * W), LDS, st, a);
     return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
 }
 
-template <int W> int launch_w(const RowLayerArgs &a, hipStream_t st)
+template <int W> int launch_w(const RowLayerArgs &a, long rows, hipStream_t st)      // rows: from a.row_first on
 {
     const bool lora = (a.o && a.Apt) || (a.qkv_out && a.Aqt);
-    if (!a.o) return lora ? launch_t<W, false, true, true>(a, st) : launch_t<W, false, true, false>(a, st);
-    if (!a.qkv_out) return lora ? launch_t<W, true, false, true>(a, st) : launch_t<W, true, false, false>(a, st);
-    return lora ? launch_t<W, true, true, true>(a, st) : launch_t<W, true, true, false>(a, st);
+    if (!a.o) return lora ? launch_t<W, false, true, true>(a, rows, st) : launch_t<W, false, true, false>(a, rows, st);
+    if (!a.qkv_out) return lora ? launch_t<W, true, false, true>(a, rows, st) : launch_t<W, true, false, false>(a, rows, st);
+    return lora ? launch_t<W, true, true, true>(a, rows, st) : launch_t<W, true, true, false>(a, rows, st);
 }
 
 }  // namespace
@@ -604,5 +603,9 @@ int launch_rowreg(const RowLayerArgs &a, int waves, hipStream_t st)
     if (a.n_out <= 0 || a.T <= 0) return POLY_OK;
     const bool lora = (a.o && a.Apt) || (a.qkv_out && a.Aqt);
     if (a.D != RR_D || a.Dm < 128 || a.Dm % 64 || a.Dm > RR_MAX_DM || (lora && a.r != 8 && a.r != 16) || ((lora || a.res_block_of_out) && a.T < 32)) return POLY_EINVAL;
-    return waves == 4 ? launch_w<4>(a, st) : launch_w<8>(a, st);
+    const long rows = (long)a.n_out * a.T, full = waves == ROWREG_BOTH ? rowreg_full(rows) : waves == 8 ? rows : 0;
+    RowLayerArgs rest = a;
+    rest.row_first = (int)full;
+    if (full > 0) { const int rc = launch_w<8>(a, full, st); if (rc != POLY_OK) return rc; }
+    return full < rows ? launch_w<4>(rest, rows - full, st) : POLY_OK;
 }

@@ -58,6 +58,23 @@ def test_against_the_oracle(F, hw, patch, Dm, r, targets, per_frame, spare, L0):
     assert np.array_equal(logits, logits[first[rows]])     # wherever in a tile a block lies
 
 
+# More than 65 536 rows: 256 tiles of 256 and, in a launch of their own, the rest on tiles of 128.  Frames of 37 tokens, those of them that have an adapter
+BOTH = [(1772, 1772), (1900, 1900), (2655, 2655), (1900, 1772), (1900, 1600)]       # 28 rows past, tiles past, 99 rows short of a round and a half; the last pairs not there, all of the rest
+
+
+@pytest.mark.parametrize("F,n", BOTH)
+@pytest.mark.parametrize("L0", [0, 1, 3])
+def test_full_rounds_and_the_rows_past_them(F, n, L0):
+    cfg, w, frames, sets, many, off, ids, rows = _case(F, 48, 8, 128, 8, 3, 1)
+    off, room = np.minimum(off, n), np.concatenate([ids[:n], np.zeros(F - n, dtype=ids.dtype)])
+    got = binding.run_forward(binding.DeviceModel(cfg, w, L0=L0), many, off, room, R_cap=F)
+    assert got["status"] == 0 and np.isnan(got["logits"][n:]).all()
+    logits = got["logits"][:n]
+    assert np.abs(logits - _want(cfg, w, frames, sets, rows, L0)[:n]).max() < BOUND
+    first = np.unique(rows, return_index=True)[1]
+    assert np.array_equal(logits, logits[first[rows[:n]]])
+
+
 ROOM = [
     (120, 400, 0),       # at one adapter a frame tiles of 64 rows are faster
     (250, 300, 0),

@@ -35,6 +35,12 @@ def test_the_sizes_reach_the_kernels_they_are_for(waves, case):
     assert (waves(T, Dm, 0, 0, F, -1), waves(T, Dm, r, 1, F, pairs + spare)) == WAVES[F, Dm]
 
 
+@pytest.mark.parametrize("F", sorted({F for F, _ in sizes.BOTH}))
+def test_rows_past_full_rounds(waves, F):
+    assert (waves(37, 128, 0, 0, F, -1), waves(37, 128, 8, 1, F, F)) == (12, 12) and waves(37, 128, 8, 1, F, F + 2) in (4, 8)
+    assert waves(64, 768, 0, 0, 1024, -1) == 8 and waves(64, 768, 0, 0, 1025, -1) == 12 and waves(64, 768, 0, 0, 1537, -1) == 8
+
+
 def test_the_lagged_loop_is_above_the_line(waves):
     F, hw, patch, Dm, r, room = sizes.LOOP
     assert waves(1 + (hw // patch) ** 2, Dm, 0, 0, F, -1) > 0 and waves(1 + (hw // patch) ** 2, Dm, r, 1, F, room * F) > 0
