@@ -25,7 +25,7 @@ __host__ __device__ constexpr int att_keys(int T) { return (T + 15) & ~15; }    
 // Bound by loading in one phase and computing in the next; what helps is another workgroup on the CU in the other phase.  K and V^T alone are in LDS, without padding and for
 // 16 keys at a time (53 KB for 197), so that three fit where 80 KB with padded rows and staged outputs let two.  us per launch, before / now, 197 tokens: 72 workgroups 7.8 / 7.9, 144 8.5 /
 // 8.1, 264 15.1 / 13.8, 516 22.1 / 18.6, 720 23.9 / 20.8, 999 30.0 / 25.3 (its bytes 20); 113 tokens (four instead of two) 360 8.6 / 7.6, 720 13.6 / 11.4, 999 16.2 / 13.8.
-template <int NKT, int W, bool FRAGMENTS>  // 32-key tiles: T <= 32 * NKT; waves, each takes the query tiles w, w + live, ..
+template <int NKT, int W, bool FRAGMENTS, bool SPLIT>  // 32-key tiles: T <= 32 * NKT; waves, each takes the query tiles w, w + live, ..; SPLIT: two workgroups, of the first four and of the other query tiles
 __global__ __launch_bounds__(64 * W, att_shares(NKT, W) ? 3 : NKT > W ? 3 : NKT <= 4 ? 4 : 1) void attn_bf16_kernel(const bf16_t *qkv, bf16_t *out, int T, int D, int heads, int n_blocks,
                                                         const int *n_blocks_dev)
 {
@@ -51,7 +51,8 @@ __global__ __launch_bounds__(64 * W, att_shares(NKT, W) ? 3 : NKT > W ? 3 : NKT 
 #pragma unroll
         for (int ds = 0; ds < 4; ++ds) qf[ds] = *(const bf16x8 *)(base + (size_t)min(qs * 32 + lm, T - 1) * ld + ds * 16 + lh * 8);
     };
-    load_q(wave);
+    const int first = SPLIT ? (int)blockIdx.y * 4 : 0;         // query tile of wave 0
+    load_q(SPLIT ? min(first + wave, NKT - 1) : wave);
     constexpr int NKP = (256 * NKT + nthreads - 1) / nthreads;     // K pieces (8 TK of up to 256 NKT) per thread
     bf16x8 kp[NKP];
 #pragma unroll
@@ -86,8 +87,8 @@ __global__ __launch_bounds__(64 * W, att_shares(NKT, W) ? 3 : NKT > W ? 3 : NKT 
     const int sw = lm >> 1 & 7;
     auto k_piece = [&](int kt, int ds) { return *(const bf16x8 *)(Ks + (kt * 32 + lm) * 64 + ((2 * ds + lh) ^ sw) * 8); };
     const int live = att_shares(NKT, W) && nb * heads > 256 ? (NKT + 1) / 2 : W;
-    if (wave >= live) return;
-    for (int qs = wave; qs * 32 < T; qs += live) {
+    if (wave >= (SPLIT ? 4 : live)) return;
+    for (int qs = first + wave; qs * 32 < T; qs += SPLIT ? NKT : live) {
         // S^T tile kt: rows = keys kt*32 + 8*(e/4) + 4*lh + e%4, column = this lane's query.  The K fragments of tile
         // kt + 1 are read while the MFMAs of tile kt run (the scheduling barriers pin that order)
         f32x16 s[NKT];
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(64 * W, att_shares(NKT, W) ? 3 : NKT > W ? 3 : NKT 
             __builtin_amdgcn_sched_barrier(0);
         }
 
-        if (att_shares(NKT, W) ? qs + live < NKT : NKT > W) load_q(min(qs + live, NKT - 1));   // for the next round: arrives under this one's softmax
+        if (!SPLIT && (att_shares(NKT, W) ? qs + live < NKT : NKT > W)) load_q(min(qs + live, NKT - 1));   // for the next round: arrives under this one's softmax
 
         // only the last key tile can hold keys past T (T > 32 * (NKT - 1) by construction)
 #pragma unroll
@@ -385,19 +386,21 @@ __global__ __launch_bounds__(256) void attn_class_kernel(const E *qkv, E *out, i
     out[(size_t)b * D + hd * 64 + lane] = (E)(y / all);
 }
 
-template <int NKT, int W, bool FRAGMENTS>
+template <int NKT, int W, bool FRAGMENTS, bool SPLIT>
 int launch_bf16(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, hipStream_t st)
 {
     const int LDS = (att_keys(T) * 128 + 64 * 4) * 2;
-    auto kern = attn_bf16_kernel<NKT, W, FRAGMENTS>;
-    POLY_LAUNCH_SHMEM(POLY_STAGE_ATTN, kern, dim3((unsigned)(n_blocks * heads)), dim3(64 * W), LDS, st, (const bf16_t *)qkv, (bf16_t *)out, T, D,
+    auto kern = attn_bf16_kernel<NKT, W, FRAGMENTS, SPLIT>;
+    POLY_LAUNCH_SHMEM(POLY_STAGE_ATTN, kern, dim3((unsigned)(n_blocks * heads), SPLIT ? 2 : 1), dim3(64 * W), LDS, st, (const bf16_t *)qkv, (bf16_t *)out, T, D,
                       heads, n_blocks, n_blocks_dev);
     return POLY_OK;
 }
 template <int NKT, int W = NKT>
-int launch_bf16(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, bool fragments, hipStream_t st)
+int launch_bf16(const void *qkv, void *out, int T, int D, int heads, int n_blocks, const int *n_blocks_dev, bool fragments, hipStream_t st, bool split = false)
 {
-    return (fragments ? launch_bf16<NKT, W, true> : launch_bf16<NKT, W, false>)(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st);
+    if constexpr (W == NKT && NKT > 4)
+        if (split && !fragments) return launch_bf16<NKT, W, false, true>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st);
+    return (fragments ? launch_bf16<NKT, W, true, false> : launch_bf16<NKT, W, false, false>)(qkv, out, T, D, heads, n_blocks, n_blocks_dev, st);
 }
 
 }  // namespace
@@ -412,15 +415,17 @@ int launch_attention(const void *qkv, void *out, int T, int D, int heads, int n_
         // workgroups than CUs, and slower below.  Half the waves from the start where the usual count says so, else the form that looks at the true
         // count (whose second workgroup cannot load beside the first).  us, by the count / half the waves, 197 tokens: 96 workgroups 7.7 / 8.8, 192 9.3 / 10.3,
         // 252 10.4 / 11.6, 264 15.2 / 14.3, 360 16.2 / 15.4, 516 21.0 / 19.3, 720 22.8 / 21.2.
-        const bool many = (long)n_usual * heads > 256;
+        // From 129 keys on, where there are two CUs for every workgroup, it is two: all waves load and four (three, two, one) compute, one per SIMD.  197 tokens: 48 workgroups
+        // 7.3 / 6.1, 96 7.6 / 6.5, 120 7.8 / 6.9, 132 8.0 / 9.4; 155 tokens 60 5.7 / 5.2, 120 6.4 / 5.8, 132 6.5 / 7.4.  (Of a bound half of what it has over the usual.)
+        const bool many = (long)n_usual * heads > 256, split = ((long)n_usual + n_blocks) * heads <= 256;
         switch ((T + 31) / 32) {
         case 1: if (launch_bf16<1>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
         case 2: if (launch_bf16<2>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
         case 3: if (launch_bf16<3>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
         case 4: if (launch_bf16<4>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
-        case 5: if (launch_bf16<5>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
-        case 6: if ((many ? launch_bf16<6, 3> : launch_bf16<6>)(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
-        case 7: if ((many ? launch_bf16<7, 4> : launch_bf16<7>)(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st) != POLY_OK) return POLY_EHIP; break;
+        case 5: if (launch_bf16<5>(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st, split) != POLY_OK) return POLY_EHIP; break;
+        case 6: if ((many ? launch_bf16<6, 3> : launch_bf16<6>)(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st, split) != POLY_OK) return POLY_EHIP; break;
+        case 7: if ((many ? launch_bf16<7, 4> : launch_bf16<7>)(qkv, out, T, D, heads, n_blocks, n_blocks_dev, fragments, st, split) != POLY_OK) return POLY_EHIP; break;
         default: return POLY_EINVAL;  // bf16 attention holds all keys of a block in LDS: T <= 224
         }
     } else {

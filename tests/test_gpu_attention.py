@@ -44,8 +44,8 @@ def test_form_by_the_true_count(hw, n, adapters, cap):
     assert got["status"] == 0 and np.abs(got["logits"][:len(ids)] - want).max() < 4e-3
 
 
-# Keys have a place in LDS 16 at a time, tiles are 32: the second half of the last tile there or not, by one key, in every number of tiles, on few workgroups and on many
-@pytest.mark.parametrize("F", [60, 150])
+# Keys have a place in LDS 16 at a time, tiles are 32: the second half of the last tile there or not, by one key, in every number of tiles, on two workgroups a head, one and fewer waves
+@pytest.mark.parametrize("F", [40, 60, 150])
 @pytest.mark.parametrize("T", [2, 16, 17, 32, 33, 48, 49, 64, 80, 81, 112, 113, 144, 145, 176, 177, 192, 193, 208, 209, 224])
 def test_the_last_tile_of_keys(T, F):
     cfg, w, eight, sets, frames, off, ids = run._case(T, F, 128, 8, 3, 3, 1, 7000 + T)
