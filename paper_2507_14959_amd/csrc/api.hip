@@ -28,7 +28,7 @@ struct FlowSegment {
     int tiles;                              // rowrun.hip: rows of a tile; 0: flow.hip
 };
 
-// blocks up to which a segment may: up to 140 tiles of 32 rows where the row kernel is the alternative, 270 where the GEMM path is (ranks
+// blocks up to which a segment may where it does not run on tiles that stay on their CUs (run_segment): up to 140 tiles of 32 rows where the row kernel is the alternative, 270 where the GEMM path is (ranks
 // it does not take, adapters on the MLP, summed terms).  DeiT-tiny, twelve layers, as tasks / layer by layer: 18 blocks of 197 tokens (126
 // tiles) 469 / 487 us, 20 (140) 494 / 491, 24 (168) 509 / 503, 32 (224) 624 / 509; 70 blocks of 50 tokens (140) 427 / 438, 96 (192) 533 / 462;
 // GEMM path, rank 32: 32 blocks of 197 tokens (224) 644 / 748, 45 (315) 883 / 791; summed terms: 678 / 835 and 936 / 895, 60 blocks of 113
