@@ -162,3 +162,35 @@ def test_summed_terms(T, F, Dm, r, targets, L, L0, most):
     rows = np.concatenate([np.arange(off8[f % 8], off8[f % 8 + 1]) for f in range(F)])
     assert np.abs(got["logits"] - want[rows]).max() < TOL
     _same_wherever_a_frame_sits(got["logits"], off)
+
+
+def test_two_calls_at_a_time_on_two_streams():
+    """Workgroups of two launches share the CUs, so that a block's may have to wait for the other call's to end: the same bits as one after the other."""
+    calls = []
+    for T, F in ((197, 30), (197, 64)):
+        cfg, w, eight, sets, frames, off, ids = _case(T, F, 768, 8, 3, 6, 1, 8000 + F)
+        model = binding.DeviceModel(cfg, w, L0=2)
+        up = lambda a: torch.from_numpy(a).to("cuda", torch.int32)  # noqa: E731
+        ws = torch.empty(binding.poly_forward_workspace_bytes(model, F, F), dtype=torch.uint8, device="cuda")
+        calls.append((model, model.frames_to_device(frames), up(off), up(ids), F, ws, torch.cuda.Stream()))
+
+    def run(call, outs, status):
+        model, frames, off, ids, F, ws, _ = call
+        binding.poly_forward(model, frames, off, ids, F, torch.empty_like(outs), ws, out_logits=outs, dev_status=status)
+
+    fresh = lambda c: (torch.full((c[4], c[0].cfg.C), float("nan"), device="cuda"), torch.full((1,), 99, dtype=torch.int32, device="cuda"))  # noqa: E731
+    alone = [fresh(c) for c in calls]
+    for c, (o, s) in zip(calls, alone):
+        run(c, o, s)
+    torch.cuda.synchronize()
+    got = [[fresh(c) for _ in range(8)] for c in calls]
+    torch.cuda.synchronize()
+    for i in range(8):
+        for c, outs in zip(calls, got):
+            with torch.cuda.stream(c[6]):
+                run(c, *outs[i])
+    torch.cuda.synchronize()
+    for (want, st), outs in zip(alone, got):
+        assert int(st.item()) == 0
+        for o, s in outs:
+            assert int(s.item()) == 0 and torch.equal(o, want)
