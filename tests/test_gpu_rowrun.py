@@ -194,3 +194,33 @@ def test_two_calls_at_a_time_on_two_streams():
         assert int(st.item()) == 0
         for o, s in outs:
             assert int(s.item()) == 0 and torch.equal(o, want)
+
+
+def test_a_captured_call_replays():
+    """The counters are cleared by the call's first kernel, so every replay starts from nothing; other frames in the same buffer in between."""
+    cfg, w, eight, sets, frames, off, ids = _case(113, 40, 768, 8, 3, 6, 1, 8200)
+    model = binding.DeviceModel(cfg, w, L0=2)
+    F = len(frames)
+    up = lambda a: torch.from_numpy(a).to("cuda", torch.int32)  # noqa: E731
+    src = [model.frames_to_device(f) for f in (frames, np.ascontiguousarray(frames[::-1]))]
+    buf, off_d, ids_d = src[0].clone(), up(off), up(ids)
+    ws = torch.empty(binding.poly_forward_workspace_bytes(model, F, F), dtype=torch.uint8, device="cuda")
+    scores, logits = (torch.zeros(F, cfg.C, device="cuda") for _ in range(2))
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    call = lambda: binding.poly_forward(model, buf, off_d, ids_d, F, scores, ws, out_logits=logits, dev_status=status)  # noqa: E731
+    want = []
+    for f in src:
+        buf.copy_(f)
+        call()
+        torch.cuda.synchronize()
+        want.append(logits.clone())
+    assert not torch.equal(*want)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for i in (0, 1, 1, 0, 1):
+        buf.copy_(src[i])
+        logits.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert int(status.item()) == 0 and torch.equal(logits, want[i])
