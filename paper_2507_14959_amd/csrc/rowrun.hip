@@ -17,7 +17,8 @@
 // 2 k are the round trip of the counter.  32 rows (50 k, 20.5 us) 18 k (15.5 k of it the chunks of 128 hidden columns: 14.7 k with no weights coming in), 7.3 k, 9.3 k, 6.5 k, 3.7 k, 4.5 k.
 // Twelve layers and everything else of a forward, us, two launches a layer before / now: 62 blocks of 197 tokens (32 frames) 497 / 349, 24 blocks 448 / 270; 24 of 113
 // with summed terms (small tasks) 417 / 298.  Tried and dropped: the next weights pulled into the L2 ahead (64 rows 1.5 % slower, 32 the same); a tile counted halfway through the q
-// products, with proj's weights requested there too (0 to 1 % slower, on few blocks 2 %).
+// products, with proj's weights requested there too (0 to 1 % slower, on few blocks 2 %); a feed-forward part of its own for the class row's tile of the last layer, a quarter of the
+// products of 64 rows (60 registers spilled, everything half as long again).
 //
 // Handing k and v over without fences: as in flow.hip.  They are stored at device scope, the stores are waited for, then the tile is counted; every layer of a
 // launch has buffers of its own, so no address is read by this launch before it has been written for good and no cache holds an old copy of it.  A 1 KB
