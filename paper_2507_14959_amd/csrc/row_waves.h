@@ -59,7 +59,7 @@ inline int rowreg_waves(int T, int D, int Dm, int r, bool by_block, const PairCo
 // have less attention).  Two launches a layer: the row-wise part as above and attention, 4.5 us and what its rows take.  Twelve layers of DeiT-tiny and everything
 // else of a forward, us, two launches a layer / tiles of 64 / of 32 rows: every layer adapted, 16 blocks of 197 tokens (64 and 112 tiles) 440 / 338 / 270, 36 (252 of 32) 461 /
 // 346 / 276, 40 463 / 340 / 528, 64 (256 of 64) 484 / 347 / 535, 72 685 / 635 / 787, 96 753 / 647, 128 781 / 699, 160 (640 of 64) 820 / 1015; ten layers shared, 64 frames
-// 507 / 402, 72 506 / 647; 113 tokens, a bound of three a frame, 1.8 each: 24 frames 424 / 331 / 250, 64 487 / 339 / 495, 96 784 / 646, 160 968 / 971; 17 tokens: 128 375 / 305 / 243, 256
+// 507 / 402, 72 506 / 647, 84 615 / 630, 87 651 / 632, 102 661 / 638; 113 tokens, a bound of three a frame, 1.8 each: 24 frames 424 / 331 / 250, 64 487 / 339 / 495, 96 784 / 646, 160 968 / 971; 17 tokens: 128 375 / 305 / 243, 256
 // 397 / 308 / 245.
 constexpr int RN_MAX_TILES = 512;   // of the usual count: two rounds
 // Four where the other way is tiles of 64 rows too (a bound far above the frames, of which one each may have an adapter; ranks and blocks that rowreg.hip does not take): it takes as
@@ -85,7 +85,8 @@ inline float rowrun_us(int rows, int T, int blocks, int most = RN_MAX_TILES)
 }
 inline float two_launches_us(int T, int D, int Dm, int r, bool by_block, const PairCount &n)
 {
-    return row_layer_us(rowreg_waves(T, D, Dm, r, by_block, n), T, r, by_block, n.usual) + 4.5f + (float)n.usual * T / 2700.f;
+    const float second = T > 192 && n.usual == n.least && n.usual * (D / 64) > 256 ? 3.f : 0.f;      // (of attention, where CUs have a second workgroup)
+    return row_layer_us(rowreg_waves(T, D, Dm, r, by_block, n), T, r, by_block, n.usual) + 4.5f + (float)n.usual * T / 2700.f + second;
 }
 inline int rowrun_rows(int T, int D, int Dm, int r, bool by_block, const PairCount &n)
 {
