@@ -107,14 +107,9 @@ template <int RT, int NKT, bool SUM> __global__ __launch_bounds__(RN_THREADS, 2)
 
     const int tid0 = threadIdx.x;
     const int nb = [&]() { const RunPtr p = run_args(); const int *dev = p->nb_dev; return dev ? min(uload(dev), p->nb) : p->nb; }();
-    if (tid0 == 0) word_s[1] = run_args()->patience;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {                          // Phi table of the GELU
-        const int i = tid0 + RN_THREADS * j;
-        if (i < GELU_TAB_ENTRIES) *(f32x2 *)(gelu_s + 2 * i) = gelu_tab_entry(i);
-    }
     if (nb <= 0) return;
-    // this launch's layers: as many as there are buffers for, of the blocks that exist
+    // this launch's layers: as many as there are buffers for, of the blocks that exist.  The host counts its launches by a bound, so there may be none left:
+    // such a launch leaves before it touches LDS, which holds what others left in it (past here the word of the looks is written in front of a barrier).
     int l0, l1;
     {
         const RunPtr p = run_args();
@@ -122,7 +117,14 @@ template <int RT, int NKT, bool SUM> __global__ __launch_bounds__(RN_THREADS, 2)
         l0 = p->launch * n;
         l1 = min(l0 + n, p->layers);
     }
-    int queue = blockIdx.x & (RN_QUEUES - 1), left = l0 < l1 ? RN_QUEUES : 0;
+    if (l0 >= l1) return;
+    if (tid0 == 0) word_s[1] = run_args()->patience;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {                          // Phi table of the GELU
+        const int i = tid0 + RN_THREADS * j;
+        if (i < GELU_TAB_ENTRIES) *(f32x2 *)(gelu_s + 2 * i) = gelu_tab_entry(i);
+    }
+    int queue = blockIdx.x & (RN_QUEUES - 1), left = RN_QUEUES;
     while (left > 0) {
     // ---- the next tile
     unsigned ticket;

@@ -224,3 +224,43 @@ def test_a_captured_call_replays():
         graph.replay()
         torch.cuda.synchronize()
         assert int(status.item()) == 0 and torch.equal(logits, want[i])
+
+
+def test_a_launch_without_layers_reports_nothing():
+    """Room for twice the blocks there are: the host counts two launches by it, the first does all layers.  The second must not read what other workgroups left
+    in LDS: those of calls without patience, on another stream meanwhile, leave a count of looks that means a stall."""
+    cfg, w, eight, sets, frames, off, ids = _case(50, 60, 128, 8, 3, 12, 1, 8400)
+    model = binding.DeviceModel(cfg, w, L0=0)
+    F, room = 60, 120
+    full = torch.empty(binding.poly_forward_workspace_bytes(model, F, room), dtype=torch.uint8, device="cuda")
+    _, want, status, prof = _forward(model, frames, off, ids, full, room)
+    assert status == 0 and prof["attention"]["launches"] == 0
+    one, ws = prof["gemm"]["launches"], None
+    for part in range(24, 8, -1):
+        ws = full[:full.numel() * part // 24 // 256 * 256]
+        _, got, status, prof = _forward(model, frames, off, ids, ws, room)
+        assert status == 0 and prof["attention"]["launches"] == 0
+        if prof["gemm"]["launches"] > one:
+            break
+    assert prof["gemm"]["launches"] > one and np.array_equal(got, want, equal_nan=True)
+
+    up = lambda a: torch.from_numpy(a).to("cuda", torch.int32)  # noqa: E731
+    src, off_d, ids_d, other = model.frames_to_device(frames), up(off), up(ids), torch.empty_like(full)
+    calls = [(torch.full((room, cfg.C), float("nan"), device="cuda"), torch.full((1,), 99, dtype=torch.int32, device="cuda")) for _ in range(24)]
+    lost, stalled = torch.zeros(room, cfg.C, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    mine, theirs = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for logits, st in calls:
+        try:
+            binding.lib().poly_wait_limit(0)
+            with torch.cuda.stream(theirs):
+                for _ in range(2):
+                    binding.poly_forward(model, src, off_d, ids_d, room, torch.empty_like(lost), other, out_logits=lost, dev_status=stalled)
+        finally:
+            binding.lib().poly_wait_limit(-1)
+        with torch.cuda.stream(mine):
+            binding.poly_forward(model, src, off_d, ids_d, room, torch.empty_like(logits), ws, out_logits=logits, dev_status=st)
+    torch.cuda.synchronize()
+    assert int(stalled.item()) == binding.POLY_ESTALL
+    for logits, st in calls:
+        assert int(st.item()) == 0 and np.array_equal(logits.cpu().numpy(), want, equal_nan=True)
