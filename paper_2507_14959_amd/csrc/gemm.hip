@@ -772,8 +772,7 @@ int launch_gemm(const GemmArgs &g, GemmCount count, int dtype, hipStream_t st)
         gf.T = (int)rows; gf.n_in = 1;          // (Tout stays the block length: it places the output blocks)
     }
     if (!bf16 || g.K % 64 != 0 || g.N % 8 != 0 || !gemm_aligned(g)) return launch_gemm_ks(gf, dtype, st);
-    // blocks of one row with a low-rank term each: the other kernel's epilogue goes through them one by one, a chain of loads for each
-    if (g.T == 1 && g.S) return launch_gemm_ks(gf, dtype, st);
+    if (g.T == 1 && g.S && one_row_split(rows, g.N, g.K, g.RP, g.out_off != nullptr, g.set_off != nullptr)) return launch_gemm_ks(gf, dtype, st);
     // A long contraction on fewer 128 x 128 tiles than half the CUs is split over the waves (gemm_ks.hip) where tiles of 32 x 64 get a CU each, and
     // above a contraction of 1024 also where tiles of 64 x 64 do.  us per product of the 768-wide backbone, split / tiles of 64 x 64 on a shared ring /
     // 128 x 128 (rows x K -> N):

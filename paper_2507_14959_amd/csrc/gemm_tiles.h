@@ -146,3 +146,20 @@ inline int cheapest_tile(const TiledProduct &p)
         if (worse[i] < worse[best]) best = i;
     return best;
 }
+
+// Where the input blocks are one row each and have low-rank terms: on tiles whose contraction is split over the waves (gemm_ks.hip) instead of the shared-ring
+// kernel, whose epilogue goes through the blocks of a tile one by one, a chain of loads for each.  On many rows the larger tiles win all the same.  us,
+// shared ring / split (n blocks, K -> N):
+//   rows that fan out (the isolated linear; two terms of rank 64 each): 192 -> 576 300 137 / 107, 2000 181 / 157, 4000 253 / 288; 768 -> 768 1100 206 / 154, 2000 280 / 291; 768 -> 2304
+//     300 152 / 126, 700 242 / 248, 4000 780 / 1132; of rank 16, one each, slower at every count: 768 -> 2304 300 46 / 51, 4000 143 / 453, 768 -> 3072 4000 139 / 588
+//   one term a block, the whole call (two layers 768 wide, adapters on all linears of the second): rank 16 128 blocks 197 / 178, 1200 627 / 525, 2400 1037 / 1000,
+//     4000 1650 / 1671; rank 64 2400 1548 / 1569, 4000 2378 / 2509, 8000 4547 / 4956; 192 wide 2400 357 / 288, 8000 891 / 850
+//   a block's terms summed: 768 wide rank 64 200 569 / 550, 300 647 / 629, 400 787 / 800, 4000 4255 / 5153; rank 16 150 336 / 336, 400 483 / 539; 192 wide 300 271 / 251, 2000
+//     488 / 473, 4000 798 / 802
+// One round of 64 x 64 tiles, of a contraction of 768 where the terms are summed, and eight times that where a block has one term.
+inline bool one_row_split(long rows, int N, int K, int RP, bool fans_out, bool summed)
+{
+    const double products = (double)rows * N * K;
+    if (fans_out) return RP > 16 && (rows + 63) / 64 * ((N + 63) / 64) <= 256;
+    return products <= (summed ? 1. : 8.) * 256 * 64 * 64 * 768;
+}

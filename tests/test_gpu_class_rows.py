@@ -51,3 +51,20 @@ def test_linear_on_blocks_of_one_row(shape):
     Y, st = gpu_lora_linear(case, scale=1.5)
     assert st == 0
     check(Y, oracle.lora_linear(case, s=1.5), BF)
+
+
+# many of them, on either side of where the split contraction is faster (ranks above 16, one round of 64 x 64 tiles); all above the calls that are one launch
+@pytest.mark.parametrize("shape", [
+    dict(n_xblocks=2500, T=1, Kdim=192, Ndim=576, n_adapters=6, r=8, per_block=2),
+    dict(n_xblocks=700, T=1, Kdim=192, Ndim=200, n_adapters=6, r=40, per_block=2),
+    dict(n_xblocks=1100, T=1, Kdim=768, Ndim=1032, n_adapters=3, r=20, per_block=1),
+])
+def test_linear_on_many_blocks_of_one_row(shape):
+    case = synth.make_lora_linear_case(dtype=BF, seed=79, **shape)
+    Y, st = gpu_lora_linear(case, scale=1.5)
+    want = oracle.lora_linear(case, s=1.5)
+    # the shrink output, scaled, and the result are rounded to eight bits, 2^-8 of them at most each; sums are in fp32
+    frame = np.repeat(np.arange(shape["n_xblocks"]), np.diff(case["row_offsets"]))
+    low = np.abs(1.5 * np.einsum("rk,rkq->rq", case["X"][frame, 0].astype(np.float64), case["A"][case["adapter_ids"]].astype(np.float64)))
+    bound = 2.0 ** -8 * (np.abs(want[:, 0]) + np.einsum("rq,rqn->rn", low, np.abs(case["B"][case["adapter_ids"]]))) * 1.01 + 2e-5
+    assert st == 0 and (np.abs(Y - want)[:, 0] <= bound).all(), (np.abs(Y - want)[:, 0] / bound).max()

@@ -21,6 +21,7 @@ extern "C" int pick(int n, int T, int K, int N, int r, int mode, float terms, in
     for (int i = 0; i < N_TILES; ++i) us[i] = tile_cost(tile_costs(i), p, product_tiles(p.n_in, p.T, N, tile_costs(i).bm, tile_costs(i).bn));
     return cheapest_tile(p);
 }
+extern "C" int one_row(long rows, int N, int K, int RP, int fans_out, int summed) { return one_row_split(rows, N, K, RP, fans_out != 0, summed != 0); }
 """
 
 
@@ -35,6 +36,7 @@ def pick(tmp_path_factory):
     def call(n, T, K, N, r, per=1, mode=0, sums=False, known=True):
         us = (ctypes.c_float * len(TILES))()
         return TILES[lib.pick(n, T, K, N, r, mode, per, mode == 0 and not sums, sums, known, us)], list(us)
+    call.one_row = lambda rows, N, K, RP, fans_out, summed: bool(lib.one_row(ctypes.c_long(rows), N, K, RP, int(fans_out), int(summed)))
     return call
 
 
@@ -110,3 +112,26 @@ def test_layers_against_the_oracle(D, Dm, hw, F, r, compose):
     err = np.abs(got["logits"] - oracle.forward(cfg, w, frames, off, ids, L0=1, compose=compose)["logits"]).max()
     # 2.1e-3 to 4.4e-3 over the cases; a bias left out of fc1 in one layer moves the logits by 1.2e-2 and more
     assert got["status"] == 0 and err < 8e-3
+
+
+# blocks of one row: us of the isolated linear (fan out) or of a whole call on the shared ring / on the split contraction
+@pytest.mark.parametrize("rows,K,N,RP,fans_out,summed,ring,split", [
+    (300, 192, 576, 16, True, False, 38.5, 42.8), (700, 192, 576, 16, True, False, 39.0, 45.6), (4000, 192, 576, 16, True, False, 63.6, 106.1),
+    (700, 768, 2304, 16, True, False, 52.9, 94.8), (65536, 768, 3072, 16, True, False, 2028.3, 9330.8), (300, 1024, 4096, 16, True, False, 50.8, 92.5),
+    (300, 192, 576, 64, True, False, 137.1, 106.8), (1100, 192, 576, 64, True, False, 150.7, 127.7), (4000, 192, 576, 64, True, False, 252.7, 287.6),
+    (700, 768, 768, 64, True, False, 164.4, 140.3), (4000, 768, 768, 64, True, False, 352.5, 467.9), (300, 768, 2304, 64, True, False, 152.3, 125.8),
+    (1100, 768, 2304, 64, True, False, 266.1, 372.4), (1100, 1024, 4096, 64, True, False, 342.7, 594.7),
+    (192, 768, 3072, 16, False, False, 196.8, 177.7), (900, 768, 3072, 64, False, False, 564.2, 503.7), (1800, 768, 3072, 16, False, False, 627.3, 525.4),
+    (12000, 768, 3072, 64, False, False, 4546.6, 4955.5), (3600, 192, 768, 16, False, False, 356.8, 287.6),
+    (300, 768, 3072, 64, False, True, 647.3, 628.7), (600, 768, 3072, 16, False, True, 577.5, 633.7), (4000, 768, 3072, 64, False, True, 4254.6, 5153.0),
+    (600, 192, 768, 16, False, True, 292.2, 275.0),
+])
+def test_one_row_blocks_take_the_faster_kernel(pick, rows, K, N, RP, fans_out, summed, ring, split):
+    assert pick.one_row(rows, N, K, RP, fans_out, summed) == (split < ring)
+
+
+def test_one_row_blocks_that_fan_out_stay_on_the_ring_up_to_rank_16(pick):
+    """The isolated linear there is what it was before short blocks had a rule of their own, at any count."""
+    for rows in (1, 70, 1000, 5000, 1 << 20, (1 << 31) - 1):
+        assert not any(pick.one_row(rows, N, K, 16, True, False) for N in (8, 576, 4096) for K in (64, 768, 3072))
+        assert not pick.one_row(max(rows, 1 << 20), 576, 192, 64, True, False)
