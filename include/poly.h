@@ -43,7 +43,8 @@ typedef enum poly_status {
     POLY_ERANGE = -2, /* adapter id outside [0, n_adapters), offsets not monotone, R above its bound */
     POLY_ECAP = -3,   /* an output or the workspace is too small */
     POLY_EHIP = -4,   /* the HIP runtime reported an error */
-    POLY_ESTALL = -5  /* dev_status only: a kernel gave up waiting for its own workgroups; two calls were using one workspace at a time */
+    POLY_ESTALL = -5  /* dev_status only: a kernel gave up waiting for its own workgroups: two calls were using one workspace at a time, or fewer than
+                         seven CUs were free for a call of a model 192 wide for half a minute */
 } poly_status;
 
 enum { POLY_F32 = 0, POLY_BF16 = 1 };

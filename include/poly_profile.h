@@ -41,12 +41,13 @@ typedef struct poly_profile {
 int poly_profile_begin(int max_launches);
 int poly_profile_end(poly_profile *out); /* host struct */
 
-/* How often a workgroup of the task-queue kernel may look at a counter that is not there yet, in calls of the calling thread from
- * now on; negative = the built-in limit (the default).  For tests of what a call does when that kernel gives up (POLY_ESTALL). */
+/* How often a workgroup of a kernel that runs many layers in one launch may look at a counter that is not there yet, in calls of the calling thread from
+ * now on; negative = the built-in limit (the default).  For tests of what a call does when such a kernel gives up (POLY_ESTALL).  (Of the tiles that stay on
+ * their CUs the wait for a block's workgroups to be there has this limit where it is below the built-in one, and else one of its own, of half a minute.) */
 void poly_wait_limit(int looks);
 
-/* Workgroups of a launch of the wide models' task queue, at most, in calls of the calling thread from now on; 0 = one per CU (the default).  For tests
- * of its progress with fewer workgroups than queues. */
+/* Workgroups of a launch of the wide models' task queue, or of tiles that stay on their CUs, at most, in calls of the calling thread from now on; 0 = one per
+ * CU (the default).  For tests of their progress with fewer workgroups than queues. */
 void poly_wait_workgroups(int most);
 
 #ifdef __cplusplus

@@ -277,7 +277,7 @@ extern "C" const char *poly_status_string(int status)
     case POLY_ERANGE: return "adapter id or row offsets out of range";
     case POLY_ECAP: return "output or workspace too small";
     case POLY_EHIP: return "HIP runtime error";
-    case POLY_ESTALL: return "a kernel gave up waiting: workspace used by two calls at a time";
+    case POLY_ESTALL: return "a kernel gave up waiting: workspace used by two calls at a time, or no CUs free for its workgroups";
     default: return "unknown status";
     }
 }
@@ -407,7 +407,7 @@ int forward_impl(const poly_model_desc *m, const poly_base_weights *base, const 
         a.n_adapters = m->n_adapters; a.r = m->r; a.scale = m->lora_scale;
         a.k = (bf16_t *)w.fl[ad].qk; a.v = (bf16_t *)w.fl[ad].vt;
         a.counters = w.fl_cnt[ad];
-        a.patience = poly_patience(); a.meta = w.meta; a.dev_status = dev_status;
+        a.patience = poly_patience(); a.workgroups = poly_workgroups(); a.meta = w.meta; a.dev_status = dev_status;
         const int first = ad ? m->L0 : 0, last = ad ? m->L : m->L0;
         const size_t ld = (size_t)first * D, lm = (size_t)first * Dm, dd = ld * D, dm = ld * Dm;
         a.layers = last - first;

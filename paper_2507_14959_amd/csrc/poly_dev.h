@@ -350,6 +350,7 @@ struct RowRunArgs {
     bf16_t *k, *v;                   // [capacity][rowrun_elements(T)]
     unsigned *counters;              // rowrun_counter_bytes, cleared by an earlier launch
     int patience;                    // as in FlowArgs, as are these
+    int workgroups;
     PolyMeta *meta;
     int *dev_status;
 };

@@ -25,12 +25,17 @@
 // piece is written by one workgroup.
 //
 // Order and progress: tickets of eight queues, block b in queue b % 8, the tiles of a block consecutive.  (Workgroups are dealt to the XCDs in turn, so a block's
-// tiles mostly share an L2; nothing rests on that.)  A workgroup finishes the tile it has drawn before it draws another, from its own queue first, then from
-// the others, and leaves when all are empty.  A tile waits only for tiles of its own block.  At any time at most one block per queue has some of its tickets
-// drawn and others not, so at most 8 x 3 workgroups (of 32 rows: 8 x 6) wait for tiles that nobody has; all others come to their end, and with 25 CUs (49) for the launch one
-// of them draws the next ticket.  How long that takes is up to whatever else runs on the GPU, so the first wait of a tile, for the last ticket of its block to be drawn, has
-// a limit of its own, of half a minute; behind it all of a block's workgroups are at work.  Nobody else writes the counters; should two calls use one workspace at a time,
-// these limits end the waits and the call reports POLY_ESTALL, as in flow.hip.
+// tiles mostly share an L2: 62 blocks of 197 tokens 349 us, drawn from one queue after the other 355.)  A workgroup finishes the tile it has drawn before it draws another, from the
+// queue it starts at first, then from the others, and leaves when all are empty.  A tile waits only for tiles of its own block.  Whoever starts at queue 0 comes to a queue
+// once those before it are empty, so at any time at most one block has some of its tickets drawn by these and others not, and `tiles` workgroups, up to seven, always get on.
+// To start at its own XCD's queue a workgroup must have seen that 8 (tiles - 1) + 1 workgroups are there: at most one block per queue is partly drawn, so one of those that are there
+// does not wait for tickets nobody has.  They are given some 30 us to come; where the GPU has no CUs for them (a partition or a stream with few of them, other kernels), work
+// starts at queue 0.  Counted under the GELU's table, on a line for each XCD, that costs what a workgroup saves that looks for a queue with tickets left in all of them at once (in turn: eight
+// round trips before it leaves): lagged loop on 64 frames, DeiT-tiny on 32, summed terms on 24, us, without / with both 410.7 / 408.6, 349.0 / 348.0, 299.7 / 298.1;
+// counted on one line, queues in turn 414.2, 354.1, 299.4.
+// How long the last of a block's tickets takes to be drawn is up to whatever else runs on the GPU, so the first wait of a tile, for that, has
+// a limit of its own, of half a minute; behind it all of a block's workgroups are at work.  Nobody else writes the counters; should two calls use one workspace at a time, or
+// fewer CUs than a block has tiles be free for that long, these limits end the waits and the call reports POLY_ESTALL, as in flow.hip.
 #include "flow_dev.h"
 
 #include <type_traits>
@@ -44,6 +49,7 @@ constexpr int RN_MAX_DM = 768;
 constexpr int RN_GELU = (GELU_TAB_ENTRIES + 1) & ~1;    // (what lies behind is read in 16-byte pieces)
 constexpr int RN_AT_STRIDE = 200;   // elements per rank row of At_k in LDS (192 + 8: rows start 4 banks apart)
 constexpr int RN_QUEUES = 8;
+constexpr int RN_GATHER = 32;        // looks, of 1 us and more, for enough workgroups to start at eight queues
 constexpr int RN_FORMING = 1 << 24;  // looks, of 1.5 us and more, for a block's last ticket
 constexpr int KT = 3, D = 64 * KT, HEADS = KT, Nq = 3 * D, NQ = (Nq + 127) / 128;
 constexpr int CT = KT;                                     // column tiles of 16 per wave of a product with D columns
@@ -103,9 +109,11 @@ template <int RT, int NKT, bool SUM> __global__ __launch_bounds__(RN_THREADS, 2)
     f32x2 *stat_s = (f32x2 *)(gelu_s + 2 * RN_GELU);       // [64][4]: mean and squared deviations of a wave's columns of a row
     s16x4 *sh_s = (s16x4 *)stat_s;                         // in C: shrink output, [4][64 lanes]; from its second round on two tiles of keys
     bf16_t *at_s = (bf16_t *)(stat_s + 64 * 4);            // At_k of the phase, [16][RN_AT_STRIDE]
-    int *word_s = (int *)((char *)stat_s + rn_end(SUM));        // [0] ticket, [1] looks left
+    int *word_s = (int *)((char *)stat_s + rn_end(SUM));        // [0] ticket, [1] looks left, [2] queue
 
     const int tid0 = threadIdx.x;
+    // this workgroup has come (nobody waits for the answer; a line for each XCD: on one line 256 of these take 2 us)
+    if (tid0 == 0) __hip_atomic_fetch_add(run_args()->counters + (blockIdx.x & (RN_QUEUES - 1)) * 16 + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int nb = [&]() { const RunPtr p = run_args(); const int *dev = p->nb_dev; return dev ? min(uload(dev), p->nb) : p->nb; }();
     if (nb <= 0) return;
     // this launch's layers: as many as there are buffers for, of the blocks that exist.  The host counts its launches by a bound, so there may be none left:
@@ -119,30 +127,58 @@ template <int RT, int NKT, bool SUM> __global__ __launch_bounds__(RN_THREADS, 2)
     }
     if (l0 >= l1) return;
     if (tid0 == 0) word_s[1] = run_args()->patience;
+    unsigned there = 0;
+    if (tid0 < RN_QUEUES) there = peek(run_args()->counters + tid0 * 16 + 1);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {                          // Phi table of the GELU
         const int i = tid0 + RN_THREADS * j;
         if (i < GELU_TAB_ENTRIES) *(f32x2 *)(gelu_s + 2 * i) = gelu_tab_entry(i);
     }
-    int queue = blockIdx.x & (RN_QUEUES - 1), left = RN_QUEUES;
-    while (left > 0) {
-    // ---- the next tile
-    unsigned ticket;
-    {
+    if (tid0 < 64) {
         const RunPtr p = run_args();
-        __syncthreads();
-        if (tid0 == 0) word_s[0] = (int)__hip_atomic_fetch_add(p->counters + queue * 16, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        ticket = __builtin_amdgcn_readfirstlane(word_s[0]);
+        const unsigned enough = (unsigned)(min(nb, RN_QUEUES) * (p->tiles - 1) + 1);
+        for (int looks = RN_GATHER;;) {
+            unsigned all = there;                          // (of lanes 0 .. 7)
+#pragma unroll
+            for (int d = 1; d < RN_QUEUES; d *= 2) all += __shfl_xor(all, d, RN_QUEUES);
+            const bool own = __builtin_amdgcn_readfirstlane(all) >= enough;
+            if (own || --looks < 0) {
+                if (tid0 == 0) word_s[2] = own ? blockIdx.x & (RN_QUEUES - 1) : 0;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+            if (tid0 < RN_QUEUES) there = peek(p->counters + tid0 * 16 + 1);
+        }
     }
     const int tiles = run_args()->tiles;
-    const int nbq = nb > queue ? (nb - queue + RN_QUEUES - 1) / RN_QUEUES : 0;
-    if (ticket >= (unsigned)(nbq * tiles)) {
-        --left;
-        queue = (queue + 1) & (RN_QUEUES - 1);
-        continue;
+    for (;;) {
+    // ---- the next tile: a ticket of the queue this workgroup is at, or of the next one that is not empty (which a queue stays)
+    __syncthreads();
+    if (tid0 < 64) {
+        unsigned *const counters = run_args()->counters;
+        auto tickets = [&](int q) { return nb > q ? (unsigned)((nb - q + RN_QUEUES - 1) / RN_QUEUES * tiles) : 0u; };
+        int q = __builtin_amdgcn_readfirstlane(word_s[2]);
+        for (;;) {
+            unsigned t = 0;
+            if (tid0 == 0) t = __hip_atomic_fetch_add(counters + q * 16, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            t = __builtin_amdgcn_readfirstlane(t);
+            const bool got = t < tickets(q);
+            unsigned some = 0;
+            if (!got) {
+                const int at = (q + 1 + tid0) & (RN_QUEUES - 1);
+                some = (unsigned)__ballot(tid0 < RN_QUEUES && peek(counters + at * 16) < tickets(at));
+            }
+            if (got || !some) {
+                if (tid0 == 0) { word_s[0] = got ? (int)t : -1; word_s[2] = q; }
+                break;
+            }
+            q = (q + 1 + __builtin_ctz(some)) & (RN_QUEUES - 1);
+        }
     }
-    const int ob = queue + RN_QUEUES * (int)(ticket / (unsigned)tiles), tile = (int)(ticket % (unsigned)tiles);
+    __syncthreads();
+    const int ticket = __builtin_amdgcn_readfirstlane(word_s[0]), queue = __builtin_amdgcn_readfirstlane(word_s[2]);
+    if (ticket < 0) break;
+    const int ob = queue + RN_QUEUES * (int)((unsigned)ticket / (unsigned)tiles), tile = (int)((unsigned)ticket % (unsigned)tiles);
     // Everything made of the thread's number is made anew for every phase from a copy that the compiler cannot see through: kept from phase to phase, or hoisted
     // out of the loop over the layers, it would be spilled.
     int tid, lane, wave, kh, wc, lm, lg, lr, wrow, wcol;
@@ -1119,7 +1155,7 @@ template <int RT, int NKT, bool SUM> int launch_t(const RowRunArgs &a, hipStream
         attr_set = true;
     }
     // a multiple of the queues, and all of a small call's at once on CUs of their own
-    const int all = (a.nb * a.tiles + RN_QUEUES - 1) / RN_QUEUES * RN_QUEUES, most = 256;
+    const int all = (a.nb * a.tiles + RN_QUEUES - 1) / RN_QUEUES * RN_QUEUES, most = a.workgroups > 0 && a.workgroups < 256 ? a.workgroups : 256;
     POLY_LAUNCH_SHMEM(POLY_STAGE_GEMM, kern, dim3((unsigned)(all < most ? all : most)), dim3(RN_THREADS), LDS, st, a);
     return hipGetLastError() == hipSuccess ? POLY_OK : POLY_EHIP;
 }

@@ -74,6 +74,17 @@ def test_against_the_oracle(rows, T, F, Dm, r, targets, L, L0, per_frame, spare)
     _same_wherever_a_frame_sits(got["logits"], off)
 
 
+def _run_of_tiles(model, frames, off, ids, **kw):
+    """run_forward, where all layers run as launches of many and one of them is too large for the small tasks."""
+    binding.poly_profile_begin(400)
+    try:
+        got = binding.run_forward(model, frames, off, ids, **kw)
+    finally:
+        prof = binding.poly_profile_end()
+    assert prof["attention"]["launches"] == 0 and (len(off) - 1) * ((model.cfg.T + 31) // 32) > 44     # (FLOW_FEW)
+    return got
+
+
 def _same_wherever_a_frame_sits(logits, off):
     for f in range(8, len(off) - 1):
         assert np.array_equal(logits[off[f]:off[f + 1]], logits[off[f % 8]:off[f % 8 + 1]])
@@ -130,6 +141,31 @@ def test_a_stall_is_reported_and_nothing_published(L0):
     got = binding.run_forward(model, frames, off, ids)
     assert got["status"] == 0
     _compare(cfg, eight, sets, got["logits"], w, L0, off)
+
+
+# as many workgroups as a block has tiles; one fewer than may start at eight queues, as many
+@pytest.mark.parametrize("T,F,L0,compose,tiles", [(197, 40, 2, "branch", 4), (197, 12, 0, "branch", 7), (113, 24, 0, "sum", 4), (65, 26, 0, "branch", 3), (193, 7, 4, "branch", 7)])
+def test_few_workgroups_come_to_the_end(T, F, L0, compose, tiles):
+    """Where few CUs are free: no more blocks are begun than the workgroups that are there can finish."""
+    cfg, w, eight, sets, frames, off, ids = _case(T, F, 128, 8, 3, 4, 1, 4200 + T)
+    model = binding.DeviceModel(cfg, w, L0=L0, compose=compose)
+    want = _run_of_tiles(model, frames, off, ids)
+    enough = min(F, 8) * (tiles - 1) + 1
+    for workgroups in (tiles, enough - 1, enough):
+        binding.lib().poly_wait_workgroups(workgroups)
+        try:
+            got = binding.run_forward(model, frames, off, ids)
+        finally:
+            binding.lib().poly_wait_workgroups(0)
+        assert got["status"] == 0 and np.array_equal(got["logits"], want["logits"]), workgroups
+    binding.lib().poly_wait_workgroups(tiles - 1)
+    binding.lib().poly_wait_limit(2000)
+    try:
+        got = binding.run_forward(model, frames, off, ids)
+    finally:
+        binding.lib().poly_wait_workgroups(0)
+        binding.lib().poly_wait_limit(-1)
+    assert got["status"] == binding.POLY_ESTALL and np.isnan(got["logits"]).all()
 
 
 def test_a_bad_adapter_id_computes_nothing():
