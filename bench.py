@@ -110,6 +110,15 @@ def attention_flops(cfg, F, R, L0):
     return sum(4.0 * (R if l >= L0 else F) * (1 if l + 1 == cfg.L else cfg.T) * cfg.T * cfg.D for l in range(cfg.L) if l < L0 or R > 0)
 
 
+def run_launches(cfg, blocks_of, L0):
+    """Launches of the linear kernels where the layers run as launches of many (rowrun_kernel), and how many of them have layers to do: the patch embedding, and for the shared
+    and the adapted layers as many as the keys and values of blocks_of = (frames, room for row-blocks, row-blocks) make with buffers of 128 MiB, which hold every layer of a launch."""
+    room = ((128 << 20) - 512) // (4 * 32 * ((cfg.T + 31) // 32) * cfg.D)      # blocks x layers
+    frames, bound, there = blocks_of
+    count = lambda layers, blocks: -(-layers // min(layers, room // blocks)) if layers else 0  # noqa: E731
+    return 1 + count(L0, frames) + count(cfg.L - L0, bound), 1 + count(L0, frames) + count(cfg.L - L0, there)
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -447,9 +456,10 @@ def main():
     prof = binding.poly_profile_end()
     flops, n_gemm = gemm_flops(cfg, F, R, args.L0)
     g = prof["gemm"]
+    n_work = n_gemm
     if prof["attention"]["launches"] == 0:          # runs of whole layers in one launch, attention in them
         flops += attention_flops(cfg, F, R, args.L0)
-        n_gemm = g["launches"] // n_prof
+        n_gemm, n_work = run_launches(cfg, (F, len(ids_d), R), args.L0)
     assert g["launches"] == n_gemm * n_prof, (g, n_gemm)
     avg_ms = g["ms"] / g["launches"]
     achieved = flops / n_gemm / (avg_ms * 1e-3) / 1e12
@@ -466,7 +476,7 @@ def main():
                 "traffic": traffic, "traffic_source": os.path.relpath(TRAFFIC_PROFILE, ROOT) if traffic else None,
                 "algorithmic_bytes_per_launch": round(alg_bytes),
                 "traffic_over_algorithmic": round(traffic / alg_bytes, 1) if traffic else None,
-                "launches_per_step": n_gemm, "avg_launch_us": round(avg_ms * 1e3, 2),
+                "launches_per_step": n_gemm, "launches_without_layers": n_gemm - n_work, "avg_launch_us": round(avg_ms * 1e3, 2),
                 "algorithmic_gflop_per_launch": round(flops / n_gemm / 1e9, 3)}
     stages = {k: {"launches_per_step": v["launches"] // n_prof, "us_per_step": round(v["ms"] * 1e3 / n_prof, 1)}
               for k, v in prof.items()}
