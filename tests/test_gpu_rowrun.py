@@ -132,6 +132,7 @@ def test_the_launches_share_the_layers_without_changing_a_bit(T, F, room, L0, se
 def test_a_stall_is_reported_and_nothing_published(L0):
     cfg, w, eight, sets, frames, off, ids = _case(197, 12, 128, 8, 3, 5, 1, 4000)
     model = binding.DeviceModel(cfg, w, L0=L0)
+    want = _run_of_tiles(model, frames, off, ids)
     binding.lib().poly_wait_limit(0)
     try:
         got = binding.run_forward(model, frames, off, ids)
@@ -139,7 +140,7 @@ def test_a_stall_is_reported_and_nothing_published(L0):
         binding.lib().poly_wait_limit(-1)
     assert got["status"] == binding.POLY_ESTALL and np.isnan(got["logits"]).all()
     got = binding.run_forward(model, frames, off, ids)
-    assert got["status"] == 0
+    assert got["status"] == 0 and np.array_equal(got["logits"], want["logits"])
     _compare(cfg, eight, sets, got["logits"], w, L0, off)
 
 
@@ -170,9 +171,11 @@ def test_few_workgroups_come_to_the_end(T, F, L0, compose, tiles):
 
 def test_a_bad_adapter_id_computes_nothing():
     cfg, w, eight, sets, frames, off, ids = _case(113, 40, 128, 8, 3, 4, 1, 4100)
+    model = binding.DeviceModel(cfg, w, L0=0)
+    _run_of_tiles(model, frames, off, ids)
     ids = ids.copy()
     ids[7] = 5
-    got = binding.run_forward(binding.DeviceModel(cfg, w, L0=0), frames, off, ids)
+    got = binding.run_forward(model, frames, off, ids)
     assert got["status"] == binding.POLY_ERANGE and np.isnan(got["logits"]).all()
 
 
@@ -206,6 +209,7 @@ def test_two_calls_at_a_time_on_two_streams():
     for T, F in ((197, 30), (197, 64)):
         cfg, w, eight, sets, frames, off, ids = _case(T, F, 768, 8, 3, 6, 1, 8000 + F)
         model = binding.DeviceModel(cfg, w, L0=2)
+        _run_of_tiles(model, frames, off, ids)
         up = lambda a: torch.from_numpy(a).to("cuda", torch.int32)  # noqa: E731
         ws = torch.empty(binding.poly_forward_workspace_bytes(model, F, F), dtype=torch.uint8, device="cuda")
         calls.append((model, model.frames_to_device(frames), up(off), up(ids), F, ws, torch.cuda.Stream()))
@@ -236,6 +240,7 @@ def test_a_captured_call_replays():
     """The counters are cleared by the call's first kernel, so every replay starts from nothing; other frames in the same buffer in between."""
     cfg, w, eight, sets, frames, off, ids = _case(113, 40, 768, 8, 3, 6, 1, 8200)
     model = binding.DeviceModel(cfg, w, L0=2)
+    _run_of_tiles(model, frames, off, ids)
     F = len(frames)
     up = lambda a: torch.from_numpy(a).to("cuda", torch.int32)  # noqa: E731
     src = [model.frames_to_device(f) for f in (frames, np.ascontiguousarray(frames[::-1]))]
