@@ -151,15 +151,18 @@ inline int cheapest_tile(const TiledProduct &p)
 // kernel, whose epilogue goes through the blocks of a tile one by one, a chain of loads for each.  On many rows the larger tiles win all the same.  us,
 // shared ring / split (n blocks, K -> N):
 //   rows that fan out (the isolated linear; two terms of rank 64 each): 192 -> 576 300 137 / 107, 2000 181 / 157, 4000 253 / 288; 768 -> 768 1100 206 / 154, 2000 280 / 291; 768 -> 2304
-//     300 152 / 126, 700 242 / 248, 4000 780 / 1132; of rank 16, one each, slower at every count: 768 -> 2304 300 46 / 51, 4000 143 / 453, 768 -> 3072 4000 139 / 588
+//     300 152 / 126, 700 242 / 248, 4000 780 / 1132; a round of 64 x 64 tiles is the line (384 -> 1152 896 rows, 252 tiles, 167 / 130, 1024, 288 tiles, 163 / 231), two of them up to a
+//     contraction of 256, whose tiles leave a CU room for a second one (192 -> 768 1664 172 / 148, 2368, 444 tiles, 223 / 159, 2752, 516, 230 / 251; of rank 20, one each,
+//     1664 96 / 93, 2368 132 / 97; two of rank 32 5 % slower
+//     to 7 % faster); of rank 16, one each, slower at every count: 768 -> 2304 300 46 / 51, 4000 143 / 453, 768 -> 3072 4000 139 / 588
 //   one term a block, the whole call (two layers 768 wide, adapters on all linears of the second): rank 16 128 blocks 197 / 178, 1200 627 / 525, 2400 1037 / 1000,
 //     4000 1650 / 1671; rank 64 2400 1548 / 1569, 4000 2378 / 2509, 8000 4547 / 4956; 192 wide 2400 357 / 288, 8000 891 / 850
 //   a block's terms summed: 768 wide rank 64 200 569 / 550, 300 647 / 629, 400 787 / 800, 4000 4255 / 5153; rank 16 150 336 / 336, 400 483 / 539; 192 wide 300 271 / 251, 2000
 //     488 / 473, 4000 798 / 802
-// One round of 64 x 64 tiles, of a contraction of 768 where the terms are summed, and eight times that where a block has one term.
+// Where the terms are summed one round of 64 x 64 tiles of a contraction of 768, where a block has one term eight times that.
 inline bool one_row_split(long rows, int N, int K, int RP, bool fans_out, bool summed)
 {
     const double products = (double)rows * N * K;
-    if (fans_out) return RP > 16 && (rows + 63) / 64 * ((N + 63) / 64) <= 256;
+    if (fans_out) return RP > 16 && (rows + 63) / 64 * ((N + 63) / 64) <= (K <= 256 ? 512 : 256);
     return products <= (summed ? 1. : 8.) * 256 * 64 * 64 * 768;
 }

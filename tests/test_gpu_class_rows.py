@@ -53,11 +53,12 @@ def test_linear_on_blocks_of_one_row(shape):
     check(Y, oracle.lora_linear(case, s=1.5), BF)
 
 
-# many of them, on either side of where the split contraction is faster (ranks above 16, one round of 64 x 64 tiles); all above the calls that are one launch
+# many of them, on either side of where the split contraction is faster (ranks above 16, one round of 64 x 64 tiles, or two); all above the calls that are one launch
 @pytest.mark.parametrize("shape", [
     dict(n_xblocks=2500, T=1, Kdim=192, Ndim=576, n_adapters=6, r=8, per_block=2),
     dict(n_xblocks=700, T=1, Kdim=192, Ndim=200, n_adapters=6, r=40, per_block=2),
     dict(n_xblocks=1100, T=1, Kdim=768, Ndim=1032, n_adapters=3, r=20, per_block=1),
+    dict(n_xblocks=2300, T=1, Kdim=192, Ndim=760, n_adapters=6, r=36, per_block=1),
 ])
 def test_linear_on_many_blocks_of_one_row(shape):
     case = synth.make_lora_linear_case(dtype=BF, seed=79, **shape)

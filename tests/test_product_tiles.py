@@ -118,6 +118,9 @@ def test_layers_against_the_oracle(D, Dm, hw, F, r, compose):
 @pytest.mark.parametrize("rows,K,N,RP,fans_out,summed,ring,split", [
     (300, 192, 576, 16, True, False, 38.5, 42.8), (700, 192, 576, 16, True, False, 39.0, 45.6), (4000, 192, 576, 16, True, False, 63.6, 106.1),
     (700, 768, 2304, 16, True, False, 52.9, 94.8), (65536, 768, 3072, 16, True, False, 2028.3, 9330.8), (300, 1024, 4096, 16, True, False, 50.8, 92.5),
+    (2240, 192, 576, 64, True, False, 173.1, 156.9), (3200, 192, 576, 64, True, False, 189.1, 167.8), (3648, 192, 576, 64, True, False, 238.6, 258.7), (2368, 192, 768, 64, True, False, 222.7, 159.1),
+    (8192, 192, 192, 64, True, False, 246.4, 231.7), (2368, 192, 768, 32, True, False, 131.7, 97.1), (1792, 192, 576, 32, True, False, 106.1, 101.1), (1024, 384, 1152, 64, True, False, 163.3, 231.0),
+    (896, 384, 1152, 64, True, False, 166.5, 130.3), (1152, 1024, 1024, 64, True, False, 201.3, 268.4),
     (300, 192, 576, 64, True, False, 137.1, 106.8), (1100, 192, 576, 64, True, False, 150.7, 127.7), (4000, 192, 576, 64, True, False, 252.7, 287.6),
     (700, 768, 768, 64, True, False, 164.4, 140.3), (4000, 768, 768, 64, True, False, 352.5, 467.9), (300, 768, 2304, 64, True, False, 152.3, 125.8),
     (1100, 768, 2304, 64, True, False, 266.1, 372.4), (1100, 1024, 4096, 64, True, False, 342.7, 594.7),
