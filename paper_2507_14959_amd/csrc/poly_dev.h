@@ -325,7 +325,7 @@ size_t flow_elements(int T, int D);
 int launch_flow(const FlowArgs &a, int dtype, hipStream_t st);
 int launch_flow_wide(const FlowArgs &a, int patience, hipStream_t st);   // called by launch_flow
 
-// A run of whole layers of a model 192 wide on tiles of 64 rows in one launch (rowrun.hip).  Weight pointers are those of the first layer of the run, one layer of a
+// A run of whole layers of a model 192 wide on tiles of 64 or 32 rows in one launch (rowrun.hip).  Weight pointers are those of the first layer of the run, one layer of a
 // stack behind the other.
 struct RowRunArgs {
     int T, Dm, layers;
